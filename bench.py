@@ -41,7 +41,7 @@ def kernel_sources_digest() -> str:
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2605_04478_amd", "csrc")
-    for name in ("device_utils.h", "radix_sort.h", "radix_sort.hip", "select.h", "segments.hip", "window.hip",
+    for name in ("device_utils.h", "radix_sort.h", "radix_sort.hip", "select.h", "segments.hip", "groups.hip", "window.hip",
                  "window_kernels.h", "dense.h", "dense.hip"):
         h.update(name.encode())
         h.update(open(os.path.join(csrc, name), "rb").read())

@@ -80,8 +80,10 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->big_list = w.take<uint32_t>(3 * (N / 65 + 2));
   c->big_ex = w.take<int64_t>(2 * N);
   c->range_c = w.take<int64_t>(N);
-  c->group_long = w.take<uint32_t>(N / GROUP_LONG_MIN + 2);
-  c->group_first = w.take<uint32_t>(N + 1);
+  c->gcode = w.take<uint16_t>(N);
+  c->comm_groups = w.take<uint32_t>((uint64_t)n_comms + 1);
+  c->comm_row = w.take<uint32_t>(n_comms);
+  c->chain_parent = w.take<uint32_t>(N + 1);
   c->alert_list = w.take<uint32_t>(NT);
   c->alert_ncand = w.take<uint32_t>(N + 2);
   if (w.off - scratch_begin < B * 48) (void)w.take<uint8_t>(B * 48 - (w.off - scratch_begin));
@@ -621,8 +623,7 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   sa.big_list = c->big_list; sa.big_cap = c->cap / 65 + 2; sa.big_ex = c->big_ex; sa.counters = c->counters;
   sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
   sa.barrier_bytes = c->p.barrier_bytes; sa.max_size = c->max_comm_size;
-  sa.gkey = c->keyC; sa.range_c = c->range_c;
-  sa.no_group = (uint64_t)c->topo.n_comms * CCLD_OP_MAX * GROUP_CLS;     // one past every group key
+  sa.gcode = c->gcode; sa.range_c = c->range_c;
   const uint32_t seg_tiles = (n + SEG_TILE - 1) / SEG_TILE;
   if (dense) {
     // every collective's row of the table is fixed by the layout; a duplicate key or a round without any
@@ -677,27 +678,15 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   launch_alert_select(st, aa);
   c->prof.split(CCLD_PROF_ALERTS, CCLD_PROF_GROUPS);
 
-  // 5. slow detection and location per detection group (Eq. 1-4): every collective of the table is keyed
-  //    (those that take no part sort behind the groups), and the evaluation reads the numbers of groups and of
-  //    usable collectives on the device, so nothing here waits for the host
-  SortBuffers sb2;
-  sb2.key[0] = c->sb.key[1 - sorted]; sb2.idx[0] = c->sb.idx[1 - sorted];
-  sb2.key[1] = c->keyC; sb2.idx[1] = c->idxC; sb2.table = c->table2; sb2.totals = c->totals2;
+  // 5. slow detection and location per detection group (Eq. 1-4); nothing here waits for the host.  The stage
+  //    words live in the third sort buffer pair, which holds nothing at this point.
   GroupArgs ga;
   std::memset(&ga, 0, sizeof(ga));
-  ga.seg = o->seg; ga.seg_cap = o->seg_cap; ga.n_seg = seg_rows; ga.ws = ws; ga.cb = cb;
-  ga.tile_counts = c->tile_flags; ga.counters = c->counters;
+  ga.seg = o->seg; ga.seg_cap = o->seg_cap; ga.counters = c->counters; ga.gcode = c->gcode; ga.range_c = c->range_c;
+  ga.n_comms = c->topo.n_comms; ga.comm_groups = c->comm_groups; ga.comm_row = c->comm_row;
+  ga.stage[0] = reinterpret_cast<uint32_t*>(c->keyC); ga.stage[1] = ga.stage[0] + c->sort_cap; ga.stage[2] = c->idxC;
   ga.gstate = c->gstate; ga.rate_root = c->rate_root; ga.group = o->group; ga.group_cap = o->group_cap; ga.p = c->p;
-  ga.range_c = c->range_c;
-  if (seg_rows) {
-    const uint64_t no_group = sa.no_group;
-    KeySource gs; gs.key = c->keyC; gs.head = 0; gs.cap = seg_rows; gs.squeeze = 0; gs.hi_shift = 0; gs.lo_bits = 0; gs.lo_mask = 0; gs.lo_sub = 0;
-    // sort C -> buffers {other main, C}: the first pass reads C and writes buffer 0, so C is free again for pass 2
-    const int r3 = radix_sort_pairs(st, gs, seg_rows, sb2, bits_for_host(no_group));
-    if (r3 < 0) return o->status = CCLD_E_HIP;
-    launch_group_heads(st, sb2.key[r3], seg_rows, no_group, c->tile_flags, c->group_first, c->counters);
-    launch_group_eval(st, ga, sb2.key[r3], sb2.idx[r3], c->group_first, c->group_long);
-  }
+  launch_groups(st, ga);
   c->prof.end(CCLD_PROF_GROUPS);
   HIP_TRY(hipGetLastError());
   // 6. blame: flags keyed by rank, sorted, one workgroup per rank sums its run; launched behind the group
@@ -709,6 +698,9 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
     c->prof.begin(CCLD_PROF_BLAME);
     launch_blame_keys(st, skey, c->flag_pos, n_flag, c->sf, c->topo, bk);
     KeySource bs; bs.key = bk; bs.head = 0; bs.cap = n_flag; bs.squeeze = 0; bs.hi_shift = 0; bs.lo_bits = 0; bs.lo_mask = 0; bs.lo_sub = 0;
+    SortBuffers sb2;
+    sb2.key[0] = c->sb.key[1 - sorted]; sb2.idx[0] = c->sb.idx[1 - sorted];
+    sb2.key[1] = c->keyC; sb2.idx[1] = c->idxC; sb2.table = c->table2; sb2.totals = c->totals2;
     const int r2 = radix_sort_pairs(st, bs, n_flag, sb2, c->rank_bits);
     if (r2 < 0) return o->status = CCLD_E_HIP;
     launch_blame_reduce(st, sb2.key[r2], sb2.idx[r2], n_flag, c->flag_pos, sa.rec_flag, c->flag_lag, c->cap, n_ranks,

@@ -86,9 +86,8 @@ constexpr int SEL_TILE = 2048;       // records per workgroup of the compaction 
 constexpr int RANKCOUNT_BLOCKS = 2048;
 
 // device counters written by kernels and read back by the host
-enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NUSABLE, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN, CNT_NLONG,
+enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
        CNT_NRETAINED, CNT_COUNT = 16 };
-constexpr uint32_t GROUP_LONG_MIN = 4096;   // a detection group of more rounds than this gets a whole workgroup
 
 }  // namespace ccld
 
@@ -131,8 +130,10 @@ struct ccld_ctx {
   uint32_t* blame_list;               // [2][n_ranks] flagged ranks, then the others, each ascending
   uint32_t* blame_tiles;              // [n_ranks / SEL_TILE + 3]
   uint32_t* blame_order;              // [n_ranks] ranks by (flags, summed lag, rank), written at the end of every analysis
-  uint32_t* group_long;               // [cap / GROUP_LONG_MIN + 2] detection groups left to the workgroup-per-group pass
-  uint32_t* group_first;              // [cap + 1]
+  uint16_t* gcode;                    // [cap] (op, size class) of every usable collective
+  uint32_t* comm_groups;              // [n_comms + 1] detection groups of each communicator
+  uint32_t* comm_row;                 // [n_comms] its first row of the collective table
+  uint32_t* chain_parent;             // [cap + 1] scratch of ccld_flag_chains
   uint32_t* alert_list;               // [cap]
   uint32_t* alert_ncand;              // [cap + 1]
   uint2* comm_info;                   // [n_comms] (first member index, members) of every communicator: one load for both

@@ -204,7 +204,7 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
     a.key = c->sb.key[c->sorted_buf]; a.idx = c->sb.idx[c->sorted_buf]; a.row = c->last_rows; a.sf = c->sf; a.T = c->topo;
     a.seg = w->seg; a.seg_cap = w->seg_cap; a.n_seg = (uint32_t)w->n_seg;
     a.rec_flag = c->last_rec_flag; a.flag_lag = c->flag_lag; a.cap_n = c->cap; a.flag_pos = c->flag_pos; a.n_flag = n_flag;
-    a.comm_first = c->chain_first; a.parent = c->group_first;
+    a.comm_first = c->chain_first; a.parent = c->chain_parent;
     // scratch that the analysis no longer needs: the third sort buffer pair and the alert candidate counts
     uint32_t* anc[2] = {reinterpret_cast<uint32_t*>(c->keyC), reinterpret_cast<uint32_t*>(c->keyC) + n_flag};
     uint32_t* dist[2] = {c->idxC, c->alert_ncand};

@@ -24,24 +24,13 @@ __device__ __forceinline__ u64 atomic_add_u64(u64* p, u64 v) {
 __device__ __forceinline__ void seg_put(const SegArgs& a, int col, u32 srow, i64 v) {
   if (srow < a.seg_cap) a.seg[(u64)col * a.seg_cap + srow] = v;
 }
-// detection-group key and intra-round range T_max - T_min (Eq. 2) of one collective
-__device__ __forceinline__ void seg_group_of(const SegArgs& a, bool usable, u32 comm, u32 op, u64 nb, i64 dmax, i64 dmin,
-                                             u64* key, i64* range) {
-  *key = a.no_group;
-  *range = 0;
-  if (usable) {
-    const u64 cls = 63 - __clzll((long long)(nb | 1));
-    *key = ((u64)comm * CCLD_OP_MAX + op) * GROUP_CLS + cls;
-    *range = dmax - dmin;
-  }
+// detection-group code (op, size class) and intra-round range T_max - T_min (Eq. 2) of one collective
+__device__ __forceinline__ u32 seg_group_code(bool usable, u32 op, u64 nb) {
+  return usable ? op * GROUP_CLS + (63 - (u32)__clzll((long long)(nb | 1))) : NO_GROUP;
 }
-__device__ __forceinline__ void seg_put_group(const SegArgs& a, u32 srow, bool usable, u32 comm, u32 op, u64 nb,
-                                              i64 dmax, i64 dmin) {
-  u64 key;
-  i64 range;
-  seg_group_of(a, usable, comm, op, nb, dmax, dmin, &key, &range);
-  a.gkey[srow] = key;
-  a.range_c[srow] = range;
+__device__ __forceinline__ void seg_put_group(const SegArgs& a, u32 srow, bool usable, u32 op, u64 nb, i64 dmax, i64 dmin) {
+  a.gcode[srow] = (uint16_t)seg_group_code(usable, op, nb);
+  a.range_c[srow] = usable ? dmax - dmin : 0;
 }
 __device__ __forceinline__ i64 absdiff(i64 a, i64 b) { return a >= b ? a - b : b - a; }
 // payload row of the j-th record in (communicator, counter, rank) order; the op word's upper bits belong
@@ -169,7 +158,7 @@ struct DenseLane {
   lds_i64* stage;
   bool staged;
 };
-// A staged table row: the 21 columns, then the detection-group key and the range T_max - T_min, at constant
+// A staged table row: the 21 columns, then the detection-group code and the range T_max - T_min, at constant
 // offsets from the row's pointer.  k_seg_wave keeps the rows STAGE_COLS words apart (an odd stride).  In
 // k_dense_stats a row lies in its collective's own cells, a multiple of 256 bytes from its neighbours, and
 // starts stage_skew(k) words into that region, so that the lanes that later read one column of 64 rows
@@ -197,9 +186,6 @@ __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane&
     // the row waits in LDS until the workgroup writes the table column by column, whole lines at a time
     lds_i64* st = L.stage;
     auto put = [&](u32 c, i64 v) { st[c] = v; };
-    u64 gk;
-    i64 gr;
-    seg_group_of(a, usable, L.comm, hop, hb, dmax, dmin, &gk, &gr);
     put(CCLD_SEG_COMM, (i64)L.comm); put(CCLD_SEG_SEQ, (i64)L.seq); put(CCLD_SEG_N, (i64)L.n); put(CCLD_SEG_INFLIGHT, (i64)ninfl);
     put(CCLD_SEG_STATE, (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) |
                             (barrier ? CCLD_SEG_BARRIER : 0) | (usable ? CCLD_SEG_USABLE : 0));
@@ -211,10 +197,10 @@ __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane&
     put(CCLD_SEG_DUR_MIN, none ? 0 : dmin); put(CCLD_SEG_DUR_MAX, none ? 0 : dmax);
     put(CCLD_SEG_ARGMIN_RANK, none ? (i64)CCLD_NO_RANK : (i64)rmin); put(CCLD_SEG_ARGMAX_RANK, none ? (i64)CCLD_NO_RANK : (i64)rmax);
     put(CCLD_SEG_INFLIGHT_ENTER_MIN, imin); put(CCLD_SEG_FIRST, (i64)L.first);
-    put(CCLD_SEG_NCOL, (i64)gk); put(CCLD_SEG_NCOL + 1, gr);
+    put(CCLD_SEG_NCOL, (i64)seg_group_code(usable, hop, hb)); put(CCLD_SEG_NCOL + 1, usable ? dmax - dmin : 0);
     return;
   }
-  seg_put_group(a, srow, usable, L.comm, hop, hb, dmax, dmin);
+  seg_put_group(a, srow, usable, hop, hb, dmax, dmin);
   if (srow >= a.seg_cap) return;
   const u32 s0 = (u32)__builtin_amdgcn_readfirstlane((int)srow);      // the first of the pass's rows that fit the table
   const u32 off = (srow - s0) * 8u;
@@ -528,7 +514,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_wave(SegArgs a) {
       const i64 v = s_stage[sl * STAGE_COLS + col];
       const u32 srow = seg0 + sl;
       if (col < (u32)CCLD_SEG_NCOL) { if (srow < a.seg_cap) a.seg[(u64)col * a.seg_cap + srow] = v; }
-      else if (col == (u32)CCLD_SEG_NCOL) a.gkey[srow] = (u64)v;
+      else if (col == (u32)CCLD_SEG_NCOL) a.gcode[srow] = (uint16_t)v;
       else a.range_c[srow] = v;
     }
   }
@@ -689,7 +675,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_multi(SegArgs a) {
       seg_put(a, CCLD_SEG_BYTES, srow, (i64)hb);
       seg_put(a, CCLD_SEG_INFLIGHT_ENTER_MIN, srow, imin);
       seg_put(a, CCLD_SEG_FIRST, srow, (i64)a0);
-      seg_put_group(a, srow, usable, comm, hop, hb, dmax, dmin);
+      seg_put_group(a, srow, usable, hop, hb, dmax, dmin);
       if (nd == 0) {
         seg_put_empty_stats(a, srow);
       } else {
@@ -1135,17 +1121,17 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_big(SegArgs a) {
   }
 }
 
-// group key and range of the collectives that a workgroup analysed (more than SEG_MULTI_MAX records), from
+// group code and range of the collectives that a workgroup analysed (more than SEG_MULTI_MAX records), from
 // their rows of the table; a row past the table's capacity is not stored and takes no part in the group stage
 __global__ __launch_bounds__(256) void k_seg_group_listed(SegArgs a) {
   const u32 nbig = (u32)a.counters[CNT_NBIG];
   for (u32 ent = blockIdx.x * 256 + threadIdx.x; ent < nbig; ent += gridDim.x * 256) {
     if (a.big_list[3 * ent + 2] <= (u32)SEG_MULTI_MAX) continue;
     const u32 srow = a.big_list[3 * ent];
-    if (srow >= a.seg_cap) { a.gkey[srow] = a.no_group; a.range_c[srow] = 0; continue; }
+    if (srow >= a.seg_cap) { a.gcode[srow] = (uint16_t)NO_GROUP; a.range_c[srow] = 0; continue; }
     const u64 C = a.seg_cap;
     const bool usable = (a.seg[(u64)CCLD_SEG_STATE * C + srow] & CCLD_SEG_USABLE) != 0;
-    seg_put_group(a, srow, usable, (u32)a.seg[(u64)CCLD_SEG_COMM * C + srow], (u32)a.seg[(u64)CCLD_SEG_OP * C + srow],
+    seg_put_group(a, srow, usable, (u32)a.seg[(u64)CCLD_SEG_OP * C + srow],
                   (u64)a.seg[(u64)CCLD_SEG_BYTES * C + srow], a.seg[(u64)CCLD_SEG_DUR_MAX * C + srow],
                   a.seg[(u64)CCLD_SEG_DUR_MIN * C + srow]);
   }
@@ -1365,7 +1351,7 @@ void k_dense_stats(SegArgs a, DenseArgs d, u64* __restrict__ skey,
           const i64 v = S[k * size * 4 + stage_skew(k) + col];
           const u32 srow = srow0 + k;
           if (col < (u32)CCLD_SEG_NCOL) { if (srow < a.seg_cap) a.seg[(u64)col * a.seg_cap + srow] = v; }
-          else if (col == (u32)CCLD_SEG_NCOL) a.gkey[srow] = (u64)v;
+          else if (col == (u32)CCLD_SEG_NCOL) a.gcode[srow] = (uint16_t)v;
           else a.range_c[srow] = v;
         }
       }

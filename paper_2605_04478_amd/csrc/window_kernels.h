@@ -33,6 +33,7 @@ constexpr uint32_t INGEST_RANGE_COMMS = 3584;     // most communicators whose co
 void launch_ingest(hipStream_t st, const IngestArgs& a, const DeviceTopology& T, const KeyFormat& kf);
 void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v);
 
+constexpr uint32_t NO_GROUP = 0xFFFFu;
 struct SegArgs {
   const uint64_t* key;       // sorted squeezed keys
   const uint32_t* idx;       // window slot of each sorted record
@@ -56,11 +57,10 @@ struct SegArgs {
   int64_t lag_floor;
   uint32_t kmad_num, kmad_den, barrier_bytes;
   uint32_t max_size;         // members of the largest communicator (host-side: which size classes can occur)
-  // detection-group key (communicator, op, size class) and T_max - T_min of every collective, for the
-  // group stage; a collective that takes no part gets no_group, one value past every real key
-  uint64_t* gkey;
+  // (op, size class) code and T_max - T_min of every collective, for the group stage; a collective that takes
+  // no part gets NO_GROUP
+  uint16_t* gcode;
   int64_t* range_c;
-  uint64_t no_group;
 };
 void launch_scan_tiles(hipStream_t st, uint32_t* counts, uint32_t n_tiles, uint64_t* total_out);
 void launch_seg_analyze(hipStream_t st, const SegArgs& a);        // small collectives, then the oversized ones
@@ -94,13 +94,15 @@ void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, 
                         uint32_t* tile_counts, uint64_t* counters, uint32_t* order);
 
 struct GroupArgs {
-  const int64_t* seg;
+  const int64_t* seg;        // collective table; its row count is read from counters[CNT_NSEG]
   uint64_t seg_cap;
-  uint32_t n_seg;            // rows present in the table
-  int ws, cb;
-  uint32_t* tile_counts;
   uint64_t* counters;
-  const int64_t* range_c;    // [n_seg] T_max - T_min of each usable collective (written with the collectives' statistics)
+  const uint16_t* gcode;     // [rows] op * GROUP_CLS + size class of each usable collective, NO_GROUP of the others
+  const int64_t* range_c;    // [rows] T_max - T_min (written with the collectives' statistics)
+  uint32_t n_comms;
+  uint32_t* comm_groups;     // [n_comms + 1] groups of each communicator
+  uint32_t* comm_row;        // [n_comms] its first row of the table
+  uint32_t* stage[3];        // [rows] what k_group_comm leaves for k_group_emit
   GroupState* gstate;
   const int64_t* rate_root;  // [n_comms] minimal-rate member per communicator (CCLD_NO_RANK before any rate pass)
   int64_t* group;
@@ -109,10 +111,7 @@ struct GroupArgs {
 };
 void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* order_in, uint32_t n_ranks, int64_t* table_out,
                       uint32_t* order_out);
-void launch_group_heads(hipStream_t st, const uint64_t* skey, uint32_t n_rows, uint64_t no_group, uint32_t* tile_counts,
-                        uint32_t* group_first, uint64_t* counters);
-void launch_group_eval(hipStream_t st, const GroupArgs& a, const uint64_t* skey, const uint32_t* sidx,
-                       const uint32_t* group_first, uint32_t* long_list);
+void launch_groups(hipStream_t st, const GroupArgs& a);        // groups.hip
 
 struct AlertArgs {
   const int64_t* seg;
