@@ -1,5 +1,6 @@
 // extern "C" entry points: context set-up, workspace carving, ingest, window analysis, blame.
 #include <algorithm>
+#include <chrono>
 #include <cstring>
 #include <new>
 
@@ -278,7 +279,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   c->h_size.assign(topo->size, topo->size + topo->n_comms);
   c->h_pinned = nullptr;
   c->ev_heads = nullptr;
-  c->ev_flags = nullptr;
+  c->ticket = 0;
 
   // derived host tables: sorted member lists, rank -> communicators CSR
   std::vector<uint32_t> sorted(topo->members, topo->members + n_members), sslot(n_members);
@@ -359,14 +360,12 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
     if (hipHostMalloc((void**)&c->h_pinned, bytes, hipHostMallocDefault) != hipSuccess) rs = CCLD_E_HIP;
   }
   if (hipEventCreateWithFlags(&c->ev_heads, hipEventDisableTiming) != hipSuccess) { c->ev_heads = nullptr; rs = CCLD_E_HIP; }
-  if (hipEventCreateWithFlags(&c->ev_flags, hipEventDisableTiming) != hipSuccess) { c->ev_flags = nullptr; rs = CCLD_E_HIP; }
   if (ccld_static_scratch_init() != CCLD_OK) rs = CCLD_E_HIP;          // address of the static array on this device
   if (hipStreamSynchronize(c->stream) != hipSuccess) rs = CCLD_E_HIP;   // host vectors above die at return
   if (rs != CCLD_OK) {
     (void)hipGetLastError();
     if (c->h_pinned) (void)hipHostFree(c->h_pinned);
     if (c->ev_heads) (void)hipEventDestroy(c->ev_heads);
-    if (c->ev_flags) (void)hipEventDestroy(c->ev_flags);
     delete c;
     return rs;
   }
@@ -379,7 +378,6 @@ ccld_status ccld_destroy(ccld_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   if (c->h_pinned) (void)hipHostFree(c->h_pinned);
   if (c->ev_heads) (void)hipEventDestroy(c->ev_heads);
-  if (c->ev_flags) (void)hipEventDestroy(c->ev_flags);
   c->prof.destroy();
   delete c;
   return CCLD_OK;
@@ -455,6 +453,25 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   return CCLD_OK;
 }
 
+// Waits until the device has reported the counters of the current ticket into pinned memory.  The report is the last
+// thing on the stream, so the stream has drained then; spinning on the word costs about 10 us less than copying the
+// counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
+// hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
+static hipError_t wait_report(ccld_ctx* c) {
+  const uint64_t* word = c->h_pinned + CNT_COUNT;
+  if (!c->prof.on) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t i = 1;; ++i) {
+      if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == c->ticket) return hipSuccess;
+      if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
+      __builtin_ia32_pause();
+    }
+  }
+  const hipError_t e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return e;
+  return __atomic_load_n(word, __ATOMIC_ACQUIRE) == c->ticket ? hipSuccess : hipErrorUnknown;
+}
+
 static void zero_counts(ccld_window_result* o) {
   o->n_records = o->n_seg = o->n_flag = o->n_group = o->n_alert = o->n_cand = 0;
 }
@@ -504,9 +521,12 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
     }
   }
   c->last_n = n;
+  c->h_pinned[CNT_COUNT] = 0;          // the batch headers were read into these words
+  c->ticket += 1;
   if (n == 0) {
-    launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order);
-    HIP_TRY(hipStreamSynchronize(st));
+    launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
     c->blame_valid = true;
     return o->status;
   }
@@ -570,7 +590,7 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   }
   DenseArgs da;
   std::memset(&da, 0, sizeof(da));
-  uint32_t dense_n_seg = 0, dense_n_fine = 0;
+  uint32_t dense_n_fine = 0;
   if (dense) {
     // the grid's layout from the batch's counter ranges; its size comes back while the partition runs
     da.win_key = c->win_key; da.win_row = c->win_row; da.head = (uint32_t)c->head; da.cap = (uint32_t)cap; da.n = n;
@@ -596,7 +616,6 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
       *fallback = true;
       return CCLD_OK;
     }
-    dense_n_seg = h_hdr[DH_N_SEG];
     dense_n_fine = h_hdr[DH_N_FINE];
     sorted = 0;
     c->sort_passes = 0;
@@ -622,7 +641,7 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   sa.lag_e = o->lag_enter; sa.lag_x = o->lag_exit; sa.flag_lag = c->flag_lag; sa.cap_n = c->cap;
   sa.big_list = c->big_list; sa.big_cap = c->cap / 65 + 2; sa.big_ex = c->big_ex; sa.counters = c->counters;
   sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
-  sa.barrier_bytes = c->p.barrier_bytes; sa.max_size = c->max_comm_size;
+  sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size;
   sa.gcode = c->gcode; sa.range_c = c->range_c;
   const uint32_t seg_tiles = (n + SEG_TILE - 1) / SEG_TILE;
   if (dense) {
@@ -631,28 +650,14 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
     c->prof.split(CCLD_PROF_DENSE_PARTITION, CCLD_PROF_SEGMENTS);
     launch_dense_stats(st, sa, da, dense_n_fine, c->sb.key[sorted], c->sb.idx[sorted], c->blame, n_ranks);
     c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
-    o->n_seg = dense_n_seg;
   } else {
   c->prof.begin(CCLD_PROF_SEG_HEADS);
   launch_keys_pass(st, skey, n, c->sf, c->topo, c->blame, c->tile_heads, c->counters);
   launch_scan_tiles(st, c->tile_heads, seg_tiles, &c->counters[CNT_NSEG]);
-  // the number of collectives is known here; it comes back while the statistics kernels run
-  HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipEventRecord(c->ev_heads, st));
   c->prof.split(CCLD_PROF_SEG_HEADS, CCLD_PROF_SEGMENTS);          // one event ends a timed span and begins the next
   launch_seg_analyze(st, sa);
   c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
-  HIP_TRY(hipEventSynchronize(c->ev_heads));
-  if (c->h_pinned[CNT_STATUS]) {
-    const uint64_t bad = c->h_pinned[CNT_STATUS];
-    HIP_TRY(hipStreamSynchronize(st));
-    c->prof.collect();
-    zero_counts(o);
-    return o->status = data_status(bad);
   }
-  o->n_seg = c->h_pinned[CNT_NSEG];
-  }
-  const uint32_t seg_rows = (uint32_t)std::min<uint64_t>(o->n_seg, o->seg_cap);
   FlagArgs fa;
   std::memset(&fa, 0, sizeof(fa));
   fa.key = skey; fa.rec_flag = sa.rec_flag; fa.flag_lag = c->flag_lag; fa.cap_n = c->cap; fa.n = n; fa.sf = c->sf;
@@ -660,24 +665,11 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   fa.tile_flags = c->tile_flags; fa.flag_pos = c->flag_pos; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
   fa.counters = c->counters;
   launch_flag_compact(st, fa);
-  // the number of flags comes back while the alert and group kernels run
-  uint64_t* h_flags = c->h_pinned + CNT_COUNT;
-  HIP_TRY(hipMemcpyAsync(h_flags, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipEventRecord(c->ev_flags, st));
   if (o->perm) launch_perm(st, sidx, rows, n, c->batch_seqno.empty() ? 0u : c->batch_seqno[0], o->perm);
-
-  // 4. hang alerts: which collectives
-  AlertArgs aa;
-  std::memset(&aa, 0, sizeof(aa));
-  aa.seg = o->seg; aa.seg_cap = o->seg_cap; aa.n_seg = seg_rows; aa.now_ns = now_ns;
-  aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = skey; aa.idx = sidx; aa.row = rows; aa.n = n;
-  aa.sf = c->sf; aa.topo = c->topo; aa.tile_counts = c->tile_heads; aa.alert_list = c->alert_list;
-  aa.alert_ncand = c->alert_ncand; aa.alert = o->alert; aa.alert_cap = o->alert_cap; aa.cand = o->cand;
-  aa.cand_cap = o->cand_cap; aa.counters = c->counters;
-  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_ALERTS);
-  launch_alert_select(st, aa);
-  c->prof.split(CCLD_PROF_ALERTS, CCLD_PROF_GROUPS);
-
+  // 4. per-rank blame
+  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_BLAME);
+  launch_blame_sums(st, fa, n_ranks, c->blame);
+  c->prof.split(CCLD_PROF_BLAME, CCLD_PROF_GROUPS);
   // 5. slow detection and location per detection group (Eq. 1-4); nothing here waits for the host.  The stage
   //    words live in the third sort buffer pair, which holds nothing at this point.
   GroupArgs ga;
@@ -688,29 +680,10 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   ga.gstate = c->gstate; ga.rate_root = c->rate_root; ga.group = o->group; ga.group_cap = o->group_cap; ga.p = c->p;
   launch_groups(st, ga);
   c->prof.end(CCLD_PROF_GROUPS);
+  // the blame order is ready when ccld_rank_blame asks for it; its kernel reports the counters
+  launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
   HIP_TRY(hipGetLastError());
-  // 6. blame: flags keyed by rank, sorted, one workgroup per rank sums its run; launched behind the group
-  //    kernels, before the host waits for them
-  HIP_TRY(hipEventSynchronize(c->ev_flags));
-  const uint32_t n_flag = (uint32_t)h_flags[CNT_NFLAG];
-  if (n_flag) {
-    uint64_t* bk = c->keyC;       // keys are written to C, first pass sorts C -> buffer 0 of sb2
-    c->prof.begin(CCLD_PROF_BLAME);
-    launch_blame_keys(st, skey, c->flag_pos, n_flag, c->sf, c->topo, bk);
-    KeySource bs; bs.key = bk; bs.head = 0; bs.cap = n_flag; bs.squeeze = 0; bs.hi_shift = 0; bs.lo_bits = 0; bs.lo_mask = 0; bs.lo_sub = 0;
-    SortBuffers sb2;
-    sb2.key[0] = c->sb.key[1 - sorted]; sb2.idx[0] = c->sb.idx[1 - sorted];
-    sb2.key[1] = c->keyC; sb2.idx[1] = c->idxC; sb2.table = c->table2; sb2.totals = c->totals2;
-    const int r2 = radix_sort_pairs(st, bs, n_flag, sb2, c->rank_bits);
-    if (r2 < 0) return o->status = CCLD_E_HIP;
-    launch_blame_reduce(st, sb2.key[r2], sb2.idx[r2], n_flag, c->flag_pos, sa.rec_flag, c->flag_lag, c->cap, n_ranks,
-                        c->blame_list, c->blame);
-    c->prof.end(CCLD_PROF_BLAME);
-  }
-  // the blame order is ready when ccld_rank_blame asks for it: its kernels are queued here, before the wait
-  launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order);
-  HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  HIP_TRY(wait_report(c));
   if (c->h_pinned[CNT_STATUS]) {
     const uint64_t bad = c->h_pinned[CNT_STATUS];
     c->prof.collect();
@@ -718,14 +691,23 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
     if (dense && (bad & DS_DENSE_FALLBACK)) { *fallback = true; return CCLD_OK; }
     return o->status = data_status(bad);
   }
+  o->n_seg = c->h_pinned[CNT_NSEG];
   o->n_flag = c->h_pinned[CNT_NFLAG];
   o->n_alert = c->h_pinned[CNT_NALERT];
   o->n_group = c->h_pinned[CNT_NGROUP];
   if (o->n_seg > o->seg_cap || o->n_flag > o->flag_cap || o->n_group > o->group_cap) o->status = CCLD_W_TRUNCATED;
 
-  // 7. hang alerts: candidates of every alert
+  // 6. hang alerts: the collectives that raise one in table order, and the candidates of every alert
   if (o->n_alert) {
+    AlertArgs aa;
+    std::memset(&aa, 0, sizeof(aa));
+    aa.seg = o->seg; aa.seg_cap = o->seg_cap; aa.n_seg = (uint32_t)std::min<uint64_t>(o->n_seg, o->seg_cap); aa.now_ns = now_ns;
+    aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = skey; aa.idx = sidx; aa.row = rows; aa.n = n;
+    aa.sf = c->sf; aa.topo = c->topo; aa.tile_counts = c->tile_heads; aa.alert_list = c->alert_list;
+    aa.alert_ncand = c->alert_ncand; aa.alert = o->alert; aa.alert_cap = o->alert_cap; aa.cand = o->cand;
+    aa.cand_cap = o->cand_cap; aa.counters = c->counters;
     c->prof.begin(CCLD_PROF_ALERTS);
+    launch_alert_select(st, aa);
     launch_alert_candidates(st, aa, (uint32_t)o->n_alert);
     c->prof.end(CCLD_PROF_ALERTS);
     HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
@@ -733,8 +715,6 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
     o->n_cand = c->h_pinned[CNT_NCAND];
     if (o->n_alert > o->alert_cap || o->n_cand > o->cand_cap) o->status = CCLD_W_TRUNCATED;
   }
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
   c->prof.collect();
   c->blame_valid = true;
   // the order of this window serves the next analysis (windows of several batches only)

@@ -87,7 +87,7 @@ constexpr int RANKCOUNT_BLOCKS = 2048;
 
 // device counters written by kernels and read back by the host
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
-       CNT_NRETAINED, CNT_COUNT = 16 };
+       CNT_NRETAINED, CNT_DONE, CNT_COUNT = 16 };
 
 }  // namespace ccld
 
@@ -127,7 +127,7 @@ struct ccld_ctx {
   int64_t* big_ex;                    // [2][cap]
   int64_t* range_c;                   // [cap] T_max - T_min of every usable collective
   int64_t* blame;                     // [CCLD_BLM_NCOL][n_ranks]
-  uint32_t* blame_list;               // [2][n_ranks] flagged ranks, then the others, each ascending
+  uint32_t* blame_list;               // [2][n_ranks] flagged ranks, then the others, each ascending (many ranks only)
   uint32_t* blame_tiles;              // [n_ranks / SEL_TILE + 3]
   uint32_t* blame_order;              // [n_ranks] ranks by (flags, summed lag, rank), written at the end of every analysis
   uint16_t* gcode;                    // [cap] (op, size class) of every usable collective
@@ -142,8 +142,8 @@ struct ccld_ctx {
   uint32_t max_comm_size;             // members of the largest communicator
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging
-  hipEvent_t ev_heads;                // marks the early readback of the collective count
-  hipEvent_t ev_flags;                // marks the early readback of the flag count
+  uint64_t ticket;                    // number of the latest report that the device was asked for (h_pinned[CNT_COUNT])
+  hipEvent_t ev_heads;                // marks the early readback of the dense layout
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location

@@ -32,6 +32,11 @@ __device__ __forceinline__ void seg_put_group(const SegArgs& a, u32 srow, bool u
   a.gcode[srow] = (uint16_t)seg_group_code(usable, op, nb);
   a.range_c[srow] = usable ? dmax - dmin : 0;
 }
+// counts a collective that raises a hang alert (an operation in flight longer than the threshold, barriers excepted);
+// the alert list itself is built only when there are any
+__device__ __forceinline__ void seg_count_alert(const SegArgs& a, u32 srow, u32 ninfl, bool barrier, i64 imin) {
+  if (ninfl && !barrier && a.now_ns - imin > a.hang_threshold_ns && srow < a.seg_cap) atomic_add_u64(&a.counters[CNT_NALERT], 1);
+}
 __device__ __forceinline__ i64 absdiff(i64 a, i64 b) { return a >= b ? a - b : b - a; }
 // payload row of the j-th record in (communicator, counter, rank) order; the op word's upper bits belong
 // to the dense placement
@@ -182,6 +187,7 @@ __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane&
                                               i64 dmin, i64 dmax, u32 rmin, u32 rmax) {
   const u32 srow = L.srow;
   const bool none = nd == 0;            // no completed record: the statistics columns are empty
+  seg_count_alert(a, srow, ninfl, barrier, imin);
   if (MODE == PUT_STAGED || (MODE == PUT_EITHER && L.staged)) {
     // the row waits in LDS until the workgroup writes the table column by column, whole lines at a time
     lds_i64* st = L.stage;
@@ -674,6 +680,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_multi(SegArgs a) {
       seg_put(a, CCLD_SEG_OP, srow, (i64)hop);
       seg_put(a, CCLD_SEG_BYTES, srow, (i64)hb);
       seg_put(a, CCLD_SEG_INFLIGHT_ENTER_MIN, srow, imin);
+      seg_count_alert(a, srow, ninfl, barrier, imin);
       seg_put(a, CCLD_SEG_FIRST, srow, (i64)a0);
       seg_put_group(a, srow, usable, hop, hb, dmax, dmin);
       if (nd == 0) {
@@ -843,6 +850,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_team(SegArgs a) {
       seg_put(a, CCLD_SEG_OP, srow, (i64)h.op);
       seg_put(a, CCLD_SEG_BYTES, srow, (i64)h.bytes);
       seg_put(a, CCLD_SEG_INFLIGHT_ENTER_MIN, srow, (i64)acc.imin);
+      seg_count_alert(a, srow, ninfl, barrier, (i64)acc.imin);
       seg_put(a, CCLD_SEG_FIRST, srow, (i64)a0);
       if (nd == 0) {
         seg_put_empty_stats(a, srow);
@@ -966,6 +974,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void k_seg_large(SegArgs a) {
       seg_put(a, CCLD_SEG_OP, srow, (i64)h.op);
       seg_put(a, CCLD_SEG_BYTES, srow, (i64)h.bytes);
       seg_put(a, CCLD_SEG_INFLIGHT_ENTER_MIN, srow, (i64)acc.imin);
+      seg_count_alert(a, srow, ninfl, barrier, (i64)acc.imin);
       seg_put(a, CCLD_SEG_FIRST, srow, (i64)a0);
       if (nd == 0) {
         seg_put_empty_stats(a, srow);
@@ -1100,10 +1109,12 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_big(SegArgs a) {
     const bool consistent = s_incons == 0;
     const bool barrier = h.op == CCLD_OP_ALLREDUCE && h.bytes < (u64)a.barrier_bytes;
     const bool usable = complete && consistent && !barrier;
-    if (tid == 0)
+    if (tid == 0) {
       seg_put(a, CCLD_SEG_STATE, srow,
               (complete ? CCLD_SEG_COMPLETE : 0) | (consistent ? CCLD_SEG_CONSISTENT : 0) |
                   (barrier ? CCLD_SEG_BARRIER : 0) | (usable ? CCLD_SEG_USABLE : 0));
+      seg_count_alert(a, srow, ninfl, barrier, (i64)s_imin);
+    }
     for (u32 i = a0 + tid; i < b0; i += SEG_THREADS) {
       i64 le = 0, lx = 0;
       u32 f = 0;

@@ -619,133 +619,183 @@ void launch_keys_pass(hipStream_t st, const uint64_t* key, uint32_t n, const Squ
                      T.size, T.n_ranks, blame, tile_heads, counters);
 }
 
-// Blame: key every flag by its rank, sort, then one wavefront per rank sums its run.
-__global__ __launch_bounds__(256) void k_blame_keys(const u64* __restrict__ key, const u32* __restrict__ flag_pos,
-                                                    u32 n_flag, SqueezedFormat sf, const u32* __restrict__ member_off,
-                                                    const u32* __restrict__ members_sorted, u64* __restrict__ out_key) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_flag) return;
-  const u64 kk = key[flag_pos[k]];
-  out_key[k] = rank_of_slot(member_off, members_sorted, (u32)(kk >> (sf.mb + sf.ws)), (u32)(kk & (((u64)1 << sf.mb) - 1)));
-}
-void launch_blame_keys(hipStream_t st, const uint64_t* key, const uint32_t* flag_pos, uint32_t n_flag,
-                       const SqueezedFormat& sf, const DeviceTopology& T, uint64_t* out_key) {
-  if (n_flag)
-    hipLaunchKernelGGL(k_blame_keys, dim3((n_flag + 255) / 256), dim3(256), 0, st, key, flag_pos, n_flag, sf,
-                       T.member_off, T.members_sorted, out_key);
-}
-// ends of every rank's run in the sorted flag keys: run[r] = first, run[n_ranks + r] = one past the
-// last (both zero for a rank without a flag; the array is cleared before)
-__global__ __launch_bounds__(256) void k_blame_runs(const u64* __restrict__ skey, u32 n_flag, u32 n_ranks,
-                                                    u32* __restrict__ run) {
-  const u32 q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= n_flag) return;
-  const u64 r = skey[q];
-  if (q == 0 || skey[q - 1] != r) run[r] = q;
-  if (q + 1 == n_flag || skey[q + 1] != r) run[n_ranks + r] = q + 1;
-}
-// gridDim.y workgroups per rank: the rank's run in the sorted flag keys is dealt to them in pieces of 1,024
-// flags, four flags per thread in flight (a faulty rank's run is tens of thousands of flags long).  The
-// table was cleared before; the integer sums do not depend on the order of the additions.
-__global__ __launch_bounds__(256) void k_blame_reduce(const u32* __restrict__ run, const u32* __restrict__ sidx,
-                                                      const u32* __restrict__ flag_pos,
-                                                      const uint8_t* __restrict__ rec_flag,
-                                                      const i64* __restrict__ flag_lag, u64 cap_n, u32 n_ranks,
-                                                      i64* __restrict__ blame) {
-  __shared__ unsigned long long s_acc[4];
-  const u32 r = blockIdx.x, tid = threadIdx.x;
-  const u32 first = run[r], last = run[n_ranks + r];
-  if ((u64)first + (u64)blockIdx.y * 1024 >= last) return;
-  if (tid < 4) s_acc[tid] = 0;
-  __syncthreads();
-  u64 ne = 0, nx = 0, se = 0, sx = 0;
-  for (u64 q1 = (u64)first + blockIdx.y * 1024 + tid; q1 < last; q1 += 1024ull * gridDim.y) {
-    const u32 q0 = (u32)q1;
-    u32 j[4], f[4];
-    i64 le[4], lx[4];
+// Late columns of the blame table.  The flags are in (communicator, counter, rank) order, so a workgroup's slice of
+// them names few ranks, each many times: it sums them in an LDS table keyed by rank (open addressing, a bounded number
+// of probes) and adds every entry with one integer atomic per column; a rank that finds no entry goes straight to
+// the blame table.  The integer sums do not depend on the order.  At 145,000 flags this takes the place of a sort by
+// rank and three more launches (0.09 ms together).
+constexpr u32 BH_SLOTS = 1024, BH_PROBES = 16, BH_NONE = 0xFFFFFFFFu, BH_BLOCKS = 128;
+__global__ __launch_bounds__(256) void k_blame_sums(FlagArgs a, u32 n_ranks, i64* __restrict__ blame) {
+  __shared__ u32 s_rank[BH_SLOTS];
+  __shared__ unsigned long long s_sum[4][BH_SLOTS];
+  const u32 n_flag = (u32)a.counters[CNT_NFLAG], tid = threadIdx.x;
+  const u32 per = ((n_flag + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+  const u64 lo = (u64)per * blockIdx.x;
+  if (lo >= n_flag) return;
+  const u32 hi = lo + per < n_flag ? (u32)(lo + per) : n_flag;
+  for (u32 i = tid; i < BH_SLOTS; i += 256) {
+    s_rank[i] = BH_NONE;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) j[u] = (u64)q0 + u * 256 < last ? flag_pos[sidx[q0 + u * 256]] : 0xFFFFFFFFu;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      f[u] = 0; le[u] = 0; lx[u] = 0;
-      if (j[u] != 0xFFFFFFFFu) { f[u] = rec_flag[j[u]]; le[u] = flag_lag[j[u]]; lx[u] = flag_lag[cap_n + j[u]]; }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (f[u] & CCLD_FLAG_LATE_ENTER) { ne += 1; se += (u64)le[u]; }
-      if (f[u] & CCLD_FLAG_LATE_EXIT) { nx += 1; sx += (u64)lx[u]; }
-    }
-  }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    ne += shfl_xor_u64(ne, m); nx += shfl_xor_u64(nx, m); se += shfl_xor_u64(se, m); sx += shfl_xor_u64(sx, m);
-  }
-  if (lane_id() == 0) {
-    atomicAdd(&s_acc[CCLD_BLM_N_LATE_ENTER], (unsigned long long)ne);
-    atomicAdd(&s_acc[CCLD_BLM_N_LATE_EXIT], (unsigned long long)nx);
-    atomicAdd(&s_acc[CCLD_BLM_SUM_LAG_ENTER], (unsigned long long)se);
-    atomicAdd(&s_acc[CCLD_BLM_SUM_LAG_EXIT], (unsigned long long)sx);
+    for (int k = 0; k < 4; ++k) s_sum[k][i] = 0;
   }
   __syncthreads();
-  if (tid < 4 && s_acc[tid])
-    atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)tid * n_ranks + r]), s_acc[tid]);
+  const u64 mmask = ((u64)1 << a.sf.mb) - 1;
+  for (u32 q = (u32)lo + tid; q < hi; q += 256) {
+    const u32 j = a.flag_pos[q];
+    const u64 key = a.key[j];
+    const u32 f = a.rec_flag[j];
+    const u64 le = (u64)a.flag_lag[j], lx = (u64)a.flag_lag[a.cap_n + j];
+    const u32 r = rank_of_slot(a.member_off, a.members_sorted, (u32)(key >> (a.sf.mb + a.sf.ws)), (u32)(key & mmask));
+    u32 at = (r * 0x9E3779B1u) >> 22;                 // BH_SLOTS = 2^10
+    bool found = false;
+    for (u32 p = 0; p < BH_PROBES && !found; ++p) {
+      const u32 was = atomicCAS(&s_rank[at], BH_NONE, r);
+      found = was == BH_NONE || was == r;
+      if (!found) at = (at + 1) & (BH_SLOTS - 1);
+    }
+    auto add = [&](int col, u64 v) {
+      if (found) atomicAdd(&s_sum[col][at], (unsigned long long)v);
+      else atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)col * n_ranks + r]), (unsigned long long)v);
+    };
+    if (f & CCLD_FLAG_LATE_ENTER) { add(CCLD_BLM_N_LATE_ENTER, 1); add(CCLD_BLM_SUM_LAG_ENTER, le); }
+    if (f & CCLD_FLAG_LATE_EXIT) { add(CCLD_BLM_N_LATE_EXIT, 1); add(CCLD_BLM_SUM_LAG_EXIT, lx); }
+  }
+  __syncthreads();
+  for (u32 i = tid; i < BH_SLOTS; i += 256) {
+    const u32 r = s_rank[i];
+    if (r == BH_NONE) continue;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (s_sum[k][i]) atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)k * n_ranks + r]), s_sum[k][i]);
+  }
 }
+static_assert(BH_SLOTS == 1024, "ten hash bits");
 static_assert(CCLD_BLM_N_LATE_ENTER == 0 && CCLD_BLM_N_LATE_EXIT == 1 && CCLD_BLM_SUM_LAG_ENTER == 2 &&
               CCLD_BLM_SUM_LAG_EXIT == 3, "blame column order");
-void launch_blame_reduce(hipStream_t st, const uint64_t* skey, const uint32_t* sidx, uint32_t n_flag,
-                         const uint32_t* flag_pos, const uint8_t* rec_flag, const int64_t* flag_lag,
-                         uint64_t cap_n, uint32_t n_ranks, uint32_t* run, int64_t* blame) {
-  launch_fill_u32(st, run, 2ull * n_ranks, 0u);
-  hipLaunchKernelGGL(k_blame_runs, dim3((n_flag + 255) / 256), dim3(256), 0, st, skey, n_flag, n_ranks, run);
-  // no run is longer than n_flag: a few thousand flags need no second workgroup per rank
-  const u32 split = std::min<u32>(std::max<u32>(n_flag / 4096, 1), 8);
-  hipLaunchKernelGGL(k_blame_reduce, dim3(n_ranks, split), dim3(256), 0, st, (const u32*)run, sidx, flag_pos, rec_flag,
-                     flag_lag, cap_n, n_ranks, blame);
+void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int64_t* blame) {
+  if (f.n) hipLaunchKernelGGL(k_blame_sums, dim3(std::min<u32>((f.n + 4095) / 4096, BH_BLOCKS)), dim3(256), 0, st, f, n_ranks, blame);
 }
 
-// order[] = ranks by (flags descending, summed lag descending, rank ascending).  Ranks with any
-// flag come first and only they need ranking: a wavefront per flagged rank counts the flagged
-// ranks that precede it.  The ranks without a flag follow in ascending order.
+// order[] = ranks by (flags descending, summed lag descending, rank ascending).  Ranks with any flag come first and
+// only they need ranking: a wavefront per flagged rank counts the flagged ranks that precede it.  The ranks without a
+// flag follow in ascending order.
+// Number of flagged ranks that come before rank r, counted by one wavefront over a list of the flagged ranks.
+template <class T>
+__device__ __forceinline__ u32 blamed_before(const i64* __restrict__ blame, u32 n_ranks, const T* list, u32 nb, u32 r, u32 lane) {
+  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
+  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
+  const i64* SE = blame + (u64)CCLD_BLM_SUM_LAG_ENTER * n_ranks;
+  const i64* SX = blame + (u64)CCLD_BLM_SUM_LAG_EXIT * n_ranks;
+  const i64 myn = NE[r] + NX[r];
+  const i64 mys = (i64)((u64)SE[r] + (u64)SX[r]);
+  u32 before = 0;
+  for (u32 i = lane; i < nb; i += CCLD_WAVE) {
+    const u32 o = list[i];
+    const i64 on = NE[o] + NX[o];
+    const i64 os = (i64)((u64)SE[o] + (u64)SX[o]);
+    before += (on > myn) || (on == myn && (os > mys || (os == mys && o < r)));
+  }
+  return wave_sum(before);
+}
+// An analysis ends here: the counters go to pinned host memory and the ticket behind them (system-scope release), on
+// which the host spins, by the last workgroup to get here.
+__device__ __forceinline__ void report_counters(u64* counters, u64* host, u64 ticket) {
+  __shared__ u32 s_last;
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomic_add_u64(&counters[CNT_DONE], 1) + 1 == gridDim.x;
+  __syncthreads();
+  if (!s_last) return;
+  if (threadIdx.x < CNT_COUNT)
+    __hip_atomic_store(&host[threadIdx.x], __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(&host[CNT_COUNT], ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+static_assert(CNT_COUNT <= 64, "one wavefront copies the counters");
+
+// Up to ORDER_ONE_RANKS ranks in one launch: every workgroup lists the flagged ranks in LDS for itself (a scan over
+// two columns of the blame table), ranks its share of them and writes its share of the others.
+constexpr u32 ORDER_ONE_RANKS = 16384, ORDER_TILE = 1024;
+__global__ __launch_bounds__(256) void k_blame_order_one(const i64* __restrict__ blame, u32 n_ranks, u64* counters,
+                                                         u32* __restrict__ order, u64* host, u64 ticket) {
+  extern __shared__ unsigned short s_flagged[];      // [n_ranks] flagged ranks, ascending
+  __shared__ u32 s_before[ORDER_ONE_RANKS / ORDER_TILE], s_wave[4];
+  const u32 tid = threadIdx.x, lane = lane_id();
+  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
+  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
+  auto flags_of_four = [&](u32 r0) -> u32 {
+    u32 m = 0;
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) if (r0 + k < n_ranks && NE[r0 + k] + NX[r0 + k] != 0) m |= 1u << k;
+    return m;
+  };
+  u32 nb = 0;
+  for (u32 t = 0; t * ORDER_TILE < n_ranks; ++t) {
+    const u32 r0 = t * ORDER_TILE + tid * 4;
+    const u32 m = flags_of_four(r0);
+    u32 tot;
+    u32 at = nb + block_exclusive_sum<256>((u32)__popc(m), s_wave, &tot);
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) if (m & (1u << k)) s_flagged[at++] = (unsigned short)(r0 + k);
+    if (tid == 0) s_before[t] = nb;
+    nb += tot;
+  }
+  __syncthreads();
+  for (u32 q = blockIdx.x * 4 + tid / CCLD_WAVE; q < nb; q += gridDim.x * 4) {
+    const u32 r = s_flagged[q];
+    const u32 before = blamed_before(blame, n_ranks, s_flagged, nb, r, lane);
+    if (lane == 0) order[before] = r;
+  }
+  for (u32 t = blockIdx.x; t * ORDER_TILE < n_ranks; t += gridDim.x) {
+    const u32 r0 = t * ORDER_TILE + tid * 4;
+    const u32 m = flags_of_four(r0);
+    u32 tot;
+    u32 before = s_before[t] + block_exclusive_sum<256>((u32)__popc(m), s_wave, &tot);       // flagged ranks below r0
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) {
+      if (r0 + k >= n_ranks) break;
+      if (m & (1u << k)) ++before; else order[nb + r0 + k - before] = r0 + k;
+    }
+  }
+  report_counters(counters, host, ticket);
+}
 struct PredBlamed {
   const i64 *ne, *nx;
   bool want;
   __device__ bool operator()(u32 r) const { return ((ne[r] + nx[r]) != 0) == want; }
 };
 __global__ __launch_bounds__(256) void k_blame_order(const i64* __restrict__ blame, u32 n_ranks,
-                                                     const u32* __restrict__ lists, const u64* __restrict__ counters,
-                                                     u32* __restrict__ order) {
+                                                     const u32* __restrict__ lists, u64* counters,
+                                                     u32* __restrict__ order, u64* host, u64 ticket) {
   const u32 nb = (u32)counters[CNT_NBLAMED];
   const u32 lane = lane_id();
-  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
-  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
-  const i64* SE = blame + (u64)CCLD_BLM_SUM_LAG_ENTER * n_ranks;
-  const i64* SX = blame + (u64)CCLD_BLM_SUM_LAG_EXIT * n_ranks;
   for (u32 q = blockIdx.x * 4 + threadIdx.x / CCLD_WAVE; q < nb; q += gridDim.x * 4) {
     const u32 r = lists[q];
-    const i64 myn = NE[r] + NX[r];
-    const i64 mys = (i64)((u64)SE[r] + (u64)SX[r]);
-    u32 before = 0;
-    for (u32 i = lane; i < nb; i += CCLD_WAVE) {
-      const u32 o = lists[i];
-      const i64 on = NE[o] + NX[o];
-      const i64 os = (i64)((u64)SE[o] + (u64)SX[o]);
-      before += (on > myn) || (on == myn && (os > mys || (os == mys && o < r)));
-    }
-    before = wave_sum(before);
+    const u32 before = blamed_before(blame, n_ranks, lists, nb, r, lane);
     if (lane == 0) order[before] = r;
   }
   const u32 stride = gridDim.x * 256;
   for (u32 i = blockIdx.x * 256 + threadIdx.x; i < n_ranks - nb; i += stride) order[nb + i] = lists[n_ranks + i];
+  report_counters(counters, host, ticket);
 }
 void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, uint32_t* lists,
-                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order) {
+                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
+                        uint64_t ticket) {
+  if (n_ranks <= ORDER_ONE_RANKS) {
+    const u32 blocks = std::min<u32>((n_ranks + 255) / 256, 32);
+    hipLaunchKernelGGL(k_blame_order_one, dim3(blocks), dim3(256), sizeof(unsigned short) * n_ranks, st, blame, n_ranks, counters,
+                       order, host_counters, ticket);
+    return;
+  }
   PredBlamed p{blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks, blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks, true};
   run_select(st, p, n_ranks, tile_counts, lists, &counters[CNT_NBLAMED]);
   p.want = false;
   run_select(st, p, n_ranks, tile_counts, lists + n_ranks, &counters[CNT_NCLEAN]);
-  const u32 blocks = std::min<u32>((n_ranks + 3) / 4, 4096);
-  hipLaunchKernelGGL(k_blame_order, dim3(std::max<u32>(blocks, 1)), dim3(256), 0, st, blame, n_ranks,
-                     (const u32*)lists, (const u64*)counters, order);
+  const u32 blocks = std::min<u32>((n_ranks + 3) / 4, 512);
+  hipLaunchKernelGGL(k_blame_order, dim3(blocks), dim3(256), 0, st, blame, n_ranks, (const u32*)lists, counters, order,
+                     host_counters, ticket);
 }
 
 // the blame table and its order handed to the caller: one launch for both

@@ -56,6 +56,7 @@ struct SegArgs {
   uint64_t* counters;
   int64_t lag_floor;
   uint32_t kmad_num, kmad_den, barrier_bytes;
+  int64_t now_ns, hang_threshold_ns;             // collectives in flight for longer are counted in counters[CNT_NALERT]
   uint32_t max_size;         // members of the largest communicator (host-side: which size classes can occur)
   // (op, size class) code and T_max - T_min of every collective, for the group stage; a collective that takes
   // no part gets NO_GROUP
@@ -85,13 +86,13 @@ void launch_flag_compact(hipStream_t st, const FlagArgs& a);
 // records per rank (added into the zeroed records column of blame)
 void launch_keys_pass(hipStream_t st, const uint64_t* key, uint32_t n, const SqueezedFormat& sf,
                       const DeviceTopology& T, int64_t* blame, uint32_t* tile_heads, uint64_t* counters);
-void launch_blame_keys(hipStream_t st, const uint64_t* key, const uint32_t* flag_pos, uint32_t n_flag,
-                       const SqueezedFormat& sf, const DeviceTopology& T, uint64_t* out_key);
-void launch_blame_reduce(hipStream_t st, const uint64_t* skey, const uint32_t* sidx, uint32_t n_flag,
-                         const uint32_t* flag_pos, const uint8_t* rec_flag, const int64_t* flag_lag,
-                         uint64_t cap_n, uint32_t n_ranks, uint32_t* run /* [2 n_ranks] scratch */, int64_t* blame);
+// adds the flag list (its length is read from the counters) to the late columns of the blame table
+void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int64_t* blame);
+// order[] = ranks by (flags, summed lag, rank); then the counters go to host_counters, followed by `ticket` in
+// host_counters[CNT_COUNT] (pinned host memory): the last words of an analysis
 void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, uint32_t* lists,
-                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order);
+                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
+                        uint64_t ticket);
 
 struct GroupArgs {
   const int64_t* seg;        // collective table; its row count is read from counters[CNT_NSEG]
