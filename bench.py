@@ -42,7 +42,7 @@ def kernel_sources_digest() -> str:
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2605_04478_amd", "csrc")
     for name in ("device_utils.h", "radix_sort.h", "radix_sort.hip", "select.h", "segments.hip", "groups.hip", "window.hip",
-                 "window_kernels.h", "dense.h", "dense.hip"):
+                 "window_kernels.h", "rows.h", "grid.h", "grid.hip"):
         h.update(name.encode())
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()
@@ -332,31 +332,34 @@ def main() -> int:
     #  sort_scatter pass 1 reads the key and writes key + index (20 B); later passes move key + index (24 B)
     #  segments     key + index (12 B) and the record's op, bytes, t_enter, t_exit (25 B) in; 13 int64 columns
     #               of statistics per collective out (104 B)
-    #  the histogram re-reads, the head marking and the dense partition are this implementation's own passes:
+    #  the histogram re-reads, the head marking and the grid partition are this implementation's own passes:
     #  no algorithmic bytes
     # "layout": what this implementation's data layout moves:
-    #  ingest       reads the 41-byte SoA record, writes an 8-byte key and a 32-byte payload row
-    #  sort_hist    reads the 8-byte key once per pass
+    #  ingest       reads the 41-byte SoA record and the communicator once more, writes an 8-byte key, a 4-byte
+    #               arrival index and a 16-byte payload row
+    #  dense_partition  (window placed on the grid) reads the key and the row, writes the row
+    #  sort_hist    (window sorted) reads the 8-byte key once per pass
     #  sort_scatter as above; when key bits + index bits <= 64 the passes move one packed word (16 B) and the
     #               last pass writes key + index (8 B in, 12 B out)
     #  seg_heads    reads the sorted key once (collective heads per tile)
-    #  segments     reads key + index, gathers the 32-byte row, writes a 21-column int64 row per collective, its
-    #               detection-group key and range (16 B) and one flag byte per record
-    #  dense_partition reads and writes the 32-byte row
+    #  segments     reads the row (and key + index when sorted), writes a 21-column int64 row per collective, its
+    #               detection-group key and range (16 B) and one flag byte (grid: one cell index) per record
     n_seg = int(res.n_seg)
     bl = lambda v: int(v).bit_length()
     # key = (communicator, operation counter, member slot inside the communicator)
     key_bits = bl(tr.topo.n_comms - 1) + bl(int(np.max(tr.topo.size)) - 1) + bl(int(tr.cols["seq"].max()))
     dense = int(res.path) == 1
+    grid = prof["dense_partition"][1] > 0 and not prof["sort_scatter"][1]
     packed = passes >= 2 and key_bits + bl(n - 1) <= 64      # key and index travel as one 64-bit word
     scatter_bytes = (16.0 * (passes - 1) + 20.0) if packed else (20.0 + 24.0 * (passes - 1))
-    if dense:
+    ingest_bytes = n * (41.0 + 4.0 + 8.0 + 4.0 + 16.0)
+    if grid:
         alg = {"ingest": n * 24.0, "segments": n * 25.0 + n_seg * 104.0}
-        layout = {"ingest": n * 81.0, "dense_partition": n * 64.0, "segments": n * (32.0 + 12.0 + 1.0) + n_seg * (21 * 8.0 + 16.0)}
+        layout = {"ingest": ingest_bytes, "dense_partition": n * 40.0, "segments": n * (16.0 + 2.0) + n_seg * (21 * 8.0 + 16.0)}
     else:
         alg = {"ingest": n * 24.0, "sort_scatter": n * (20.0 + 24.0 * (passes - 1)), "segments": n * 37.0 + n_seg * 104.0}
-        layout = {"ingest": n * 81.0, "sort_hist": n * 8.0 * passes, "sort_scatter": n * scatter_bytes,
-                  "seg_heads": n * 8.0, "segments": n * (12.0 + 32.0 + 1.0) + n_seg * (21 * 8.0 + 16.0)}
+        layout = {"ingest": ingest_bytes, "sort_hist": n * 8.0 * passes, "sort_scatter": n * scatter_bytes,
+                  "seg_heads": n * 8.0, "segments": n * (12.0 + 16.0 + 1.0) + n_seg * (21 * 8.0 + 16.0)}
     kernels = {k: {"ms_per_step": round(v[0] / args.steps, 4), "launches_per_step": v[1] / args.steps}
                for k, v in prof.items() if v[1]}
     for k, v in kernels.items():
@@ -372,7 +375,7 @@ def main() -> int:
     launches_per_step = max(d_cnt // args.steps, 1)
     d_avg_ms = d_ms / max(d_cnt, 1)
     kname = {"ingest": "k_ingest_staged", "sort_scatter": "k_radix_scatter",
-             "segments": "k_dense_stats" if dense else "k_seg_wave"}[dominant]
+             "segments": "k_grid_stats" if grid else "k_seg_wave"}[dominant]
     traffic = measured_traffic(kname)
     # the whole step: algorithmic and layout bytes over the step time; the counted bytes are what the L2 exchanged
     # with the fabric (memory-side cache and HBM together), so they are not set against the HBM peak

@@ -81,13 +81,13 @@ typedef struct {
   uint32_t placement;          /* [CCLD_PLACEMENT_SORT] how ccld_analyze_window brings a collective's records together */
 } ccld_params;
 
-/* ccld_params.placement.  SORT: the window is sorted by (communicator, operation counter, rank).  DENSE: a
- * window of one batch is first analysed without sorting: every rank of a communicator bumps the same
- * operation counter (Section 5.1), so the Trace ID and the member slot fix a record's cell in a dense
- * (communicator, counter, member) grid, and one partition pass brings the records of a cell range together.
- * A window of several batches, a window with a round in which no member has a record or with counters
- * that are far apart, and a topology with a communicator of more than 2,048 members are sorted as under
- * SORT.  Both give the same tables; ccld_window_result.path tells which one ran. */
+/* ccld_params.placement.  Every rank of a communicator bumps the same operation counter (Section 5.1), so the
+ * Trace ID and the member slot fix a record's cell in a dense (communicator, counter, member) grid, and one
+ * partition pass brings the records of a cell range together.  A window whose grid is nearly full is analysed
+ * that way; one with counters that are far apart, with a round in which no member has a record, or of a topology
+ * with a communicator of more than 2,048 members is sorted by (communicator, operation counter, rank).  DENSE gives
+ * the grid memory of its own, where SORT lays it over the sort's buffers in large contexts (so it is left sooner there).
+ * Both give the same tables; ccld_window_result.path is 1 for a window of one batch that DENSE analysed on the grid. */
 enum { CCLD_PLACEMENT_SORT = 0, CCLD_PLACEMENT_DENSE = 1 };
 
 /* Communicator table (host pointers, copied by ccld_create). */

@@ -6,12 +6,15 @@
 
 #include "ccld_internal.h"
 #include "window_kernels.h"
-#include "merge.h"
-#include "dense.h"
+#include "grid.h"
 
 using namespace ccld;
 
 #define HIP_TRY(x) do { if ((x) != hipSuccess) { (void)hipGetLastError(); return CCLD_E_HIP; } } while (0)
+
+// words of the pinned buffer: the counters come first
+constexpr size_t PINNED_FINE = 32, PINNED_META = 64;
+static_assert(CNT_COUNT <= PINNED_FINE, "the counters come first");
 
 static int bits_for_host(uint64_t v) { int b = 0; while (v) { ++b; v >>= 1; } return b; }
 
@@ -48,19 +51,42 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->comm_info = w.take<uint2>(n_comms);
   // window
   c->win_key = w.take<uint64_t>(N);
-  c->win_row = w.take<Row>(N);
+  c->win_row = w.take<uint4>(N);
+  c->win_wide = w.take<int64_t>(3 * N);
+  c->win_arrival = w.take<uint32_t>(c->n_buckets > 1 ? N : 1);
   c->batch_meta = w.take<BatchMeta>((uint64_t)c->p.window_batches + 2);
-  c->ing_table = w.take<uint32_t>((uint64_t)INGEST_MAX_BUCKETS * INGEST_BLOCKS);
-  c->ing_base = w.take<uint32_t>(INGEST_MAX_BUCKETS + 2);
+  const uint64_t n_meta = (uint64_t)c->p.window_batches + 2;
+  c->ing_table = w.take<uint32_t>((uint64_t)c->n_buckets * INGEST_BLOCKS);
+  c->ing_base = w.take<uint32_t>(n_meta * (c->n_buckets + 1) + 4);
+  c->ing_done = w.take<uint32_t>(1);
+  c->comm_range = c->grid_capable ? w.take<uint64_t>(n_meta * n_comms * 2) : nullptr;
   // sort
   // (the hang pass sorts its root list, at most one entry per communicator member, in these buffers too)
   const uint64_t NS = std::max<uint64_t>(N, n_members);
   c->sort_cap = NS;
   const uint64_t tw = sort_table_words(NS);
+  // The partitioned rows of the grid placement and the arrays that run beside them.  A window is either sorted or placed
+  // on the grid, so in large contexts they lie over the sort buffers; small ones, and contexts that ask for
+  // the placement, have them apart.
+  auto take_grid = [&](Carver& g) {
+    const uint64_t cells = c->cell_cap;
+    c->g_rows = g.take<uint4>(cells);
+    c->g_slots = g.take<uint32_t>(cells);
+    c->g_cell_row = g.take<uint16_t>(cells);
+    c->flag_stage = g.take<uint32_t>(N);
+  };
+  const uint64_t sort_begin = w.off;
   for (int i = 0; i < 2; ++i) { c->sb.key[i] = w.take<uint64_t>(NS); c->sb.idx[i] = w.take<uint32_t>(NS); }
+  c->keyC = w.take<uint64_t>(NS);
+  if (c->grid_capable && c->grid_over_sort) {
+    Carver g{w.base, sort_begin};
+    take_grid(g);
+    w.off = std::max(w.off, g.off);
+  } else if (c->grid_capable) {
+    take_grid(w);
+  }
   c->sb.table = w.take<uint32_t>(tw);
   c->sb.totals = w.take<uint32_t>(SORT_RADIX);
-  c->keyC = w.take<uint64_t>(NS); c->idxC = w.take<uint32_t>(NS);
   c->table2 = w.take<uint32_t>(tw);
   c->totals2 = w.take<uint32_t>(SORT_RADIX);
   // analysis scratch
@@ -79,7 +105,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->flag_pos = w.take<uint32_t>(N);
   c->flag_lag = w.take<int64_t>(2 * N);
   c->big_list = w.take<uint32_t>(3 * (N / 65 + 2));
-  c->big_ex = w.take<int64_t>(2 * N);
+  c->flag_key = w.take<uint64_t>(N);
   c->range_c = w.take<int64_t>(N);
   c->gcode = w.take<uint16_t>(N);
   c->comm_groups = w.take<uint32_t>((uint64_t)n_comms + 1);
@@ -93,18 +119,16 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   // the counters and the blame table are cleared together at the start of every analysis
   c->counters = w.take<uint64_t>(CNT_COUNT);
   c->blame = w.take<int64_t>((uint64_t)CCLD_BLM_NCOL * n_ranks);
-  // dense placement: counter ranges, layout, fine-bucket fill counts and the partitioned rows (room for an
-  // eighth more cells than records, and one partly filled fine bucket per communicator)
-  c->fine_cap = 0;
-  c->comm_range = nullptr; c->d_lay = nullptr; c->d_hdr = nullptr; c->d_fill = nullptr; c->d_rows = nullptr; c->d_desc = nullptr;
-  if (c->dense_capable) {
-    c->fine_cap = (uint32_t)((N + N / 8) / DENSE_B + n_comms + 16);
-    c->comm_range = w.take<uint64_t>(2ull * n_comms);
-    c->d_lay = w.take<CommLayout>((uint64_t)n_comms + 1);
-    c->d_hdr = w.take<uint32_t>(DH_COUNT);
-    c->d_fill = w.take<uint32_t>((uint64_t)c->fine_cap + 4);
-    c->d_rows = w.take<Row>((uint64_t)c->fine_cap * DENSE_STRIDE);
-    c->d_desc = w.take<FineDesc>((uint64_t)c->fine_cap);
+  c->g_lay = nullptr; c->g_hdr = nullptr; c->g_desc = nullptr;
+  if (c->grid_capable) {
+    const uint64_t F = (uint64_t)c->fine_cap + 4;
+    c->g_lay = w.take<CommLayout>((uint64_t)n_comms + 1);
+    c->g_hdr = w.take<GridHeader>(1);
+    c->g_desc = w.take<FineDesc>(F);
+    const uint64_t pieces = c->n_buckets == 1 ? 1 : (uint64_t)c->n_buckets * c->p.window_batches;
+    c->g_piece_at = w.take<uint32_t>(pieces + 1); c->g_piece_slot = w.take<uint32_t>(pieces);
+    c->g_fill = w.take<uint32_t>(F); c->g_rec0 = w.take<uint32_t>(F);
+    c->g_nflag = w.take<uint32_t>(F); c->g_long = w.take<uint32_t>(F);
   }
   // hang location
   const uint64_t SN = std::max<uint64_t>(c->snap_cap, 1);
@@ -168,12 +192,41 @@ ccld_status check_topology(const ccld_topology* t, uint64_t* n_members) {
   return CCLD_OK;
 }
 
-// Windows of one batch can be analysed by dense placement when every communicator fits a fine bucket and
-// the counting kernel's LDS holds a counter range per communicator.
-bool dense_capable(const ccld_params* p, const ccld_topology* t) {
-  if (p->placement != CCLD_PLACEMENT_DENSE || p->window_batches != 1 || t->n_comms > DENSE_MAX_COMMS) return false;
-  for (uint32_t k = 0; k < t->n_comms; ++k) if (t->size[k] > DENSE_B) return false;
-  return true;
+// What follows from the parameters, the topology and the capacities: the key format, whether windows can be placed on the
+// grid, and the communicator buckets of the ingest.
+void plan(ccld_ctx* c, const ccld_params* p, const ccld_topology* t, uint64_t n_members, uint64_t cap, uint64_t batch_cap, uint64_t snap_cap) {
+  c->p = *p;
+  c->cap = cap; c->batch_cap = batch_cap; c->snap_cap = snap_cap;
+  uint32_t max_size = 1;
+  for (uint32_t k = 0; k < t->n_comms; ++k) max_size = std::max(max_size, t->size[k]);
+  const int mb = bits_for_host(max_size - 1), cb = bits_for_host(t->n_comms - 1);
+  c->max_comm_size = max_size;
+  c->kf.mb = mb; c->kf.cb = cb; c->kf.sb = 64 - mb - cb;
+  const uint64_t N = std::max<uint64_t>(cap, 1), W = p->window_batches;
+  c->grid_capable = cap > 0 && max_size <= GRID_B && t->n_comms <= GRID_MAX_COMMS && (W + 2) * t->n_comms * 16 <= (64ull << 20);
+  c->dense_asked = p->placement == CCLD_PLACEMENT_DENSE && W == 1;
+  // cells beyond the records: a fifth, so that windows with members missing here and there stay on the grid; small
+  // contexts can afford twice the records and take the arrays of their own
+  c->grid_over_sort = N >= (4u << 20) && p->placement != CCLD_PLACEMENT_DENSE;
+  c->cell_cap = (uint32_t)std::min<uint64_t>(N >= (4u << 20) ? N + N / 5 : 2 * N + 4096, 0xFFFFFF00u);
+  c->fine_cap = c->cell_cap / GRID_MIN_FILL + t->n_comms + 16;
+  // Communicator buckets of the ingest.  A partition workgroup addresses GRID_SPAN fine buckets at a time, so a window that
+  // may have more of them is placed by bucket, into as many buckets as leave about GRID_TARGET fine buckets in one:
+  // fewer shorten the runs that the partition writes, more those that the ingest writes (82M records in 64 / 128 / 256
+  // buckets: ingest 1627 / 1729 / 1869 us, partition 1447 / 1295 / 1172 us).  A window that cannot be placed on the grid
+  // takes buckets whose rows (16 bytes per record) stay within about 100 MB, which the memory-side cache holds while the
+  // statistics gather from one.
+  int bb = 0;
+  if (c->grid_capable) {
+    const uint64_t fine = N / 1400 + t->n_comms;
+    if (fine > GRID_ONE_BUCKET) while (bb < 8 && (fine >> bb) > GRID_TARGET) ++bb;
+    while (bb > 0 && ((W << bb) > GRID_MAX_PIECES)) --bb;
+    if (bb > 0 && W > GRID_MAX_BATCHES) c->grid_capable = false;
+  }
+  if (!c->grid_capable) { bb = 0; while (bb < 6 && ((N * 16) >> bb) > 100000000ull) ++bb; }
+  c->bshift = cb > bb ? cb - bb : 0;
+  c->n_buckets = ((t->n_comms - 1) >> c->bshift) + 1;
+  c->n_members = n_members;
 }
 
 ccld_status data_status(uint64_t bits) {
@@ -221,8 +274,7 @@ ccld_status ccld_query_workspace(const ccld_params* params, const ccld_topology*
       max_snapshot_rows >= (1ull << 31))
     return CCLD_E_CAPACITY;
   ccld_ctx tmp;
-  tmp.p = *params; tmp.cap = max_window_records; tmp.batch_cap = max_batch_records; tmp.snap_cap = max_snapshot_rows;
-  tmp.dense_capable = dense_capable(params, topo);
+  plan(&tmp, params, topo, n_members, max_window_records, max_batch_records, max_snapshot_rows);
   Carver w{nullptr, 0};
   carve_all(&tmp, w, topo->n_ranks, topo->n_comms, n_members);
   *bytes = w.off + 256;
@@ -238,47 +290,24 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   ccld_status s = ccld_query_workspace(params, topo, max_window_records, max_batch_records, max_snapshot_rows, &need);
   if (s != CCLD_OK) return s;
   if (workspace_bytes < need || ((uintptr_t)workspace & 255) != 0) return CCLD_E_WORKSPACE;
-  uint32_t max_size = 1;
-  for (uint32_t k = 0; k < topo->n_comms; ++k) max_size = std::max(max_size, topo->size[k]);
-  const int mb = bits_for_host(max_size - 1), cb = bits_for_host(topo->n_comms - 1);
-  if (mb + cb > 63) return CCLD_E_KEY_WIDTH;
   ccld_ctx* c = new (std::nothrow) ccld_ctx();
   if (!c) return CCLD_E_BAD_ARG;
-  c->p = *params;
-  c->stream = (hipStream_t)hip_stream;
-  c->cap = max_window_records; c->batch_cap = max_batch_records; c->snap_cap = max_snapshot_rows;
-  c->kf.mb = mb; c->kf.cb = cb; c->kf.sb = 64 - mb - cb;
-  c->dense_capable = dense_capable(params, topo);
-  c->last_path = 0;
-  c->chain_ready = false;
-  c->max_comm_size = max_size;
-  c->rank_bits = bits_for_host(topo->n_ranks - 1);
-  c->head = 0; c->count = 0; c->next_slot = 0; c->total_ingested = 0;
-  // Communicator buckets of the window placement: enough of them that one bucket's payload rows
-  // (32 bytes per record) stay within about 100 MB, which the memory-side cache holds while the
-  // analysis gathers from that bucket; no more than that, because every further bucket shortens the
-  // runs a workgroup writes at ingest (measured at 82M records: 17 buckets 8.46 ms per step, 34
-  // buckets 8.60 ms, 9 buckets 8.51 ms, one bucket 9.45 ms).
-  {
-    int bb = 0;
-    while (bb < 6 && ((max_window_records * 32) >> bb) > 100000000ull) ++bb;
-    // dense placement partitions every bucket once more: about half a million records per bucket keep the
-    // fine buckets of two neighbouring buckets within what a partition workgroup addresses
-    if (c->dense_capable) while (bb < 8 && (max_window_records >> bb) > 512 * 1024) ++bb;
-    c->bshift = cb > bb ? cb - bb : 0;
-  }
-  c->n_buckets = ((topo->n_comms - 1) >> c->bshift) + 1;
-  c->sorted_buf = 0; c->last_n = 0; c->blame_valid = false; c->sort_passes = 0;
-  c->inc_ok = false; c->inc_head = c->inc_count = c->inc_total = 0;
-  c->sf.mb = mb; c->sf.ws = 0; c->sf.seq_base = 0;
   uint64_t n_members = 0;
   check_topology(topo, &n_members);
+  plan(c, params, topo, n_members, max_window_records, max_batch_records, max_snapshot_rows);
+  const int mb = c->kf.mb, cb = c->kf.cb;
+  if (mb + cb > 63) { delete c; return CCLD_E_KEY_WIDTH; }
+  c->stream = (hipStream_t)hip_stream;
+  c->chain_ready = false;
+  c->rank_bits = bits_for_host(topo->n_ranks - 1);
+  c->head = 0; c->count = 0; c->next_slot = 0; c->total_ingested = 0;
+  c->sorted_buf = 0; c->last_n = 0; c->blame_valid = false; c->sort_passes = 0;
+  c->sf.mb = mb; c->sf.ws = 0; c->sf.seq_base = 0;
   Carver w{(uint8_t*)workspace, 0};
   carve_all(c, w, topo->n_ranks, topo->n_comms, n_members);
   c->topo.n_ranks = topo->n_ranks; c->topo.n_comms = topo->n_comms;
   c->h_size.assign(topo->size, topo->size + topo->n_comms);
   c->h_pinned = nullptr;
-  c->ev_heads = nullptr;
   c->ticket = 0;
 
   // derived host tables: sorted member lists, rank -> communicators CSR
@@ -351,21 +380,22 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (!fits_cell4) c->topo.rank_cell4 = nullptr;
   if (hipMemsetAsync(c->gstate, 0, sizeof(GroupState) * (uint64_t)topo->n_comms * GROUP_SLOTS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->batch_meta, 0, sizeof(BatchMeta) * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
+  if (c->comm_range && hipMemsetAsync(c->comm_range, 0, 16ull * topo->n_comms * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
+  if (hipMemsetAsync(c->ing_done, 0, sizeof(uint32_t), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
   if (hipMemsetAsync(c->f_last, 0, sizeof(uint64_t) * 2 * CCLD_FRAME_CHANNELS * n_members, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)topo->n_ranks, c->stream) != hipSuccess) rs = CCLD_E_HIP;
-  {     // pinned readback buffer: the counters, or the headers of every batch slot
-    const size_t bytes = std::max<size_t>(4096 * sizeof(uint64_t), sizeof(BatchMeta) * ((size_t)c->p.window_batches + 2));
+  {     // pinned words: the counters, the ticket and the fine buckets of a layout, then the headers of every batch slot
+    const size_t bytes = std::max<size_t>(4096 * sizeof(uint64_t), (PINNED_META) * sizeof(uint64_t) + sizeof(BatchMeta) * ((size_t)c->p.window_batches + 2));
     if (hipHostMalloc((void**)&c->h_pinned, bytes, hipHostMallocDefault) != hipSuccess) rs = CCLD_E_HIP;
+    else std::memset(c->h_pinned, 0, bytes);
   }
-  if (hipEventCreateWithFlags(&c->ev_heads, hipEventDisableTiming) != hipSuccess) { c->ev_heads = nullptr; rs = CCLD_E_HIP; }
   if (ccld_static_scratch_init() != CCLD_OK) rs = CCLD_E_HIP;          // address of the static array on this device
   if (hipStreamSynchronize(c->stream) != hipSuccess) rs = CCLD_E_HIP;   // host vectors above die at return
   if (rs != CCLD_OK) {
     (void)hipGetLastError();
     if (c->h_pinned) (void)hipHostFree(c->h_pinned);
-    if (c->ev_heads) (void)hipEventDestroy(c->ev_heads);
     delete c;
     return rs;
   }
@@ -377,7 +407,6 @@ ccld_status ccld_destroy(ccld_ctx* c) {
   if (!c) return CCLD_E_NULL;
   (void)hipStreamSynchronize(c->stream);
   if (c->h_pinned) (void)hipHostFree(c->h_pinned);
-  if (c->ev_heads) (void)hipEventDestroy(c->ev_heads);
   c->prof.destroy();
   delete c;
   return CCLD_OK;
@@ -386,7 +415,6 @@ ccld_status ccld_destroy(ccld_ctx* c) {
 ccld_status ccld_reset_window(ccld_ctx* c) {
   if (!c) return CCLD_E_NULL;
   c->head = 0; c->count = 0; c->batch_n.clear(); c->batch_slot.clear(); c->batch_seqno.clear();
-  c->inc_ok = false;
   c->chain_ready = false;
   return CCLD_OK;
 }
@@ -407,8 +435,8 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   IngestArgs a;
   std::memset(&a, 0, sizeof(a));
   const uint32_t slot = c->next_slot;
-  a.meta = c->batch_meta + slot;
-  if (n == 0) HIP_TRY(hipMemsetAsync(a.meta, 0, sizeof(BatchMeta), c->stream));     // otherwise the counting kernel clears it
+  const uint32_t n_meta = c->p.window_batches + 2, next = (slot + 1) % n_meta;
+  a.meta = c->batch_meta + slot; a.meta_next = c->batch_meta + next;
   if (b->on_device) {
     a.rank = b->rank; a.comm = b->comm; a.seq = b->seq; a.op = b->op; a.bytes = b->bytes;
     a.t_enter = b->t_enter; a.t_exit = b->t_exit;
@@ -427,14 +455,14 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
     HIP_TRY(hipMemcpyAsync(d_op, b->op, n, hipMemcpyHostToDevice, c->stream));
     a.rank = d_rank; a.comm = d_comm; a.seq = d_seq; a.op = d_op; a.bytes = d_bytes; a.t_enter = d_te; a.t_exit = d_tx;
   }
-  a.n = n; a.win_key = c->win_key; a.win_row = c->win_row;
+  a.n = n; a.win_key = c->win_key; a.win_row = c->win_row; a.win_wide = c->win_wide; a.win_arrival = c->win_arrival;
   a.tail = (uint32_t)((head + count) % std::max<uint64_t>(c->cap, 1));
   a.cap = (uint32_t)c->cap;
-  a.table = c->ing_table; a.bucket_base = c->ing_base; a.scratch_total = &c->counters[CNT_COUNT - 1];
+  a.table = c->ing_table; a.bucket_base = c->ing_base + (uint64_t)slot * (c->n_buckets + 1); a.done = c->ing_done; a.scratch_total = &c->counters[CNT_COUNT - 1];
   a.n_buckets = c->n_buckets; a.bshift = c->bshift; a.seqno0 = (uint32_t)c->total_ingested;
-  if (c->dense_capable && n) {
-    a.range = c->comm_range;
-    HIP_TRY(hipMemsetAsync(a.range, 0, 16ull * c->topo.n_comms, c->stream));
+  if (c->grid_capable) {
+    a.range = c->comm_range + (uint64_t)slot * c->topo.n_comms * 2;
+    a.range_next = c->comm_range + (uint64_t)next * c->topo.n_comms * 2;
   }
   c->prof.begin(CCLD_PROF_INGEST);
   launch_ingest(c->stream, a, c->topo, c->kf);
@@ -448,7 +476,7 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   c->batch_slot.push_back(slot);
   c->batch_seqno.push_back((uint32_t)c->total_ingested);
   c->total_ingested += n;
-  c->next_slot = (slot + 1) % (c->p.window_batches + 2);
+  c->next_slot = next;
   c->head = head; c->count = count + n;
   return CCLD_OK;
 }
@@ -457,238 +485,75 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
 // thing on the stream, so the stream has drained then; spinning on the word costs about 10 us less than copying the
 // counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
 // hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
+static bool reported(const ccld_ctx* c) {
+  for (int i = 0; i < CNT_COUNT; ++i)
+    if ((__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED) >> REPORT_BITS) != (c->ticket & 0xFFFF)) return false;
+  return true;
+}
 static hipError_t wait_report(ccld_ctx* c) {
-  const uint64_t* word = c->h_pinned + CNT_COUNT;
+  bool there = false;
   if (!c->prof.on) {
     const auto t0 = std::chrono::steady_clock::now();
-    for (uint32_t i = 1;; ++i) {
-      if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == c->ticket) return hipSuccess;
+    for (uint32_t i = 1; !(there = reported(c)); ++i) {
       if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
       __builtin_ia32_pause();
     }
   }
-  const hipError_t e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return e;
-  return __atomic_load_n(word, __ATOMIC_ACQUIRE) == c->ticket ? hipSuccess : hipErrorUnknown;
+  if (!there) {
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return e;
+    if (!reported(c)) return hipErrorUnknown;
+  }
+  for (int i = 0; i < CNT_COUNT; ++i) c->h_pinned[i] &= REPORT_MASK;
+  return hipSuccess;
 }
 
 static void zero_counts(ccld_window_result* o) {
   o->n_records = o->n_seg = o->n_flag = o->n_group = o->n_alert = o->n_cand = 0;
 }
 
-// One analysis of the resident window.  dense: bring the collectives together by dense placement instead of
-// sorting; *fallback is set (and nothing of the context's detection state has changed) when the window turns
-// out not to fill a dense grid, and the caller then sorts.
-static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_result* o, bool dense, bool* fallback) {
-  zero_counts(o);
-  o->status = CCLD_OK;
-  o->path = dense ? 1 : 0;
-  *fallback = false;
-  c->chain_ready = false;
-  c->blame_valid = false;
-  if (!o->seg || o->seg_cap == 0) return o->status = CCLD_E_NULL;
-  if ((o->flag_cap && !o->flag) || (o->group_cap && !o->group) || (o->alert_cap && !o->alert) ||
-      (o->cand_cap && !o->cand))
-    return o->status = CCLD_E_NULL;
+// Waits for the number of fine buckets of a layout (a window large enough that launching for the most there could be
+// would cost more than the wait): 0 = the layout is not feasible.
+static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine) {
+  const uint32_t* word = reinterpret_cast<const uint32_t*>(c->h_pinned + PINNED_FINE);
+  const auto t0 = std::chrono::steady_clock::now();
+  uint32_t v;
+  for (uint32_t i = 1; (v = __atomic_load_n(word, __ATOMIC_ACQUIRE)) == 0; ++i) {
+    if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) {
+      const hipError_t e = hipStreamSynchronize(c->stream);
+      if (e != hipSuccess) return e;
+      if ((v = __atomic_load_n(word, __ATOMIC_ACQUIRE)) == 0) return hipErrorUnknown;
+      break;
+    }
+    __builtin_ia32_pause();
+  }
+  *n_fine = (v & 0x80000000u) ? 0u : v - 1;
+  return hipSuccess;
+}
+// Most fine buckets that a launch is sized for without asking for their number.
+constexpr uint32_t FINE_BOUND = 4096;
+
+// Everything behind the statistics and the flags: groups, the blame order and the report of the counters.
+static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_result* o, const SegArgs& sa, bool grid, bool* fallback) {
   hipStream_t st = c->stream;
-  const uint32_t n = (uint32_t)c->count;
-  const uint32_t n_ranks = c->topo.n_ranks;
-
-  // 1. data errors found at ingest, and the widest sequence number in the window
-  const size_t nb = c->batch_slot.size();
-  uint64_t bits = 0, max_seq = 0, min_seq = ~0ull;
-  if (nb) {
-    const uint32_t n_meta = c->p.window_batches + 2;
-    HIP_TRY(hipMemcpyAsync(c->h_pinned, c->batch_meta, sizeof(BatchMeta) * n_meta, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    const BatchMeta* hm = (const BatchMeta*)c->h_pinned;
-    for (size_t i = 0; i < nb; ++i) {
-      const BatchMeta& m = hm[c->batch_slot[i]];
-      bits |= m.status; max_seq = std::max(max_seq, m.max_seq); min_seq = std::min(min_seq, ~m.max_inv_seq);
-    }
-  }
-  if (bits) { c->inc_ok = false; return o->status = data_status(bits); }     // the kept order does not survive a bad batch
-  o->n_records = n;
-  {
-    const size_t blame_bytes = sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks;
-    uint8_t* c0 = reinterpret_cast<uint8_t*>(c->counters);
-    uint8_t* b0 = reinterpret_cast<uint8_t*>(c->blame);
-    if (b0 >= c0 && (size_t)(b0 - c0) < 4096) {        // adjacent in the workspace: one fill
-      HIP_TRY(hipMemsetAsync(c0, 0, (size_t)(b0 - c0) + blame_bytes, st));
-    } else {
-      HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
-      HIP_TRY(hipMemsetAsync(c->blame, 0, blame_bytes, st));
-    }
-  }
-  c->last_n = n;
-  c->h_pinned[CNT_COUNT] = 0;          // the batch headers were read into these words
-  c->ticket += 1;
-  if (n == 0) {
-    launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(wait_report(c));
-    c->blame_valid = true;
-    return o->status;
-  }
-
-  // 2. sort by (communicator, operation counter, rank) on the significant bits only
-  // the operation counters of the window relative to its smallest one
-  if (min_seq > max_seq) min_seq = max_seq;
-  const int mb = c->kf.mb, cb = c->kf.cb, ws = bits_for_host(max_seq - min_seq);
-  c->sf.mb = mb; c->sf.ws = ws; c->sf.seq_base = min_seq;
-  KeySource src;
-  src.key = c->win_key; src.head = (uint32_t)c->head; src.cap = (uint32_t)c->cap;
-  src.squeeze = 1;
-  src.hi_shift = 64 - cb;                                  // 64 when there is a single communicator
-  src.lo_bits = mb + ws;
-  src.lo_mask = cb > 0 ? (((uint64_t)1 << (64 - cb)) - 1) : ~0ull;      // everything below the communicator field
-  src.lo_sub = min_seq << mb;
-  // A window of several batches that still holds at least half of the previously analysed window keeps that
-  // window's order: the new records are sorted on their own and merged with the previous order, whose keys are
-  // re-based to this window's format and whose entries of the batches that left are dropped on the way.
-  const bool was_ok = c->inc_ok && !dense;
-  c->inc_ok = false;
-  const uint64_t cap = std::max<uint64_t>(c->cap, 1);
-  const uint64_t n_new = c->total_ingested - c->inc_total;
-  int sorted = -1;
-  if (was_ok && n_new > 0 && n_new < n && c->inc_sf.mb == mb && mb + ws + cb <= 64 && mb + ws < 64 &&
-      c->inc_sf.mb + c->inc_sf.ws < 64) {
-    const uint64_t kept = n - n_new;                                     // records of the previous window still here
-    if (kept >= n_new && kept <= c->inc_count) {
-      const uint64_t exp_n = c->inc_count - kept;
-      const uint64_t old_tail = (c->inc_head + c->inc_count) % cap;
-      if ((c->inc_head + exp_n) % cap == c->head && (old_tail + n_new) % cap == (c->head + n) % cap) {
-        // the new records end in the third buffer pair (a sort of p passes ends in its buffer (p - 1) % 2), so
-        // that the merge can read the previous order where it lies and write beside it
-        const int s = c->sorted_buf;
-        const int passes = (mb + ws + cb) <= 0 ? 1 : (mb + ws + cb + SORT_RBITS - 1) / SORT_RBITS;
-        const int third = (passes - 1) % 2;
-        SortBuffers sbn;
-        sbn.key[third] = c->keyC; sbn.idx[third] = c->idxC;
-        sbn.key[1 - third] = c->sb.key[1 - s]; sbn.idx[1 - third] = c->sb.idx[1 - s];
-        sbn.table = c->table2; sbn.totals = c->totals2;
-        KeySource fresh = src;
-        fresh.head = (uint32_t)old_tail;
-        const int rb = radix_sort_pairs(st, fresh, (uint32_t)n_new, sbn, mb + ws + cb, &c->prof, CCLD_PROF_SORT_HIST,
-                                        CCLD_PROF_SORT_SCAN, CCLD_PROF_SORT_SCATTER);
-        if (rb < 0) return o->status = CCLD_E_HIP;
-        if (rb != third) {
-          HIP_TRY(hipMemcpyAsync(c->keyC, sbn.key[rb], sizeof(uint64_t) * n_new, hipMemcpyDeviceToDevice, st));
-          HIP_TRY(hipMemcpyAsync(c->idxC, sbn.idx[rb], sizeof(uint32_t) * n_new, hipMemcpyDeviceToDevice, st));
-        }
-        c->prof.begin(CCLD_PROF_SORT_SCATTER);
-        RetainArgs ra;
-        ra.key = c->sb.key[s]; ra.idx = c->sb.idx[s]; ra.n = (uint32_t)c->inc_count; ra.from = c->inc_sf; ra.to = c->sf;
-        ra.exp_lo = (uint32_t)c->inc_head; ra.exp_n = (uint32_t)exp_n; ra.cap = (uint32_t)cap;
-        ra.tile_counts = c->tile_flags; ra.total_out = &c->counters[CNT_NRETAINED];
-        ra.key_out = c->sb.key[1 - s]; ra.idx_out = c->sb.idx[1 - s];
-        launch_merge_kept(st, ra, c->keyC, c->idxC, (uint32_t)n_new, c->tile_heads);
-        c->prof.end(CCLD_PROF_SORT_SCATTER);
-        sorted = 1 - s;
-      }
-    }
-  }
-  DenseArgs da;
-  std::memset(&da, 0, sizeof(da));
-  uint32_t dense_n_fine = 0;
-  if (dense) {
-    // the grid's layout from the batch's counter ranges; its size comes back while the partition runs
-    da.win_key = c->win_key; da.win_row = c->win_row; da.head = (uint32_t)c->head; da.cap = (uint32_t)cap; da.n = n;
-    da.kf = c->kf; da.comm_size = c->topo.size; da.n_comms = c->topo.n_comms;
-    da.bucket_base = c->ing_base; da.n_buckets = c->n_buckets; da.bshift = c->bshift;
-    da.range = c->comm_range; da.lay = (CommLayout*)c->d_lay; da.hdr = c->d_hdr; da.fill = c->d_fill;
-    da.rows = c->d_rows; da.fine_cap = c->fine_cap; da.counters = c->counters;
-    da.desc = (FineDesc*)c->d_desc; da.seq_base = c->sf.seq_base;
-    c->prof.begin(CCLD_PROF_DENSE_PARTITION);
-    launch_dense_layout(st, da);
-    uint32_t* h_hdr = reinterpret_cast<uint32_t*>(c->h_pinned + 2 * CNT_COUNT);
-    HIP_TRY(hipMemcpyAsync(h_hdr, c->d_hdr, sizeof(uint32_t) * DH_COUNT, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipEventRecord(c->ev_heads, st));
-    launch_fill_u64(st, reinterpret_cast<uint64_t*>(c->d_fill), ((uint64_t)c->fine_cap + 4) / 2, 0ull);
-    launch_dense_partition(st, da);
-    launch_scan_tiles(st, c->d_fill, c->fine_cap + 1, &c->counters[CNT_NRETAINED]);
-    launch_dense_desc(st, da);
-    HIP_TRY(hipEventSynchronize(c->ev_heads));
-    if (!h_hdr[DH_FEASIBLE]) {          // far-apart counters or too many fine buckets: the kernels above did nothing
-      HIP_TRY(hipStreamSynchronize(st));
-      c->prof.end(CCLD_PROF_DENSE_PARTITION);
-      c->prof.collect();
-      *fallback = true;
-      return CCLD_OK;
-    }
-    dense_n_fine = h_hdr[DH_N_FINE];
-    sorted = 0;
-    c->sort_passes = 0;
-  } else {
-  if (sorted < 0)
-    sorted = radix_sort_pairs(st, src, n, c->sb, mb + ws + cb, &c->prof, CCLD_PROF_SORT_HIST,
-                              CCLD_PROF_SORT_SCAN, CCLD_PROF_SORT_SCATTER);
-  c->sort_passes = (mb + ws + cb) <= 0 ? 1 : (mb + ws + cb + SORT_RBITS - 1) / SORT_RBITS;
-  if (sorted < 0) return o->status = CCLD_E_HIP;
-  }
-  c->sorted_buf = sorted;
-  const uint64_t* skey = c->sb.key[sorted];
-  const uint32_t* sidx = c->sb.idx[sorted];
-  const Row* rows = dense ? c->d_rows : c->win_row;     // payload rows that sidx addresses
-
-  // 3. collectives: heads per tile, their scan, statistics, flags
-  SegArgs sa;
-  std::memset(&sa, 0, sizeof(sa));
-  sa.key = skey; sa.idx = sidx; sa.row = rows; sa.n = n; sa.sf = c->sf; sa.comm_size = c->topo.size;
-  sa.member_off = c->topo.member_off; sa.members_sorted = c->topo.members_sorted; sa.comm_info = c->comm_info;
-  sa.tile_heads = c->tile_heads; sa.seg = o->seg; sa.seg_cap = o->seg_cap;
-  sa.rec_flag = o->rec_flag ? o->rec_flag : c->rec_flag;
-  sa.lag_e = o->lag_enter; sa.lag_x = o->lag_exit; sa.flag_lag = c->flag_lag; sa.cap_n = c->cap;
-  sa.big_list = c->big_list; sa.big_cap = c->cap / 65 + 2; sa.big_ex = c->big_ex; sa.counters = c->counters;
-  sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
-  sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size;
-  sa.gcode = c->gcode; sa.range_c = c->range_c;
-  const uint32_t seg_tiles = (n + SEG_TILE - 1) / SEG_TILE;
-  if (dense) {
-    // every collective's row of the table is fixed by the layout; a duplicate key or a round without any
-    // record shows in the status word at the end (the group stage leaves the detection state alone then)
-    c->prof.split(CCLD_PROF_DENSE_PARTITION, CCLD_PROF_SEGMENTS);
-    launch_dense_stats(st, sa, da, dense_n_fine, c->sb.key[sorted], c->sb.idx[sorted], c->blame, n_ranks);
-    c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
-  } else {
-  c->prof.begin(CCLD_PROF_SEG_HEADS);
-  launch_keys_pass(st, skey, n, c->sf, c->topo, c->blame, c->tile_heads, c->counters);
-  launch_scan_tiles(st, c->tile_heads, seg_tiles, &c->counters[CNT_NSEG]);
-  c->prof.split(CCLD_PROF_SEG_HEADS, CCLD_PROF_SEGMENTS);          // one event ends a timed span and begins the next
-  launch_seg_analyze(st, sa);
-  c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
-  }
-  FlagArgs fa;
-  std::memset(&fa, 0, sizeof(fa));
-  fa.key = skey; fa.rec_flag = sa.rec_flag; fa.flag_lag = c->flag_lag; fa.cap_n = c->cap; fa.n = n; fa.sf = c->sf;
-  fa.member_off = c->topo.member_off; fa.members_sorted = c->topo.members_sorted;
-  fa.tile_flags = c->tile_flags; fa.flag_pos = c->flag_pos; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
-  fa.counters = c->counters;
-  launch_flag_compact(st, fa);
-  if (o->perm) launch_perm(st, sidx, rows, n, c->batch_seqno.empty() ? 0u : c->batch_seqno[0], o->perm);
-  // 4. per-rank blame
-  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_BLAME);
-  launch_blame_sums(st, fa, n_ranks, c->blame);
-  c->prof.split(CCLD_PROF_BLAME, CCLD_PROF_GROUPS);
-  // 5. slow detection and location per detection group (Eq. 1-4); nothing here waits for the host.  The stage
-  //    words live in the third sort buffer pair, which holds nothing at this point.
+  // slow detection and location per detection group (Eq. 1-4)
   GroupArgs ga;
   std::memset(&ga, 0, sizeof(ga));
   ga.seg = o->seg; ga.seg_cap = o->seg_cap; ga.counters = c->counters; ga.gcode = c->gcode; ga.range_c = c->range_c;
   ga.n_comms = c->topo.n_comms; ga.comm_groups = c->comm_groups; ga.comm_row = c->comm_row;
-  ga.stage[0] = reinterpret_cast<uint32_t*>(c->keyC); ga.stage[1] = ga.stage[0] + c->sort_cap; ga.stage[2] = c->idxC;
+  ga.stage[0] = c->alert_list; ga.stage[1] = c->alert_ncand; ga.stage[2] = c->chain_parent;      // nothing lives there yet
   ga.gstate = c->gstate; ga.rate_root = c->rate_root; ga.group = o->group; ga.group_cap = o->group_cap; ga.p = c->p;
   launch_groups(st, ga);
   c->prof.end(CCLD_PROF_GROUPS);
   // the blame order is ready when ccld_rank_blame asks for it; its kernel reports the counters
-  launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
+  launch_blame_order(st, c->blame, c->topo.n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   if (c->h_pinned[CNT_STATUS]) {
     const uint64_t bad = c->h_pinned[CNT_STATUS];
     c->prof.collect();
     zero_counts(o);
-    if (dense && (bad & DS_DENSE_FALLBACK)) { *fallback = true; return CCLD_OK; }
+    if (grid && (bad & DS_DENSE_FALLBACK)) { *fallback = true; return CCLD_OK; }
     return o->status = data_status(bad);
   }
   o->n_seg = c->h_pinned[CNT_NSEG];
@@ -697,12 +562,16 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   o->n_group = c->h_pinned[CNT_NGROUP];
   if (o->n_seg > o->seg_cap || o->n_flag > o->flag_cap || o->n_group > o->group_cap) o->status = CCLD_W_TRUNCATED;
 
-  // 6. hang alerts: the collectives that raise one in table order, and the candidates of every alert
+  // hang alerts: the collectives that raise one in table order, and the candidates of every alert
   if (o->n_alert) {
     AlertArgs aa;
     std::memset(&aa, 0, sizeof(aa));
     aa.seg = o->seg; aa.seg_cap = o->seg_cap; aa.n_seg = (uint32_t)std::min<uint64_t>(o->n_seg, o->seg_cap); aa.now_ns = now_ns;
-    aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = skey; aa.idx = sidx; aa.row = rows; aa.n = n;
+    aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = sa.key; aa.idx = sa.idx; aa.win = sa.win; aa.n = sa.n;
+    if (grid) {
+      aa.grid.lay = (const CommLayout*)c->g_lay; aa.grid.rows = c->g_rows; aa.grid.cell_row = c->g_cell_row; aa.grid.wide = c->win_wide;
+      aa.grid.hdr = (const GridHeader*)c->g_hdr;
+    }
     aa.sf = c->sf; aa.topo = c->topo; aa.tile_counts = c->tile_heads; aa.alert_list = c->alert_list;
     aa.alert_ncand = c->alert_ncand; aa.alert = o->alert; aa.alert_cap = o->alert_cap; aa.cand = o->cand;
     aa.cand_cap = o->cand_cap; aa.counters = c->counters;
@@ -717,29 +586,195 @@ static ccld_status analyze_window_once(ccld_ctx* c, int64_t now_ns, ccld_window_
   }
   c->prof.collect();
   c->blame_valid = true;
-  // the order of this window serves the next analysis (windows of several batches only)
-  c->inc_ok = c->p.window_batches > 1 && !dense;
-  c->last_path = dense ? 1 : 0;
   c->chain_ready = true;
   c->last_seg = o->seg; c->last_seg_cap = o->seg_cap; c->last_n_seg = o->n_seg; c->last_n_flag = o->n_flag;
-  c->last_rec_flag = sa.rec_flag; c->last_rows = rows;
-  c->inc_sf = c->sf; c->inc_head = c->head; c->inc_count = n; c->inc_total = c->total_ingested;
+  c->last_rec_flag = sa.rec_flag; c->last_grid = grid; c->last_win = sa.win;
+  return o->status;
+}
+
+// what the statistics kernels of both placements share
+static SegArgs seg_args(ccld_ctx* c, int64_t now_ns, const ccld_window_result* o, uint32_t n) {
+  SegArgs sa;
+  std::memset(&sa, 0, sizeof(sa));
+  sa.n = n; sa.comm_size = c->topo.size;
+  sa.member_off = c->topo.member_off; sa.members_sorted = c->topo.members_sorted; sa.comm_info = c->comm_info;
+  sa.seg = o->seg; sa.seg_cap = o->seg_cap;
+  sa.lag_e = o->lag_enter; sa.lag_x = o->lag_exit; sa.flag_lag = c->flag_lag; sa.cap_n = c->cap;
+  sa.counters = c->counters;
+  sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
+  sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size;
+  sa.gcode = c->gcode; sa.range_c = c->range_c;
+  const uint32_t n_meta = c->p.window_batches + 2;
+  sa.win.row = c->win_row; sa.win.wide = c->win_wide; sa.win.meta = c->batch_meta; sa.win.n_meta = n_meta;
+  sa.win.n_batch = (uint32_t)c->batch_slot.size(); sa.win.slot0 = c->batch_slot.empty() ? 0 : c->batch_slot[0];
+  sa.win.head = (uint32_t)c->head; sa.win.cap = (uint32_t)std::max<uint64_t>(c->cap, 1);
+  sa.seqno_head = c->batch_seqno.empty() ? 0u : c->batch_seqno[0];
+  sa.arrival = c->n_buckets > 1 ? c->win_arrival : nullptr;
+  return sa;
+}
+
+// One analysis of the resident window on the grid placement.  Nothing waits for the host before the end, unless the window
+// is large enough to ask for its number of fine buckets.  *fallback is set (and nothing of the context's detection state
+// has changed) when the window turns out not to fill a grid; the caller then sorts.
+static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_result* o, bool* fallback) {
+  hipStream_t st = c->stream;
+  const uint32_t n = (uint32_t)c->count, n_ranks = c->topo.n_ranks;
+  o->path = c->dense_asked ? 1 : 0;
+  o->n_records = n;
+  SegArgs sa = seg_args(c, now_ns, o, n);
+  sa.rec_flag = o->rec_flag; sa.perm = o->perm; sa.flag_pos = c->flag_stage;
+  GridArgs d;
+  std::memset(&d, 0, sizeof(d));
+  d.win_key = c->win_key; d.win_row = c->win_row; d.head = sa.win.head; d.cap = sa.win.cap; d.n = n;
+  d.meta = c->batch_meta; d.n_meta = sa.win.n_meta; d.slot0 = sa.win.slot0; d.nb = sa.win.n_batch;
+  d.kf = c->kf; d.comm_size = c->topo.size; d.n_comms = c->topo.n_comms;
+  d.bucket_base = c->ing_base; d.n_buckets = c->n_buckets; d.bshift = c->bshift; d.range = c->comm_range;
+  d.lay = (CommLayout*)c->g_lay; d.hdr = (GridHeader*)c->g_hdr; d.piece_at = c->g_piece_at; d.piece_slot = c->g_piece_slot;
+  d.fill = c->g_fill; d.rec0 = c->g_rec0; d.nflag = c->g_nflag; d.desc = (FineDesc*)c->g_desc; d.long_list = c->g_long;
+  // cells that this window may take, and the fine buckets that they can make
+  d.cell_cap = (uint32_t)std::min<uint64_t>(c->cell_cap, (c->cap >= (4u << 20) ? (uint64_t)n + n / 5 : 2ull * n) + 4096);
+  d.fine_cap = std::min(c->fine_cap, d.cell_cap / GRID_MIN_FILL + c->topo.n_comms);
+  d.rows = c->g_rows; d.slots = o->perm ? c->g_slots : nullptr;
+  d.cell_row = c->g_cell_row; d.counters = c->counters;
+  d.blame = (uint64_t*)c->blame; d.n_blame = CCLD_BLM_NCOL * n_ranks;
+  d.host_fine = reinterpret_cast<uint32_t*>(c->h_pinned + PINNED_FINE);
+  *d.host_fine = 0;
+  c->prof.begin(CCLD_PROF_DENSE_PARTITION);
+  launch_grid_layout(st, d);
+  launch_grid_partition(st, d);
+  c->prof.split(CCLD_PROF_DENSE_PARTITION, CCLD_PROF_SEGMENTS);
+  c->sort_passes = 1;
+  uint32_t fine = d.fine_cap;
+  if (fine > FINE_BOUND) {
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_fine(c, &fine));
+  }
+  if (fine) launch_grid_stats(st, sa, d, fine, c->blame, n_ranks);
+  c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
+  FlagArgs fa;
+  std::memset(&fa, 0, sizeof(fa));
+  fa.flag_lag = c->flag_lag; fa.cap_n = c->cap; fa.n = n; fa.member_off = c->topo.member_off; fa.members_sorted = c->topo.members_sorted;
+  fa.flag_pos = c->flag_pos; fa.flag_key = c->flag_key; fa.flag_stage = c->flag_stage; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
+  fa.counters = c->counters;
+  if (fine) launch_grid_flags(st, d, fa, fine);
+  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_GROUPS);
+  return finish_analysis(c, now_ns, o, sa, true, fallback);
+}
+
+// One analysis of the resident window by sorting it.
+static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_result* o) {
+  hipStream_t st = c->stream;
+  const uint32_t n = (uint32_t)c->count, n_ranks = c->topo.n_ranks;
+  o->path = 0;
+  // 1. data errors found at ingest, and the range of the operation counters in the window
+  SegArgs sa = seg_args(c, now_ns, o, n);
+  uint64_t bits = 0, max_seq = 0, min_seq = ~0ull;
+  if (!c->batch_slot.empty()) {
+    BatchMeta* hm = (BatchMeta*)(c->h_pinned + PINNED_META);
+    HIP_TRY(hipMemcpyAsync(hm, c->batch_meta, sizeof(BatchMeta) * sa.win.n_meta, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    bool first = true;
+    for (uint32_t slot : c->batch_slot) {
+      const BatchMeta& m = hm[slot];
+      bits |= m.status;
+      if (m.n == 0) continue;
+      max_seq = std::max(max_seq, m.max_seq); min_seq = std::min(min_seq, ~m.max_inv_seq);
+      if (first) { sa.win.ref = m.ref; first = false; }
+      else if ((((uint64_t)m.ref - (uint64_t)sa.win.ref + (1ull << 42)) >> 43) != 0) sa.win.far = 1;
+    }
+  }
+  if (bits) return o->status = data_status(bits);
+  o->n_records = n;
+  HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
+  HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
+  c->ticket += 1;
+  // 2. sort by (communicator, operation counter, rank) on the significant bits only, the operation counters relative to
+  //    the smallest one of the window
+  if (min_seq > max_seq) min_seq = max_seq;
+  const int mb = c->kf.mb, cb = c->kf.cb, ws = bits_for_host(max_seq - min_seq);
+  c->sf.mb = mb; c->sf.ws = ws; c->sf.seq_base = min_seq;
+  KeySource src;
+  src.key = c->win_key; src.head = sa.win.head; src.cap = sa.win.cap;
+  src.squeeze = 1;
+  src.hi_shift = 64 - cb;                                  // 64 when there is a single communicator
+  src.lo_bits = mb + ws;
+  src.lo_mask = cb > 0 ? (((uint64_t)1 << (64 - cb)) - 1) : ~0ull;      // everything below the communicator field
+  src.lo_sub = min_seq << mb;
+  const int sorted = radix_sort_pairs(st, src, n, c->sb, mb + ws + cb, &c->prof, CCLD_PROF_SORT_HIST,
+                                      CCLD_PROF_SORT_SCAN, CCLD_PROF_SORT_SCATTER);
+  c->sort_passes = (mb + ws + cb) <= 0 ? 1 : (mb + ws + cb + SORT_RBITS - 1) / SORT_RBITS;
+  if (sorted < 0) return o->status = CCLD_E_HIP;
+  c->sorted_buf = sorted;
+
+  // 3. collectives: heads per tile, their scan, statistics, flags
+  sa.key = c->sb.key[sorted]; sa.idx = c->sb.idx[sorted]; sa.sf = c->sf;
+  sa.tile_heads = c->tile_heads; sa.rec_flag = o->rec_flag ? o->rec_flag : c->rec_flag;
+  sa.big_list = c->big_list; sa.big_cap = c->cap / 65 + 2;
+  sa.big_e = reinterpret_cast<int64_t*>(c->sb.key[1 - sorted]); sa.big_x = reinterpret_cast<int64_t*>(c->keyC);
+  const uint32_t seg_tiles = (n + SEG_TILE - 1) / SEG_TILE;
+  c->prof.begin(CCLD_PROF_SEG_HEADS);
+  launch_keys_pass(st, sa.key, n, c->sf, c->topo, c->blame, c->tile_heads, c->counters);
+  launch_scan_tiles(st, c->tile_heads, seg_tiles, &c->counters[CNT_NSEG]);
+  c->prof.split(CCLD_PROF_SEG_HEADS, CCLD_PROF_SEGMENTS);          // one event ends a timed span and begins the next
+  launch_seg_analyze(st, sa);
+  c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
+  FlagArgs fa;
+  std::memset(&fa, 0, sizeof(fa));
+  fa.key = sa.key; fa.rec_flag = sa.rec_flag; fa.flag_lag = c->flag_lag; fa.cap_n = c->cap; fa.n = n; fa.sf = c->sf;
+  fa.member_off = c->topo.member_off; fa.members_sorted = c->topo.members_sorted;
+  fa.tile_flags = c->tile_flags; fa.flag_pos = c->flag_pos; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
+  fa.counters = c->counters;
+  launch_flag_compact(st, fa);
+  if (o->perm) launch_perm(st, sa.idx, sa.arrival, n, sa.seqno_head, sa.win.head, sa.win.cap, o->perm);
+  // 4. per-rank blame
+  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_BLAME);
+  launch_blame_sums(st, fa, n_ranks, c->blame);
+  c->prof.split(CCLD_PROF_BLAME, CCLD_PROF_GROUPS);
+  bool fallback = false;
+  return finish_analysis(c, now_ns, o, sa, false, &fallback);
+}
+
+// a window without records: an all-zero blame table and the ranks in ascending order
+static ccld_status analyze_empty(ccld_ctx* c, ccld_window_result* o) {
+  hipStream_t st = c->stream;
+  const uint32_t n_ranks = c->topo.n_ranks;
+  HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
+  HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
+  c->ticket += 1;
+  launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(wait_report(c));
+  c->blame_valid = true;
   return o->status;
 }
 
 ccld_status ccld_analyze_window(ccld_ctx* c, int64_t now_ns, ccld_window_result* o) {
   if (!c || !o) return CCLD_E_NULL;
-  bool fallback = false;
+  zero_counts(o);
+  o->status = CCLD_OK;
+  o->path = 0;
+  c->chain_ready = false;
+  c->blame_valid = false;
+  if (!o->seg || o->seg_cap == 0) return o->status = CCLD_E_NULL;
+  if ((o->flag_cap && !o->flag) || (o->group_cap && !o->group) || (o->alert_cap && !o->alert) ||
+      (o->cand_cap && !o->cand))
+    return o->status = CCLD_E_NULL;
+  c->last_n = c->count;
   ccld_status s = CCLD_OK;
-  // a window of one batch is first tried by dense placement; one that does not fill a dense grid is sorted
-  if (c->dense_capable && c->batch_n.size() == 1 && c->count > 0) s = analyze_window_once(c, now_ns, o, true, &fallback);
-  else fallback = true;
-  if (fallback) s = analyze_window_once(c, now_ns, o, false, &fallback);
+  if (c->count == 0) {
+    s = analyze_empty(c, o);
+  } else {
+    bool fallback = !c->grid_capable;
+    if (c->grid_capable) {
+      c->ticket += 1;
+      s = analyze_on_grid(c, now_ns, o, &fallback);
+    }
+    if (s >= 0 && fallback) s = analyze_sorted(c, now_ns, o);
+  }
   if (s < 0) {       // an error return may have left work queued and timed spans open
     (void)hipStreamSynchronize(c->stream);
     (void)hipGetLastError();
     c->prof.abandon();
-    c->inc_ok = false;
   }
   return s;
 }

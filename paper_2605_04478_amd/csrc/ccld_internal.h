@@ -10,14 +10,6 @@
 
 namespace ccld {
 
-// One stored record: the payload the analysis gathers by sorted position (32 bytes, one
-// aligned access); communicator, sequence number and member slot live in the key.
-struct __attribute__((aligned(32))) Row {
-  int64_t t_enter, t_exit;
-  uint64_t bytes;
-  uint32_t op, pad;
-};
-
 // Key layout at ingest: comm << (64 - cb) | seq << mb | slot.  slot is the record's rank counted
 // among its communicator's members in ascending rank order, so keys order like (comm, seq, rank)
 // while the field needs only as many bits as the largest communicator has members; mb / cb are
@@ -74,11 +66,21 @@ enum { DS_UNKNOWN_COMM = 1, DS_NOT_MEMBER = 2, DS_RANGE = 4, DS_KEY_WIDTH = 8, D
        DS_SUSPECT = 64,     // snapshot grid placed without the presence bitmap: a cell still holds the fill pattern
        DS_DENSE_FALLBACK = 128 };   // the window does not fill a dense grid (far-apart counters, a round without any record): sort instead
 
-struct BatchSlot { uint64_t n; };
+// device-side header of a batch: status bits, largest operation counter and largest complement of one (i.e.
+// ~smallest counter), so that a zeroed header means "no record yet"; the time its rows are relative to, its first
+// window slot and its records
+struct BatchMeta { uint64_t status; uint64_t max_seq; uint64_t max_inv_seq; int64_t ref; uint64_t tail; uint64_t n; };
 
-// device-side header of per-batch results: status bits, largest operation counter, and the largest
-// complement of one (i.e. ~smallest counter), so that a zeroed header means "no record yet"
-struct BatchMeta { uint64_t status; uint64_t max_seq; uint64_t max_inv_seq; uint64_t pad; };
+// The window's rows (rows.h) and what it takes to read one by its slot.
+struct WindowRows {
+  const uint4* row;          // [cap] 16-byte rows
+  const int64_t* wide;       // [cap][3] t_enter, t_exit, bytes of the rows that do not fit
+  int64_t ref;               // time the rows are relative to ...
+  uint32_t far;              // ... unless the window's batches lie hours apart: then the batch's own
+  const BatchMeta* meta;     // headers of the window's batches: n_batch of them from slot0 on, modulo n_meta
+  uint32_t n_meta, slot0, n_batch;
+  uint32_t head, cap;
+};
 
 constexpr int SEG_TILE = 1024;       // sorted records owned by one workgroup of the segment kernels
 constexpr int SEG_THREADS = 256;
@@ -88,6 +90,10 @@ constexpr int RANKCOUNT_BLOCKS = 2048;
 // device counters written by kernels and read back by the host
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
        CNT_NRETAINED, CNT_DONE, CNT_COUNT = 16 };
+
+// how the device reports a counter to the host: its value with the analysis's ticket in the upper bits
+constexpr int REPORT_BITS = 48;
+constexpr uint64_t REPORT_MASK = (1ull << REPORT_BITS) - 1;
 
 }  // namespace ccld
 
@@ -106,16 +112,19 @@ struct ccld_ctx {
   std::vector<uint32_t> batch_slot;   // meta slot of each resident batch
   uint32_t next_slot;
   uint64_t* win_key;
-  ccld::Row* win_row;
-  ccld::BatchMeta* batch_meta;        // [window_batches + 1]
+  uint4* win_row;                     // [cap] 16-byte rows (rows.h)
+  int64_t* win_wide;                  // [cap][3] values of the rows that do not fit
+  uint32_t* win_arrival;              // [cap] arrival number of each slot (batches placed by bucket)
+  ccld::BatchMeta* batch_meta;        // [window_batches + 2]
   std::vector<uint32_t> batch_seqno;  // arrival number of each resident batch's first record
   uint64_t total_ingested;
   uint32_t* ing_table;                // [n_buckets][INGEST_BLOCKS]
-  uint32_t* ing_base;                 // [n_buckets + 1]
+  uint32_t* ing_base;                 // [window_batches + 2][n_buckets + 1]
+  uint32_t* ing_done;                 // zero between launches
   uint32_t n_buckets; int bshift;
   // sort
   ccld::SortBuffers sb;               // main sort
-  uint64_t* keyC; uint32_t* idxC;     // third pair for the small sorts
+  uint64_t* keyC;                     // third array of keys
   uint32_t* table2; uint32_t* totals2;
   // analysis scratch
   uint32_t* tile_heads;               // [seg tiles + 1]
@@ -124,7 +133,7 @@ struct ccld_ctx {
   uint32_t* flag_pos;                 // [cap] sorted position of the k-th flagged record
   int64_t* flag_lag;                  // [2][cap]
   uint32_t* big_list;                 // [cap / 65 + 2][3]  (segment ordinal, first position, length) of the collectives over 64 records
-  int64_t* big_ex;                    // [2][cap]
+  uint64_t* flag_key;                 // [cap] grid placement: table row << 32 | member slot of the k-th flagged record
   int64_t* range_c;                   // [cap] T_max - T_min of every usable collective
   int64_t* blame;                     // [CCLD_BLM_NCOL][n_ranks]
   uint32_t* blame_list;               // [2][n_ranks] flagged ranks, then the others, each ascending (many ranks only)
@@ -142,8 +151,7 @@ struct ccld_ctx {
   uint32_t max_comm_size;             // members of the largest communicator
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging
-  uint64_t ticket;                    // number of the latest report that the device was asked for (h_pinned[CNT_COUNT])
-  hipEvent_t ev_heads;                // marks the early readback of the dense layout
+  uint64_t ticket;                    // number of the latest report that the device was asked for
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location
@@ -160,28 +168,30 @@ struct ccld_ctx {
   uint64_t* f_last;                   // [n_members][CCLD_FRAME_CHANNELS][2] remembered (operation counter, sent | recv << 32) per member and channel
   uint32_t* f_seen;                   // [n_ranks / 32 + 1] ranks that delivered a frame in the current call
   uint8_t* h_stage;                   // [snap_cap * 32] device staging for host-resident snapshots
-  // dense placement (single-batch windows)
-  bool dense_capable;                 // window_batches == 1, every communicator fits a fine bucket, few enough communicators
-  uint64_t* comm_range;               // [n_comms][2] per communicator of the latest batch: largest counter, largest complement
-  void* d_lay;                        // [n_comms + 1] CommLayout
-  uint32_t* d_hdr;                    // [DH_COUNT]
-  uint32_t* d_fill;                   // [fine_cap + 2]
-  ccld::Row* d_rows;                  // [fine_cap * DENSE_STRIDE]
-  void* d_desc;                       // [fine_cap] FineDesc
-  uint32_t fine_cap;
-  int last_path;                      // 1: the last analysis used the dense placement
+  // grid placement (grid.h)
+  bool grid_capable;                  // communicators fit a fine bucket, few enough of them, few enough batches
+  bool grid_over_sort;                // its arrays lie over the sort buffers
+  bool dense_asked;                   // CCLD_PLACEMENT_DENSE and windows of one batch: results name the path taken
+  uint64_t* comm_range;               // [window_batches + 2][n_comms][2] per batch and communicator: largest counter, largest complement
+  void* g_lay;                        // [n_comms + 1] CommLayout
+  void* g_hdr;                        // GridHeader
+  void* g_desc;                       // [fine_cap] FineDesc
+  uint32_t *g_piece_at, *g_piece_slot;
+  uint32_t *g_fill, *g_rec0, *g_nflag, *g_long;   // [fine_cap + 1]
+  uint4* g_rows;                      // [cell_cap]
+  uint32_t* g_slots;                  // [cell_cap]
+  uint16_t* g_cell_row;               // [cell_cap]
+  uint32_t* flag_stage;               // [cap]
+  uint32_t fine_cap, cell_cap;
   // what ccld_flag_chains needs of the most recent analysis
   bool chain_ready;                   // the sorted order, flag positions and lags of that analysis are still in the workspace
   const int64_t* last_seg; uint64_t last_seg_cap, last_n_seg, last_n_flag;
   const uint8_t* last_rec_flag;
-  const ccld::Row* last_rows;         // payload rows that the sorted row indices address
+  bool last_grid;                     // the analysis ran on the grid placement
+  ccld::WindowRows last_win;          // the window's rows
   uint32_t* chain_first;              // [n_comms + 2] first table row of each communicator
   // last analysis
   int sorted_buf;                     // which ping-pong buffer holds the sorted window
-  // the order of the last analysed window, kept for the next analysis of a window of several batches
-  bool inc_ok;                        // sb.key/idx[sorted_buf] hold it, in format inc_sf
-  ccld::SqueezedFormat inc_sf;
-  uint64_t inc_head, inc_count, inc_total;   // that window's first slot, records, and total_ingested at the time
   uint64_t last_n;
   ccld::SqueezedFormat sf;
   bool blame_valid;

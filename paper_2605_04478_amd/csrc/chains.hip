@@ -8,8 +8,8 @@
 #include <cstring>
 
 #include "ccld_internal.h"
-#include "device_utils.h"
-#include "window_kernels.h"
+#include "grid.h"
+#include "rows.h"
 
 using namespace ccld;
 
@@ -19,8 +19,11 @@ constexpr i64 T_INFLIGHT = INT64_MAX;
 
 struct ChainArgs {
   const u64* key;            // squeezed keys in (communicator, counter, rank) order
-  const u32* idx;            // payload row of each sorted record
-  const Row* row;
+  const u32* idx;            // window slot of each sorted record
+  WindowRows win;
+  GridView grid;             // the window's records on the grid placement
+  const u64* flag_key;       // grid placement: table row << 32 | member slot of the k-th flag
+  const u32* flag_stage;     // grid placement: cell | kind << 16 of the k-th flag at flag_pos[k]
   SqueezedFormat sf;
   DeviceTopology T;
   const i64* seg;            // the analysis's collective table
@@ -29,7 +32,7 @@ struct ChainArgs {
   const uint8_t* rec_flag;   // by sorted position
   const i64* flag_lag;       // [2][cap_n] lags of the flagged records by sorted position
   u64 cap_n;
-  const u32* flag_pos;       // sorted position of the k-th flag
+  const u32* flag_pos;       // sorted position of the k-th flag; on the grid placement where its lags are
   u32 n_flag;
   u32* comm_first;           // [n_comms + 1] first table row of each communicator
   u32* parent;               // [n_flag] parent flag or ~0
@@ -45,29 +48,63 @@ __global__ __launch_bounds__(256) void k_chain_comm_rows(ChainArgs a) {
   a.comm_first[c] = lo;
 }
 
-// sorted position of the record of member slot `slot` in table row `row`, or ~0
-__device__ __forceinline__ u32 chain_record_of(const ChainArgs& a, u32 row, u32 slot, u32 size) {
+// The record of member slot `slot` in table row `row`: its times, or false if there is none.  *pos: its sorted
+// position, or its row among the partitioned ones.
+template <bool GRID>
+__device__ __forceinline__ bool chain_record_of(const ChainArgs& a, u32 comm, u32 row, u32 slot, u32 size, u32* pos, i64* te, i64* tx) {
+  if (GRID) {
+    const CommLayout L = a.grid.lay[comm];
+    const u32 k = row - L.seg_base, fr = k / L.rpb;
+    const u32 li = a.grid.cell_row[L.cell_base + k * L.size + slot];
+    if (li == GRID_EMPTY) return false;
+    *pos = L.cell_base + fr * L.rpb * L.size + li;
+    const Rec r = unpack_row(a.grid.rows[*pos], a.grid.hdr->ref, a.grid.wide);
+    *te = r.t_enter; *tx = r.t_exit;
+    return true;
+  }
   const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + row];
-  if (n == size) return first + slot;
-  const u64 mmask = ((u64)1 << a.sf.mb) - 1;
-  u32 lo = first, hi = first + n;
-  while (lo < hi) { const u32 m = (lo + hi) >> 1; if ((u32)(a.key[m] & mmask) < slot) lo = m + 1; else hi = m; }
-  return (lo < first + n && (u32)(a.key[lo] & mmask) == slot) ? lo : ~0u;
+  u32 p = first + slot;
+  if (n != size) {
+    const u64 mmask = ((u64)1 << a.sf.mb) - 1;
+    u32 lo = first, hi = first + n;
+    while (lo < hi) { const u32 m = (lo + hi) >> 1; if ((u32)(a.key[m] & mmask) < slot) lo = m + 1; else hi = m; }
+    if (lo >= first + n || (u32)(a.key[lo] & mmask) != slot) return false;
+    p = lo;
+  }
+  *pos = p;
+  const Rec r = load_rec(a.win, a.idx[p]);
+  *te = r.t_enter; *tx = r.t_exit;
+  return true;
+}
+struct ChainFlag { u32 comm, slot, row, kind; };       // row: of the collective table, grid placement only
+template <bool GRID>
+__device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
+  ChainFlag f;
+  if (GRID) {
+    const u64 w = a.flag_key[k];
+    f.row = (u32)(w >> 32); f.slot = (u32)w; f.kind = a.flag_stage[a.flag_pos[k]] >> 16;
+    f.comm = (u32)a.seg[(u64)CCLD_SEG_COMM * a.seg_cap + f.row];
+  } else {
+    const u32 j = a.flag_pos[k];
+    const u64 key = a.key[j];
+    f.row = 0; f.slot = (u32)(key & (((u64)1 << a.sf.mb) - 1)); f.comm = (u32)(key >> (a.sf.mb + a.sf.ws)); f.kind = a.rec_flag[j];
+  }
+  return f;
 }
 
 // One thread per flag: the parent of a late entry.
+template <bool GRID>
 __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
   if (k >= a.n_flag) return;
-  const u32 j = a.flag_pos[k];
+  const ChainFlag F = chain_flag<GRID>(a, k);
   u32 parent = ~0u;
-  if (a.rec_flag[j] & CCLD_FLAG_LATE_ENTER) {
-    const int mb = a.sf.mb;
-    const u64 mmask = ((u64)1 << mb) - 1;
-    const u64 key = a.key[j];
-    const u32 comm = (u32)(key >> (mb + a.sf.ws));
-    const u32 r = a.T.members_sorted[a.T.member_off[comm] + (u32)(key & mmask)];
-    const i64 t = a.row[a.idx[j]].t_enter;
+  if (F.kind & CCLD_FLAG_LATE_ENTER) {
+    const u32 r = a.T.members_sorted[a.T.member_off[F.comm] + F.slot];
+    u32 own = a.flag_pos[k];
+    i64 t, own_exit;
+    if (GRID) { if (!chain_record_of<GRID>(a, F.comm, F.row, F.slot, a.T.size[F.comm], &own, &t, &own_exit)) t = 0; }
+    else t = load_rec(a.win, a.idx[own]).t_enter;
     // the operation this rank ran just before: per communicator of the rank the last round that the rank left
     // before t (its rounds are in time order; a round without a record of the rank is skipped), then the latest
     bool have = false;
@@ -76,49 +113,55 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
     for (u32 q = a.T.rank_comm_off[r]; q < a.T.rank_comm_off[r + 1]; ++q) {
       const u32 c2 = a.T.rank_comms[q], slot2 = a.T.rank_slots[q], size2 = a.T.size[c2];
       u32 lo = a.comm_first[c2], hi = a.comm_first[c2 + 1];
-      const u32 row_lo = lo;
       bool found = false;
       u32 f_row = 0;
       i64 f_exit = 0, f_enter = 0;
       while (lo < hi) {
         const u32 mid = (lo + hi) >> 1;
         // the nearest round at or below mid in which the rank has a record
-        u32 probe = mid, pos = ~0u;
+        u32 probe = mid, pos = 0;
+        i64 te = 0, tx = 0;
+        bool here;
         while (true) {
-          pos = chain_record_of(a, probe, slot2, size2);
-          if (pos != ~0u || probe == lo) break;
+          here = chain_record_of<GRID>(a, c2, probe, slot2, size2, &pos, &te, &tx);
+          if (here || probe == lo) break;
           --probe;
         }
-        bool ok = false;
-        i64 te = 0, tx = 0;
-        if (pos != ~0u) {
-          const Row rw = a.row[a.idx[pos]];
-          te = rw.t_enter; tx = rw.t_exit;
-          ok = pos != j && tx != T_INFLIGHT && tx <= t;
-        }
+        const bool ok = here && pos != own && tx != T_INFLIGHT && tx <= t;
         if (ok) { found = true; f_row = probe; f_exit = tx; f_enter = te; lo = mid + 1; }
-        else if (pos == ~0u) lo = mid + 1;       // no record of the rank in [lo, mid]
+        else if (!here) lo = mid + 1;            // no record of the rank in [lo, mid]
         else hi = probe;
       }
-      (void)row_lo;
       if (!found) continue;
       const bool better = !have || f_exit > b_exit || (f_exit == b_exit && (f_enter > b_enter || (f_enter == b_enter && c2 > b_comm)));
       if (better) { have = true; b_exit = f_exit; b_enter = f_enter; b_comm = c2; b_row = f_row; }
     }
     if (have) {
       // who ended it late: the late entry with the largest lag (ties: smallest rank = first in rank order)
-      const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + b_row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + b_row];
-      u32 m_pos = ~0u;
+      bool any = false;
       i64 m_lag = 0;
-      for (u32 p = first; p < first + n; ++p)
-        if (a.rec_flag[p] & CCLD_FLAG_LATE_ENTER) {
-          const i64 lag = a.flag_lag[p];
-          if (m_pos == ~0u || lag > m_lag) { m_pos = p; m_lag = lag; }
+      if (GRID) {
+        u32 lo = 0, hi = a.n_flag;               // the collective's first flag
+        while (lo < hi) { const u32 m = (lo + hi) >> 1; if ((u32)(a.flag_key[m] >> 32) < b_row) lo = m + 1; else hi = m; }
+        for (; lo < a.n_flag && (u32)(a.flag_key[lo] >> 32) == b_row; ++lo) {
+          const u32 at = a.flag_pos[lo];
+          if (!((a.flag_stage[at] >> 16) & CCLD_FLAG_LATE_ENTER)) continue;
+          const i64 lag = a.flag_lag[at];
+          if (!any || lag > m_lag) { any = true; parent = lo; m_lag = lag; }
         }
-      if (m_pos != ~0u) {
-        u32 lo = 0, hi = a.n_flag;
-        while (lo < hi) { const u32 m = (lo + hi) >> 1; if (a.flag_pos[m] < m_pos) lo = m + 1; else hi = m; }
-        parent = lo;
+      } else {
+        const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + b_row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + b_row];
+        u32 m_pos = 0;
+        for (u32 p = first; p < first + n; ++p)
+          if (a.rec_flag[p] & CCLD_FLAG_LATE_ENTER) {
+            const i64 lag = a.flag_lag[p];
+            if (!any || lag > m_lag) { any = true; m_pos = p; m_lag = lag; }
+          }
+        if (any) {
+          u32 lo = 0, hi = a.n_flag;
+          while (lo < hi) { const u32 m = (lo + hi) >> 1; if (a.flag_pos[m] < m_pos) lo = m + 1; else hi = m; }
+          parent = lo;
+        }
       }
     }
   }
@@ -152,15 +195,14 @@ __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool o
     todo &= ~same;
   }
 }
+template <bool GRID>
 __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, const u32* anc, const u32* dist, i64* chain, u64 chain_cap,
                                                     i64* per_rank) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
   if (k >= a.n_flag) return;
-  const int mb = a.sf.mb;
-  const u64 mmask = ((u64)1 << mb) - 1;
   auto rank_at = [&](u32 flag) -> u32 {
-    const u64 key = a.key[a.flag_pos[flag]];
-    return a.T.members_sorted[a.T.member_off[(u32)(key >> (mb + a.sf.ws))] + (u32)(key & mmask)];
+    const ChainFlag f = chain_flag<GRID>(a, flag);
+    return a.T.members_sorted[a.T.member_off[f.comm] + f.slot];
   };
   const u32 root = anc[k], p = a.parent[k];
   const u32 root_rank = rank_at(root);
@@ -171,7 +213,7 @@ __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, const u32* anc,
     chain[(u64)CCLD_CHN_DEPTH * chain_cap + k] = (i64)dist[k];
   }
   if (per_rank) {
-    const bool on = (a.rec_flag[a.flag_pos[k]] & CCLD_FLAG_LATE_ENTER) != 0;
+    const bool on = (chain_flag<GRID>(a, k).kind & CCLD_FLAG_LATE_ENTER) != 0;
     const u32 n_ranks = a.T.n_ranks;
     const u32 mine = on ? rank_at(k) : 0u;
     wave_count_by_index(per_rank + (u64)CCLD_CHR_ROOT_ENTRIES * n_ranks, mine, on && p == ~0u);
@@ -201,16 +243,21 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
   if (n_flag) {
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.key = c->sb.key[c->sorted_buf]; a.idx = c->sb.idx[c->sorted_buf]; a.row = c->last_rows; a.sf = c->sf; a.T = c->topo;
+    const bool grid = c->last_grid;
+    a.key = c->sb.key[c->sorted_buf]; a.idx = c->sb.idx[c->sorted_buf]; a.win = c->last_win; a.sf = c->sf; a.T = c->topo;
+    a.grid.lay = (const CommLayout*)c->g_lay; a.grid.rows = c->g_rows; a.grid.cell_row = c->g_cell_row; a.grid.wide = c->win_wide;
+    a.grid.hdr = (const GridHeader*)c->g_hdr;
+    a.flag_key = c->flag_key; a.flag_stage = c->flag_stage;
     a.seg = w->seg; a.seg_cap = w->seg_cap; a.n_seg = (uint32_t)w->n_seg;
     a.rec_flag = c->last_rec_flag; a.flag_lag = c->flag_lag; a.cap_n = c->cap; a.flag_pos = c->flag_pos; a.n_flag = n_flag;
     a.comm_first = c->chain_first; a.parent = c->chain_parent;
-    // scratch that the analysis no longer needs: the third sort buffer pair and the alert candidate counts
-    uint32_t* anc[2] = {reinterpret_cast<uint32_t*>(c->keyC), reinterpret_cast<uint32_t*>(c->keyC) + n_flag};
-    uint32_t* dist[2] = {c->idxC, c->alert_ncand};
+    // scratch that the analysis no longer needs
+    uint32_t* anc[2] = {c->alert_list, c->alert_ncand};
+    uint32_t* dist[2] = {reinterpret_cast<uint32_t*>(c->range_c), reinterpret_cast<uint32_t*>(c->range_c) + n_flag};
     const uint32_t blocks = (n_flag + 255) / 256;
     hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_chain_parent, dim3(blocks), dim3(256), 0, st, a);
+    if (grid) hipLaunchKernelGGL(k_chain_parent<true>, dim3(blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(k_chain_parent<false>, dim3(blocks), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_chain_init, dim3(blocks), dim3(256), 0, st, (const u32*)a.parent, n_flag, anc[0], dist[0]);
     int cur = 0;
     for (uint64_t reach = 1; reach < n_flag; reach *= 2) {        // after i rounds every flag has looked 2^i links up
@@ -218,8 +265,12 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
                          anc[1 - cur], dist[1 - cur]);
       cur = 1 - cur;
     }
-    hipLaunchKernelGGL(k_chain_emit, dim3(blocks), dim3(256), 0, st, a, (const u32*)anc[cur], (const u32*)dist[cur], o->chain,
-                       o->chain_cap, o->per_rank);
+    if (grid)
+      hipLaunchKernelGGL(k_chain_emit<true>, dim3(blocks), dim3(256), 0, st, a, (const u32*)anc[cur], (const u32*)dist[cur], o->chain,
+                         o->chain_cap, o->per_rank);
+    else
+      hipLaunchKernelGGL(k_chain_emit<false>, dim3(blocks), dim3(256), 0, st, a, (const u32*)anc[cur], (const u32*)dist[cur], o->chain,
+                         o->chain_cap, o->per_rank);
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(st));

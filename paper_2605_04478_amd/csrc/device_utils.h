@@ -77,6 +77,21 @@ __device__ __forceinline__ u32 block_exclusive_sum(u32 v, u32* s_wave, u32* tota
   return base + inc - v;
 }
 
+// Words that workgroups of one launch hand to one another: stored and loaded past the caches that are not coherent
+// between the XCDs, so that no cache has to be written back for them.
+__device__ __forceinline__ void store_agent(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ u32 load_agent(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// True in the last of `blocks` workgroups to get here.  What the others stored with store_agent or added with atomics
+// before is there for load_agent: the barrier waits until a wavefront's stores are done.  (A release fence in every thread
+// would write the L2 back once per wavefront: 40 us over the 4,096 wavefronts of a counting pass.)  s_last: a word of LDS.
+__device__ __forceinline__ bool last_block(u32* done, u32 blocks, u32* s_last) {
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) *s_last = atomicAdd(done, 1u) + 1 == blocks;
+  __syncthreads();
+  return *s_last != 0;
+}
+
 __device__ __forceinline__ int bits_for(u64 max_value) {   // bits needed to store 0..max_value
   return max_value == 0 ? 0 : 64 - __clzll((long long)max_value);
 }

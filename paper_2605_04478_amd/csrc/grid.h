@@ -1,0 +1,98 @@
+// The grid placement of a window.  Every rank bumps the same operation counter per communicator (the Trace ID of
+// Section 5.1), so (communicator, counter - smallest counter, member slot) is a grid in which the cell of every record
+// follows from its key.  The grid is cut into fine buckets of whole collectives that fit LDS; one partition pass
+// moves every 16-byte row into its fine bucket, and the statistics kernel places a bucket's rows in LDS by cell and
+// reads the collectives in (communicator, counter, rank) order.  Windows that do not fill such a grid (counters far
+// apart, rounds without any record, communicators larger than a fine bucket) are sorted instead.
+#pragma once
+#include "ccld_internal.h"
+#include "window_kernels.h"
+
+namespace ccld {
+
+constexpr uint32_t GRID_B = 2048;            // grid cells (= LDS cells of the statistics kernels) per fine bucket
+constexpr uint32_t GRID_MIN_FILL = 1025;     // a full fine bucket holds at least this many cells (whole rounds of <= GRID_B members)
+constexpr uint32_t GRID_SPAN = 4096;         // fine buckets of one coarse bucket that a partition workgroup addresses
+constexpr uint32_t GRID_ONE_BUCKET = 3500;   // windows of no more fine buckets are partitioned in one go, without communicator buckets
+constexpr uint32_t GRID_TARGET = 600;        // fine buckets per communicator bucket of the others
+constexpr uint32_t GRID_MAX_COMMS = INGEST_RANGE_COMMS;
+constexpr uint32_t GRID_MAX_BATCHES = 256;   // batches of a window whose batches are placed by communicator bucket
+constexpr uint32_t GRID_MAX_PIECES = 4096;   // (coarse bucket, batch) pairs of such a window
+
+// Per communicator: where its part of the grid lies.  Rounds are numbered from the window's smallest
+// operation counter of the communicator; rpb rounds make one fine bucket.
+struct __attribute__((aligned(16))) CommLayout {
+  uint64_t seq_min;        // smallest operation counter in the window
+  uint32_t fb_base;        // first fine bucket
+  uint32_t rpb;            // rounds per fine bucket: GRID_B / members
+  uint32_t rounds;         // largest - smallest operation counter + 1 (0: no record)
+  uint32_t seg_base;       // row of the collective table of the first round
+  uint32_t cell_base;      // first cell
+  uint32_t size;           // members
+};
+
+// One fine bucket (written by the partition kernel).
+struct __attribute__((aligned(16))) FineDesc {
+  uint32_t comm, size;     // communicator and its members
+  uint32_t K;              // collectives (rounds) in the bucket
+  uint32_t srow0;          // row of the collective table of the bucket's first round
+  uint32_t cell0;          // first cell, and first row of the partitioned rows
+  uint32_t pad;
+  uint64_t seq0;           // operation counter of the first round
+};
+
+// device-side header of the layout
+struct GridHeader {
+  uint32_t feasible, n_fine, n_seg, n_pieces;
+  int64_t ref;             // time the window's rows are relative to
+  uint32_t n_long, done;   // fine buckets of communicators of more than 64 members; workgroups that have finished
+};
+
+struct GridArgs {
+  // window: n records, nb batches whose headers start at slot0 (modulo n_meta)
+  const uint64_t* win_key;
+  const uint4* win_row;
+  uint32_t head, cap, n;
+  const BatchMeta* meta;
+  uint32_t n_meta, slot0, nb;
+  KeyFormat kf;
+  const uint32_t* comm_size;
+  uint32_t n_comms;
+  // coarse buckets (communicator >> bshift) as ingest placed them: first record of each bucket in every batch
+  const uint32_t* bucket_base;   // [n_meta][n_buckets + 1]
+  uint32_t n_buckets;
+  int bshift;
+  // counter ranges per batch and communicator: largest counter, largest complement (zero pair: no record)
+  const uint64_t* range;         // [n_meta][n_comms][2]
+  // layout
+  CommLayout* lay;               // [n_comms + 1]
+  GridHeader* hdr;
+  uint32_t* piece_at;            // [pieces + 1] records before each (coarse bucket, batch) piece, bucket by bucket
+  uint32_t* piece_slot;          // [pieces] its first window slot
+  // fine buckets
+  uint32_t* fill;                // [fine_cap + 1] records of each, then (rec0) the records before it
+  uint32_t* rec0;                // [fine_cap + 1]
+  uint32_t* nflag;               // [fine_cap + 1] flagged records of each
+  FineDesc* desc;                // [fine_cap]
+  uint32_t* long_list;           // [fine_cap] fine buckets of communicators of more than 64 members
+  uint32_t fine_cap, cell_cap;
+  uint4* rows;                   // [cell_cap] partitioned rows
+  uint32_t* slots;               // [cell_cap] their window slots, or null: not wanted
+  uint16_t* cell_row;            // [cell_cap] row of each cell inside its bucket, GRID_EMPTY: no record
+  uint64_t* counters;
+  uint64_t* blame;               // cleared here: [n_blame] words
+  uint32_t n_blame;
+  // pinned host words: 1 + fine buckets once the layout is known (0x80000000: it is not feasible)
+  uint32_t* host_fine;
+};
+constexpr uint32_t GRID_EMPTY = 0xFFFFu;
+
+void launch_grid_layout(hipStream_t st, const GridArgs& d);
+void launch_grid_partition(hipStream_t st, const GridArgs& d);
+
+// statistics of every collective (segments.hip); fine_bound: no fewer than the layout's fine buckets
+void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks);
+
+void launch_grid_flags(hipStream_t st, const GridArgs& d, const FlagArgs& a, uint32_t fine_bound);      // window.hip
+
+}  // namespace ccld

@@ -1,0 +1,351 @@
+// Grid placement for gfx950: the layout of the (communicator, operation counter, member slot) grid from the
+// window's counter ranges, and the partition pass that moves every payload row into the fine bucket of its cell.
+#include <algorithm>
+
+#include "grid.h"
+#include "rows.h"
+
+namespace ccld {
+
+// ---- layout ------------------------------------------------------------------------------------------
+// One workgroup: data errors of the batches; per communicator the rounds in the window, its fine buckets, cells and rows
+// of the collective table (exclusive scans over the communicators); the pieces of the window that hold each coarse
+// bucket.  The layout is infeasible (the host then sorts) when the grid has more cells or rounds than the buffers and
+// the records allow (counters that are far apart), when a coarse bucket spans more fine buckets than a partition
+// workgroup addresses, or when the batches lie so far apart that no single time serves all rows.
+// Bound by the latency of its few dependent loads: 4 to 8 us at 1,088 to 3,200 communicators.
+__global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
+  __shared__ u32 s_wave[1024 / CCLD_WAVE];
+  __shared__ u32 s_bad, s_any;
+  __shared__ unsigned long long s_status;
+  const u32 tid = threadIdx.x;
+  if (tid == 0) { s_bad = 0; s_status = 0; s_any = 0xFFFFFFFFu; }
+  if (tid < CNT_COUNT) d.counters[tid] = 0;
+  __syncthreads();
+  auto meta_of = [&](u32 i) -> const BatchMeta& { return d.meta[(d.slot0 + i) % d.n_meta]; };
+  for (u32 i = tid; i < d.nb; i += 1024) {
+    const BatchMeta& m = meta_of(i);
+    if (m.status) atomicOr(&s_status, (unsigned long long)m.status);
+    if (m.n) atomicMin(&s_any, i);
+  }
+  __syncthreads();
+  bool bad = false;
+  const i64 ref = meta_of(s_any < d.nb ? s_any : 0).ref;
+  for (u32 i = tid; i < d.nb; i += 1024) {
+    const BatchMeta& m = meta_of(i);
+    const u64 off = (u64)m.ref - (u64)ref + ((u64)1 << 42);
+    if (m.n && (off >> 43) != 0) bad = true;
+  }
+  // consecutive communicators per thread: all their counter ranges are loaded at once, one scan orders them
+  constexpr u32 PER = (GRID_MAX_COMMS + 1023) / 1024;
+  const u32 per = (d.n_comms + 1023) / 1024, c0 = tid * per;        // per <= PER
+  u64 mx[PER], inv[PER];
+  u32 size[PER];
+#pragma unroll
+  for (u32 k = 0; k < PER; ++k) {
+    mx[k] = 0; inv[k] = 0; size[k] = 0;
+    if (k < per && c0 + k < d.n_comms) size[k] = d.comm_size[c0 + k];
+  }
+  u32 m = d.slot0;
+#pragma unroll 2
+  for (u32 i = 0; i < d.nb; ++i) {
+    const ulonglong2* __restrict__ rng = reinterpret_cast<const ulonglong2*>(d.range) + (u64)m * d.n_comms;
+    m = m + 1 == d.n_meta ? 0 : m + 1;
+#pragma unroll
+    for (u32 k = 0; k < PER; ++k)
+      if (k < per && c0 + k < d.n_comms) {
+        const ulonglong2 r = rng[c0 + k];
+        mx[k] = r.x > mx[k] ? r.x : mx[k]; inv[k] = r.y > inv[k] ? r.y : inv[k];
+      }
+  }
+  u32 rounds[PER], nfb_sum = 0, rounds_sum = 0;
+  u64 cells_sum = 0;
+#pragma unroll
+  for (u32 k = 0; k < PER; ++k) {
+    rounds[k] = 0;
+    if (!(mx[k] | inv[k])) continue;
+    const u64 r = mx[k] - ~inv[k] + 1;                 // largest >= smallest; r == 0 only for the full 64-bit range
+    if (r == 0 || r > 0x7FFFFFFFull || r * size[k] > (u64)d.cell_cap) { bad = true; continue; }
+    rounds[k] = (u32)r;
+    const u32 rpb = GRID_B / size[k];                  // size <= GRID_B: the host checked
+    nfb_sum += (rounds[k] + rpb - 1) / rpb; rounds_sum += rounds[k]; cells_sum += (u64)rounds[k] * size[k];
+  }
+  // the sum of the cells can pass 32 bits, so it is taken in halves (where it does, the layout is refused, and where it
+  // does not, the sums of buckets and rounds do not either)
+  u32 fb_total, seg_total, tl, th;
+  u32 fb = block_exclusive_sum<1024>(nfb_sum, s_wave, &fb_total);
+  u32 seg = block_exclusive_sum<1024>(rounds_sum, s_wave, &seg_total);
+  const u32 el = block_exclusive_sum<1024>((u32)cells_sum & 0xFFFFu, s_wave, &tl);
+  const u32 eh = block_exclusive_sum<1024>((u32)(cells_sum >> 16), s_wave, &th);
+  u64 cell = (u64)el + ((u64)eh << 16);
+  const u64 cell_total = (u64)tl + ((u64)th << 16);
+#pragma unroll
+  for (u32 k = 0; k < PER; ++k) {
+    if (k >= per || c0 + k >= d.n_comms) continue;
+    const u32 rpb = GRID_B / size[k];
+    CommLayout L;
+    L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.fb_base = fb; L.rpb = rpb; L.rounds = rounds[k]; L.seg_base = seg;
+    L.cell_base = (u32)cell; L.size = size[k];
+    d.lay[c0 + k] = L;
+    fb += (rounds[k] + rpb - 1) / rpb; seg += rounds[k]; cell += (u64)rounds[k] * size[k];
+  }
+  // more rounds than records means a round without any record: the sort handles such windows
+  if (cell_total > d.cell_cap || fb_total > d.fine_cap || seg_total > d.n) bad = true;        // uniform
+  const u64 fb_carry = fb_total, seg_carry = seg_total, cell_carry = cell_total;
+  if (tid == 0) {
+    CommLayout L;
+    L.seq_min = 0; L.fb_base = (u32)(fb_carry > d.fine_cap ? d.fine_cap : fb_carry); L.rpb = 1; L.rounds = 0;
+    L.seg_base = (u32)seg_carry; L.cell_base = (u32)cell_carry; L.size = 1;
+    d.lay[d.n_comms] = L;
+  }
+  if (bad) atomicOr(&s_bad, 1u);
+  __threadfence_block();
+  __syncthreads();
+  if (!s_bad) {
+    bool wide = false;
+    for (u32 b = tid; b < d.n_buckets; b += 1024) {
+      u64 c0 = (u64)b << d.bshift, c1 = (u64)(b + 1) << d.bshift;
+      if (c0 > d.n_comms) c0 = d.n_comms;
+      if (c1 > d.n_comms) c1 = d.n_comms;
+      if (d.lay[c1].fb_base - d.lay[c0].fb_base > GRID_SPAN) wide = true;
+    }
+    if (wide) atomicOr(&s_bad, 1u);
+  }
+  __syncthreads();
+  const bool ok = s_bad == 0 && s_status == 0;
+  const u32 n_fine = ok ? (u32)fb_carry : 0u;
+  // pieces: a window placed without buckets is one contiguous stretch of slots; otherwise every batch holds its own
+  // stretch of every bucket
+  u32 n_pieces = 1;
+  if (d.n_buckets == 1) {
+    if (tid == 0) { d.piece_at[0] = 0; d.piece_at[1] = d.n; d.piece_slot[0] = d.head; }
+  } else {
+    n_pieces = d.n_buckets * d.nb;
+    u32 carry = 0;
+    for (u32 base = 0; base < n_pieces; base += 1024) {
+      const u32 k = base + tid;
+      u32 cnt = 0, slot = 0;
+      if (k < n_pieces) {
+        const u32 b = k / d.nb, i = k % d.nb, m = (d.slot0 + i) % d.n_meta;
+        const u32* bb = d.bucket_base + (u64)m * (d.n_buckets + 1);
+        if (d.meta[m].n) {
+          cnt = bb[b + 1] - bb[b];
+          const u64 p = d.meta[m].tail + bb[b];
+          slot = (u32)(p >= d.cap ? p - d.cap : p);
+        }
+      }
+      u32 tot;
+      const u32 ex = block_exclusive_sum<1024>(cnt, s_wave, &tot);
+      if (k < n_pieces) { d.piece_at[k] = carry + ex; d.piece_slot[k] = slot; }
+      carry += tot;
+    }
+    if (tid == 0) d.piece_at[n_pieces] = carry;
+  }
+  for (u32 f = tid; f <= n_fine; f += 1024) d.fill[f] = 0;
+  if (tid == 0) {
+    GridHeader h;
+    h.feasible = ok ? 1u : 0u; h.n_fine = n_fine; h.n_seg = ok ? (u32)seg_carry : 0u; h.n_pieces = n_pieces; h.ref = ref;
+    h.n_long = 0; h.done = 0;
+    *d.hdr = h;
+    if (s_status) d.counters[CNT_STATUS] = s_status;
+    else if (!ok) d.counters[CNT_STATUS] = DS_DENSE_FALLBACK;
+    d.counters[CNT_NSEG] = ok ? seg_carry : 0;
+    __hip_atomic_store(d.host_fine, ok ? n_fine + 1 : 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+void launch_grid_layout(hipStream_t st, const GridArgs& d) {
+  hipLaunchKernelGGL(k_grid_layout, dim3(1), dim3(1024), 0, st, d);
+}
+
+// ---- partition --------------------------------------------------------------------------------------
+// A workgroup takes one slice of the window, bucket by bucket: PART_CHUNK records per round, each counted into its fine
+// bucket in LDS; the round's share of every fine bucket is reserved with one atomic, the rows are staged in LDS in
+// (bucket, rank) order and leave with consecutive lanes on consecutive 16-byte pieces.  Pieces of a line that the round
+// writes completely leave with the streaming hint, which keeps them from displacing the partially written lines at the
+// buckets' frontiers from the L2.  A bucket takes as many rows as it has cells; more can only be duplicate keys.
+// Rounds of 4,096 records: the longest runs that fit LDS beside the tables of GRID_SPAN buckets.
+constexpr u32 PART_THREADS = 1024, PART_U = 4, PART_CHUNK = PART_THREADS * PART_U;
+constexpr u32 PART_BLOCKS = 256;
+
+template <bool SLOTS>
+__global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
+  extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 3 x [GRID_SPAN] tables | [PART_CHUNK] slots
+  __shared__ u32 s_wave[PART_THREADS / CCLD_WAVE];
+  __shared__ u32 s_at[GRID_MAX_BATCHES + 1], s_slot0[GRID_MAX_BATCHES];
+  __shared__ u32 s_total, s_b0, s_last;
+  const u32 tid = threadIdx.x;
+  if (d.hdr->feasible == 0) return;
+  u32* s_dst = reinterpret_cast<u32*>(s_row + PART_CHUNK);
+  u32* s_cnt = s_dst + PART_CHUNK;      // rows of the round per fine bucket
+  u32* s_pre = s_cnt + GRID_SPAN;       // exclusive scan of the counts
+  u32* s_start = s_pre + GRID_SPAN;     // first row reserved in each bucket
+  u32* s_src = s_start + GRID_SPAN;
+  // the fine buckets' descriptors and the blame table: every workgroup's share
+  const u32 n_fine = d.hdr->n_fine, G = gridDim.x;
+  for (u32 f = blockIdx.x * PART_THREADS + tid; f < n_fine; f += G * PART_THREADS) {
+    // the communicator whose fine buckets include f: the last one whose first bucket is <= f
+    u32 lo = 0, hi = d.n_comms;
+    while (lo < hi) { const u32 m = (lo + hi) >> 1; if (d.lay[m].fb_base <= f) lo = m + 1; else hi = m; }
+    const u32 c = lo - 1;
+    const CommLayout L = d.lay[c];
+    const u32 r0 = (f - L.fb_base) * L.rpb;
+    FineDesc D;
+    D.comm = c; D.size = L.size;
+    D.K = (L.rounds - r0) < L.rpb ? (L.rounds - r0) : L.rpb;
+    D.srow0 = L.seg_base + r0; D.cell0 = L.cell_base + r0 * L.size; D.pad = 0; D.seq0 = L.seq_min + r0;
+    d.desc[f] = D;
+    if (L.size > CCLD_WAVE) d.long_list[atomicAdd(&d.hdr->n_long, 1u)] = f;
+    d.nflag[f] = 0;
+  }
+  for (u32 i = blockIdx.x * PART_THREADS + tid; i < d.n_blame; i += G * PART_THREADS) d.blame[i] = 0;
+  const u64 lo_mask = d.kf.cb > 0 ? (((u64)1 << (64 - d.kf.cb)) - 1) : ~0ull;
+  const u32 slot_mask = d.kf.mb < 32 ? (1u << d.kf.mb) - 1 : ~0u;
+  const u32 per = ((d.n + G - 1) / G + CCLD_WAVE - 1) / CCLD_WAVE * CCLD_WAVE;
+  const u64 lo64 = (u64)per * blockIdx.x;
+  const u32 lo = lo64 < d.n ? (u32)lo64 : d.n, hi = lo64 + per < d.n ? (u32)(lo64 + per) : d.n;
+  u64 status = 0;
+  const u32 nb = d.n_buckets == 1 ? 1u : d.nb;          // pieces of one coarse bucket
+  if (tid == 0 && lo < hi) {
+    u32 a = 0, b = d.n_buckets;                         // the coarse bucket that holds record lo
+    while (b - a > 1) { const u32 m = (a + b) >> 1; if (d.piece_at[(u64)m * nb] <= lo) a = m; else b = m; }
+    s_b0 = a;
+  }
+  for (u32 i = tid; i < GRID_SPAN; i += PART_THREADS) s_cnt[i] = 0;
+  __syncthreads();
+  u32 pos = lo;
+  for (u32 b = lo < hi ? s_b0 : d.n_buckets; b < d.n_buckets && pos < hi; ++b) {
+    // the bucket's pieces, its records of this slice and its fine buckets
+    for (u32 i = tid; i <= nb; i += PART_THREADS) {
+      s_at[i] = d.piece_at[b * nb + i];
+      if (i < nb) s_slot0[i] = d.piece_slot[b * nb + i];
+    }
+    __syncthreads();
+    const u32 end = s_at[nb] < hi ? s_at[nb] : hi;
+    u64 c0 = (u64)b << d.bshift, c1 = (u64)(b + 1) << d.bshift;
+    if (c0 > d.n_comms) c0 = d.n_comms;
+    if (c1 > d.n_comms) c1 = d.n_comms;
+    const u32 f_lo = d.lay[c0].fb_base, span = d.lay[c1].fb_base - f_lo;
+    // next round's keys and rows are on their way while a round is staged and written
+    u64 key[PART_U], nkey[PART_U];
+    uint4 row[PART_U], nrow[PART_U];
+    u32 src[PART_U], nsrc[PART_U];
+    u32 piece = 0;
+    auto load_round = [&](u32 base, u64 (&K)[PART_U], uint4 (&R)[PART_U], u32 (&S)[PART_U]) {
+#pragma unroll
+      for (u32 u = 0; u < PART_U; ++u) {
+        const u32 j = base + u * PART_THREADS + tid;
+        K[u] = 0; S[u] = 0;
+        if (j < end) {
+          while (j >= s_at[piece + 1]) ++piece;          // j < end <= s_at[nb]: ends within the table
+          u32 p = s_slot0[piece] + (j - s_at[piece]);
+          if (p >= d.cap) p -= d.cap;
+          S[u] = p;
+          K[u] = __builtin_nontemporal_load(d.win_key + p);
+          typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+          const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.win_row + p));
+          R[u] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+      }
+    };
+    load_round(pos, key, row, src);
+    for (u32 base = pos; base < end; base += PART_CHUNK) {
+      u32 fi[PART_U], at[PART_U], cell[PART_U], first[PART_U], room[PART_U];
+      bool on[PART_U];
+      if (base + PART_CHUNK < end) load_round(base + PART_CHUNK, nkey, nrow, nsrc);
+#pragma unroll
+      for (u32 u = 0; u < PART_U; ++u) {
+        on[u] = base + u * PART_THREADS + tid < end;
+        if (!on[u]) continue;
+        const u64 k = key[u];
+        const u32 comm = d.kf.cb ? (u32)(k >> (64 - d.kf.cb)) : 0u;
+        const CommLayout L = d.lay[comm];
+        const u32 rel = (u32)(((k & lo_mask) >> d.kf.mb) - L.seq_min);
+        const u32 fr = rel / L.rpb, rr = rel - fr * L.rpb, left = L.rounds - fr * L.rpb;
+        fi[u] = L.fb_base + fr - f_lo;
+        cell[u] = rr * L.size + ((u32)k & slot_mask);
+        first[u] = L.cell_base + fr * L.rpb * L.size;
+        room[u] = (left < L.rpb ? left : L.rpb) * L.size;
+        on[u] = fi[u] < span;
+        if (on[u]) at[u] = atomicAdd(&s_cnt[fi[u]], 1u);
+      }
+      __syncthreads();
+      {     // exclusive scan of the round's counts, and one reservation per bucket
+        constexpr u32 PER = GRID_SPAN / PART_THREADS;
+        u32 v[PER], sum = 0;
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; v[i] = q < span ? s_cnt[q] : 0u; sum += v[i]; }
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) if (v[i]) s_start[PER * tid + i] = atomicAdd(&d.fill[f_lo + PER * tid + i], v[i]);
+        u32 tot;
+        u32 ex = block_exclusive_sum<PART_THREADS>(sum, s_wave, &tot);
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; if (q < span) { s_pre[q] = ex; s_cnt[q] = 0; } ex += v[i]; }
+        if (tid == 0) s_total = tot;
+      }
+      __syncthreads();
+#pragma unroll
+      for (u32 u = 0; u < PART_U; ++u) {
+        if (!on[u]) continue;
+        const u32 q = s_pre[fi[u]] + at[u], w = s_start[fi[u]] + at[u];
+        if (w >= room[u]) status |= DS_DUPLICATE;
+        s_dst[q] = w < room[u] ? first[u] + w : ~0u;
+        s_row[q] = make_uint4(row[u].x, row[u].y | (cell[u] << ROW_CELL_SHIFT), row[u].z, row[u].w);
+        if (SLOTS) s_src[q] = src[u];
+      }
+      __syncthreads();
+      const u32 total = s_total;
+      for (u32 i = tid; i < total; i += PART_THREADS) {
+        const u32 D = s_dst[i];
+        if (D == ~0u) continue;
+        const u32 o = D & 7;
+        const bool full = i >= o && i + 7 - o < total && s_dst[i - o] == D - o && s_dst[i + 7 - o] == D + 7 - o;
+        const uint4 v = s_row[i];
+        typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 vv = {v.x, v.y, v.z, v.w};
+        if (full) __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(d.rows + D));
+        else d.rows[D] = v;
+        if (SLOTS) d.slots[D] = s_src[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (u32 u = 0; u < PART_U; ++u) { key[u] = nkey[u]; row[u] = nrow[u]; src[u] = nsrc[u]; }
+    }
+    pos = end;
+    __syncthreads();        // the piece table is rewritten for the next bucket
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) status |= shfl_xor_u64(status, m);
+  if (lane_id() == 0 && status) atomicOr((unsigned long long*)&d.counters[CNT_STATUS], (unsigned long long)status);
+  // the last workgroup to finish scans the records per fine bucket
+  if (!last_block(&d.hdr->done, G, &s_last)) return;
+  u32 carry = 0;
+  for (u32 base = 0; base < n_fine; base += PART_THREADS * 4) {
+    u32 v[4], sum = 0;
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) { const u32 f = base + tid * 4 + i; v[i] = f < n_fine ? load_agent(&d.fill[f]) : 0u; sum += v[i]; }
+    u32 tot;
+    u32 ex = carry + block_exclusive_sum<PART_THREADS>(sum, s_wave, &tot);
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) { const u32 f = base + tid * 4 + i; if (f < n_fine) d.rec0[f] = ex; ex += v[i]; }
+    carry += tot;
+  }
+  if (tid == 0) d.rec0[n_fine] = carry;
+}
+static_assert(GRID_SPAN % PART_THREADS == 0, "whole buckets per thread");
+
+void launch_grid_partition(hipStream_t st, const GridArgs& d) {
+  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, lds_slots = lds + (size_t)PART_CHUNK * 4;
+  static bool raised = false;          // more than 64 KB of dynamic LDS has to be asked for once
+  if (!raised) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_slots);
+    raised = true;
+  }
+  // small windows: a thousand records per workgroup, so that there are several of them
+  const u32 g = std::min<u32>(PART_BLOCKS, std::max<u32>((d.n + PART_THREADS - 1) / PART_THREADS, 1));
+  if (d.slots) hipLaunchKernelGGL(k_grid_partition<true>, dim3(g), dim3(PART_THREADS), lds_slots, st, d);
+  else hipLaunchKernelGGL(k_grid_partition<false>, dim3(g), dim3(PART_THREADS), lds, st, d);
+}
+
+}  // namespace ccld

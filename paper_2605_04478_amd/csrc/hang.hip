@@ -938,8 +938,7 @@ extern "C" ccld_status ccld_locate_hang(ccld_ctx* c, const ccld_snapshots* sn, u
   const ccld_status s = check_hang_args(c, sn, n_rows, o, &n_cell);
   if (s != CCLD_OK) return s;
   if (n_cell > c->snap_cap || n_rows > c->snap_cap) return o->status = CCLD_E_CAPACITY;
-  c->inc_ok = false;            // the root list is sorted in the window's sort buffers
-  c->chain_ready = false;
+  c->chain_ready = false;       // the root list is sorted in the window's sort buffers
   return locate_hang_on(c, scratch_of_context(c), sn, n_rows, n_cell, o);
 }
 

@@ -4,10 +4,10 @@
 // (order statistic floor((n-1)/2)), maximum, and then the median absolute deviation.  Collectives
 // of 65 to 512 records take a wavefront each with 2, 4 or 8 values per lane in registers, those of
 // up to 16,384 records a workgroup each with a bitonic sort in LDS (k_seg_team, k_seg_large), and longer ones
-// the counting selection of k_seg_big.
+// the counting selection of k_seg_big.  Windows on the grid placement (grid.h) have kernels of their own at the end.
 #include "window_kernels.h"
-#include "dense.h"
-#include "device_utils.h"
+#include "grid.h"
+#include "rows.h"
 
 namespace ccld {
 
@@ -38,13 +38,8 @@ __device__ __forceinline__ void seg_count_alert(const SegArgs& a, u32 srow, u32 
   if (ninfl && !barrier && a.now_ns - imin > a.hang_threshold_ns && srow < a.seg_cap) atomic_add_u64(&a.counters[CNT_NALERT], 1);
 }
 __device__ __forceinline__ i64 absdiff(i64 a, i64 b) { return a >= b ? a - b : b - a; }
-// payload row of the j-th record in (communicator, counter, rank) order; the op word's upper bits belong
-// to the dense placement
-__device__ __forceinline__ Row load_row(const SegArgs& a, u32 j) {
-  Row r = a.row[a.idx[j]];
-  r.op &= 15u;
-  return r;
-}
+// the j-th record in (communicator, counter, rank) order
+__device__ __forceinline__ Rec load_row(const SegArgs& a, u32 j) { return load_rec(a.win, a.idx[j]); }
 __device__ __forceinline__ bool is_late(i64 lag, i64 floor_ns, u32 knum, u32 kden, i64 mad) {
   return lag > floor_ns && (i128)lag * (i128)kden > (i128)knum * (i128)mad;
 }
@@ -152,8 +147,7 @@ struct DenseLane {
   u64 nb;            // bytes
   u32 op, rank;
   bool valid;        // the lane's member has a record in this collective
-  u64 pm;            // lanes of this lane's collective whose members have a record
-  u32 fl;            // first such lane
+  u32 fl;            // first lane of this lane's collective that has a record
   u32 n, first, j;   // records of the collective, sorted position of its first record and of this record
   u32 srow;          // the collective's row of the table
   u32 comm;
@@ -162,15 +156,13 @@ struct DenseLane {
   // straight to the table.  A flag and not a null pointer: LDS address 0 is a valid address (the first staged row).
   lds_i64* stage;
   bool staged;
+  // grid placement: the record's cell in its fine bucket, where the bucket's flags are collected, their number so far
+  u32 cell, rec0;
+  struct GridFlags* flags;
 };
-// A staged table row: the 21 columns, then the detection-group code and the range T_max - T_min, at constant
-// offsets from the row's pointer.  k_seg_wave keeps the rows STAGE_COLS words apart (an odd stride).  In
-// k_dense_stats a row lies in its collective's own cells, a multiple of 256 bytes from its neighbours, and
-// starts stage_skew(k) words into that region, so that the lanes that later read one column of 64 rows
-// spread over eight bank pairs.
-constexpr u32 STAGE_COLS = CCLD_SEG_NCOL + 2, STAGE_REGION = 32;
-__device__ __forceinline__ u32 stage_skew(u32 k) { return k & 7u; }
-static_assert(STAGE_COLS + 7 <= STAGE_REGION, "a skewed row fits its region");
+// A staged table row of k_seg_wave: the 21 columns, then the detection-group code and the range T_max - T_min; the
+// rows are STAGE_COLS words apart (an odd stride).
+constexpr u32 STAGE_COLS = CCLD_SEG_NCOL + 2;
 
 // Table rows of the collectives of one wavefront pass (called by the first lane of every collective; the rows of a
 // pass are consecutive).  A staged row goes to LDS and the workgroup writes it out later; a row that is not staged
@@ -179,7 +171,8 @@ static_assert(STAGE_COLS + 7 <= STAGE_REGION, "a skewed row fits its region");
 // not stay in scalar registers across the whole pass (212 spilled scalar registers become 20).  Storing G words of
 // a row per instruction from the G lanes of its group (3 instead of 23 store instructions at G = 8) was measured
 // too: the selects that bring each lane its word cost more than the stores save (2.18 -> 2.56 ms).
-enum { PUT_DIRECT = 0, PUT_STAGED = 1, PUT_EITHER = 2 };     // where a table row goes: known when compiled, or by L.staged
+// PUT_SORTED: the sorted window's pass, rows staged where L.staged; PUT_GRID: the grid placement's, rows written directly
+enum { PUT_SORTED = 0, PUT_GRID = 1 };
 template <int MODE>
 __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane& L, u32 ninfl, bool complete, bool incons,
                                               bool barrier, bool usable, u32 hop, u64 hb, i64 imin, u32 nd, i64 min_e,
@@ -188,7 +181,7 @@ __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane&
   const u32 srow = L.srow;
   const bool none = nd == 0;            // no completed record: the statistics columns are empty
   seg_count_alert(a, srow, ninfl, barrier, imin);
-  if (MODE == PUT_STAGED || (MODE == PUT_EITHER && L.staged)) {
+  if (MODE == PUT_SORTED && L.staged) {
     // the row waits in LDS until the workgroup writes the table column by column, whole lines at a time
     lds_i64* st = L.stage;
     auto put = [&](u32 c, i64 v) { st[c] = v; };
@@ -233,11 +226,35 @@ __device__ __forceinline__ void dense_put_row(const SegArgs& a, const DenseLane&
   put(imin);
   put((i64)L.first);
 }
-__device__ __forceinline__ void dense_put_record(const SegArgs& a, u32 j, u32 f, i64 le, i64 lx) {
-  a.rec_flag[j] = (uint8_t)f;
+// One record's lags and flags.  Sorted windows mark every record's flag byte and leave the lags of flagged records at
+// their sorted position; the grid placement collects the flagged records of a fine bucket from the bucket's first sorted
+// position on (a.flag_pos takes cell | kind << 16), in any order: grid_order_flags orders them by cell.
+struct GridFlags {
+  u32 n;                     // flagged records so far
+  u32 bits[GRID_B / 32];     // their cells
+  u32 pre[GRID_B / 32];      // flagged cells before each word
+};
+__device__ __forceinline__ void grid_put_record(const SegArgs& a, u32 j, u32 cell, u32 rec0, GridFlags* F, u32 f, i64 le, i64 lx) {
+  if (a.rec_flag) a.rec_flag[j] = (uint8_t)f;
   if (a.lag_e) a.lag_e[j] = le;
   if (a.lag_x) a.lag_x[j] = lx;
-  if (f) { a.flag_lag[j] = le; a.flag_lag[a.cap_n + j] = lx; }
+  if (f) {
+    const u32 at = rec0 + atomicAdd(&F->n, 1u);
+    atomicOr(&F->bits[cell >> 5], 1u << (cell & 31));
+    a.flag_pos[at] = cell | (f << 16);
+    a.flag_lag[at] = le; a.flag_lag[a.cap_n + at] = lx;
+  }
+}
+template <int MODE>
+__device__ __forceinline__ void dense_put_record(const SegArgs& a, const DenseLane& L, u32 f, i64 le, i64 lx) {
+  if constexpr (MODE == PUT_GRID) {
+    grid_put_record(a, L.j, L.cell, L.rec0, L.flags, f, le, lx);
+  } else {
+    a.rec_flag[L.j] = (uint8_t)f;
+    if (a.lag_e) a.lag_e[L.j] = le;
+    if (a.lag_x) a.lag_x[L.j] = lx;
+    if (f) { a.flag_lag[L.j] = le; a.flag_lag[a.cap_n + L.j] = lx; }
+  }
 }
 
 // Statistics of the collectives of one wavefront pass in 64-bit arithmetic (any spread of the times).
@@ -283,7 +300,7 @@ __device__ __forceinline__ void dense_pass64(const SegArgs& a, const DenseLane& 
     if (is_late(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
     if (is_late(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
   }
-  dense_put_record(a, L.j, f, le, lx);
+  dense_put_record<MODE>(a, L, f, le, lx);
 }
 
 // ---- the same statistics on 32-bit times relative to the collective's first record --------------------
@@ -323,6 +340,18 @@ __device__ __forceinline__ i32 merge_groups32(i32 v, u32 lane) {
   if constexpr (G >= 8) v = cmpx32<4>(v, lane);
   if constexpr (G >= 4) v = cmpx32<2>(v, lane);
   if constexpr (G >= 2) v = cmpx32<1>(v, lane);
+  return v;
+}
+// all-reduce of an unsigned 32-bit word inside a group
+template <int G, bool MAXIMUM>
+__device__ __forceinline__ u32 reduce_u32(u32 v) {
+#define CCLD_U32_STEP(M)                                                                         \
+  if constexpr (G > M) {                                                                         \
+    const u32 o = xor_lane_u32<M>(v);                                                            \
+    v = MAXIMUM ? (o > v ? o : v) : (o < v ? o : v);                                             \
+  }
+  CCLD_U32_STEP(1) CCLD_U32_STEP(2) CCLD_U32_STEP(4) CCLD_U32_STEP(8) CCLD_U32_STEP(16) CCLD_U32_STEP(32)
+#undef CCLD_U32_STEP
   return v;
 }
 // all-reduce of an unsigned 64-bit word inside a group
@@ -390,7 +419,7 @@ __device__ __forceinline__ void dense_pass32(const SegArgs& a, const DenseLane& 
     if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
     if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
   }
-  dense_put_record(a, L.j, f, (i64)le, (i64)lx);
+  dense_put_record<MODE>(a, L, f, (i64)le, (i64)lx);
 }
 
 // ---- collectives of up to 64 records, 64/G of them per wavefront pass --------------------------
@@ -417,7 +446,6 @@ __device__ __forceinline__ void seg_wave_batches(const SegArgs& a, u32 base, u32
     L.valid = small && l < n;
     L.e = 0; L.x = T_INFLIGHT; L.nb = 0; L.op = 0; L.rank = 0;
     L.first = base + a0; L.j = L.first + l; L.fl = gbase; L.n = n; L.srow = seg0 + sl;
-    L.pm = 0;
     // rows beyond the staging area (a tile of many short collectives) go straight to the table
     L.staged = sl < SEG_STAGE_ROWS;
     L.stage = (lds_i64*)s_stage + sl * STAGE_COLS;
@@ -425,7 +453,7 @@ __device__ __forceinline__ void seg_wave_batches(const SegArgs& a, u32 base, u32
     u32 size = 0;
     if (L.valid) {
       key = a.key[L.j];
-      const Row rw = load_row(a, L.j);
+      const Rec rw = load_row(a, L.j);
       // first member and size of the communicator in one load; the slot -> rank lookup overlaps the row gather
       const uint2 ci = a.comm_info[(u32)(key >> (mb + a.sf.ws))];
       L.rank = a.members_sorted[ci.x + (u32)(key & mmask)];
@@ -439,8 +467,8 @@ __device__ __forceinline__ void seg_wave_batches(const SegArgs& a, u32 base, u32
     const i64 oe = L.e - ref, ox = L.x - ref;
     constexpr i64 LIM = (i64)1 << 30;
     const bool wide = L.valid && (oe < -LIM || oe >= LIM || (L.x != T_INFLIGHT && (ox < -LIM || ox >= LIM)));
-    if (ballot64(wide) == 0) dense_pass32<G, PUT_EITHER>(a, L, ref, (i32)oe, (i32)ox, size, lane, gbase, gmask);
-    else dense_pass64<G, PUT_EITHER>(a, L, size, lane, gbase, gmask);
+    if (ballot64(wide) == 0) dense_pass32<G, PUT_SORTED>(a, L, ref, (i32)oe, (i32)ox, size, lane, gbase, gmask);
+    else dense_pass64<G, PUT_SORTED>(a, L, size, lane, gbase, gmask);
   }
 }
 
@@ -597,11 +625,10 @@ __device__ __forceinline__ i64 mad_of_sorted(const i64 (&v)[E], u32 nd, u32 km) 
   return r;
 }
 
-// One wavefront per listed collective of 32 E + 1 .. 64 E records (E = 1: of 1 .. 64 records; only the dense
-// placement lists collectives that short, those of communicators with more than 64 members).
+// One wavefront per listed collective of 32 E + 1 .. 64 E records.
 template <int E>
 __global__ __launch_bounds__(SEG_THREADS) void k_seg_multi(SegArgs a) {
-  constexpr u32 LO = E == 1 ? 1 : 32 * E + 1, HI = 64 * E, NW = SEG_THREADS / CCLD_WAVE;
+  constexpr u32 LO = 32 * E + 1, HI = 64 * E, NW = SEG_THREADS / CCLD_WAVE;
   const u32 lane = lane_id();
   const int mb = a.sf.mb;
   const u64 mmask = ((u64)1 << mb) - 1, smask = ((u64)1 << a.sf.ws) - 1;
@@ -630,7 +657,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_multi(SegArgs a) {
       if (valid) {
         const u32 j = a0 + i;
         const u64 key = a.key[j];
-        const Row rw = load_row(a, j);
+        const Rec rw = load_row(a, j);
         rank = ms[(u32)(key & mmask)];
         e[r] = rw.t_enter; x[r] = rw.t_exit; nb = rw.bytes; op = rw.op;
       }
@@ -780,7 +807,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_team(SegArgs a) {
     if (nn < LO || nn > CAPN) continue;
     const u32 srow = a.big_list[3 * ent], a0 = a.big_list[3 * ent + 1];
     const u64 k0 = a.key[a0];
-    const Row h = load_row(a, a0);
+    const Rec h = load_row(a, a0);
     if (t == 0) {
       acc.imin = (unsigned long long)T_INFLIGHT; acc.dmin = INT64_MAX; acc.dmax = INT64_MIN;
       acc.ninfl = 0; acc.incons = 0; acc.rmin = 0xFFFFFFFFu; acc.rmax = 0xFFFFFFFFu;
@@ -792,7 +819,7 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_team(SegArgs a) {
       i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN;
       for (u32 i = t; i < nn; i += TT) {
         const u32 j = a0 + i;
-        const Row rw = load_row(a, j);
+        const Rec rw = load_row(a, j);
         E[i] = rw.t_enter; X[i] = rw.t_exit;
         inc |= (rw.op != h.op || rw.bytes != h.bytes);
         if (rw.t_exit == T_INFLIGHT) {
@@ -893,15 +920,15 @@ __global__ __launch_bounds__(LARGE_THREADS) void k_seg_large(SegArgs a) {
   const u32 t = threadIdx.x;
   const int mb = a.sf.mb;
   const u64 mmask = ((u64)1 << mb) - 1, smask = ((u64)1 << a.sf.ws) - 1;
-  i64* big_e = a.big_ex;
-  i64* big_x = a.big_ex + a.cap_n;
+  i64* big_e = a.big_e;
+  i64* big_x = a.big_x;
   const u32 nbig = (u32)a.counters[CNT_NBIG];
   for (u32 ent = blockIdx.x; ent < nbig; ent += gridDim.x) {
     const u32 nn = a.big_list[3 * ent + 2];
     if (nn <= (u32)SEG_TEAM_MAX || nn > (u32)SEG_LARGE_MAX) continue;
     const u32 srow = a.big_list[3 * ent], a0 = a.big_list[3 * ent + 1];
     const u64 k0 = a.key[a0];
-    const Row h = load_row(a, a0);
+    const Rec h = load_row(a, a0);
     if (t == 0) {
       acc.imin = (unsigned long long)T_INFLIGHT; acc.dmin = INT64_MAX; acc.dmax = INT64_MIN;
       acc.ninfl = 0; acc.incons = 0; acc.rmin = 0xFFFFFFFFu; acc.rmax = 0xFFFFFFFFu;
@@ -913,7 +940,7 @@ __global__ __launch_bounds__(LARGE_THREADS) void k_seg_large(SegArgs a) {
       i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN;
       for (u32 i = t; i < nn; i += LARGE_THREADS) {
         const u32 j = a0 + i;
-        const Row rw = load_row(a, j);
+        const Rec rw = load_row(a, j);
         big_e[j] = rw.t_enter; big_x[j] = rw.t_exit;
         inc |= (rw.op != h.op || rw.bytes != h.bytes);
         if (rw.t_exit == T_INFLIGHT) {
@@ -1015,8 +1042,8 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_big(SegArgs a) {
   const u32 tid = threadIdx.x;
   const int mb = a.sf.mb;
   const u64 mmask = ((u64)1 << mb) - 1, smask = ((u64)1 << a.sf.ws) - 1;
-  i64* big_e = a.big_ex;
-  i64* big_x = a.big_ex + a.cap_n;
+  i64* big_e = a.big_e;
+  i64* big_x = a.big_x;
   const u32 nbig = (u32)a.counters[CNT_NBIG];
   for (u32 ent = blockIdx.x; ent < nbig; ent += gridDim.x) {
     if (a.big_list[3 * ent + 2] <= (u32)SEG_LARGE_MAX) continue;    // a workgroup kernel has taken it
@@ -1034,11 +1061,11 @@ __global__ __launch_bounds__(SEG_THREADS) void k_seg_big(SegArgs a) {
       if (stop) break;
     }
     const u32 b0 = s_end, nn = b0 - a0;
-    const Row h = load_row(a, a0);
+    const Rec h = load_row(a, a0);
     {
       u32 ni = 0; bool inc = false; i64 imin = T_INFLIGHT;
       for (u32 j = a0 + tid; j < b0; j += SEG_THREADS) {
-        const Row rw = load_row(a, j);
+        const Rec rw = load_row(a, j);
         big_e[j] = rw.t_enter; big_x[j] = rw.t_exit;
         if (rw.t_exit == T_INFLIGHT) { ++ni; imin = rw.t_enter < imin ? rw.t_enter : imin; }
         inc |= (rw.op != h.op || rw.bytes != h.bytes);
@@ -1148,244 +1175,658 @@ __global__ __launch_bounds__(256) void k_seg_group_listed(SegArgs a) {
   }
 }
 
-// ---- dense placement: statistics straight from the partitioned rows -----------------------------------
-// One workgroup per fine bucket: the bucket's rows (in arrival order) are placed in LDS by grid cell
-// (round inside the bucket x member slot), which puts every collective's records side by side in rank
-// order with empty cells where a member has no record; the wavefronts then take the collectives
-// 64 / G at a time exactly as k_seg_wave does.  The kernel also writes the records' squeezed keys and row
-// indices in (communicator, counter, rank) order, which the flag, blame, group and alert stages read, and
-// adds the records per rank to the blame table.
-constexpr int DENSE_THREADS = 512;
+// ---- grid placement: statistics straight from the partitioned rows --------------------------------------
+// One workgroup per fine bucket: the bucket's rows (in arrival order) are placed in LDS by cell (round inside the bucket
+// x member slot), which puts every collective's records side by side in rank order with empty cells where a member has
+// no record; the wavefronts then take the collectives 64 / G at a time.  The kernel leaves, beside the table, the row
+// of every cell (2 bytes), which the chains and the alerts look records up by, and the bucket's flagged records.
+struct GridShared {
+  uint4 row[GRID_B];                     // rows by cell; y bits 16-26: number of the row in its bucket
+  u32 pres[GRID_B / 32];
+  unsigned short pre[GRID_B];            // records of the bucket before each of its rounds
+  u32 wave[8];
+  GridFlags flags;
+};
+// Places bucket f's rows in LDS.  Returns status bits: a cell taken twice or more rows than cells (duplicate keys), a
+// round without any record (a hole in the grid).  Ends with a barrier.
+template <int THREADS>
+__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, GridShared& S) {
+  constexpr u32 U = GRID_B / THREADS;
+  const u32 tid = threadIdx.x, cells = D.K * D.size;
+  typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 v[U];
+  bool dup = cnt > cells;
+  if (dup) cnt = cells;
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    const u32 i = tid + u * THREADS;
+    if (i < cnt) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.rows + D.cell0 + i));
+  }
+  for (u32 i = tid; i < GRID_B / 32; i += THREADS) { S.pres[i] = 0; S.flags.bits[i] = 0; }
+  if (tid == 0) S.flags.n = 0;
+  __syncthreads();
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    const u32 i = tid + u * THREADS;
+    if (i >= cnt) continue;
+    const u32 cell = (v[u].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK;
+    if (cell >= cells) { dup = true; continue; }
+    const u32 bit = 1u << (cell & 31);
+    if (atomicOr(&S.pres[cell >> 5], bit) & bit) { dup = true; continue; }
+    S.row[cell] = make_uint4(v[u].x, (v[u].y & ~(ROW_CELL_MASK << ROW_CELL_SHIFT)) | (i << ROW_CELL_SHIFT), v[u].z, v[u].w);
+  }
+  __syncthreads();
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    const u32 c = tid + u * THREADS;
+    if (c >= cells) continue;
+    const bool on = (S.pres[c >> 5] >> (c & 31)) & 1u;
+    d.cell_row[D.cell0 + c] = (uint16_t)(on ? (S.row[c].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK : GRID_EMPTY);
+  }
+  // records per round and their exclusive scan
+  bool gap = false;
+  u32 n[U], sum = 0;
+#pragma unroll
+  for (u32 q = 0; q < U; ++q) {
+    const u32 k = U * tid + q;
+    n[q] = 0;
+    if (k < D.K) {
+      const u32 b0 = k * D.size, b1 = b0 + D.size;      // bits [b0, b1)
+      for (u32 w = b0 >> 5; w <= (b1 - 1) >> 5; ++w) {
+        u32 m = S.pres[w];
+        if (w == (b0 >> 5)) m &= ~0u << (b0 & 31);
+        if (w == ((b1 - 1) >> 5) && (b1 & 31)) m &= (1u << (b1 & 31)) - 1;
+        n[q] += (u32)__popc(m);
+      }
+      gap |= n[q] == 0;
+    }
+    sum += n[q];
+  }
+  u32 tot;
+  u32 ex = block_exclusive_sum<THREADS>(sum, S.wave, &tot);
+#pragma unroll
+  for (u32 q = 0; q < U; ++q) {
+    const u32 k = U * tid + q;
+    if (k < D.K) S.pre[k] = (unsigned short)ex;
+    ex += n[q];
+  }
+  __syncthreads();
+  return (dup ? (u64)DS_DUPLICATE : 0) | (gap ? (u64)DS_DENSE_FALLBACK : 0);
+}
+// Puts the flagged records of a fine bucket in (counter, rank) order and adds them to the late columns of the blame table.
+// Called by the whole workgroup behind a barrier; few buckets have any.
+template <int THREADS>
+__device__ __forceinline__ void grid_order_flags(const SegArgs& a, const FineDesc& D, u32 rec0, GridFlags& F, u32* s_wave,
+                                                 i64* __restrict__ blame, u32 n_ranks) {
+  const u32 n = F.n, tid = threadIdx.x;
+  if (n == 0) return;
+  static_assert(GRID_B / 32 <= CCLD_WAVE, "one word per lane");
+  if (tid < CCLD_WAVE) {
+    const u32 c = tid < GRID_B / 32 ? (u32)__popc(F.bits[tid]) : 0u;
+    const u32 inc = wave_inclusive_sum(c);
+    if (tid < GRID_B / 32) F.pre[tid] = inc - c;
+  }
+  __syncthreads();
+  constexpr u32 U = GRID_B / THREADS;
+  u32 w[U], at[U];
+  i64 le[U], lx[U];
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    const u32 i = tid + u * THREADS;
+    w[u] = 0;
+    if (i < n) {
+      w[u] = a.flag_pos[rec0 + i]; le[u] = a.flag_lag[rec0 + i]; lx[u] = a.flag_lag[a.cap_n + rec0 + i];
+      const u32 cell = w[u] & 0xFFFFu;
+      at[u] = F.pre[cell >> 5] + (u32)__popc(F.bits[cell >> 5] & ((1u << (cell & 31)) - 1u));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    if (__ballot(w[u] != 0) == 0) continue;
+    if (w[u]) { a.flag_pos[rec0 + at[u]] = w[u]; a.flag_lag[rec0 + at[u]] = le[u]; a.flag_lag[a.cap_n + rec0 + at[u]] = lx[u]; }
+    // the blame of one wavefront's records: one set of atomics per member slot that occurs
+    const u32 kind = w[u] >> 16, slot = w[u] ? (w[u] & 0xFFFFu) % D.size : 0u;
+    u64 todo = ballot64(w[u] != 0);
+    while (todo) {
+      const u32 v = (u32)__shfl((int)slot, (int)__builtin_ctzll(todo), CCLD_WAVE);
+      const u64 same = ballot64(w[u] != 0 && slot == v);
+      const bool me = (same >> lane_id()) & 1;
+      const bool en = me && (kind & CCLD_FLAG_LATE_ENTER), ex = me && (kind & CCLD_FLAG_LATE_EXIT);
+      const u64 ne = (u64)__popcll(ballot64(en)), nx = (u64)__popcll(ballot64(ex));
+      u64 se = en ? (u64)le[u] : 0, sx = ex ? (u64)lx[u] : 0;
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) { se += shfl_xor_u64(se, m); sx += shfl_xor_u64(sx, m); }
+      if (lane_id() < 4) {
+        const u64 val = lane_id() == 0 ? ne : lane_id() == 1 ? nx : lane_id() == 2 ? se : sx;
+        const u32 r = a.members_sorted[a.member_off[D.comm] + v];
+        if (val) atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)lane_id() * n_ranks + r]), (unsigned long long)val);
+      }
+      todo &= ~same;
+    }
+  }
+}
+static_assert(CCLD_BLM_N_LATE_ENTER == 0 && CCLD_BLM_N_LATE_EXIT == 1 && CCLD_BLM_SUM_LAG_ENTER == 2 &&
+              CCLD_BLM_SUM_LAG_EXIT == 3, "blame column order");
+// position in the window's arrival order of a partitioned row
+__device__ __forceinline__ u32 grid_arrival(const SegArgs& a, const GridArgs& d, u32 at) {
+  const u32 slot = d.slots[at];
+  if (a.arrival) return a.arrival[slot] - a.seqno_head;
+  return slot >= d.head ? slot - d.head : slot + d.cap - d.head;
+}
 
-template <int G, bool STAGED>
-__device__ __forceinline__ u32 dense_wave_batches(const SegArgs& a, uint4* s_cell, const u32* s_pres,
-                                                  const u32* s_pre, u32 K, u32 size, u32 comm, u64 rel0, u32 srow0,
-                                                  u32 rec0, u32 row0, u64* __restrict__ skey, u32* __restrict__ sidx,
-                                                  u32 lane, u32 wave) {
-  constexpr int SPW = CCLD_WAVE / G, NW = DENSE_THREADS / CCLD_WAVE;
-  const int mb = a.sf.mb;
+// A collective's table row waits in its own cells (16 words; from four members on they are large enough) until the
+// workgroup writes the table, 64 rows per store instruction.  The words are rotated by the round's number, so that
+// neither the lanes that write one row nor those that read one word of 64 rows meet in few banks.
+//   0-1 arrival of the first record | 2-5 arrival min, median, max, MAD | 6-9 the same of the completion, all relative to
+//   words 0-1 | 10-11 T_min, T_max | 12-13 their ranks | 14 bytes, low | 15 state, op << 4, bytes, high << 8, n << 13
+// word 15 = ROW_NOT_STAGED: the row was written directly (times that do not fit 30 bits, operations in flight).
+constexpr u32 ROW_WORDS = 16, ROW_NOT_STAGED = 0xFFFFFFFFu;
+__device__ __forceinline__ u32 stage_word(u32 k, u32 size, u32 w) {
+  return k * size * 4 + (((w + k) & 15u) | (size >= 8 ? k & 16u : 0u));
+}
+
+template <int G>
+__device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
+                                            GridShared& S, u32 lane, u32 wave, u32 n_waves) {
+  constexpr int SPW = CCLD_WAVE / G;
+  constexpr i64 LIM = (i64)1 << 30;
+  const u32 K = D.K, size = D.size;
+  const bool stage = size >= 4;
   const u32 q = lane / G, l = lane % G, gbase = q * G;
   const u64 gmask = (G == 64 ? ~0ull : (((u64)1 << (G & 63)) - 1)) << gbase;
   const u64 below = ((u64)1 << lane) - 1;
-  const u32* __restrict__ ms = a.members_sorted + a.member_off[comm];
-  const u32 rank = l < size ? ms[l] : 0u;
+  const u32 rank = l < size ? a.members_sorted[a.member_off[D.comm] + l] : 0u;
+  u32* stw = reinterpret_cast<u32*>(S.row);
   u32 mine = 0;                                    // records seen in this lane's member slot
-  for (u32 b = wave; b * SPW < K; b += NW) {
+  for (u32 b = wave; b * SPW < K; b += n_waves) {
     const u32 k = b * SPW + q;
     const bool in = k < K && l < size;
-    const u32 cell = k * size + l;
-    DenseLane L;
-    L.valid = in && ((s_pres[cell >> 5] >> (cell & 31)) & 1u);
-    L.pm = ballot64(L.valid) & gmask;
-    L.n = (u32)__popcll(L.pm);
-    L.e = 0; L.x = T_INFLIGHT; L.nb = 0; L.op = 0; L.rank = rank; L.comm = comm;
-    // the collective's own cells (size x 32 bytes, at least one region) take its row once they are read
-    L.staged = STAGED;
-    L.stage = (lds_i64*)reinterpret_cast<i64*>(s_cell) + k * size * 4 + stage_skew(k);
-    u32 ai = 0;
-    if (L.valid) {
-      const uint4 h0 = s_cell[2 * cell], h1 = s_cell[2 * cell + 1];
-      L.e = (i64)(((u64)h0.y << 32) | h0.x); L.x = (i64)(((u64)h0.w << 32) | h0.z);
-      L.nb = ((u64)h1.y << 32) | h1.x; L.op = h1.z & 15u; ai = h1.z >> 4;
-      ++mine;
+    const u32 cell = in ? k * size + l : 0u;
+    const bool valid = in && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
+    const u64 pm = ballot64(valid) & gmask;
+    const u32 n = (u32)__popcll(pm), fl = pm ? (u32)__builtin_ctzll(pm) : gbase;
+    const uint4 v = S.row[cell];
+    const uint4 lead = S.row[pm ? k * size + (fl - gbase) : 0u];      // one address per group: a broadcast
+    __builtin_amdgcn_wave_barrier();                                  // read before the row is staged over it
+    mine += valid ? 1u : 0u;
+    const u32 first = rec0 + (k < K ? S.pre[k] : 0u), j = first + (u32)__popcll(pm & below);
+    const u64 t0 = row_t44(lead);
+    const i64 off = t44_diff(row_t44(v), t0);
+    const bool infl = valid && v.z == ROW_INFLIGHT, done = valid && !infl;
+    const bool wide = valid && (v.z == ROW_WIDE || lead.z == ROW_WIDE || off < -LIM || off >= LIM ||
+                                (done && ((i64)v.z >= LIM || off + (i64)v.z >= LIM)));
+    const i64 ref = wref + t44_diff(t0, (u64)wref);
+    if (valid && a.perm) a.perm[j] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+    if (ballot64(wide) != 0) {
+      DenseLane L;
+      const Rec r = valid ? unpack_row(v, wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
+      L.e = r.t_enter; L.x = r.t_exit; L.nb = r.bytes; L.op = r.op; L.rank = rank; L.valid = valid; L.fl = fl;
+      L.n = n; L.first = first; L.j = j; L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k;
+      L.stage = nullptr; L.staged = false; L.cell = cell; L.rec0 = rec0; L.flags = &S.flags;
+      dense_pass64<G, PUT_GRID>(a, L, size, lane, gbase, gmask);
+      if (stage && valid && lane == fl) stw[stage_word(k, size, 15)] = ROW_NOT_STAGED;
+      continue;
     }
-    L.first = rec0 + (k < K ? s_pre[k] : 0u);
-    L.j = L.first + (u32)__popcll(L.pm & below);
-    L.fl = L.pm ? (u32)__builtin_ctzll(L.pm) : gbase;
-    L.srow = srow0 + k;
-    const u64 rel = rel0 + k;
-    L.seq = rel + a.sf.seq_base;
-    if (L.valid) {
-      skey[L.j] = ((u64)comm << (mb + a.sf.ws)) | (rel << mb) | (u64)l;
-      sidx[L.j] = row0 + ai;
+    const i32 er = (i32)off, xr = er + (i32)v.z;
+    const u32 nd = (u32)__popcll(ballot64(done) & gmask), ninfl = n - nd;
+    const u32 km = nd ? (nd - 1) / 2 : 0, kl = nd ? nd - 1 : 0;
+    const i32 se = sort_groups32<G>(done ? er : REL_NONE, lane);
+    const i32 sx = sort_groups32<G>(done ? xr : REL_NONE, lane);
+    const i32 med_e = __shfl(se, (int)(gbase + km), CCLD_WAVE), med_x = __shfl(sx, (int)(gbase + km), CCLD_WAVE);
+    // deviations of the sorted offsets (the first nd lanes of a group hold its finished records): they fall to zero
+    // at the median and rise again, so one merge sorts them
+    const bool held = l < nd;
+    const i32 sde = merge_groups32<G>(held ? (se >= med_e ? se - med_e : med_e - se) : REL_NONE, lane);
+    const i32 sdx = merge_groups32<G>(held ? (sx >= med_x ? sx - med_x : med_x - sx) : REL_NONE, lane);
+    // T_min / T_max of the Duration Time; the first lane that attains one has the smallest rank
+    const u32 dmin = reduce_u32<G, false>(done ? v.z : ~0u), dmax = reduce_u32<G, true>(done ? v.z : 0u);
+    const u64 mmin = ballot64(done && v.z == dmin) & gmask, mmax = ballot64(done && v.z == dmax) & gmask;
+    const bool incons = (ballot64(valid && (v.w != lead.w || ((v.y ^ lead.y) & ROW_SAME_MASK))) & gmask) != 0;
+    const u64 hb = row_bytes(lead);
+    const u32 hop = row_op(lead);
+    const bool complete = n == size && ninfl == 0;
+    const bool barrier = hop == CCLD_OP_ALLREDUCE && hb < (u64)a.barrier_bytes;
+    const bool usable = complete && !incons && !barrier;
+    const u32 rmin = __shfl(rank, (int)(mmin ? (u32)__builtin_ctzll(mmin) : lane), CCLD_WAVE);
+    const u32 rmax = __shfl(rank, (int)(mmax ? (u32)__builtin_ctzll(mmax) : lane), CCLD_WAVE);
+    if (stage && ninfl == 0 && n) {
+      // every lane writes the words it holds
+      if (l == 0) { stw[stage_word(k, size, 2)] = (u32)se; stw[stage_word(k, size, 6)] = (u32)sx; }
+      if (l == km) {
+        stw[stage_word(k, size, 3)] = (u32)se; stw[stage_word(k, size, 7)] = (u32)sx;
+        stw[stage_word(k, size, 5)] = (u32)sde; stw[stage_word(k, size, 9)] = (u32)sdx;
+      }
+      if (l == kl) { stw[stage_word(k, size, 4)] = (u32)se; stw[stage_word(k, size, 8)] = (u32)sx; }
+      if (lane == fl) {
+        stw[stage_word(k, size, 0)] = (u32)(u64)ref; stw[stage_word(k, size, 1)] = (u32)((u64)ref >> 32);
+        stw[stage_word(k, size, 10)] = dmin; stw[stage_word(k, size, 11)] = dmax;
+        stw[stage_word(k, size, 12)] = rmin; stw[stage_word(k, size, 13)] = rmax;
+        stw[stage_word(k, size, 14)] = (u32)hb;
+        stw[stage_word(k, size, 15)] = (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) |
+                                       (barrier ? CCLD_SEG_BARRIER : 0) | (usable ? CCLD_SEG_USABLE : 0) | (hop << 4) |
+                                       ((u32)(hb >> 32) << 8) | (n << 13);
+      }
     }
-    // offsets from the arrival of the collective's first present member
-    const i64 ref = shfl_i64(L.e, (int)L.fl);
-    const i64 oe = L.e - ref, ox = L.x - ref;
-    constexpr i64 LIM = (i64)1 << 30;
-    const bool wide = L.valid && (oe < -LIM || oe >= LIM || (L.x != T_INFLIGHT && (ox < -LIM || ox >= LIM)));
-    if (ballot64(wide) == 0) dense_pass32<G, STAGED ? PUT_STAGED : PUT_DIRECT>(a, L, ref, (i32)oe, (i32)ox, size, lane, gbase, gmask);
-    else dense_pass64<G, STAGED ? PUT_STAGED : PUT_DIRECT>(a, L, size, lane, gbase, gmask);
+    if (ballot64(!stage || ninfl != 0)) {
+      // short communicators and operations in flight: the row goes straight to the table
+      const i32 min_e = __shfl(se, (int)gbase, CCLD_WAVE), max_e = __shfl(se, (int)(gbase + kl), CCLD_WAVE);
+      const i32 min_x = __shfl(sx, (int)gbase, CCLD_WAVE), max_x = __shfl(sx, (int)(gbase + kl), CCLD_WAVE);
+      const i32 mad_e = __shfl(sde, (int)(gbase + km), CCLD_WAVE), mad_x = __shfl(sdx, (int)(gbase + km), CCLD_WAVE);
+      const i32 imin = (i32)(reduce_u32<G, false>(infl ? (u32)er ^ 0x80000000u : ~0u) ^ 0x80000000u);
+      if (valid && lane == fl && (!stage || ninfl)) {
+        DenseLane L;
+        L.n = n; L.first = first; L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k; L.staged = false;
+        dense_put_row<PUT_GRID>(a, L, ninfl, complete, incons, barrier, usable, hop, hb, ninfl ? ref + imin : T_INFLIGHT, nd,
+                                ref + min_e, ref + med_e, ref + max_e, (i64)mad_e, ref + min_x, ref + med_x, ref + max_x,
+                                (i64)mad_x, (i64)dmin, (i64)dmax, rmin, rmax);
+        if (stage) stw[stage_word(k, size, 15)] = ROW_NOT_STAGED;
+      }
+    }
+    i32 le = 0, lx = 0;
+    u32 f = 0;
+    if (usable) { le = er - med_e; lx = xr - med_x; }
+    // a lag within the floor is never late (most wavefronts end here)
+    if (ballot64(valid && ((i64)le > a.lag_floor || (i64)lx > a.lag_floor))) {
+      const i32 mad_e = __shfl(sde, (int)(gbase + km), CCLD_WAVE), mad_x = __shfl(sdx, (int)(gbase + km), CCLD_WAVE);
+      if (usable) {
+        if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
+        if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
+      }
+    }
+    if (valid) grid_put_record(a, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
   }
   return mine;
 }
 
-// One workgroup per fine bucket, two workgroups of eight wavefronts per compute unit (their LDS allows no more):
-// while one of them waits for its rows or at a barrier the other one computes.  Measured at the 4,096-rank
-// trace: a grid-stride loop over the buckets makes the compiler keep the loop's invariants in some 230
-// registers (two wavefronts per SIMD, 2.2 ms; capped at 128 registers it spills, 3.3 ms); one bucket per
-// workgroup needs 97 registers, and 512 threads take 1.7 ms (256: 2.0, 384: 2.7, 640: 2.3, 1,024: 2.2 ms).
-__global__ __launch_bounds__(DENSE_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_dense_stats(SegArgs a, DenseArgs d, u64* __restrict__ skey,
-                                                               u32* __restrict__ sidx, i64* __restrict__ blame,
-                                                               u32 n_ranks) {
-  constexpr int U = (DENSE_STRIDE + DENSE_THREADS - 1) / DENSE_THREADS;        // rows per thread
-  __shared__ uint4 s_cell[2 * DENSE_B];
-  __shared__ u32 s_pres[DENSE_B / 32];
-  __shared__ unsigned short s_n[DENSE_B];
-  __shared__ u32 s_aux[DENSE_B + 4];          // [K] first record of each collective, then [size] records per member slot
-  __shared__ u32 s_wave[DENSE_THREADS / CCLD_WAVE];
-  if (d.hdr[DH_FEASIBLE] == 0) return;
-  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
-  const u32 f = blockIdx.x;
-  if (f >= d.hdr[DH_N_FINE]) return;
-  const uint4* __restrict__ rows4 = reinterpret_cast<const uint4*>(d.rows);
-  unsigned long long* nrec = (unsigned long long*)(blame + (u64)CCLD_BLM_N_RECORDS * n_ranks);
-  typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 h0[U], h1[U];
-  auto fetch = [&](u32 f, u32 cnt) {
-    const u64 row0 = (u64)f * DENSE_STRIDE;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const u32 i = tid + u * DENSE_THREADS;
-      if (i < cnt) {
-        h0[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(rows4 + 2 * (row0 + i)));
-        h1[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(rows4 + 2 * (row0 + i) + 1));
-      }
-    }
-  };
-  auto clamp = [](u32 c) { return c < DENSE_STRIDE ? c : DENSE_STRIDE; };
+constexpr int GRID_THREADS = 256;
+__global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+  __shared__ GridShared S;
+  __shared__ u32 s_slot[CCLD_WAVE];
+  constexpr u32 NW = GRID_THREADS / CCLD_WAVE;
+  const u32 f = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  if (d.hdr->feasible == 0 || f >= d.hdr->n_fine) return;
   const FineDesc D = d.desc[f];
-  {
-    const u32 c = D.comm, size = D.size, K = D.K, rec0 = D.rec0, cnt = clamp(D.cnt);
-    const u32 row0 = f * DENSE_STRIDE;
-    u32* s_pre = s_aux;
-    u32* s_slot = s_aux + K;
-    fetch(f, cnt);                    // the rows are on their way while the bucket's LDS state is cleared
-    for (u32 i = tid; i < DENSE_B / 32; i += DENSE_THREADS) s_pres[i] = 0;
-    for (u32 i = tid; i < size; i += DENSE_THREADS) s_slot[i] = 0;
-    __syncthreads();
-    // 1. every row into its cell; a cell taken twice is a duplicate key
-    bool dup = D.cnt > DENSE_STRIDE;
+  if (D.size > (u32)SEG_WAVE_MAX) return;               // k_grid_long takes it
+  const i64 wref = d.hdr->ref;
+  const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size;
+  if (tid < CCLD_WAVE) s_slot[tid] = 0;
+  u64 bad = grid_place<GRID_THREADS>(d, D, cnt, S);
+  u32 mine;
+  if (size <= 2) mine = grid_batches<2>(a, d, D, rec0, wref, S, lane, wave, NW);
+  else if (size <= 4) mine = grid_batches<4>(a, d, D, rec0, wref, S, lane, wave, NW);
+  else if (size <= 8) mine = grid_batches<8>(a, d, D, rec0, wref, S, lane, wave, NW);
+  else if (size <= 16) mine = grid_batches<16>(a, d, D, rec0, wref, S, lane, wave, NW);
+  else if (size <= 32) mine = grid_batches<32>(a, d, D, rec0, wref, S, lane, wave, NW);
+  else mine = grid_batches<64>(a, d, D, rec0, wref, S, lane, wave, NW);
+  // the lane's member slot is the same in every pass
+  u32 G = 2; while (G < size) G <<= 1;
+  if (mine) atomicAdd(&s_slot[lane % G], mine);
+  if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
+  __syncthreads();
+  if (tid == 0) d.nflag[f] = S.flags.n;
+  // the staged rows: every wavefront takes 64 of them
+  if (size >= 4) {
+    const u32* stw = reinterpret_cast<const u32*>(S.row);
+    for (u32 k = wave * CCLD_WAVE + lane; k < D.K; k += GRID_THREADS) {
+      u32 w[ROW_WORDS];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const u32 i = tid + u * DENSE_THREADS;
-      if (i >= cnt) continue;
-      const u32 cell = (h1[u].z >> 4) & (DENSE_B - 1);
-      if (cell >= K * size) { dup = true; continue; }
-      const u32 bit = 1u << (cell & 31);
-      if (atomicOr(&s_pres[cell >> 5], bit) & bit) { dup = true; continue; }
-      s_cell[2 * cell] = make_uint4(h0[u].x, h0[u].y, h0[u].z, h0[u].w);
-      s_cell[2 * cell + 1] = make_uint4(h1[u].x, h1[u].y, (h1[u].z & 15u) | (i << 4), h1[u].w);
+      for (u32 i = 0; i < ROW_WORDS; ++i) w[i] = stw[stage_word(k, size, i)];
+      if (w[15] == ROW_NOT_STAGED) continue;
+      const u32 srow = D.srow0 + k;
+      const u32 state = w[15] & 15u, op = (w[15] >> 4) & 15u, n = w[15] >> 13;
+      const u64 nb = (u64)w[14] | ((u64)((w[15] >> 8) & 31u) << 32);
+      const bool usable = (state & CCLD_SEG_USABLE) != 0;
+      a.gcode[srow] = (uint16_t)seg_group_code(usable, op, nb);
+      a.range_c[srow] = usable ? (i64)(w[11] - w[10]) : 0;
+      if (srow >= a.seg_cap) continue;
+      const i64 ref = (i64)((u64)w[0] | ((u64)w[1] << 32));
+      i64* p = a.seg + srow;
+      auto put = [&](i64 v) { *p = v; p += a.seg_cap; };
+      put((i64)D.comm); put((i64)(D.seq0 + k)); put((i64)n); put(0); put((i64)state); put((i64)op); put((i64)nb);
+      put(ref + (i32)w[2]); put(ref + (i32)w[3]); put(ref + (i32)w[4]); put((i64)w[5]);
+      put(ref + (i32)w[6]); put(ref + (i32)w[7]); put(ref + (i32)w[8]); put((i64)w[9]);
+      put((i64)w[10]); put((i64)w[11]); put((i64)w[12]); put((i64)w[13]);
+      put(T_INFLIGHT); put((i64)(rec0 + S.pre[k]));
     }
-    __syncthreads();
-    // 2. records per collective, their exclusive scan; a round without any record is a hole in the grid
-    for (u32 k = tid; k < K; k += DENSE_THREADS) {
-      const u32 b0 = k * size, b1 = b0 + size;      // bits [b0, b1)
-      u32 nk = 0;
-      for (u32 w = b0 >> 5; w <= (b1 - 1) >> 5; ++w) {
-        u32 m = s_pres[w];
-        if (w == (b0 >> 5)) m &= ~0u << (b0 & 31);
-        if (w == ((b1 - 1) >> 5) && (b1 & 31)) m &= (1u << (b1 & 31)) - 1;
-        nk += __popc(m);
-      }
-      s_n[k] = (unsigned short)nk;
-    }
-    __syncthreads();
-    bool gap = false;
-    {
-      constexpr int PER = (DENSE_B + DENSE_THREADS - 1) / DENSE_THREADS;
-      u32 v[PER], sum = 0;
+  }
+  // records per rank
+  unsigned long long* nrec = (unsigned long long*)(blame + (u64)CCLD_BLM_N_RECORDS * n_ranks);
+  if (tid < size && s_slot[tid]) atomicAdd(&nrec[a.members_sorted[a.member_off[D.comm] + tid]], (unsigned long long)s_slot[tid]);
+  grid_order_flags<GRID_THREADS>(a, D, rec0, S.flags, S.wave, blame, n_ranks);
+}
+
+// ---- fine buckets of communicators of 65 to GRID_B members ------------------------------------------------
+// Registers of 64 E members, as in k_seg_multi, on 32-bit offsets from the first record where they fit.
+__device__ __forceinline__ i32 lane_xor63(i32 v) { return (i32)xor_lane_u32<63>((u32)v); }
+template <int E>
+__device__ __forceinline__ void sort_multi32(i32 (&v)[E], u32 lane) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const u32 k = PER * tid + i;
-        v[i] = k < K ? s_n[k] : 0u;
-        gap |= k < K && v[i] == 0;
-        sum += v[i];
-      }
-      u32 tot;
-      u32 ex = block_exclusive_sum<DENSE_THREADS>(sum, s_wave, &tot);
+  for (int r = 0; r < E; ++r) v[r] = sort_groups32<64>(v[r], lane);
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const u32 k = PER * tid + i;
-        if (k < K) s_pre[k] = ex;
-        ex += v[i];
+  for (int kb = 2; kb <= E; kb <<= 1) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      if ((r & (kb >> 1)) == 0) {
+        const int q = r ^ (kb - 1);
+        const i32 b = lane_xor63(v[q]), lo = b < v[r] ? b : v[r], hi = b < v[r] ? v[r] : b;
+        v[r] = lo; v[q] = lane_xor63(hi);
       }
     }
-    __syncthreads();
-    u64 bad = (dup ? (u64)DS_DUPLICATE : 0) | (gap ? (u64)DS_DENSE_FALLBACK : 0);
-    // 3. the collectives
-    const u64 rel0 = D.rel0;
-    const u32 srow0 = D.srow0;
-    if (size <= (u32)SEG_WAVE_MAX) {
-      u32 mine;
-      // from eight members on, a collective's cells are large enough to hold its table row
-      if (size <= 2) mine = dense_wave_batches<2, false>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else if (size <= 4) mine = dense_wave_batches<4, false>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else if (size < 8) mine = dense_wave_batches<8, false>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else if (size == 8) mine = dense_wave_batches<8, true>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else if (size <= 16) mine = dense_wave_batches<16, true>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else if (size <= 32) mine = dense_wave_batches<32, true>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      else mine = dense_wave_batches<64, true>(a, s_cell, s_pres, s_pre, K, size, c, rel0, srow0, rec0, row0, skey, sidx, lane, wave);
-      // the lane's member slot is the same in every pass
-      u32 G = 2; while (G < size) G <<= 1;
-      if (mine) atomicAdd(&s_slot[lane % G], mine);
-    } else {
-      // communicators of more than 64 members: the records are written out in rank order and every
-      // collective goes on the list of the kernels that take long collectives
-      const int mb = a.sf.mb;
-      for (u32 k = wave; k < K; k += DENSE_THREADS / CCLD_WAVE) {
-        const u32 nk = s_n[k];
-        if (nk == 0) continue;
-        const u32 first = rec0 + s_pre[k];
-        u32 run = 0;
-        for (u32 s0 = 0; s0 < size; s0 += CCLD_WAVE) {
-          const u32 slot = s0 + lane, cell = k * size + slot;
-          const bool valid = slot < size && ((s_pres[cell >> 5] >> (cell & 31)) & 1u);
-          const u64 pm = ballot64(valid);
-          if (valid) {
-            const u32 j = first + run + mbcnt64(pm);
-            skey[j] = ((u64)c << (mb + a.sf.ws)) | ((rel0 + k) << mb) | (u64)slot;
-            sidx[j] = row0 + (s_cell[2 * cell + 1].z >> 4);
-            atomicAdd(&s_slot[slot], 1u);
-          }
-          run += (u32)__popcll(pm);
+#pragma unroll
+    for (int jb = kb >> 2; jb >= 1; jb >>= 1)
+#pragma unroll
+      for (int r = 0; r < E; ++r)
+        if ((r & jb) == 0) {
+          const i32 x = v[r], y = v[r | jb];
+          v[r] = y < x ? y : x; v[r | jb] = y < x ? x : y;
         }
-        if (lane == 0) {
-          const u64 at = atomic_add_u64(&a.counters[CNT_NBIG], 1);
-          if (at < a.big_cap) {
-            a.big_list[3 * at] = srow0 + k; a.big_list[3 * at + 1] = first; a.big_list[3 * at + 2] = nk;
-          } else {
-            bad |= (u64)DS_DENSE_FALLBACK;      // more listed collectives than the list holds
-          }
-        }
-      }
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = merge_groups32<64>(v[r], lane);
+  }
+}
+// What a collective of a long communicator leaves for its table row; the times are absolute.
+struct LongRow {
+  i64 stat[2][4];            // arrival, completion: min, lower median, max, MAD
+  i64 imin, dmin, dmax;
+  u64 bytes;
+  u32 n, ninfl, state, op, rmin, rmax;
+};
+// Lower median of |value - median| over the nd smallest values of a sorted sequence at(0), at(1), ... (nd >= 1): see
+// mad_of_sorted
+template <class At>
+__device__ __forceinline__ i64 mad_of(At at, u32 nd) {
+  const u32 km = (nd - 1) / 2;
+  const i64 med = at(km);
+  const u32 nl = km + 1, nr = nd - nl, d = km + 1;
+  auto under = [&](u32 j) { return med - at(km - j); };
+  auto above = [&](u32 j) { return at(km + 1 + j) - med; };
+  u32 lo = d > nr ? d - nr : 0u, hi = d < nl ? d : nl;
+  while (lo < hi) {
+    const u32 mid = (lo + hi) >> 1;
+    if (under(mid) <= above(d - 1 - mid)) lo = mid + 1; else hi = mid;
+  }
+  i64 r = lo > 0 ? under(lo - 1) : INT64_MIN;
+  if (d - lo > 0) { const i64 u = above(d - lo - 1); r = u > r ? u : r; }
+  return r;
+}
+template <int E>
+__device__ __forceinline__ i32 kth_multi32(const i32 (&v)[E], u32 k) {
+  i32 sel = v[0];
+#pragma unroll
+  for (int r = 1; r < E; ++r) if ((k >> 6) == (u32)r) sel = v[r];
+  return __shfl(sel, (int)(k & 63), CCLD_WAVE);
+}
+
+// One wavefront, one collective of up to 64 E members.
+template <int E>
+__device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
+                                          GridShared& S, u32* s_slot, LongRow* out, u32 k, u32 lane) {
+  const u32 size = D.size, *ms = a.members_sorted + a.member_off[D.comm];
+  i64 e[E], x[E];
+  u32 n = 0, ninfl = 0, before[E];
+  bool valid[E], inc = false, wide = false;
+  i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN, ref = 0;
+  u32 rmin = 0xFFFFFFFFu, rmax = 0xFFFFFFFFu, hop = 0;
+  u64 hb = 0;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const u32 slot = r * CCLD_WAVE + lane, cell = k * size + (slot < size ? slot : 0u);
+    valid[r] = slot < size && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
+    const u64 pm = ballot64(valid[r]);
+    before[r] = n + mbcnt64(pm);
+    const uint4 v = S.row[cell];
+    const Rec rec = valid[r] ? unpack_row(v, wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
+    e[r] = rec.t_enter; x[r] = rec.t_exit;
+    if (n == 0 && pm) {        // the first record of the collective
+      const int fl = (int)__builtin_ctzll(pm);
+      hb = shfl_u64(rec.bytes, fl); hop = __shfl(rec.op, fl, CCLD_WAVE); ref = shfl_i64(e[r], fl);
     }
-    if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
-    __syncthreads();
-    // the staged table rows: every wavefront writes whole columns, consecutive lanes to consecutive rows
-    if (size >= 8 && size <= (u32)SEG_WAVE_MAX) {
-      const i64* S = reinterpret_cast<const i64*>(s_cell);
-      for (u32 col = wave; col < STAGE_COLS; col += DENSE_THREADS / CCLD_WAVE) {
-        for (u32 k = lane; k < K; k += CCLD_WAVE) {
-          if (s_n[k] == 0) continue;                   // a round without any record has no row
-          const i64 v = S[k * size * 4 + stage_skew(k) + col];
-          const u32 srow = srow0 + k;
-          if (col < (u32)CCLD_SEG_NCOL) { if (srow < a.seg_cap) a.seg[(u64)col * a.seg_cap + srow] = v; }
-          else if (col == (u32)CCLD_SEG_NCOL) a.gcode[srow] = (uint16_t)v;
-          else a.range_c[srow] = v;
-        }
-      }
-    }
-    // 4. records per rank
-    {
-      const u32* __restrict__ ms = a.members_sorted + a.member_off[c];
-      for (u32 sl = tid; sl < size; sl += DENSE_THREADS) {
-        const u32 v = s_slot[sl];
-        if (v) atomicAdd(&nrec[ms[sl]], (unsigned long long)v);
+    n += (u32)__popcll(pm);
+    inc |= valid[r] && (rec.bytes != hb || rec.op != hop);
+    const bool done = valid[r] && x[r] != T_INFLIGHT;
+    ninfl += (u32)__popcll(ballot64(valid[r] && !done));
+    if (valid[r]) {
+      atomicAdd(&s_slot[slot], 1u);
+      if (a.perm) a.perm[rec0 + S.pre[k] + before[r]] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+      if (!done) {
+        imin = e[r] < imin ? e[r] : imin;
+      } else {
+        const i64 du = x[r] - e[r];
+        const u32 rank = ms[slot];
+        if (du < dmin || (du == dmin && rank < rmin)) { dmin = du; rmin = rank; }
+        if (du > dmax || (du == dmax && rank < rmax)) { dmax = du; rmax = rank; }
+        constexpr i64 LIM = (i64)1 << 30;
+        const u64 oe = (u64)(e[r] - ref) + (u64)LIM, ox = (u64)(x[r] - ref) + (u64)LIM;
+        wide |= oe >= 2 * (u64)LIM || ox >= 2 * (u64)LIM;
       }
     }
   }
+  const bool incons = ballot64(inc) != 0;
+  if (ninfl) imin = reduce_min<64>(imin);
+  reduce_dur<64, false>(dmin, rmin);
+  reduce_dur<64, true>(dmax, rmax);
+  const u32 nd = n - ninfl, km = nd ? (nd - 1) / 2 : 0, kl = nd ? nd - 1 : 0;
+  i64 st_min[2] = {0, 0}, st_med[2] = {0, 0}, st_max[2] = {0, 0}, st_mad[2] = {0, 0};
+  const bool rel = ballot64(wide) == 0;
+#pragma unroll 1
+  for (int w = 0; w < 2; ++w) {                  // 0 arrival, 1 completion
+    if (nd == 0) break;
+    if (rel) {
+      i32 v[E];
+#pragma unroll
+      for (int r = 0; r < E; ++r) v[r] = x[r] != T_INFLIGHT ? (i32)((w ? x[r] : e[r]) - ref) : REL_NONE;
+      sort_multi32<E>(v, lane);
+      st_min[w] = ref + kth_multi32<E>(v, 0); st_med[w] = ref + kth_multi32<E>(v, km); st_max[w] = ref + kth_multi32<E>(v, kl);
+      st_mad[w] = mad_of([&](u32 i) -> i64 { return (i64)kth_multi32<E>(v, i); }, nd);
+    } else {
+      i64 v[E];
+#pragma unroll
+      for (int r = 0; r < E; ++r) v[r] = x[r] != T_INFLIGHT ? (w ? x[r] : e[r]) : T_INFLIGHT;
+      sort_multi<E>(v, lane);
+      st_min[w] = kth_multi<E>(v, 0); st_med[w] = kth_multi<E>(v, km); st_max[w] = kth_multi<E>(v, kl);
+      st_mad[w] = mad_of_sorted<E>(v, nd, km);
+    }
+  }
+  const bool complete = n == size && ninfl == 0;
+  const bool barrier = hop == CCLD_OP_ALLREDUCE && hb < (u64)a.barrier_bytes;
+  const bool usable = complete && !incons && !barrier;
+  if (lane == 0) {
+    LongRow& R = out[k];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) { R.stat[w][0] = st_min[w]; R.stat[w][1] = st_med[w]; R.stat[w][2] = st_max[w]; R.stat[w][3] = st_mad[w]; }
+    R.imin = imin; R.dmin = dmin; R.dmax = dmax; R.bytes = hb; R.n = n; R.ninfl = ninfl; R.op = hop; R.rmin = rmin; R.rmax = rmax;
+    R.state = (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) | (barrier ? CCLD_SEG_BARRIER : 0) |
+              (usable ? CCLD_SEG_USABLE : 0);
+  }
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    if (!valid[r]) continue;
+    i64 le = 0, lx = 0;
+    u32 f = 0;
+    if (usable) {
+      le = e[r] - st_med[0]; lx = x[r] - st_med[1];
+      if (is_late(le, a.lag_floor, a.kmad_num, a.kmad_den, st_mad[0])) f |= CCLD_FLAG_LATE_ENTER;
+      if (is_late(lx, a.lag_floor, a.kmad_num, a.kmad_den, st_mad[1])) f |= CCLD_FLAG_LATE_EXIT;
+    }
+    grid_put_record(a, rec0 + S.pre[k] + before[r], k * size + r * CCLD_WAVE + lane, rec0, &S.flags, f, le, lx);
+  }
 }
 
-// the collectives on the list (more than 64 records; from the dense placement also shorter ones)
-static void launch_seg_listed(hipStream_t st, const SegArgs& a, bool with_short) {
+// A workgroup takes the fine buckets on the list in turn.  Collectives of up to 512 members go to a wavefront each; the
+// larger ones (at most three in a bucket) are taken by the whole workgroup, one after the other: their times are sorted
+// in LDS, the median of the deviations is selected from the sorted sequence.
+constexpr u32 LONG_ROUNDS = GRID_B / (SEG_WAVE_MAX + 1);        // most rounds of such a bucket
+__global__ __launch_bounds__(SEG_THREADS) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+  __shared__ GridShared S;
+  __shared__ i64 s_v[GRID_B];                  // the larger collectives' sort
+  __shared__ u32 s_slot[GRID_B];
+  __shared__ LongRow s_out[LONG_ROUNDS];
+  __shared__ TeamAcc s_acc;
+  __shared__ u32 s_first;
+  constexpr u32 NW = SEG_THREADS / CCLD_WAVE, U = GRID_B / SEG_THREADS;
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  if (d.hdr->feasible == 0) return;
+  const u32 n_long = d.hdr->n_long;
+  const i64 wref = d.hdr->ref;
+  for (u32 ent = blockIdx.x; ent < n_long; ent += gridDim.x) {
+    const u32 f = d.long_list[ent];
+    const FineDesc D = d.desc[f];
+    const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size, K = D.K;
+    for (u32 i = tid; i < size; i += SEG_THREADS) s_slot[i] = 0;
+    const u64 bad = grid_place<SEG_THREADS>(d, D, cnt, S);
+    if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
+    if (size <= (u32)SEG_MULTI_MAX) {
+      for (u32 k = wave; k < K; k += NW) {
+        if (size <= 128) long_wave<2>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
+        else if (size <= 256) long_wave<4>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
+        else long_wave<8>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
+      }
+      __syncthreads();
+    } else {
+      for (u32 k = 0; k < K; ++k) {
+        if (tid == 0) {
+          s_acc.imin = (unsigned long long)T_INFLIGHT; s_acc.dmin = INT64_MAX; s_acc.dmax = INT64_MIN;
+          s_acc.ninfl = 0; s_acc.incons = 0; s_acc.rmin = 0xFFFFFFFFu; s_acc.rmax = 0xFFFFFFFFu;
+          s_first = 0xFFFFFFFFu;
+        }
+        __syncthreads();
+        // consecutive slots per thread, so that a record's place among the present ones is one scan away
+        Rec rec[U];
+        bool valid[U];
+        u32 here = 0, first_slot = 0xFFFFFFFFu;
+#pragma unroll
+        for (u32 u = 0; u < U; ++u) {
+          const u32 slot = tid * U + u, cell = k * size + slot;
+          valid[u] = slot < size && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
+          rec[u] = valid[u] ? unpack_row(S.row[cell], wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
+          if (valid[u]) { ++here; if (first_slot == 0xFFFFFFFFu) first_slot = slot; }
+        }
+        if (here) atomicMin(&s_first, first_slot);
+        u32 n;
+        const u32 before = block_exclusive_sum<SEG_THREADS>(here, S.wave, &n);
+        const Rec h = n ? unpack_row(S.row[k * size + s_first], wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
+        {
+          u32 ni = 0, rmin = 0xFFFFFFFFu, rmax = 0xFFFFFFFFu;
+          bool inc = false;
+          i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN;
+#pragma unroll
+          for (u32 u = 0; u < U; ++u) {
+            if (!valid[u]) continue;
+            inc |= rec[u].op != h.op || rec[u].bytes != h.bytes;
+            s_slot[tid * U + u] += 1;
+            if (rec[u].t_exit == T_INFLIGHT) {
+              ++ni; imin = rec[u].t_enter < imin ? rec[u].t_enter : imin;
+            } else {
+              const i64 du = rec[u].t_exit - rec[u].t_enter;      // slots ascend with the ranks: ties keep the first
+              if (du < dmin) { dmin = du; rmin = tid * U + u; }
+              if (du > dmax) { dmax = du; rmax = tid * U + u; }
+            }
+          }
+          if (ni) { atomicAdd(&s_acc.ninfl, ni); atomicMin(&s_acc.imin, (unsigned long long)imin); }
+          if (inc) atomicOr(&s_acc.incons, 1u);
+          if (rmin != 0xFFFFFFFFu) { atomicMin(&s_acc.dmin, (long long)dmin); atomicMax(&s_acc.dmax, (long long)dmax); }
+          __syncthreads();
+          if (rmin != 0xFFFFFFFFu && dmin == (i64)s_acc.dmin) atomicMin(&s_acc.rmin, rmin);
+          if (rmax != 0xFFFFFFFFu && dmax == (i64)s_acc.dmax) atomicMin(&s_acc.rmax, rmax);
+        }
+        const u32 ninfl = s_acc.ninfl, nd = n - ninfl, km = nd ? (nd - 1) / 2 : 0, kl = nd ? nd - 1 : 0;
+        u32 P = 2;
+        while (P < size) P <<= 1;
+        i64 stat[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+        for (int w = 0; w < 2; ++w) {
+          if (nd == 0) break;                          // uniform
+#pragma unroll
+          for (u32 u = 0; u < U; ++u) {
+            const u32 i = tid * U + u;
+            if (i < P) s_v[i] = valid[u] && rec[u].t_exit != T_INFLIGHT ? (w ? rec[u].t_exit : rec[u].t_enter) : T_INFLIGHT;
+          }
+          __syncthreads();
+          team_sort(s_v, P, tid);
+          stat[w][0] = s_v[0]; stat[w][1] = s_v[km]; stat[w][2] = s_v[kl];
+          stat[w][3] = mad_of([&](u32 i) -> i64 { return s_v[i]; }, nd);
+          __syncthreads();
+        }
+        const bool complete = n == size && ninfl == 0;
+        const bool consistent = s_acc.incons == 0;
+        const bool barrier = h.op == CCLD_OP_ALLREDUCE && h.bytes < (u64)a.barrier_bytes;
+        const bool usable = complete && consistent && !barrier;
+        if (tid == 0) {
+          const u32* ms = a.members_sorted + a.member_off[D.comm];
+          LongRow& R = s_out[k];
+          for (int w = 0; w < 2; ++w) for (int q = 0; q < 4; ++q) R.stat[w][q] = stat[w][q];
+          R.imin = (i64)s_acc.imin; R.dmin = s_acc.dmin; R.dmax = s_acc.dmax; R.bytes = h.bytes; R.n = n; R.ninfl = ninfl; R.op = h.op;
+          R.rmin = nd ? ms[s_acc.rmin] : CCLD_NO_RANK; R.rmax = nd ? ms[s_acc.rmax] : CCLD_NO_RANK;
+          R.state = (complete ? CCLD_SEG_COMPLETE : 0) | (consistent ? CCLD_SEG_CONSISTENT : 0) | (barrier ? CCLD_SEG_BARRIER : 0) |
+                    (usable ? CCLD_SEG_USABLE : 0);
+        }
+        u32 j = rec0 + S.pre[k] + before;
+#pragma unroll
+        for (u32 u = 0; u < U; ++u) {
+          if (!valid[u]) continue;
+          i64 le = 0, lx = 0;
+          u32 fl = 0;
+          if (usable) {
+            le = rec[u].t_enter - stat[0][1]; lx = rec[u].t_exit - stat[1][1];
+            if (is_late(le, a.lag_floor, a.kmad_num, a.kmad_den, stat[0][3])) fl |= CCLD_FLAG_LATE_ENTER;
+            if (is_late(lx, a.lag_floor, a.kmad_num, a.kmad_den, stat[1][3])) fl |= CCLD_FLAG_LATE_EXIT;
+          }
+          const u32 cell = k * size + tid * U + u;
+          if (a.perm) a.perm[j] = grid_arrival(a, d, D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+          grid_put_record(a, j, cell, rec0, &S.flags, fl, le, lx);
+          ++j;
+        }
+        __syncthreads();     // the accumulator and the sort array are reused by the next round
+      }
+    }
+    __syncthreads();
+    if (tid == 0) d.nflag[f] = S.flags.n;
+    grid_order_flags<SEG_THREADS>(a, D, rec0, S.flags, S.wave, blame, n_ranks);
+    // the table rows: a lane per round, a column at a time
+    for (u32 col = wave; col < STAGE_COLS; col += NW) {
+      const u32 k = lane;
+      if (k >= K) continue;
+      const LongRow& R = s_out[k];
+      const u32 srow = D.srow0 + k;
+      const bool none = R.n == R.ninfl, usable = (R.state & CCLD_SEG_USABLE) != 0;
+      const bool barrier = (R.state & CCLD_SEG_BARRIER) != 0;
+      if (col == (u32)CCLD_SEG_NCOL) { a.gcode[srow] = (uint16_t)seg_group_code(usable, R.op, R.bytes); continue; }
+      if (col == (u32)CCLD_SEG_NCOL + 1) { a.range_c[srow] = usable ? R.dmax - R.dmin : 0; seg_count_alert(a, srow, R.ninfl, barrier, R.imin); continue; }
+      i64 v = 0;
+      switch (col) {
+        case CCLD_SEG_COMM: v = (i64)D.comm; break;
+        case CCLD_SEG_SEQ: v = (i64)(D.seq0 + k); break;
+        case CCLD_SEG_N: v = (i64)R.n; break;
+        case CCLD_SEG_INFLIGHT: v = (i64)R.ninfl; break;
+        case CCLD_SEG_STATE: v = (i64)R.state; break;
+        case CCLD_SEG_OP: v = (i64)R.op; break;
+        case CCLD_SEG_BYTES: v = (i64)R.bytes; break;
+        case CCLD_SEG_DUR_MIN: v = none ? 0 : R.dmin; break;
+        case CCLD_SEG_DUR_MAX: v = none ? 0 : R.dmax; break;
+        case CCLD_SEG_ARGMIN_RANK: v = none ? (i64)CCLD_NO_RANK : (i64)R.rmin; break;
+        case CCLD_SEG_ARGMAX_RANK: v = none ? (i64)CCLD_NO_RANK : (i64)R.rmax; break;
+        case CCLD_SEG_INFLIGHT_ENTER_MIN: v = R.imin; break;
+        case CCLD_SEG_FIRST: v = (i64)(rec0 + S.pre[k]); break;
+        default: v = none ? 0 : R.stat[(col - CCLD_SEG_ENTER_MIN) >> 2][(col - CCLD_SEG_ENTER_MIN) & 3]; break;
+      }
+      seg_put(a, (int)col, srow, v);
+    }
+    unsigned long long* nrec = (unsigned long long*)(blame + (u64)CCLD_BLM_N_RECORDS * n_ranks);
+    for (u32 i = tid; i < size; i += SEG_THREADS)
+      if (s_slot[i]) atomicAdd(&nrec[a.members_sorted[a.member_off[D.comm] + i]], (unsigned long long)s_slot[i]);
+    __syncthreads();     // LDS is reused by the next bucket
+  }
+}
+static_assert(LONG_ROUNDS <= CCLD_WAVE, "a lane per round");
+static_assert(CCLD_SEG_ENTER_MIN == 7 && CCLD_SEG_EXIT_MIN == 11 && CCLD_SEG_DUR_MIN == 15, "four columns of arrival, four of completion");
+
+// the collectives on the list (more than 64 records)
+static void launch_seg_listed(hipStream_t st, const SegArgs& a) {
   // a collective has at most as many records as its communicator has members (a longer one holds a
   // duplicate, which ends the analysis with an error): size classes that cannot occur are not launched
   const uint32_t m = a.max_size;
   if (m <= (uint32_t)SEG_WAVE_MAX) return;
   hipLaunchKernelGGL(k_seg_lengths, dim3(1024), dim3(SEG_THREADS), 0, st, a);
-  if (with_short) hipLaunchKernelGGL(k_seg_multi<1>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   hipLaunchKernelGGL(k_seg_multi<2>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   if (m > 128) hipLaunchKernelGGL(k_seg_multi<4>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   if (m > 256) hipLaunchKernelGGL(k_seg_multi<8>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
@@ -1403,17 +1844,15 @@ static void launch_seg_listed(hipStream_t st, const SegArgs& a, bool with_short)
   if (m > (uint32_t)SEG_MULTI_MAX) hipLaunchKernelGGL(k_seg_group_listed, dim3(256), dim3(256), 0, st, a);
 }
 
-void launch_dense_stats(hipStream_t st, const SegArgs& a, const DenseArgs& d, uint32_t n_fine, uint64_t* skey,
-                        uint32_t* sidx, int64_t* blame, uint32_t n_ranks) {
-  if (a.n == 0 || n_fine == 0) return;
-  hipLaunchKernelGGL(k_dense_stats, dim3(n_fine), dim3(DENSE_THREADS), 0, st, a, d, skey, sidx, blame, n_ranks);
-  launch_seg_listed(st, a, true);
+void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks) {
+  if (fine_bound) hipLaunchKernelGGL(k_grid_stats, dim3(fine_bound), dim3(GRID_THREADS), 0, st, a, d, blame, n_ranks);
+  if (a.max_size > (uint32_t)SEG_WAVE_MAX) hipLaunchKernelGGL(k_grid_long, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
 }
 
 void launch_seg_analyze(hipStream_t st, const SegArgs& a) {
   if (a.n == 0) return;
   hipLaunchKernelGGL(k_seg_wave, dim3((a.n + SEG_TILE - 1) / SEG_TILE), dim3(SEG_THREADS), 0, st, a);
-  launch_seg_listed(st, a, false);
+  launch_seg_listed(st, a);
 }
 
 }  // namespace ccld

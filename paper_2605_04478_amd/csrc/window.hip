@@ -4,6 +4,8 @@
 // sort in radix_sort.hip.
 #include "window_kernels.h"
 #include "device_utils.h"
+#include "grid.h"
+#include "rows.h"
 #include "select.h"
 
 namespace ccld {
@@ -34,51 +36,72 @@ void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Ingest: validate each record, key it by Trace ID (communicator id, operation counter) plus
-// rank, store key and payload row at the window's tail.
-// Records per communicator bucket in each workgroup's slice of the batch (first half of the
-// two-step placement below).
-// With RANGE the kernel also reads the operation counters and leaves, per communicator, the batch's
-// largest counter and the largest complement of one (i.e. ~smallest) in a.range (zeroed before): the
-// dense placement lays the window out from these.
-template <bool RANGE>
+// Ingest: validate each record, key it by Trace ID (communicator id, operation counter) plus member slot, pack its
+// payload into a 16-byte row (rows.h) and store both at the window's tail.  Small windows keep the order of arrival; in
+// large ones a batch's records are placed grouped by communicator bucket, so that the grid placement, which takes the
+// window bucket by bucket, meets few fine buckets at a time.
+//
+// Every kernel also leaves, per communicator, the batch's largest operation counter and largest complement of one (i.e.
+// ~smallest) in a.range: the grid is laid out from these.  The header and the ranges of a batch start from zero: the
+// ingest of the batch before cleared them (clear_next), the first ones were cleared at create.
+__device__ __forceinline__ void clear_next(const IngestArgs& a, u32 n_comms, u32 tid, u32 threads) {
+  if (blockIdx.x == 0 && tid == 0) {
+    BatchMeta z = {0, 0, 0, 0, 0, 0};
+    *a.meta_next = z;
+  }
+  if (a.range_next)
+    for (u64 i = (u64)blockIdx.x * threads + tid; i < 2ull * n_comms; i += (u64)gridDim.x * threads) a.range_next[i] = 0;
+}
+// what is known of the batch before its first record is read
+__device__ __forceinline__ void put_header(const IngestArgs& a, i64 ref) {
+  a.meta->ref = ref; a.meta->tail = a.tail; a.meta->n = a.n;
+}
+
+// Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Small
+// tables are scanned by the last workgroup to finish.
+constexpr u32 INGEST_SCAN_WORDS = 8192;
 __global__ __launch_bounds__(256) void k_ingest_hist(IngestArgs a, u32 n_comms) {
-  extern __shared__ u32 s_cnt[];
-  // [n_buckets] counts, then (RANGE) [n_comms][2] extreme counters, 8-byte aligned
-  unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_cnt + ((a.n_buckets + 1) & ~1u));
+  extern __shared__ u32 s_cnt[];        // [n_buckets]
+  __shared__ u32 s_wave[4], s_last;
   for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) s_cnt[b] = 0;
-  if (RANGE) for (u32 i = threadIdx.x; i < 2 * n_comms; i += 256) s_rng[i] = 0;
-  // the batch's header starts from zero (the placement kernel, next on the stream, accumulates into it)
-  if (blockIdx.x == 0 && threadIdx.x == 0) { a.meta->status = 0; a.meta->max_seq = 0; a.meta->max_inv_seq = 0; a.meta->pad = 0; }
   __syncthreads();
   const u64 chunk = a.chunk / a.hist_split;
   const u64 i_end = (chunk * (blockIdx.x + 1)) < a.n ? chunk * (blockIdx.x + 1) : a.n;
   const u32* __restrict__ in_comm = a.comm;
-  const u64* __restrict__ in_seq = a.seq;
   for (u64 i0 = chunk * blockIdx.x + threadIdx.x; i0 < i_end; i0 += 256 * 8) {
     u32 c[8];
-    u64 q[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const bool on = i0 + (u64)u * 256 < i_end;
       c[u] = on ? __builtin_nontemporal_load(in_comm + i0 + (u64)u * 256) : 0xFFFFFFFFu;
-      if (RANGE) q[u] = on ? __builtin_nontemporal_load(in_seq + i0 + (u64)u * 256) : 0ull;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (i0 + (u64)u * 256 < i_end) {
-        atomicAdd(&s_cnt[c[u] < n_comms ? (c[u] >> a.bshift) : 0u], 1u);
-        if (RANGE && c[u] < n_comms) {
-          atomicMax(&s_rng[2 * c[u]], (unsigned long long)q[u]);
-          atomicMax(&s_rng[2 * c[u] + 1], (unsigned long long)~q[u]);
-        }
-      }
+      if (i0 + (u64)u * 256 < i_end) atomicAdd(&s_cnt[c[u] < n_comms ? (c[u] >> a.bshift) : 0u], 1u);
   }
   __syncthreads();
-  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) a.table[(u64)b * gridDim.x + blockIdx.x] = s_cnt[b];
-  if (RANGE)
-    for (u32 i = threadIdx.x; i < 2 * n_comms; i += 256)
-      if (s_rng[i]) atomicMax((unsigned long long*)&a.range[i], s_rng[i]);
+  const u32 g = gridDim.x;
+  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) store_agent(&a.table[(u64)b * g + blockIdx.x], s_cnt[b]);
+  if (a.n_buckets * g > INGEST_SCAN_WORDS) return;
+  if (!last_block(a.done, g, &s_last)) return;
+  if (threadIdx.x == 0) *a.done = 0;
+  // bucket by bucket: the counts of the workgroups become offsets inside the bucket, then the buckets' starts
+  u32 carry = 0;
+  for (u32 b = 0; b < a.n_buckets; ++b) {
+    u32* row = a.table + (u64)b * g;
+    u32 in_bucket = 0;
+    for (u32 i0 = 0; i0 < g; i0 += 256) {
+      const u32 i = i0 + threadIdx.x;
+      const u32 v = i < g ? load_agent(&row[i]) : 0u;
+      u32 tot;
+      const u32 ex = block_exclusive_sum<256>(v, s_wave, &tot);
+      if (i < g) row[i] = in_bucket + ex;
+      in_bucket += tot;
+    }
+    if (threadIdx.x == 0) a.bucket_base[b] = carry;
+    carry += in_bucket;
+  }
+  if (threadIdx.x == 0) a.bucket_base[a.n_buckets] = carry;
 }
 // exclusive scan of every bucket's row of per-workgroup counts (row length <= 2048)
 __global__ __launch_bounds__(256) void k_ingest_scan(u32* table, u32* totals, u32 n_blocks) {
@@ -127,10 +150,11 @@ __device__ __forceinline__ u64 ingest_key(u32 r, u32 c, u64 sq, u32 op, i64 te, 
   return key;
 }
 
-// status bits and the extreme operation counters of a workgroup leave through one set of atomics
+// status bits and the extreme operation counters of a workgroup leave through one set of atomics, its counter ranges
+// per communicator (s_rng: [n_comms][2], null if nobody wants them) through one pair per communicator that it met
 template <int THREADS>
 __device__ __forceinline__ void ingest_publish(u64 status, u64 maxseq, u64 maxinv, u64* s_status, u64* s_max,
-                                               u64* s_inv, BatchMeta* meta) {
+                                               u64* s_inv, const IngestArgs& a, const unsigned long long* s_rng, u32 n_comms) {
   u64 st = status;
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) st |= shfl_xor_u64(st, m);
@@ -143,48 +167,40 @@ __device__ __forceinline__ void ingest_publish(u64 status, u64 maxseq, u64 maxin
     for (int w = 0; w < THREADS / CCLD_WAVE; ++w) {
       S |= s_status[w]; M = s_max[w] > M ? s_max[w] : M; I = s_inv[w] > I ? s_inv[w] : I;
     }
-    if (S) atomic_or_u64(&meta->status, S);
-    if (M) atomicMax((unsigned long long*)&meta->max_seq, (unsigned long long)M);
-    if (I) atomicMax((unsigned long long*)&meta->max_inv_seq, (unsigned long long)I);
+    if (S) atomic_or_u64(&a.meta->status, S);
+    if (M) atomicMax((unsigned long long*)&a.meta->max_seq, (unsigned long long)M);
+    if (I) atomicMax((unsigned long long*)&a.meta->max_inv_seq, (unsigned long long)I);
   }
+  if (a.range)
+    for (u32 i = threadIdx.x; i < 2 * n_comms; i += THREADS)
+      if (s_rng[i]) atomicMax((unsigned long long*)&a.range[i], s_rng[i]);
+}
+// the counter range of a record's communicator: after the first few records of a communicator neither end moves, so the
+// entries are read before they are raised
+__device__ __forceinline__ void note_range(unsigned long long* s_rng, u32 c, u64 seq) {
+  const unsigned long long hi = seq, lo = ~seq;
+  if (hi > s_rng[2 * c]) atomicMax(&s_rng[2 * c], hi);
+  if (lo > s_rng[2 * c + 1]) atomicMax(&s_rng[2 * c + 1], lo);
 }
 
-// Validates and keys every record and stores it in the window.  Inside the batch's slot range the
-// records are placed grouped by communicator bucket (the order inside a bucket is arbitrary), so
-// that the analysis, which walks the window in (communicator, ...) order, gathers its payload rows
-// from a small region at a time instead of from the whole window.
-// THREADS = 512 with LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS (16 bytes per
-// rank): with records in random order that lookup is a gather with no locality, cheaper from LDS
-// than from the L2.
-template <int THREADS, bool LDS_TABLE>
+// Windows that keep the order of arrival: slot = tail + number in the batch.  Small batches: one launch, a few records
+// per thread.
+template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 4;               // records per thread in flight
-  extern __shared__ uint4 s_dyn[];   // [n_ranks] membership rows (LDS_TABLE), then the buckets' next free slots
+  extern __shared__ unsigned long long s_rng[];   // [n_comms][2] if a.range
   __shared__ u64 s_status[THREADS / CCLD_WAVE], s_max[THREADS / CCLD_WAVE], s_inv[THREADS / CCLD_WAVE];
-  u32* s_off = reinterpret_cast<u32*>(s_dyn + (LDS_TABLE ? T.n_ranks : 0u));
-  for (u32 b = threadIdx.x; b < a.n_buckets; b += THREADS)
-    s_off[b] = a.bucket_base[b] + a.table[((u64)b * gridDim.x + blockIdx.x) * a.hist_split];
-  if (LDS_TABLE) {
-    const uint4* __restrict__ g = reinterpret_cast<const uint4*>(T.rank_memb4);
-    for (u32 r = threadIdx.x; r < T.n_ranks; r += THREADS) s_dyn[r] = g[r];
-  }
+  if (a.range) for (u32 i = threadIdx.x; i < 2 * T.n_comms; i += THREADS) s_rng[i] = 0;
+  const i64 ref = a.t_enter[0];
+  clear_next(a, T.n_comms, threadIdx.x, THREADS);
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_header(a, ref);
   __syncthreads();
   u64 status = 0, maxseq = 0, maxinv = 0;      // maxinv = ~(smallest operation counter)
-  const u32* __restrict__ in_rank = a.rank;
-  const u32* __restrict__ in_comm = a.comm;
-  const u64* __restrict__ in_seq = a.seq;
-  const uint8_t* __restrict__ in_op = a.op;
-  const u64* __restrict__ in_bytes = a.bytes;
-  const i64* __restrict__ in_te = a.t_enter;
-  const i64* __restrict__ in_tx = a.t_exit;
-  u64* __restrict__ out_key = a.win_key;
-  Row* __restrict__ out_row = a.win_row;
   const uint4* __restrict__ memb4 = reinterpret_cast<const uint4*>(T.rank_memb4);
   const u32 slot_mask = kf.mb < 32 ? (1u << kf.mb) - 1 : ~0u;
-  // every workgroup walks one contiguous slice of the batch, so its nine streams advance page by page
-  const u64 chunk = a.chunk;
-  const u64 i_end = (chunk * (blockIdx.x + 1)) < a.n ? chunk * (blockIdx.x + 1) : a.n;
-  for (u64 i0 = chunk * blockIdx.x + threadIdx.x; i0 < i_end; i0 += THREADS * U) {
+  // every workgroup walks one contiguous slice of the batch
+  const u64 i_end = (a.chunk * (blockIdx.x + 1)) < a.n ? a.chunk * (blockIdx.x + 1) : a.n;
+  for (u64 i0 = a.chunk * blockIdx.x + threadIdx.x; i0 < i_end; i0 += THREADS * U) {
     u32 r[U], c[U], op[U];
     u64 sq[U], nb[U];
     i64 te[U], tx[U];
@@ -193,10 +209,10 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
     for (int u = 0; u < U; ++u) {
       const u64 i = i0 + (u64)u * THREADS;
       if (i < i_end) {
-        r[u] = __builtin_nontemporal_load(in_rank + i); c[u] = __builtin_nontemporal_load(in_comm + i);
-        sq[u] = __builtin_nontemporal_load(in_seq + i); op[u] = __builtin_nontemporal_load(in_op + i);
-        nb[u] = __builtin_nontemporal_load(in_bytes + i);
-        te[u] = __builtin_nontemporal_load(in_te + i); tx[u] = __builtin_nontemporal_load(in_tx + i);
+        r[u] = __builtin_nontemporal_load(a.rank + i); c[u] = __builtin_nontemporal_load(a.comm + i);
+        sq[u] = __builtin_nontemporal_load(a.seq + i); op[u] = __builtin_nontemporal_load(a.op + i);
+        nb[u] = __builtin_nontemporal_load(a.bytes + i);
+        te[u] = __builtin_nontemporal_load(a.t_enter + i); tx[u] = __builtin_nontemporal_load(a.t_exit + i);
       }
     }
     // the communicators of each rank with its member slot in each: one 16-byte row of words
@@ -204,7 +220,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       mem[u] = make_uint4(~0u, ~0u, ~0u, ~0u);
-      if (i0 + (u64)u * THREADS < i_end && memb4 && r[u] < T.n_ranks) mem[u] = LDS_TABLE ? s_dyn[r[u]] : memb4[r[u]];
+      if (i0 + (u64)u * THREADS < i_end && memb4 && r[u] < T.n_ranks) mem[u] = memb4[r[u]];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -212,35 +228,39 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
       if (i >= i_end) continue;
       const u64 key = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem[u], memb4, T, kf, slot_mask, status, maxseq,
                                  maxinv);
-      const u32 at = atomicAdd(&s_off[c[u] < T.n_comms ? (c[u] >> a.bshift) : 0u], 1u);
-      u64 p = (u64)a.tail + at;
+      if (a.range && c[u] < T.n_comms) note_range(s_rng, c[u], sq[u]);
+      u64 p = (u64)a.tail + i;
       if (p >= a.cap) p -= a.cap;
-      out_key[p] = key;
-      Row rw;
-      rw.t_enter = te[u]; rw.t_exit = tx[u]; rw.bytes = nb[u]; rw.op = op[u];
-      rw.pad = a.seqno0 + (u32)i;          // arrival number of the record (modulo 2^32)
-      out_row[p] = rw;
+      a.win_key[p] = key;
+      uint4 row;
+      if (!pack_row(te[u], tx[u], nb[u], op[u], ref, (u32)p, &row)) {
+        a.win_wide[3 * p] = te[u]; a.win_wide[3 * p + 1] = tx[u]; a.win_wide[3 * p + 2] = (i64)nb[u];
+      }
+      a.win_row[p] = row;
     }
   }
-  ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a.meta);
+  ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a, s_rng, T.n_comms);
 }
-// Large batches: the same placement with the write-out regrouped in LDS.  A workgroup takes CHUNK
-// records per round, gives each its slot in its bucket (LDS atomic, as above), then stages keys and
-// rows in LDS ordered by (bucket, slot) and writes them out with consecutive lanes on consecutive
-// 16-byte pieces: every bucket's share of the round leaves as one contiguous run instead of one
-// scattered 40-byte store per lane.  At most INGEST_STAGED_BUCKETS buckets.
+// Windows placed by bucket.  A workgroup takes CHUNK records per round, gives each its slot in its bucket (LDS atomic),
+// then stages keys, rows and arrival numbers in LDS ordered by (bucket, slot) and writes them out with consecutive lanes
+// on consecutive pieces: every bucket's share of the round leaves as one contiguous run instead of one scattered store
+// per lane.  LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS: with records in random order that
+// lookup is a gather with no locality, cheaper from LDS than from the L2.
+// At most INGEST_STAGED_BUCKETS buckets.
 template <int THREADS, bool LDS_TABLE>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
   constexpr u32 CHUNK = THREADS * U;
-  // [n_ranks] membership rows (LDS_TABLE) | [2 CHUNK] row halves | [CHUNK] keys | [CHUNK] window slots
+  // [n_ranks] membership rows (LDS_TABLE) | [CHUNK] rows | [CHUNK] keys | [n_comms][2] ranges | [CHUNK] window slots | [CHUNK] numbers in the round
   extern __shared__ uint4 s_dyn[];
   __shared__ u64 s_status[THREADS / CCLD_WAVE], s_max[THREADS / CCLD_WAVE], s_inv[THREADS / CCLD_WAVE];
   __shared__ u32 s_off[INGEST_STAGED_BUCKETS], s_start[INGEST_STAGED_BUCKETS], s_pre[INGEST_STAGED_BUCKETS], s_total;
   __shared__ u32 s_scan[THREADS / CCLD_WAVE];
   uint4* s_row = s_dyn + (LDS_TABLE ? T.n_ranks : 0u);
-  u64* s_key = reinterpret_cast<u64*>(s_row + 2 * CHUNK);
-  u32* s_p = reinterpret_cast<u32*>(s_key + CHUNK);
+  u64* s_key = reinterpret_cast<u64*>(s_row + CHUNK);
+  unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + CHUNK);
+  u32* s_p = reinterpret_cast<u32*>(s_rng + (a.range ? 2 * T.n_comms : 0u));
+  unsigned short* s_num = reinterpret_cast<unsigned short*>(s_p + CHUNK);
   const u32 tid = threadIdx.x;
   if (tid < a.n_buckets) {
     const u32 o = a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
@@ -250,6 +270,10 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
     const uint4* __restrict__ g = reinterpret_cast<const uint4*>(T.rank_memb4);
     for (u32 r = tid; r < T.n_ranks; r += THREADS) s_dyn[r] = g[r];
   }
+  if (a.range) for (u32 i = tid; i < 2 * T.n_comms; i += THREADS) s_rng[i] = 0;
+  const i64 ref = a.t_enter[0];
+  clear_next(a, T.n_comms, tid, THREADS);
+  if (blockIdx.x == 0 && tid == 0) put_header(a, ref);
   __syncthreads();
   u64 status = 0, maxseq = 0, maxinv = 0;
   const u32* __restrict__ in_rank = a.rank;
@@ -260,7 +284,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   const i64* __restrict__ in_te = a.t_enter;
   const i64* __restrict__ in_tx = a.t_exit;
   u64* __restrict__ out_key = a.win_key;
-  uint4* __restrict__ out_row = reinterpret_cast<uint4*>(a.win_row);
+  uint4* __restrict__ out_row = a.win_row;
   const uint4* __restrict__ memb4 = reinterpret_cast<const uint4*>(T.rank_memb4);
   const u32 slot_mask = kf.mb < 32 ? (1u << kf.mb) - 1 : ~0u;
   const u64 i_begin = a.chunk * blockIdx.x;
@@ -295,6 +319,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       uint4 mem = make_uint4(~0u, ~0u, ~0u, ~0u);
       if (memb4 && r[u] < T.n_ranks) mem = LDS_TABLE ? s_dyn[r[u]] : memb4[r[u]];
       key[u] = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem, memb4, T, kf, slot_mask, status, maxseq, maxinv);
+      if (a.range && c[u] < T.n_comms) note_range(s_rng, c[u], sq[u]);
       bk[u] = c[u] < T.n_comms ? (c[u] >> a.bshift) : 0u;
       at[u] = atomicAdd(&s_off[bk[u]], 1u);
     }
@@ -323,37 +348,36 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       u64 p = (u64)a.tail + at[u];
       if (p >= a.cap) p -= a.cap;
       s_p[q] = (u32)p;
+      s_num[q] = (unsigned short)((u32)u * THREADS + tid);
       s_key[q] = key[u];
-      const u64 last = (u64)op[u] | ((u64)(a.seqno0 + (u32)(base + (u64)u * THREADS + tid)) << 32);   // op, arrival number
-      s_row[2 * q] = make_uint4((u32)te[u], (u32)((u64)te[u] >> 32), (u32)tx[u], (u32)((u64)tx[u] >> 32));
-      s_row[2 * q + 1] = make_uint4((u32)nb[u], (u32)(nb[u] >> 32), (u32)last, (u32)(last >> 32));
+      uint4 row;
+      if (!pack_row(te[u], tx[u], nb[u], op[u], ref, (u32)p, &row)) {
+        a.win_wide[3 * p] = te[u]; a.win_wide[3 * p + 1] = tx[u]; a.win_wide[3 * p + 2] = (i64)nb[u];
+      }
+      s_row[q] = row;
     }
     __syncthreads();
-    const u32 total = s_total;
+    const u32 total = s_total, num0 = a.seqno0 + (u32)base;
     // Pieces of a line that this round writes completely leave with the streaming hint: they do not stay in
     // the L2, where they would displace the partially written lines at the buckets' frontiers before the
     // next round completes them.
     {
       typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-      for (u32 i = tid; i < 2 * total; i += THREADS) {
-        const u64 D = 2ull * s_p[i >> 1] + (i & 1);
-        const u32 o = (u32)(D & 7);
-        bool full = false;
-        if (i >= o && i + 7 - o < 2 * total) {
-          const u32 lo = i - o, hi = i + 7 - o;
-          full = (2ull * s_p[lo >> 1] + (lo & 1) == D - o) && (2ull * s_p[hi >> 1] + (hi & 1) == D + 7 - o);
-        }
-        const uint4 v = s_row[i];
+      for (u32 q = tid; q < total; q += THREADS) {
+        const u32 D = s_p[q];
+        const u32 o = D & 7;
+        const bool full = q >= o && q + 7 - o < total && (s_p[q - o] == D - o) && (s_p[q + 7 - o] == D + 7 - o);
+        const uint4 v = s_row[q];
         if (full) { u32x4 vv = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(out_row + D)); }
         else out_row[D] = v;
       }
       for (u32 q = tid; q < total; q += THREADS) {
         const u32 D = s_p[q];
         const u32 o = D & 15;
-        bool full = false;
-        if (q >= o && q + 15 - o < total) full = (s_p[q - o] == D - o) && (s_p[q + 15 - o] == D + 15 - o);
+        const bool full = q >= o && q + 15 - o < total && (s_p[q - o] == D - o) && (s_p[q + 15 - o] == D + 15 - o);
         if (full) __builtin_nontemporal_store(s_key[q], out_key + D);
         else out_key[D] = s_key[q];
+        a.win_arrival[D] = num0 + s_num[q];
       }
     }
     if (tid < a.n_buckets) s_start[tid] = s_off[tid];
@@ -363,54 +387,54 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       r[u] = nr[u]; c[u] = nc[u]; sq[u] = nsq[u]; op[u] = nop[u]; nb[u] = nnb[u]; te[u] = nte[u]; tx[u] = ntx[u];
     }
   }
-  ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a.meta);
+  ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a, s_rng, T.n_comms);
+}
+// a batch without records: its header names its place in the window
+__global__ __launch_bounds__(256) void k_ingest_empty(IngestArgs a, u32 n_comms) {
+  clear_next(a, n_comms, threadIdx.x, 256);
+  if (blockIdx.x == 0 && threadIdx.x == 0) put_header(a, 0);
 }
 
 void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology& T, const KeyFormat& kf) {
-  if (a_in.n == 0) return;
   IngestArgs a = a_in;
-  u64 g = (a.n + 255) / 256;
-  if (g > INGEST_BLOCKS) g = INGEST_BLOCKS;
-  a.hist_split = 1;
-  const bool range = a.range != nullptr;
-  const size_t lds = sizeof(u32) * a.n_buckets;
-  const size_t lds_hist = sizeof(u32) * ((a.n_buckets + 1) & ~1u) + (range ? (size_t)16 * T.n_comms : 0);
-  // large batches: one 1,024-thread workgroup per compute unit with the write-out regrouped in LDS, the
-  // membership rows in LDS too when they fit beside the staging area; four counting workgroups per
-  // placement workgroup
-  const bool staged = a.n >= (1u << 22) && a.n_buckets <= INGEST_STAGED_BUCKETS;
-  const size_t stage_bytes = (size_t)2048 * (32 + 8 + 4);
-  const bool staged_table = staged && T.rank_memb4 && (u64)T.n_ranks * 16 + stage_bytes <= 156 * 1024;
-  // otherwise, large batches over few enough ranks: half as many workgroups of twice the size, each with the
-  // membership rows in LDS (two workgroups per compute unit)
-  const bool lds_table = !staged && T.rank_memb4 && (u64)T.n_ranks * 16 + lds <= 72 * 1024 && a.n >= (1u << 22);
-  if (staged) { g = 256; a.hist_split = 4; }
-  else if (lds_table) g = (g + 1) / 2;
-  const u64 unit = 256ull * a.hist_split;
-  a.chunk = ((a.n + g - 1) / g + unit - 1) / unit * unit;
-  const u32 g_hist = (u32)(g * a.hist_split);
-  if (range) hipLaunchKernelGGL(k_ingest_hist<true>, dim3(g_hist), dim3(256), lds_hist, st, a, T.n_comms);
-  else hipLaunchKernelGGL(k_ingest_hist<false>, dim3(g_hist), dim3(256), lds_hist, st, a, T.n_comms);
-  hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
-  launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
+  const size_t range_lds = a.range ? (size_t)16 * T.n_comms : 0;
+  if (a.n == 0) {
+    hipLaunchKernelGGL(k_ingest_empty, dim3(8), dim3(256), 0, st, a, T.n_comms);
+    return;
+  }
   static bool raised = false;       // more than 64 KB of dynamic LDS has to be asked for once
   if (!raised) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ingest<512, true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ingest_staged<1024, true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ingest_staged<1024, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
     raised = true;
   }
-  if (staged_table)
+  if (a.n_buckets == 1) {
+    // four records per thread and workgroup until the chip is full, then longer slices
+    const u64 g = std::min<u64>((a.n + 1023) / 1024, 1024);
+    a.chunk = ((a.n + g - 1) / g + 255) / 256 * 256;
+    hipLaunchKernelGGL(k_ingest<256>, dim3((u32)g), dim3(256), range_lds, st, a, T, kf);
+    return;
+  }
+  // one 1,024-thread workgroup per compute unit; four counting workgroups per placement workgroup where a batch is
+  // large enough, one (and the scan of the counts without a launch of its own) otherwise
+  const u64 g = std::min<u64>((a.n + 2047) / 2048, 256);
+  a.hist_split = a.n >= (1u << 23) ? 4 : 1;
+  const u64 unit = 256ull * a.hist_split;
+  a.chunk = ((a.n + g - 1) / g + unit - 1) / unit * unit;
+  const u32 g_hist = (u32)(g * a.hist_split);
+  hipLaunchKernelGGL(k_ingest_hist, dim3(g_hist), dim3(256), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
+  if (a.n_buckets * g_hist > INGEST_SCAN_WORDS) {
+    hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
+    launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
+  }
+  // the membership rows go to LDS when they fit beside the staging area
+  const size_t stage_bytes = (size_t)2048 * (16 + 8 + 4 + 2) + range_lds;
+  if (T.rank_memb4 && (u64)T.n_ranks * 16 + stage_bytes <= 156 * 1024)
     hipLaunchKernelGGL((k_ingest_staged<1024, true>), dim3((u32)g), dim3(1024), stage_bytes + (size_t)T.n_ranks * 16, st, a, T, kf);
-  else if (staged)
-    hipLaunchKernelGGL((k_ingest_staged<1024, false>), dim3((u32)g), dim3(1024), stage_bytes, st, a, T, kf);
-  else if (lds_table)
-    hipLaunchKernelGGL((k_ingest<512, true>), dim3((u32)g), dim3(512), lds + (size_t)T.n_ranks * 16, st, a, T, kf);
   else
-    hipLaunchKernelGGL((k_ingest<256, false>), dim3((u32)g), dim3(256), lds, st, a, T, kf);
+    hipLaunchKernelGGL((k_ingest_staged<1024, false>), dim3((u32)g), dim3(1024), stage_bytes, st, a, T, kf);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -625,55 +649,123 @@ void launch_keys_pass(hipStream_t st, const uint64_t* key, uint32_t n, const Squ
 // the blame table.  The integer sums do not depend on the order.  At 145,000 flags this takes the place of a sort by
 // rank and three more launches (0.09 ms together).
 constexpr u32 BH_SLOTS = 1024, BH_PROBES = 16, BH_NONE = 0xFFFFFFFFu, BH_BLOCKS = 128;
+struct BlameSums {
+  u32 rank[BH_SLOTS];
+  unsigned long long sum[4][BH_SLOTS];
+  __device__ __forceinline__ void clear() {
+    for (u32 i = threadIdx.x; i < BH_SLOTS; i += blockDim.x) {
+      rank[i] = BH_NONE;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sum[k][i] = 0;
+    }
+  }
+  __device__ __forceinline__ void add(u32 r, u32 f, u64 le, u64 lx, i64* __restrict__ blame, u32 n_ranks) {
+    u32 at = (r * 0x9E3779B1u) >> 22;                 // BH_SLOTS = 2^10
+    bool found = false;
+    for (u32 p = 0; p < BH_PROBES && !found; ++p) {
+      const u32 was = atomicCAS(&rank[at], BH_NONE, r);
+      found = was == BH_NONE || was == r;
+      if (!found) at = (at + 1) & (BH_SLOTS - 1);
+    }
+    auto one = [&](int col, u64 v) {
+      if (found) atomicAdd(&sum[col][at], (unsigned long long)v);
+      else atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)col * n_ranks + r]), (unsigned long long)v);
+    };
+    if (f & CCLD_FLAG_LATE_ENTER) { one(CCLD_BLM_N_LATE_ENTER, 1); one(CCLD_BLM_SUM_LAG_ENTER, le); }
+    if (f & CCLD_FLAG_LATE_EXIT) { one(CCLD_BLM_N_LATE_EXIT, 1); one(CCLD_BLM_SUM_LAG_EXIT, lx); }
+  }
+  __device__ __forceinline__ void flush(i64* __restrict__ blame, u32 n_ranks) {
+    for (u32 i = threadIdx.x; i < BH_SLOTS; i += blockDim.x) {
+      const u32 r = rank[i];
+      if (r == BH_NONE) continue;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (sum[k][i]) atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)k * n_ranks + r]), sum[k][i]);
+    }
+  }
+};
 __global__ __launch_bounds__(256) void k_blame_sums(FlagArgs a, u32 n_ranks, i64* __restrict__ blame) {
-  __shared__ u32 s_rank[BH_SLOTS];
-  __shared__ unsigned long long s_sum[4][BH_SLOTS];
+  __shared__ BlameSums B;
   const u32 n_flag = (u32)a.counters[CNT_NFLAG], tid = threadIdx.x;
   const u32 per = ((n_flag + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
   const u64 lo = (u64)per * blockIdx.x;
   if (lo >= n_flag) return;
   const u32 hi = lo + per < n_flag ? (u32)(lo + per) : n_flag;
-  for (u32 i = tid; i < BH_SLOTS; i += 256) {
-    s_rank[i] = BH_NONE;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s_sum[k][i] = 0;
-  }
+  B.clear();
   __syncthreads();
   const u64 mmask = ((u64)1 << a.sf.mb) - 1;
   for (u32 q = (u32)lo + tid; q < hi; q += 256) {
     const u32 j = a.flag_pos[q];
     const u64 key = a.key[j];
-    const u32 f = a.rec_flag[j];
-    const u64 le = (u64)a.flag_lag[j], lx = (u64)a.flag_lag[a.cap_n + j];
     const u32 r = rank_of_slot(a.member_off, a.members_sorted, (u32)(key >> (a.sf.mb + a.sf.ws)), (u32)(key & mmask));
-    u32 at = (r * 0x9E3779B1u) >> 22;                 // BH_SLOTS = 2^10
-    bool found = false;
-    for (u32 p = 0; p < BH_PROBES && !found; ++p) {
-      const u32 was = atomicCAS(&s_rank[at], BH_NONE, r);
-      found = was == BH_NONE || was == r;
-      if (!found) at = (at + 1) & (BH_SLOTS - 1);
-    }
-    auto add = [&](int col, u64 v) {
-      if (found) atomicAdd(&s_sum[col][at], (unsigned long long)v);
-      else atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)col * n_ranks + r]), (unsigned long long)v);
-    };
-    if (f & CCLD_FLAG_LATE_ENTER) { add(CCLD_BLM_N_LATE_ENTER, 1); add(CCLD_BLM_SUM_LAG_ENTER, le); }
-    if (f & CCLD_FLAG_LATE_EXIT) { add(CCLD_BLM_N_LATE_EXIT, 1); add(CCLD_BLM_SUM_LAG_EXIT, lx); }
+    B.add(r, a.rec_flag[j], (u64)a.flag_lag[j], (u64)a.flag_lag[a.cap_n + j], blame, n_ranks);
   }
   __syncthreads();
-  for (u32 i = tid; i < BH_SLOTS; i += 256) {
-    const u32 r = s_rank[i];
-    if (r == BH_NONE) continue;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s_sum[k][i]) atomicAdd(reinterpret_cast<unsigned long long*>(&blame[(u64)k * n_ranks + r]), s_sum[k][i]);
-  }
+  B.flush(blame, n_ranks);
 }
 static_assert(BH_SLOTS == 1024, "ten hash bits");
 static_assert(CCLD_BLM_N_LATE_ENTER == 0 && CCLD_BLM_N_LATE_EXIT == 1 && CCLD_BLM_SUM_LAG_ENTER == 2 &&
               CCLD_BLM_SUM_LAG_EXIT == 3, "blame column order");
 void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int64_t* blame) {
   if (f.n) hipLaunchKernelGGL(k_blame_sums, dim3(std::min<u32>((f.n + 4095) / 4096, BH_BLOCKS)), dim3(256), 0, st, f, n_ranks, blame);
+}
+
+// ---- flags of a window on the grid placement ----------------------------------------------------------
+// The statistics kernels left the flagged records of every fine bucket in (counter, rank) order; here a wavefront per
+// bucket writes them to their place in the list and in the flag table.  The flags of the buckets before it are summed by
+// the workgroup itself (a few thousand words from the L2), or were scanned before (SCANNED: many buckets).
+constexpr u32 GF_SELF_SUM = 4096;
+template <bool SCANNED>
+__global__ __launch_bounds__(256) void k_grid_flags(GridArgs d, FlagArgs a) {
+  __shared__ u32 s_wave[4];
+  if (d.hdr->feasible == 0) return;
+  const u32 n_fine = d.hdr->n_fine, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  const u32 f0 = blockIdx.x * 4;
+  if (f0 >= n_fine) return;
+  const u32 f = f0 + wave;
+  u32 nf, pos;
+  if (SCANNED) {
+    if (f >= n_fine) return;
+    pos = d.nflag[f];
+    nf = d.nflag[f + 1] - pos;
+  } else {
+    u32 before = 0;
+    for (u32 i = tid; i < f0; i += 256) before += d.nflag[i];
+    u32 base;
+    block_exclusive_sum<256>(before, s_wave, &base);
+    u32 mine[4];
+#pragma unroll
+    for (u32 q = 0; q < 4; ++q) mine[q] = f0 + q < n_fine ? d.nflag[f0 + q] : 0u;
+    pos = base + (wave > 0 ? mine[0] : 0u) + (wave > 1 ? mine[1] : 0u) + (wave > 2 ? mine[2] : 0u);
+    nf = wave == 0 ? mine[0] : wave == 1 ? mine[1] : wave == 2 ? mine[2] : mine[3];
+    if (tid == 0 && f0 + 4 >= n_fine) a.counters[CNT_NFLAG] = (u64)base + mine[0] + mine[1] + mine[2] + mine[3];
+  }
+  if (nf == 0) return;
+  const FineDesc D = d.desc[f];
+  const u32 r0 = d.rec0[f];
+  for (u32 i = lane; i < nf; i += CCLD_WAVE) {
+    const u32 w = a.flag_stage[r0 + i], cell = w & 0xFFFFu, kind = w >> 16;
+    const u32 k = pos + i, round = cell / D.size, slot = cell - round * D.size;
+    a.flag_key[k] = ((u64)(D.srow0 + round) << 32) | slot;
+    a.flag_pos[k] = r0 + i;
+    if (a.flag && k < a.flag_cap) {
+      a.flag[(u64)CCLD_FLG_COMM * a.flag_cap + k] = (i64)D.comm;
+      a.flag[(u64)CCLD_FLG_SEQ * a.flag_cap + k] = (i64)(D.seq0 + round);
+      a.flag[(u64)CCLD_FLG_RANK * a.flag_cap + k] = (i64)rank_of_slot(a.member_off, a.members_sorted, D.comm, slot);
+      a.flag[(u64)CCLD_FLG_KIND * a.flag_cap + k] = (i64)kind;
+      a.flag[(u64)CCLD_FLG_LAG_ENTER * a.flag_cap + k] = a.flag_lag[r0 + i];
+      a.flag[(u64)CCLD_FLG_LAG_EXIT * a.flag_cap + k] = a.flag_lag[a.cap_n + r0 + i];
+    }
+  }
+}
+void launch_grid_flags(hipStream_t st, const GridArgs& d, const FlagArgs& a, uint32_t fine_bound) {
+  const u32 blocks = (fine_bound + 3) / 4;
+  if (fine_bound <= GF_SELF_SUM) {
+    hipLaunchKernelGGL(k_grid_flags<false>, dim3(blocks), dim3(256), 0, st, d, a);
+  } else {
+    launch_scan_tiles(st, d.nflag, fine_bound, &a.counters[CNT_NFLAG]);      // the bound is the exact number here
+    hipLaunchKernelGGL(k_grid_flags<true>, dim3(blocks), dim3(256), 0, st, d, a);
+  }
 }
 
 // order[] = ranks by (flags descending, summed lag descending, rank ascending).  Ranks with any flag come first and
@@ -697,31 +789,26 @@ __device__ __forceinline__ u32 blamed_before(const i64* __restrict__ blame, u32 
   }
   return wave_sum(before);
 }
-// An analysis ends here: the counters go to pinned host memory and the ticket behind them (system-scope release), on
-// which the host spins, by the last workgroup to get here.
+// An analysis ends here: the last workgroup to get here writes the counters to pinned host memory, each with the ticket
+// in its upper 16 bits.  The host waits until every word carries the ticket, so the words need no order among
+// themselves, and no cache is written back on the way (what the kernel wrote for later kernels is, at its end).
 __device__ __forceinline__ void report_counters(u64* counters, u64* host, u64 ticket) {
   __shared__ u32 s_last;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) s_last = atomic_add_u64(&counters[CNT_DONE], 1) + 1 == gridDim.x;
-  __syncthreads();
-  if (!s_last) return;
-  if (threadIdx.x < CNT_COUNT)
-    __hip_atomic_store(&host[threadIdx.x], __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(&host[CNT_COUNT], ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (!last_block(reinterpret_cast<u32*>(&counters[CNT_DONE]), gridDim.x, &s_last)) return;
+  if (threadIdx.x < CNT_COUNT) {
+    const u64 v = __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&host[threadIdx.x], (v & REPORT_MASK) | (ticket << REPORT_BITS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 static_assert(CNT_COUNT <= 64, "one wavefront copies the counters");
 
 // Up to ORDER_ONE_RANKS ranks in one launch: every workgroup lists the flagged ranks in LDS for itself (a scan over
 // two columns of the blame table), ranks its share of them and writes its share of the others.
-constexpr u32 ORDER_ONE_RANKS = 16384, ORDER_TILE = 1024;
-__global__ __launch_bounds__(256) void k_blame_order_one(const i64* __restrict__ blame, u32 n_ranks, u64* counters,
+constexpr u32 ORDER_ONE_RANKS = 16384, ORDER_THREADS = 1024, ORDER_TILE = 4 * ORDER_THREADS;
+__global__ __launch_bounds__(ORDER_THREADS) void k_blame_order_one(const i64* __restrict__ blame, u32 n_ranks, u64* counters,
                                                          u32* __restrict__ order, u64* host, u64 ticket) {
   extern __shared__ unsigned short s_flagged[];      // [n_ranks] flagged ranks, ascending
-  __shared__ u32 s_before[ORDER_ONE_RANKS / ORDER_TILE], s_wave[4];
+  __shared__ u32 s_before[ORDER_ONE_RANKS / ORDER_TILE], s_wave[ORDER_THREADS / CCLD_WAVE];
   const u32 tid = threadIdx.x, lane = lane_id();
   const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
   const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
@@ -736,14 +823,15 @@ __global__ __launch_bounds__(256) void k_blame_order_one(const i64* __restrict__
     const u32 r0 = t * ORDER_TILE + tid * 4;
     const u32 m = flags_of_four(r0);
     u32 tot;
-    u32 at = nb + block_exclusive_sum<256>((u32)__popc(m), s_wave, &tot);
+    u32 at = nb + block_exclusive_sum<ORDER_THREADS>((u32)__popc(m), s_wave, &tot);
 #pragma unroll
     for (u32 k = 0; k < 4; ++k) if (m & (1u << k)) s_flagged[at++] = (unsigned short)(r0 + k);
     if (tid == 0) s_before[t] = nb;
     nb += tot;
   }
   __syncthreads();
-  for (u32 q = blockIdx.x * 4 + tid / CCLD_WAVE; q < nb; q += gridDim.x * 4) {
+  constexpr u32 NW = ORDER_THREADS / CCLD_WAVE;
+  for (u32 q = blockIdx.x * NW + tid / CCLD_WAVE; q < nb; q += gridDim.x * NW) {
     const u32 r = s_flagged[q];
     const u32 before = blamed_before(blame, n_ranks, s_flagged, nb, r, lane);
     if (lane == 0) order[before] = r;
@@ -752,7 +840,7 @@ __global__ __launch_bounds__(256) void k_blame_order_one(const i64* __restrict__
     const u32 r0 = t * ORDER_TILE + tid * 4;
     const u32 m = flags_of_four(r0);
     u32 tot;
-    u32 before = s_before[t] + block_exclusive_sum<256>((u32)__popc(m), s_wave, &tot);       // flagged ranks below r0
+    u32 before = s_before[t] + block_exclusive_sum<ORDER_THREADS>((u32)__popc(m), s_wave, &tot);       // flagged ranks below r0
 #pragma unroll
     for (u32 k = 0; k < 4; ++k) {
       if (r0 + k >= n_ranks) break;
@@ -784,8 +872,8 @@ void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, 
                         uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
                         uint64_t ticket) {
   if (n_ranks <= ORDER_ONE_RANKS) {
-    const u32 blocks = std::min<u32>((n_ranks + 255) / 256, 32);
-    hipLaunchKernelGGL(k_blame_order_one, dim3(blocks), dim3(256), sizeof(unsigned short) * n_ranks, st, blame, n_ranks, counters,
+    const u32 blocks = std::min<u32>((n_ranks + 255) / 256, 16);
+    hipLaunchKernelGGL(k_blame_order_one, dim3(blocks), dim3(ORDER_THREADS), sizeof(unsigned short) * n_ranks, st, blame, n_ranks, counters,
                        order, host_counters, ticket);
     return;
   }
@@ -831,8 +919,27 @@ void launch_alert_select(hipStream_t st, const AlertArgs& a) {
   run_select(st, p, a.n_seg, a.tile_counts, a.alert_list, &a.counters[CNT_NALERT]);
 }
 
+// Where the records of a collective are found: by binary search among the sorted keys, or by cell on the grid.
+// t_exit of member slot q's record in table row s, or false: no record
+template <bool GRID>
+__device__ __forceinline__ bool alert_record(const AlertArgs& a, u32 s, u32 comm, u32 first, u32 nn, u32 q, i64* t_exit) {
+  if (GRID) {
+    const CommLayout L = a.grid.lay[comm];
+    const u32 k = s - L.seg_base, fr = k / L.rpb;
+    const u32 li = a.grid.cell_row[L.cell_base + k * L.size + q];
+    if (li == GRID_EMPTY) return false;
+    *t_exit = unpack_row(a.grid.rows[L.cell_base + fr * L.rpb * L.size + li], a.grid.hdr->ref, a.grid.wide).t_exit;
+    return true;
+  }
+  const u64 mmask = ((u64)1 << a.sf.mb) - 1;      // key slot = position among the members in ascending rank order
+  u32 lo = first, hi = first + nn;
+  while (lo < hi) { const u32 m = (lo + hi) / 2; if ((u32)(a.key[m] & mmask) < q) lo = m + 1; else hi = m; }
+  if (lo >= first + nn || (u32)(a.key[lo] & mmask) != q) return false;
+  *t_exit = load_rec(a.win, a.idx[lo]).t_exit;
+  return true;
+}
 // candidates of one alert, in ascending rank order; EMIT = false only counts them
-template <bool EMIT>
+template <bool EMIT, bool GRID>
 __global__ __launch_bounds__(256) void k_alert_cand(AlertArgs a, u32 n_alert) {
   __shared__ u32 s_wave[4];
   const u32 al = blockIdx.x, tid = threadIdx.x;
@@ -842,44 +949,27 @@ __global__ __launch_bounds__(256) void k_alert_cand(AlertArgs a, u32 n_alert) {
   const u32 nn = (u32)a.seg[CCLD_SEG_N * C + s], ninfl = (u32)a.seg[CCLD_SEG_INFLIGHT * C + s];
   const u32 first = (u32)a.seg[CCLD_SEG_FIRST * C + s];
   const u32 size = a.topo.size[comm], moff = a.topo.member_off[comm];
-  const u64 mmask = ((u64)1 << a.sf.mb) - 1;      // key slot = position among the members in ascending rank order
   const u32 off = EMIT ? a.alert_ncand[al] : 0u;
-  int cls;
+  // not entered: the members with no record for this operation counter; else inconsistent: everyone entered, and the
+  // ranks that completed are the root; else all hung: needs the Send/Recv counters
+  const int cls = nn < size ? CCLD_HANG_H1_NOT_ENTERED : ninfl < nn ? CCLD_HANG_H2_INCONSISTENT : CCLD_HANG_H3_HARDWARE;
   u32 total = 0;
-  if (nn < size) {
-    cls = CCLD_HANG_H1_NOT_ENTERED;          // members with no record for this operation counter
+  if (cls != CCLD_HANG_H3_HARDWARE) {
     for (u32 q0 = 0; q0 < size; q0 += 256) {
       const u32 q = q0 + tid;
-      bool miss = false;
+      bool hit = false;
       u32 r = 0;
       if (q < size) {
         r = a.topo.members_sorted[moff + q];
-        u32 lo = first, hi = first + nn;
-        while (lo < hi) { const u32 m = (lo + hi) / 2; if ((u32)(a.key[m] & mmask) < q) lo = m + 1; else hi = m; }
-        miss = !(lo < first + nn && (u32)(a.key[lo] & mmask) == q);
+        i64 tx = T_INFLIGHT;
+        const bool here = alert_record<GRID>(a, s, comm, first, nn, q, &tx);
+        hit = cls == CCLD_HANG_H1_NOT_ENTERED ? !here : (here && tx != T_INFLIGHT);
       }
       u32 tot;
-      const u32 ex = block_exclusive_sum<256>(miss ? 1u : 0u, s_wave, &tot);
-      if (EMIT && miss && (u64)off + total + ex < a.cand_cap) a.cand[off + total + ex] = (i64)r;
+      const u32 ex = block_exclusive_sum<256>(hit ? 1u : 0u, s_wave, &tot);
+      if (EMIT && hit && (u64)off + total + ex < a.cand_cap) a.cand[off + total + ex] = (i64)r;
       total += tot;
     }
-  } else if (ninfl < nn) {
-    cls = CCLD_HANG_H2_INCONSISTENT;         // everyone entered; the ranks that completed are the root
-    for (u32 j0 = 0; j0 < nn; j0 += 256) {
-      const u32 j = j0 + tid;
-      bool done = false;
-      u32 r = 0;
-      if (j < nn) {
-        r = a.topo.members_sorted[moff + (u32)(a.key[first + j] & mmask)];
-        done = a.row[a.idx[first + j]].t_exit != T_INFLIGHT;
-      }
-      u32 tot;
-      const u32 ex = block_exclusive_sum<256>(done ? 1u : 0u, s_wave, &tot);
-      if (EMIT && done && (u64)off + total + ex < a.cand_cap) a.cand[off + total + ex] = (i64)r;
-      total += tot;
-    }
-  } else {
-    cls = CCLD_HANG_H3_HARDWARE;             // all hung: needs the Send/Recv counters
   }
   if (tid != 0) return;
   if (!EMIT) { a.alert_ncand[al] = total; return; }
@@ -895,22 +985,27 @@ __global__ __launch_bounds__(256) void k_alert_cand(AlertArgs a, u32 n_alert) {
 }
 void launch_alert_candidates(hipStream_t st, const AlertArgs& a, uint32_t n_alert) {
   if (n_alert == 0) return;
-  hipLaunchKernelGGL(k_alert_cand<false>, dim3(n_alert), dim3(256), 0, st, a, n_alert);
+  const bool grid = a.grid.lay != nullptr;
+  if (grid) hipLaunchKernelGGL((k_alert_cand<false, true>), dim3(n_alert), dim3(256), 0, st, a, n_alert);
+  else hipLaunchKernelGGL((k_alert_cand<false, false>), dim3(n_alert), dim3(256), 0, st, a, n_alert);
   launch_scan_tiles(st, a.alert_ncand, n_alert, &a.counters[CNT_NCAND]);
-  hipLaunchKernelGGL(k_alert_cand<true>, dim3(n_alert), dim3(256), 0, st, a, n_alert);
+  if (grid) hipLaunchKernelGGL((k_alert_cand<true, true>), dim3(n_alert), dim3(256), 0, st, a, n_alert);
+  else hipLaunchKernelGGL((k_alert_cand<true, false>), dim3(n_alert), dim3(256), 0, st, a, n_alert);
 }
 
 // ------------------------------------------------------------------------------------------
-// position of every sorted record in the window's arrival order: its arrival number minus that of
-// the window's oldest record (both modulo 2^32)
-__global__ __launch_bounds__(256) void k_perm(const u32* __restrict__ idx, const Row* __restrict__ row, u32 n,
-                                              u32 seqno_head, u32* perm) {
+// position of every sorted record in the window's arrival order: its slot's distance from the window's first slot, or,
+// where batches are placed by bucket, its arrival number minus that of the window's oldest record (modulo 2^32)
+__global__ __launch_bounds__(256) void k_perm(const u32* __restrict__ idx, const u32* __restrict__ arrival, u32 n, u32 seqno_head,
+                                              u32 head, u32 cap, u32* perm) {
   const u32 j = blockIdx.x * 256 + threadIdx.x;
   if (j >= n) return;
-  perm[j] = row[idx[j]].pad - seqno_head;
+  const u32 p = idx[j];
+  perm[j] = arrival ? arrival[p] - seqno_head : (p >= head ? p - head : p + cap - head);
 }
-void launch_perm(hipStream_t st, const uint32_t* idx, const Row* row, uint32_t n, uint32_t seqno_head, uint32_t* perm) {
-  if (n) hipLaunchKernelGGL(k_perm, dim3((n + 255) / 256), dim3(256), 0, st, idx, row, n, seqno_head, perm);
+void launch_perm(hipStream_t st, const uint32_t* idx, const uint32_t* arrival, uint32_t n, uint32_t seqno_head, uint32_t head,
+                 uint32_t cap, uint32_t* perm) {
+  if (n) hipLaunchKernelGGL(k_perm, dim3((n + 255) / 256), dim3(256), 0, st, idx, arrival, n, seqno_head, head, cap, perm);
 }
 
 }  // namespace ccld

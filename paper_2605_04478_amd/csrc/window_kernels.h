@@ -12,22 +12,24 @@ struct IngestArgs {
   const int64_t *t_enter, *t_exit;
   uint64_t n;
   uint64_t* win_key;
-  Row* win_row;
+  uint4* win_row;
+  int64_t* win_wide;         // [cap][3]
+  uint32_t* win_arrival;     // [cap] arrival number (modulo 2^32) of each slot; only where batches are placed by bucket
   uint32_t tail, cap;
-  BatchMeta* meta;
+  BatchMeta *meta, *meta_next;   // this batch's header and the one that the next batch will use
   uint32_t* table;           // [n_buckets][workgroups] records per communicator bucket and workgroup
-  uint32_t* bucket_base;     // [n_buckets + 1]
+  uint32_t* bucket_base;     // [n_buckets + 1] of this batch
+  uint32_t* done;            // zero between launches
   uint64_t* scratch_total;
   uint32_t n_buckets;
   int bshift;                // bucket = comm >> bshift
   uint32_t seqno0;           // arrival number of the batch's first record
-  uint64_t* range;           // [n_comms][2] per communicator: largest operation counter, largest complement of one
-                             // (zeroed by the caller); null: not wanted.  At most INGEST_RANGE_COMMS communicators.
+  uint64_t *range, *range_next;  // [n_comms][2] per communicator: largest operation counter, largest complement of one; null:
+                             // not wanted.  At most INGEST_RANGE_COMMS communicators.
   uint64_t chunk;            // records per placement workgroup (a multiple of 256 * hist_split)
   uint32_t hist_split;       // counting workgroups per placement workgroup
 };
 constexpr uint32_t INGEST_BLOCKS = 1024;
-constexpr uint32_t INGEST_MAX_BUCKETS = 4096;
 constexpr uint32_t INGEST_STAGED_BUCKETS = 256;   // most buckets the LDS-regrouped placement kernel handles
 constexpr uint32_t INGEST_RANGE_COMMS = 3584;     // most communicators whose counter ranges fit the counting kernel's LDS
 void launch_ingest(hipStream_t st, const IngestArgs& a, const DeviceTopology& T, const KeyFormat& kf);
@@ -37,7 +39,7 @@ constexpr uint32_t NO_GROUP = 0xFFFFu;
 struct SegArgs {
   const uint64_t* key;       // sorted squeezed keys
   const uint32_t* idx;       // window slot of each sorted record
-  const Row* row;
+  WindowRows win;
   uint32_t n;
   SqueezedFormat sf;
   const uint32_t* comm_size;
@@ -46,13 +48,17 @@ struct SegArgs {
   uint32_t* tile_heads;      // [tiles + 1] head counts, then (after the scan) first segment ordinal of each tile
   int64_t* seg;
   uint64_t seg_cap;
-  uint8_t* rec_flag;
+  uint8_t* rec_flag;         // (optional on the grid placement)
   int64_t *lag_e, *lag_x;    // optional per-record outputs
-  int64_t* flag_lag;         // [2][cap_n] lags of flagged records by sorted position
+  uint32_t* perm;            // optional, grid placement only (a sorted window's comes from launch_perm)
+  const uint32_t* arrival;   // arrival number of each window slot (null: slots are in order of arrival), and that of the
+  uint32_t seqno_head;       //   window's oldest record
+  int64_t* flag_lag;         // [2][cap_n] lags of flagged records: by sorted position; on the grid placement with flag_pos
+  uint32_t* flag_pos;        // grid placement: cell | kind << 16 of the flagged records of each fine bucket
   uint64_t cap_n;
   uint32_t* big_list;
   uint64_t big_cap;          // entries the list holds
-  int64_t* big_ex;           // [2][cap_n]
+  int64_t *big_e, *big_x;    // [cap_n] each: times of the collectives that do not fit LDS
   uint64_t* counters;
   int64_t lag_floor;
   uint32_t kmad_num, kmad_den, barrier_bytes;
@@ -75,7 +81,9 @@ struct FlagArgs {
   SqueezedFormat sf;
   const uint32_t *member_off, *members_sorted;
   uint32_t* tile_flags;      // [tiles + 1]
-  uint32_t* flag_pos;
+  uint32_t* flag_pos;        // list: sorted position of each flagged record; on the grid placement its place in flag_stage
+  uint64_t* flag_key;        // grid placement, list: row of the collective table << 32 | member slot
+  const uint32_t* flag_stage;// grid placement: what the statistics kernels collected, cell | kind << 16
   int64_t* flag;             // caller's table (may be NULL)
   uint64_t flag_cap;
   uint64_t* counters;
@@ -114,6 +122,17 @@ void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* orde
                       uint32_t* order_out);
 void launch_groups(hipStream_t st, const GroupArgs& a);        // groups.hip
 
+struct CommLayout;
+struct GridHeader;
+// What the chains and the alerts need of a window on the grid placement (grid.h).
+struct GridView {
+  const CommLayout* lay;
+  const uint4* rows;         // partitioned rows
+  const uint16_t* cell_row;  // row of every cell inside its fine bucket
+  const int64_t* wide;
+  const GridHeader* hdr;
+};
+
 struct AlertArgs {
   const int64_t* seg;
   uint64_t seg_cap;
@@ -121,9 +140,10 @@ struct AlertArgs {
   int64_t now_ns, hang_threshold_ns;
   const uint64_t* key;
   const uint32_t* idx;
-  const Row* row;
+  WindowRows win;
   uint32_t n;
   SqueezedFormat sf;
+  GridView grid;             // lay is null for a sorted window
   DeviceTopology topo;
   uint32_t* tile_counts;
   uint32_t* alert_list;
@@ -137,6 +157,7 @@ struct AlertArgs {
 void launch_alert_select(hipStream_t st, const AlertArgs& a);
 void launch_alert_candidates(hipStream_t st, const AlertArgs& a, uint32_t n_alert);
 
-void launch_perm(hipStream_t st, const uint32_t* idx, const Row* row, uint32_t n, uint32_t seqno_head, uint32_t* perm);
+void launch_perm(hipStream_t st, const uint32_t* idx, const uint32_t* arrival, uint32_t n, uint32_t seqno_head, uint32_t head,
+                 uint32_t cap, uint32_t* perm);
 
 }  // namespace ccld

@@ -1,0 +1,77 @@
+"""GPU parity of the grid placement where its kernels can go wrong: communicators at the edges of the lanes and fine
+buckets that a collective takes, members without a record, operations in flight, values that do not fit a row, batches
+that lie hours apart, and windows placed with and without communicator buckets."""
+import numpy as np
+import pytest
+
+from oracle import ccld_oracle as orc
+from paper_2605_04478_amd import tracegen as tg
+from tests.helpers import INFLIGHT, T0, toy_cols
+from tests.test_gpu_window import FAR, compare
+
+pytestmark = pytest.mark.gpu
+
+SIZES = {"short": [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64],
+         "long": [65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1024, 1025, 2047, 2048]}
+ONE_GO, BUCKETED = 0, 6_000_000       # window capacities: the records of the test, and one that takes communicator buckets
+
+
+def _batch(rng, sizes, rounds, seq0, t0, missing, wide):
+    """rows of `rounds` collectives per communicator, the first member always there"""
+    rows = []
+    for c, n in enumerate(sizes):
+        for s in range(rounds + c % 3):
+            t = t0 + s * 1_000_000 + c * 1000
+            b = int(rng.integers(1, 1 << 30)) if not wide or s % 3 else 1 << (36 + c % 3)
+            for r in range(n):
+                if r and s % 2 and rng.random() < missing:
+                    continue
+                te = t + int(rng.integers(0, 900_000))
+                tx = te + int(rng.integers(0, 5_000_000))
+                u = rng.random()
+                if s % 2 and u < 0.01:
+                    tx = INFLIGHT
+                elif wide and u < 0.05:
+                    tx = te + int(rng.choice([2**32 - 3, 2**32 - 2, 2**32 - 1, 2**32, 2**40, 2**43]))
+                elif wide and u < 0.08:
+                    te = t0 + int(rng.choice([2**42 - 1, 2**42, 2**42 + 1, 1 - 2**42, -2**42, -2**42 - 1]))
+                    tx = te + 77
+                rows.append((r, c, seq0 + s, c % 6, b, te, tx))
+    return rows
+
+
+@pytest.mark.parametrize("cap", [ONE_GO, BUCKETED], ids=["one_go", "bucketed"])
+@pytest.mark.parametrize("far_ns", [0, 2 * 3_600_000_000_000], ids=["near", "far"])
+@pytest.mark.parametrize("missing,wide", [(0.0, False), (0.08, True)], ids=["full", "wide"])
+@pytest.mark.parametrize("kind", ["short", "long"])
+def test_grid_edges(kind, missing, wide, far_ns, cap):
+    from paper_2605_04478_amd import ccld
+    sizes = SIZES[kind] * (7 if kind == "short" else 1)
+    topo = tg.make_topology(max(sizes), [list(range(n))[::-1] for n in sizes])
+    rng = np.random.default_rng(len(sizes) + wide)
+    rounds = 9 if kind == "short" else 3
+    batches = [_batch(rng, sizes, rounds, 1000 + i * (rounds + 2), T0 + i * far_ns, missing, wide) for i in range(3)]
+    # the counters of one communicator follow on from batch to batch: no round without a record
+    nxt = [1000] * len(sizes)
+    for i, rows in enumerate(batches):
+        for j, r in enumerate(rows):
+            rows[j] = (r[0], r[1], nxt[r[1]] + r[2] - 1000 - i * (rounds + 2)) + r[3:]
+        for c in range(len(sizes)):
+            nxt[c] += rounds + c % 3
+    n = sum(map(len, batches))
+    kw = dict(window_batches=2, tbase_init_ns=200_000, hang_threshold_ns=10**9, kmad_num=1, kmad_den=1, lag_floor_ns=50_000)
+    an = ccld.Analyzer(topo, max_window_records=max(cap, n), max_batch_records=max(map(len, batches)), **kw)
+    o, prev, flags = orc.Oracle(topo, kw), None, 0
+    for i, rows in enumerate(batches):
+        cols = toy_cols(rows)
+        p = rng.permutation(len(rows))
+        cols = {k: v[p] for k, v in cols.items()}
+        an.ingest(an.to_device(cols))
+        win = cols if prev is None else {k: np.concatenate([prev[k], cols[k]]) for k in cols}
+        m = len(win["rank"])
+        g, ref = an.analyze_window(FAR, n_records=m, alert_cap=m, cand_cap=2 * m, per_record=True), o.analyze_window(win, FAR)
+        flags += len(ref.flag["comm"])
+        compare(g, ref, *an.rank_blame(), what=f"batch{i}")
+        prev = cols
+    an.close()
+    assert flags > 0
