@@ -48,6 +48,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->topo.rank_slots = w.take<uint32_t>(n_members);
   c->topo.rank_memb4 = w.take<uint32_t>(4ull * n_ranks);
   c->topo.rank_cell4 = w.take<uint32_t>(4ull * n_ranks);
+  c->topo.member_comm = w.take<uint32_t>(n_members);
   c->comm_info = w.take<uint2>(n_comms);
   // window
   c->win_key = w.take<uint64_t>(N);
@@ -141,7 +142,6 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->h_wait_slot = w.take<int32_t>(n_members);
   c->h_cand = w.take<uint8_t>(n_members);
   c->h_layer_max = w.take<uint64_t>(n_members);
-  c->h_root_list = w.take<uint32_t>(n_members + 1);
   c->f_last = w.take<uint64_t>(2ull * CCLD_FRAME_CHANNELS * n_members);
   c->f_seen = w.take<uint32_t>(n_ranks / 32 + 1);
   c->h_stage = w.take<uint8_t>(SN * 32);
@@ -355,6 +355,9 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
       rp4[4ull * r + (q - rc_off[r])] = (k << pb) | (off + sslot[off + rs_slot[q]]);
     }
   c->topo.pb = pb;
+  std::vector<uint32_t> mcomm(n_members);
+  for (uint32_t k = 0; k < topo->n_comms; ++k)
+    std::fill_n(mcomm.begin() + topo->member_off[k], topo->size[k], k);
 
   ccld_status rs = CCLD_OK;
   auto up = [&](const void* dst, const void* src, size_t bytes) {
@@ -376,6 +379,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   std::vector<uint2> cinfo(topo->n_comms);
   for (uint32_t k = 0; k < topo->n_comms; ++k) cinfo[k] = make_uint2(topo->member_off[k], topo->size[k]);
   up(c->comm_info, cinfo.data(), sizeof(uint2) * cinfo.size());
+  up(c->topo.member_comm, mcomm.data(), 4ull * n_members);
   up(c->topo.rank_cell4, rp4.data(), 4ull * rp4.size());
   if (!fits_cell4) c->topo.rank_cell4 = nullptr;
   if (hipMemsetAsync(c->gstate, 0, sizeof(GroupState) * (uint64_t)topo->n_comms * GROUP_SLOTS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
@@ -490,7 +494,7 @@ static bool reported(const ccld_ctx* c) {
     if ((__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED) >> REPORT_BITS) != (c->ticket & 0xFFFF)) return false;
   return true;
 }
-static hipError_t wait_report(ccld_ctx* c) {
+extern "C++" hipError_t wait_report(ccld_ctx* c) {
   bool there = false;
   if (!c->prof.on) {
     const auto t0 = std::chrono::steady_clock::now();

@@ -42,6 +42,7 @@ struct DeviceTopology {
   const uint32_t* rank_memb4;       // [n_ranks][4] words comm << mb | position (padded with 0xFFFFFFFF); null if a rank is in more than four communicators or cb + mb > 31
   const uint32_t* rank_cell4;       // [n_ranks][4] words comm << pb | member index (member_off[comm] + slot in members[]), padded alike; null if a rank is in more than four communicators or cb + pb > 31
   int pb;                           // bits of the largest member index
+  const uint32_t* member_comm;      // [members] communicator of every member slot
 };
 
 // rank of the record whose key carries (comm, slot)
@@ -89,7 +90,7 @@ constexpr int RANKCOUNT_BLOCKS = 2048;
 
 // device counters written by kernels and read back by the host
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
-       CNT_NRETAINED, CNT_DONE, CNT_COUNT = 16 };
+       CNT_NRETAINED, CNT_DONE, CNT_NCELL, CNT_COUNT = 16 };
 
 // how the device reports a counter to the host: its value with the analysis's ticket in the upper bits
 constexpr int REPORT_BITS = 48;
@@ -163,7 +164,6 @@ struct ccld_ctx {
   int32_t* h_wait_slot;               // [n_members] slot waited on, -1 = none
   uint8_t* h_cand;                    // [n_members]
   uint64_t* h_layer_max;              // [n_members]
-  uint32_t* h_root_list;              // [n_members]
   int64_t* rate_root;                 // [n_comms] member of minimal SendRate / RecvRate from the latest rate pass, or CCLD_NO_RANK
   uint64_t* f_last;                   // [n_members][CCLD_FRAME_CHANNELS][2] remembered (operation counter, sent | recv << 32) per member and channel
   uint32_t* f_seen;                   // [n_ranks / 32 + 1] ranks that delivered a frame in the current call
@@ -201,3 +201,5 @@ struct ccld_ctx {
 
 // looks up the device address of the library's static scratch array on the current device (hang.hip)
 ccld_status ccld_static_scratch_init();
+// waits for the report of the current ticket (api.hip); the counters are then in h_pinned
+hipError_t wait_report(ccld_ctx* c);

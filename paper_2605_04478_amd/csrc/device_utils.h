@@ -80,6 +80,8 @@ __device__ __forceinline__ u32 block_exclusive_sum(u32 v, u32* s_wave, u32* tota
 // Words that workgroups of one launch hand to one another: stored and loaded past the caches that are not coherent
 // between the XCDs, so that no cache has to be written back for them.
 __device__ __forceinline__ void store_agent(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_agent(i64* p, i64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ i64 load_agent(const i64* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ u32 load_agent(const u32* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // True in the last of `blocks` workgroups to get here.  What the others stored with store_agent or added with atomics
 // before is there for load_agent: the barrier waits until a wavefront's stores are done.  (A release fence in every thread

@@ -1,15 +1,14 @@
-// Hang location from progress-counter snapshots for gfx950: rows are placed into a dense grid
-// [member slot][channel][snapshot], one wavefront per (rank, communicator) scans its channels'
-// time series, one workgroup per communicator applies the hang decision tree and builds the
-// ring / tree wait-for edges, victims are filtered across communicators, and the edges are
-// walked to the roots.
+// Hang location and progress rates from progress-counter snapshots for gfx950, and Probing Frames.  Rows arrive in any
+// order; they are regrouped by region (a range of member slots) and a workgroup per region works its rows off in LDS.  One
+// workgroup per communicator then applies the hang decision tree, builds the ring / tree wait-for edges and follows
+// them to the roots; victims are filtered across communicators at the end.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
 
 #include "ccld_internal.h"
 #include "device_utils.h"
-#include "select.h"
+#include "report.h"
 #include "window_kernels.h"
 
 using namespace ccld;
@@ -31,6 +30,8 @@ struct HangArgs {
   u32* cnt;           // presence bitmap, one bit per cell
   int exact;          // 1: the bitmap is kept (duplicates and gaps told apart); 0: cells start from an all-ones fill and a
                       //    cell that still holds it is suspect
+  ulonglong2* final;  // [n_members * n_ch] state of every (member, channel) in the last snapshot
+  u32* mark;          // [n_members][2] 1 + the last snapshot that differs from the last one; 1: not stalled
   // tables
   i64* pair;          // [CCLD_HPAIR_NCOL][n_members]
   i64* hcomm;         // [CCLD_HCOMM_NCOL][n_comms]
@@ -39,12 +40,24 @@ struct HangArgs {
   u64* layer_max;
   u64* counters;
   u32 stall_snapshots, fifo_depth;
+  u64 n_cell;
+  int checked;        // the host has found the rows in order
+  int hops_known;     // no communicator is too large for its hops to be found in LDS
+  i64* root_key;      // [n_members] rank << cb | communicator of every root
+  int cb;             // bits of a communicator
+  i64 *out_pair, *out_comm, *out_root;
+  u64 pair_cap, comm_cap, root_cap;
+  u64 *host, ticket;  // pinned words of the report
   // two-step placement of large grids: rows regrouped by region of 2^rb cells
   ulonglong2* part_pay;   // [n_regions << rb] cell contents
   u32* part_idx;          // [n_regions << rb] cell number inside the region
   u32* part_fill;         // [n_regions] rows received
   int rb;
   u32 n_regions;
+  // hang location of large grids: rows regrouped by region of 2^sb members
+  ulonglong2* part_row;   // [n_cell]
+  int sb;
+  u32 snap_inv;           // ceil(2^32 / n_snap)
 };
 
 #define PAIR(a, col, p) (a.pair[(u64)(col) * a.n_members + (p)])
@@ -275,84 +288,380 @@ __global__ __launch_bounds__(256) void k_hang_place_regions(HangArgs a, u32 wpr)
   cell2[k] = make_ulonglong2(t.x, t.y);
 }
 
-// ---- per (rank, communicator): stalled, operation counter, chunk totals, onset -------------------
-// One wavefront per member slot; lanes read consecutive snapshots of one channel.
-__global__ __launch_bounds__(256) void k_hang_pairs(HangArgs a) {
-  const u32 lane = lane_id();
-  const u64 p = (u64)blockIdx.x * 4 + threadIdx.x / CCLD_WAVE;
-  if (p >= a.n_members) return;
-  const u32 L = a.n_snap - 1, W = a.stall_snapshots;
-  const bool can_stall = L >= W;
-  bool stalled = can_stall;
-  u64 seq = 0, S = 0, R = 0;
-  u32 onset = 0;
-  u64 status = 0;
-  for (u32 ch = 0; ch < a.n_ch; ++ch) {
-    const u64 base = (p * a.n_ch + ch) * a.n_snap;
-    const u64 sL0 = a.cell[2 * (base + L)], sL1 = a.cell[2 * (base + L) + 1];
-    if (can_stall) {
-      const u64 o0 = a.cell[2 * (base + L - W)], o1 = a.cell[2 * (base + L - W) + 1];
-      if (o0 != sL0 || o1 != sL1) stalled = false;
-    }
-    u32 last_diff = 0;        // 1 + the last snapshot whose state differs from the final one
-    for (u32 s0 = 0; s0 < a.n_snap; s0 += CCLD_WAVE) {
-      const u32 s = s0 + lane;
-      bool diff = false;
-      if (s < a.n_snap) {
-        const u64 w0 = a.cell[2 * (base + s)], w1 = a.cell[2 * (base + s) + 1];
-        diff = w0 != sL0 || w1 != sL1;
-        status |= cell_status(a, base + s, w0, w1);
-      }
-      const u64 m = ballot64(diff);
-      if (m) last_diff = s0 + (64 - (u32)__clzll((long long)m));
-    }
-    onset = last_diff > onset ? last_diff : onset;
-    seq = sL0 > seq ? sL0 : seq;
-    S += sL1 & 0xFFFFFFFFull;
-    R += sL1 >> 32;
-  }
+// ---- hang location: two passes over the rows instead of a grid ------------------------------------------
+// Of a (member, channel)'s time series the pass needs the final state and the last snapshot that differs from it, and
+// that every cell of the grid has exactly one row.  So the rows are not placed: a first pass picks the rows
+// of the last snapshot, a second one compares every row with its final state and sets the row's bit in a bitmap of the cells.
+
+// First pass: reads the snapshot numbers, and the other columns of the last snapshot's rows only.  A wavefront lists the
+// rows it found in LDS and then loads them side by side: one in n_snap rows is found, and taking each
+// where it is found would be a chain of misses.
+constexpr int LAST_U = 8;
+__global__ __launch_bounds__(256) void k_hang_last(HangArgs a) {
+  __shared__ u32 s_found[4][LAST_U * CCLD_WAVE];
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  const u64 stride = (u64)gridDim.x * 256, t0 = (u64)blockIdx.x * 256 + tid;
+  // what the second pass adds to is cleared on the way
+  if (blockIdx.x == 0 && tid < CNT_COUNT) a.counters[tid] = 0;
+  for (u64 i = t0; i < (a.n_cell + 31) / 32; i += stride) a.cnt[i] = 0;
+  for (u64 i = t0; i < 2 * a.n_members; i += stride) a.mark[i] = 0;
+  const u32 L = a.n_snap - 1;
+  const u64 waves = (u64)gridDim.x * 4;
+  for (u64 base = ((u64)blockIdx.x * 4 + wave) * (LAST_U * CCLD_WAVE); base < a.n_rows; base += waves * (LAST_U * CCLD_WAVE)) {
+    u32 sn[LAST_U];
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) status |= shfl_xor_u64(status, m);
-  if (lane == 0) {
-    if (status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
-    // communicator of this slot: the last one whose offset is <= p
-    u32 lo = 0, hi = a.T.n_comms;
-    while (hi - lo > 1) { const u32 m = (lo + hi) / 2; if (a.T.member_off[m] <= p) lo = m; else hi = m; }
-    PAIR(a, CCLD_HPAIR_RANK, p) = a.T.members[p];
-    PAIR(a, CCLD_HPAIR_COMM, p) = lo;
-    PAIR(a, CCLD_HPAIR_STALLED, p) = stalled ? 1 : 0;
-    PAIR(a, CCLD_HPAIR_ENTERED, p) = 0;
-    PAIR(a, CCLD_HPAIR_SEQ, p) = (i64)seq;
-    PAIR(a, CCLD_HPAIR_SENT, p) = (i64)S;
-    PAIR(a, CCLD_HPAIR_RECV, p) = (i64)R;
-    PAIR(a, CCLD_HPAIR_WAITS_ON, p) = CCLD_NO_RANK;
-    PAIR(a, CCLD_HPAIR_HOPS, p) = -1;
-    PAIR(a, CCLD_HPAIR_ONSET, p) = onset;
-    a.wait_slot[p] = -1;
-    a.cand[p] = 0;
-    a.layer_max[p] = 0;
+    for (int u = 0; u < LAST_U; ++u) {
+      const u64 i = base + (u64)u * CCLD_WAVE + lane;
+      sn[u] = i < a.n_rows ? __builtin_nontemporal_load(a.snap + i) : ~0u;
+    }
+    u32 found = 0;
+#pragma unroll
+    for (int u = 0; u < LAST_U; ++u) {
+      const u64 m = ballot64(sn[u] == L && base + (u64)u * CCLD_WAVE + lane < a.n_rows);
+      if ((m >> lane) & 1) s_found[wave][found + mbcnt64(m)] = (u32)(u * CCLD_WAVE) + lane;
+      found += (u32)__popcll(m);
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (u32 k = lane; k < found; k += CCLD_WAVE) {
+      const u64 i = base + s_found[wave][k];
+      const u32 c = a.comm[i], r = a.rank[i], ch = a.channel[i];
+      const u64 sq = a.seq_posted[i];
+      const u32 se = a.sent[i], rv = a.recv[i];
+      const i64 p = c < a.T.n_comms ? grid_row_of(a, c, r, grid_row_lookup(a, r)) : -1;
+      if (p >= 0 && ch < a.n_ch) a.final[(u64)p * a.n_ch + ch] = make_ulonglong2(sq, (u64)se | ((u64)rv << 32));
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-// ---- per communicator: entered, idle test, decision tree, wait-for edges ------------------------
-__global__ __launch_bounds__(256) void k_hang_comm(HangArgs a) {
-  __shared__ unsigned long long s_seqmax, s_minsum, s_minrecv, s_worst;
-  __shared__ u32 s_flags, s_best, s_ncand;      // flags: 1 not all entered, 2 any stalled, 4 not all stalled, 8 not idle
-  const u32 c = blockIdx.x, tid = threadIdx.x;
-  const u32 n = a.T.size[c], off = a.T.member_off[c];
-  const bool tree = a.T.algo[c] == CCLD_ALGO_TREE;
-  if (tid == 0) { s_seqmax = 0; s_minsum = ~0ull; s_minrecv = ~0ull; s_worst = 0; s_flags = 0; s_best = 0xFFFFFFFFu; s_ncand = 0; }
-  __syncthreads();
-  {     // every thread reduces its own members first: one LDS atomic per thread, not per member
-    unsigned long long mine = 0;
-    for (u32 q = tid; q < n; q += 256) {
-      const unsigned long long v = (unsigned long long)PAIR(a, CCLD_HPAIR_SEQ, off + q);
-      mine = v > mine ? v : mine;
+// Second pass.
+template <int U>
+__global__ __launch_bounds__(256) void k_hang_scan(HangArgs a) {
+  u64 status = 0;
+  const u32 L = a.n_snap - 1, W = a.stall_snapshots;
+  const u32 s_stall = L >= W ? L - W : ~0u;
+  const u64 stride = (u64)gridDim.x * 256;
+  for (u64 i0 = (u64)blockIdx.x * 256 + threadIdx.x; i0 < a.n_rows; i0 += stride * U) {
+    u32 c[U], r[U], ch[U], sn[U], se[U], rv[U];
+    u64 sq[U];
+    bool on[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const u64 i = i0 + stride * u;
+      on[u] = i < a.n_rows;
+      if (on[u]) {
+        c[u] = __builtin_nontemporal_load(a.comm + i); r[u] = __builtin_nontemporal_load(a.rank + i);
+        ch[u] = __builtin_nontemporal_load(a.channel + i); sn[u] = __builtin_nontemporal_load(a.snap + i);
+        sq[u] = __builtin_nontemporal_load(a.seq_posted + i);
+        se[u] = __builtin_nontemporal_load(a.sent + i); rv[u] = __builtin_nontemporal_load(a.recv + i);
+      }
     }
-    if (tid < n) atomicMax(&s_seqmax, mine);
+    uint4 m[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m[u] = on[u] ? grid_row_lookup(a, r[u]) : make_uint4(~0u, ~0u, ~0u, ~0u);
+    i64 p[U];
+    ulonglong2 f[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!on[u]) continue;
+      on[u] = false;
+      if (c[u] >= a.T.n_comms) { status |= DS_UNKNOWN_COMM; continue; }
+      p[u] = grid_row_of(a, c[u], r[u], m[u]);
+      if (p[u] < 0) { status |= DS_NOT_MEMBER; continue; }
+      if (ch[u] >= a.n_ch || sn[u] >= a.n_snap) { status |= DS_RANGE; continue; }
+      on[u] = true;
+      f[u] = a.final[(u64)p[u] * a.n_ch + ch[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!on[u]) continue;
+      const u64 k = ((u64)p[u] * a.n_ch + ch[u]) * a.n_snap + sn[u];
+      atomicOr(&a.cnt[k >> 5], 1u << (k & 31));
+      if (f[u].x == sq[u] && f[u].y == ((u64)se[u] | ((u64)rv[u] << 32))) continue;
+      u32* mk = a.mark + 2 * (u64)p[u];
+      if (sn[u] == s_stall) mk[1] = 1;
+      // the mark only grows: one read beforehand leaves out most of the atomics
+      if (mk[0] < sn[u] + 1) atomicMax(&mk[0], sn[u] + 1);
+    }
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) status |= shfl_xor_u64(status, m);
+  if (lane_id() == 0 && status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
+}
+
+// Both of these passes touch random lines for every row (16.8M rows: the final states 150 us, the bitmap's atomics
+// 400 us).  So they serve only the rows that cannot be regrouped; normally the rows are first regrouped by region, a range of
+// members whose part of the bitmap and of the final states fits LDS, and a workgroup per region then streams its rows.
+// A row leaves as 16 bytes:
+//   x   operation counter << SPLIT_CELL_BITS | cell inside the region
+//   y   sent | received << 32
+// Rows with an operation counter of 2^46 or more do not fit; the host then takes the two passes above.  Bytes bound it:
+// 32 in and 16 out, then 16 in.  At 16.8M rows in 256 regions the split takes 186 us (4.3 TB/s), the regions 47 us
+// (5.7 TB/s), where placing the rows in a grid in memory and scanning that took 540 us.  Rounds of 3,072 rows: each
+// reserves room in every region with an atomic, and rounds of 2,048 rows with 512 regions spend 340 us on them; larger
+// rounds leave one workgroup per CU and nothing to hide the phases behind.
+constexpr int SPLIT_CELL_BITS = 18;
+constexpr u32 SPLIT_REGIONS = 512;
+constexpr size_t SPLIT_LDS = 64000, RATE_LDS = 156000;      // LDS of a region: hang location, rates
+inline size_t rate_region_lds(u32 n_ch, u32 n_snap, int sb) {
+  const u64 cells = (u64)n_ch * n_snap << sb;
+  return cells * 16 + (32ull << sb) + (cells + 31) / 32 * 4;
+}
+inline size_t region_lds(u32 n_ch, u32 n_snap, int sb) {
+  return ((20ull * n_ch + 4) << sb) + ((((u64)n_ch * n_snap << sb) + 31) / 32) * 4;
+}
+template <int THREADS, int U>
+__global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
+  constexpr u32 CHUNK = THREADS * U;
+  extern __shared__ ulonglong2 s_row[];                                // [CHUNK] rows | [CHUNK] their regions
+  unsigned short* s_reg = reinterpret_cast<unsigned short*>(s_row + CHUNK);
+  __shared__ u32 s_cnt[SPLIT_REGIONS], s_pre[SPLIT_REGIONS], s_off[SPLIT_REGIONS], s_scan[THREADS / CCLD_WAVE], s_total;
+  constexpr u32 PER = (SPLIT_REGIONS + THREADS - 1) / THREADS;         // regions per thread
+  const u32 tid = threadIdx.x;
+  const u32 L = a.n_snap - 1, per_member = a.n_ch * a.n_snap, cap = per_member << a.sb, smask = (1u << a.sb) - 1;
+  u64 status = 0;
+  const u64 i_begin = chunk * blockIdx.x;
+  const u64 i_end = chunk * (blockIdx.x + 1) < a.n_rows ? chunk * (blockIdx.x + 1) : a.n_rows;
+  u32 c[U], r[U], ch[U], sn[U], se[U], rv[U];
+  u64 sq[U];
+  auto load_round = [&](u64 base) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const u64 i = base + (u64)u * THREADS + tid;
+      if (i < i_end) {
+        c[u] = __builtin_nontemporal_load(a.comm + i); r[u] = __builtin_nontemporal_load(a.rank + i);
+        ch[u] = __builtin_nontemporal_load(a.channel + i); sn[u] = __builtin_nontemporal_load(a.snap + i);
+        sq[u] = __builtin_nontemporal_load(a.seq_posted + i);
+        se[u] = __builtin_nontemporal_load(a.sent + i); rv[u] = __builtin_nontemporal_load(a.recv + i);
+      }
+    }
+  };
+  load_round(i_begin);
+  for (u32 i = tid; i < SPLIT_REGIONS; i += THREADS) s_cnt[i] = 0;
+  __syncthreads();
+  for (u64 base = i_begin; base < i_end; base += CHUNK) {              // uniform over the workgroup
+    uint4 m[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      m[u] = base + (u64)u * THREADS + tid < i_end ? grid_row_lookup(a, r[u]) : make_uint4(~0u, ~0u, ~0u, ~0u);
+    u32 at[U];                                                         // region << 16 | rank among its rows, ~0: no row
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      at[u] = ~0u;
+      if (base + (u64)u * THREADS + tid >= i_end) continue;
+      if (c[u] >= a.T.n_comms) { status |= DS_UNKNOWN_COMM; continue; }
+      const i64 p = grid_row_of(a, c[u], r[u], m[u]);
+      if (p < 0) { status |= DS_NOT_MEMBER; continue; }
+      if (ch[u] >= a.n_ch || sn[u] >= a.n_snap) { status |= DS_RANGE; continue; }
+      if (sq[u] >> (64 - SPLIT_CELL_BITS)) { status |= DS_SUSPECT; continue; }
+      if (sn[u] == L) a.final[(u64)p * a.n_ch + ch[u]] = make_ulonglong2(sq[u], (u64)se[u] | ((u64)rv[u] << 32));
+      const u32 reg = (u32)p >> a.sb;
+      sq[u] = sq[u] << SPLIT_CELL_BITS | (((u32)p & smask) * per_member + ch[u] * a.n_snap + sn[u]);
+      at[u] = reg << 16 | atomicAdd(&s_cnt[reg], 1u);
+    }
+    __syncthreads();
+    {
+      u32 v[PER], sum = 0;
+#pragma unroll
+      for (u32 k = 0; k < PER; ++k) { v[k] = PER * tid + k < a.n_regions ? s_cnt[PER * tid + k] : 0u; sum += v[k]; }
+      u32 f[PER];
+#pragma unroll
+      for (u32 k = 0; k < PER; ++k) if (v[k]) f[k] = atomicAdd(&a.part_fill[PER * tid + k], v[k]);
+      u32 tot;
+      u32 ex = block_exclusive_sum<THREADS>(sum, s_scan, &tot);
+#pragma unroll
+      for (u32 k = 0; k < PER; ++k)
+        if (PER * tid + k < a.n_regions) {
+          s_pre[PER * tid + k] = ex;
+          if (v[k]) s_off[PER * tid + k] = f[k] - ex;
+          ex += v[k];
+          s_cnt[PER * tid + k] = 0;
+        }
+      if (tid == 0) s_total = tot;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (at[u] == ~0u) continue;
+      const u32 q = s_pre[at[u] >> 16] + (at[u] & 0xFFFFu);
+      s_reg[q] = (unsigned short)(at[u] >> 16);
+      s_row[q] = make_ulonglong2(sq[u], (u64)se[u] | ((u64)rv[u] << 32));
+    }
+    __syncthreads();
+    load_round(base + CHUNK);                                          // on their way while this round is written
+    const u32 total = s_total;
+    for (u32 i = tid; i < total; i += THREADS) {
+      const u32 reg = s_reg[i], pos = s_off[reg] + i;
+      if (pos < cap && (u64)reg * cap + pos < a.n_cell) {
+        a.part_row[(u64)reg * cap + pos] = s_row[i];
+      } else {
+        status |= DS_DUPLICATE;            // more rows than cells
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int m2 = 32; m2 >= 1; m2 >>= 1) status |= shfl_xor_u64(status, m2);
+  if (lane_id() == 0 && status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
+}
+__global__ __launch_bounds__(SPLIT_REGIONS) void k_hang_clear(HangArgs a) {
+  if (threadIdx.x < CNT_COUNT) a.counters[threadIdx.x] = 0;
+  if (threadIdx.x < a.n_regions) a.part_fill[threadIdx.x] = 0;
+}
+__device__ __forceinline__ void store_member(const HangArgs& a, u64 p, u64 seq, u64 S, u64 R, u32 onset, bool moved) {
+  PAIR(a, CCLD_HPAIR_STALLED, p) = a.n_snap - 1 >= a.stall_snapshots && !moved ? 1 : 0;
+  PAIR(a, CCLD_HPAIR_SEQ, p) = (i64)seq;
+  PAIR(a, CCLD_HPAIR_SENT, p) = (i64)S;
+  PAIR(a, CCLD_HPAIR_RECV, p) = (i64)R;
+  PAIR(a, CCLD_HPAIR_WAITS_ON, p) = CCLD_NO_RANK;
+  PAIR(a, CCLD_HPAIR_ONSET, p) = onset;
+  a.wait_slot[p] = -1;
+  a.cand[p] = 0;
+  a.layer_max[p] = 0;          // takes the place of the marks
+}
+// One workgroup per region: its rows in order of arrival against the final states, then its members.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_hang_region(HangArgs a) {
+  extern __shared__ ulonglong2 s_final[];                              // final states | onsets | bitmap | moved
+  const u32 tid = threadIdx.x, reg = blockIdx.x;
+  const u32 per_member = a.n_ch * a.n_snap, cap = per_member << a.sb, n_ser = a.n_ch << a.sb, words = (cap + 31) / 32;
+  u32* s_onset = reinterpret_cast<u32*>(s_final + n_ser);
+  u32* s_bits = s_onset + n_ser;
+  u32* s_moved = s_bits + words;                                       // [2^sb]
+  __shared__ u32 s_cells;
+  const u64 p0 = (u64)reg << a.sb, q0 = p0 * a.n_ch, q_end = a.n_members * a.n_ch;
+  const u32 have = a.part_fill[reg], n = have < cap ? have : cap;
+  const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * cap;
+  for (u32 i = tid; i < n_ser; i += THREADS) {
+    s_final[i] = q0 + i < q_end ? a.final[q0 + i] : make_ulonglong2(0, 0);
+    s_onset[i] = 0;
+  }
+  for (u32 i = tid; i < words + (1u << a.sb); i += THREADS) s_bits[i] = 0;
+  if (tid == 0) s_cells = 0;
+  __syncthreads();
+  const u32 s_stall = a.n_snap - 1 >= a.stall_snapshots ? a.n_snap - 1 - a.stall_snapshots : ~0u;
+  constexpr int U = 4;
+  typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+  for (u32 i0 = tid; i0 < n; i0 += THREADS * U) {
+    u64x2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * THREADS < n) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * THREADS >= n) continue;
+      const u32 k = (u32)v[u].x & ((1u << SPLIT_CELL_BITS) - 1);
+      const u32 ser = (u32)(((u64)k * a.snap_inv) >> 32), s = k - ser * a.n_snap;
+      atomicOr(&s_bits[k >> 5], 1u << (k & 31));
+      const ulonglong2 f = s_final[ser];
+      if (f.x == v[u].x >> SPLIT_CELL_BITS && f.y == v[u].y) continue;
+      if (s_onset[ser] < s + 1) atomicMax(&s_onset[ser], s + 1);
+      if (s == s_stall) s_moved[ser / a.n_ch] = 1;
+    }
   }
   __syncthreads();
-  const u64 seq_max = s_seqmax;
+  u32 cells = 0;
+  for (u32 i = tid; i < words; i += THREADS) cells += (u32)__popc(s_bits[i]);
+  cells = wave_sum(cells);
+  if (lane_id() == 0) atomicAdd(&s_cells, cells);
+  for (u32 i = tid; i < (1u << a.sb) && p0 + i < a.n_members; i += THREADS) {
+    u64 seq = 0, S = 0, R = 0;
+    u32 onset = 0;
+    for (u32 ch = 0; ch < a.n_ch; ++ch) {
+      const ulonglong2 f = s_final[i * a.n_ch + ch];
+      const u32 o = s_onset[i * a.n_ch + ch];
+      seq = f.x > seq ? f.x : seq;
+      S += f.y & 0xFFFFFFFFull;
+      R += f.y >> 32;
+      onset = o > onset ? o : onset;
+    }
+    store_member(a, p0 + i, seq, S, R, onset, s_moved[i] != 0);
+  }
+  __syncthreads();
+  if (tid == 0) atomicAdd((unsigned long long*)&a.counters[CNT_NCELL], (unsigned long long)s_cells);
+}
+
+// Members and cells after the second pass: stalled, operation counter, chunk totals, onset of every (rank, communicator),
+// eight lanes to a member, and the cells that have a row.
+constexpr u32 PAIR_LANES = 8;
+__global__ __launch_bounds__(256) void k_hang_pairs(HangArgs a) {
+  __shared__ u32 s_cells;
+  const u32 tid = threadIdx.x;
+  const u64 t = (u64)blockIdx.x * 256 + tid, p = t / PAIR_LANES;
+  const u32 l = tid % PAIR_LANES;
+  if (tid == 0) s_cells = 0;
+  __syncthreads();
+  u32 cells = 0;
+  for (u64 i = t; i < (a.n_cell + 31) / 32; i += (u64)gridDim.x * 256) cells += (u32)__popc(a.cnt[i]);
+  cells = wave_sum(cells);
+  if (lane_id() == 0) atomicAdd(&s_cells, cells);
+  u64 seq = 0, S = 0, R = 0;
+  if (p < a.n_members)
+    for (u32 ch = l; ch < a.n_ch; ch += PAIR_LANES) {
+      const ulonglong2 f = a.final[p * a.n_ch + ch];
+      seq = f.x > seq ? f.x : seq;
+      S += f.y & 0xFFFFFFFFull;
+      R += f.y >> 32;
+    }
+#pragma unroll
+  for (u32 m = PAIR_LANES / 2; m >= 1; m >>= 1) {
+    const u64 o = shfl_xor_u64(seq, m);
+    seq = o > seq ? o : seq;
+    S += shfl_xor_u64(S, m); R += shfl_xor_u64(R, m);
+  }
+  if (p < a.n_members && l == 0) {
+    store_member(a, p, seq, S, R, a.mark[2 * p], a.mark[2 * p + 1] != 0);
+  }
+  __syncthreads();
+  if (tid == 0) atomicAdd((unsigned long long*)&a.counters[CNT_NCELL], (unsigned long long)s_cells);
+}
+
+// every row valid and exactly one for each cell
+__device__ __forceinline__ bool hang_rows_ok(const HangArgs& a) {
+  return a.checked || (a.counters[CNT_STATUS] == 0 && a.n_rows == a.n_cell && a.counters[CNT_NCELL] == a.n_cell);
+}
+
+// ---- per communicator: entered, idle test, decision tree, wait-for edges ------------------------
+__device__ __forceinline__ u64 wave_min_u64(u64 v) { return ~wave_max_u64(~v); }
+__device__ __forceinline__ u32 wave_min_u32(u32 v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) { const u32 o = __shfl_xor(v, m, CCLD_WAVE); v = o < v ? o : v; }
+  return v;
+}
+// One workgroup per communicator; K members per thread in registers (0: communicators of any size, re-read by every
+// step).  Each step is a chain of a load and a reduction, so what counts is how few there are: members are read once,
+// and a wavefront reduces in registers before its one LDS atomic (atomics of all lanes on one word run one after the
+// other; 4,096 members: 44 us with an atomic per thread and every step reading).
+struct HangMember { u64 seq; i64 sent, recv; bool stalled; };
+template <u32 THREADS, u32 K>
+__global__ __launch_bounds__(THREADS) void k_hang_comm(HangArgs a) {
+  __shared__ unsigned long long s_seqmax, s_minsum, s_minrecv, s_worst;
+  __shared__ u32 s_flags, s_best, s_ncand;      // flags: 1 not all entered, 2 any stalled, 4 not all stalled, 8 not idle
+  __shared__ u32 s_link[K ? K * THREADS : 1];   // hops << 16 | slot they lead to, LINK_ROOT set: a root
+  constexpr u32 LINK_ROOT = 0x8000u;
+  static_assert(K * THREADS <= LINK_ROOT / 2, "hops and slots fit 15 bits");
+  const u32 c = blockIdx.x, tid = threadIdx.x, lane = lane_id();
+  const u32 n = a.T.size[c], off = a.T.member_off[c];
+  const bool tree = a.T.algo[c] == CCLD_ALGO_TREE, ok = hang_rows_ok(a);
+  auto load_member = [&](u32 q) -> HangMember {
+    const u64 p = (u64)off + q;
+    return {(u64)PAIR(a, CCLD_HPAIR_SEQ, p), PAIR(a, CCLD_HPAIR_SENT, p), PAIR(a, CCLD_HPAIR_RECV, p), PAIR(a, CCLD_HPAIR_STALLED, p) != 0};
+  };
+  HangMember mem[K ? K : 1];
+#pragma unroll
+  for (u32 k = 0; k < K; ++k) if (tid + k * THREADS < n) mem[k] = load_member(tid + k * THREADS);
+  auto each = [&](auto&& f) {
+    if constexpr (K != 0) {
+#pragma unroll
+      for (u32 k = 0; k < K; ++k) if (tid + k * THREADS < n) f(tid + k * THREADS, mem[k]);
+    } else {
+      for (u32 q = tid; q < n; q += THREADS) f(q, load_member(q));
+    }
+  };
+  if (tid == 0) { s_seqmax = 0; s_minsum = ~0ull; s_minrecv = ~0ull; s_worst = 0; s_flags = 0; s_best = 0xFFFFFFFFu; s_ncand = 0; }
+  __syncthreads();
+  if (!ok) return;                              // the same for every thread
+  const bool some = (tid & ~(u32)(CCLD_WAVE - 1)) < n;      // the wavefront has members
   // depth of a slot in the tree (layers are contiguous in BFS order)
   auto depth_of = [&](u32 q) -> u32 {
     u32 d = 0;
@@ -361,48 +670,56 @@ __global__ __launch_bounds__(256) void k_hang_comm(HangArgs a) {
   };
   {
     u32 fl = 0;
-    unsigned long long minsum = ~0ull;
-    for (u32 q = tid; q < n; q += 256) {
-      const u64 p = off + q;
-      const bool entered = (u64)PAIR(a, CCLD_HPAIR_SEQ, p) == seq_max;
-      PAIR(a, CCLD_HPAIR_ENTERED, p) = entered ? 1 : 0;
-      if (!entered) fl |= 1 | 8;
-      if (PAIR(a, CCLD_HPAIR_STALLED, p)) fl |= 2; else fl |= 4;
+    u64 seqmax = 0, minsum = ~0ull;
+    each([&](u32 q, const HangMember& m) {
+      const u64 p = (u64)off + q, sum = (u64)(m.sent + m.recv);
+      seqmax = m.seq > seqmax ? m.seq : seqmax;
+      minsum = sum < minsum ? sum : minsum;
+      fl |= m.stalled ? 2 : 4;
       // identical totals across comparable ranks: every adjacent pair of the same layer
       if (q > 0 && (!tree || depth_of(q) == depth_of(q - 1)) &&
-          (PAIR(a, CCLD_HPAIR_SENT, p) != PAIR(a, CCLD_HPAIR_SENT, p - 1) ||
-           PAIR(a, CCLD_HPAIR_RECV, p) != PAIR(a, CCLD_HPAIR_RECV, p - 1)))
+          (m.sent != PAIR(a, CCLD_HPAIR_SENT, p - 1) || m.recv != PAIR(a, CCLD_HPAIR_RECV, p - 1)))
         fl |= 8;
-      const unsigned long long sum = (unsigned long long)(PAIR(a, CCLD_HPAIR_SENT, p) + PAIR(a, CCLD_HPAIR_RECV, p));
-      minsum = sum < minsum ? sum : minsum;
-      if (tree) atomicMax((unsigned long long*)&a.layer_max[off + depth_of(q)], sum);
+      if (tree) atomicMax((unsigned long long*)&a.layer_max[off + depth_of(q)], (unsigned long long)sum);
+    });
+    if (some) {
+      seqmax = wave_max_u64(seqmax); minsum = wave_min_u64(minsum);
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) fl |= __shfl_xor(fl, m, CCLD_WAVE);
+      if (lane == 0) { atomicMax(&s_seqmax, (unsigned long long)seqmax); atomicMin(&s_minsum, (unsigned long long)minsum); atomicOr(&s_flags, fl); }
     }
-    if (fl) atomicOr(&s_flags, fl);
-    if (tid < n) atomicMin(&s_minsum, minsum);
   }
   __syncthreads();
+  const u64 seq_max = s_seqmax, min_sum = s_minsum;
   // fewest SendCount + RecvCount, then fewest received, then smallest rank
   {
-    const unsigned long long ms = s_minsum;
-    unsigned long long mr = ~0ull;
-    for (u32 q = tid; q < n; q += 256)
-      if ((u64)(PAIR(a, CCLD_HPAIR_SENT, off + q) + PAIR(a, CCLD_HPAIR_RECV, off + q)) == ms) {
-        const unsigned long long v = (unsigned long long)PAIR(a, CCLD_HPAIR_RECV, off + q);
-        mr = v < mr ? v : mr;
-      }
-    if (mr != ~0ull) atomicMin(&s_minrecv, mr);
+    u32 fl = 0;
+    u64 mr = ~0ull;
+    each([&](u32 q, const HangMember& m) {
+      PAIR(a, CCLD_HPAIR_ENTERED, (u64)off + q) = m.seq == seq_max ? 1 : 0;
+      if (m.seq != seq_max) fl |= 1 | 8;
+      if ((u64)(m.sent + m.recv) == min_sum) mr = (u64)m.recv < mr ? (u64)m.recv : mr;
+    });
+    if (some) {
+      mr = wave_min_u64(mr);
+      const u64 late = ballot64(fl != 0);
+      if (lane == 0 && mr != ~0ull) atomicMin(&s_minrecv, (unsigned long long)mr);
+      if (lane == 0 && late) atomicOr(&s_flags, 1u | 8u);
+    }
   }
   __syncthreads();
   {
-    const unsigned long long ms = s_minsum, mr = s_minrecv;
+    const u64 mr = s_minrecv;
     u32 best = 0xFFFFFFFFu;
-    for (u32 q = tid; q < n; q += 256)
-      if ((u64)(PAIR(a, CCLD_HPAIR_SENT, off + q) + PAIR(a, CCLD_HPAIR_RECV, off + q)) == ms &&
-          (u64)PAIR(a, CCLD_HPAIR_RECV, off + q) == mr) {
-        const u32 rk = (u32)PAIR(a, CCLD_HPAIR_RANK, off + q);
-        best = rk < best ? rk : best;
-      }
-    if (best != 0xFFFFFFFFu) atomicMin(&s_best, best);
+    each([&](u32 q, const HangMember& m) {
+      if ((u64)(m.sent + m.recv) != min_sum || (u64)m.recv != mr) return;
+      const u32 rk = a.T.members[off + q];
+      best = rk < best ? rk : best;
+    });
+    if (some) {
+      best = wave_min_u32(best);
+      if (lane == 0 && best != 0xFFFFFFFFu) atomicMin(&s_best, best);
+    }
   }
   __syncthreads();
   const u32 flags = s_flags;
@@ -411,193 +728,330 @@ __global__ __launch_bounds__(256) void k_hang_comm(HangArgs a) {
   int cls = 0;
   if (hung) cls = !all_entered ? CCLD_HANG_H1_NOT_ENTERED : (!all_stalled ? CCLD_HANG_H2_INCONSISTENT : CCLD_HANG_H3_HARDWARE);
   if (tid == 0) {
-    HCOMM(a, CCLD_HCOMM_COMM, c) = c;
-    HCOMM(a, CCLD_HCOMM_HUNG, c) = hung ? 1 : 0;
-    HCOMM(a, CCLD_HCOMM_CLASS, c) = cls;
-    HCOMM(a, CCLD_HCOMM_SEQ_MAX, c) = (i64)seq_max;
-    HCOMM(a, CCLD_HCOMM_ROOT_BY_COUNT, c) = hung ? (i64)s_best : CCLD_NO_RANK;
-    HCOMM(a, CCLD_HCOMM_NCAND, c) = 0;
+    const i64 row[CCLD_HCOMM_NCOL] = {(i64)c, hung ? 1 : 0, cls, (i64)seq_max, hung ? (i64)s_best : CCLD_NO_RANK, 0};
+    for (int col = 0; col < CCLD_HCOMM_NCOL; ++col) {
+      HCOMM(a, col, c) = row[col];
+      if (a.out_comm && c < a.comm_cap) a.out_comm[(u64)col * a.comm_cap + c] = row[col];
+    }
+    if (hung) atomicAdd((unsigned long long*)&a.counters[CNT_NALERT], 1ull);
   }
   if (!hung) return;
   if (cls == CCLD_HANG_H1_NOT_ENTERED) {
-    for (u32 q = tid; q < n; q += 256) if (!PAIR(a, CCLD_HPAIR_ENTERED, off + q)) a.cand[off + q] = 1;
+    each([&](u32 q, const HangMember& m) { if (m.seq != seq_max) a.cand[off + q] = 1; });
     return;
   }
   if (cls == CCLD_HANG_H2_INCONSISTENT) {
-    for (u32 q = tid; q < n; q += 256) if (!PAIR(a, CCLD_HPAIR_STALLED, off + q)) a.cand[off + q] = 1;
+    each([&](u32 q, const HangMember& m) { if (!m.stalled) a.cand[off + q] = 1; });
     return;
   }
   // all entered, all hung
   if (!tree) {
-    for (u32 q = tid; q < n; q += 256) {
-      const u32 pred = (q + n - 1) % n, succ = (q + 1) % n;
-      const i64 Rq = PAIR(a, CCLD_HPAIR_RECV, off + q), Sq = PAIR(a, CCLD_HPAIR_SENT, off + q);
-      if (n > 1 && Rq >= PAIR(a, CCLD_HPAIR_SENT, off + pred)) {
-        PAIR(a, CCLD_HPAIR_WAITS_ON, off + q) = PAIR(a, CCLD_HPAIR_RANK, off + pred);
-        a.wait_slot[off + q] = (int)pred;
-      } else if (n > 1 && Sq - PAIR(a, CCLD_HPAIR_RECV, off + succ) >= (i64)a.fifo_depth) {
-        PAIR(a, CCLD_HPAIR_WAITS_ON, off + q) = PAIR(a, CCLD_HPAIR_RANK, off + succ);
-        a.wait_slot[off + q] = (int)succ;
-      } else {
+    each([&](u32 q, const HangMember& m) {
+      const u32 pred = q ? q - 1 : n - 1, succ = q + 1 < n ? q + 1 : 0;
+      u32 on = q;                               // itself: a root
+      if (n > 1 && m.recv >= PAIR(a, CCLD_HPAIR_SENT, off + pred)) on = pred;
+      else if (n > 1 && m.sent - PAIR(a, CCLD_HPAIR_RECV, off + succ) >= (i64)a.fifo_depth) on = succ;
+      if (on == q) {
         a.cand[off + q] = 1;
-        atomicAdd(&s_ncand, 1u);
+        s_ncand = 1;
+      } else {
+        PAIR(a, CCLD_HPAIR_WAITS_ON, off + q) = a.T.members[off + on];
+        a.wait_slot[off + q] = (int)on;
       }
-    }
+      if (K) s_link[q] = on == q ? q | LINK_ROOT : on | 1u << 16;
+    });
   } else {
-    for (u32 q = tid; q < n; q += 256) {
-      const u64 def = a.layer_max[off + depth_of(q)] - (u64)(PAIR(a, CCLD_HPAIR_SENT, off + q) + PAIR(a, CCLD_HPAIR_RECV, off + q));
+    each([&](u32 q, const HangMember& m) {
+      const u64 def = a.layer_max[off + depth_of(q)] - (u64)(m.sent + m.recv);
       atomicMax(&s_worst, (unsigned long long)def);
-    }
+    });
     __syncthreads();
     const u64 worst = s_worst;
     if (worst > 0)
-      for (u32 q = tid; q < n; q += 256) {
-        const u64 def = a.layer_max[off + depth_of(q)] - (u64)(PAIR(a, CCLD_HPAIR_SENT, off + q) + PAIR(a, CCLD_HPAIR_RECV, off + q));
-        if (def == worst) { a.cand[off + q] = 1; atomicAdd(&s_ncand, 1u); }
-      }
+      each([&](u32 q, const HangMember& m) {
+        const u64 def = a.layer_max[off + depth_of(q)] - (u64)(m.sent + m.recv);
+        if (def == worst) { a.cand[off + q] = 1; s_ncand = 1; }
+      });
   }
   __syncthreads();
-  if (s_ncand == 0)      // a pure cycle: the rank with the fewest counts
-    for (u32 q = tid; q < n; q += 256) if ((u32)PAIR(a, CCLD_HPAIR_RANK, off + q) == s_best) a.cand[off + q] = 1;
+  const bool cycle = s_ncand == 0;      // a pure cycle: the rank with the fewest counts
+  if (cycle)
+    each([&](u32 q, const HangMember&) {
+      if (a.T.members[off + q] != s_best) return;
+      a.cand[off + q] = 1;
+      if (K) s_link[q] = q | LINK_ROOT;
+    });
+  // Hops to a root by pointer jumping: after round r a link leads 2^r edges on, or to the root before that.
+  if (K && !tree) {
+    u32 link[K ? K : 1];
+    for (u32 span = 1; span < n; span <<= 1) {
+      __syncthreads();
+#pragma unroll
+      for (u32 k = 0; k < K; ++k) {
+        const u32 q = tid + k * THREADS;
+        if (q >= n) continue;
+        link[k] = s_link[q];
+        if (!(link[k] & LINK_ROOT)) {
+          const u32 m = s_link[link[k] & 0xFFFFu];
+          link[k] = (m & 0xFFFFu) | (((link[k] >> 16) + (m >> 16)) << 16);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (u32 k = 0; k < K; ++k) if (tid + k * THREADS < n) s_link[tid + k * THREADS] = link[k];
+    }
+    __syncthreads();
+    each([&](u32 q, const HangMember&) { PAIR(a, CCLD_HPAIR_HOPS, off + q) = s_link[q] & LINK_ROOT ? (i64)(s_link[q] >> 16) : -1; });
+  }
 }
 
-// ---- a not-entered rank that has entered another hung communicator is a victim --------------------
-__global__ __launch_bounds__(256) void k_hang_filter(HangArgs a) {
-  const u64 p = (u64)blockIdx.x * 256 + threadIdx.x;
-  if (p >= a.n_members || !a.cand[p]) return;
-  const u32 c = (u32)PAIR(a, CCLD_HPAIR_COMM, p), r = (u32)PAIR(a, CCLD_HPAIR_RANK, p);
-  if (HCOMM(a, CCLD_HCOMM_CLASS, c) != CCLD_HANG_H1_NOT_ENTERED) return;
+// ---- victims, hops along the wait-for edges to a root, candidates per communicator, the tables and the roots -------
+// A not-entered rank that has entered another hung communicator is a victim: no candidate.
+__device__ __forceinline__ bool is_victim(const HangArgs& a, u32 c, u32 r) {
+  if (HCOMM(a, CCLD_HCOMM_CLASS, c) != CCLD_HANG_H1_NOT_ENTERED) return false;
+  auto entered_hung = [&](u32 c2, u64 p2) { return (HCOMM(a, CCLD_HCOMM_HUNG, c2) != 0) & (PAIR(a, CCLD_HPAIR_ENTERED, p2) != 0); };
+  if (a.T.rank_cell4) {                    // the rank's (at most four) memberships in one load, then all looked at side by side
+    const uint4 m = grid_row_lookup(a, r);
+    const u32 w[4] = {m.x, m.y, m.z, m.w};
+    bool hit = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const u32 c2 = w[k] == ~0u ? c : w[k] >> a.T.pb;
+      hit |= entered_hung(c2, c2 == c ? 0 : w[k] & ((1u << a.T.pb) - 1)) && c2 != c;
+    }
+    return hit;
+  }
   for (u32 k = a.T.rank_comm_off[r]; k < a.T.rank_comm_off[r + 1]; ++k) {
-    const u32 c2 = a.T.rank_comms[k];
-    if (c2 == c || !HCOMM(a, CCLD_HCOMM_HUNG, c2)) continue;
-    const int q2 = slot_of(a.T, c2, r);
-    if (q2 >= 0 && PAIR(a, CCLD_HPAIR_ENTERED, (u64)a.T.member_off[c2] + q2)) { a.cand[p] = 2; return; }   // 2 = dropped
+    const u32 c2 = a.T.rank_comms[k], off2 = a.T.member_off[c2];
+    if (c2 != c && entered_hung(c2, (u64)off2 + a.T.sorted_slot[off2 + a.T.rank_slots[k]])) return true;
   }
+  return false;
 }
 
-// ---- hops along the wait-for edges to a root; candidates per communicator ---------------------------
-__global__ __launch_bounds__(256) void k_hang_hops(HangArgs a) {
+// Roots in (rank, communicator) order: the last workgroup sorts up to ROOTS_ONE of them in LDS.  More are sorted by
+// the host's radix sort afterwards: that many ranks freeze at once only when whole parts of a job never enter.
+constexpr u32 ROOTS_ONE = 1024;
+__device__ __forceinline__ void emit_root(const HangArgs& a, u32 k, u64 key) {
+  const u32 c = (u32)(key & (((u64)1 << a.cb) - 1));
+  store_agent(&a.out_root[CCLD_HROOT_RANK * a.root_cap + k], (i64)(key >> a.cb));
+  store_agent(&a.out_root[CCLD_HROOT_COMM * a.root_cap + k], (i64)c);
+  store_agent(&a.out_root[CCLD_HROOT_CLASS * a.root_cap + k], HCOMM(a, CCLD_HCOMM_CLASS, c));
+}
+__global__ __launch_bounds__(256) void k_hang_final(HangArgs a) {
+  __shared__ u64 s_key[ROOTS_ONE];
+  __shared__ u32 s_last;
   const u64 p = (u64)blockIdx.x * 256 + threadIdx.x;
-  if (p >= a.n_members) return;
-  const u32 c = (u32)PAIR(a, CCLD_HPAIR_COMM, p);
-  if (a.cand[p] == 1) atomicAdd((unsigned long long*)&HCOMM(a, CCLD_HCOMM_NCAND, c), 1ull);
-  if (!HCOMM(a, CCLD_HCOMM_HUNG, c)) return;
-  const u32 off = a.T.member_off[c], n = a.T.size[c];
-  u32 cur = (u32)(p - off);
-  i64 hops = 0;
-  while (true) {
-    if (a.cand[off + cur] == 1) break;
-    const int w = a.wait_slot[off + cur];
-    if (w < 0 || hops >= (i64)n) { hops = -1; break; }
-    cur = (u32)w;
-    ++hops;
+  const u32 tid = threadIdx.x, lane = lane_id();
+  if (hang_rows_ok(a)) {
+    bool root = false;
+    u32 c = ~0u, rank = 0;
+    if (p < a.n_members) {
+      c = a.T.member_comm[p];
+      rank = a.T.members[p];
+      // only a communicator that not everyone has entered has victims, and it has no wait-for edges: no walk meets one
+      root = a.cand[p] && !is_victim(a, c, rank);
+      i64 hops = -1;
+      if (root) {
+        hops = 0;
+      } else if (HCOMM(a, CCLD_HCOMM_CLASS, c) == CCLD_HANG_H3_HARDWARE && a.T.algo[c] != CCLD_ALGO_TREE) {
+        if (a.hops_known) hops = PAIR(a, CCLD_HPAIR_HOPS, p);
+        const u32 off = a.T.member_off[c], n = a.T.size[c];
+        u32 cur = (u32)(p - off);
+        i64 walked = 0;
+        while (!a.hops_known) {
+          const int w = a.wait_slot[off + cur];
+          if (w < 0 || walked >= (i64)n) break;
+          cur = (u32)w;
+          ++walked;
+          if (a.cand[off + cur]) { hops = walked; break; }
+        }
+      }
+      if (a.out_pair && p < a.pair_cap) {
+        const i64 row[CCLD_HPAIR_NCOL] = {(i64)rank, (i64)c, PAIR(a, CCLD_HPAIR_STALLED, p), PAIR(a, CCLD_HPAIR_ENTERED, p),
+                                          PAIR(a, CCLD_HPAIR_SEQ, p), PAIR(a, CCLD_HPAIR_SENT, p), PAIR(a, CCLD_HPAIR_RECV, p),
+                                          PAIR(a, CCLD_HPAIR_WAITS_ON, p), hops, PAIR(a, CCLD_HPAIR_ONSET, p)};
+#pragma unroll
+        for (int col = 0; col < CCLD_HPAIR_NCOL; ++col) store_agent(&a.out_pair[(u64)col * a.pair_cap + p], row[col]);
+      }
+    }
+    // roots of a wavefront take their places together, and count together per communicator
+    u64 m = ballot64(root);
+    if (m) {
+      u32 base = 0;
+      if (lane == 0) base = atomicAdd(reinterpret_cast<u32*>(&a.counters[CNT_NCAND]), (u32)__popcll(m));
+      base = __shfl(base, 0, CCLD_WAVE);
+      if (root) store_agent(&a.root_key[base + mbcnt64(m)], (i64)(((u64)rank << a.cb) | c));
+      while (m) {
+        const u32 first = (u32)__builtin_ctzll(m);
+        const u32 c1 = __shfl(c, (int)first, CCLD_WAVE);
+        const u64 same = ballot64(root && c == c1) & m;
+        if (lane == first && a.out_comm && c1 < a.comm_cap)
+          atomicAdd((unsigned long long*)&a.out_comm[(u64)CCLD_HCOMM_NCAND * a.comm_cap + c1], (unsigned long long)__popcll(same));
+        m &= ~same;
+      }
+    }
   }
-  PAIR(a, CCLD_HPAIR_HOPS, p) = hops;
+  if (!last_block(reinterpret_cast<u32*>(&a.counters[CNT_DONE]), gridDim.x, &s_last)) return;
+  const u32 n_root = load_agent(reinterpret_cast<const u32*>(&a.counters[CNT_NCAND]));
+  if (n_root && n_root <= ROOTS_ONE && a.root_cap) {
+    u32 n2 = 1;
+    while (n2 < n_root) n2 <<= 1;
+    for (u32 k = tid; k < n2; k += 256) {
+      s_key[k] = k < n_root ? (u64)load_agent(&a.root_key[k]) : ~0ull;
+    }
+    __syncthreads();
+    for (u32 len = 2; len <= n2; len <<= 1)
+      for (u32 d = len / 2; d >= 1; d >>= 1) {
+        for (u32 k = tid; k < n2 / 2; k += 256) {
+          const u32 i = 2 * k - (k & (d - 1)), j = i + d;
+          const bool up = (i & len) == 0;
+          if ((s_key[i] > s_key[j]) == up) {
+            const u64 tk = s_key[i]; s_key[i] = s_key[j]; s_key[j] = tk;
+          }
+        }
+        __syncthreads();
+      }
+    for (u32 k = tid; k < n_root && k < a.root_cap; k += 256) emit_root(a, k, s_key[k]);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  }
+  report_words(a.counters, a.host, a.ticket);
 }
-
-struct PredRoot {
-  const uint8_t* cand;
-  __device__ bool operator()(u32 p) const { return cand[p] == 1; }
-};
-struct PredHung {
-  const i64* hung;
-  __device__ bool operator()(u32 c) const { return hung[c] != 0; }
-};
-
-__global__ __launch_bounds__(256) void k_hang_root_keys(HangArgs a, const u32* list, u32 n_root, int cb, u64* key) {
+__global__ __launch_bounds__(256) void k_hang_root_emit(HangArgs a, const u32* sidx, u32 n_root) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_root) return;
-  const u32 p = list[k];
-  key[k] = ((u64)PAIR(a, CCLD_HPAIR_RANK, p) << cb) | (u64)PAIR(a, CCLD_HPAIR_COMM, p);
-}
-__global__ __launch_bounds__(256) void k_hang_root_emit(HangArgs a, const u32* list, const u32* sidx, u32 n_root,
-                                                        i64* root, u64 root_cap) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_root || k >= root_cap) return;
-  const u32 p = list[sidx[k]];
-  const u32 c = (u32)PAIR(a, CCLD_HPAIR_COMM, p);
-  root[CCLD_HROOT_RANK * root_cap + k] = PAIR(a, CCLD_HPAIR_RANK, p);
-  root[CCLD_HROOT_COMM * root_cap + k] = c;
-  root[CCLD_HROOT_CLASS * root_cap + k] = HCOMM(a, CCLD_HCOMM_CLASS, c);
-}
-
-// copy the first `rows` rows of every column of a column-major table into a table of another capacity
-__global__ __launch_bounds__(256) void k_copy_table(const i64* src, u64 src_cap, i64* dst, u64 dst_cap, u64 rows, int ncol) {
-  const u64 i = (u64)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows * (u64)ncol) return;
-  const u64 col = i / rows, r = i % rows;
-  dst[col * dst_cap + r] = src[col * src_cap + r];
+  if (k < n_root && k < a.root_cap) emit_root(a, k, (u64)a.root_key[sidx[k]]);
 }
 
 // ---- SendRate / RecvRate: count changes per operation (Section 4.1.2) ------------------------------
 #define RPAIR(a, col, p) (a.pair[(u64)(col) * a.n_members + (p)])
-#define RCOMM(a, col, c) (a.hcomm[(u64)(col) * a.T.n_comms + (c)])
 
-// One wavefront per member slot, lanes on consecutive snapshots of one channel.  A run of equal
-// operation counters is committed when the next run starts, so the open last run never counts.
+// One wavefront per time series, lanes on consecutive snapshots.  A run of equal operation counters is committed when the
+// next run starts, so the open last run never counts.
+struct RateSums { u64 ops_s, chg_s, ops_r, chg_r; };
+template <class Sample>
+__device__ __forceinline__ void rate_series(u32 n_snap, u32 lane, RateSums& t, Sample&& sample) {
+  const u64 below = ((u64)1 << lane) - 1;                // lanes before this one
+  u64 c_seq = 0, c_cnt = 0;                              // last sample of the previous chunk
+  u32 pend_s = 0, pend_r = 0;                            // changes seen so far in the run that is still open
+  for (u32 s0 = 0; s0 < n_snap; s0 += CCLD_WAVE) {
+    const u32 s = s0 + lane;
+    const bool in = s < n_snap;
+    u64 seq = 0, cnt = 0;
+    if (in) sample(s, &seq, &cnt);
+    u64 pseq = shfl_u64(seq, (int)lane - 1), pcnt = shfl_u64(cnt, (int)lane - 1);
+    if (lane == 0) { pseq = c_seq; pcnt = c_cnt; }
+    const bool start = in && (s == 0 || seq != pseq);
+    if (start) pcnt = 0;                                 // a run's first sample is compared with zero
+    const u64 B = ballot64(start);
+    const u64 Cs = ballot64(in && (u32)cnt != (u32)pcnt);
+    const u64 Cr = ballot64(in && (u32)(cnt >> 32) != (u32)(pcnt >> 32));
+    if (B == 0) {
+      pend_s += (u32)__popcll(Cs); pend_r += (u32)__popcll(Cr);
+    } else {
+      const u32 last = 63 - (u32)__clzll((long long)B);               // start of the run still open
+      const u64 closed = ((u64)1 << last) - 1;                        // samples of runs that close here
+      // this lane's run begins at the highest start at or below it (or came in from the last chunk)
+      const u64 Bat = B & (below | ((u64)1 << lane));
+      const bool carried = Bat == 0;
+      const u32 rs = carried ? 0u : 63 - (u32)__clzll((long long)Bat);
+      const u64 run_before = below & ~(((u64)1 << rs) - 1);           // lanes of my run before me
+      const bool mine = ((closed >> lane) & 1) != 0;
+      const bool first_s = mine && ((Cs >> lane) & 1) && (Cs & run_before) == 0 && !(carried && pend_s);
+      const bool first_r = mine && ((Cr >> lane) & 1) && (Cr & run_before) == 0 && !(carried && pend_r);
+      const u32 first_start = (u32)__builtin_ctzll(B);
+      // the carried run closes at the chunk's first start: it is one operation if it had a change
+      // earlier, else if one of its lanes here is a first change (counted below)
+      t.ops_s += (u64)__popcll(ballot64(first_s)) + ((pend_s && first_start <= last) ? 1 : 0);
+      t.ops_r += (u64)__popcll(ballot64(first_r)) + ((pend_r && first_start <= last) ? 1 : 0);
+      t.chg_s += pend_s + (u64)__popcll(Cs & closed);
+      t.chg_r += pend_r + (u64)__popcll(Cr & closed);
+      pend_s = (u32)__popcll(Cs & ~closed); pend_r = (u32)__popcll(Cr & ~closed);
+    }
+    c_seq = shfl_u64(seq, 63); c_cnt = shfl_u64(cnt, 63);
+  }
+}
+__device__ __forceinline__ void store_rates(const HangArgs& a, u64 p, const RateSums& t) {
+  RPAIR(a, CCLD_RATE_OPS_SEND, p) = (i64)t.ops_s;
+  RPAIR(a, CCLD_RATE_CHANGES_SEND, p) = (i64)t.chg_s;
+  RPAIR(a, CCLD_RATE_OPS_RECV, p) = (i64)t.ops_r;
+  RPAIR(a, CCLD_RATE_CHANGES_RECV, p) = (i64)t.chg_r;
+}
+// From the grid in memory: one wavefront per member slot.
 __global__ __launch_bounds__(256) void k_rate_pairs(HangArgs a) {
   const u32 lane = lane_id();
   const u64 p = (u64)blockIdx.x * 4 + threadIdx.x / CCLD_WAVE;
   if (p >= a.n_members) return;
-  u64 ops_s = 0, chg_s = 0, ops_r = 0, chg_r = 0, status = 0;
-  const u64 below = ((u64)1 << lane) - 1;                // lanes before this one
+  RateSums t{0, 0, 0, 0};
+  u64 status = 0;
   for (u32 ch = 0; ch < a.n_ch; ++ch) {
     const u64 base = (p * a.n_ch + ch) * a.n_snap;
-    u64 c_seq = 0, c_cnt = 0;                            // last sample of the previous chunk
-    u32 pend_s = 0, pend_r = 0;                          // changes seen so far in the run that is still open
-    for (u32 s0 = 0; s0 < a.n_snap; s0 += CCLD_WAVE) {
-      const u32 s = s0 + lane;
-      const bool in = s < a.n_snap;
-      u64 seq = 0, cnt = 0;
-      if (in) {
-        seq = a.cell[2 * (base + s)]; cnt = a.cell[2 * (base + s) + 1];
-        status |= cell_status(a, base + s, seq, cnt);
-      }
-      u64 pseq = shfl_u64(seq, (int)lane - 1), pcnt = shfl_u64(cnt, (int)lane - 1);
-      if (lane == 0) { pseq = c_seq; pcnt = c_cnt; }
-      const bool start = in && (s == 0 || seq != pseq);
-      if (start) pcnt = 0;                               // a run's first sample is compared with zero
-      const u64 B = ballot64(start);
-      const u64 Cs = ballot64(in && (u32)cnt != (u32)pcnt);
-      const u64 Cr = ballot64(in && (u32)(cnt >> 32) != (u32)(pcnt >> 32));
-      if (B == 0) {
-        pend_s += (u32)__popcll(Cs); pend_r += (u32)__popcll(Cr);
-      } else {
-        const u32 last = 63 - (u32)__clzll((long long)B);             // start of the run still open
-        const u64 closed = ((u64)1 << last) - 1;                      // samples of runs that close here
-        // this lane's run begins at the highest start at or below it (or came in from the last chunk)
-        const u64 Bat = B & (below | ((u64)1 << lane));
-        const bool carried = Bat == 0;
-        const u32 rs = carried ? 0u : 63 - (u32)__clzll((long long)Bat);
-        const u64 run_before = below & ~(((u64)1 << rs) - 1);         // lanes of my run before me
-        const bool mine = ((closed >> lane) & 1) != 0;
-        const bool first_s = mine && ((Cs >> lane) & 1) && (Cs & run_before) == 0 && !(carried && pend_s);
-        const bool first_r = mine && ((Cr >> lane) & 1) && (Cr & run_before) == 0 && !(carried && pend_r);
-        const u32 first_start = (u32)__builtin_ctzll(B);
-        // the carried run closes at the chunk's first start: it is one operation if it had a change
-        // earlier, else if one of its lanes here is a first change (counted below)
-        ops_s += (u64)__popcll(ballot64(first_s)) + ((pend_s && first_start <= last) ? 1 : 0);
-        ops_r += (u64)__popcll(ballot64(first_r)) + ((pend_r && first_start <= last) ? 1 : 0);
-        chg_s += pend_s + (u64)__popcll(Cs & closed);
-        chg_r += pend_r + (u64)__popcll(Cr & closed);
-        pend_s = (u32)__popcll(Cs & ~closed); pend_r = (u32)__popcll(Cr & ~closed);
-      }
-      c_seq = shfl_u64(seq, 63); c_cnt = shfl_u64(cnt, 63);
-    }
+    rate_series(a.n_snap, lane, t, [&](u32 s, u64* seq, u64* cnt) {
+      *seq = a.cell[2 * (base + s)]; *cnt = a.cell[2 * (base + s) + 1];
+      status |= cell_status(a, base + s, *seq, *cnt);
+    });
   }
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) status |= shfl_xor_u64(status, m);
   if (lane == 0) {
     if (status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
-    u32 lo = 0, hi = a.T.n_comms;
-    while (hi - lo > 1) { const u32 m = (lo + hi) / 2; if (a.T.member_off[m] <= p) lo = m; else hi = m; }
-    RPAIR(a, CCLD_RATE_RANK, p) = a.T.members[p];
-    RPAIR(a, CCLD_RATE_COMM, p) = lo;
-    RPAIR(a, CCLD_RATE_OPS_SEND, p) = (i64)ops_s;
-    RPAIR(a, CCLD_RATE_CHANGES_SEND, p) = (i64)chg_s;
-    RPAIR(a, CCLD_RATE_OPS_RECV, p) = (i64)ops_r;
-    RPAIR(a, CCLD_RATE_CHANGES_RECV, p) = (i64)chg_r;
+    store_rates(a, p, t);
   }
+}
+// From the regrouped rows: a workgroup places the rows of its region in LDS by cell, then its wavefronts take the
+// series one by one.  The rows are read once and the grid never exists in memory.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_rate_region(HangArgs a) {
+  extern __shared__ ulonglong2 s_cell[];                               // [cap] cells | sums of every member | bitmap
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE, reg = blockIdx.x;
+  const u32 per_member = a.n_ch * a.n_snap, cap = per_member << a.sb, words = (cap + 31) / 32, members = 1u << a.sb;
+  u64* s_sum = reinterpret_cast<u64*>(s_cell + cap);
+  u32* s_bits = reinterpret_cast<u32*>(s_sum + 4 * members);
+  __shared__ u32 s_cells;
+  const u64 p0 = (u64)reg << a.sb;
+  const u32 have = a.part_fill[reg], n = have < cap ? have : cap;
+  const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * cap;
+  for (u32 i = tid; i < words; i += THREADS) s_bits[i] = 0;
+  for (u32 i = tid; i < 4 * members; i += THREADS) s_sum[i] = 0;
+  if (tid == 0) s_cells = 0;
+  __syncthreads();
+  constexpr int U = 4;
+  typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+  for (u32 i0 = tid; i0 < n; i0 += THREADS * U) {
+    u64x2 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * THREADS < n) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * THREADS >= n) continue;
+      const u32 k = (u32)v[u].x & ((1u << SPLIT_CELL_BITS) - 1);
+      s_cell[k] = make_ulonglong2(v[u].x >> SPLIT_CELL_BITS, v[u].y);
+      atomicOr(&s_bits[k >> 5], 1u << (k & 31));
+    }
+  }
+  __syncthreads();
+  u32 cells = 0;
+  for (u32 i = tid; i < words; i += THREADS) cells += (u32)__popc(s_bits[i]);
+  cells = wave_sum(cells);
+  if (lane == 0) atomicAdd(&s_cells, cells);
+  const u64 left = a.n_members - p0;
+  const u32 n_ser = (u32)(left < members ? left : members) * a.n_ch;
+  for (u32 q = wave; q < n_ser; q += THREADS / CCLD_WAVE) {
+    RateSums t{0, 0, 0, 0};
+    const ulonglong2* cells_q = s_cell + q * a.n_snap;
+    rate_series(a.n_snap, lane, t, [&](u32 s, u64* seq, u64* cnt) { *seq = cells_q[s].x; *cnt = cells_q[s].y; });
+    unsigned long long* sum = reinterpret_cast<unsigned long long*>(s_sum + 4 * (q / a.n_ch));
+    if (lane == 0) {
+      if (t.ops_s) atomicAdd(&sum[0], (unsigned long long)t.ops_s);
+      if (t.chg_s) atomicAdd(&sum[1], (unsigned long long)t.chg_s);
+      if (t.ops_r) atomicAdd(&sum[2], (unsigned long long)t.ops_r);
+      if (t.chg_r) atomicAdd(&sum[3], (unsigned long long)t.chg_r);
+    }
+  }
+  __syncthreads();
+  for (u32 i = tid; i < members && i < left; i += THREADS)
+    store_rates(a, p0 + i, RateSums{s_sum[4 * i], s_sum[4 * i + 1], s_sum[4 * i + 2], s_sum[4 * i + 3]});
+  if (tid == 0) atomicAdd((unsigned long long*)&a.counters[CNT_NCELL], (unsigned long long)s_cells);
 }
 
 // a rate (ops / changes, rank); changes == 0 means "no rate" and loses against everything
@@ -610,39 +1064,52 @@ __device__ __forceinline__ bool rate_less(const RateCand& x, const RateCand& y) 
   return x.rank < y.rank;
 }
 
-// One workgroup per communicator: the member of minimal SendRate, RecvRate, and of both kinds.
+// One workgroup per communicator: the member of minimal SendRate, RecvRate, and of both kinds; the caller's tables.
+// Small workgroups, and the report in a launch of its own: 1,008 ranks in 343 communicators took 30 us with 1,024 threads
+// each and the last one reporting (their arrivals are atomics on one word), 13 us before the tables were written here.
 __global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__ rate_root) {
-  __shared__ RateCand s_best[3][256];
+  __shared__ RateCand s_best[2][256];
   const u32 c = blockIdx.x, tid = threadIdx.x;
   const u32 off = a.T.member_off[c], n = a.T.size[c];
-  RateCand best[3] = {{0, 0, 0xFFFFFFFFu}, {0, 0, 0xFFFFFFFFu}, {0, 0, 0xFFFFFFFFu}};
+  if (!hang_rows_ok(a)) return;                  // the same for every thread
+  RateCand best[2] = {{0, 0, 0xFFFFFFFFu}, {0, 0, 0xFFFFFFFFu}};
   for (u32 q = tid; q < n; q += 256) {
     const u64 p = (u64)off + q;
-    const u32 rk = (u32)RPAIR(a, CCLD_RATE_RANK, p);
+    const u32 rk = a.T.members[p];
     const RateCand snd{(u64)RPAIR(a, CCLD_RATE_OPS_SEND, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_SEND, p), rk};
     const RateCand rcv{(u64)RPAIR(a, CCLD_RATE_OPS_RECV, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_RECV, p), rk};
+    if (a.out_pair && p < a.pair_cap) {
+      a.out_pair[CCLD_RATE_RANK * a.pair_cap + p] = (i64)rk;
+      a.out_pair[CCLD_RATE_COMM * a.pair_cap + p] = (i64)c;
+      a.out_pair[CCLD_RATE_OPS_SEND * a.pair_cap + p] = (i64)snd.ops;
+      a.out_pair[CCLD_RATE_CHANGES_SEND * a.pair_cap + p] = (i64)snd.chg;
+      a.out_pair[CCLD_RATE_OPS_RECV * a.pair_cap + p] = (i64)rcv.ops;
+      a.out_pair[CCLD_RATE_CHANGES_RECV * a.pair_cap + p] = (i64)rcv.chg;
+    }
     if (rate_less(snd, best[0])) best[0] = snd;
     if (rate_less(rcv, best[1])) best[1] = rcv;
-    if (rate_less(snd, best[2])) best[2] = snd;
-    if (rate_less(rcv, best[2])) best[2] = rcv;
   }
-  for (int k = 0; k < 3; ++k) s_best[k][tid] = best[k];
+  s_best[0][tid] = best[0]; s_best[1][tid] = best[1];
   __syncthreads();
-  for (u32 w = 128; w >= 1; w >>= 1) {
-    if (tid < w)
-      for (int k = 0; k < 3; ++k)
-        if (rate_less(s_best[k][tid + w], s_best[k][tid])) s_best[k][tid] = s_best[k][tid + w];
+  u32 w = 128;
+  while (w >= 1 && w >= n) w >>= 1;             // threads beyond the members have nothing to add
+  for (; w >= 1; w >>= 1) {
+    if (tid < 2 * w) {                          // both kinds side by side
+      const u32 k = tid >= w, i = k ? tid - w : tid;
+      if (rate_less(s_best[k][i + w], s_best[k][i])) s_best[k][i] = s_best[k][i + w];
+    }
     __syncthreads();
   }
   if (tid == 0) {
-    RCOMM(a, CCLD_RCOMM_COMM, c) = c;
-    RCOMM(a, CCLD_RCOMM_ROOT_SEND, c) = s_best[0][0].chg ? (i64)s_best[0][0].rank : (i64)CCLD_NO_RANK;
-    RCOMM(a, CCLD_RCOMM_ROOT_RECV, c) = s_best[1][0].chg ? (i64)s_best[1][0].rank : (i64)CCLD_NO_RANK;
-    const i64 root = s_best[2][0].chg ? (i64)s_best[2][0].rank : (i64)CCLD_NO_RANK;
-    RCOMM(a, CCLD_RCOMM_ROOT, c) = root;
-    rate_root[c] = root;
+    const RateCand snd = s_best[0][0], rcv = s_best[1][0], both = rate_less(snd, rcv) ? snd : rcv;
+    const i64 row[CCLD_RCOMM_NCOL] = {(i64)c, snd.chg ? (i64)snd.rank : (i64)CCLD_NO_RANK, rcv.chg ? (i64)rcv.rank : (i64)CCLD_NO_RANK,
+                                      both.chg ? (i64)both.rank : (i64)CCLD_NO_RANK};
+    if (a.out_comm && c < a.comm_cap)
+      for (int col = 0; col < CCLD_RCOMM_NCOL; ++col) a.out_comm[(u64)col * a.comm_cap + c] = row[col];
+    rate_root[c] = row[CCLD_RCOMM_ROOT];
   }
 }
+__global__ __launch_bounds__(CCLD_WAVE) void k_report(const u64* counters, u64* host, u64 ticket) { report_words(counters, host, ticket); }
 
 // ---- Probing Frames (Section 5.1) -------------------------------------------------------------------
 struct FrameArgs {
@@ -761,38 +1228,31 @@ struct HangScratch {
   int32_t* wait_slot;        // [n_members]
   uint8_t* cand;             // [n_members]
   uint64_t* layer_max;       // [n_members]
-  uint32_t* root_list;       // [n_members + 1]
-  uint32_t* tiles_a;         // [n_members / SEL_TILE + 2] per-tile counts of the root selection
-  uint32_t* tiles_b;         // [n_comms / SEL_TILE + 2] per-tile counts of the hung-communicator selection
-  uint32_t* comm_list;       // [n_comms] hung communicators
   SortBuffers sb;            // root list sort: n_members items
   uint64_t* keyC;            // [n_members]
   uint64_t sort_cap;
+  ulonglong2* split_row;     // [n_cell] regrouped rows, or null: no room for them
+  ulonglong2* split_final;   // [n_members * n_channels]
   uint8_t* stage;            // [stage_bytes] staging for host-resident rows, or null
   uint64_t stage_bytes;
-  bool fill_kernels;         // clear with fill kernels instead of hipMemsetAsync
 };
 
-static HangScratch scratch_of_context(ccld_ctx* c) {
+static HangScratch scratch_of_context(ccld_ctx* c, bool on_device) {
   HangScratch S;
   S.counters = c->counters; S.cell = c->h_cell; S.cnt = c->h_cnt; S.pair = c->h_pair; S.hcomm = c->h_comm;
-  S.wait_slot = c->h_wait_slot; S.cand = c->h_cand; S.layer_max = c->h_layer_max; S.root_list = c->h_root_list;
-  S.tiles_a = c->tile_flags; S.tiles_b = c->tile_heads; S.comm_list = c->alert_list;
+  S.wait_slot = c->h_wait_slot; S.cand = c->h_cand; S.layer_max = c->h_layer_max;
   S.sb.key[0] = c->sb.key[0]; S.sb.idx[0] = c->sb.idx[0]; S.sb.key[1] = c->sb.key[1]; S.sb.idx[1] = c->sb.idx[1];
   S.sb.table = c->table2; S.sb.totals = c->totals2;
-  S.keyC = c->keyC; S.sort_cap = c->sort_cap; S.stage = c->h_stage; S.stage_bytes = c->snap_cap * 32; S.fill_kernels = false;
+  S.keyC = c->keyC; S.sort_cap = c->sort_cap; S.stage = c->h_stage; S.stage_bytes = c->snap_cap * 32;
+  // rows that are on the device already leave the staging area free
+  S.split_row = on_device ? reinterpret_cast<ulonglong2*>(c->h_stage) : nullptr;
+  S.split_final = reinterpret_cast<ulonglong2*>(c->h_cell);
   return S;
 }
 
-static hipError_t clear_bytes(hipStream_t st, void* p, int value, uint64_t bytes, bool fill_kernels) {
-  if (!fill_kernels) return hipMemsetAsync(p, value, bytes, st);
-  launch_fill_u64(st, (uint64_t*)p, (bytes + 7) / 8, value ? ~0ull : 0ull);     // regions are padded to 256 bytes
-  return hipGetLastError();
-}
-
-// Stages host-resident rows, clears the grid's presence counts and places every row in its cell.
-static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_snapshots* sn, uint64_t n_rows,
-                                  uint64_t n_cell, HangArgs& a, bool exact) {
+// Stages host-resident rows; the arguments that the passes share.
+static hipError_t snapshot_args(ccld_ctx* c, const HangScratch& S, const ccld_snapshots* sn, uint64_t n_rows,
+                                uint64_t n_cell, HangArgs& a) {
   hipStream_t st = c->stream;
   std::memset(&a, 0, sizeof(a));
   hipError_t e = hipSuccess;
@@ -813,12 +1273,21 @@ static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_
   a.cell = S.cell; a.cnt = S.cnt; a.pair = S.pair; a.hcomm = S.hcomm; a.wait_slot = S.wait_slot;
   a.cand = S.cand; a.layer_max = S.layer_max; a.counters = S.counters;
   a.stall_snapshots = c->p.stall_snapshots; a.fifo_depth = c->p.fifo_depth;
+  a.n_cell = n_cell; a.mark = reinterpret_cast<uint32_t*>(S.layer_max);
+  a.root_key = reinterpret_cast<int64_t*>(S.keyC); a.cb = c->kf.cb; a.host = c->h_pinned;
+  return hipSuccess;
+}
 
+// Clears the grid's presence counts and places every row in its cell.
+static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_snapshots* sn, uint64_t n_rows,
+                                  uint64_t n_cell, HangArgs& a, bool exact) {
+  hipStream_t st = c->stream;
+  hipError_t e = hipSuccess;
   c->prof.begin(CCLD_PROF_HANG_PLACE);
-  if ((e = clear_bytes(st, S.counters, 0, sizeof(uint64_t) * CNT_COUNT, S.fill_kernels)) != hipSuccess) return e;
+  if ((e = hipMemsetAsync(S.counters, 0, sizeof(uint64_t) * CNT_COUNT, st)) != hipSuccess) return e;
   a.exact = exact ? 1 : 0;
-  if (exact) e = clear_bytes(st, S.cnt, 0, sizeof(uint32_t) * ((n_cell + 31) / 32), S.fill_kernels);
-  else e = clear_bytes(st, S.cell, 0xFF, 16 * n_cell, S.fill_kernels);
+  if (exact) e = hipMemsetAsync(S.cnt, 0, sizeof(uint32_t) * ((n_cell + 31) / 32), st);
+  else e = hipMemsetAsync(S.cell, 0xFF, 16 * n_cell, st);
   if (e != hipSuccess) return e;
   // large grids whose rows are already on the device (the staging area is free then) are placed in two steps
   int rb = 16;
@@ -831,7 +1300,7 @@ static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_
     a.part_pay = reinterpret_cast<ulonglong2*>(S.stage);
     a.part_idx = reinterpret_cast<uint32_t*>(S.stage + (n_regions << rb) * 16);
     a.part_fill = S.cnt;                       // the presence bitmap is not in use in this mode
-    if ((e = clear_bytes(st, S.cnt, 0, sizeof(uint32_t) * PART_REGIONS, S.fill_kernels)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(S.cnt, 0, sizeof(uint32_t) * PART_REGIONS, st)) != hipSuccess) return e;
     uint64_t g = (n_rows + PART_CHUNK - 1) / PART_CHUNK; if (g > 1024) g = 1024;
     uint64_t chunk = (n_rows + g - 1) / g;
     chunk = (chunk + PART_CHUNK - 1) / PART_CHUNK * PART_CHUNK;
@@ -868,65 +1337,97 @@ static ccld_status check_hang_args(ccld_ctx* c, const ccld_snapshots* sn, uint64
   return CCLD_OK;
 }
 
+// The regions of a grid: false where its rows are not regrouped.  As many regions as one workgroup each keeps the chip
+// busy with (129 to 256; more cost the split pass an atomic each per round), as far as a region fits LDS.
+static bool split_regions(HangArgs& a, const HangScratch& S, size_t (*lds)(u32, u32, int), size_t lds_max) {
+  const uint64_t per_member = (uint64_t)a.n_ch * a.n_snap;
+  if (!S.split_row || !a.n_rows || a.n_cell >= (1ull << 31) || a.n_snap < 2 || a.n_snap > 16384 || a.n_ch > 1024) return false;
+  int sb = 0;
+  while (((a.n_members - 1) >> sb) >= SPLIT_REGIONS / 2) ++sb;
+  while (sb > 0 && ((per_member << sb) > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, sb) > lds_max)) --sb;
+  const uint64_t regions = ((a.n_members - 1) >> sb) + 1;
+  if (regions > SPLIT_REGIONS || per_member > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, sb) > lds_max ||
+      regions > a.n_cell / 32 + 1) return false;
+  a.sb = sb; a.n_regions = (uint32_t)regions; a.snap_inv = (uint32_t)((1ull << 32) / a.n_snap + 1);
+  a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.cnt;
+  return true;
+}
+template <int THREADS, int U>
+static void launch_split_of(hipStream_t st, const HangArgs& a) {
+  constexpr uint32_t CHUNK = THREADS * U;
+  uint64_t g = std::min<uint64_t>((a.n_rows + CHUNK - 1) / CHUNK, 512);
+  const uint64_t chunk = ((a.n_rows + g - 1) / g + CHUNK - 1) / CHUNK * CHUNK;
+  g = (a.n_rows + chunk - 1) / chunk;
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(k_hang_split<THREADS, U>), dim3((uint32_t)g), dim3(THREADS), CHUNK * 18, st, a, chunk);
+}
+static void launch_split(hipStream_t st, const HangArgs& a) {
+  hipLaunchKernelGGL(k_hang_clear, dim3(1), dim3(SPLIT_REGIONS), 0, st, a);
+  // few rows: smaller rounds, for the sake of more workgroups
+  if (a.n_rows < (1u << 18)) launch_split_of<512, 2>(st, a);
+  else launch_split_of<512, 6>(st, a);
+}
+static void launch_scan(hipStream_t st, const HangArgs& a) {
+  const uint64_t want = std::max<uint64_t>((a.n_rows + 255) / 256, 1);
+  hipLaunchKernelGGL(k_hang_last, dim3((uint32_t)std::min<uint64_t>(want, 2048)), dim3(256), 0, st, a);
+  if (a.n_rows) hipLaunchKernelGGL(k_hang_scan<4>, dim3((uint32_t)std::min<uint64_t>(want, 4096)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_hang_pairs, dim3((uint32_t)((a.n_members * PAIR_LANES + 255) / 256)), dim3(256), 0, st, a);
+}
+
+// Data errors of a pass that counted the cells with a row: fewer of them than valid rows means that some cell has two.
+static uint64_t snapshot_status(const ccld_ctx* c, uint64_t n_rows, uint64_t n_cell) {
+  const uint64_t bits = c->h_pinned[CNT_STATUS], cells = c->h_pinned[CNT_NCELL];
+  return bits ? bits : cells < n_rows ? (uint64_t)DS_DUPLICATE : cells < n_cell ? (uint64_t)DS_SNAPSHOT_GAP : 0;
+}
+
 // the hang pass proper, on scratch memory S (n_cell cells and n_rows rows fit it)
 static ccld_status locate_hang_on(ccld_ctx* c, const HangScratch& S, const ccld_snapshots* sn, uint64_t n_rows,
                                   uint64_t n_cell, ccld_hang_result* o) {
   hipStream_t st = c->stream;
   HangArgs a;
   const uint32_t nm = (uint32_t)c->n_members;
-  // One row per cell is the normal case: the rows are placed without the presence bitmap (its atomics are a
-  // third of the placement's time) and the per-member pass looks for cells that nobody wrote.  If it finds one
-  // and no row was refused for a worse reason, or if the row count already rules the normal case out, the
-  // placement is repeated with the bitmap, which tells duplicates from gaps.
-  for (bool exact = n_rows != n_cell;; exact = true) {
-    HIP_TRY(place_snapshots(c, S, sn, n_rows, n_cell, a, exact));
-    hipLaunchKernelGGL(k_hang_pairs, dim3((nm + 3) / 4), dim3(256), 0, st, a);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(c->h_pinned, S.counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (exact || c->h_pinned[CNT_STATUS] != (uint64_t)DS_SUSPECT) break;
+  HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));
+  a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
+  a.out_root = o->root; a.root_cap = o->root_cap;
+  for (bool split = split_regions(a, S, region_lds, SPLIT_LDS);; split = false) {
+    a.ticket = ++c->ticket;
+    if (!split) a.final = reinterpret_cast<ulonglong2*>(S.cell);
+    c->prof.begin(CCLD_PROF_HANG_PLACE);
+    if (split) {
+      launch_split(st, a);
+      const size_t lds = region_lds(a.n_ch, a.n_snap, a.sb);
+      if (((uint64_t)a.n_ch * a.n_snap << a.sb) >= 8192) hipLaunchKernelGGL(k_hang_region<1024>, dim3(a.n_regions), dim3(1024), lds, st, a);
+      else hipLaunchKernelGGL(k_hang_region<256>, dim3(a.n_regions), dim3(256), lds, st, a);
+    } else {
+      launch_scan(st, a);
+    }
+    c->prof.split(CCLD_PROF_HANG_PLACE, CCLD_PROF_HANG);
+    const dim3 comms(c->topo.n_comms);
+    a.hops_known = c->max_comm_size <= 4096;
+    if (c->max_comm_size <= 256) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_hang_comm<256, 1>), comms, dim3(256), 0, st, a);
+    else if (c->max_comm_size <= 4096) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_hang_comm<1024, 4>), comms, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_hang_comm<1024, 0>), comms, dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(k_hang_final, dim3((nm + 255) / 256), dim3(256), 0, st, a);
     c->prof.end(CCLD_PROF_HANG);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
+    if (!split || !(c->h_pinned[CNT_STATUS] & DS_SUSPECT)) break;      // an operation counter too large to be regrouped
   }
-  if (c->h_pinned[CNT_STATUS]) { c->prof.end(CCLD_PROF_HANG); c->prof.collect(); return o->status = hang_status(c->h_pinned[CNT_STATUS]); }
-
-  hipLaunchKernelGGL(k_hang_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_hang_filter, dim3((nm + 255) / 256), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(k_hang_hops, dim3((nm + 255) / 256), dim3(256), 0, st, a);
-  // roots in (rank, communicator) order
-  PredRoot pr{S.cand};
-  run_select(st, pr, nm, S.tiles_a, S.root_list, &S.counters[CNT_NCAND]);
-  PredHung ph{S.hcomm + (uint64_t)CCLD_HCOMM_HUNG * c->topo.n_comms};
-  run_select(st, ph, c->topo.n_comms, S.tiles_b, S.comm_list, &S.counters[CNT_NALERT]);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(c->h_pinned, S.counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  const uint64_t bits = snapshot_status(c, n_rows, n_cell);
+  if (bits) { c->prof.collect(); return o->status = hang_status(bits); }
   const uint32_t n_root = (uint32_t)c->h_pinned[CNT_NCAND];
   o->n_root = n_root;
   o->n_hung_comm = c->h_pinned[CNT_NALERT];
   o->n_pair = c->n_members;
-  if (n_root && o->root_cap) {
+  if (n_root > ROOTS_ONE && o->root_cap) {
     const SortBuffers& sb2 = S.sb;
     if (n_root > S.sort_cap) return o->status = CCLD_E_CAPACITY;
-    hipLaunchKernelGGL(k_hang_root_keys, dim3((n_root + 255) / 256), dim3(256), 0, st, a, (const u32*)S.root_list, n_root, c->kf.cb, S.keyC);
     KeySource ks; ks.key = S.keyC; ks.head = 0; ks.cap = n_root; ks.squeeze = 0; ks.hi_shift = 0; ks.lo_bits = 0; ks.lo_mask = 0; ks.lo_sub = 0;
     const int r = radix_sort_pairs(st, ks, n_root, sb2, c->kf.cb + c->rank_bits);
     if (r < 0) return o->status = CCLD_E_HIP;
-    hipLaunchKernelGGL(k_hang_root_emit, dim3((n_root + 255) / 256), dim3(256), 0, st, a, (const u32*)S.root_list,
-                       (const u32*)sb2.idx[r], n_root, o->root, o->root_cap);
+    hipLaunchKernelGGL(k_hang_root_emit, dim3((n_root + 255) / 256), dim3(256), 0, st, a, (const u32*)sb2.idx[r], n_root);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
   }
-  if (o->pair && o->pair_cap) {
-    const uint64_t rows = std::min<uint64_t>(o->pair_cap, c->n_members);
-    hipLaunchKernelGGL(k_copy_table, dim3((uint32_t)((rows * CCLD_HPAIR_NCOL + 255) / 256)), dim3(256), 0, st,
-                       (const i64*)S.pair, c->n_members, o->pair, o->pair_cap, rows, (int)CCLD_HPAIR_NCOL);
-  }
-  if (o->comm && o->comm_cap) {
-    const uint64_t rows = std::min<uint64_t>(o->comm_cap, c->topo.n_comms);
-    hipLaunchKernelGGL(k_copy_table, dim3((uint32_t)((rows * CCLD_HCOMM_NCOL + 255) / 256)), dim3(256), 0, st,
-                       (const i64*)S.hcomm, (uint64_t)c->topo.n_comms, o->comm, o->comm_cap, rows, (int)CCLD_HCOMM_NCOL);
-  }
-  c->prof.end(CCLD_PROF_HANG);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
   c->prof.collect();
   if (o->n_root > o->root_cap || (o->pair && o->pair_cap < c->n_members) || (o->comm && o->comm_cap < c->topo.n_comms))
     o->status = CCLD_W_TRUNCATED;
@@ -939,7 +1440,7 @@ extern "C" ccld_status ccld_locate_hang(ccld_ctx* c, const ccld_snapshots* sn, u
   if (s != CCLD_OK) return s;
   if (n_cell > c->snap_cap || n_rows > c->snap_cap) return o->status = CCLD_E_CAPACITY;
   c->chain_ready = false;       // the root list is sorted in the window's sort buffers
-  return locate_hang_on(c, scratch_of_context(c), sn, n_rows, n_cell, o);
+  return locate_hang_on(c, scratch_of_context(c, sn->on_device), sn, n_rows, n_cell, o);
 }
 
 // ---- hang location on the library's static device array ------------------------------------------------
@@ -1008,10 +1509,6 @@ extern "C" ccld_status ccld_locate_hang_static(ccld_ctx* c, const ccld_snapshots
   S.wait_slot = w.take<int32_t>(nm);
   S.cand = w.take<uint8_t>(nm);
   S.layer_max = w.take<uint64_t>(nm);
-  S.root_list = w.take<uint32_t>(nm + 1);
-  S.tiles_a = w.take<uint32_t>(nm / SEL_TILE + 3);
-  S.tiles_b = w.take<uint32_t>(nc / SEL_TILE + 3);
-  S.comm_list = w.take<uint32_t>(nc + 1);
   for (int i = 0; i < 2; ++i) { S.sb.key[i] = w.take<uint64_t>(nm + 1); S.sb.idx[i] = w.take<uint32_t>(nm + 1); }
   S.sb.table = w.take<uint32_t>(sort_table_words(nm + 1));
   S.sb.totals = w.take<uint32_t>(SORT_RADIX);
@@ -1019,8 +1516,11 @@ extern "C" ccld_status ccld_locate_hang_static(ccld_ctx* c, const ccld_snapshots
   S.sort_cap = nm;
   S.stage = sn->on_device ? nullptr : w.take<uint8_t>(n_rows * 32);
   S.stage_bytes = sn->on_device ? 0 : n_rows * 32;
-  S.fill_kernels = true;
   if (w.off > CCLD_STATIC_SCRATCH_BYTES) return o->status = CCLD_E_CAPACITY;
+  // the grid's cells take the regrouped rows, what is left of the array the final states
+  const uint64_t final_bytes = nm * sn->n_channels * 16;
+  S.split_row = w.off + final_bytes <= CCLD_STATIC_SCRATCH_BYTES ? reinterpret_cast<ulonglong2*>(S.cell) : nullptr;
+  S.split_final = reinterpret_cast<ulonglong2*>(base + w.off);
   return locate_hang_on(c, S, sn, n_rows, n_cell, o);
 }
 
@@ -1035,36 +1535,58 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
   if (n_cell > c->snap_cap || n_rows > c->snap_cap) return o->status = CCLD_E_CAPACITY;
   hipStream_t st = c->stream;
   HangArgs a;
+  const HangScratch S = scratch_of_context(c, sn->on_device);
   const uint32_t nm = (uint32_t)c->n_members;
-  for (bool exact = n_rows != n_cell;; exact = true) {       // see ccld_locate_hang
-    HIP_TRY(place_snapshots(c, scratch_of_context(c), sn, n_rows, n_cell, a, exact));
-    if (nm) hipLaunchKernelGGL(k_rate_pairs, dim3((nm + 3) / 4), dim3(256), 0, st, a);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (exact || c->h_pinned[CNT_STATUS] != (uint64_t)DS_SUSPECT) break;
+  auto tables = [&](bool checked) {
+    a.checked = checked ? 1 : 0;
+    a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
+    a.ticket = ++c->ticket;
+    hipLaunchKernelGGL(k_rate_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a, c->rate_root);
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(CCLD_WAVE), 0, st, (const u64*)a.counters, a.host, a.ticket);
     c->prof.end(CCLD_PROF_HANG);
+  };
+  HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));
+  bool split = split_regions(a, S, rate_region_lds, RATE_LDS);
+  if (split) {
+    c->prof.begin(CCLD_PROF_HANG_PLACE);
+    launch_split(st, a);
+    c->prof.split(CCLD_PROF_HANG_PLACE, CCLD_PROF_HANG);
+    const size_t lds = rate_region_lds(a.n_ch, a.n_snap, a.sb);
+    if (((uint64_t)a.n_ch * a.n_snap << a.sb) >= 2048) {
+      if (lds > 65536) HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rate_region<1024>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)RATE_LDS));
+      hipLaunchKernelGGL(k_rate_region<1024>, dim3(a.n_regions), dim3(1024), lds, st, a);
+    } else {
+      hipLaunchKernelGGL(k_rate_region<256>, dim3(a.n_regions), dim3(256), lds, st, a);
+    }
+    tables(false);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
+    const uint64_t bits = snapshot_status(c, n_rows, n_cell);
+    split = !(bits & DS_SUSPECT);
+    if (split && bits) { c->prof.collect(); return o->status = hang_status(bits); }
   }
-  if (c->h_pinned[CNT_STATUS]) { c->prof.end(CCLD_PROF_HANG); c->prof.collect(); return o->status = hang_status(c->h_pinned[CNT_STATUS]); }
-  if (c->topo.n_comms) hipLaunchKernelGGL(k_rate_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a, c->rate_root);
+  if (!split) {
+    // One row per cell is the normal case: the rows are placed without the presence bitmap (its atomics are a
+    // third of the placement's time) and the per-member pass looks for cells that nobody wrote.  If it finds one
+    // and no row was refused for a worse reason, or if the row count already rules the normal case out, the
+    // placement is repeated with the bitmap, which tells duplicates from gaps.
+    for (bool exact = n_rows != n_cell;; exact = true) {
+      HIP_TRY(place_snapshots(c, S, sn, n_rows, n_cell, a, exact));
+      if (nm) hipLaunchKernelGGL(k_rate_pairs, dim3((nm + 3) / 4), dim3(256), 0, st, a);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));
+      if (exact || c->h_pinned[CNT_STATUS] != (uint64_t)DS_SUSPECT) break;
+      c->prof.end(CCLD_PROF_HANG);
+    }
+    if (c->h_pinned[CNT_STATUS]) { c->prof.end(CCLD_PROF_HANG); c->prof.collect(); return o->status = hang_status(c->h_pinned[CNT_STATUS]); }
+    tables(true);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
+  }
+  c->prof.collect();
   o->n_pair = c->n_members;
   o->n_comm = c->topo.n_comms;
-  if (o->pair && o->pair_cap) {
-    const uint64_t rows = std::min<uint64_t>(o->pair_cap, c->n_members);
-    if (rows)
-      hipLaunchKernelGGL(k_copy_table, dim3((uint32_t)((rows * CCLD_RATE_NCOL + 255) / 256)), dim3(256), 0, st,
-                         (const i64*)c->h_pair, c->n_members, o->pair, o->pair_cap, rows, (int)CCLD_RATE_NCOL);
-  }
-  if (o->comm && o->comm_cap) {
-    const uint64_t rows = std::min<uint64_t>(o->comm_cap, c->topo.n_comms);
-    if (rows)
-      hipLaunchKernelGGL(k_copy_table, dim3((uint32_t)((rows * CCLD_RCOMM_NCOL + 255) / 256)), dim3(256), 0, st,
-                         (const i64*)c->h_comm, (uint64_t)c->topo.n_comms, o->comm, o->comm_cap, rows, (int)CCLD_RCOMM_NCOL);
-  }
-  c->prof.end(CCLD_PROF_HANG);
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
-  c->prof.collect();
   if (o->pair_cap < o->n_pair && o->pair) o->status = CCLD_W_TRUNCATED;
   if (o->comm_cap < o->n_comm && o->comm) o->status = CCLD_W_TRUNCATED;
   return o->status;

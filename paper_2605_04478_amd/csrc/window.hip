@@ -5,6 +5,7 @@
 #include "window_kernels.h"
 #include "device_utils.h"
 #include "grid.h"
+#include "report.h"
 #include "rows.h"
 #include "select.h"
 
@@ -789,19 +790,6 @@ __device__ __forceinline__ u32 blamed_before(const i64* __restrict__ blame, u32 
   }
   return wave_sum(before);
 }
-// An analysis ends here: the last workgroup to get here writes the counters to pinned host memory, each with the ticket
-// in its upper 16 bits.  The host waits until every word carries the ticket, so the words need no order among
-// themselves, and no cache is written back on the way (what the kernel wrote for later kernels is, at its end).
-__device__ __forceinline__ void report_counters(u64* counters, u64* host, u64 ticket) {
-  __shared__ u32 s_last;
-  if (!last_block(reinterpret_cast<u32*>(&counters[CNT_DONE]), gridDim.x, &s_last)) return;
-  if (threadIdx.x < CNT_COUNT) {
-    const u64 v = __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&host[threadIdx.x], (v & REPORT_MASK) | (ticket << REPORT_BITS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-}
-static_assert(CNT_COUNT <= 64, "one wavefront copies the counters");
-
 // Up to ORDER_ONE_RANKS ranks in one launch: every workgroup lists the flagged ranks in LDS for itself (a scan over
 // two columns of the blame table), ranks its share of them and writes its share of the others.
 constexpr u32 ORDER_ONE_RANKS = 16384, ORDER_THREADS = 1024, ORDER_TILE = 4 * ORDER_THREADS;

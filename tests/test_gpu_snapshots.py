@@ -1,0 +1,76 @@
+"""GPU parity of hang location and progress rates where the regrouping of the rows can go wrong: few and many regions,
+members at a region's edge, series of 2 to 200 snapshots, counters that do not fit a regrouped row, duplicates and gaps,
+rings whose hops are found in LDS or by walking, and more roots than one workgroup sorts."""
+import numpy as np
+import pytest
+
+from paper_2605_04478_amd import tracegen as tg
+from tests import test_gpu_hang, test_gpu_rates
+from tests.helpers import ring_topology
+
+pytestmark = pytest.mark.gpu
+
+
+def _cols(topo, seq, sent, recv, rng):
+    """[members, channels, snapshots] states -> shuffled rows"""
+    m, ch, sn = np.meshgrid(*(np.arange(k) for k in seq.shape), indexing="ij")
+    comm = np.repeat(np.arange(topo.n_comms), topo.size)
+    p = rng.permutation(m.size)
+    flat = lambda a, dt: np.ascontiguousarray(np.broadcast_to(a, seq.shape).reshape(-1)[p].astype(dt))
+    return {"snap": flat(sn, np.uint32), "rank": flat(topo.members[m], np.uint32), "comm": flat(comm[m], np.uint32),
+            "channel": flat(ch, np.uint32), "seq_posted": flat(seq, np.uint64), "chunks_sent": flat(sent, np.uint32),
+            "chunks_recv": flat(recv, np.uint32)}
+
+
+def _random(topo, n_snap, n_ch, rng, seq0):
+    shape = (int(topo.size.sum()), n_ch, n_snap)
+    moves = rng.random(shape) < 0.3
+    moves[rng.random(shape[0]) < 0.5, :, n_snap // 2:] = False             # half of the members stop
+    seq = seq0 + np.cumsum(moves & (rng.random(shape) < 0.5), axis=2)
+    cnt = np.cumsum(moves, axis=2) * 8 % 4096
+    return _cols(topo, seq, cnt, cnt + (np.arange(shape[0]) % 3)[:, None, None], rng)
+
+
+def _both(topo, cols, n_snap, n_ch, what, **params):
+    test_gpu_hang.run_both(topo, cols, n_snap, n_ch, what=what, stall_snapshots=min(3, n_snap - 1), **params)
+    test_gpu_rates.run_both(topo, cols, n_snap, n_ch, what=what)
+
+
+@pytest.mark.parametrize("seq0", [0, 2**46 - 20, 2**62], ids=["small", "edge", "wide"])
+@pytest.mark.parametrize("n,n_snap,n_ch", [(1, 2, 1), (63, 5, 3), (255, 64, 1), (256, 65, 2), (257, 33, 5), (513, 200, 1),
+                                           (700, 130, 4), (1500, 7, 16)])
+def test_sizes_and_wide_counters(n, n_snap, n_ch, seq0):
+    rng = np.random.default_rng(n + n_snap)
+    topo = ring_topology(n, comms=[list(range(n)), list(range(n // 2 + 1))[::-1]])
+    _both(topo, _random(topo, n_snap, n_ch, rng, seq0), n_snap, n_ch, (n, n_snap, n_ch, seq0))
+
+
+@pytest.mark.parametrize("n,n_snap", [(40, 6), (600, 70)])
+def test_duplicates_gaps_and_extra_rows(n, n_snap):
+    rng = np.random.default_rng(n)
+    topo = ring_topology(n)
+    cols = _random(topo, n_snap, 2, rng, 100)
+    gap = {k: v[:-1] for k, v in cols.items()}
+    extra = {k: np.concatenate([v, v[:3]]) for k, v in cols.items()}
+    same = {k: np.concatenate([v[:-400], np.repeat(v[:1], 400)]) for k, v in cols.items()}
+    for what, c in (("gap", gap), ("extra", extra), ("same", same)):
+        _both(topo, c, n_snap, 2, what)
+
+
+@pytest.mark.parametrize("n", [64, 255, 257, 4096, 4097])
+def test_hops_along_rings(n):
+    topo, rng = ring_topology(n), np.random.default_rng(n)
+    S, R = tg.ring_steady_state(n, n // 3, np.array([5, 9]), 1 << 20, 8)
+    st = lambda a: np.repeat(np.asarray(a).astype(np.int64)[:, :, None], 4, axis=2)
+    g, o = test_gpu_hang.run_both(topo, _cols(topo, np.full((n, 2, 4), 9), st(S), st(R), rng), 4, 2, what=n, stall_snapshots=2)
+    assert g.n_root == 1 and int(o.pair["hops"].max()) > n // 4
+
+
+@pytest.mark.parametrize("n_late", [1024, 1025])
+def test_many_roots(n_late):
+    n, rng = 2500, np.random.default_rng(n_late)
+    topo = ring_topology(n)
+    seq = np.full((n, 1, 5), 8)
+    seq[rng.permutation(n)[:n_late]] = 7
+    g, _ = test_gpu_hang.run_both(topo, _cols(topo, seq, np.full(seq.shape, 3), np.full(seq.shape, 3), rng), 5, 1, what=n_late, stall_snapshots=2)
+    assert g.n_root == n_late
