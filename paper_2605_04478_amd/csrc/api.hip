@@ -143,7 +143,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->h_cand = w.take<uint8_t>(n_members);
   c->h_layer_max = w.take<uint64_t>(n_members);
   c->f_last = w.take<uint64_t>(2ull * CCLD_FRAME_CHANNELS * n_members);
-  c->f_seen = w.take<uint32_t>(n_ranks / 32 + 1);
+  c->f_frame = w.take<uint64_t>((uint64_t)n_ranks + 1);
   c->h_stage = w.take<uint8_t>(SN * 32);
 }
 
@@ -388,6 +388,8 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (hipMemsetAsync(c->ing_done, 0, sizeof(uint32_t), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
+  c->f_status = c->f_frame + topo->n_ranks;
+  if (hipMemsetAsync(c->f_frame, 0, 8ull * ((uint64_t)topo->n_ranks + 1), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->f_last, 0, sizeof(uint64_t) * 2 * CCLD_FRAME_CHANNELS * n_members, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)topo->n_ranks, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   {     // pinned words: the counters, the ticket and the fine buckets of a layout, then the headers of every batch slot
@@ -489,16 +491,16 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
 // thing on the stream, so the stream has drained then; spinning on the word costs about 10 us less than copying the
 // counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
 // hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
-static bool reported(const ccld_ctx* c) {
-  for (int i = 0; i < CNT_COUNT; ++i)
+static bool reported(const ccld_ctx* c, int words) {
+  for (int i = 0; i < words; ++i)
     if ((__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED) >> REPORT_BITS) != (c->ticket & 0xFFFF)) return false;
   return true;
 }
-extern "C++" hipError_t wait_report(ccld_ctx* c) {
+extern "C++" hipError_t wait_report(ccld_ctx* c, int words) {
   bool there = false;
   if (!c->prof.on) {
     const auto t0 = std::chrono::steady_clock::now();
-    for (uint32_t i = 1; !(there = reported(c)); ++i) {
+    for (uint32_t i = 1; !(there = reported(c, words)); ++i) {
       if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) break;
       __builtin_ia32_pause();
     }
@@ -506,9 +508,9 @@ extern "C++" hipError_t wait_report(ccld_ctx* c) {
   if (!there) {
     const hipError_t e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return e;
-    if (!reported(c)) return hipErrorUnknown;
+    if (!reported(c, words)) return hipErrorUnknown;
   }
-  for (int i = 0; i < CNT_COUNT; ++i) c->h_pinned[i] &= REPORT_MASK;
+  for (int i = 0; i < words; ++i) c->h_pinned[i] &= REPORT_MASK;
   return hipSuccess;
 }
 
@@ -583,8 +585,9 @@ static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_resu
     launch_alert_select(st, aa);
     launch_alert_candidates(st, aa, (uint32_t)o->n_alert);
     c->prof.end(CCLD_PROF_ALERTS);
-    HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    launch_report(st, c->counters, c->h_pinned, ++c->ticket);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
     o->n_cand = c->h_pinned[CNT_NCAND];
     if (o->n_alert > o->alert_cap || o->n_cand > o->cand_cap) o->status = CCLD_W_TRUNCATED;
   }
@@ -788,8 +791,9 @@ ccld_status ccld_rank_blame(ccld_ctx* c, int64_t* blame, uint32_t* order) {
   if (!c->blame_valid) return CCLD_E_BAD_ARG;
   const uint32_t n_ranks = c->topo.n_ranks;
   launch_blame_out(c->stream, c->blame, c->blame_order, n_ranks, blame, order);
+  launch_report(c->stream, c->counters, c->h_pinned, ++c->ticket);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  HIP_TRY(wait_report(c));
   return CCLD_OK;
 }
 

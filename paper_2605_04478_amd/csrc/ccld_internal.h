@@ -166,7 +166,9 @@ struct ccld_ctx {
   uint64_t* h_layer_max;              // [n_members]
   int64_t* rate_root;                 // [n_comms] member of minimal SendRate / RecvRate from the latest rate pass, or CCLD_NO_RANK
   uint64_t* f_last;                   // [n_members][CCLD_FRAME_CHANNELS][2] remembered (operation counter, sent | recv << 32) per member and channel
-  uint32_t* f_seen;                   // [n_ranks / 32 + 1] ranks that delivered a frame in the current call
+  uint64_t* f_frame;                  // [n_ranks] call << 32 | frame that the rank delivered in it
+  uint64_t* f_status;                 // call << 8 | error of it
+  uint32_t f_call;                    // calls so far
   uint8_t* h_stage;                   // [snap_cap * 32] device staging for host-resident snapshots
   // grid placement (grid.h)
   bool grid_capable;                  // communicators fit a fine bucket, few enough of them, few enough batches
@@ -201,5 +203,5 @@ struct ccld_ctx {
 
 // looks up the device address of the library's static scratch array on the current device (hang.hip)
 ccld_status ccld_static_scratch_init();
-// waits for the report of the current ticket (api.hip); the counters are then in h_pinned
-hipError_t wait_report(ccld_ctx* c);
+// waits for the report of the current ticket (api.hip): its words are then in h_pinned
+hipError_t wait_report(ccld_ctx* c, int words = ccld::CNT_COUNT);

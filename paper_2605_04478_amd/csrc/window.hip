@@ -874,6 +874,12 @@ void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, 
                      host_counters, ticket);
 }
 
+// The end of a pass whose last kernel does not report: every launch before it is over.
+__global__ __launch_bounds__(CCLD_WAVE) void k_report(const u64* counters, u64* host, u64 ticket) { report_words(counters, host, ticket); }
+void launch_report(hipStream_t st, const uint64_t* counters, uint64_t* host, uint64_t ticket) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(CCLD_WAVE), 0, st, counters, host, ticket);
+}
+
 // the blame table and its order handed to the caller: one launch for both
 __global__ __launch_bounds__(256) void k_blame_out(const i64* __restrict__ blame, const u32* __restrict__ order_in,
                                                    u32 n_ranks, i64* __restrict__ table_out, u32* __restrict__ order_out) {

@@ -118,6 +118,7 @@ struct GroupArgs {
   uint64_t group_cap;
   ccld_params p;
 };
+void launch_report(hipStream_t st, const uint64_t* counters, uint64_t* host, uint64_t ticket);
 void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* order_in, uint32_t n_ranks, int64_t* table_out,
                       uint32_t* order_out);
 void launch_groups(hipStream_t st, const GroupArgs& a);        // groups.hip
