@@ -260,6 +260,7 @@ class Analyzer:
         self.max_snapshot_rows = int(max_snapshot_rows)
         self._algo = np.ascontiguousarray(topo.algo, dtype=np.uint8)
         self._size = np.ascontiguousarray(topo.size, dtype=np.uint32)
+        self._n_members = int(self._size.sum())
         self._off = np.ascontiguousarray(topo.member_off, dtype=np.uint32)
         self._members = np.ascontiguousarray(topo.members, dtype=np.uint32)
         self._tp = None if topo.tree_parent is None else np.ascontiguousarray(topo.tree_parent, dtype=np.int32)
@@ -372,15 +373,16 @@ class Analyzer:
         {root_entries, secondary_entries, caused} per rank)."""
         t = self.torch
         cap = max(int(result.n_flag), 1)
-        chain = t.empty(len(CHAIN_COLS) * cap, dtype=t.int64, device=self.device)
-        per_rank = t.empty(len(CHAIN_RANK_COLS) * self.n_ranks, dtype=t.int64, device=self.device)
-        o = _ChainResult(cap, chain.data_ptr(), per_rank.data_ptr())
+        n_chain, n_rank = len(CHAIN_COLS) * cap, len(CHAIN_RANK_COLS) * self.n_ranks
+        out = t.empty(n_chain + n_rank, dtype=t.int64, device=self.device)      # both tables: one copy to the host
+        o = _ChainResult(cap, out.data_ptr(), out.data_ptr() + 8 * n_chain)
         st = self.L.ccld_flag_chains(self._ctx, C.addressof(result.raw), C.addressof(o))
         if st not in (0, 1):
             raise CcldError(st, "ccld_flag_chains")
-        n = int(o.n_chain)
-        return (STATUS.get(st, str(st)), _table(chain, CHAIN_COLS, cap, n),
-                _table(per_rank, CHAIN_RANK_COLS, self.n_ranks, self.n_ranks))
+        n, host = min(int(o.n_chain), cap), out.cpu().numpy()
+        chain, per_rank = host[:n_chain].reshape(-1, cap)[:, :n], host[n_chain:].reshape(-1, self.n_ranks)
+        return (STATUS.get(st, str(st)), {nm: np.ascontiguousarray(chain[i]) for i, nm in enumerate(CHAIN_COLS)},
+                {nm: np.ascontiguousarray(per_rank[i]) for i, nm in enumerate(CHAIN_RANK_COLS)})
 
     def rank_blame(self, to_host: bool = True, buffers=None):
         """-> (blame columns, order).  to_host=False leaves both on the device (column-major int64 table
@@ -443,7 +445,7 @@ class Analyzer:
         if buffers is not None:
             caps, dev = buffers
         else:
-            caps = {"root": int(root_cap), "pair": int(pair_cap or int(self._size.sum())),
+            caps = {"root": int(root_cap), "pair": int(pair_cap or self._n_members),
                     "comm": int(comm_cap or self.n_comms)}
             i64 = dict(dtype=t.int64, device=self.device)
             dev = {"root": t.empty(len(HANG_ROOT_COLS) * caps["root"], **i64),
@@ -475,7 +477,7 @@ class Analyzer:
             n = int(fr.shape[0])
             fptr, rptr = buf.ctypes.data_as(C.c_void_p), fr.ctypes.data_as(C.c_void_p)
             keep = (buf, fr)
-        cap = int(self._size.sum()) * int(n_channels)
+        cap = self._n_members * int(n_channels)
         i32 = dict(dtype=t.int32, device=self.device)
         out = {k: t.empty(cap, **i32) for k in ("snap", "rank", "comm", "channel", "chunks_sent", "chunks_recv")}
         out["seq_posted"] = t.empty(cap, dtype=t.int64, device=self.device)
@@ -506,7 +508,7 @@ class Analyzer:
         sn = _Snapshots(ptr("snap"), ptr("rank"), ptr("comm"), ptr("channel"), ptr("seq_posted"),
                         ptr("chunks_sent"), ptr("chunks_recv"), 1 if on_device else 0, int(n_snapshots),
                         int(n_channels))
-        caps = {"pair": int(pair_cap or int(self._size.sum())), "comm": int(comm_cap or self.n_comms)}
+        caps = {"pair": int(pair_cap or self._n_members), "comm": int(comm_cap or self.n_comms)}
         i64 = dict(dtype=t.int64, device=self.device)
         dev = {"pair": t.empty(len(RATE_PAIR_COLS) * caps["pair"], **i64),
                "comm": t.empty(len(RATE_COMM_COLS) * caps["comm"], **i64)}

@@ -10,6 +10,7 @@
 #include "ccld_internal.h"
 #include "grid.h"
 #include "rows.h"
+#include "window_kernels.h"
 
 using namespace ccld;
 
@@ -34,8 +35,10 @@ struct ChainArgs {
   u64 cap_n;
   const u32* flag_pos;       // sorted position of the k-th flag; on the grid placement where its lags are
   u32 n_flag;
-  u32* comm_first;           // [n_comms + 1] first table row of each communicator
+  u32* comm_first;           // [n_comms + 1] first table row of each communicator (sorted window; the grid's layout has it)
   u32* parent;               // [n_flag] parent flag or ~0
+  u64* link;                 // [n_flag] an ancestor, links up to it << 32; a root leads to itself
+  i64* per_rank;             // cleared by the parent kernel, or null
 };
 
 // first row of the collective table of every communicator (the table is ordered by communicator)
@@ -92,11 +95,19 @@ __device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
   return f;
 }
 
-// One thread per flag: the parent of a late entry.
+// The parent of a late entry: PARENT_LANES lanes per flag.  What takes the time is chains of dependent loads (the binary
+// search over a communicator's rounds makes two per step), so the lanes of a flag search its rank's communicators
+// side by side, and the flag list in PARENT_LANES + 1 parts at a time (8,000 flags: 42 us with a thread per flag).
+constexpr u32 PARENT_LANES = 4;
+struct ChainBefore { i64 exit, enter; u32 comm, row; bool have; };
 template <bool GRID>
 __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= a.n_flag) return;
+  const u32 t256 = blockIdx.x * 256 + threadIdx.x;
+  if (a.per_rank)
+    for (u64 i = t256; i < (u64)CCLD_CHR_NCOL * a.T.n_ranks; i += (u64)gridDim.x * 256) a.per_rank[i] = 0;
+  const u32 k = t256 / PARENT_LANES, l = t256 % PARENT_LANES;
+  const u32 group0 = lane_id() & ~(PARENT_LANES - 1);
+  if (k >= a.n_flag) return;                     // whole groups
   const ChainFlag F = chain_flag<GRID>(a, k);
   u32 parent = ~0u;
   if (F.kind & CCLD_FLAG_LATE_ENTER) {
@@ -107,15 +118,16 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
     else t = load_rec(a.win, a.idx[own]).t_enter;
     // the operation this rank ran just before: per communicator of the rank the last round that the rank left
     // before t (its rounds are in time order; a round without a record of the rank is skipped), then the latest
-    bool have = false;
-    i64 b_exit = 0, b_enter = 0;
-    u32 b_comm = 0, b_row = 0;
-    for (u32 q = a.T.rank_comm_off[r]; q < a.T.rank_comm_off[r + 1]; ++q) {
+    ChainBefore B{0, 0, 0, 0, false};
+    const auto take = [&](const ChainBefore& f) {
+      if (f.have && (!B.have || f.exit > B.exit || (f.exit == B.exit && (f.enter > B.enter || (f.enter == B.enter && f.comm > B.comm))))) B = f;
+    };
+    for (u32 q = a.T.rank_comm_off[r] + l; q < a.T.rank_comm_off[r + 1]; q += PARENT_LANES) {
       const u32 c2 = a.T.rank_comms[q], slot2 = a.T.rank_slots[q], size2 = a.T.size[c2];
-      u32 lo = a.comm_first[c2], hi = a.comm_first[c2 + 1];
-      bool found = false;
-      u32 f_row = 0;
-      i64 f_exit = 0, f_enter = 0;
+      u32 lo, hi;
+      if (GRID) { lo = a.grid.lay[c2].seg_base; hi = lo + a.grid.lay[c2].rounds; }
+      else { lo = a.comm_first[c2]; hi = a.comm_first[c2 + 1]; }
+      ChainBefore f{0, 0, c2, 0, false};
       while (lo < hi) {
         const u32 mid = (lo + hi) >> 1;
         // the nearest round at or below mid in which the rank has a record
@@ -128,29 +140,44 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
           --probe;
         }
         const bool ok = here && pos != own && tx != T_INFLIGHT && tx <= t;
-        if (ok) { found = true; f_row = probe; f_exit = tx; f_enter = te; lo = mid + 1; }
+        if (ok) { f.have = true; f.row = probe; f.exit = tx; f.enter = te; lo = mid + 1; }
         else if (!here) lo = mid + 1;            // no record of the rank in [lo, mid]
         else hi = probe;
       }
-      if (!found) continue;
-      const bool better = !have || f_exit > b_exit || (f_exit == b_exit && (f_enter > b_enter || (f_enter == b_enter && c2 > b_comm)));
-      if (better) { have = true; b_exit = f_exit; b_enter = f_enter; b_comm = c2; b_row = f_row; }
+      take(f);
     }
-    if (have) {
+#pragma unroll
+    for (u32 m = 1; m < PARENT_LANES; m <<= 1) {
+      const ChainBefore o{(i64)shfl_xor_u64((u64)B.exit, m), (i64)shfl_xor_u64((u64)B.enter, m), __shfl_xor(B.comm, m, CCLD_WAVE),
+                          __shfl_xor(B.row, m, CCLD_WAVE), __shfl_xor((int)B.have, m, CCLD_WAVE) != 0};
+      take(o);
+    }
+    if (B.have) {
       // who ended it late: the late entry with the largest lag (ties: smallest rank = first in rank order)
       bool any = false;
       i64 m_lag = 0;
       if (GRID) {
-        u32 lo = 0, hi = a.n_flag;               // the collective's first flag
-        while (lo < hi) { const u32 m = (lo + hi) >> 1; if ((u32)(a.flag_key[m] >> 32) < b_row) lo = m + 1; else hi = m; }
-        for (; lo < a.n_flag && (u32)(a.flag_key[lo] >> 32) == b_row; ++lo) {
+        u32 lo = 0, hi = a.n_flag;               // the collective's first flag: every lane of the group looks at one point
+        while (lo < hi) {
+          const u32 step = (hi - lo) / (PARENT_LANES + 1), m = lo + (l + 1) * step;
+          const bool less = step ? (u32)(a.flag_key[m] >> 32) < B.row : (lo + l < hi && (u32)(a.flag_key[lo + l] >> 32) < B.row);
+          const u32 n_less = (u32)__popcll((ballot64(less) >> group0) & ((1u << PARENT_LANES) - 1));
+          if (step) {
+            if (n_less < PARENT_LANES) hi = lo + (n_less + 1) * step;
+            if (n_less) lo = lo + n_less * step + 1;
+          } else {
+            lo += n_less;
+            if (n_less < PARENT_LANES) hi = lo;
+          }
+        }
+        for (; lo < a.n_flag && (u32)(a.flag_key[lo] >> 32) == B.row; ++lo) {
           const u32 at = a.flag_pos[lo];
           if (!((a.flag_stage[at] >> 16) & CCLD_FLAG_LATE_ENTER)) continue;
           const i64 lag = a.flag_lag[at];
           if (!any || lag > m_lag) { any = true; parent = lo; m_lag = lag; }
         }
       } else {
-        const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + b_row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + b_row];
+        const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + B.row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + B.row];
         u32 m_pos = 0;
         for (u32 p = first; p < first + n; ++p)
           if (a.rec_flag[p] & CCLD_FLAG_LATE_ENTER) {
@@ -165,24 +192,12 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
       }
     }
   }
-  a.parent[k] = parent;
+  if (l == 0) {
+    a.parent[k] = parent;
+    a.link[k] = parent == ~0u ? (u64)k : (u64)parent | (u64)1 << 32;
+  }
 }
 
-// pointer jumping: anc = current ancestor (a root points to itself), dist = links between the flag and it
-__global__ __launch_bounds__(256) void k_chain_init(const u32* parent, u32 n_flag, u32* anc, u32* dist) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_flag) return;
-  const u32 p = parent[k];
-  anc[k] = p == ~0u ? k : p;
-  dist[k] = p == ~0u ? 0u : 1u;
-}
-__global__ __launch_bounds__(256) void k_chain_jump(const u32* anc_in, const u32* dist_in, u32 n_flag, u32* anc_out, u32* dist_out) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_flag) return;
-  const u32 a1 = anc_in[k], a2 = anc_in[a1];
-  anc_out[k] = a2;
-  dist_out[k] = dist_in[k] + (a2 != a1 ? dist_in[a1] : 0u);
-}
 // column[idx] += 1 for every lane with `on`, one atomic per distinct idx in the wavefront: a faulty rank's thousands
 // of entries would otherwise queue up at one address.  Called by every active lane of the wavefront.
 __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool on) {
@@ -195,22 +210,36 @@ __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool o
     todo &= ~same;
   }
 }
+// Every flag follows its links to the root and keeps what it finds, in place: a link always leads to some ancestor, so
+// whatever the others have written by then is right, nobody waits for anybody, and the links double in length as all
+// flags go on at once (one launch in place of a jump per doubling: 14 for 8,000 flags).  Each step takes the link past the
+// caches that the XCDs do not share.
 template <bool GRID>
-__global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, const u32* anc, const u32* dist, i64* chain, u64 chain_cap,
-                                                    i64* per_rank) {
+__global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64 chain_cap) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
   if (k >= a.n_flag) return;
   auto rank_at = [&](u32 flag) -> u32 {
     const ChainFlag f = chain_flag<GRID>(a, flag);
     return a.T.members_sorted[a.T.member_off[f.comm] + f.slot];
   };
-  const u32 root = anc[k], p = a.parent[k];
+  u64 v = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[k]));
+  // Parents end earlier, so there are no cycles; records that contradict their own clocks could make one, and the bound
+  // on the links ends the walk there.
+  while ((v >> 32) <= a.n_flag) {
+    const u32 up = (u32)v;
+    const u64 w = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[up]));
+    if ((u32)w == up) break;                     // up is a root
+    v = (u64)(u32)w | ((v >> 32) + (w >> 32)) << 32;
+    store_agent(reinterpret_cast<i64*>(&a.link[k]), (i64)v);
+  }
+  const u32 root = (u32)v, p = a.parent[k];
+  i64* per_rank = a.per_rank;
   const u32 root_rank = rank_at(root);
   if (k < chain_cap) {
     chain[(u64)CCLD_CHN_PARENT * chain_cap + k] = p == ~0u ? -1 : (i64)p;
     chain[(u64)CCLD_CHN_ROOT * chain_cap + k] = (i64)root;
     chain[(u64)CCLD_CHN_ROOT_RANK * chain_cap + k] = (i64)root_rank;
-    chain[(u64)CCLD_CHN_DEPTH * chain_cap + k] = (i64)dist[k];
+    chain[(u64)CCLD_CHN_DEPTH * chain_cap + k] = (i64)(v >> 32);
   }
   if (per_rank) {
     const bool on = (chain_flag<GRID>(a, k).kind & CCLD_FLAG_LATE_ENTER) != 0;
@@ -239,7 +268,7 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
   hipStream_t st = c->stream;
   const uint32_t n_flag = (uint32_t)c->last_n_flag, n_ranks = c->topo.n_ranks;
   o->n_chain = n_flag;
-  if (o->per_rank) HIP_TRY(hipMemsetAsync(o->per_rank, 0, sizeof(int64_t) * CCLD_CHR_NCOL * (uint64_t)n_ranks, st));
+  if (o->per_rank && !n_flag) HIP_TRY(hipMemsetAsync(o->per_rank, 0, sizeof(int64_t) * CCLD_CHR_NCOL * (uint64_t)n_ranks, st));
   if (n_flag) {
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -251,29 +280,21 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
     a.seg = w->seg; a.seg_cap = w->seg_cap; a.n_seg = (uint32_t)w->n_seg;
     a.rec_flag = c->last_rec_flag; a.flag_lag = c->flag_lag; a.cap_n = c->cap; a.flag_pos = c->flag_pos; a.n_flag = n_flag;
     a.comm_first = c->chain_first; a.parent = c->chain_parent;
-    // scratch that the analysis no longer needs
-    uint32_t* anc[2] = {c->alert_list, c->alert_ncand};
-    uint32_t* dist[2] = {reinterpret_cast<uint32_t*>(c->range_c), reinterpret_cast<uint32_t*>(c->range_c) + n_flag};
-    const uint32_t blocks = (n_flag + 255) / 256;
-    hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
-    if (grid) hipLaunchKernelGGL(k_chain_parent<true>, dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(k_chain_parent<false>, dim3(blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_chain_init, dim3(blocks), dim3(256), 0, st, (const u32*)a.parent, n_flag, anc[0], dist[0]);
-    int cur = 0;
-    for (uint64_t reach = 1; reach < n_flag; reach *= 2) {        // after i rounds every flag has looked 2^i links up
-      hipLaunchKernelGGL(k_chain_jump, dim3(blocks), dim3(256), 0, st, (const u32*)anc[cur], (const u32*)dist[cur], n_flag,
-                         anc[1 - cur], dist[1 - cur]);
-      cur = 1 - cur;
+    a.link = reinterpret_cast<uint64_t*>(c->range_c);                // scratch that the analysis no longer needs
+    a.per_rank = o->per_rank;
+    const dim3 blocks((n_flag + 255) / 256), parents((uint32_t)(((uint64_t)n_flag * PARENT_LANES + 255) / 256));
+    if (grid) {
+      hipLaunchKernelGGL(k_chain_parent<true>, parents, dim3(256), 0, st, a);
+      hipLaunchKernelGGL(k_chain_emit<true>, blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+    } else {
+      hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
+      hipLaunchKernelGGL(k_chain_parent<false>, parents, dim3(256), 0, st, a);
+      hipLaunchKernelGGL(k_chain_emit<false>, blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
     }
-    if (grid)
-      hipLaunchKernelGGL(k_chain_emit<true>, dim3(blocks), dim3(256), 0, st, a, (const u32*)anc[cur], (const u32*)dist[cur], o->chain,
-                         o->chain_cap, o->per_rank);
-    else
-      hipLaunchKernelGGL(k_chain_emit<false>, dim3(blocks), dim3(256), 0, st, a, (const u32*)anc[cur], (const u32*)dist[cur], o->chain,
-                         o->chain_cap, o->per_rank);
   }
+  launch_report(st, c->counters, c->h_pinned, ++c->ticket);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
+  HIP_TRY(wait_report(c));
   if (o->n_chain > o->chain_cap) o->status = CCLD_W_TRUNCATED;
   return o->status;
 }
