@@ -38,15 +38,18 @@ __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int m) {
   return ((u64)hi << 32) | lo;
 }
 
-// inclusive prefix sum over the wavefront
+// inclusive prefix sum over the wavefront: inside rows of 16 lanes by DPP shifts, which read zero past the row's start, then
+// the sum of the row before goes to every second row and that of the lower half to the upper one.  Six instructions with
+// an add each; shuffles through the LDS crossbar took six dependent trips of it.
 __device__ __forceinline__ u32 wave_inclusive_sum(u32 v) {
-  u32 lane = lane_id();
-#pragma unroll
-  for (int off = 1; off < CCLD_WAVE; off <<= 1) {
-    u32 y = __shfl_up(v, off, CCLD_WAVE);
-    if (lane >= (u32)off) v += y;
-  }
-  return v;
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);       // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);       // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);       // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);       // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);      // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);      // row_bcast:31 into rows 2 and 3
+  return (u32)x;
 }
 __device__ __forceinline__ u32 wave_sum(u32 v) {
 #pragma unroll

@@ -310,15 +310,38 @@ __device__ __forceinline__ void dense_pass64(const SegArgs& a, const DenseLane& 
 // times where they are stored.  A pass in which some offset does not fit takes the 64-bit form.
 constexpr i32 REL_NONE = 0x7FFFFFFF;         // sorts behind every real offset (those stay below 2^30 in magnitude)
 
+//
+// A compare-exchange is one exchange and one median of three: with the smallest or the largest integer as the third value
+// the median is the minimum or the maximum, so each lane's side of an exchange is a word that is set up once per kernel
+// (minimum, maximum and a select were three instructions).  The word is computed and not selected: a value known to be one
+// of two would make the median a select again.  Distances of 16 and 32 lanes are swaps of rows and halves in registers;
+// through the LDS crossbar they were the longest waits of the chain.
+__device__ __forceinline__ i32 med3_i32(i32 x, i32 y, i32 bound) {
+  const i32 lo = x < y ? x : y, hi = x < y ? y : x, c = hi < bound ? hi : bound;
+  return lo < c ? c : lo;
+}
+// The mirrored exchanges beyond a row of 16 lanes meet the same pairs of values as cmpx<31> and cmpx<63>, but leave the
+// larger ones in another order (the exchanges that follow sort either): 31 turns every second row round first, 63
+// expects the complements of the upper half's values in rising order.
 template <int M>
 __device__ __forceinline__ i32 cmpx32(i32 v, u32 lane) {
-  const i32 p = (i32)xor_lane_u32<M>((u32)v);
-  const bool upper = (lane & high_bit(M)) != 0;
-  const i32 lo = p < v ? p : v, hi = p < v ? v : p;
-  return upper ? hi : lo;
+  constexpr int B = M == 31 ? 16 : M == 63 ? 32 : high_bit(M);
+  const i32 bound = 0x7FFFFFFF ^ (i32)(((lane & B) / B) - 1u);        // without the bit its complement, the smallest integer
+  if constexpr (M == 31) v = __builtin_amdgcn_update_dpp(v, v, 0x140, 0xA, 0xF, false);       // rows 1 and 3: row_mirror
+  if constexpr (M == 63) v ^= -(i32)(lane >> 5);
+  if constexpr (B == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap((u32)v, (u32)v, false, false);
+    return med3_i32((i32)r[0], (i32)r[1], bound);
+  } else if constexpr (B == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap((u32)v, (u32)v, false, false);
+    return med3_i32((i32)r[0], (i32)r[1], bound);
+  } else {
+    return med3_i32((i32)xor_lane_u32<M>((u32)v), v, bound);
+  }
 }
 template <int G>
 __device__ __forceinline__ i32 sort_groups32(i32 v, u32 lane) {
+  if constexpr (G >= 64) v ^= -(i32)(lane >> 5);
   if constexpr (G >= 2) { v = cmpx32<1>(v, lane); }
   if constexpr (G >= 4) { v = cmpx32<3>(v, lane); v = cmpx32<1>(v, lane); }
   if constexpr (G >= 8) { v = cmpx32<7>(v, lane); v = cmpx32<2>(v, lane); v = cmpx32<1>(v, lane); }
@@ -345,13 +368,19 @@ __device__ __forceinline__ i32 merge_groups32(i32 v, u32 lane) {
 // all-reduce of an unsigned 32-bit word inside a group
 template <int G, bool MAXIMUM>
 __device__ __forceinline__ u32 reduce_u32(u32 v) {
-#define CCLD_U32_STEP(M)                                                                         \
-  if constexpr (G > M) {                                                                         \
-    const u32 o = xor_lane_u32<M>(v);                                                            \
-    v = MAXIMUM ? (o > v ? o : v) : (o < v ? o : v);                                             \
+  auto take = [](u32 x, u32 y) { return MAXIMUM ? (x > y ? x : y) : (x < y ? x : y); };
+  if constexpr (G > 1) v = take(v, xor_lane_u32<1>(v));
+  if constexpr (G > 2) v = take(v, xor_lane_u32<2>(v));
+  if constexpr (G > 4) v = take(v, xor_lane_u32<7>(v));       // four lanes hold the same word by now: the mirrors
+  if constexpr (G > 8) v = take(v, xor_lane_u32<15>(v));      // reach the other half like the exchanges by 4 and by 8
+  if constexpr (G > 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = take(r[0], r[1]);
   }
-  CCLD_U32_STEP(1) CCLD_U32_STEP(2) CCLD_U32_STEP(4) CCLD_U32_STEP(8) CCLD_U32_STEP(16) CCLD_U32_STEP(32)
-#undef CCLD_U32_STEP
+  if constexpr (G > 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = take(r[0], r[1]);
+  }
   return v;
 }
 // all-reduce of an unsigned 64-bit word inside a group

@@ -82,3 +82,24 @@ def test_the_schedules_checked_here_are_the_kernels():
     assert _kernel_schedule("merge_groups") == MERGE_MASKS
     assert _kernel_schedule("sort_groups32", "i32", "cmpx32") == SORT_MASKS           # the passes on 32-bit offsets
     assert _kernel_schedule("merge_groups32", "i32", "cmpx32") == MERGE_MASKS
+
+
+def turned(v, g):
+    """the 32-bit sort's steps beyond a row of 16 lanes: every second row turned round by its mirror, the upper half by
+    sorting its complements, then halving exchanges only"""
+    low = SORT_MASKS[16]
+    lanes = np.arange(g)
+    v = np.where(lanes & 32, ~v, v) if g == 64 else v
+    v = run(v, low)
+    v = np.where(lanes & 16, v[..., lanes ^ 15], v)
+    v = run(v, [16, 8, 4, 2, 1])
+    return run(np.where(lanes & 32, ~v, v), [32, 16, 8, 4, 2, 1]) if g == 64 else v
+
+
+@pytest.mark.parametrize("g", [32, 64])
+def test_sort_schedule_with_turned_runs(g):
+    rng = np.random.default_rng(g + 1)
+    x = rng.integers(-50, 50, size=(20000, g))
+    z = -(rng.random((20000, g)) < rng.random((20000, 1))).astype(np.int64)       # both values turn into each other
+    for v in (x, z):
+        assert np.array_equal(turned(v, g), np.sort(v, axis=-1))
