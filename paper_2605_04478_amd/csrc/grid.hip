@@ -164,22 +164,26 @@ void launch_grid_layout(hipStream_t st, const GridArgs& d) {
 // (bucket, rank) order and leave with consecutive lanes on consecutive 16-byte pieces.  Pieces of a line that the round
 // writes completely leave with the streaming hint, which keeps them from displacing the partially written lines at the
 // buckets' frontiers from the L2.  A bucket takes as many rows as it has cells; more can only be duplicate keys.
-// Rounds of 4,096 records: the longest runs that fit LDS beside the tables of GRID_SPAN buckets.
+//
+// Bound by the lines that are written in pieces, so the runs are as long as LDS allows: rounds of 4,096 records and one
+// workgroup per compute unit (two of 2,048 records, which overlap their phases, took 4.10 instead of 3.89 ms for a
+// window of 82M records, two with 1,024 threads each 4.90).  Workgroups go to the eight XCDs in turn and every XCD has an L2
+// of its own: those of one XCD take neighbouring slices, so that a bucket's frontier lines are completed in one L2
+// instead of leaving several in parts (82M records 4.13 -> 3.89 ms, where a communicator bucket is four slices long).
 constexpr u32 PART_THREADS = 1024, PART_U = 4, PART_CHUNK = PART_THREADS * PART_U;
-constexpr u32 PART_BLOCKS = 256;
+constexpr u32 PART_BLOCKS = 256, PART_XCDS = 8;
 
 template <bool SLOTS>
 __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
-  extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 3 x [GRID_SPAN] tables | [PART_CHUNK] slots
+  extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 2 x [GRID_SPAN] tables | [PART_CHUNK] slots
   __shared__ u32 s_wave[PART_THREADS / CCLD_WAVE];
   __shared__ u32 s_at[GRID_MAX_BATCHES + 1], s_slot0[GRID_MAX_BATCHES];
   __shared__ u32 s_total, s_b0, s_last;
   const u32 tid = threadIdx.x;
   if (d.hdr->feasible == 0) return;
   u32* s_dst = reinterpret_cast<u32*>(s_row + PART_CHUNK);
-  u32* s_cnt = s_dst + PART_CHUNK;      // rows of the round per fine bucket
-  u32* s_pre = s_cnt + GRID_SPAN;       // exclusive scan of the counts
-  u32* s_start = s_pre + GRID_SPAN;     // first row reserved in each bucket
+  u32* s_cnt = s_dst + PART_CHUNK;      // rows of the round per fine bucket, then their exclusive scan
+  u32* s_start = s_cnt + GRID_SPAN;     // first row reserved in each bucket
   u32* s_src = s_start + GRID_SPAN;
   // the fine buckets' descriptors and the blame table: every workgroup's share
   const u32 n_fine = d.hdr->n_fine, G = gridDim.x;
@@ -202,7 +206,9 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   const u64 lo_mask = d.kf.cb > 0 ? (((u64)1 << (64 - d.kf.cb)) - 1) : ~0ull;
   const u32 slot_mask = d.kf.mb < 32 ? (1u << d.kf.mb) - 1 : ~0u;
   const u32 per = ((d.n + G - 1) / G + CCLD_WAVE - 1) / CCLD_WAVE * CCLD_WAVE;
-  const u64 lo64 = (u64)per * blockIdx.x;
+  // a permutation of the slices for grids of whole XCD rounds, which all windows of more than 256K records take
+  const u32 slice = G % PART_XCDS == 0 ? (blockIdx.x % PART_XCDS) * (G / PART_XCDS) + blockIdx.x / PART_XCDS : blockIdx.x;
+  const u64 lo64 = (u64)per * slice;
   const u32 lo = lo64 < d.n ? (u32)lo64 : d.n, hi = lo64 + per < d.n ? (u32)(lo64 + per) : d.n;
   u64 status = 0;
   const u32 nb = d.n_buckets == 1 ? 1u : d.nb;          // pieces of one coarse bucket
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
     if (c0 > d.n_comms) c0 = d.n_comms;
     if (c1 > d.n_comms) c1 = d.n_comms;
     const u32 f_lo = d.lay[c0].fb_base, span = d.lay[c1].fb_base - f_lo;
-    // next round's keys and rows are on their way while a round is staged and written
+    // the next round's keys and rows are on their way while a round is staged and written
     u64 key[PART_U], nkey[PART_U];
     uint4 row[PART_U], nrow[PART_U];
     u32 src[PART_U], nsrc[PART_U];
@@ -252,7 +258,6 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
     for (u32 base = pos; base < end; base += PART_CHUNK) {
       u32 fi[PART_U], at[PART_U], cell[PART_U], first[PART_U], room[PART_U];
       bool on[PART_U];
-      if (base + PART_CHUNK < end) load_round(base + PART_CHUNK, nkey, nrow, nsrc);
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) {
         on[u] = base + u * PART_THREADS + tid < end;
@@ -280,14 +285,17 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         u32 tot;
         u32 ex = block_exclusive_sum<PART_THREADS>(sum, s_wave, &tot);
 #pragma unroll
-        for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; if (q < span) { s_pre[q] = ex; s_cnt[q] = 0; } ex += v[i]; }
+        for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; if (q < span) s_cnt[q] = ex; ex += v[i]; }
         if (tid == 0) s_total = tot;
       }
       __syncthreads();
+      // loads and returning atomics complete in order: asked for before the reservations, the next rows would be waited for
+      // with them
+      if (base + PART_CHUNK < end) load_round(base + PART_CHUNK, nkey, nrow, nsrc);
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) {
         if (!on[u]) continue;
-        const u32 q = s_pre[fi[u]] + at[u], w = s_start[fi[u]] + at[u];
+        const u32 q = s_cnt[fi[u]] + at[u], w = s_start[fi[u]] + at[u];
         if (w >= room[u]) status |= DS_DUPLICATE;
         s_dst[q] = w < room[u] ? first[u] + w : ~0u;
         s_row[q] = make_uint4(row[u].x, row[u].y | (cell[u] << ROW_CELL_SHIFT), row[u].z, row[u].w);
@@ -295,6 +303,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
       }
       __syncthreads();
       const u32 total = s_total;
+      for (u32 i = tid; i < span; i += PART_THREADS) s_cnt[i] = 0;
       for (u32 i = tid; i < total; i += PART_THREADS) {
         const u32 D = s_dst[i];
         if (D == ~0u) continue;
@@ -335,7 +344,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
 static_assert(GRID_SPAN % PART_THREADS == 0, "whole buckets per thread");
 
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
-  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, lds_slots = lds + (size_t)PART_CHUNK * 4;
+  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 8, lds_slots = lds + (size_t)PART_CHUNK * 4;
   static bool raised = false;          // more than 64 KB of dynamic LDS has to be asked for once
   if (!raised) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
