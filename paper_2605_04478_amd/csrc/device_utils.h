@@ -23,7 +23,11 @@ __device__ __forceinline__ u32 mbcnt64(u64 m) {
   return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
 }
 
-__device__ __forceinline__ u64 ballot64(bool p) { return __ballot(p); }
+// the lanes where p holds (__ballot takes an integer: the predicate would be turned into one and compared again)
+__device__ __forceinline__ u64 ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// the value that lane `src` (below 64) holds
+__device__ __forceinline__ u32 lane_read(u32 v, u32 src) { return (u32)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)v); }
+__device__ __forceinline__ i32 lane_read(i32 v, u32 src) { return __builtin_amdgcn_ds_bpermute((int)(src << 2), v); }
 
 __device__ __forceinline__ u64 shfl_u64(u64 v, int src) {
   u32 lo = __shfl((u32)v, src, CCLD_WAVE), hi = __shfl((u32)(v >> 32), src, CCLD_WAVE);

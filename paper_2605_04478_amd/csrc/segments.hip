@@ -1252,14 +1252,21 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
     const bool on = (S.pres[c >> 5] >> (c & 31)) & 1u;
     d.cell_row[D.cell0 + c] = (uint16_t)(on ? (S.row[c].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK : GRID_EMPTY);
   }
-  // records per round and their exclusive scan
+  // records per round and their exclusive scan; a bucket with as many rows as cells has a record in every cell, unless one
+  // was taken twice, which fails the analysis
   bool gap = false;
+  if (cnt == cells) {
+    for (u32 k = tid; k < D.K; k += THREADS) S.pre[k] = (unsigned short)(k * D.size);
+    __syncthreads();
+    return dup ? (u64)DS_DUPLICATE : 0;
+  }
   u32 n[U], sum = 0;
+  const u32 per = (D.K + THREADS - 1) / THREADS;          // <= U
 #pragma unroll
   for (u32 q = 0; q < U; ++q) {
-    const u32 k = U * tid + q;
+    const u32 k = per * tid + q;
     n[q] = 0;
-    if (k < D.K) {
+    if (q < per && k < D.K) {
       const u32 b0 = k * D.size, b1 = b0 + D.size;      // bits [b0, b1)
       for (u32 w = b0 >> 5; w <= (b1 - 1) >> 5; ++w) {
         u32 m = S.pres[w];
@@ -1275,8 +1282,8 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
   u32 ex = block_exclusive_sum<THREADS>(sum, S.wave, &tot);
 #pragma unroll
   for (u32 q = 0; q < U; ++q) {
-    const u32 k = U * tid + q;
-    if (k < D.K) S.pre[k] = (unsigned short)ex;
+    const u32 k = per * tid + q;
+    if (q < per && k < D.K) S.pre[k] = (unsigned short)ex;
     ex += n[q];
   }
   __syncthreads();
@@ -1345,125 +1352,145 @@ __device__ __forceinline__ u32 grid_arrival(const SegArgs& a, const GridArgs& d,
 }
 
 // A collective's table row waits in its own cells (16 words; from four members on they are large enough) until the
-// workgroup writes the table, 64 rows per store instruction.  The words are rotated by the round's number, so that
+// workgroup writes the table, 64 rows per store instruction.  The words are permuted by the round's number, so that
 // neither the lanes that write one row nor those that read one word of 64 rows meet in few banks.
-//   0-1 arrival of the first record | 2-5 arrival min, median, max, MAD | 6-9 the same of the completion, all relative to
-//   words 0-1 | 10-11 T_min, T_max | 12-13 their ranks | 14 bytes, low | 15 state, op << 4, bytes, high << 8, n << 13
-// word 15 = ROW_NOT_STAGED: the row was written directly (times that do not fit 30 bits, operations in flight).
+//   0-1 x and y of the first record's row | 2-5 arrival min, median, max, MAD | 6-9 the same of the completion, all relative
+//   to the first record's arrival | 10-11 T_min, T_max | 12-13 their ranks | 14 bytes, low | 15 records | inconsistent << 8
+// word 15 = ROW_NOT_STAGED: the row was written directly (times that do not fit 30 bits, operations in flight).  What
+// follows from these words alone is computed where the table is written: once per collective there, but once per
+// lane in the passes below.
 constexpr u32 ROW_WORDS = 16, ROW_NOT_STAGED = 0xFFFFFFFFu;
-__device__ __forceinline__ u32 stage_word(u32 k, u32 size, u32 w) {
-  return k * size * 4 + (((w + k) & 15u) | (size >= 8 ? k & 16u : 0u));
+struct StageRow {            // where round k's words are
+  u32 base, turn;            // byte offsets
+  __device__ __forceinline__ StageRow(u32 k, u32 size) : base(k * size * 16 + (size >= 8 ? (k & 16u) * 4 : 0u)), turn((k & 15u) * 4) {}
+  __device__ __forceinline__ u32* word(uint4* rows, u32 w) const {
+    return reinterpret_cast<u32*>(reinterpret_cast<char*>(rows) + ((turn ^ (w * 4)) + base));
+  }
+};
+// The bits of a ballot that belong to the calling lane's group of G lanes: one word below 64 lanes, and where the
+// group is the wavefront the same 64 bits in every lane.
+template <int G>
+__device__ __forceinline__ auto group_bits(u64 m, u32 gbase) {
+  if constexpr (G == 64) return m;
+  else if constexpr (G == 32) return (u32)(m >> gbase);
+  else return (u32)(m >> gbase) & ((1u << G) - 1u);
 }
+__device__ __forceinline__ u32 count_bits(u32 m) { return (u32)__builtin_popcount(m); }
+__device__ __forceinline__ u32 count_bits(u64 m) { return (u32)__builtin_popcountll(m); }
+__device__ __forceinline__ u32 first_bit(u32 m) { return (u32)__builtin_ctz(m); }      // m != 0
+__device__ __forceinline__ u32 first_bit(u64 m) { return (u32)__builtin_ctzll(m); }
 
+// Bound by the vector instructions of this loop (82 % of the cycles at 388 per 64 records when it was first counted), so
+// every lane does only what its own record needs.
 template <int G>
 __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
                                             GridShared& S, u32 lane, u32 wave, u32 n_waves) {
   constexpr int SPW = CCLD_WAVE / G;
-  constexpr i64 LIM = (i64)1 << 30;
+  constexpr u32 LIM = 1u << 30;
   const u32 K = D.K, size = D.size;
-  const bool stage = size >= 4;
+  const bool stage = size >= 4, per_record = a.rec_flag || a.lag_e || a.lag_x;
+  const i32 floor32 = a.lag_floor > 0x7FFFFFFF ? 0x7FFFFFFF : a.lag_floor < -0x7FFFFFFF ? -0x7FFFFFFF : (i32)a.lag_floor;
   const u32 q = lane / G, l = lane % G, gbase = q * G;
-  const u64 gmask = (G == 64 ? ~0ull : (((u64)1 << (G & 63)) - 1)) << gbase;
-  const u64 below = ((u64)1 << lane) - 1;
   const u32 rank = l < size ? a.members_sorted[a.member_off[D.comm] + l] : 0u;
-  u32* stw = reinterpret_cast<u32*>(S.row);
   u32 mine = 0;                                    // records seen in this lane's member slot
   for (u32 b = wave; b * SPW < K; b += n_waves) {
     const u32 k = b * SPW + q;
     const bool in = k < K && l < size;
     const u32 cell = in ? k * size + l : 0u;
     const bool valid = in && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
-    const u64 pm = ballot64(valid) & gmask;
-    const u32 n = (u32)__popcll(pm), fl = pm ? (u32)__builtin_ctzll(pm) : gbase;
+    const auto pm = group_bits<G>(ballot64(valid), gbase);
+    const u32 n = count_bits(pm), fl = pm ? first_bit(pm) : 0u;
     const uint4 v = S.row[cell];
-    const uint4 lead = S.row[pm ? k * size + (fl - gbase) : 0u];      // one address per group: a broadcast
+    const uint4 lead = S.row[pm ? k * size + fl : 0u];                // one address per group: a broadcast
     __builtin_amdgcn_wave_barrier();                                  // read before the row is staged over it
     mine += valid ? 1u : 0u;
-    const u32 first = rec0 + (k < K ? S.pre[k] : 0u), j = first + (u32)__popcll(pm & below);
-    const u64 t0 = row_t44(lead);
-    const i64 off = t44_diff(row_t44(v), t0);
-    const bool infl = valid && v.z == ROW_INFLIGHT, done = valid && !infl;
-    const bool wide = valid && (v.z == ROW_WIDE || lead.z == ROW_WIDE || off < -LIM || off >= LIM ||
-                                (done && ((i64)v.z >= LIM || off + (i64)v.z >= LIM)));
-    const i64 ref = wref + t44_diff(t0, (u64)wref);
-    if (valid && a.perm) a.perm[j] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+    // arrival relative to the first record's: the 44 bits of the times sit at the bottom of x and y
+    const u64 diff = (((u64)v.y << 32) | v.x) - (((u64)lead.y << 32) | lead.x);
+    const i32 er = (i32)(u32)diff, xr = (i32)((u32)er + v.z);
+    const bool infl = valid && v.z == ROW_INFLIGHT, done = valid && v.z != ROW_INFLIGHT;
+    // (a first record of full width shows in its own lane)
+    const bool wide = (valid && ((((u32)(diff >> 32) ^ (u32)(er >> 31)) & 0xFFFu) != 0 || (u32)er + LIM >= 2 * LIM)) ||
+                      (done && (v.z >= LIM || xr >= (i32)LIM));
+    const u32 first = rec0 + (k < K ? S.pre[k] : 0u);
+    const auto j_of = [&] { return first + (G == 64 ? mbcnt64((u64)pm) : count_bits((u32)pm & ((1u << l) - 1u))); };
+    if (a.perm && valid) a.perm[j_of()] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+    const StageRow at(k, size);
     if (ballot64(wide) != 0) {
       DenseLane L;
       const Rec r = valid ? unpack_row(v, wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
-      L.e = r.t_enter; L.x = r.t_exit; L.nb = r.bytes; L.op = r.op; L.rank = rank; L.valid = valid; L.fl = fl;
-      L.n = n; L.first = first; L.j = j; L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k;
+      L.e = r.t_enter; L.x = r.t_exit; L.nb = r.bytes; L.op = r.op; L.rank = rank; L.valid = valid; L.fl = gbase + fl;
+      L.n = n; L.first = first; L.j = j_of(); L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k;
       L.stage = nullptr; L.staged = false; L.cell = cell; L.rec0 = rec0; L.flags = &S.flags;
+      const u64 gmask = (G == 64 ? ~0ull : (((u64)1 << (G & 63)) - 1)) << gbase;
       dense_pass64<G, PUT_GRID>(a, L, size, lane, gbase, gmask);
-      if (stage && valid && lane == fl) stw[stage_word(k, size, 15)] = ROW_NOT_STAGED;
+      if (stage && valid && l == fl) *at.word(S.row, 15) = ROW_NOT_STAGED;
       continue;
     }
-    const i32 er = (i32)off, xr = er + (i32)v.z;
-    const u32 nd = (u32)__popcll(ballot64(done) & gmask), ninfl = n - nd;
-    const u32 km = nd ? (nd - 1) / 2 : 0, kl = nd ? nd - 1 : 0;
+    const u32 nd = count_bits(group_bits<G>(ballot64(done), gbase)), ninfl = n - nd;
+    const u32 kl = nd ? nd - 1 : 0, km = kl / 2;
     const i32 se = sort_groups32<G>(done ? er : REL_NONE, lane);
     const i32 sx = sort_groups32<G>(done ? xr : REL_NONE, lane);
-    const i32 med_e = __shfl(se, (int)(gbase + km), CCLD_WAVE), med_x = __shfl(sx, (int)(gbase + km), CCLD_WAVE);
+    const i32 med_e = lane_read(se, gbase + km), med_x = lane_read(sx, gbase + km);
     // deviations of the sorted offsets (the first nd lanes of a group hold its finished records): they fall to zero
     // at the median and rise again, so one merge sorts them
     const bool held = l < nd;
-    const i32 sde = merge_groups32<G>(held ? (se >= med_e ? se - med_e : med_e - se) : REL_NONE, lane);
-    const i32 sdx = merge_groups32<G>(held ? (sx >= med_x ? sx - med_x : med_x - sx) : REL_NONE, lane);
+    auto deviation = [](i32 x, i32 med) { const i32 t = (i32)((u32)x - (u32)med), u = (i32)(0u - (u32)t); return t > u ? t : u; };
+    const i32 sde = merge_groups32<G>(held ? deviation(se, med_e) : REL_NONE, lane);
+    const i32 sdx = merge_groups32<G>(held ? deviation(sx, med_x) : REL_NONE, lane);
     // T_min / T_max of the Duration Time; the first lane that attains one has the smallest rank
     const u32 dmin = reduce_u32<G, false>(done ? v.z : ~0u), dmax = reduce_u32<G, true>(done ? v.z : 0u);
-    const u64 mmin = ballot64(done && v.z == dmin) & gmask, mmax = ballot64(done && v.z == dmax) & gmask;
-    const bool incons = (ballot64(valid && (v.w != lead.w || ((v.y ^ lead.y) & ROW_SAME_MASK))) & gmask) != 0;
+    const auto mmin = group_bits<G>(ballot64(done && v.z == dmin), gbase), mmax = group_bits<G>(ballot64(done && v.z == dmax), gbase);
+    const bool incons = group_bits<G>(ballot64(valid && (v.w != lead.w || ((v.y ^ lead.y) & ROW_SAME_MASK))), gbase) != 0;
+    if (stage && ninfl == 0 && n) {
+      // every lane writes the words it holds
+      if (l == 0) {
+        *at.word(S.row, 0) = lead.x; *at.word(S.row, 1) = lead.y; *at.word(S.row, 2) = (u32)se; *at.word(S.row, 6) = (u32)sx;
+        *at.word(S.row, 10) = dmin; *at.word(S.row, 11) = dmax; *at.word(S.row, 14) = lead.w;
+        *at.word(S.row, 15) = n | (incons ? 256u : 0u);
+      }
+      if (l == km) {
+        *at.word(S.row, 3) = (u32)se; *at.word(S.row, 7) = (u32)sx;
+        *at.word(S.row, 5) = (u32)sde; *at.word(S.row, 9) = (u32)sdx;
+      }
+      if (l == kl) { *at.word(S.row, 4) = (u32)se; *at.word(S.row, 8) = (u32)sx; }
+      if (l == first_bit(mmin)) *at.word(S.row, 12) = rank;
+      if (l == first_bit(mmax)) *at.word(S.row, 13) = rank;
+    }
+    // a lag within the floor is never late (most wavefronts end here), and only finished complete collectives have lags
+    i32 le = (i32)((u32)er - (u32)med_e), lx = (i32)((u32)xr - (u32)med_x);
+    const bool direct = ballot64(!stage || ninfl != 0) != 0;
+    if (!direct && !per_record && ballot64(valid && (le > floor32 || lx > floor32)) == 0) continue;
     const u64 hb = row_bytes(lead);
     const u32 hop = row_op(lead);
     const bool complete = n == size && ninfl == 0;
     const bool barrier = hop == CCLD_OP_ALLREDUCE && hb < (u64)a.barrier_bytes;
     const bool usable = complete && !incons && !barrier;
-    const u32 rmin = __shfl(rank, (int)(mmin ? (u32)__builtin_ctzll(mmin) : lane), CCLD_WAVE);
-    const u32 rmax = __shfl(rank, (int)(mmax ? (u32)__builtin_ctzll(mmax) : lane), CCLD_WAVE);
-    if (stage && ninfl == 0 && n) {
-      // every lane writes the words it holds
-      if (l == 0) { stw[stage_word(k, size, 2)] = (u32)se; stw[stage_word(k, size, 6)] = (u32)sx; }
-      if (l == km) {
-        stw[stage_word(k, size, 3)] = (u32)se; stw[stage_word(k, size, 7)] = (u32)sx;
-        stw[stage_word(k, size, 5)] = (u32)sde; stw[stage_word(k, size, 9)] = (u32)sdx;
-      }
-      if (l == kl) { stw[stage_word(k, size, 4)] = (u32)se; stw[stage_word(k, size, 8)] = (u32)sx; }
-      if (lane == fl) {
-        stw[stage_word(k, size, 0)] = (u32)(u64)ref; stw[stage_word(k, size, 1)] = (u32)((u64)ref >> 32);
-        stw[stage_word(k, size, 10)] = dmin; stw[stage_word(k, size, 11)] = dmax;
-        stw[stage_word(k, size, 12)] = rmin; stw[stage_word(k, size, 13)] = rmax;
-        stw[stage_word(k, size, 14)] = (u32)hb;
-        stw[stage_word(k, size, 15)] = (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) |
-                                       (barrier ? CCLD_SEG_BARRIER : 0) | (usable ? CCLD_SEG_USABLE : 0) | (hop << 4) |
-                                       ((u32)(hb >> 32) << 8) | (n << 13);
-      }
-    }
-    if (ballot64(!stage || ninfl != 0)) {
+    if (direct) {
       // short communicators and operations in flight: the row goes straight to the table
-      const i32 min_e = __shfl(se, (int)gbase, CCLD_WAVE), max_e = __shfl(se, (int)(gbase + kl), CCLD_WAVE);
-      const i32 min_x = __shfl(sx, (int)gbase, CCLD_WAVE), max_x = __shfl(sx, (int)(gbase + kl), CCLD_WAVE);
-      const i32 mad_e = __shfl(sde, (int)(gbase + km), CCLD_WAVE), mad_x = __shfl(sdx, (int)(gbase + km), CCLD_WAVE);
+      const i64 ref = wref + t44_diff(row_t44(lead), (u64)wref);
+      const i32 min_e = lane_read(se, gbase), max_e = lane_read(se, gbase + kl);
+      const i32 min_x = lane_read(sx, gbase), max_x = lane_read(sx, gbase + kl);
+      const i32 mad_e = lane_read(sde, gbase + km), mad_x = lane_read(sdx, gbase + km);
+      const u32 rmin = lane_read(rank, mmin ? gbase + first_bit(mmin) : lane), rmax = lane_read(rank, mmax ? gbase + first_bit(mmax) : lane);
       const i32 imin = (i32)(reduce_u32<G, false>(infl ? (u32)er ^ 0x80000000u : ~0u) ^ 0x80000000u);
-      if (valid && lane == fl && (!stage || ninfl)) {
+      if (valid && l == fl && (!stage || ninfl)) {
         DenseLane L;
         L.n = n; L.first = first; L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k; L.staged = false;
         dense_put_row<PUT_GRID>(a, L, ninfl, complete, incons, barrier, usable, hop, hb, ninfl ? ref + imin : T_INFLIGHT, nd,
                                 ref + min_e, ref + med_e, ref + max_e, (i64)mad_e, ref + min_x, ref + med_x, ref + max_x,
                                 (i64)mad_x, (i64)dmin, (i64)dmax, rmin, rmax);
-        if (stage) stw[stage_word(k, size, 15)] = ROW_NOT_STAGED;
+        if (stage) *at.word(S.row, 15) = ROW_NOT_STAGED;
       }
     }
-    i32 le = 0, lx = 0;
     u32 f = 0;
-    if (usable) { le = er - med_e; lx = xr - med_x; }
-    // a lag within the floor is never late (most wavefronts end here)
-    if (ballot64(valid && ((i64)le > a.lag_floor || (i64)lx > a.lag_floor))) {
-      const i32 mad_e = __shfl(sde, (int)(gbase + km), CCLD_WAVE), mad_x = __shfl(sdx, (int)(gbase + km), CCLD_WAVE);
-      if (usable) {
-        if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
-        if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
-      }
+    const i32 mad_e = lane_read(sde, gbase + km), mad_x = lane_read(sdx, gbase + km);
+    if (usable) {
+      if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
+      if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
+    } else {
+      le = 0; lx = 0;
     }
-    if (valid) grid_put_record(a, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
+    if (valid) grid_put_record(a, per_record ? j_of() : 0u, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
   }
   return mine;
 }
@@ -1496,22 +1523,28 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
   if (tid == 0) d.nflag[f] = S.flags.n;
   // the staged rows: every wavefront takes 64 of them
   if (size >= 4) {
-    const u32* stw = reinterpret_cast<const u32*>(S.row);
+    // a wavefront-uniform pointer that steps from column to column and a 32-bit offset per lane
+    const u64 stride = a.seg_cap * 8u;
     for (u32 k = wave * CCLD_WAVE + lane; k < D.K; k += GRID_THREADS) {
+      const StageRow at(k, size);
       u32 w[ROW_WORDS];
 #pragma unroll
-      for (u32 i = 0; i < ROW_WORDS; ++i) w[i] = stw[stage_word(k, size, i)];
+      for (u32 i = 0; i < ROW_WORDS; ++i) w[i] = *at.word(S.row, i);
       if (w[15] == ROW_NOT_STAGED) continue;
       const u32 srow = D.srow0 + k;
-      const u32 state = w[15] & 15u, op = (w[15] >> 4) & 15u, n = w[15] >> 13;
-      const u64 nb = (u64)w[14] | ((u64)((w[15] >> 8) & 31u) << 32);
-      const bool usable = (state & CCLD_SEG_USABLE) != 0;
+      const u32 n = w[15] & 255u, op = (w[1] >> 12) & 15u;
+      const u64 nb = (u64)w[14] | ((u64)(w[1] >> 27) << 32);
+      const bool complete = n == size, incons = w[15] >> 8 != 0, barrier = op == CCLD_OP_ALLREDUCE && nb < (u64)a.barrier_bytes;
+      const bool usable = complete && !incons && !barrier;
+      const u32 state = (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) | (barrier ? CCLD_SEG_BARRIER : 0) |
+                        (usable ? CCLD_SEG_USABLE : 0);
       a.gcode[srow] = (uint16_t)seg_group_code(usable, op, nb);
       a.range_c[srow] = usable ? (i64)(w[11] - w[10]) : 0;
       if (srow >= a.seg_cap) continue;
-      const i64 ref = (i64)((u64)w[0] | ((u64)w[1] << 32));
-      i64* p = a.seg + srow;
-      auto put = [&](i64 v) { *p = v; p += a.seg_cap; };
+      const i64 ref = wref + t44_diff((u64)w[0] | ((u64)(w[1] & 0xFFFu) << 32), (u64)wref);
+      char* p = reinterpret_cast<char*>(a.seg + D.srow0);
+      const u32 off = k * 8u;
+      auto put = [&](i64 v) { *reinterpret_cast<i64*>(p + off) = v; p += stride; };
       put((i64)D.comm); put((i64)(D.seq0 + k)); put((i64)n); put(0); put((i64)state); put((i64)op); put((i64)nb);
       put(ref + (i32)w[2]); put(ref + (i32)w[3]); put(ref + (i32)w[4]); put((i64)w[5]);
       put(ref + (i32)w[6]); put(ref + (i32)w[7]); put(ref + (i32)w[8]); put((i64)w[9]);
