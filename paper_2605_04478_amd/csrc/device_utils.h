@@ -84,6 +84,11 @@ __device__ __forceinline__ u32 block_exclusive_sum(u32 v, u32* s_wave, u32* tota
   return base + inc - v;
 }
 
+// Waits until the wavefront's loads and stores are done.  Where a round's loads are issued conditionally one round ahead, the
+// compiler cannot count what was issued behind them and waits for everything at their first use in the loop, which is
+// right after the next round's loads were issued: such loops wait here, at the place that is meant.
+__device__ __forceinline__ void wait_vector_memory() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
 // Words that workgroups of one launch hand to one another: stored and loaded past the caches that are not coherent
 // between the XCDs, so that no cache has to be written back for them.
 __device__ __forceinline__ void store_agent(u32* p, u32 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }

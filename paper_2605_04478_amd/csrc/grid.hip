@@ -172,18 +172,21 @@ void launch_grid_layout(hipStream_t st, const GridArgs& d) {
 // instead of leaving several in parts (82M records 4.13 -> 3.89 ms, where a communicator bucket is four slices long).
 constexpr u32 PART_THREADS = 1024, PART_U = 4, PART_CHUNK = PART_THREADS * PART_U;
 constexpr u32 PART_BLOCKS = 256, PART_XCDS = 8;
+constexpr u32 PART_LAY = 64;           // communicators of a bucket whose layout rows wait in LDS
 
 template <bool SLOTS>
 __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
-  extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 2 x [GRID_SPAN] tables | [PART_CHUNK] slots
+  extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 3 x [GRID_SPAN] tables | [PART_CHUNK] slots
   __shared__ u32 s_wave[PART_THREADS / CCLD_WAVE];
   __shared__ u32 s_at[GRID_MAX_BATCHES + 1], s_slot0[GRID_MAX_BATCHES];
   __shared__ u32 s_total, s_b0, s_last;
+  __shared__ CommLayout s_lay[PART_LAY];
   const u32 tid = threadIdx.x;
   if (d.hdr->feasible == 0) return;
   u32* s_dst = reinterpret_cast<u32*>(s_row + PART_CHUNK);
   u32* s_cnt = s_dst + PART_CHUNK;      // rows of the round per fine bucket, then their exclusive scan
-  u32* s_start = s_cnt + GRID_SPAN;     // first row reserved in each bucket
+  u32* s_next = s_cnt + GRID_SPAN;      // the same of the next round: cleared one round ahead
+  u32* s_start = s_next + GRID_SPAN;    // first row reserved in each bucket
   u32* s_src = s_start + GRID_SPAN;
   // the fine buckets' descriptors and the blame table: every workgroup's share
   const u32 n_fine = d.hdr->n_fine, G = gridDim.x;
@@ -217,21 +220,24 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
     while (b - a > 1) { const u32 m = (a + b) >> 1; if (d.piece_at[(u64)m * nb] <= lo) a = m; else b = m; }
     s_b0 = a;
   }
-  for (u32 i = tid; i < GRID_SPAN; i += PART_THREADS) s_cnt[i] = 0;
+  for (u32 i = tid; i < 2 * GRID_SPAN; i += PART_THREADS) s_cnt[i] = 0;
   __syncthreads();
-  u32 pos = lo;
+  u32 pos = lo, widest = 0;              // of the spans so far: entries behind a bucket's own may be another's
   for (u32 b = lo < hi ? s_b0 : d.n_buckets; b < d.n_buckets && pos < hi; ++b) {
     // the bucket's pieces, its records of this slice and its fine buckets
     for (u32 i = tid; i <= nb; i += PART_THREADS) {
       s_at[i] = d.piece_at[b * nb + i];
       if (i < nb) s_slot0[i] = d.piece_slot[b * nb + i];
     }
-    __syncthreads();
-    const u32 end = s_at[nb] < hi ? s_at[nb] : hi;
     u64 c0 = (u64)b << d.bshift, c1 = (u64)(b + 1) << d.bshift;
     if (c0 > d.n_comms) c0 = d.n_comms;
     if (c1 > d.n_comms) c1 = d.n_comms;
+    const bool near = c1 - c0 <= PART_LAY;
+    if (near && tid < c1 - c0) s_lay[tid] = d.lay[c0 + tid];
+    __syncthreads();
+    const u32 end = s_at[nb] < hi ? s_at[nb] : hi;
     const u32 f_lo = d.lay[c0].fb_base, span = d.lay[c1].fb_base - f_lo;
+    widest = span > widest ? span : widest;
     // the next round's keys and rows are on their way while a round is staged and written
     u64 key[PART_U], nkey[PART_U];
     uint4 row[PART_U], nrow[PART_U];
@@ -255,8 +261,10 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
       }
     };
     load_round(pos, key, row, src);
+    wait_vector_memory();        // so that no register of the loop below is waited for behind the loads inside it
     for (u32 base = pos; base < end; base += PART_CHUNK) {
-      u32 fi[PART_U], at[PART_U], cell[PART_U], first[PART_U], room[PART_U];
+      // (packed: at 128 registers per thread the kernel spills with a word for each)
+      u32 fi_cell[PART_U], at_room[PART_U], first[PART_U];       // fi | cell << 16, at | room << 16
       bool on[PART_U];
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) {
@@ -264,46 +272,58 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         if (!on[u]) continue;
         const u64 k = key[u];
         const u32 comm = d.kf.cb ? (u32)(k >> (64 - d.kf.cb)) : 0u;
-        const CommLayout L = d.lay[comm];
+        CommLayout L;
+        if (near) {
+          L = s_lay[comm - (u32)c0];
+        } else {
+          L = d.lay[comm];
+          wait_vector_memory();        // nothing of this branch is waited for behind it
+        }
         const u32 rel = (u32)(((k & lo_mask) >> d.kf.mb) - L.seq_min);
         const u32 fr = rel / L.rpb, rr = rel - fr * L.rpb, left = L.rounds - fr * L.rpb;
-        fi[u] = L.fb_base + fr - f_lo;
-        cell[u] = rr * L.size + ((u32)k & slot_mask);
+        const u32 fi = L.fb_base + fr - f_lo, room = (left < L.rpb ? left : L.rpb) * L.size;
         first[u] = L.cell_base + fr * L.rpb * L.size;
-        room[u] = (left < L.rpb ? left : L.rpb) * L.size;
-        on[u] = fi[u] < span;
-        if (on[u]) at[u] = atomicAdd(&s_cnt[fi[u]], 1u);
+        on[u] = fi < span;
+        fi_cell[u] = fi | ((rr * L.size + ((u32)k & slot_mask)) << 16);
+        if (on[u]) at_room[u] = atomicAdd(&s_cnt[fi], 1u) | (room << 16);
       }
       __syncthreads();
-      {     // exclusive scan of the round's counts, and one reservation per bucket
+      {     // one reservation per bucket, all on their way at once, and meanwhile the exclusive scan of the round's counts
         constexpr u32 PER = GRID_SPAN / PART_THREADS;
-        u32 v[PER], sum = 0;
+        u32 v[PER], got[PER], sum = 0;
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) {
+          const u32 q = tid + i * PART_THREADS, c = q < span ? s_cnt[q] : 0u;
+          got[i] = 0;
+          if (c) got[i] = atomicAdd(&d.fill[f_lo + q], c);
+        }
 #pragma unroll
         for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; v[i] = q < span ? s_cnt[q] : 0u; sum += v[i]; }
-#pragma unroll
-        for (u32 i = 0; i < PER; ++i) if (v[i]) s_start[PER * tid + i] = atomicAdd(&d.fill[f_lo + PER * tid + i], v[i]);
         u32 tot;
         u32 ex = block_exclusive_sum<PART_THREADS>(sum, s_wave, &tot);
 #pragma unroll
         for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; if (q < span) s_cnt[q] = ex; ex += v[i]; }
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) { const u32 q = tid + i * PART_THREADS; if (q < span) s_start[q] = got[i]; }
         if (tid == 0) s_total = tot;
       }
       __syncthreads();
       // loads and returning atomics complete in order: asked for before the reservations, the next rows would be waited for
       // with them
       if (base + PART_CHUNK < end) load_round(base + PART_CHUNK, nkey, nrow, nsrc);
+      for (u32 i = tid; i < widest; i += PART_THREADS) s_next[i] = 0;
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) {
         if (!on[u]) continue;
-        const u32 q = s_cnt[fi[u]] + at[u], w = s_start[fi[u]] + at[u];
-        if (w >= room[u]) status |= DS_DUPLICATE;
-        s_dst[q] = w < room[u] ? first[u] + w : ~0u;
-        s_row[q] = make_uint4(row[u].x, row[u].y | (cell[u] << ROW_CELL_SHIFT), row[u].z, row[u].w);
+        const u32 fi = fi_cell[u] & 0xFFFFu, at = at_room[u] & 0xFFFFu, room = at_room[u] >> 16;
+        const u32 q = s_cnt[fi] + at, w = s_start[fi] + at;
+        if (w >= room) status |= DS_DUPLICATE;
+        s_dst[q] = w < room ? first[u] + w : ~0u;
+        s_row[q] = make_uint4(row[u].x, row[u].y | (fi_cell[u] & 0xFFFF0000u), row[u].z, row[u].w);
         if (SLOTS) s_src[q] = src[u];
       }
       __syncthreads();
       const u32 total = s_total;
-      for (u32 i = tid; i < span; i += PART_THREADS) s_cnt[i] = 0;
       for (u32 i = tid; i < total; i += PART_THREADS) {
         const u32 D = s_dst[i];
         if (D == ~0u) continue;
@@ -316,7 +336,8 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         else d.rows[D] = v;
         if (SLOTS) d.slots[D] = s_src[i];
       }
-      __syncthreads();
+      // no barrier here: the staging area is written again behind two barriers of the next round
+      u32* const t = s_cnt; s_cnt = s_next; s_next = t;
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) { key[u] = nkey[u]; row[u] = nrow[u]; src[u] = nsrc[u]; }
     }
@@ -342,9 +363,10 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   if (tid == 0) d.rec0[n_fine] = carry;
 }
 static_assert(GRID_SPAN % PART_THREADS == 0, "whole buckets per thread");
+static_assert(ROW_CELL_SHIFT == 16 && ROW_CELL_MASK == GRID_B - 1, "the cell is packed as the row has it");
 
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
-  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 8, lds_slots = lds + (size_t)PART_CHUNK * 4;
+  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, lds_slots = lds + (size_t)PART_CHUNK * 4;
   static bool raised = false;          // more than 64 KB of dynamic LDS has to be asked for once
   if (!raised) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

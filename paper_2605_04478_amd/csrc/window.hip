@@ -120,9 +120,9 @@ __global__ __launch_bounds__(256) void k_ingest_scan(u32* table, u32* totals, u3
 }
 
 // Validation and key of one record (Trace ID = communicator id + operation counter, then the rank's
-// member slot).  mem = the rank's packed membership row when the topology has one (memb4 != null).
+// member slot).  mem = the rank's packed membership row when the topology has them (packed).
 __device__ __forceinline__ u64 ingest_key(u32 r, u32 c, u64 sq, u32 op, i64 te, i64 tx, const uint4& mem,
-                                          const uint4* memb4, const DeviceTopology& T, const KeyFormat& kf,
+                                          bool packed, const DeviceTopology& T, const KeyFormat& kf,
                                           u32 slot_mask, u64& status, u64& maxseq, u64& maxinv) {
   u64 key = 0;
   if (c >= T.n_comms) {
@@ -131,13 +131,14 @@ __device__ __forceinline__ u64 ingest_key(u32 r, u32 c, u64 sq, u32 op, i64 te, 
   }
   bool member = false;
   u32 slot = 0;
-  if (memb4) {
+  if (packed) {
     const u32 w = c == (mem.x >> kf.mb) ? mem.x : c == (mem.y >> kf.mb) ? mem.y : c == (mem.z >> kf.mb) ? mem.z : mem.w;
     member = c == (w >> kf.mb);
     slot = w & slot_mask;
   } else if (r < T.n_ranks) {
     for (u32 q = T.rank_comm_off[r]; q < T.rank_comm_off[r + 1]; ++q)
       if (T.rank_comms[q] == c) { member = true; slot = T.rank_slots[q]; }
+    wait_vector_memory();              // nothing of this branch is waited for behind it
   }
   if (!member) status |= DS_NOT_MEMBER;
   if (op >= CCLD_OP_MAX || te < 0 || te == T_INFLIGHT || tx < te) status |= DS_RANGE;
@@ -227,8 +228,8 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
     for (int u = 0; u < U; ++u) {
       const u64 i = i0 + (u64)u * THREADS;
       if (i >= i_end) continue;
-      const u64 key = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem[u], memb4, T, kf, slot_mask, status, maxseq,
-                                 maxinv);
+      const u64 key = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem[u], memb4 != nullptr, T, kf, slot_mask, status,
+                                 maxseq, maxinv);
       if (a.range && c[u] < T.n_comms) note_range(s_rng, c[u], sq[u]);
       u64 p = (u64)a.tail + i;
       if (p >= a.cap) p -= a.cap;
@@ -307,19 +308,26 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
     }
   };
   load_round(i_begin, r, c, sq, op, nb, te, tx);
+  wait_vector_memory();
   for (u64 base = i_begin; base < i_end; base += CHUNK) {        // uniform over the workgroup
     u32 at[U], bk[U];
     u64 key[U];
     bool on[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) on[u] = base + (u64)u * THREADS + tid < i_end;
+    // the packed membership rows, if not from LDS then before the next round's columns are asked for: loads complete in order
+    uint4 mem[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mem[u] = make_uint4(~0u, ~0u, ~0u, ~0u);
+      if (on[u] && (LDS_TABLE || memb4) && r[u] < T.n_ranks) mem[u] = LDS_TABLE ? s_dyn[r[u]] : memb4[r[u]];
+    }
+    if (!LDS_TABLE) wait_vector_memory();
     load_round(base + CHUNK, nr, nc, nsq, nop, nnb, nte, ntx);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (!on[u]) continue;
-      uint4 mem = make_uint4(~0u, ~0u, ~0u, ~0u);
-      if (memb4 && r[u] < T.n_ranks) mem = LDS_TABLE ? s_dyn[r[u]] : memb4[r[u]];
-      key[u] = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem, memb4, T, kf, slot_mask, status, maxseq, maxinv);
+      key[u] = ingest_key(r[u], c[u], sq[u], op[u], te[u], tx[u], mem[u], LDS_TABLE || memb4, T, kf, slot_mask, status, maxseq, maxinv);
       if (a.range && c[u] < T.n_comms) note_range(s_rng, c[u], sq[u]);
       bk[u] = c[u] < T.n_comms ? (c[u] >> a.bshift) : 0u;
       at[u] = atomicAdd(&s_off[bk[u]], 1u);
@@ -358,6 +366,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       s_row[q] = row;
     }
     __syncthreads();
+    wait_vector_memory();              // the next round's columns; the stores below have the next round's time
     const u32 total = s_total, num0 = a.seqno0 + (u32)base;
     // Pieces of a line that this round writes completely leave with the streaming hint: they do not stay in
     // the L2, where they would displace the partially written lines at the buckets' frontiers before the
