@@ -54,7 +54,8 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->win_key = w.take<uint64_t>(N);
   c->win_row = w.take<uint4>(N);
   c->win_wide = w.take<int64_t>(3 * N);
-  c->win_arrival = w.take<uint32_t>(c->n_buckets > 1 ? N : 1);
+  c->rounds_cap = c->n_buckets > 1 ? ingest_rounds_cap(N, c->p.window_batches) : 0;
+  c->ing_rounds = w.take<uint32_t>(c->rounds_cap * c->n_buckets + 1);
   c->batch_meta = w.take<BatchMeta>((uint64_t)c->p.window_batches + 2);
   const uint64_t n_meta = (uint64_t)c->p.window_batches + 2;
   c->ing_table = w.take<uint32_t>((uint64_t)c->n_buckets * INGEST_BLOCKS);
@@ -300,7 +301,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   c->stream = (hipStream_t)hip_stream;
   c->chain_ready = false;
   c->rank_bits = bits_for_host(topo->n_ranks - 1);
-  c->head = 0; c->count = 0; c->next_slot = 0; c->total_ingested = 0;
+  c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0;
   c->sorted_buf = 0; c->last_n = 0; c->blame_valid = false; c->sort_passes = 0;
   c->sf.mb = mb; c->sf.ws = 0; c->sf.seq_base = 0;
   Carver w{(uint8_t*)workspace, 0};
@@ -420,7 +421,7 @@ ccld_status ccld_destroy(ccld_ctx* c) {
 
 ccld_status ccld_reset_window(ccld_ctx* c) {
   if (!c) return CCLD_E_NULL;
-  c->head = 0; c->count = 0; c->batch_n.clear(); c->batch_slot.clear(); c->batch_seqno.clear();
+  c->head = 0; c->count = 0; c->batch_n.clear(); c->batch_slot.clear();
   c->chain_ready = false;
   return CCLD_OK;
 }
@@ -461,11 +462,18 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
     HIP_TRY(hipMemcpyAsync(d_op, b->op, n, hipMemcpyHostToDevice, c->stream));
     a.rank = d_rank; a.comm = d_comm; a.seq = d_seq; a.op = d_op; a.bytes = d_bytes; a.t_enter = d_te; a.t_exit = d_tx;
   }
-  a.n = n; a.win_key = c->win_key; a.win_row = c->win_row; a.win_wide = c->win_wide; a.win_arrival = c->win_arrival;
+  a.n = n; a.win_key = c->win_key; a.win_row = c->win_row; a.win_wide = c->win_wide;
   a.tail = (uint32_t)((head + count) % std::max<uint64_t>(c->cap, 1));
   a.cap = (uint32_t)c->cap;
   a.table = c->ing_table; a.bucket_base = c->ing_base + (uint64_t)slot * (c->n_buckets + 1); a.done = c->ing_done; a.scratch_total = &c->counters[CNT_COUNT - 1];
-  a.n_buckets = c->n_buckets; a.bshift = c->bshift; a.seqno0 = (uint32_t)c->total_ingested;
+  a.n_buckets = c->n_buckets; a.bshift = c->bshift;
+  uint64_t rounds_end = c->rounds_next;
+  if (c->n_buckets > 1) {
+    const IngestShape shape = ingest_shape(n);
+    const uint64_t r = (uint64_t)shape.groups * shape.per_group, at = c->rounds_next + r <= c->rounds_cap ? c->rounds_next : 0;
+    a.rounds = c->ing_rounds; a.round0 = (uint32_t)at;
+    rounds_end = at + r;
+  }
   if (c->grid_capable) {
     a.range = c->comm_range + (uint64_t)slot * c->topo.n_comms * 2;
     a.range_next = c->comm_range + (uint64_t)next * c->topo.n_comms * 2;
@@ -477,11 +485,9 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   if (!b->on_device && n) HIP_TRY(hipStreamSynchronize(c->stream));   // the host buffers may go away on return
   c->batch_n.erase(c->batch_n.begin(), c->batch_n.begin() + drop);
   c->batch_slot.erase(c->batch_slot.begin(), c->batch_slot.begin() + drop);
-  c->batch_seqno.erase(c->batch_seqno.begin(), c->batch_seqno.begin() + drop);
   c->batch_n.push_back(n);
   c->batch_slot.push_back(slot);
-  c->batch_seqno.push_back((uint32_t)c->total_ingested);
-  c->total_ingested += n;
+  c->rounds_next = rounds_end;
   c->next_slot = next;
   c->head = head; c->count = count + n;
   return CCLD_OK;
@@ -615,8 +621,7 @@ static SegArgs seg_args(ccld_ctx* c, int64_t now_ns, const ccld_window_result* o
   sa.win.row = c->win_row; sa.win.wide = c->win_wide; sa.win.meta = c->batch_meta; sa.win.n_meta = n_meta;
   sa.win.n_batch = (uint32_t)c->batch_slot.size(); sa.win.slot0 = c->batch_slot.empty() ? 0 : c->batch_slot[0];
   sa.win.head = (uint32_t)c->head; sa.win.cap = (uint32_t)std::max<uint64_t>(c->cap, 1);
-  sa.seqno_head = c->batch_seqno.empty() ? 0u : c->batch_seqno[0];
-  sa.arrival = c->n_buckets > 1 ? c->win_arrival : nullptr;
+  sa.win.bucket_base = c->ing_base; sa.win.rounds = c->n_buckets > 1 ? c->ing_rounds : nullptr; sa.win.n_buckets = c->n_buckets;
   return sa;
 }
 
@@ -732,7 +737,7 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   fa.tile_flags = c->tile_flags; fa.flag_pos = c->flag_pos; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
   fa.counters = c->counters;
   launch_flag_compact(st, fa);
-  if (o->perm) launch_perm(st, sa.idx, sa.arrival, n, sa.seqno_head, sa.win.head, sa.win.cap, o->perm);
+  if (o->perm) launch_perm(st, sa.idx, sa.win, n, o->perm);
   // 4. per-rank blame
   c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_BLAME);
   launch_blame_sums(st, fa, n_ranks, c->blame);

@@ -70,7 +70,12 @@ enum { DS_UNKNOWN_COMM = 1, DS_NOT_MEMBER = 2, DS_RANGE = 4, DS_KEY_WIDTH = 8, D
 // device-side header of a batch: status bits, largest operation counter and largest complement of one (i.e.
 // ~smallest counter), so that a zeroed header means "no record yet"; the time its rows are relative to, its first
 // window slot and its records
-struct BatchMeta { uint64_t status; uint64_t max_seq; uint64_t max_inv_seq; int64_t ref; uint64_t tail; uint64_t n; };
+struct BatchMeta {
+  uint64_t status; uint64_t max_seq; uint64_t max_inv_seq; int64_t ref; uint64_t tail; uint64_t n;
+  // a batch placed by bucket: records per placement workgroup, and its rounds in the rounds table (the first one's
+  // number, how many, how many per workgroup)
+  uint64_t chunk; uint32_t round0, n_rounds, per_group, pad;
+};
 
 // The window's rows (rows.h) and what it takes to read one by its slot.
 struct WindowRows {
@@ -81,7 +86,16 @@ struct WindowRows {
   const BatchMeta* meta;     // headers of the window's batches: n_batch of them from slot0 on, modulo n_meta
   uint32_t n_meta, slot0, n_batch;
   uint32_t head, cap;
+  // batches placed by bucket (null: slots are in order of arrival): first record of every bucket in each batch, first record
+  // of every round in each bucket
+  const uint32_t* bucket_base;   // [n_meta][n_buckets + 1]
+  const uint32_t* rounds;        // [rounds][n_buckets]
+  uint32_t n_buckets;
 };
+constexpr uint32_t INGEST_ROUND = 2048;      // records that a placement workgroup regroups at a time
+// Rounds of all resident batches and of one more: a batch of n records has at most 3 n / 2048 + 2, and as much again keeps
+// a batch's rounds in one piece where the table starts over.
+inline uint64_t ingest_rounds_cap(uint64_t records, uint64_t batches) { return 2 * (3 * records / INGEST_ROUND + 2 * batches) + 64; }
 
 constexpr int SEG_TILE = 1024;       // sorted records owned by one workgroup of the segment kernels
 constexpr int SEG_THREADS = 256;
@@ -115,10 +129,9 @@ struct ccld_ctx {
   uint64_t* win_key;
   uint4* win_row;                     // [cap] 16-byte rows (rows.h)
   int64_t* win_wide;                  // [cap][3] values of the rows that do not fit
-  uint32_t* win_arrival;              // [cap] arrival number of each slot (batches placed by bucket)
+  uint32_t* ing_rounds;               // [rounds_cap][n_buckets] (batches placed by bucket)
+  uint64_t rounds_cap, rounds_next;   // the next batch's rounds start there
   ccld::BatchMeta* batch_meta;        // [window_batches + 2]
-  std::vector<uint32_t> batch_seqno;  // arrival number of each resident batch's first record
-  uint64_t total_ingested;
   uint32_t* ing_table;                // [n_buckets][INGEST_BLOCKS]
   uint32_t* ing_base;                 // [window_batches + 2][n_buckets + 1]
   uint32_t* ing_done;                 // zero between launches

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         const u32 q = s_cnt[fi] + at, w = s_start[fi] + at;
         if (w >= room) status |= DS_DUPLICATE;
         s_dst[q] = w < room ? first[u] + w : ~0u;
-        s_row[q] = make_uint4(row[u].x, row[u].y | (fi_cell[u] & 0xFFFF0000u), row[u].z, row[u].w);
+        s_row[q] = make_uint4(row[u].x, (row[u].y & ~(ROW_CELL_MASK << ROW_CELL_SHIFT)) | (fi_cell[u] & (ROW_CELL_MASK << ROW_CELL_SHIFT)), row[u].z, row[u].w);
         if (SLOTS) s_src[q] = src[u];
       }
       __syncthreads();

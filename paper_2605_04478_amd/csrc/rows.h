@@ -1,8 +1,8 @@
 // The window's payload rows: 16 bytes per record.
 //
 //   x        low 32 bits of t_enter
-//   y        bits 0-11 t_enter 32..43 | 12-15 op | 16-26 free (the grid placement puts the record's cell here) |
-//            27-31 bytes 32..36
+//   y        bits 0-11 t_enter 32..43 | 12-15 op | 16-26 number of the record in its round of the ingest where
+//            batches are placed by bucket (the grid placement puts the record's cell here) | 27-31 bytes 32..36
 //   z        t_exit - t_enter, ROW_INFLIGHT while the operation runs, ROW_WIDE for a row that does not fit
 //   w        low 32 bits of bytes; the window slot for a row that does not fit
 //
@@ -64,6 +64,30 @@ __device__ __forceinline__ i64 ref_of_slot(const WindowRows& W, u32 slot) {
   }
   return W.ref;
 }
+// Position of a window slot in the window's order of arrival.  A batch that was placed by bucket has the record's number
+// in its round in the row; the round follows from the slot, since every round has a stretch of its own in every bucket.
+// (Two searches for the few callers that ask, instead of 4 bytes more per record at ingest: 82M records 3.69 -> 3.50 ms.)
+__device__ __forceinline__ u32 arrival_of_slot(const WindowRows& W, u32 slot) {
+  const u32 off = slot >= W.head ? slot - W.head : slot + W.cap - W.head;
+  if (!W.rounds) return off;
+  for (u32 m = 0; m < W.n_batch; ++m) {
+    const u32 at = (W.slot0 + m) % W.n_meta;
+    const BatchMeta& b = W.meta[at];
+    const u32 t = (u32)b.tail, start = t >= W.head ? t - W.head : t + W.cap - W.head;
+    if (!b.n || off - start >= (u32)b.n) continue;
+    const u32 o = off - start;
+    const u32* base = W.bucket_base + (u64)at * (W.n_buckets + 1);
+    u32 lo = 0, hi = W.n_buckets;                       // the bucket: the last one that starts at or before o
+    while (hi - lo > 1) { const u32 mid = (lo + hi) >> 1; if (base[mid] <= o) lo = mid; else hi = mid; }
+    const u32* col = W.rounds + (u64)b.round0 * W.n_buckets + lo;
+    u32 r = 0, end = b.n_rounds;                        // the round, likewise
+    while (end - r > 1) { const u32 mid = (r + end) >> 1; if (col[(u64)mid * W.n_buckets] <= o) r = mid; else end = mid; }
+    const u32 num = (W.row[slot].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK;
+    return start + (u32)(r / b.per_group * b.chunk) + r % b.per_group * INGEST_ROUND + num;
+  }
+  return off;
+}
+static_assert(INGEST_ROUND == ROW_CELL_MASK + 1, "a round's numbers fit the row's free bits");
 __device__ __forceinline__ Rec load_rec(const WindowRows& W, u32 slot) {
   return unpack_row(W.row[slot], ref_of_slot(W, slot), W.wide);
 }

@@ -1346,9 +1346,7 @@ static_assert(CCLD_BLM_N_LATE_ENTER == 0 && CCLD_BLM_N_LATE_EXIT == 1 && CCLD_BL
               CCLD_BLM_SUM_LAG_EXIT == 3, "blame column order");
 // position in the window's arrival order of a partitioned row
 __device__ __forceinline__ u32 grid_arrival(const SegArgs& a, const GridArgs& d, u32 at) {
-  const u32 slot = d.slots[at];
-  if (a.arrival) return a.arrival[slot] - a.seqno_head;
-  return slot >= d.head ? slot - d.head : slot + d.cap - d.head;
+  return arrival_of_slot(a.win, d.slots[at]);
 }
 
 // A collective's table row waits in its own cells (16 words; from four members on they are large enough) until the

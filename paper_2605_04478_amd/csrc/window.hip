@@ -47,7 +47,7 @@ void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v) {
 // ingest of the batch before cleared them (clear_next), the first ones were cleared at create.
 __device__ __forceinline__ void clear_next(const IngestArgs& a, u32 n_comms, u32 tid, u32 threads) {
   if (blockIdx.x == 0 && tid == 0) {
-    BatchMeta z = {0, 0, 0, 0, 0, 0};
+    BatchMeta z = {};
     *a.meta_next = z;
   }
   if (a.range_next)
@@ -56,6 +56,7 @@ __device__ __forceinline__ void clear_next(const IngestArgs& a, u32 n_comms, u32
 // what is known of the batch before its first record is read
 __device__ __forceinline__ void put_header(const IngestArgs& a, i64 ref) {
   a.meta->ref = ref; a.meta->tail = a.tail; a.meta->n = a.n;
+  a.meta->chunk = a.chunk; a.meta->round0 = a.round0; a.meta->n_rounds = a.per_group * gridDim.x; a.meta->per_group = a.per_group;
 }
 
 // Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Small
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
   ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a, s_rng, T.n_comms);
 }
 // Windows placed by bucket.  A workgroup takes CHUNK records per round, gives each its slot in its bucket (LDS atomic),
-// then stages keys, rows and arrival numbers in LDS ordered by (bucket, slot) and writes them out with consecutive lanes
+// then stages keys and rows in LDS ordered by (bucket, slot) and writes them out with consecutive lanes
 // on consecutive pieces: every bucket's share of the round leaves as one contiguous run instead of one scattered store
 // per lane.  LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS: with records in random order that
 // lookup is a gather with no locality, cheaper from LDS than from the L2.
@@ -253,7 +254,8 @@ template <int THREADS, bool LDS_TABLE>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
   constexpr u32 CHUNK = THREADS * U;
-  // [n_ranks] membership rows (LDS_TABLE) | [CHUNK] rows | [CHUNK] keys | [n_comms][2] ranges | [CHUNK] window slots | [CHUNK] numbers in the round
+  static_assert(CHUNK == INGEST_ROUND, "a row has room for the record's number in its round");
+  // [n_ranks] membership rows (LDS_TABLE) | [CHUNK] rows | [CHUNK] keys | [n_comms][2] ranges | [CHUNK] window slots
   extern __shared__ uint4 s_dyn[];
   __shared__ u64 s_status[THREADS / CCLD_WAVE], s_max[THREADS / CCLD_WAVE], s_inv[THREADS / CCLD_WAVE];
   __shared__ u32 s_off[INGEST_STAGED_BUCKETS], s_start[INGEST_STAGED_BUCKETS], s_pre[INGEST_STAGED_BUCKETS], s_total;
@@ -262,7 +264,6 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   u64* s_key = reinterpret_cast<u64*>(s_row + CHUNK);
   unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + CHUNK);
   u32* s_p = reinterpret_cast<u32*>(s_rng + (a.range ? 2 * T.n_comms : 0u));
-  unsigned short* s_num = reinterpret_cast<unsigned short*>(s_p + CHUNK);
   const u32 tid = threadIdx.x;
   if (tid < a.n_buckets) {
     const u32 o = a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
@@ -307,6 +308,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       }
     }
   };
+  u32* round_row = a.rounds + ((u64)a.round0 + (u64)blockIdx.x * a.per_group) * a.n_buckets + tid;      // used below n_buckets only
   load_round(i_begin, r, c, sq, op, nb, te, tx);
   wait_vector_memory();
   for (u64 base = i_begin; base < i_end; base += CHUNK) {        // uniform over the workgroup
@@ -357,17 +359,17 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       u64 p = (u64)a.tail + at[u];
       if (p >= a.cap) p -= a.cap;
       s_p[q] = (u32)p;
-      s_num[q] = (unsigned short)((u32)u * THREADS + tid);
       s_key[q] = key[u];
       uint4 row;
       if (!pack_row(te[u], tx[u], nb[u], op[u], ref, (u32)p, &row)) {
         a.win_wide[3 * p] = te[u]; a.win_wide[3 * p + 1] = tx[u]; a.win_wide[3 * p + 2] = (i64)nb[u];
       }
+      row.y |= ((u32)u * THREADS + tid) << ROW_CELL_SHIFT;
       s_row[q] = row;
     }
     __syncthreads();
     wait_vector_memory();              // the next round's columns; the stores below have the next round's time
-    const u32 total = s_total, num0 = a.seqno0 + (u32)base;
+    const u32 total = s_total;
     // Pieces of a line that this round writes completely leave with the streaming hint: they do not stay in
     // the L2, where they would displace the partially written lines at the buckets' frontiers before the
     // next round completes them.
@@ -387,16 +389,19 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
         const bool full = q >= o && q + 15 - o < total && (s_p[q - o] == D - o) && (s_p[q + 15 - o] == D + 15 - o);
         if (full) __builtin_nontemporal_store(s_key[q], out_key + D);
         else out_key[D] = s_key[q];
-        a.win_arrival[D] = num0 + s_num[q];
       }
     }
-    if (tid < a.n_buckets) s_start[tid] = s_off[tid];
+    if (tid < a.n_buckets) { *round_row = s_start[tid]; s_start[tid] = s_off[tid]; }
+    round_row += a.n_buckets;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       r[u] = nr[u]; c[u] = nc[u]; sq[u] = nsq[u]; op[u] = nop[u]; nb[u] = nnb[u]; te[u] = nte[u]; tx[u] = ntx[u];
     }
   }
+  // rounds that this workgroup did not need: they start where it ends
+  for (u32 k = (u32)((i_end > i_begin ? i_end - i_begin + CHUNK - 1 : 0) / CHUNK); k < a.per_group; ++k, round_row += a.n_buckets)
+    if (tid < a.n_buckets) *round_row = s_start[tid];
   ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a, s_rng, T.n_comms);
 }
 // a batch without records: its header names its place in the window
@@ -405,6 +410,18 @@ __global__ __launch_bounds__(256) void k_ingest_empty(IngestArgs a, u32 n_comms)
   if (blockIdx.x == 0 && threadIdx.x == 0) put_header(a, 0);
 }
 
+// One 1,024-thread workgroup per compute unit; four counting workgroups per placement workgroup where a batch is large
+// enough, one (and the scan of the counts without a launch of its own) otherwise.
+IngestShape ingest_shape(uint64_t n) {
+  IngestShape s = {0, 0, 1, 0};
+  if (n == 0) return s;
+  s.groups = (uint32_t)std::min<uint64_t>((n + INGEST_ROUND - 1) / INGEST_ROUND, 256);
+  s.hist_split = n >= (1u << 23) ? 4 : 1;
+  const uint64_t unit = 256ull * s.hist_split;
+  s.chunk = ((n + s.groups - 1) / s.groups + unit - 1) / unit * unit;
+  s.per_group = (uint32_t)((s.chunk + INGEST_ROUND - 1) / INGEST_ROUND);
+  return s;
+}
 void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology& T, const KeyFormat& kf) {
   IngestArgs a = a_in;
   const size_t range_lds = a.range ? (size_t)16 * T.n_comms : 0;
@@ -427,12 +444,9 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     hipLaunchKernelGGL(k_ingest<256>, dim3((u32)g), dim3(256), range_lds, st, a, T, kf);
     return;
   }
-  // one 1,024-thread workgroup per compute unit; four counting workgroups per placement workgroup where a batch is
-  // large enough, one (and the scan of the counts without a launch of its own) otherwise
-  const u64 g = std::min<u64>((a.n + 2047) / 2048, 256);
-  a.hist_split = a.n >= (1u << 23) ? 4 : 1;
-  const u64 unit = 256ull * a.hist_split;
-  a.chunk = ((a.n + g - 1) / g + unit - 1) / unit * unit;
+  const IngestShape shape = ingest_shape(a.n);
+  const u64 g = shape.groups;
+  a.hist_split = shape.hist_split; a.chunk = shape.chunk; a.per_group = shape.per_group;
   const u32 g_hist = (u32)(g * a.hist_split);
   hipLaunchKernelGGL(k_ingest_hist, dim3(g_hist), dim3(256), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
   if (a.n_buckets * g_hist > INGEST_SCAN_WORDS) {
@@ -440,7 +454,7 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
   // the membership rows go to LDS when they fit beside the staging area
-  const size_t stage_bytes = (size_t)2048 * (16 + 8 + 4 + 2) + range_lds;
+  const size_t stage_bytes = (size_t)INGEST_ROUND * (16 + 8 + 4) + range_lds;
   if (T.rank_memb4 && (u64)T.n_ranks * 16 + stage_bytes <= 156 * 1024)
     hipLaunchKernelGGL((k_ingest_staged<1024, true>), dim3((u32)g), dim3(1024), stage_bytes + (size_t)T.n_ranks * 16, st, a, T, kf);
   else
@@ -997,18 +1011,13 @@ void launch_alert_candidates(hipStream_t st, const AlertArgs& a, uint32_t n_aler
 }
 
 // ------------------------------------------------------------------------------------------
-// position of every sorted record in the window's arrival order: its slot's distance from the window's first slot, or,
-// where batches are placed by bucket, its arrival number minus that of the window's oldest record (modulo 2^32)
-__global__ __launch_bounds__(256) void k_perm(const u32* __restrict__ idx, const u32* __restrict__ arrival, u32 n, u32 seqno_head,
-                                              u32 head, u32 cap, u32* perm) {
+// position of every sorted record in the window's arrival order
+__global__ __launch_bounds__(256) void k_perm(const u32* __restrict__ idx, WindowRows win, u32 n, u32* perm) {
   const u32 j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  const u32 p = idx[j];
-  perm[j] = arrival ? arrival[p] - seqno_head : (p >= head ? p - head : p + cap - head);
+  if (j < n) perm[j] = arrival_of_slot(win, idx[j]);
 }
-void launch_perm(hipStream_t st, const uint32_t* idx, const uint32_t* arrival, uint32_t n, uint32_t seqno_head, uint32_t head,
-                 uint32_t cap, uint32_t* perm) {
-  if (n) hipLaunchKernelGGL(k_perm, dim3((n + 255) / 256), dim3(256), 0, st, idx, arrival, n, seqno_head, head, cap, perm);
+void launch_perm(hipStream_t st, const uint32_t* idx, const WindowRows& win, uint32_t n, uint32_t* perm) {
+  if (n) hipLaunchKernelGGL(k_perm, dim3((n + 255) / 256), dim3(256), 0, st, idx, win, n, perm);
 }
 
 }  // namespace ccld

@@ -14,7 +14,6 @@ struct IngestArgs {
   uint64_t* win_key;
   uint4* win_row;
   int64_t* win_wide;         // [cap][3]
-  uint32_t* win_arrival;     // [cap] arrival number (modulo 2^32) of each slot; only where batches are placed by bucket
   uint32_t tail, cap;
   BatchMeta *meta, *meta_next;   // this batch's header and the one that the next batch will use
   uint32_t* table;           // [n_buckets][workgroups] records per communicator bucket and workgroup
@@ -23,12 +22,17 @@ struct IngestArgs {
   uint64_t* scratch_total;
   uint32_t n_buckets;
   int bshift;                // bucket = comm >> bshift
-  uint32_t seqno0;           // arrival number of the batch's first record
+  uint32_t* rounds;          // [rounds][n_buckets] of the window's batches; this batch's start at round0
+  uint32_t round0;
   uint64_t *range, *range_next;  // [n_comms][2] per communicator: largest operation counter, largest complement of one; null:
                              // not wanted.  At most INGEST_RANGE_COMMS communicators.
   uint64_t chunk;            // records per placement workgroup (a multiple of 256 * hist_split)
   uint32_t hist_split;       // counting workgroups per placement workgroup
+  uint32_t per_group;        // rounds per placement workgroup
 };
+// How a batch that is placed by bucket is dealt out: workgroups, records and rounds of each, counting workgroups per workgroup
+struct IngestShape { uint32_t groups, per_group, hist_split; uint64_t chunk; };
+IngestShape ingest_shape(uint64_t n);
 constexpr uint32_t INGEST_BLOCKS = 1024;
 constexpr uint32_t INGEST_STAGED_BUCKETS = 256;   // most buckets the LDS-regrouped placement kernel handles
 constexpr uint32_t INGEST_RANGE_COMMS = 3584;     // most communicators whose counter ranges fit the counting kernel's LDS
@@ -51,8 +55,6 @@ struct SegArgs {
   uint8_t* rec_flag;         // (optional on the grid placement)
   int64_t *lag_e, *lag_x;    // optional per-record outputs
   uint32_t* perm;            // optional, grid placement only (a sorted window's comes from launch_perm)
-  const uint32_t* arrival;   // arrival number of each window slot (null: slots are in order of arrival), and that of the
-  uint32_t seqno_head;       //   window's oldest record
   int64_t* flag_lag;         // [2][cap_n] lags of flagged records: by sorted position; on the grid placement with flag_pos
   uint32_t* flag_pos;        // grid placement: cell | kind << 16 of the flagged records of each fine bucket
   uint64_t cap_n;
@@ -158,7 +160,6 @@ struct AlertArgs {
 void launch_alert_select(hipStream_t st, const AlertArgs& a);
 void launch_alert_candidates(hipStream_t st, const AlertArgs& a, uint32_t n_alert);
 
-void launch_perm(hipStream_t st, const uint32_t* idx, const uint32_t* arrival, uint32_t n, uint32_t seqno_head, uint32_t head,
-                 uint32_t cap, uint32_t* perm);
+void launch_perm(hipStream_t st, const uint32_t* idx, const WindowRows& win, uint32_t n, uint32_t* perm);
 
 }  // namespace ccld

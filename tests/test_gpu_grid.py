@@ -75,3 +75,38 @@ def test_grid_edges(kind, missing, wide, far_ns, cap):
         prev = cols
     an.close()
     assert flags > 0
+
+
+def _rounds(rng, n_comms, size, seq0, rounds, step, disjoint):
+    """columns of `rounds` collectives of every communicator in a random order, three records left out"""
+    comm, seq, slot = (x.ravel() for x in np.meshgrid(np.arange(n_comms), np.arange(rounds), np.arange(size), indexing="ij"))
+    keep = rng.permutation(comm.size)[3:]
+    comm, seq, slot = comm[keep], seq[keep], slot[keep]
+    te = T0 + (seq0 + seq) * 1_000_000 + rng.integers(0, 500_000, keep.size)
+    return {"rank": (slot + size * comm * disjoint).astype(np.uint32), "comm": comm.astype(np.uint32),
+            "seq": (seq0 + seq * step).astype(np.uint64), "op": np.ones(keep.size, np.uint8),
+            "bytes": np.full(keep.size, 1 << 20, np.uint64), "t_enter": te, "t_exit": te + rng.integers(1, 400_000, keep.size)}
+
+
+@pytest.mark.parametrize("step", [1, 1000], ids=["grid", "sorted"])
+@pytest.mark.parametrize("disjoint", [1, 0], ids=["lookup_in_lds", "many_comms_per_rank"])
+def test_order_of_arrival_over_many_ingest_rounds(disjoint, step):
+    """batches placed by communicator bucket: one round and many rounds per workgroup, a window that slides past one"""
+    from paper_2605_04478_amd import ccld
+    n_comms, size = 40, 16
+    topo = tg.make_topology(size * (n_comms if disjoint else 1),
+                            [[r + size * c * disjoint for r in range(size)] for c in range(n_comms)])
+    rng = np.random.default_rng(3 + disjoint)
+    batches, seq0 = [], 100
+    for rounds in (1100, 2, 830, 3, 900):
+        batches.append(_rounds(rng, n_comms, size, seq0, rounds, step, disjoint))
+        seq0 += rounds * step
+    an = ccld.Analyzer(topo, max_window_records=6_000_000, max_batch_records=704_000, window_batches=2)
+    prev = None
+    for b in batches:
+        an.ingest(an.to_device(b))
+        win = b if prev is None else {k: np.concatenate([prev[k], b[k]]) for k in b}
+        res = an.analyze_window(FAR, n_records=len(win["rank"]), per_record=True)
+        assert np.array_equal(res.per_record()["perm"], np.lexsort((win["rank"], win["seq"], win["comm"])))
+        prev = b
+    an.close()
