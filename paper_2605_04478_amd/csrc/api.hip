@@ -202,6 +202,8 @@ void plan(ccld_ctx* c, const ccld_params* p, const ccld_topology* t, uint64_t n_
   for (uint32_t k = 0; k < t->n_comms; ++k) max_size = std::max(max_size, t->size[k]);
   const int mb = bits_for_host(max_size - 1), cb = bits_for_host(t->n_comms - 1);
   c->max_comm_size = max_size;
+  c->long_classes = 0;
+  for (uint32_t k = 0; k < t->n_comms; ++k) if (t->size[k] > 64) c->long_classes |= t->size[k] <= 128 ? 1u : t->size[k] <= 256 ? 2u : t->size[k] <= 512 ? 4u : 8u;
   c->kf.mb = mb; c->kf.cb = cb; c->kf.sb = 64 - mb - cb;
   const uint64_t N = std::max<uint64_t>(cap, 1), W = p->window_batches;
   c->grid_capable = cap > 0 && max_size <= GRID_B && t->n_comms <= GRID_MAX_COMMS && (W + 2) * t->n_comms * 16 <= (64ull << 20);
@@ -615,7 +617,7 @@ static SegArgs seg_args(ccld_ctx* c, int64_t now_ns, const ccld_window_result* o
   sa.lag_e = o->lag_enter; sa.lag_x = o->lag_exit; sa.flag_lag = c->flag_lag; sa.cap_n = c->cap;
   sa.counters = c->counters;
   sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
-  sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size;
+  sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size; sa.long_classes = c->long_classes;
   sa.gcode = c->gcode; sa.range_c = c->range_c;
   const uint32_t n_meta = c->p.window_batches + 2;
   sa.win.row = c->win_row; sa.win.wide = c->win_wide; sa.win.meta = c->batch_meta; sa.win.n_meta = n_meta;

@@ -163,6 +163,7 @@ struct ccld_ctx {
   ccld::GroupState* gstate;           // [n_comms][GROUP_SLOTS]
   uint64_t* counters;                 // [CNT_COUNT] device
   uint32_t max_comm_size;             // members of the largest communicator
+  uint32_t long_classes;              // which sizes beyond 64 members there are (SegArgs)
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging
   uint64_t ticket;                    // number of the latest report that the device was asked for

@@ -1209,17 +1209,18 @@ __global__ __launch_bounds__(256) void k_seg_group_listed(SegArgs a) {
 // x member slot), which puts every collective's records side by side in rank order with empty cells where a member has
 // no record; the wavefronts then take the collectives 64 / G at a time.  The kernel leaves, beside the table, the row
 // of every cell (2 bytes), which the chains and the alerts look records up by, and the bucket's flagged records.
+template <u32 ROUNDS>                      // most rounds of a bucket
 struct GridShared {
   uint4 row[GRID_B];                     // rows by cell; y bits 16-26: number of the row in its bucket
   u32 pres[GRID_B / 32];
-  unsigned short pre[GRID_B];            // records of the bucket before each of its rounds
+  unsigned short pre[ROUNDS];            // records of the bucket before each of its rounds
   u32 wave[8];
   GridFlags flags;
 };
 // Places bucket f's rows in LDS.  Returns status bits: a cell taken twice or more rows than cells (duplicate keys), a
 // round without any record (a hole in the grid).  Ends with a barrier.
-template <int THREADS>
-__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, GridShared& S) {
+template <int THREADS, u32 ROUNDS>
+__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, GridShared<ROUNDS>& S) {
   constexpr u32 U = GRID_B / THREADS;
   const u32 tid = threadIdx.x, cells = D.K * D.size;
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
@@ -1382,7 +1383,7 @@ __device__ __forceinline__ u32 first_bit(u64 m) { return (u32)__builtin_ctzll(m)
 // every lane does only what its own record needs.
 template <int G>
 __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
-                                            GridShared& S, u32 lane, u32 wave, u32 n_waves) {
+                                            GridShared<GRID_B>& S, u32 lane, u32 wave, u32 n_waves) {
   constexpr int SPW = CCLD_WAVE / G;
   constexpr u32 LIM = 1u << 30;
   const u32 K = D.K, size = D.size;
@@ -1495,7 +1496,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
 
 constexpr int GRID_THREADS = 256;
 __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
-  __shared__ GridShared S;
+  __shared__ GridShared<GRID_B> S;
   __shared__ u32 s_slot[CCLD_WAVE];
   constexpr u32 NW = GRID_THREADS / CCLD_WAVE;
   const u32 f = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
@@ -1610,23 +1611,132 @@ __device__ __forceinline__ i64 mad_of(At at, u32 nd) {
   if (d - lo > 0) { const i64 u = above(d - lo - 1); r = u > r ? u : r; }
   return r;
 }
-template <int E>
-__device__ __forceinline__ i32 kth_multi32(const i32 (&v)[E], u32 k) {
-  i32 sel = v[0];
-#pragma unroll
-  for (int r = 1; r < E; ++r) if ((k >> 6) == (u32)r) sel = v[r];
-  return __shfl(sel, (int)(k & 63), CCLD_WAVE);
-}
+// most rounds of a fine bucket of such a communicator
+constexpr u32 LONG_ROUNDS = GRID_B / (SEG_WAVE_MAX + 1);
+using LongShared = GridShared<LONG_ROUNDS>;
 
-// One wavefront, one collective of up to 64 E members.
+// One wavefront, one collective of up to 64 E members, on 32-bit offsets from its first record's arrival.  False, and nothing
+// done, if some time does not fit them.
+template <int E>
+__device__ __forceinline__ bool long_wave32(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
+                                            LongShared& S, u32 (&mine)[E], LongRow* out, u32 k, u32 lane) {
+  constexpr u32 LIM = 1u << 30;
+  const u32 size = D.size;
+  u64 pm[E], dm[E];                 // the records present, and those of finished operations
+  u32 n = 0, first_slot = 0;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const u32 slot = r * CCLD_WAVE + lane, cell = k * size + (slot < size ? slot : 0u);
+    pm[r] = ballot64(slot < size && ((S.pres[cell >> 5] >> (cell & 31)) & 1u));
+    if (n == 0 && pm[r]) first_slot = r * CCLD_WAVE + (u32)__builtin_ctzll(pm[r]);
+    n += (u32)__popcll(pm[r]);
+  }
+  const uint4 lead = S.row[k * size + first_slot];
+  i32 er[E];
+  u32 z[E], nd = 0;
+  bool wide = false, inc = false;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const u32 slot = r * CCLD_WAVE + lane, cell = k * size + (slot < size ? slot : 0u);
+    const uint4 v = S.row[cell];
+    const bool valid = (pm[r] >> lane) & 1u;
+    const u64 diff = (((u64)v.y << 32) | v.x) - (((u64)lead.y << 32) | lead.x);
+    er[r] = (i32)(u32)diff; z[r] = v.z;
+    const bool done = valid && v.z != ROW_INFLIGHT;
+    wide |= (valid && ((((u32)(diff >> 32) ^ (u32)(er[r] >> 31)) & 0xFFFu) != 0 || (u32)er[r] + LIM >= 2 * LIM)) ||
+            (done && (v.z >= LIM || (i32)((u32)er[r] + v.z) >= (i32)LIM));
+    inc |= valid && (v.w != lead.w || ((v.y ^ lead.y) & ROW_SAME_MASK));
+    dm[r] = ballot64(done);
+    nd += (u32)__popcll(dm[r]);
+  }
+  if (ballot64(wide)) return false;
+  const bool incons = ballot64(inc) != 0;
+  const u32 ninfl = n - nd, kl = nd ? nd - 1 : 0, km = kl / 2;
+  const i64 ref = wref + t44_diff(row_t44(lead), (u64)wref);
+  // T_min / T_max with the first slot, i.e. the smallest rank, that attains them
+  u32 dmin = ~0u, dmax = 0, rmin = CCLD_WAVE * E, rmax = CCLD_WAVE * E;
+  i32 imin = 0x7FFFFFFF;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const bool done = (dm[r] >> lane) & 1u, valid = (pm[r] >> lane) & 1u;
+    mine[r] += valid ? 1u : 0u;
+    if (done) { dmin = z[r] < dmin ? z[r] : dmin; dmax = z[r] > dmax ? z[r] : dmax; }
+    else if (valid) imin = er[r] < imin ? er[r] : imin;
+  }
+  dmin = reduce_u32<64, false>(dmin); dmax = reduce_u32<64, true>(dmax);
+#pragma unroll
+  for (int r = E - 1; r >= 0; --r) {
+    const u64 lo = ballot64(z[r] == dmin) & dm[r], hi = ballot64(z[r] == dmax) & dm[r];
+    if (lo) rmin = r * CCLD_WAVE + (u32)__builtin_ctzll(lo);
+    if (hi) rmax = r * CCLD_WAVE + (u32)__builtin_ctzll(hi);
+  }
+  i32 st[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {                  // 0 arrival, 1 completion
+    if (nd == 0) break;
+    i32 v[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = (dm[r] >> lane) & 1u ? (w ? (i32)((u32)er[r] + z[r]) : er[r]) : REL_NONE;
+    sort_multi32<E>(v, lane);
+    auto kth = [&](u32 q) -> i32 {               // q is the same in every lane
+      i32 sel = v[0];
+#pragma unroll
+      for (int r = 1; r < E; ++r) if ((q >> 6) == (u32)r) sel = v[r];
+      return __builtin_amdgcn_readlane(sel, (int)(q & 63));
+    };
+    st[w][0] = kth(0); st[w][1] = kth(km); st[w][2] = kth(kl);
+    st[w][3] = (i32)mad_of([&](u32 i) -> i64 { return (i64)kth(i); }, nd);
+  }
+  const u64 hb = row_bytes(lead);
+  const u32 hop = row_op(lead);
+  const bool complete = n == size && ninfl == 0;
+  const bool barrier = hop == CCLD_OP_ALLREDUCE && hb < (u64)a.barrier_bytes;
+  const bool usable = complete && !incons && !barrier;
+  if (ninfl) imin = (i32)(reduce_u32<64, false>((u32)imin ^ 0x80000000u) ^ 0x80000000u);
+  if (lane == 0) {
+    const u32* ms = a.members_sorted + a.member_off[D.comm];
+    LongRow& R = out[k];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      R.stat[w][0] = ref + st[w][0]; R.stat[w][1] = ref + st[w][1]; R.stat[w][2] = ref + st[w][2]; R.stat[w][3] = st[w][3];
+    }
+    R.imin = ninfl ? ref + imin : T_INFLIGHT;
+    R.dmin = nd ? (i64)dmin : INT64_MAX; R.dmax = nd ? (i64)dmax : INT64_MIN;
+    R.rmin = nd ? ms[rmin] : 0xFFFFFFFFu; R.rmax = nd ? ms[rmax] : 0xFFFFFFFFu;
+    R.bytes = hb; R.n = n; R.ninfl = ninfl; R.op = hop;
+    R.state = (complete ? CCLD_SEG_COMPLETE : 0) | (!incons ? CCLD_SEG_CONSISTENT : 0) | (barrier ? CCLD_SEG_BARRIER : 0) |
+              (usable ? CCLD_SEG_USABLE : 0);
+  }
+  const bool per_record = a.rec_flag || a.lag_e || a.lag_x || a.perm;
+  u32 before = rec0 + S.pre[k];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const bool valid = (pm[r] >> lane) & 1u;
+    i32 le = 0, lx = 0;
+    u32 f = 0;
+    if (usable) {
+      le = er[r] - st[0][1]; lx = (i32)((u32)er[r] + z[r]) - st[1][1];
+      if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, st[0][3])) f |= CCLD_FLAG_LATE_ENTER;
+      if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, st[1][3])) f |= CCLD_FLAG_LATE_EXIT;
+    }
+    if (valid && (f || per_record)) {
+      const u32 cell = k * size + r * CCLD_WAVE + lane, j = before + mbcnt64(pm[r]);
+      if (a.perm) a.perm[j] = grid_arrival(a, d, D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+      grid_put_record(a, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
+    }
+    before += (u32)__popcll(pm[r]);
+  }
+  return true;
+}
+// The same with times of any spread.
 template <int E>
 __device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
-                                          GridShared& S, u32* s_slot, LongRow* out, u32 k, u32 lane) {
+                                          LongShared& S, u32 (&mine)[E], LongRow* out, u32 k, u32 lane) {
   const u32 size = D.size, *ms = a.members_sorted + a.member_off[D.comm];
   i64 e[E], x[E];
   u32 n = 0, ninfl = 0, before[E];
-  bool valid[E], inc = false, wide = false;
-  i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN, ref = 0;
+  bool valid[E], inc = false;
+  i64 imin = T_INFLIGHT, dmin = INT64_MAX, dmax = INT64_MIN;
   u32 rmin = 0xFFFFFFFFu, rmax = 0xFFFFFFFFu, hop = 0;
   u64 hb = 0;
 #pragma unroll
@@ -1640,14 +1750,14 @@ __device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, c
     e[r] = rec.t_enter; x[r] = rec.t_exit;
     if (n == 0 && pm) {        // the first record of the collective
       const int fl = (int)__builtin_ctzll(pm);
-      hb = shfl_u64(rec.bytes, fl); hop = __shfl(rec.op, fl, CCLD_WAVE); ref = shfl_i64(e[r], fl);
+      hb = shfl_u64(rec.bytes, fl); hop = __shfl(rec.op, fl, CCLD_WAVE);
     }
     n += (u32)__popcll(pm);
     inc |= valid[r] && (rec.bytes != hb || rec.op != hop);
     const bool done = valid[r] && x[r] != T_INFLIGHT;
     ninfl += (u32)__popcll(ballot64(valid[r] && !done));
     if (valid[r]) {
-      atomicAdd(&s_slot[slot], 1u);
+      ++mine[r];
       if (a.perm) a.perm[rec0 + S.pre[k] + before[r]] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
       if (!done) {
         imin = e[r] < imin ? e[r] : imin;
@@ -1656,9 +1766,6 @@ __device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, c
         const u32 rank = ms[slot];
         if (du < dmin || (du == dmin && rank < rmin)) { dmin = du; rmin = rank; }
         if (du > dmax || (du == dmax && rank < rmax)) { dmax = du; rmax = rank; }
-        constexpr i64 LIM = (i64)1 << 30;
-        const u64 oe = (u64)(e[r] - ref) + (u64)LIM, ox = (u64)(x[r] - ref) + (u64)LIM;
-        wide |= oe >= 2 * (u64)LIM || ox >= 2 * (u64)LIM;
       }
     }
   }
@@ -1668,25 +1775,15 @@ __device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, c
   reduce_dur<64, true>(dmax, rmax);
   const u32 nd = n - ninfl, km = nd ? (nd - 1) / 2 : 0, kl = nd ? nd - 1 : 0;
   i64 st_min[2] = {0, 0}, st_med[2] = {0, 0}, st_max[2] = {0, 0}, st_mad[2] = {0, 0};
-  const bool rel = ballot64(wide) == 0;
 #pragma unroll 1
   for (int w = 0; w < 2; ++w) {                  // 0 arrival, 1 completion
     if (nd == 0) break;
-    if (rel) {
-      i32 v[E];
+    i64 v[E];
 #pragma unroll
-      for (int r = 0; r < E; ++r) v[r] = x[r] != T_INFLIGHT ? (i32)((w ? x[r] : e[r]) - ref) : REL_NONE;
-      sort_multi32<E>(v, lane);
-      st_min[w] = ref + kth_multi32<E>(v, 0); st_med[w] = ref + kth_multi32<E>(v, km); st_max[w] = ref + kth_multi32<E>(v, kl);
-      st_mad[w] = mad_of([&](u32 i) -> i64 { return (i64)kth_multi32<E>(v, i); }, nd);
-    } else {
-      i64 v[E];
-#pragma unroll
-      for (int r = 0; r < E; ++r) v[r] = x[r] != T_INFLIGHT ? (w ? x[r] : e[r]) : T_INFLIGHT;
-      sort_multi<E>(v, lane);
-      st_min[w] = kth_multi<E>(v, 0); st_med[w] = kth_multi<E>(v, km); st_max[w] = kth_multi<E>(v, kl);
-      st_mad[w] = mad_of_sorted<E>(v, nd, km);
-    }
+    for (int r = 0; r < E; ++r) v[r] = x[r] != T_INFLIGHT ? (w ? x[r] : e[r]) : T_INFLIGHT;
+    sort_multi<E>(v, lane);
+    st_min[w] = kth_multi<E>(v, 0); st_med[w] = kth_multi<E>(v, km); st_max[w] = kth_multi<E>(v, kl);
+    st_mad[w] = mad_of_sorted<E>(v, nd, km);
   }
   const bool complete = n == size && ninfl == 0;
   const bool barrier = hop == CCLD_OP_ALLREDUCE && hb < (u64)a.barrier_bytes;
@@ -1713,14 +1810,30 @@ __device__ __forceinline__ void long_wave(const SegArgs& a, const GridArgs& d, c
   }
 }
 
-// A workgroup takes the fine buckets on the list in turn.  Collectives of up to 512 members go to a wavefront each; the
-// larger ones (at most three in a bucket) are taken by the whole workgroup, one after the other: their times are sorted
-// in LDS, the median of the deviations is selected from the sorted sequence.
-constexpr u32 LONG_ROUNDS = GRID_B / (SEG_WAVE_MAX + 1);        // most rounds of such a bucket
-__global__ __launch_bounds__(SEG_THREADS) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
-  __shared__ GridShared S;
-  __shared__ i64 s_v[GRID_B];                  // the larger collectives' sort
-  __shared__ u32 s_slot[GRID_B];
+template <int E>
+__device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref, LongShared& S,
+                                            u32* s_slot, LongRow* out, u32 lane, u32 wave, u32 n_waves) {
+  u32 mine[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) mine[r] = 0;
+  for (u32 k = wave; k < D.K; k += n_waves)
+    if (!long_wave32<E>(a, d, D, rec0, wref, S, mine, out, k, lane)) long_wave<E>(a, d, D, rec0, wref, S, mine, out, k, lane);
+#pragma unroll
+  for (int r = 0; r < E; ++r) if (mine[r]) atomicAdd(&s_slot[r * CCLD_WAVE + lane], mine[r]);
+}
+
+// A workgroup takes the fine buckets on the list in turn.  E: those whose collectives go to a wavefront each, E members per
+// lane (up to 64 E and more than half as many); E = 0: the larger ones (at most three in a bucket), taken by the whole
+// workgroup one after the other: their times are sorted in LDS, the median of the deviations is selected from the sorted
+// sequence.  A kernel each, because the sort's LDS would leave the wavefronts half of their occupancy (four workgroups per
+// compute unit without it), and the registers of eight members per lane those with two.
+template <int E>
+__global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+  constexpr bool WAVES = E > 0;
+  constexpr u32 MEMBERS = WAVES ? E * CCLD_WAVE : GRID_B, ABOVE = E == 0 ? SEG_MULTI_MAX : E * CCLD_WAVE / 2;
+  __shared__ LongShared S;
+  __shared__ i64 s_v[WAVES ? 1 : GRID_B];      // the larger collectives' sort
+  __shared__ u32 s_slot[MEMBERS];
   __shared__ LongRow s_out[LONG_ROUNDS];
   __shared__ TeamAcc s_acc;
   __shared__ u32 s_first;
@@ -1733,15 +1846,12 @@ __global__ __launch_bounds__(SEG_THREADS) void k_grid_long(SegArgs a, GridArgs d
     const u32 f = d.long_list[ent];
     const FineDesc D = d.desc[f];
     const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size, K = D.K;
+    if (size <= ABOVE || size > MEMBERS) continue;
     for (u32 i = tid; i < size; i += SEG_THREADS) s_slot[i] = 0;
     const u64 bad = grid_place<SEG_THREADS>(d, D, cnt, S);
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
-    if (size <= (u32)SEG_MULTI_MAX) {
-      for (u32 k = wave; k < K; k += NW) {
-        if (size <= 128) long_wave<2>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
-        else if (size <= 256) long_wave<4>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
-        else long_wave<8>(a, d, D, rec0, wref, S, s_slot, s_out, k, lane);
-      }
+    if constexpr (WAVES) {
+      long_rounds<E>(a, d, D, rec0, wref, S, s_slot, s_out, lane, wave, NW);
       __syncthreads();
     } else {
       for (u32 k = 0; k < K; ++k) {
@@ -1906,7 +2016,11 @@ static void launch_seg_listed(hipStream_t st, const SegArgs& a) {
 
 void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks) {
   if (fine_bound) hipLaunchKernelGGL(k_grid_stats, dim3(fine_bound), dim3(GRID_THREADS), 0, st, a, d, blame, n_ranks);
-  if (a.max_size > (uint32_t)SEG_WAVE_MAX) hipLaunchKernelGGL(k_grid_long, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
+  // as many workgroups as are resident at once, which take the listed buckets in turn
+  if (a.long_classes & 1) hipLaunchKernelGGL(k_grid_long<2>, dim3(1024), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
+  if (a.long_classes & 2) hipLaunchKernelGGL(k_grid_long<4>, dim3(1024), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
+  if (a.long_classes & 4) hipLaunchKernelGGL(k_grid_long<8>, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
+  if (a.long_classes & 8) hipLaunchKernelGGL(k_grid_long<0>, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
 }
 
 void launch_seg_analyze(hipStream_t st, const SegArgs& a) {

@@ -66,6 +66,7 @@ struct SegArgs {
   uint32_t kmad_num, kmad_den, barrier_bytes;
   int64_t now_ns, hang_threshold_ns;             // collectives in flight for longer are counted in counters[CNT_NALERT]
   uint32_t max_size;         // members of the largest communicator (host-side: which size classes can occur)
+  uint32_t long_classes;     // which there are: bit 0 65 to 128 members, 1 up to 256, 2 up to 512, 3 more
   // (op, size class) code and T_max - T_min of every collective, for the group stage; a collective that takes
   // no part gets NO_GROUP
   uint16_t* gcode;
