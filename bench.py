@@ -335,8 +335,8 @@ def main() -> int:
     #  the histogram re-reads, the head marking and the grid partition are this implementation's own passes:
     #  no algorithmic bytes
     # "layout": what this implementation's data layout moves:
-    #  ingest       reads the 41-byte SoA record and the communicator once more, writes an 8-byte key, a 4-byte
-    #               arrival index and a 16-byte payload row
+    #  ingest       reads the 41-byte SoA record and the communicator once more, writes an 8-byte key and
+    #               a 16-byte payload row
     #  dense_partition  (window placed on the grid) reads the key and the row, writes the row
     #  sort_hist    (window sorted) reads the 8-byte key once per pass
     #  sort_scatter as above; when key bits + index bits <= 64 the passes move one packed word (16 B) and the
@@ -352,7 +352,7 @@ def main() -> int:
     grid = prof["dense_partition"][1] > 0 and not prof["sort_scatter"][1]
     packed = passes >= 2 and key_bits + bl(n - 1) <= 64      # key and index travel as one 64-bit word
     scatter_bytes = (16.0 * (passes - 1) + 20.0) if packed else (20.0 + 24.0 * (passes - 1))
-    ingest_bytes = n * (41.0 + 4.0 + 8.0 + 4.0 + 16.0)
+    ingest_bytes = n * (41.0 + 4.0 + 8.0 + 16.0)
     if grid:
         alg = {"ingest": n * 24.0, "segments": n * 25.0 + n_seg * 104.0}
         layout = {"ingest": ingest_bytes, "dense_partition": n * 40.0, "segments": n * (16.0 + 2.0) + n_seg * (21 * 8.0 + 16.0)}
