@@ -1379,8 +1379,8 @@ __device__ __forceinline__ u32 count_bits(u64 m) { return (u32)__builtin_popcoun
 __device__ __forceinline__ u32 first_bit(u32 m) { return (u32)__builtin_ctz(m); }      // m != 0
 __device__ __forceinline__ u32 first_bit(u64 m) { return (u32)__builtin_ctzll(m); }
 
-// Bound by the vector instructions of this loop (82 % of the cycles at 388 per 64 records when it was first counted), so
-// every lane does only what its own record needs.
+// Bound by the vector instructions of this loop, so every lane does only what its own record needs: 252 instead of 388 per 64
+// records over the whole kernel, 82M records in 8.4M collectives 1,053 -> 822 us (3.0 GB: 3.7 TB/s).
 template <int G>
 __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
                                             GridShared<GRID_B>& S, u32 lane, u32 wave, u32 n_waves) {
@@ -1826,7 +1826,8 @@ __device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d,
 // lane (up to 64 E and more than half as many); E = 0: the larger ones (at most three in a bucket), taken by the whole
 // workgroup one after the other: their times are sorted in LDS, the median of the deviations is selected from the sorted
 // sequence.  A kernel each, because the sort's LDS would leave the wavefronts half of their occupancy (four workgroups per
-// compute unit without it), and the registers of eight members per lane those with two.
+// compute unit without it), and the registers of eight members per lane those with two.  Bound by the chain of one collective
+// (two sorts, two selections): 4M records in collectives of 128 members 150 -> 106 us.
 template <int E>
 __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   constexpr bool WAVES = E > 0;
