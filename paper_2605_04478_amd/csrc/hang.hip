@@ -57,6 +57,7 @@ struct HangArgs {
   // hang location of large grids: rows regrouped by region of 2^sb members
   ulonglong2* part_row;   // [n_cell]
   int sb;
+  int pb;                 // rates: the members of a region are taken 2^pb at a time
   u32 snap_inv;           // ceil(2^32 / n_snap)
 };
 
@@ -403,6 +404,7 @@ __global__ __launch_bounds__(256) void k_hang_scan(HangArgs a) {
 constexpr int SPLIT_CELL_BITS = 18;
 constexpr u32 SPLIT_REGIONS = 512;
 constexpr size_t SPLIT_LDS = 64000, RATE_LDS = 156000;      // LDS of a region: hang location, rates
+constexpr int RATE_PARTS = 3;                               // a region of rates is taken in up to 2^3 parts
 inline size_t rate_region_lds(u32 n_ch, u32 n_snap, int sb) {
   const u64 cells = (u64)n_ch * n_snap << sb;
   return cells * 16 + (32ull << sb) + (cells + 31) / 32 * 4;
@@ -998,18 +1000,25 @@ __global__ __launch_bounds__(256) void k_rate_pairs(HangArgs a) {
   }
 }
 // From the regrouped rows: a workgroup places the rows of its region in LDS by cell, then its wavefronts take the
-// series one by one.  The rows are read once and the grid never exists in memory.
+// series one by one.  The grid never exists in memory.  Where the cells of a whole region do not fit LDS, a workgroup takes
+// one part of its members and passes over the other rows: the parts of a region run side by side on one XCD (workgroups go
+// to the eight XCDs in turn), whose L2 has the rows then.  Up to eight parts: the grid in memory, which the others take, costs
+// about as much as reading the rows that often (4,096 ranks x 16 channels x 64 snapshots in four parts 545 -> 369 us per call).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_rate_region(HangArgs a) {
   extern __shared__ ulonglong2 s_cell[];                               // [cap] cells | sums of every member | bitmap
-  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE, reg = blockIdx.x;
-  const u32 per_member = a.n_ch * a.n_snap, cap = per_member << a.sb, words = (cap + 31) / 32, members = 1u << a.sb;
+  const int db = a.sb - a.pb;
+  const u32 part = (blockIdx.x >> 3) & ((1u << db) - 1);
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE, reg = db ? ((blockIdx.x >> 3) >> db) * 8 + (blockIdx.x & 7) : blockIdx.x;
+  const u32 per_member = a.n_ch * a.n_snap, room = per_member << a.sb, cap = per_member << a.pb, words = (cap + 31) / 32, members = 1u << a.pb;
+  const u32 cell0 = db ? part * cap : 0u;
+  if (reg >= a.n_regions || ((u64)reg << a.sb) + (db ? (u64)part << a.pb : 0) >= a.n_members) return;
   u64* s_sum = reinterpret_cast<u64*>(s_cell + cap);
   u32* s_bits = reinterpret_cast<u32*>(s_sum + 4 * members);
   __shared__ u32 s_cells;
-  const u64 p0 = (u64)reg << a.sb;
-  const u32 have = a.part_fill[reg], n = have < cap ? have : cap;
-  const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * cap;
+  const u64 p0 = ((u64)reg << a.sb) + (db ? (u64)part << a.pb : 0);
+  const u32 have = a.part_fill[reg], n = have < room ? have : room;
+  const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * room;
   for (u32 i = tid; i < words; i += THREADS) s_bits[i] = 0;
   for (u32 i = tid; i < 4 * members; i += THREADS) s_sum[i] = 0;
   if (tid == 0) s_cells = 0;
@@ -1020,11 +1029,15 @@ __global__ __launch_bounds__(THREADS) void k_rate_region(HangArgs a) {
     u64x2 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (i0 + u * THREADS < n) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS));
+      if (i0 + u * THREADS < n) {
+        const u64x2* row = reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS);
+        v[u] = db ? *row : __builtin_nontemporal_load(row);
+      }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (i0 + u * THREADS >= n) continue;
-      const u32 k = (u32)v[u].x & ((1u << SPLIT_CELL_BITS) - 1);
+      const u32 k = ((u32)v[u].x & ((1u << SPLIT_CELL_BITS) - 1)) - cell0;
+      if (k >= cap) continue;                                          // another part's
       s_cell[k] = make_ulonglong2(v[u].x >> SPLIT_CELL_BITS, v[u].y);
       atomicOr(&s_bits[k >> 5], 1u << (k & 31));
     }
@@ -1350,16 +1363,21 @@ static ccld_status check_hang_args(ccld_ctx* c, const ccld_snapshots* sn, uint64
 
 // The regions of a grid: false where its rows are not regrouped.  As many regions as one workgroup each keeps the chip
 // busy with (129 to 256; more cost the split pass an atomic each per round), as far as a region fits LDS.
-static bool split_regions(HangArgs& a, const HangScratch& S, size_t (*lds)(u32, u32, int), size_t lds_max) {
+// parts: the cells of a region may be taken in up to 2^parts passes over its rows.
+static bool split_regions(HangArgs& a, const HangScratch& S, size_t (*lds)(u32, u32, int), size_t lds_max, int parts) {
   const uint64_t per_member = (uint64_t)a.n_ch * a.n_snap;
   if (!S.split_row || !a.n_rows || a.n_cell >= (1ull << 31) || a.n_snap < 2 || a.n_snap > 16384 || a.n_ch > 1024) return false;
   int sb = 0;
   while (((a.n_members - 1) >> sb) >= SPLIT_REGIONS / 2) ++sb;
-  while (sb > 0 && ((per_member << sb) > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, sb) > lds_max)) --sb;
+  while (sb > 0 && (per_member << sb) > (1ull << SPLIT_CELL_BITS)) --sb;
+  int pb = sb;
+  while (pb > 0 && lds(a.n_ch, a.n_snap, pb) > lds_max) --pb;
+  // smaller regions rather than several parts, as far as the regions go
+  while (sb > pb && ((a.n_members - 1) >> (sb - 1)) < SPLIT_REGIONS) --sb;
   const uint64_t regions = ((a.n_members - 1) >> sb) + 1;
-  if (regions > SPLIT_REGIONS || per_member > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, sb) > lds_max ||
+  if (regions > SPLIT_REGIONS || per_member > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, pb) > lds_max || sb - pb > parts ||
       regions > a.n_cell / 32 + 1) return false;
-  a.sb = sb; a.n_regions = (uint32_t)regions; a.snap_inv = (uint32_t)((1ull << 32) / a.n_snap + 1);
+  a.sb = sb; a.pb = pb; a.n_regions = (uint32_t)regions; a.snap_inv = (uint32_t)((1ull << 32) / a.n_snap + 1);
   a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.cnt;
   return true;
 }
@@ -1399,7 +1417,7 @@ static ccld_status locate_hang_on(ccld_ctx* c, const HangScratch& S, const ccld_
   HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));
   a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
   a.out_root = o->root; a.root_cap = o->root_cap;
-  for (bool split = split_regions(a, S, region_lds, SPLIT_LDS);; split = false) {
+  for (bool split = split_regions(a, S, region_lds, SPLIT_LDS, 0);; split = false) {
     a.ticket = ++c->ticket;
     if (!split) a.final = reinterpret_cast<ulonglong2*>(S.cell);
     c->prof.begin(CCLD_PROF_HANG_PLACE);
@@ -1557,17 +1575,18 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
     c->prof.end(CCLD_PROF_HANG);
   };
   HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));
-  bool split = split_regions(a, S, rate_region_lds, RATE_LDS);
+  bool split = split_regions(a, S, rate_region_lds, RATE_LDS, RATE_PARTS);
   if (split) {
     c->prof.begin(CCLD_PROF_HANG_PLACE);
     launch_split(st, a);
     c->prof.split(CCLD_PROF_HANG_PLACE, CCLD_PROF_HANG);
-    const size_t lds = rate_region_lds(a.n_ch, a.n_snap, a.sb);
-    if (((uint64_t)a.n_ch * a.n_snap << a.sb) >= 2048) {
+    const size_t lds = rate_region_lds(a.n_ch, a.n_snap, a.pb);
+    const uint32_t groups = a.sb == a.pb ? a.n_regions : ((a.n_regions + 7) / 8 * 8) << (a.sb - a.pb);
+    if (((uint64_t)a.n_ch * a.n_snap << a.pb) >= 2048) {
       if (lds > 65536) HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rate_region<1024>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)RATE_LDS));
-      hipLaunchKernelGGL(k_rate_region<1024>, dim3(a.n_regions), dim3(1024), lds, st, a);
+      hipLaunchKernelGGL(k_rate_region<1024>, dim3(groups), dim3(1024), lds, st, a);
     } else {
-      hipLaunchKernelGGL(k_rate_region<256>, dim3(a.n_regions), dim3(256), lds, st, a);
+      hipLaunchKernelGGL(k_rate_region<256>, dim3(groups), dim3(256), lds, st, a);
     }
     tables(false);
     HIP_TRY(hipGetLastError());

@@ -74,3 +74,11 @@ def test_many_roots(n_late):
     seq[rng.permutation(n)[:n_late]] = 7
     g, _ = test_gpu_hang.run_both(topo, _cols(topo, seq, np.full(seq.shape, 3), np.full(seq.shape, 3), rng), 5, 1, what=n_late, stall_snapshots=2)
     assert g.n_root == n_late
+
+
+@pytest.mark.parametrize("n,n_snap,n_ch", [(600, 500, 16), (733, 1000, 8)])
+def test_rates_of_regions_in_parts(n, n_snap, n_ch):
+    """one member's series fill LDS, more members than regions: two and four parts per region, the last ones empty"""
+    rng = np.random.default_rng(n)
+    topo = ring_topology(n, comms=[list(range(n)), list(range(n // 2 + 1))[::-1]])
+    test_gpu_rates.run_both(topo, _random(topo, n_snap, n_ch, rng, 7), n_snap, n_ch, what=(n, n_snap, n_ch))
