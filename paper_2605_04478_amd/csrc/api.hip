@@ -501,7 +501,7 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
 // hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
 static bool reported(const ccld_ctx* c, int words) {
   for (int i = 0; i < words; ++i)
-    if ((__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED) >> REPORT_BITS) != (c->ticket & 0xFFFF)) return false;
+    if (!report_arrived(__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED), c->ticket)) return false;
   return true;
 }
 extern "C++" hipError_t wait_report(ccld_ctx* c, int words) {
@@ -518,7 +518,7 @@ extern "C++" hipError_t wait_report(ccld_ctx* c, int words) {
     if (e != hipSuccess) return e;
     if (!reported(c, words)) return hipErrorUnknown;
   }
-  for (int i = 0; i < words; ++i) c->h_pinned[i] &= REPORT_MASK;
+  for (int i = 0; i < words; ++i) c->h_pinned[i] = report_value(c->h_pinned[i]);
   return hipSuccess;
 }
 
@@ -593,7 +593,7 @@ static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_resu
     launch_alert_select(st, aa);
     launch_alert_candidates(st, aa, (uint32_t)o->n_alert);
     c->prof.end(CCLD_PROF_ALERTS);
-    launch_report(st, c->counters, c->h_pinned, ++c->ticket);
+    launch_report(st, c->counters, c->h_pinned, take_ticket(c));
     HIP_TRY(hipGetLastError());
     HIP_TRY(wait_report(c));
     o->n_cand = c->h_pinned[CNT_NCAND];
@@ -701,7 +701,7 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   o->n_records = n;
   HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
   HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
-  c->ticket += 1;
+  take_ticket(c);
   // 2. sort by (communicator, operation counter, rank) on the significant bits only, the operation counters relative to
   //    the smallest one of the window
   if (min_seq > max_seq) min_seq = max_seq;
@@ -754,7 +754,7 @@ static ccld_status analyze_empty(ccld_ctx* c, ccld_window_result* o) {
   const uint32_t n_ranks = c->topo.n_ranks;
   HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
   HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
-  c->ticket += 1;
+  take_ticket(c);
   launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
@@ -780,7 +780,7 @@ ccld_status ccld_analyze_window(ccld_ctx* c, int64_t now_ns, ccld_window_result*
   } else {
     bool fallback = !c->grid_capable;
     if (c->grid_capable) {
-      c->ticket += 1;
+      take_ticket(c);
       s = analyze_on_grid(c, now_ns, o, &fallback);
     }
     if (s >= 0 && fallback) s = analyze_sorted(c, now_ns, o);
@@ -798,7 +798,7 @@ ccld_status ccld_rank_blame(ccld_ctx* c, int64_t* blame, uint32_t* order) {
   if (!c->blame_valid) return CCLD_E_BAD_ARG;
   const uint32_t n_ranks = c->topo.n_ranks;
   launch_blame_out(c->stream, c->blame, c->blame_order, n_ranks, blame, order);
-  launch_report(c->stream, c->counters, c->h_pinned, ++c->ticket);
+  launch_report(c->stream, c->counters, c->h_pinned, take_ticket(c));
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   return CCLD_OK;

@@ -7,6 +7,7 @@
 #include "ccld.h"
 #include "radix_sort.h"
 #include "profiler.h"
+#include "ticket.h"
 
 namespace ccld {
 
@@ -106,10 +107,6 @@ constexpr int RANKCOUNT_BLOCKS = 2048;
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
        CNT_NRETAINED, CNT_DONE, CNT_NCELL, CNT_COUNT = 16 };
 
-// how the device reports a counter to the host: its value with the analysis's ticket in the upper bits
-constexpr int REPORT_BITS = 48;
-constexpr uint64_t REPORT_MASK = (1ull << REPORT_BITS) - 1;
-
 }  // namespace ccld
 
 struct ccld_ctx {
@@ -166,7 +163,7 @@ struct ccld_ctx {
   uint32_t long_classes;              // which sizes beyond 64 members there are (SegArgs)
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging
-  uint64_t ticket;                    // number of the latest report that the device was asked for
+  uint64_t ticket;                    // of the latest report that the device was asked for
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location
@@ -217,5 +214,7 @@ struct ccld_ctx {
 
 // looks up the device address of the library's static scratch array on the current device (hang.hip)
 ccld_status ccld_static_scratch_init();
+// the ticket of the report that the device is asked for next
+inline uint64_t take_ticket(ccld_ctx* c) { return c->ticket = ccld::next_ticket(c->ticket); }
 // waits for the report of the current ticket (api.hip): its words are then in h_pinned
 hipError_t wait_report(ccld_ctx* c, int words = ccld::CNT_COUNT);

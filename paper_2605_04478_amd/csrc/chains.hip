@@ -292,7 +292,7 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
       hipLaunchKernelGGL(k_chain_emit<false>, blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
     }
   }
-  launch_report(st, c->counters, c->h_pinned, ++c->ticket);
+  launch_report(st, c->counters, c->h_pinned, take_ticket(c));
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   if (o->n_chain > o->chain_cap) o->status = CCLD_W_TRUNCATED;

@@ -1225,7 +1225,7 @@ __global__ __launch_bounds__(256) void k_frame_rows(FrameArgs a, ccld_snapshot_r
 // the call's end: every launch before it is over
 __global__ void k_frame_report(const u64* status, u32 call, u64* host, u64 ticket) {
   const u64 s = *status;
-  __hip_atomic_store(host, ((s >> 8) == call ? s & 0xFF : 0) | (ticket << REPORT_BITS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(host, report_word((s >> 8) == call ? s & 0xFF : 0, ticket), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace ccld
@@ -1418,7 +1418,7 @@ static ccld_status locate_hang_on(ccld_ctx* c, const HangScratch& S, const ccld_
   a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
   a.out_root = o->root; a.root_cap = o->root_cap;
   for (bool split = split_regions(a, S, region_lds, SPLIT_LDS, 0);; split = false) {
-    a.ticket = ++c->ticket;
+    a.ticket = take_ticket(c);
     if (!split) a.final = reinterpret_cast<ulonglong2*>(S.cell);
     c->prof.begin(CCLD_PROF_HANG_PLACE);
     if (split) {
@@ -1569,7 +1569,7 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
   auto tables = [&](bool checked) {
     a.checked = checked ? 1 : 0;
     a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
-    a.ticket = ++c->ticket;
+    a.ticket = take_ticket(c);
     hipLaunchKernelGGL(k_rate_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a, c->rate_root);
     launch_report(st, a.counters, a.host, a.ticket);
     c->prof.end(CCLD_PROF_HANG);
@@ -1658,7 +1658,7 @@ extern "C" ccld_status ccld_decode_frames(ccld_ctx* c, const ccld_frames* fr, co
   }
   a.n_frames = fr->n_frames; a.n_ch = fr->n_channels; a.snap = fr->snapshot; a.mb = c->kf.mb; a.T = c->topo;
   a.n_members = c->n_members; a.last = c->f_last; a.frame_of = c->f_frame; a.status = c->f_status; a.call = ++c->f_call;
-  a.ticket = ++c->ticket;
+  a.ticket = take_ticket(c);
   c->prof.begin(CCLD_PROF_FRAMES);
   const uint64_t slots = c->n_members * CCLD_FRAME_CHANNELS;
   if (fr->n_frames) hipLaunchKernelGGL(k_frames_check, dim3((uint32_t)((fr->n_frames + 3) / 4)), dim3(256), 0, st, a);

@@ -5,12 +5,12 @@
 
 namespace ccld {
 
-// Each counter goes out with the ticket in its upper 16 bits.  The host waits until every word carries the ticket, so the
+// Each counter goes out with its ticket (ticket.h).  The host waits until every word carries the ticket, so the
 // words need no order among themselves.  Called by the first wavefronts of one workgroup.
 __device__ __forceinline__ void report_words(const u64* counters, u64* host, u64 ticket) {
   if (threadIdx.x < CNT_COUNT) {
     const u64 v = __hip_atomic_load(&counters[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&host[threadIdx.x], (v & REPORT_MASK) | (ticket << REPORT_BITS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host[threadIdx.x], report_word(v, ticket), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 static_assert(CNT_COUNT <= 64, "one wavefront copies the counters");
