@@ -307,7 +307,9 @@ ccld_status ccld_analyze_window(ccld_ctx *ctx, int64_t now_ns, ccld_window_resul
  * without a late entry there F is a root flag: r is late of its own.  Late exits have no parent.  Parents
  * are followed to the chain's first flag.  A delay that a whole communicator carries in step for several
  * operations leaves no late entry there, so a chain can end before it reaches the rank that injected the
- * delay: the chains separate the direct consequences, not every later echo. */
+ * delay: the chains separate the direct consequences, not every later echo.  Records whose clocks contradict each
+ * other can make parents lead round in a loop, which has no first flag; every flag whose chain leads into one gets
+ * the ancestor that doubling the links ceil(log2(flags)) times reaches, and the number of links to it. */
 ccld_status ccld_flag_chains(ccld_ctx *ctx, const ccld_window_result *analysed, ccld_chain_result *out);
 
 /* Locates the root of a hang from progress-counter snapshots (Section 4.2.2, hang decision tree;

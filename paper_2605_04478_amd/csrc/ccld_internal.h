@@ -105,7 +105,7 @@ constexpr int RANKCOUNT_BLOCKS = 2048;
 
 // device counters written by kernels and read back by the host
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
-       CNT_NRETAINED, CNT_DONE, CNT_NCELL, CNT_COUNT = 16 };
+       CNT_CHAIN_LOOP, CNT_DONE, CNT_NCELL, CNT_COUNT = 16 };
 
 }  // namespace ccld
 
@@ -153,7 +153,7 @@ struct ccld_ctx {
   uint16_t* gcode;                    // [cap] (op, size class) of every usable collective
   uint32_t* comm_groups;              // [n_comms + 1] detection groups of each communicator
   uint32_t* comm_row;                 // [n_comms] its first row of the collective table
-  uint32_t* chain_parent;             // [cap + 1] scratch of ccld_flag_chains
+  uint32_t* chain_parent;             // [cap + 1] scratch of ccld_flag_chains: parent of every flag
   uint32_t* alert_list;               // [cap]
   uint32_t* alert_ncand;              // [cap + 1]
   uint2* comm_info;                   // [n_comms] (first member index, members) of every communicator: one load for both

@@ -2,8 +2,8 @@
 // anomaly may propagate across ranks; the location step separates the rank that triggered it from the
 // ranks that pass it on).  Per late-entry flag: the operation its rank ran just before (found by binary
 // search over the rounds of each of the rank's communicators, on the rank's own timestamps), the member
-// whose late arrival ended that operation late (its parent flag), then pointer jumping to the chain's
-// first flag.
+// whose late arrival ended that operation late (its parent flag), then the links from parent to parent up to
+// the chain's first flag.
 #include <algorithm>
 #include <cstring>
 
@@ -39,6 +39,8 @@ struct ChainArgs {
   u32* parent;               // [n_flag] parent flag or ~0
   u64* link;                 // [n_flag] an ancestor, links up to it << 32; a root leads to itself
   i64* per_rank;             // cleared by the parent kernel, or null
+  u64* looped;               // set if some links lead round in a loop
+  u32 *anc[2], *dist[2];     // [n_flag] each: ancestors and links to them, where they do
 };
 
 // first row of the collective table of every communicator (the table is ordered by communicator)
@@ -198,6 +200,23 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
   }
 }
 
+// Links that lead round in a loop: jumps in step, 2^i links after the i-th, from one pair of arrays into the other.
+__global__ __launch_bounds__(256) void k_chain_init(ChainArgs a) {
+  const u32 k = blockIdx.x * 256 + threadIdx.x;
+  if (a.per_rank)
+    for (u64 i = k; i < (u64)CCLD_CHR_NCOL * a.T.n_ranks; i += (u64)gridDim.x * 256) a.per_rank[i] = 0;
+  if (k >= a.n_flag) return;
+  const u32 p = a.parent[k];
+  a.anc[0][k] = p == ~0u ? k : p;
+  a.dist[0][k] = p == ~0u ? 0u : 1u;
+}
+__global__ __launch_bounds__(256) void k_chain_jump(ChainArgs a) {
+  const u32 k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= a.n_flag) return;
+  const u32 a1 = a.anc[0][k], a2 = a.anc[0][a1];
+  a.anc[1][k] = a2;
+  a.dist[1][k] = a.dist[0][k] + (a2 != a1 ? a.dist[0][a1] : 0u);
+}
 // column[idx] += 1 for every lane with `on`, one atomic per distinct idx in the wavefront: a faulty rank's thousands
 // of entries would otherwise queue up at one address.  Called by every active lane of the wavefront.
 __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool on) {
@@ -214,7 +233,10 @@ __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool o
 // whatever the others have written by then is right, nobody waits for anybody, and the links double in length as all
 // flags go on at once (one launch in place of a jump per doubling: 14 for 8,000 flags).  Each step takes the link past the
 // caches that the XCDs do not share.
-template <bool GRID>
+// Parents end earlier, so links do not lead back; records that contradict their own clocks can make them.  Then there is
+// no root and what a flag finds would depend on who was faster, so the call is repeated with LOOPED on the ancestors that
+// the kernels below find, the same ones every time.
+template <bool GRID, bool LOOPED>
 __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64 chain_cap) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
   if (k >= a.n_flag) return;
@@ -223,14 +245,17 @@ __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64
     return a.T.members_sorted[a.T.member_off[f.comm] + f.slot];
   };
   u64 v = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[k]));
-  // Parents end earlier, so there are no cycles; records that contradict their own clocks could make one, and the bound
-  // on the links ends the walk there.
-  while ((v >> 32) <= a.n_flag) {
-    const u32 up = (u32)v;
-    const u64 w = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[up]));
-    if ((u32)w == up) break;                     // up is a root
-    v = (u64)(u32)w | ((v >> 32) + (w >> 32)) << 32;
-    store_agent(reinterpret_cast<i64*>(&a.link[k]), (i64)v);
+  if (LOOPED) {
+    v = (u64)a.anc[0][k] | (u64)a.dist[0][k] << 32;
+  } else {
+    while (true) {
+      const u32 up = (u32)v;
+      const u64 w = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[up]));
+      if ((w >> 32) == 0) break;                 // up is a root: every other link has a length, a loop's included
+      v = (u64)(u32)w | ((v >> 32) + (w >> 32)) << 32;
+      if ((v >> 32) > a.n_flag) { *a.looped = 1; break; }        // more links than flags: a loop
+      store_agent(reinterpret_cast<i64*>(&a.link[k]), (i64)v);
+    }
   }
   const u32 root = (u32)v, p = a.parent[k];
   i64* per_rank = a.per_rank;
@@ -269,7 +294,14 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
   const uint32_t n_flag = (uint32_t)c->last_n_flag, n_ranks = c->topo.n_ranks;
   o->n_chain = n_flag;
   if (o->per_rank && !n_flag) HIP_TRY(hipMemsetAsync(o->per_rank, 0, sizeof(int64_t) * CCLD_CHR_NCOL * (uint64_t)n_ranks, st));
-  if (n_flag) {
+  auto report = [&]() -> hipError_t {
+    launch_report(st, c->counters, c->h_pinned, take_ticket(c));
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : wait_report(c);
+  };
+  if (!n_flag) {
+    HIP_TRY(report());
+  } else {
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
     const bool grid = c->last_grid;
@@ -283,18 +315,30 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
     a.link = reinterpret_cast<uint64_t*>(c->range_c);                // scratch that the analysis no longer needs
     a.per_rank = o->per_rank;
     const dim3 blocks((n_flag + 255) / 256), parents((uint32_t)(((uint64_t)n_flag * PARENT_LANES + 255) / 256));
+    a.looped = &c->counters[CNT_CHAIN_LOOP];       // cleared by the analysis; its flags lead round or they do not
     if (grid) {
       hipLaunchKernelGGL(k_chain_parent<true>, parents, dim3(256), 0, st, a);
-      hipLaunchKernelGGL(k_chain_emit<true>, blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
     } else {
       hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
       hipLaunchKernelGGL(k_chain_parent<false>, parents, dim3(256), 0, st, a);
-      hipLaunchKernelGGL(k_chain_emit<false>, blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+    }
+    HIP_TRY(report());
+    if (c->h_pinned[CNT_CHAIN_LOOP]) {
+      a.anc[0] = reinterpret_cast<uint32_t*>(a.link); a.dist[0] = a.anc[0] + n_flag;
+      a.anc[1] = c->alert_list; a.dist[1] = c->alert_ncand;
+      hipLaunchKernelGGL(k_chain_init, blocks, dim3(256), 0, st, a);
+      for (uint64_t reach = 1; reach < n_flag; reach *= 2) {
+        hipLaunchKernelGGL(k_chain_jump, blocks, dim3(256), 0, st, a);
+        std::swap(a.anc[0], a.anc[1]);
+        std::swap(a.dist[0], a.dist[1]);
+      }
+      if (grid) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      HIP_TRY(report());
     }
   }
-  launch_report(st, c->counters, c->h_pinned, take_ticket(c));
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(wait_report(c));
   if (o->n_chain > o->chain_cap) o->status = CCLD_W_TRUNCATED;
   return o->status;
 }

@@ -104,3 +104,75 @@ def test_members_without_records_in_flight_operations_and_ties():
     cols = toy_cols(rows)
     p = np.random.default_rng(0).permutation(len(rows))
     run_both(topo, {k: v[p] for k, v in cols.items()}, t + 10**9, what="ragged")
+
+
+def _jumps_in_step(parent):
+    """Ancestors and links to them by doubling jumps of all flags at once: 2^i links after the i-th (a root stays)."""
+    n = len(parent)
+    anc = np.where(parent >= 0, parent, np.arange(n))
+    depth = (parent >= 0).astype(np.int64)
+    reach = 1
+    while reach < n:
+        nxt = anc[anc]
+        depth = depth + np.where(nxt != anc, depth[anc], 0)
+        anc, reach = nxt, 2 * reach
+    return anc, depth
+
+
+@pytest.mark.parametrize("loop,tail,sort", [(2, 0, False), (3, 1, False), (7, 40, True), (40, 3, False), (129, 200, True),
+                                            (1500, 700, False)])
+def test_clocks_that_contradict_each_other(loop, tail, sort):
+    """Communicator i = {i, i + 1 modulo `loop`, two more}: its rank i enters late and its rank i + 1 has left before that,
+    so the late entries name each other as parents all the way round; `tail` ranks whose chain leads into the loop, and one
+    flag with a root.  Every flag then has the ancestor that jumps in step find, however often it is asked for."""
+    from paper_2605_04478_amd import ccld
+    LATE = 50 * MS
+    comms, rows, r = [], [], loop + tail + 1
+
+    def coll(members, late, t, seq=0):
+        c = len(comms)
+        comms.append(members)
+        for m in members:
+            te = t + (LATE if m == late else 0)
+            rows.append((m, c, seq, tg.OP_ALLREDUCE, 1 << 20, te, te + MS // 2))
+
+    for i in range(loop):
+        coll(sorted({i, (i + 1) % loop}) + [r, r + 1, r + 2], i, T0)
+        r += 3
+    for j in range(tail):                   # rank loop + j: in the collective of the one before it, then late in its own
+        coll([0 if j == 0 else loop + j - 1, loop + j, r, r + 1, r + 2], 0 if j == 0 else loop + j - 1, T0 + 10**10 + j * LATE * 3)
+        r += 3
+    coll([loop + tail, r, r + 1, r + 2], loop + tail, T0)
+    r += 3
+    if sort:                                # a round that nobody recorded: the window is sorted
+        coll([r], -1, T0)
+        rows.append((r, len(comms) - 1, 2, tg.OP_ALLREDUCE, 1 << 20, T0 + 10 * MS, T0 + 11 * MS))
+        r += 1
+    cols = toy_cols(rows)
+    p = np.random.default_rng(loop).permutation(len(rows))
+    cols = {k: v[p] for k, v in cols.items()}
+    topo = tg.make_topology(r, comms)
+    now = T0 + 10**13
+    ref = orc.Oracle(topo).analyze_window(cols, now)
+    n_flag, late = len(ref.flag["comm"]), ref.flag["rank"].astype(np.int64)
+    assert n_flag == loop + tail + 1 and (ref.flag["kind"] & orc.FLAG_LATE_ENTER).all()
+    with pytest.raises(ValueError):
+        orc.Oracle(topo).flag_chains(cols, ref)              # it refuses loops
+    parent = np.concatenate([(np.arange(loop) - 1) % loop, np.arange(loop - 1, loop + tail - 1), [-1]])
+    if tail:                                # rank 0 leaves its late collective last, so its next one hangs on that
+        parent[loop] = 0
+    root, depth = _jumps_in_step(parent)
+    per = {"root_entries": np.bincount(late[parent < 0], minlength=r), "secondary_entries": np.bincount(late[parent >= 0], minlength=r),
+           "caused": np.bincount(late[root], minlength=r)}
+    for placement in (0, 1):
+        an = ccld.Analyzer(topo, max_window_records=len(rows), placement=placement)
+        an.ingest(an.to_device(cols))
+        g = an.analyze_window(now, n_records=len(rows))
+        for again in range(4):
+            st, chain, per_rank = an.flag_chains(g)
+            assert st == "OK"
+            for name, want in (("parent", parent), ("root", root), ("root_rank", late[root]), ("depth", depth)):
+                assert np.array_equal(chain[name], want), (name, again, np.nonzero(chain[name] != want)[0][:5])
+            for name in per:
+                assert np.array_equal(per_rank[name], per[name]), (name, again)
+        an.close()
