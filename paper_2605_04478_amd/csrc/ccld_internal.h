@@ -212,6 +212,18 @@ struct ccld_ctx {
   int sort_passes;                    // passes of the last main sort
 };
 
+namespace ccld {
+// Kernels that take more than 64 KB of dynamic LDS have to be allowed it on every device: ccld_create asks for the device
+// that is current (one function per file of kernels).
+inline hipError_t allow_lds(const void* kernel, size_t bytes) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+hipError_t allow_lds_window();
+hipError_t allow_lds_grid();
+hipError_t allow_lds_segments();
+hipError_t allow_lds_hang();
+}  // namespace ccld
+
 // looks up the device address of the library's static scratch array on the current device (hang.hip)
 ccld_status ccld_static_scratch_init();
 // the ticket of the report that the device is asked for next

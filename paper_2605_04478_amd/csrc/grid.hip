@@ -365,18 +365,16 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
 static_assert(GRID_SPAN % PART_THREADS == 0, "whole buckets per thread");
 static_assert(ROW_CELL_SHIFT == 16 && ROW_CELL_MASK == GRID_B - 1, "the cell is packed as the row has it");
 
+constexpr size_t PART_LDS = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, PART_LDS_SLOTS = PART_LDS + (size_t)PART_CHUNK * 4;
+hipError_t allow_lds_grid() {
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_grid_partition<false>), PART_LDS);
+  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_grid_partition<true>), PART_LDS_SLOTS);
+}
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
-  constexpr size_t lds = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, lds_slots = lds + (size_t)PART_CHUNK * 4;
-  static bool raised = false;          // more than 64 KB of dynamic LDS has to be asked for once
-  if (!raised) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_grid_partition<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_slots);
-    raised = true;
-  }
   // small windows: a thousand records per workgroup, so that there are several of them
   const u32 g = std::min<u32>(PART_BLOCKS, std::max<u32>((d.n + PART_THREADS - 1) / PART_THREADS, 1));
-  if (d.slots) hipLaunchKernelGGL(k_grid_partition<true>, dim3(g), dim3(PART_THREADS), lds_slots, st, d);
-  else hipLaunchKernelGGL(k_grid_partition<false>, dim3(g), dim3(PART_THREADS), lds, st, d);
+  if (d.slots) hipLaunchKernelGGL(k_grid_partition<true>, dim3(g), dim3(PART_THREADS), PART_LDS_SLOTS, st, d);
+  else hipLaunchKernelGGL(k_grid_partition<false>, dim3(g), dim3(PART_THREADS), PART_LDS, st, d);
 }
 
 }  // namespace ccld

@@ -1302,6 +1302,12 @@ static hipError_t snapshot_args(ccld_ctx* c, const HangScratch& S, const ccld_sn
   return hipSuccess;
 }
 
+constexpr size_t PART_LDS = (size_t)PART_CHUNK * (16 + 4 + 4);
+hipError_t ccld::allow_lds_hang() {
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_hang_part), PART_LDS);
+  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_rate_region<1024>), RATE_LDS);
+}
+
 // Clears the grid's presence counts and places every row in its cell.
 static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_snapshots* sn, uint64_t n_rows,
                                   uint64_t n_cell, HangArgs& a, bool exact) {
@@ -1328,13 +1334,7 @@ static hipError_t place_snapshots(ccld_ctx* c, const HangScratch& S, const ccld_
     uint64_t g = (n_rows + PART_CHUNK - 1) / PART_CHUNK; if (g > 1024) g = 1024;
     uint64_t chunk = (n_rows + g - 1) / g;
     chunk = (chunk + PART_CHUNK - 1) / PART_CHUNK * PART_CHUNK;
-    static bool raised = false;       // more than 64 KB of dynamic LDS has to be asked for once
-    constexpr size_t part_lds = (size_t)PART_CHUNK * (16 + 4 + 4);
-    if (!raised) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hang_part), hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_lds);
-      raised = true;
-    }
-    hipLaunchKernelGGL(k_hang_part, dim3((uint32_t)g), dim3(PART_THREADS), part_lds, st, a, chunk);
+    hipLaunchKernelGGL(k_hang_part, dim3((uint32_t)g), dim3(PART_THREADS), PART_LDS, st, a, chunk);
     const uint32_t wpr = (uint32_t)((((uint64_t)1 << rb) + PLACE_ROWS - 1) / PLACE_ROWS);
     const uint64_t g2 = 8 * ((n_regions + 7) / 8) * wpr;
     hipLaunchKernelGGL(k_hang_place_regions, dim3((uint32_t)g2), dim3(256), 0, st, a, wpr);
@@ -1583,7 +1583,6 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
     const size_t lds = rate_region_lds(a.n_ch, a.n_snap, a.pb);
     const uint32_t groups = a.sb == a.pb ? a.n_regions : ((a.n_regions + 7) / 8 * 8) << (a.sb - a.pb);
     if (((uint64_t)a.n_ch * a.n_snap << a.pb) >= 2048) {
-      if (lds > 65536) HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rate_region<1024>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)RATE_LDS));
       hipLaunchKernelGGL(k_rate_region<1024>, dim3(groups), dim3(1024), lds, st, a);
     } else {
       hipLaunchKernelGGL(k_rate_region<256>, dim3(groups), dim3(256), lds, st, a);

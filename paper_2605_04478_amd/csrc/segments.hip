@@ -1991,6 +1991,9 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
 static_assert(LONG_ROUNDS <= CCLD_WAVE, "a lane per round");
 static_assert(CCLD_SEG_ENTER_MIN == 7 && CCLD_SEG_EXIT_MIN == 11 && CCLD_SEG_DUR_MIN == 15, "four columns of arrival, four of completion");
 
+constexpr size_t LARGE_LDS = sizeof(int64_t) * SEG_LARGE_MAX;
+hipError_t allow_lds_segments() { return allow_lds(reinterpret_cast<const void*>(&k_seg_large), LARGE_LDS); }
+
 // the collectives on the list (more than 64 records)
 static void launch_seg_listed(hipStream_t st, const SegArgs& a) {
   // a collective has at most as many records as its communicator has members (a longer one holds a
@@ -2002,15 +2005,7 @@ static void launch_seg_listed(hipStream_t st, const SegArgs& a) {
   if (m > 128) hipLaunchKernelGGL(k_seg_multi<4>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   if (m > 256) hipLaunchKernelGGL(k_seg_multi<8>, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   if (m > (uint32_t)SEG_MULTI_MAX) hipLaunchKernelGGL(k_seg_team, dim3(1024), dim3(SEG_THREADS), 0, st, a);
-  if (m > (uint32_t)SEG_TEAM_MAX) {
-    static bool raised = false;       // more than 64 KB of dynamic LDS has to be asked for once
-    constexpr size_t lds = sizeof(int64_t) * SEG_LARGE_MAX;
-    if (!raised) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_seg_large), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      raised = true;
-    }
-    hipLaunchKernelGGL(k_seg_large, dim3(512), dim3(LARGE_THREADS), lds, st, a);
-  }
+  if (m > (uint32_t)SEG_TEAM_MAX) hipLaunchKernelGGL(k_seg_large, dim3(512), dim3(LARGE_THREADS), LARGE_LDS, st, a);
   if (m > (uint32_t)SEG_LARGE_MAX) hipLaunchKernelGGL(k_seg_big, dim3(2048), dim3(SEG_THREADS), 0, st, a);
   if (m > (uint32_t)SEG_MULTI_MAX) hipLaunchKernelGGL(k_seg_group_listed, dim3(256), dim3(256), 0, st, a);
 }

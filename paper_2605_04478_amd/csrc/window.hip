@@ -424,20 +424,16 @@ IngestShape ingest_shape(uint64_t n) {
   s.per_group = (uint32_t)((s.chunk + INGEST_ROUND - 1) / INGEST_ROUND);
   return s;
 }
+hipError_t allow_lds_window() {
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_ingest_staged<1024, true>), 156 * 1024);
+  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_ingest_staged<1024, false>), 156 * 1024);
+}
 void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology& T, const KeyFormat& kf) {
   IngestArgs a = a_in;
   const size_t range_lds = a.range ? (size_t)16 * T.n_comms : 0;
   if (a.n == 0) {
     hipLaunchKernelGGL(k_ingest_empty, dim3(8), dim3(256), 0, st, a, T.n_comms);
     return;
-  }
-  static bool raised = false;       // more than 64 KB of dynamic LDS has to be asked for once
-  if (!raised) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ingest_staged<1024, true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ingest_staged<1024, false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
-    raised = true;
   }
   if (a.n_buckets == 1) {
     // four records per thread and workgroup until the chip is full, then longer slices
