@@ -9,6 +9,7 @@ namespace ccld {
 
 constexpr u32 GC_THREADS = 512;
 constexpr u32 GC_BATCH = 64;               // groups still averaging their baseline that one walk handles
+constexpr u32 GC_WALK = 8;                 // rows of one thread per step of that walk (a byte of a word each)
 constexpr u32 GC_NONE = 0xFFFFFFFFu;
 
 // first row of the table with communicator >= c, found by one wavefront (64 probes per step)
@@ -32,24 +33,28 @@ __device__ __forceinline__ u32 first_row_of(const i64* __restrict__ comm, u32 n,
 // cross-multiplied.
 // The rows of a communicator are read as a 2-byte (op, size class) code and an 8-byte range, twice (largest range
 // of every group, then the first row that attains it): 10 bytes per collective from memory, the second time from
-// the L2.  Groups whose baseline is not frozen yet and that have new rounds take two further passes over the rows;
-// the round that ends a baseline by its count is found by an ordered walk, once in a group's life.
+// the L2.  Groups whose baseline is not frozen yet and that have new rounds are walked once more, 4,096 rows a step from the
+// first new one on, and only until the last of them has its baseline: 100 rounds by default, which a communicator watched
+// for long has in its first few thousand rows (see the walk for the times).
 // At 8.4M collectives of 1,088 communicators this replaces a three-pass sort of the collectives by group (0.23 ms)
 // and a wavefront per group (0.13 ms).
 // What is left per group for k_group_emit, in the order of the (op, class) codes at the communicator's rows:
 // stage[0] = code | dynamic << 10 | slow << 11 | class << 12, stage[1] = row of Eq. 2's round, stage[2] = usable rounds.
-__global__ __launch_bounds__(GC_THREADS) void k_group_comm(GroupArgs a) {
+// (Four workgroups per compute unit: with the registers that the compiler takes by itself there are three, and a stream's 3,200
+// communicators take 49 us instead of 38.)
+__global__ __launch_bounds__(GC_THREADS, 8) void k_group_comm(GroupArgs a) {
   __shared__ u32 s_cnt[GROUP_SLOTS], s_row[GROUP_SLOTS], s_last[GROUP_SLOTS];
   __shared__ unsigned long long s_best[GROUP_SLOTS];
   __shared__ unsigned short s_list[GROUP_SLOTS];
   __shared__ u32 s_wave[GC_THREADS / CCLD_WAVE];
-  __shared__ u32 s_lo, s_hi, s_need, s_left;
+  __shared__ u32 s_lo, s_hi, s_need, s_left, s_n_rank;
   // the batch of groups that Eq. 1 has new rounds for
   __shared__ uint8_t s_map[GROUP_SLOTS];
   __shared__ unsigned long long s_wm[GC_BATCH], s_sum[GC_BATCH];
   __shared__ i64 s_t0[GC_BATCH];
+  __shared__ unsigned long long s_min_wm;
   __shared__ u32 s_i0[GC_BATCH], s_istar[GC_BATCH], s_new[GC_BATCH], s_lim[GC_BATCH], s_seen[GC_BATCH], s_m[GC_BATCH],
-      s_lastb[GC_BATCH], s_code[GC_BATCH];
+      s_lastb[GC_BATCH], s_code[GC_BATCH], s_rank[GC_BATCH];
   // a data error found by an earlier kernel of this analysis: the tables are not valid and the detection state
   // stays as it is
   if (a.counters[CNT_STATUS] != 0) return;
@@ -133,7 +138,7 @@ __global__ __launch_bounds__(GC_THREADS) void k_group_comm(GroupArgs a) {
   for (u32 done = 0; done < n_need;) {
     // the next groups of the list, GC_BATCH at a time (a group leaves the list by its new watermark)
     __syncthreads();
-    if (tid == 0) s_left = 0;
+    if (tid == 0) { s_left = 0; s_min_wm = ~0ull; s_n_rank = 0; }
     for (u32 i = tid; i < (u32)GROUP_SLOTS; i += GC_THREADS) s_map[i] = 0xFF;
     __syncthreads();
     for (u32 p = tid; p < n_group; p += GC_THREADS) {
@@ -144,68 +149,80 @@ __global__ __launch_bounds__(GC_THREADS) void k_group_comm(GroupArgs a) {
       if (m >= GC_BATCH) continue;
       s_map[g] = (uint8_t)m; s_code[m] = g; s_wm[m] = G.baselined_wm; s_sum[m] = 0; s_i0[m] = GC_NONE; s_istar[m] = GC_NONE;
       s_new[m] = 0; s_seen[m] = 0; s_m[m] = 0; s_lastb[m] = 0;
+      s_t0[m] = G.t0; s_lim[m] = a.p.tbase_rounds > G.cnt ? a.p.tbase_rounds - G.cnt : 0u;
+      atomicMin(&s_min_wm, (unsigned long long)G.baselined_wm);
     }
     __syncthreads();
     const u32 nb = s_left < GC_BATCH ? s_left : GC_BATCH;
     if (nb == 0) break;
     done += nb;
-    for (u32 i = lo + tid; i < hi; i += GC_THREADS) {
-      const u32 g = code[i];
-      const u32 m = g < (u32)GROUP_SLOTS ? s_map[g] : 0xFFu;
-      if (m != 0xFF && (u64)SEQ[i] + 1 > s_wm[m]) { atomicMin(&s_i0[m], i); atomicAdd(&s_new[m], 1u); }
+    // The walk.  A baseline ends before the first new round past the warm-up span and before the new round number s_lim, and
+    // a group whose baseline has ended costs nothing from the next step on.  A step: its new rounds per group; the
+    // round that ends a group by its count, where the step has it (a scan over the step's rows, once in a group's
+    // life); the first one past the warm-up span; the sums up to there.  On first windows this takes the place of four passes
+    // over all rows, one of them by a single wavefront (analysis of 40M records of 8 ranks, 3M rounds in a communicator:
+    // 18.3 -> 6.0 ms; 10M of 16 ranks: 2.55 -> 1.19).
+    if (tid == 0) s_left = nb;            // (what it says already, or more)
+    u32 start = lo;
+    for (u32 end = hi; end - start > GC_THREADS * GC_WALK;) {         // 512 probes at a time; few rows are walked unsearched
+      const u32 step = (end - start) / GC_THREADS, was = start;
+      const u32 k = (u32)__syncthreads_count((u64)SEQ[start + tid * step] < s_min_wm);     // a prefix of the probes
+      if (k == 0) break;
+      start = was + (k - 1) * step + 1;
+      end = k < GC_THREADS ? was + k * step : end;
     }
     __syncthreads();
-    if (tid == 0) s_left = 0;
-    __syncthreads();
-    if (tid < nb) {
-      const GroupState G = gs[s_code[tid]];
-      s_t0[tid] = G.cnt == 0 ? EMIN[s_i0[tid]] : G.t0;
-      // the round of this number among the new ones ends the baseline by its count, if there are as many
-      const u32 lim = a.p.tbase_rounds > G.cnt ? a.p.tbase_rounds - G.cnt : 0u;
-      s_lim[tid] = lim < s_new[tid] ? lim : GC_NONE;
-      if (s_lim[tid] != GC_NONE) atomicAdd(&s_left, 1u);
-    }
-    __syncthreads();
-    // the first new round that lies past the warm-up span
-    for (u32 i = lo + tid; i < hi; i += GC_THREADS) {
-      const u32 g = code[i];
-      const u32 m = g < (u32)GROUP_SLOTS ? s_map[g] : 0xFFu;
-      if (m != 0xFF && i >= s_i0[m] && EMIN[i] - s_t0[m] > a.p.tbase_warmup_ns) atomicMin(&s_istar[m], i);
-    }
-    __syncthreads();
-    if (s_left && wave == 0) {
-      u32 open = s_left;
-      u32 g = lo + lane < hi ? code[lo + lane] : NO_GROUP;
-      for (u32 base = lo; base < hi && open; base += CCLD_WAVE) {
-        const u32 i = base + lane;
-        const u32 gn = i + CCLD_WAVE < hi ? code[i + CCLD_WAVE] : NO_GROUP;
-        const u32 m = g < (u32)GROUP_SLOTS ? s_map[g] : 0xFFu;
-        const bool on = m != 0xFF && s_lim[m] != GC_NONE && i >= s_i0[m];
-        u64 todo = ballot64(on);
-        while (todo) {
-          const u32 lead = (u32)__builtin_ctzll(todo);
-          const u32 lm = (u32)__shfl((int)m, (int)lead, CCLD_WAVE);
-          const u64 same = ballot64(on && m == lm);
-          const u32 seen = s_seen[lm], want = s_lim[lm], add = (u32)__popcll(same);
-          if (on && m == lm && seen + mbcnt64(same) == want) atomicMin(&s_istar[lm], i);
-          if (want >= seen && want < seen + add) --open;
-          __builtin_amdgcn_wave_barrier();
-          if (lane == lead) s_seen[lm] = seen + add;
-          __builtin_amdgcn_wave_barrier();
-          todo &= ~same;
+    bool timed = tid < nb && gs[s_code[tid]].cnt != 0, ended = false;
+    for (u32 base = start, open = nb; base < hi && open;) {
+      // consecutive rows per thread, so that the scan numbers them; few rows are spread over all threads
+      const u32 per = hi - base < GC_THREADS * GC_WALK ? (hi - base + GC_THREADS - 1) / GC_THREADS : GC_WALK;
+      const u32 i0 = base + tid * per;
+      base += GC_THREADS * per;
+      u64 mine8 = ~0ull;                 // a byte per row: its group in the batch, 0xFF: takes no part
+#pragma unroll 1
+      for (u32 u = 0; u < per; ++u) {
+        const u32 i = i0 + u, g = i < hi ? code[i] : NO_GROUP, m = g < (u32)GROUP_SLOTS ? s_map[g] : 0xFFu;
+        if (m == 0xFF || s_istar[m] != GC_NONE || (u64)SEQ[i] + 1 <= s_wm[m]) continue;
+        atomicMin(&s_i0[m], i);
+        atomicAdd(&s_new[m], 1u);
+        mine8 ^= (u64)(m ^ 0xFF) << (8 * u);
+      }
+      if (!__syncthreads_or(mine8 != ~0ull)) continue;
+      if (tid < nb && s_new[tid]) {
+        if (!timed) { s_t0[tid] = EMIN[s_i0[tid]]; timed = true; }
+        if (s_lim[tid] - s_seen[tid] < s_new[tid]) s_rank[atomicAdd(&s_n_rank, 1u)] = tid;      // s_seen <= s_lim while it is open
+      }
+      __syncthreads();
+      for (u32 q = 0; q < s_n_rank; ++q) {
+        const u32 who = s_rank[q];
+        u32 cnt = 0, tot;
+        for (u32 u = 0; u < per; ++u) cnt += (u32)(uint8_t)(mine8 >> (8 * u)) == who;
+        u32 at = s_seen[who] + block_exclusive_sum<GC_THREADS>(cnt, s_wave, &tot);
+        for (u32 u = 0; u < per; ++u)
+          if ((u32)(uint8_t)(mine8 >> (8 * u)) == who && at++ == s_lim[who]) atomicMin(&s_istar[who], i0 + u);
+      }
+#pragma unroll 1
+      for (u32 u = 0; u < per; ++u) {
+        const u32 m = (uint8_t)(mine8 >> (8 * u));
+        if (m != 0xFF && EMIN[i0 + u] - s_t0[m] > a.p.tbase_warmup_ns) atomicMin(&s_istar[m], i0 + u);
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (u32 u = 0; u < per; ++u) {
+        const u32 m = (uint8_t)(mine8 >> (8 * u));
+        if (m != 0xFF && i0 + u < s_istar[m]) {
+          atomicAdd(&s_sum[m], (unsigned long long)DMAX[i0 + u]);
+          atomicAdd(&s_m[m], 1u);
+          atomicMax(&s_lastb[m], i0 + u);
         }
-        g = gn;
       }
-    }
-    __syncthreads();
-    for (u32 i = lo + tid; i < hi; i += GC_THREADS) {
-      const u32 g = code[i];
-      const u32 m = g < (u32)GROUP_SLOTS ? s_map[g] : 0xFFu;
-      if (m != 0xFF && i >= s_i0[m] && i < s_istar[m]) {
-        atomicAdd(&s_sum[m], (unsigned long long)DMAX[i]);
-        atomicAdd(&s_m[m], 1u);
-        atomicMax(&s_lastb[m], i);
+      if (tid < nb) {
+        s_seen[tid] += s_new[tid]; s_new[tid] = 0;
+        if (!ended && s_istar[tid] != GC_NONE) { ended = true; atomicSub(&s_left, 1u); }
       }
+      if (tid == 0) s_n_rank = 0;
+      __syncthreads();
+      open = s_left;
     }
     __syncthreads();
     if (tid < nb) {

@@ -58,3 +58,22 @@ def test_more_communicators_than_one_wavefront_sums():
             for c in range(0, n, 3) for s in range(2) for r in (c, (c + 1) % n)]
     ref = _windows(topo, [rows], tbase_init_ns=50)
     assert len(ref.group["comm"]) == 2 * len(range(0, n, 3))
+
+
+@pytest.mark.parametrize("tbase_rounds,warmup_rounds", [(1, 10**6), (4095, 10**6), (4096, 10**6), (4097, 10**6), (100, 4096), (10**6, 4095),
+                                                        (5000, 5000), (10**6, 10**6)])
+def test_baselines_that_end_at_the_edges_of_a_walk(tbase_rounds, warmup_rounds):
+    """A communicator of 9,000 rounds per window: baselines that end by their count or by the warm-up span in the first
+    step of the walk over its rows, at its edges, later or not at all, a group of its own every 700 rounds, and one that
+    only the second window has."""
+    topo = ring_topology(2)
+    SPACING = 1000
+    windows = []
+    for w in range(3):
+        rows, rng = [], np.random.default_rng(w)
+        for j in range(w * 9000, (w + 1) * 9000):
+            t, op = T0 + j * SPACING, 3 if j % 700 == 699 else 5 if 9000 <= j < 18000 and j % 50 == 7 else 0
+            rows += [(r, 0, j, op, 1 << 20, t, t + 100 + int(d)) for r, d in enumerate(rng.integers(0, 900, 2))]
+        windows.append(rows)
+    ref = _windows(topo, windows, tbase_rounds=tbase_rounds, tbase_init_ns=300, tbase_warmup_ns=warmup_rounds * SPACING)
+    assert len(ref.group["comm"]) == 2
