@@ -400,9 +400,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
     if (hipHostMalloc((void**)&c->h_pinned, bytes, hipHostMallocDefault) != hipSuccess) rs = CCLD_E_HIP;
     else std::memset(c->h_pinned, 0, bytes);
   }
-  for (hipError_t e : {allow_lds_window(), allow_lds_grid(), allow_lds_segments(), allow_lds_hang()})
-    if (e != hipSuccess) rs = CCLD_E_HIP;
-  if (ccld_static_scratch_init() != CCLD_OK) rs = CCLD_E_HIP;          // address of the static array on this device
+  if (ccld_device_init() != CCLD_OK) rs = CCLD_E_HIP;
   if (hipStreamSynchronize(c->stream) != hipSuccess) rs = CCLD_E_HIP;   // host vectors above die at return
   if (rs != CCLD_OK) {
     (void)hipGetLastError();

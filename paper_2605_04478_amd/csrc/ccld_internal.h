@@ -213,8 +213,8 @@ struct ccld_ctx {
 };
 
 namespace ccld {
-// Kernels that take more than 64 KB of dynamic LDS have to be allowed it on every device: ccld_create asks for the device
-// that is current (one function per file of kernels).
+// Kernels that take more than 64 KB of dynamic LDS have to be allowed it on every device (one function per file of kernels,
+// called by ccld_device_init).
 inline hipError_t allow_lds(const void* kernel, size_t bytes) {
   return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
@@ -224,8 +224,9 @@ hipError_t allow_lds_segments();
 hipError_t allow_lds_hang();
 }  // namespace ccld
 
-// looks up the device address of the library's static scratch array on the current device (hang.hip)
-ccld_status ccld_static_scratch_init();
+// what every device needs once, for the current one (hang.hip): kernels with much LDS allowed it, and the device address of
+// the library's static scratch array
+ccld_status ccld_device_init();
 // the ticket of the report that the device is asked for next
 inline uint64_t take_ticket(ccld_ctx* c) { return c->ticket = ccld::next_ticket(c->ticket); }
 // waits for the report of the current ticket (api.hip): its words are then in h_pinned

@@ -1484,13 +1484,16 @@ constexpr int MAX_DEVICES = 64;
 unsigned char* g_scratch_ptr[MAX_DEVICES] = {nullptr};     // device address of `scratch` on each GPU
 std::mutex g_scratch_mutex;
 
-// device address of the static array on the current device (looked up on the first call per device)
-ccld_status static_scratch_address(unsigned char** out) {
+// device address of the static array on the current device; the first call per device looks it up and allows the kernels
+// their LDS
+ccld_status device_scratch(unsigned char** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) { (void)hipGetLastError(); return CCLD_E_HIP; }
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
   if (!g_scratch_ptr[dev]) {
     void* p = nullptr;
+    for (hipError_t e : {allow_lds_window(), allow_lds_grid(), allow_lds_segments(), allow_lds_hang()})
+      if (e != hipSuccess) { (void)hipGetLastError(); return CCLD_E_HIP; }
     if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) { (void)hipGetLastError(); return CCLD_E_HIP; }
     g_scratch_ptr[dev] = static_cast<unsigned char*>(p);
   }
@@ -1509,10 +1512,10 @@ struct StaticCarver {
 };
 }  // namespace
 
-// called by ccld_create with the context's device current: the first look-up happens at set-up
-ccld_status ccld_static_scratch_init() {
+// called by ccld_create with the context's device current: no other call comes first on a device
+ccld_status ccld_device_init() {
   unsigned char* p = nullptr;
-  return static_scratch_address(&p);
+  return device_scratch(&p);
 }
 
 extern "C" ccld_status ccld_locate_hang_static(ccld_ctx* c, const ccld_snapshots* sn, uint64_t n_rows,
@@ -1521,7 +1524,7 @@ extern "C" ccld_status ccld_locate_hang_static(ccld_ctx* c, const ccld_snapshots
   const ccld_status s = check_hang_args(c, sn, n_rows, o, &n_cell);
   if (s != CCLD_OK) return s;
   unsigned char* base = nullptr;
-  const ccld_status sa = static_scratch_address(&base);
+  const ccld_status sa = device_scratch(&base);
   if (sa != CCLD_OK) return o->status = sa;
   const uint64_t nm = c->n_members, nc = c->topo.n_comms;
   // every size below is bounded before it is multiplied: a grid beyond the array is refused here

@@ -1,5 +1,5 @@
-"""Nothing that belongs to a device is kept per process: which kernels may take how much LDS is asked for by every
-ccld_create, for the device that is current then (a source check: it runs without a GPU)."""
+"""Nothing that belongs to a device is kept per process: which kernels may take how much LDS is asked for once per device,
+under a lock, by the first ccld_create on it (a source check: it runs without a GPU)."""
 import os
 import re
 
@@ -16,11 +16,14 @@ def test_no_mutable_statics_in_functions(name):
 
 
 def test_create_asks_for_every_kernel_with_more_lds_than_the_default():
-    create = FILES["api.hip"].split("ccld_status ccld_create(")[1].split("ccld_status ccld_destroy(")[0]
+    assert "ccld_device_init()" in FILES["api.hip"].split("ccld_status ccld_create(")[1].split("ccld_status ccld_destroy(")[0]
+    assert "device_scratch(" in FILES["hang.hip"].split("ccld_status ccld_device_init() {")[1].split("}")[0]
+    first = FILES["hang.hip"].split("ccld_status device_scratch(")[1].split("\n}")[0]
+    assert first.index("lock_guard") < first.index("allow_lds") < first.index("g_scratch_ptr[dev] =")
     for name, text in FILES.items():
         fn = re.findall(r"hipError_t (?:ccld::)?(allow_lds_\w+)\(\) \{", text)
         assert len(fn) == len(re.findall(r"hipError_t (?:ccld::)?allow_lds_\w+\(\) \{", text)) <= 1
         for f in fn:
-            assert f + "()" in create, (name, f)
+            assert f + "()" in first, (name, f)
         # nobody else sets the attribute
         assert text.count("hipFuncSetAttribute") == (1 if name == "ccld_internal.h" else 0), name
