@@ -7,6 +7,7 @@
 #include "ccld_internal.h"
 #include "window_kernels.h"
 #include "grid.h"
+#include "merge.h"
 
 using namespace ccld;
 
@@ -303,7 +304,8 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   c->stream = (hipStream_t)hip_stream;
   c->chain_ready = false;
   c->rank_bits = bits_for_host(topo->n_ranks - 1);
-  c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0;
+  c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0; c->total_ingested = 0;
+  c->inc_ok = false; c->inc_head = c->inc_count = c->inc_total = 0;
   c->sorted_buf = 0; c->last_n = 0; c->blame_valid = false; c->sort_passes = 0;
   c->sf.mb = mb; c->sf.ws = 0; c->sf.seq_base = 0;
   Carver w{(uint8_t*)workspace, 0};
@@ -424,6 +426,7 @@ ccld_status ccld_destroy(ccld_ctx* c) {
 ccld_status ccld_reset_window(ccld_ctx* c) {
   if (!c) return CCLD_E_NULL;
   c->head = 0; c->count = 0; c->batch_n.clear(); c->batch_slot.clear();
+  c->inc_ok = false;
   c->chain_ready = false;
   return CCLD_OK;
 }
@@ -492,6 +495,7 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   c->rounds_next = rounds_end;
   c->next_slot = next;
   c->head = head; c->count = count + n;
+  c->total_ingested += n;
   return CCLD_OK;
 }
 
@@ -675,6 +679,47 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   return finish_analysis(c, now_ns, o, sa, true, fallback);
 }
 
+// The order of a window that still holds at least half of the one that was sorted last: the new records are sorted on their
+// own and merged with that order, whose keys are re-based to this window's format and whose entries of the batches that
+// left are dropped on the way.  Half the time of sorting a window of ten batches again (20M records at 16,384 ranks in
+// 5,184 communicators: 0.25 instead of 0.49 ms, a step 1.18 instead of 1.49).  Returns the buffer of the result, -1 for a failed launch, -2 where
+// there is no such order.
+static int merge_new_records(ccld_ctx* c, const KeySource& src, uint32_t n) {
+  const uint64_t cap = std::max<uint64_t>(c->cap, 1), n_new = c->total_ingested - c->inc_total;
+  const int bits = src.lo_bits + c->kf.cb;
+  if (!c->inc_ok || n_new == 0 || n_new >= n || bits > 64 || src.lo_bits >= 64 || c->inc_sf.mb != c->sf.mb || c->inc_sf.mb + c->inc_sf.ws >= 64)
+    return -2;
+  const uint64_t kept = n - n_new, old_tail = (c->inc_head + c->inc_count) % cap;       // kept: records of that window still here
+  if (kept < n_new || kept > c->inc_count) return -2;
+  const uint64_t exp_n = c->inc_count - kept;
+  if ((c->inc_head + exp_n) % cap != c->head || (old_tail + n_new) % cap != (c->head + n) % cap) return -2;
+  // the new records end in a third pair of buffers (a sort of p passes ends in its buffer (p - 1) % 2), so that the merge can
+  // read the kept order where it lies and write beside it; flag_pos is written by the flags, later
+  const int s = c->sorted_buf, passes = bits <= 0 ? 1 : (bits + SORT_RBITS - 1) / SORT_RBITS, third = (passes - 1) % 2;
+  SortBuffers fresh;
+  fresh.key[third] = c->keyC; fresh.idx[third] = c->flag_pos;
+  fresh.key[1 - third] = c->sb.key[1 - s]; fresh.idx[1 - third] = c->sb.idx[1 - s];
+  fresh.table = c->table2; fresh.totals = c->totals2;
+  KeySource from = src;
+  from.head = (uint32_t)old_tail;
+  const int r = radix_sort_pairs(c->stream, from, (uint32_t)n_new, fresh, bits, &c->prof, CCLD_PROF_SORT_HIST, CCLD_PROF_SORT_SCAN,
+                                 CCLD_PROF_SORT_SCATTER);
+  if (r < 0) return -1;
+  if (r != third &&       // few records are sorted in one launch, whose result may be in the other pair
+      (hipMemcpyAsync(c->keyC, fresh.key[r], sizeof(uint64_t) * n_new, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
+       hipMemcpyAsync(c->flag_pos, fresh.idx[r], sizeof(uint32_t) * n_new, hipMemcpyDeviceToDevice, c->stream) != hipSuccess))
+    return -1;
+  c->prof.begin(CCLD_PROF_SORT_SCATTER);
+  RetainArgs ra;
+  ra.key = c->sb.key[s]; ra.idx = c->sb.idx[s]; ra.n = (uint32_t)c->inc_count; ra.from = c->inc_sf; ra.to = c->sf;
+  ra.exp_lo = (uint32_t)c->inc_head; ra.exp_n = (uint32_t)exp_n; ra.cap = (uint32_t)cap;
+  ra.tile_counts = c->tile_flags; ra.total_out = &c->counters[CNT_COUNT - 1];
+  ra.key_out = c->sb.key[1 - s]; ra.idx_out = c->sb.idx[1 - s];
+  launch_merge_kept(c->stream, ra, c->keyC, c->flag_pos, (uint32_t)n_new, c->tile_heads);
+  c->prof.end(CCLD_PROF_SORT_SCATTER);
+  return 1 - s;
+}
+
 // One analysis of the resident window by sorting it.
 static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_result* o) {
   hipStream_t st = c->stream;
@@ -714,8 +759,10 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   src.lo_bits = mb + ws;
   src.lo_mask = cb > 0 ? (((uint64_t)1 << (64 - cb)) - 1) : ~0ull;      // everything below the communicator field
   src.lo_sub = min_seq << mb;
-  const int sorted = radix_sort_pairs(st, src, n, c->sb, mb + ws + cb, &c->prof, CCLD_PROF_SORT_HIST,
-                                      CCLD_PROF_SORT_SCAN, CCLD_PROF_SORT_SCATTER);
+  int sorted = merge_new_records(c, src, n);
+  c->inc_ok = false;
+  if (sorted == -2)
+    sorted = radix_sort_pairs(st, src, n, c->sb, mb + ws + cb, &c->prof, CCLD_PROF_SORT_HIST, CCLD_PROF_SORT_SCAN, CCLD_PROF_SORT_SCATTER);
   c->sort_passes = (mb + ws + cb) <= 0 ? 1 : (mb + ws + cb + SORT_RBITS - 1) / SORT_RBITS;
   if (sorted < 0) return o->status = CCLD_E_HIP;
   c->sorted_buf = sorted;
@@ -745,7 +792,11 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   launch_blame_sums(st, fa, n_ranks, c->blame);
   c->prof.split(CCLD_PROF_BLAME, CCLD_PROF_GROUPS);
   bool fallback = false;
-  return finish_analysis(c, now_ns, o, sa, false, &fallback);
+  const ccld_status s = finish_analysis(c, now_ns, o, sa, false, &fallback);
+  // the order serves the next analysis (windows of several batches only)
+  c->inc_ok = s >= 0 && c->p.window_batches > 1;
+  c->inc_sf = c->sf; c->inc_head = c->head; c->inc_count = n; c->inc_total = c->total_ingested;
+  return s;
 }
 
 // a window without records: an all-zero blame table and the ranks in ascending order
@@ -781,6 +832,7 @@ ccld_status ccld_analyze_window(ccld_ctx* c, int64_t now_ns, ccld_window_result*
     bool fallback = !c->grid_capable;
     if (c->grid_capable) {
       take_ticket(c);
+      c->inc_ok = false;       // the grid's rows lie where the order is kept
       s = analyze_on_grid(c, now_ns, o, &fallback);
     }
     if (s >= 0 && fallback) s = analyze_sorted(c, now_ns, o);
@@ -789,6 +841,7 @@ ccld_status ccld_analyze_window(ccld_ctx* c, int64_t now_ns, ccld_window_result*
     (void)hipStreamSynchronize(c->stream);
     (void)hipGetLastError();
     c->prof.abandon();
+    c->inc_ok = false;
   }
   return s;
 }

@@ -203,6 +203,11 @@ struct ccld_ctx {
   bool last_grid;                     // the analysis ran on the grid placement
   ccld::WindowRows last_win;          // the window's rows
   uint32_t* chain_first;              // [n_comms + 2] first table row of each communicator
+  // the order of the latest analysis that sorted, for windows of several batches (merge.h)
+  uint64_t total_ingested;
+  bool inc_ok;                        // sb.key/idx[sorted_buf] hold it, in format inc_sf
+  ccld::SqueezedFormat inc_sf;
+  uint64_t inc_head, inc_count, inc_total;   // that window's first slot, records, and total_ingested at the time
   // last analysis
   int sorted_buf;                     // which ping-pong buffer holds the sorted window
   uint64_t last_n;

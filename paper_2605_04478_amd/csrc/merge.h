@@ -1,4 +1,4 @@
-// Keeping the window's order from one analysis to the next (windows of several batches): the sorted
+// Keeping the window's order from one analysis to the next (windows of several batches that are sorted): the sorted
 // (key, window slot) arrays of the previous analysis lose the records of the batches that left the
 // window and are re-based to the new window's key format while they are merged with the sorted new records.
 #pragma once

@@ -90,3 +90,68 @@ def test_kept_window_order_survives_odd_sequences():
         blame, order = an.rank_blame()
         compare(g, ref, blame, order, what=f"batch{i}")
     an.close()
+
+
+@pytest.mark.parametrize("wb,sizes", [(4, [7, 1, 0, 12, 3, 3, 25, 2, 9, 9, 4, 30, 1, 1, 6]), (2, [5, 5, 1, 6, 2]),
+                                      (3, [40, 20, 21, 19, 1, 0, 0, 1, 50, 2])])
+def test_kept_order_of_windows_that_are_sorted(wb, sizes):
+    """The same of windows that cannot be placed on a grid (one communicator has 2,100 members): the kept order, merged with
+    the new records, must be the one that sorting the window gives, whatever the sequence of calls; a batch with a
+    duplicate fails and leaves no order behind."""
+    from paper_2605_04478_amd import ccld
+    from tests.helpers import T0, concat_cols, toy_cols
+    from tests.test_gpu_window import FAR
+    from tests.test_oracle_hang import snap_rows
+    R = 2100
+    comms = [list(range(R))] + [[4 * c + i for i in range(4)] for c in range(60)] + [[5]]
+    topo = tg.make_topology(R, comms)
+    rng = np.random.default_rng(wb)
+
+    def batch(i):                                            # some communicators' counters run ahead, some stand still
+        rows = []
+        for j in range(starts[i], starts[i + 1]):
+            for c, mem in enumerate(comms):
+                if (c == 0 and j % 9) or (c and rng.random() < 0.1):
+                    continue
+                late = mem[int(rng.integers(0, len(mem)))]
+                for r in mem:
+                    te = T0 + j * 10**8 + int(rng.integers(0, 2000)) + (10**7 if r == late and j % 4 == 0 else 0)
+                    rows.append((r, c, (1 << 33) + j * (1 + 300 * (c == 7)), 0, 1 << 20, te, te + 10**6 + int(rng.integers(0, 3000))))
+        p = rng.permutation(len(rows))
+        return {k: v[p] for k, v in toy_cols(rows).items()}
+
+    starts = np.cumsum([0] + sizes)
+    batches = [batch(i) for i in range(len(sizes))]
+    n_b = [len(b["rank"]) for b in batches]
+    cap = max(sum(n_b[i:i + wb]) for i in range(len(n_b))) + 13
+    n_cells = int(topo.size.sum()) * 4
+    an = ccld.Analyzer(topo, max_window_records=cap, max_batch_records=max(n_b) + 1, window_batches=wb, max_snapshot_rows=n_cells, stall_snapshots=2)
+    o = orc.Oracle(topo, dict(window_batches=wb, stall_snapshots=2))
+    held = []
+    for i, b in enumerate(batches):
+        if i == 11:
+            an.reset_window()
+            held = []
+        if i == 4:                                           # a duplicate: an error, and the batch has to leave first
+            an.reset_window()
+            an.ingest(an.to_device(concat_cols(b, {k: v[:1] for k, v in b.items()})))
+            assert an.analyze_window(FAR, n_records=cap, seg_cap=cap).status == ("E_DUPLICATE_KEY" if len(b["rank"]) else "OK")
+            an.reset_window()
+            held = []
+        an.ingest(an.to_device(b))
+        held = (held + [b])[-wb:]
+        if i in (1, 9):                                      # no analysis after these ingests
+            continue
+        if i == 7:                                           # the hang pass sorts its roots in the same buffers
+            rows = snap_rows(topo, 4, 1, lambda s, c, q, ch: (3, 5, 5) if q else (2, 9, 9))
+            h = an.locate_hang(an.snapshots_to_device(rows), 4, 1, root_cap=n_cells)
+            assert h.status == "OK" and h.n_root > 0
+        cols = {k: np.concatenate([w[k] for w in held]) for k in b}
+        n = len(cols["rank"])
+        g = an.analyze_window(FAR, n_records=max(n, 1), per_record=True)
+        ref = o.analyze_window(cols, FAR)
+        compare(g, ref, *an.rank_blame(), what=f"batch{i}")
+        if g.n_flag:
+            st, chain, per_rank = an.flag_chains(g)
+            assert st == "OK" and len(chain["parent"]) == g.n_flag
+    an.close()
