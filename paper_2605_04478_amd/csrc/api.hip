@@ -531,8 +531,8 @@ static void zero_counts(ccld_window_result* o) {
 }
 
 // Waits for the number of fine buckets of a layout (a window large enough that launching for the most there could be
-// would cost more than the wait): 0 = the layout is not feasible.
-static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine) {
+// would cost more than the wait): 0 = the layout is not feasible.  *full: there may be a record for every cell.
+static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine, bool* full) {
   const uint32_t* word = reinterpret_cast<const uint32_t*>(c->h_pinned + PINNED_FINE);
   const auto t0 = std::chrono::steady_clock::now();
   uint32_t v;
@@ -545,7 +545,8 @@ static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine) {
     }
     __builtin_ia32_pause();
   }
-  *n_fine = (v & 0x80000000u) ? 0u : v - 1;
+  *full = (v & GRID_FULL) != 0;
+  *n_fine = (v & GRID_INFEASIBLE) ? 0u : (v & ~GRID_FULL) - 1;
   return hipSuccess;
 }
 // Most fine buckets that a launch is sized for without asking for their number.
@@ -665,7 +666,9 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   uint32_t fine = d.fine_cap;
   if (fine > FINE_BOUND) {
     HIP_TRY(hipGetLastError());
-    HIP_TRY(wait_fine(c, &fine));
+    bool full;
+    HIP_TRY(wait_fine(c, &fine, &full));
+    if (fine && !full) launch_grid_gaps(st, d, fine);
   }
   if (fine) launch_grid_stats(st, sa, d, fine, c->blame, n_ranks);
   c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);

@@ -82,13 +82,17 @@ struct GridArgs {
   uint64_t* counters;
   uint64_t* blame;               // cleared here: [n_blame] words
   uint32_t n_blame;
-  // pinned host words: 1 + fine buckets once the layout is known (0x80000000: it is not feasible)
+  // pinned host word: 1 + fine buckets once the layout is known, GRID_FULL if the window has as many records as the grid has
+  // cells (GRID_INFEASIBLE: it is not feasible)
   uint32_t* host_fine;
 };
+constexpr uint32_t GRID_INFEASIBLE = 0x80000000u, GRID_FULL = 0x40000000u;
 constexpr uint32_t GRID_EMPTY = 0xFFFFu;
 
 void launch_grid_layout(hipStream_t st, const GridArgs& d);
 void launch_grid_partition(hipStream_t st, const GridArgs& d);
+// ends the placement of a window that has a round without any record (behind the partition)
+void launch_grid_gaps(hipStream_t st, const GridArgs& d, uint32_t n_fine);
 
 // statistics of every collective (segments.hip); fine_bound: no fewer than the layout's fine buckets
 void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks);

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     if (s_status) d.counters[CNT_STATUS] = s_status;
     else if (!ok) d.counters[CNT_STATUS] = DS_DENSE_FALLBACK;
     d.counters[CNT_NSEG] = ok ? seg_carry : 0;
-    __hip_atomic_store(d.host_fine, ok ? n_fine + 1 : 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(d.host_fine, ok ? (n_fine + 1) | (cell_carry == d.n ? GRID_FULL : 0u) : GRID_INFEASIBLE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -375,6 +375,50 @@ void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   const u32 g = std::min<u32>(PART_BLOCKS, std::max<u32>((d.n + PART_THREADS - 1) / PART_THREADS, 1));
   if (d.slots) hipLaunchKernelGGL(k_grid_partition<true>, dim3(g), dim3(PART_THREADS), PART_LDS_SLOTS, st, d);
   else hipLaunchKernelGGL(k_grid_partition<false>, dim3(g), dim3(PART_THREADS), PART_LDS, st, d);
+}
+
+// ---- rounds without any record ------------------------------------------------------------------------
+// The statistics find them too, but behind them the whole window has still to be sorted: here they end the placement of a
+// window whose statistics take long, before these run.  A round can only be missing from a fine bucket that has at least
+// that many records fewer than cells; such buckets mark the rounds of their rows, a wavefront each.  Taken by windows of
+// more than FINE_BOUND fine buckets that have fewer records than cells: 20M records with one round missing 1.99 -> 1.79 ms,
+// the steps of a 20M-record stream that have one in the window 1.41 -> 1.27; where no round is missing it costs 5 us.
+constexpr u32 GAP_THREADS = 256, GAP_BLOCKS = 2048;
+__global__ __launch_bounds__(GAP_THREADS) void k_grid_gaps(GridArgs d) {
+  constexpr u32 NW = GAP_THREADS / CCLD_WAVE, WORDS = GRID_B / 32, U = 8;
+  static_assert(WORDS <= CCLD_WAVE, "a word of the bitmap per lane");
+  __shared__ u32 s_round[NW][WORDS];
+  const u32 n_fine = d.hdr->n_fine, lane = lane_id(), wave = threadIdx.x / CCLD_WAVE;
+  u32* const mark = s_round[wave];
+  for (u32 f = blockIdx.x * NW + wave; f < n_fine; f += gridDim.x * NW) {
+    const FineDesc D = d.desc[f];
+    const u32 cells = D.K * D.size, cnt = d.rec0[f + 1] - d.rec0[f];
+    if (cnt + D.size > cells) continue;
+    if (lane < WORDS) mark[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    for (u32 i0 = lane; i0 < cnt; i0 += U * CCLD_WAVE) {
+      u32 y[U];
+#pragma unroll
+      for (u32 u = 0; u < U; ++u) y[u] = i0 + u * CCLD_WAVE < cnt ? d.rows[D.cell0 + i0 + u * CCLD_WAVE].y : ~0u;
+#pragma unroll
+      for (u32 u = 0; u < U; ++u) {
+        const u32 cell = (y[u] >> ROW_CELL_SHIFT) & ROW_CELL_MASK, round = cell / D.size;
+        if (i0 + u * CCLD_WAVE < cnt && round < D.K) atomicOr(&mark[round >> 5], 1u << (round & 31));
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const u32 left = lane * 32 < D.K ? D.K - lane * 32 : 0u, want = left >= 32 ? ~0u : (1u << left) - 1;
+    const u32 have = lane < WORDS ? mark[lane] : 0u;
+    if (have != want && lane < WORDS) {
+      atomicOr((unsigned long long*)&d.counters[CNT_STATUS], (unsigned long long)DS_DENSE_FALLBACK);
+      d.hdr->feasible = 0;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+void launch_grid_gaps(hipStream_t st, const GridArgs& d, uint32_t n_fine) {
+  const u32 blocks = std::min<u32>((n_fine + 3) / 4, GAP_BLOCKS);
+  hipLaunchKernelGGL(k_grid_gaps, dim3(blocks), dim3(GAP_THREADS), 0, st, d);
 }
 
 }  // namespace ccld

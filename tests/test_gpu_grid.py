@@ -110,3 +110,48 @@ def test_order_of_arrival_over_many_ingest_rounds(disjoint, step):
         assert np.array_equal(res.per_record()["perm"], np.lexsort((win["rank"], win["seq"], win["comm"])))
         prev = b
     an.close()
+
+
+GAP_SIZES = [1, 2, 3, 31, 64, 65, 700, 2048]
+
+
+@pytest.mark.parametrize("comm,place", [(0, 1), (0, 2047), (0, 2048), (0, 2078), (1, 1023), (1, 1024), (2, 681), (2, 700), (3, 66), (4, 31),
+                                        (4, 40), (5, 30), (6, 1), (7, 2), (None, 0), (None, 1)])
+def test_rounds_that_nobody_recorded_in_large_layouts(comm, place):
+    """Layouts of more than 4,096 fine buckets, where a round without any record is looked for before the statistics: in the
+    first and last rounds of fine buckets and words of their bitmaps, for communicators of 1 to 2,048 members; and
+    windows that only lack single records, which stay on the grid."""
+    from paper_2605_04478_amd import ccld
+    rng = np.random.default_rng(place)
+    many = 3_500
+    R = 4096
+    comms = [list(range(n)) for n in GAP_SIZES] + [[int(x) for x in rng.choice(R, 2, replace=False)] for _ in range(many)]
+    rounds = [2100, 1100, 720, 140, 70, 64, 6, 4] + [20] * many
+    cols = {k: [] for k in ("rank", "comm", "seq", "t_enter")}
+    for c, (mem, n) in enumerate(zip(comms, rounds)):
+        q = np.repeat(np.arange(n), len(mem))
+        keep = np.ones(q.size, dtype=bool)
+        if comm is None and place and len(mem) > 1:          # a record missing here and there, never a whole round
+            keep = (np.tile(np.arange(len(mem)), n) == q % len(mem)) | (rng.random(q.size) > 0.05)
+        if c == comm:
+            keep = q != place
+        cols["rank"].append(np.tile(mem, n)[keep])
+        cols["comm"].append(np.full(keep.sum(), c))
+        cols["seq"].append(10 + q[keep])
+        cols["t_enter"].append(T0 + q[keep] * 1_000_000 + rng.integers(0, 900_000, keep.sum()))
+    cols = {k: np.concatenate(v) for k, v in cols.items()}
+    n = cols["rank"].size
+    cols["t_exit"] = cols["t_enter"] + rng.integers(0, 3_000_000, n)
+    p = rng.permutation(n)
+    dt = {"rank": np.uint32, "comm": np.uint32, "seq": np.uint64, "t_enter": np.int64, "t_exit": np.int64}
+    cols = {k: v[p].astype(dt[k]) for k, v in cols.items()}
+    cols["op"], cols["bytes"] = np.zeros(n, dtype=np.uint8), np.full(n, 1 << 20, dtype=np.uint64)
+    topo = tg.make_topology(R, comms)
+    an = ccld.Analyzer(topo, max_window_records=4_000_000, max_batch_records=n)
+    an.ingest(an.to_device(cols))
+    an.profile_enable(True)
+    g, ref = an.analyze_window(FAR, n_records=n, per_record=True), orc.Oracle(topo).analyze_window(cols, FAR)
+    compare(g, ref, *an.rank_blame(), what=f"gap at {comm}, {place}")
+    times, _ = an.profile_read()
+    assert (times["sort_hist"][1] > 0) == (comm is not None)
+    an.close()
