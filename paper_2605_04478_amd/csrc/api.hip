@@ -306,12 +306,11 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   c->rank_bits = bits_for_host(topo->n_ranks - 1);
   c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0; c->total_ingested = 0;
   c->inc_ok = false; c->inc_head = c->inc_count = c->inc_total = 0;
-  c->sorted_buf = 0; c->last_n = 0; c->blame_valid = false; c->sort_passes = 0;
+  c->sorted_buf = 0; c->blame_valid = false; c->sort_passes = 0;
   c->sf.mb = mb; c->sf.ws = 0; c->sf.seq_base = 0;
   Carver w{(uint8_t*)workspace, 0};
   carve_all(c, w, topo->n_ranks, topo->n_comms, n_members);
   c->topo.n_ranks = topo->n_ranks; c->topo.n_comms = topo->n_comms;
-  c->h_size.assign(topo->size, topo->size + topo->n_comms);
   c->h_pinned = nullptr;
   c->ticket = 0;
 
@@ -827,7 +826,6 @@ ccld_status ccld_analyze_window(ccld_ctx* c, int64_t now_ns, ccld_window_result*
   if ((o->flag_cap && !o->flag) || (o->group_cap && !o->group) || (o->alert_cap && !o->alert) ||
       (o->cand_cap && !o->cand))
     return o->status = CCLD_E_NULL;
-  c->last_n = c->count;
   ccld_status s = CCLD_OK;
   if (c->count == 0) {
     s = analyze_empty(c, o);

@@ -116,7 +116,6 @@ struct ccld_ctx {
   ccld::KeyFormat kf;
   int rank_bits;                      // bit width of the largest rank
   // topology
-  std::vector<uint32_t> h_size;
   ccld::DeviceTopology topo;
   // window (circular)
   uint64_t head, count;
@@ -210,7 +209,6 @@ struct ccld_ctx {
   uint64_t inc_head, inc_count, inc_total;   // that window's first slot, records, and total_ingested at the time
   // last analysis
   int sorted_buf;                     // which ping-pong buffer holds the sorted window
-  uint64_t last_n;
   ccld::SqueezedFormat sf;
   bool blame_valid;
   ccld::Profiler prof;

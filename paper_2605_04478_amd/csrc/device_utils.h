@@ -33,10 +33,6 @@ __device__ __forceinline__ u64 shfl_u64(u64 v, int src) {
   u32 lo = __shfl((u32)v, src, CCLD_WAVE), hi = __shfl((u32)(v >> 32), src, CCLD_WAVE);
   return ((u64)hi << 32) | lo;
 }
-__device__ __forceinline__ u64 shfl_up_u64(u64 v, int d) {
-  u32 lo = __shfl_up((u32)v, d, CCLD_WAVE), hi = __shfl_up((u32)(v >> 32), d, CCLD_WAVE);
-  return ((u64)hi << 32) | lo;
-}
 __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int m) {
   u32 lo = __shfl_xor((u32)v, m, CCLD_WAVE), hi = __shfl_xor((u32)(v >> 32), m, CCLD_WAVE);
   return ((u64)hi << 32) | lo;
@@ -104,10 +100,6 @@ __device__ __forceinline__ bool last_block(u32* done, u32 blocks, u32* s_last) {
   if (threadIdx.x == 0) *s_last = atomicAdd(done, 1u) + 1 == blocks;
   __syncthreads();
   return *s_last != 0;
-}
-
-__device__ __forceinline__ int bits_for(u64 max_value) {   // bits needed to store 0..max_value
-  return max_value == 0 ? 0 : 64 - __clzll((long long)max_value);
 }
 
 }  // namespace ccld

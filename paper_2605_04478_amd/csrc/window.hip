@@ -22,14 +22,6 @@ __device__ __forceinline__ u64 atomic_add_u64(u64* p, u64 v) {
 __global__ __launch_bounds__(256) void k_fill_u64(u64* p, u64 n, u64 v) {
   for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) p[i] = v;
 }
-__global__ __launch_bounds__(256) void k_fill_u32(u32* p, u64 n, u32 v) {
-  for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) p[i] = v;
-}
-static void launch_fill_u32(hipStream_t st, uint32_t* p, uint64_t n, uint32_t v) {
-  if (n == 0) return;
-  u32 g = (u32)((n + 255) / 256); if (g > 4096) g = 4096;
-  hipLaunchKernelGGL(k_fill_u32, dim3(g), dim3(256), 0, st, p, n, v);
-}
 void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v) {
   if (n == 0) return;
   u32 g = (u32)((n + 255) / 256); if (g > 4096) g = 4096;
