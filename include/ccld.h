@@ -14,8 +14,12 @@
  *    caller's workspace (ccld_query_workspace / ccld_create).  It never frees or
  *    keeps caller memory other than that workspace.
  *  - All work is enqueued on the HIP stream given to ccld_create.  Calls that
- *    return counts (analyze, locate, blame) synchronise that stream before they
- *    return; ccld_ingest does not.
+ *    return counts or a status of their data (analyze, blame, chains, locate, rates,
+ *    frames) return when their output tables are complete in device memory, for any
+ *    stream and for copies to the host, and their inputs have been read.  The stream
+ *    may then still be ending its last kernel, which touches nothing of the caller's:
+ *    only the stream itself says when it has drained.  ccld_ingest returns before the
+ *    records are read, unless they are in host memory.
  *  - Every function returns a ccld_status: 0 = CCLD_OK, negative = error,
  *    positive = warning.  Nothing throws, aborts or prints.
  *  - Output tables are column-major int64 matrices: column c of a table with

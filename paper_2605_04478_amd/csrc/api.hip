@@ -499,8 +499,8 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
 }
 
 // Waits until the device has reported the counters of the current ticket into pinned memory.  The report is the last
-// thing on the stream, so the stream has drained then; spinning on the word costs about 10 us less than copying the
-// counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
+// thing on the stream: what the caller asked for is in memory by then, although the reporting kernel may still be on its way
+// out.  Spinning on the words costs about 10 us less than copying the counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
 // hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
 static bool reported(const ccld_ctx* c, int words) {
   for (int i = 0; i < words; ++i)

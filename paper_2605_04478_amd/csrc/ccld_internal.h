@@ -196,7 +196,7 @@ struct ccld_ctx {
   uint32_t* flag_stage;               // [cap]
   uint32_t fine_cap, cell_cap;
   // what ccld_flag_chains needs of the most recent analysis
-  bool chain_ready;                   // the sorted order, flag positions and lags of that analysis are still in the workspace
+  bool chain_ready;                   // its order (sorted or on the grid), flag positions and lags are still in the workspace
   const int64_t* last_seg; uint64_t last_seg_cap, last_n_seg, last_n_flag;
   const uint8_t* last_rec_flag;
   bool last_grid;                     // the analysis ran on the grid placement

@@ -13,7 +13,8 @@ namespace ccld {
 // bucket.  The layout is infeasible (the host then sorts) when the grid has more cells or rounds than the buffers and
 // the records allow (counters that are far apart), when a coarse bucket spans more fine buckets than a partition
 // workgroup addresses, or when the batches lie so far apart that no single time serves all rows.
-// Bound by the latency of its few dependent loads: 4 to 8 us at 1,088 to 3,200 communicators.
+// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 11 to 13 us at 1,088
+// communicators and one batch, 31 us at 3,200 and ten.
 __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   __shared__ u32 s_wave[1024 / CCLD_WAVE];
   __shared__ u32 s_bad, s_any;

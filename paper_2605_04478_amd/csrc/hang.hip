@@ -1158,7 +1158,7 @@ __device__ __forceinline__ uint4 block_counts(const uint8_t* F, u32 b, u32 ch) {
 }
 
 // The validity checks, before anything is remembered: one wavefront per frame, lane = 8 * block + channel.  All of a frame's
-// loads are in flight together; what the kernel takes (6 us at 4,096 frames) is that one trip to memory, the lookup
+// loads are in flight together; what the kernel takes (4 us at 4,096 frames) is that one trip to memory, the lookup
 // of the rank and the exchange that finds a second frame of it.
 __global__ __launch_bounds__(256) void k_frames_check(FrameArgs a) {
   const u32 lane = lane_id();

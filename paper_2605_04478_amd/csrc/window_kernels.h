@@ -99,8 +99,8 @@ void launch_keys_pass(hipStream_t st, const uint64_t* key, uint32_t n, const Squ
                       const DeviceTopology& T, int64_t* blame, uint32_t* tile_heads, uint64_t* counters);
 // adds the flag list (its length is read from the counters) to the late columns of the blame table
 void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int64_t* blame);
-// order[] = ranks by (flags, summed lag, rank); then the counters go to host_counters, followed by `ticket` in
-// host_counters[CNT_COUNT] (pinned host memory): the last words of an analysis
+// order[] = ranks by (flags, summed lag, rank); then the counters are reported to host_counters (pinned host memory), each
+// word with `ticket`: the last words of an analysis
 void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, uint32_t* lists,
                         uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
                         uint64_t ticket);

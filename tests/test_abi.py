@@ -44,8 +44,9 @@ def test_host_only_calls():
 
 def test_workspace_sizes_of_the_benchmark_configuration():
     """ccld_query_workspace is host arithmetic: the 82M-record window of the 4,096-rank layout needs about 10 GiB
-    with the default placement (window 40 B, sort buffers 36 B and per-record scratch 57 B per record; host batches
-    are staged inside that scratch) and about 13 GiB with the dense placement's partition buffers."""
+    with the default placement (window 48 B, sort buffers 32 B, over which the grid's rows lie, and per-record scratch
+    51 B per record; host batches are staged inside that scratch) and about 13 GiB with the dense placement, whose
+    partitioned rows lie apart."""
     import numpy as np
     from paper_2605_04478_amd import tracegen as tg
     L = ccld.lib()

@@ -48,10 +48,11 @@ def test_streaming_window_matches_oracle_every_step():
 
 
 def test_kept_window_order_survives_odd_sequences():
-    """Windows of several batches keep the previous window's order and merge the new records into it.
-    Here the sequence of calls varies: several ingests between two analyses, an empty batch, batches
+    """Windows of several batches that are placed on the grid, which keep nothing from one analysis to the next but the
+    detection state.  The sequence of calls varies: several ingests between two analyses, an empty batch, batches
     of very different sizes, a hang location in between (it borrows the sort buffers), a reset, and
-    operation counters that move the window's key format from step to step."""
+    operation counters that move the grid from step to step.  (The next test has windows that are sorted, whose order is
+    kept.)"""
     from paper_2605_04478_amd import ccld
     from tests.test_gpu_window import FAR
     from tests.test_oracle_hang import snap_rows
@@ -95,7 +96,7 @@ def test_kept_window_order_survives_odd_sequences():
 @pytest.mark.parametrize("wb,sizes", [(4, [7, 1, 0, 12, 3, 3, 25, 2, 9, 9, 4, 30, 1, 1, 6]), (2, [5, 5, 1, 6, 2]),
                                       (3, [40, 20, 21, 19, 1, 0, 0, 1, 50, 2])])
 def test_kept_order_of_windows_that_are_sorted(wb, sizes):
-    """The same of windows that cannot be placed on a grid (one communicator has 2,100 members): the kept order, merged with
+    """The same with windows that cannot be placed on a grid (one communicator has 2,100 members): the kept order, merged with
     the new records, must be the one that sorting the window gives, whatever the sequence of calls; a batch with a
     duplicate fails and leaves no order behind."""
     from paper_2605_04478_amd import ccld
