@@ -499,9 +499,10 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
 }
 
 // Waits until the device has reported the counters of the current ticket into pinned memory.  The report is the last
-// thing on the stream: what the caller asked for is in memory by then, although the reporting kernel may still be on its way
-// out.  Spinning on the words costs about 10 us less than copying the counters with a queued copy and synchronising.  A wait that takes long (a very large window, or a device error) ends in
-// hipStreamSynchronize, as does every wait while spans are timed (their events must have completed).
+// thing on the stream: what the caller asked for is in memory by then, although the reporting kernel may still be on its
+// way out.  Spinning on the words costs about 10 us less than copying the counters with a queued copy and synchronising.
+// A wait that takes long (a very large window, or a device error) ends in hipStreamSynchronize, as does every wait while
+// spans are timed (their events must have completed).
 static bool reported(const ccld_ctx* c, int words) {
   for (int i = 0; i < words; ++i)
     if (!report_arrived(__atomic_load_n(c->h_pinned + i, __ATOMIC_RELAXED), c->ticket)) return false;
@@ -684,8 +685,8 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
 // The order of a window that still holds at least half of the one that was sorted last: the new records are sorted on their
 // own and merged with that order, whose keys are re-based to this window's format and whose entries of the batches that
 // left are dropped on the way.  Half the time of sorting a window of ten batches again (20M records at 16,384 ranks in
-// 5,184 communicators: 0.25 instead of 0.49 ms, a step 1.18 instead of 1.49).  Returns the buffer of the result, -1 for a failed launch, -2 where
-// there is no such order.
+// 5,184 communicators: 0.25 instead of 0.49 ms, a step 1.18 instead of 1.49).  Returns the buffer of the result, -1 for a
+// failed launch, -2 where there is no such order.
 static int merge_new_records(ccld_ctx* c, const KeySource& src, uint32_t n) {
   const uint64_t cap = std::max<uint64_t>(c->cap, 1), n_new = c->total_ingested - c->inc_total;
   const int bits = src.lo_bits + c->kf.cb;
