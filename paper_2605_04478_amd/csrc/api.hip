@@ -5,6 +5,7 @@
 #include <new>
 
 #include "ccld_internal.h"
+#include "device_utils.h"
 #include "window_kernels.h"
 #include "grid.h"
 #include "merge.h"
@@ -119,6 +120,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   if (w.off - scratch_begin < B * 48) (void)w.take<uint8_t>(B * 48 - (w.off - scratch_begin));
   c->gstate = w.take<GroupState>((uint64_t)n_comms * GROUP_SLOTS);
   c->chain_first = w.take<uint32_t>((uint64_t)n_comms + 2);
+  c->arrivals = w.take<uint32_t>(ARRIVAL_WORDS);
   // the counters and the blame table are cleared together at the start of every analysis
   c->counters = w.take<uint64_t>(CNT_COUNT);
   c->blame = w.take<int64_t>((uint64_t)CCLD_BLM_NCOL * n_ranks);
@@ -391,6 +393,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (c->comm_range && hipMemsetAsync(c->comm_range, 0, 16ull * topo->n_comms * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->ing_done, 0, sizeof(uint32_t), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
+  if (hipMemsetAsync(c->arrivals, 0, sizeof(uint32_t) * ARRIVAL_WORDS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
   c->f_status = c->f_frame + topo->n_ranks;
   if (hipMemsetAsync(c->f_frame, 0, 8ull * ((uint64_t)topo->n_ranks + 1), c->stream) != hipSuccess) rs = CCLD_E_HIP;
@@ -552,20 +555,28 @@ static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine, bool* full) {
 // Most fine buckets that a launch is sized for without asking for their number.
 constexpr uint32_t FINE_BOUND = 4096;
 
-// Everything behind the statistics and the flags: groups, the blame order and the report of the counters.
-static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_result* o, const SegArgs& sa, bool grid, bool* fallback) {
+// The last launches of an analysis: groups, flags (d and f: a window on the grid placement), blame order, report.
+static void launch_end(ccld_ctx* c, EndArgs& e, const GridArgs* d, const FlagArgs* f, uint32_t fine) {
+  e.counters = c->counters; e.blame = c->blame; e.n_ranks = c->topo.n_ranks; e.order = c->blame_order;
+  e.arrivals = c->arrivals; e.host = c->h_pinned; e.ticket = c->ticket;
+  if (!launch_window_end(c->stream, e, d, f, fine))
+    launch_blame_order(c->stream, c->blame, c->topo.n_ranks, c->blame_list, c->blame_tiles, c->counters, c->arrivals, c->blame_order, c->h_pinned, c->ticket);
+}
+
+// Everything behind the statistics: what the last launch does, its report, and the alerts.  d, f and fine are those of a window
+// on the grid placement.
+static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_result* o, const SegArgs& sa, const GridArgs* d, const FlagArgs* f,
+                                   uint32_t fine, bool* fallback) {
   hipStream_t st = c->stream;
-  // slow detection and location per detection group (Eq. 1-4)
-  GroupArgs ga;
-  std::memset(&ga, 0, sizeof(ga));
-  ga.seg = o->seg; ga.seg_cap = o->seg_cap; ga.counters = c->counters; ga.gcode = c->gcode; ga.range_c = c->range_c;
-  ga.n_comms = c->topo.n_comms; ga.comm_groups = c->comm_groups; ga.comm_row = c->comm_row;
-  ga.stage[0] = c->alert_list; ga.stage[1] = c->alert_ncand; ga.stage[2] = c->chain_parent;      // nothing lives there yet
-  ga.gstate = c->gstate; ga.rate_root = c->rate_root; ga.group = o->group; ga.group_cap = o->group_cap; ga.p = c->p;
-  launch_groups(st, ga);
+  const bool grid = d != nullptr;
+  EndArgs e;
+  std::memset(&e, 0, sizeof(e));
+  e.seg = o->seg; e.seg_cap = o->seg_cap; e.gcode = c->gcode; e.range_c = c->range_c; e.n_comms = c->topo.n_comms;
+  e.gstate = c->gstate; e.rate_root = c->rate_root; e.group = o->group; e.group_cap = o->group_cap; e.p = c->p;
+  e.comm_groups = c->comm_groups; e.comm_row = c->comm_row;
+  e.stage[0] = c->alert_list; e.stage[1] = c->alert_ncand; e.stage[2] = c->chain_parent;      // nothing lives there yet
+  launch_end(c, e, d, f, fine);
   c->prof.end(CCLD_PROF_GROUPS);
-  // the blame order is ready when ccld_rank_blame asks for it; its kernel reports the counters
-  launch_blame_order(st, c->blame, c->topo.n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   if (c->h_pinned[CNT_STATUS]) {
@@ -671,15 +682,13 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
     if (fine && !full) launch_grid_gaps(st, d, fine);
   }
   if (fine) launch_grid_stats(st, sa, d, fine, c->blame, n_ranks);
-  c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_FLAGS);
+  c->prof.split(CCLD_PROF_SEGMENTS, CCLD_PROF_GROUPS);
   FlagArgs fa;
   std::memset(&fa, 0, sizeof(fa));
   fa.flag_lag = c->flag_lag; fa.cap_n = c->cap; fa.n = n; fa.member_off = c->topo.member_off; fa.members_sorted = c->topo.members_sorted;
   fa.flag_pos = c->flag_pos; fa.flag_key = c->flag_key; fa.flag_stage = c->flag_stage; fa.flag = o->flag; fa.flag_cap = o->flag_cap;
   fa.counters = c->counters;
-  if (fine) launch_grid_flags(st, d, fa, fine);
-  c->prof.split(CCLD_PROF_FLAGS, CCLD_PROF_GROUPS);
-  return finish_analysis(c, now_ns, o, sa, true, fallback);
+  return finish_analysis(c, now_ns, o, sa, &d, &fa, fine, fallback);
 }
 
 // The order of a window that still holds at least half of the one that was sorted last: the new records are sorted on their
@@ -795,7 +804,7 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   launch_blame_sums(st, fa, n_ranks, c->blame);
   c->prof.split(CCLD_PROF_BLAME, CCLD_PROF_GROUPS);
   bool fallback = false;
-  const ccld_status s = finish_analysis(c, now_ns, o, sa, false, &fallback);
+  const ccld_status s = finish_analysis(c, now_ns, o, sa, nullptr, nullptr, 0, &fallback);
   // the order serves the next analysis (windows of several batches only)
   c->inc_ok = s >= 0 && c->p.window_batches > 1;
   c->inc_sf = c->sf; c->inc_head = c->head; c->inc_count = n; c->inc_total = c->total_ingested;
@@ -809,7 +818,9 @@ static ccld_status analyze_empty(ccld_ctx* c, ccld_window_result* o) {
   HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
   HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
   take_ticket(c);
-  launch_blame_order(st, c->blame, n_ranks, c->blame_list, c->blame_tiles, c->counters, c->blame_order, c->h_pinned, c->ticket);
+  EndArgs e;
+  std::memset(&e, 0, sizeof(e));
+  launch_end(c, e, nullptr, nullptr, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   c->blame_valid = true;
@@ -852,8 +863,7 @@ ccld_status ccld_rank_blame(ccld_ctx* c, int64_t* blame, uint32_t* order) {
   if (!c) return CCLD_E_NULL;
   if (!c->blame_valid) return CCLD_E_BAD_ARG;
   const uint32_t n_ranks = c->topo.n_ranks;
-  launch_blame_out(c->stream, c->blame, c->blame_order, n_ranks, blame, order);
-  launch_report(c->stream, c->counters, c->h_pinned, take_ticket(c));
+  launch_blame_out(c->stream, c->blame, c->blame_order, n_ranks, blame, order, c->counters, c->arrivals, c->h_pinned, take_ticket(c));
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   return CCLD_OK;

@@ -158,6 +158,7 @@ struct ccld_ctx {
   uint2* comm_info;                   // [n_comms] (first member index, members) of every communicator: one load for both
   ccld::GroupState* gstate;           // [n_comms][GROUP_SLOTS]
   uint64_t* counters;                 // [CNT_COUNT] device
+  uint32_t* arrivals;                 // [ARRIVAL_WORDS] of the kernels whose last workgroup reports; zero between launches
   uint32_t max_comm_size;             // members of the largest communicator
   uint32_t long_classes;              // which sizes beyond 64 members there are (SegArgs)
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)

@@ -1,9 +1,13 @@
-// Slow-detection rules (Eq. 1-4) per detection group for gfx950.  The collective table is in (communicator,
-// operation counter) order, so a communicator's collectives are one run of rows and a group (communicator, op,
-// size class) is a subset of that run in ascending counter order: one workgroup per communicator accumulates
-// all of its groups in LDS, with no sort.
-#include "window_kernels.h"
+// The end of an analysis, in two launches: what follows from the statistics alone (k_window_lists: the slow-detection rules
+// of Eq. 1-4 per detection group, the flag list of a window on the grid placement, the blame order; workgroups of their own
+// for each), then the group table and the report of the counters (k_window_end).
+#include <algorithm>
+
+#include "blame_order.h"
 #include "device_utils.h"
+#include "grid.h"
+#include "report.h"
+#include "window_kernels.h"
 
 namespace ccld {
 
@@ -12,6 +16,7 @@ constexpr u32 GC_BATCH = 64;               // groups still averaging their basel
 constexpr u32 GC_WALK = 8;                 // rows of one thread per step of that walk (a byte of a word each)
 constexpr u32 GC_NONE = 0xFFFFFFFFu;
 
+// ---- groups -------------------------------------------------------------------------------------------------
 // first row of the table with communicator >= c, found by one wavefront (64 probes per step)
 __device__ __forceinline__ u32 first_row_of(const i64* __restrict__ comm, u32 n, u32 c, u32 lane) {
   u32 lo = 0, hi = n;
@@ -38,27 +43,32 @@ __device__ __forceinline__ u32 first_row_of(const i64* __restrict__ comm, u32 n,
 // for long has in its first few thousand rows (see the walk for the times).
 // At 8.4M collectives of 1,088 communicators this replaces a three-pass sort of the collectives by group (0.23 ms)
 // and a wavefront per group (0.13 ms).
-// What is left per group for k_group_emit, in the order of the (op, class) codes at the communicator's rows:
+// What is left per group for k_window_end, in the order of the (op, class) codes at the communicator's rows:
 // stage[0] = code | dynamic << 10 | slow << 11 | class << 12, stage[1] = row of Eq. 2's round, stage[2] = usable rounds.
-// (Four workgroups per compute unit: with the registers that the compiler takes by itself there are three, and a stream's 3,200
-// communicators take 49 us instead of 38.)
-__global__ __launch_bounds__(GC_THREADS, 8) void k_group_comm(GroupArgs a) {
-  __shared__ u32 s_cnt[GROUP_SLOTS], s_row[GROUP_SLOTS], s_last[GROUP_SLOTS];
-  __shared__ unsigned long long s_best[GROUP_SLOTS];
-  __shared__ unsigned short s_list[GROUP_SLOTS];
-  __shared__ u32 s_wave[GC_THREADS / CCLD_WAVE];
-  __shared__ u32 s_lo, s_hi, s_need, s_left, s_n_rank;
+struct GroupShared {
+  unsigned long long best[GROUP_SLOTS];
+  u32 cnt[GROUP_SLOTS], row[GROUP_SLOTS], last[GROUP_SLOTS];
+  unsigned short list[GROUP_SLOTS];
+  uint8_t map[GROUP_SLOTS];
   // the batch of groups that Eq. 1 has new rounds for
-  __shared__ uint8_t s_map[GROUP_SLOTS];
-  __shared__ unsigned long long s_wm[GC_BATCH], s_sum[GC_BATCH];
-  __shared__ i64 s_t0[GC_BATCH];
-  __shared__ unsigned long long s_min_wm;
-  __shared__ u32 s_i0[GC_BATCH], s_istar[GC_BATCH], s_new[GC_BATCH], s_lim[GC_BATCH], s_seen[GC_BATCH], s_m[GC_BATCH],
-      s_lastb[GC_BATCH], s_code[GC_BATCH], s_rank[GC_BATCH];
-  // a data error found by an earlier kernel of this analysis: the tables are not valid and the detection state
-  // stays as it is
-  if (a.counters[CNT_STATUS] != 0) return;
-  const u32 c = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  unsigned long long wm[GC_BATCH], sum[GC_BATCH], min_wm;
+  i64 t0[GC_BATCH];
+  u32 i0[GC_BATCH], istar[GC_BATCH], fresh[GC_BATCH], lim[GC_BATCH], seen[GC_BATCH], m[GC_BATCH], lastb[GC_BATCH], code[GC_BATCH], rank[GC_BATCH];
+  u32 wave[GC_THREADS / CCLD_WAVE], lo, hi, need, left, n_rank;
+};
+__device__ __forceinline__ void list_groups(const EndArgs& a, GroupShared& S, const u32 c) {
+  auto &s_cnt = S.cnt, &s_row = S.row, &s_last = S.last;
+  auto& s_best = S.best;
+  auto& s_list = S.list;
+  auto& s_wave = S.wave;
+  u32 &s_lo = S.lo, &s_hi = S.hi, &s_need = S.need, &s_left = S.left, &s_n_rank = S.n_rank;
+  auto& s_map = S.map;
+  auto &s_wm = S.wm, &s_sum = S.sum;
+  auto& s_t0 = S.t0;
+  auto& s_min_wm = S.min_wm;
+  auto &s_i0 = S.i0, &s_istar = S.istar, &s_new = S.fresh, &s_lim = S.lim, &s_seen = S.seen, &s_m = S.m, &s_lastb = S.lastb, &s_code = S.code,
+       &s_rank = S.rank;
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
   const u64 n_seg = a.counters[CNT_NSEG];
   const u32 n = (u32)(n_seg < a.seg_cap ? n_seg : a.seg_cap);          // rows that the table holds
   const i64* __restrict__ COMM = a.seg + (u64)CCLD_SEG_COMM * a.seg_cap;
@@ -75,10 +85,6 @@ __global__ __launch_bounds__(GC_THREADS, 8) void k_group_comm(GroupArgs a) {
   for (u32 i = tid; i < (u32)GROUP_SLOTS; i += GC_THREADS) { s_cnt[i] = 0; s_best[i] = 0; s_row[i] = GC_NONE; s_last[i] = 0; }
   __syncthreads();
   const u32 lo = s_lo, hi = s_hi;
-  if (lo >= hi) {
-    if (tid == 0) { a.comm_groups[c] = 0; a.comm_row[c] = lo; }
-    return;
-  }
   constexpr u32 U = 4;
   for (u32 i0 = lo + tid; i0 < hi; i0 += GC_THREADS * U) {
     u32 g[U];
@@ -268,69 +274,194 @@ __global__ __launch_bounds__(GC_THREADS, 8) void k_group_comm(GroupArgs a) {
 }
 static_assert(GROUP_SLOTS == 1024 && GROUP_SLOTS % GC_THREADS == 0, "ten bits of group code");
 
-// Rows of the group table: a wavefront per communicator.  The communicators before it are summed by the wavefront
-// itself (a few thousand counts from the L2) unless the counts were scanned before (SCANNED: many communicators,
-// where that would be quadratic).
-template <bool SCANNED>
-__global__ __launch_bounds__(256) void k_group_emit(GroupArgs a) {
-  if (a.counters[CNT_STATUS] != 0) return;
-  const u32 c = blockIdx.x * 4 + threadIdx.x / CCLD_WAVE, lane = lane_id();
-  if (c >= a.n_comms) return;
-  u32 pos = 0, cnt;
-  if (SCANNED) {
-    pos = a.comm_groups[c];
-    cnt = a.comm_groups[c + 1] - pos;
+// ---- flags of a window on the grid placement -------------------------------------------------------------
+// The statistics kernels left the flagged records of every fine bucket in (counter, rank) order; here a thread per flag finds
+// its bucket by the flags before it and writes it to its place in the list and in the flag table: a few buckets hold most of the
+// flags (those of a slow rank's communicators), so a workgroup or a wavefront per bucket would wait for those.  The flags before
+// every bucket are scanned by each workgroup in LDS, or were scanned before (many buckets).
+constexpr u32 END_SCAN_FINE = 4096;
+struct FlagShared { u32 pre[END_SCAN_FINE + 1], wave[GC_THREADS / CCLD_WAVE]; };
+__device__ __forceinline__ void list_flags(const EndArgs& e, const GridArgs& d, const FlagArgs& a, FlagShared& S, u32 block, u32 blocks) {
+  const u32 n_fine = d.hdr->n_fine, tid = threadIdx.x;
+  u32 total;
+  if (e.flags_scanned) {
+    total = d.nflag[n_fine];
   } else {
-    for (u32 i = lane; i < c; i += CCLD_WAVE) pos += a.comm_groups[i];
-    pos = wave_sum(pos);
-    cnt = a.comm_groups[c];
-    if (c + 1 == a.n_comms && lane == 0) a.counters[CNT_NGROUP] = (u64)pos + cnt;
+    constexpr u32 PER = END_SCAN_FINE / GC_THREADS;
+    u32 v[PER], sum = 0;
+#pragma unroll
+    for (u32 q = 0; q < PER; ++q) { v[q] = tid * PER + q < n_fine ? d.nflag[tid * PER + q] : 0u; sum += v[q]; }
+    u32 ex = block_exclusive_sum<GC_THREADS>(sum, S.wave, &total);
+#pragma unroll
+    for (u32 q = 0; q < PER; ++q) { S.pre[tid * PER + q] = ex; ex += v[q]; }
+    if (block == 0 && tid == 0) e.counters[CNT_NFLAG] = total;
+    __syncthreads();
   }
-  const u32 lo = a.comm_row[c];
-  const u64 C = a.group_cap;
-  i64* __restrict__ O = a.group;
-  for (u32 p = lane; p < cnt; p += CCLD_WAVE) {
-    const u64 g = (u64)pos + p;
-    if (g >= C) break;
-    const u32 w = a.stage[0][lo + p], sx = a.stage[1][lo + p];
-    const u32 code = w & 1023u, cls = w >> 12;
-    const bool dynamic = (w >> 10) & 1u, slow = (w >> 11) & 1u;
-    const GroupState G = a.gstate[(u64)c * GROUP_SLOTS + code];
-    auto col = [&](int k) -> i64 { return a.seg[(u64)k * a.seg_cap + sx]; };
-    O[CCLD_GRP_COMM * C + g] = (i64)c;
-    O[CCLD_GRP_OP * C + g] = (i64)(code / GROUP_CLS);
-    O[CCLD_GRP_CLS * C + g] = (i64)(code % GROUP_CLS);
-    O[CCLD_GRP_N_USABLE * C + g] = (i64)a.stage[2][lo + p];
-    O[CCLD_GRP_RSTAR_SEQ * C + g] = col(CCLD_SEG_SEQ);
-    O[CCLD_GRP_TMAX * C + g] = col(CCLD_SEG_DUR_MAX);
-    O[CCLD_GRP_TMIN * C + g] = col(CCLD_SEG_DUR_MIN);
-    O[CCLD_GRP_TBASE * C + g] = dynamic ? G.tbase_dyn : a.p.tbase_init_ns;
-    O[CCLD_GRP_STATIC * C + g] = dynamic ? 0 : 1;
-    O[CCLD_GRP_FROZEN * C + g] = G.frozen;
-    O[CCLD_GRP_M * C + g] = G.cnt;
-    O[CCLD_GRP_SLOW * C + g] = slow ? 1 : 0;
-    O[CCLD_GRP_CLASS * C + g] = (i64)cls;
-    O[CCLD_GRP_ROOT_S1 * C + g] = (slow && cls != CCLD_SLOW_S2_COMMUNICATION) ? col(CCLD_SEG_ARGMIN_RANK) : (i64)CCLD_NO_RANK;
-    // communication-slow root (Eq. 4): the communicator's member of minimal SendRate / RecvRate
-    O[CCLD_GRP_ROOT_S2 * C + g] =
-        (cls == CCLD_SLOW_S2_COMMUNICATION || cls == CCLD_SLOW_S3_MIXED) ? a.rate_root[c] : (i64)CCLD_NO_RANK;
-    O[CCLD_GRP_REPEATS * C + g] = G.repeats;
-    O[CCLD_GRP_LOCATE * C + g] = (slow && G.repeats >= a.p.repeat_threshold) ? 1 : 0;
+  for (u32 k = block * GC_THREADS + tid; k < total; k += blocks * GC_THREADS) {
+    u32 lo = 0, hi = n_fine, first = 0;          // the bucket that holds flag k: the last one that starts at or before it
+    while (hi - lo > 1) {
+      const u32 m = (lo + hi) >> 1, v = e.flags_scanned ? d.nflag[m] : S.pre[m];
+      if (v <= k) { lo = m; first = v; } else hi = m;
+    }
+    const FineDesc D = d.desc[lo];
+    const u32 at = d.rec0[lo] + (k - first);
+    const u32 w = a.flag_stage[at], cell = w & 0xFFFFu, kind = w >> 16, round = cell / D.size, slot = cell - round * D.size;
+    a.flag_key[k] = ((u64)(D.srow0 + round) << 32) | slot;
+    a.flag_pos[k] = at;
+    if (a.flag && k < a.flag_cap) {
+      auto put = [&](int col, i64 v) { a.flag[(u64)col * a.flag_cap + k] = v; };
+      put(CCLD_FLG_COMM, (i64)D.comm);
+      put(CCLD_FLG_SEQ, (i64)(D.seq0 + round));
+      put(CCLD_FLG_RANK, (i64)rank_of_slot(a.member_off, a.members_sorted, D.comm, slot));
+      put(CCLD_FLG_KIND, (i64)kind);
+      put(CCLD_FLG_LAG_ENTER, a.flag_lag[at]);
+      put(CCLD_FLG_LAG_EXIT, a.flag_lag[a.cap_n + at]);
+    }
   }
 }
 
-// From this many communicators on the counts are scanned by a launch of their own
-constexpr u32 GROUP_SCAN_COMMS = 8192;
+// ---- blame order -----------------------------------------------------------------------------------------
+// Every workgroup lists the flagged ranks in LDS for itself (a scan over two columns of the blame table), ranks its share of
+// them and writes its share of the others.
+constexpr u32 ORDER_TILE = 4 * GC_THREADS;
+struct OrderShared { unsigned short flagged[END_ORDER_RANKS]; u32 before[END_ORDER_RANKS / ORDER_TILE], wave[GC_THREADS / CCLD_WAVE]; };
+__device__ __forceinline__ void list_order(const EndArgs& a, OrderShared& S, u32 block, u32 blocks) {
+  const i64* __restrict__ blame = a.blame;
+  const u32 tid = threadIdx.x, lane = lane_id(), n_ranks = a.n_ranks;
+  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
+  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
+  auto flags_of_four = [&](u32 r0) -> u32 {
+    u32 m = 0;
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) if (r0 + k < n_ranks && NE[r0 + k] + NX[r0 + k] != 0) m |= 1u << k;
+    return m;
+  };
+  u32 nb = 0;
+  for (u32 t = 0; t * ORDER_TILE < n_ranks; ++t) {
+    const u32 r0 = t * ORDER_TILE + tid * 4;
+    const u32 m = flags_of_four(r0);
+    u32 tot;
+    u32 at = nb + block_exclusive_sum<GC_THREADS>((u32)__popc(m), S.wave, &tot);
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) if (m & (1u << k)) S.flagged[at++] = (unsigned short)(r0 + k);
+    if (tid == 0) S.before[t] = nb;
+    nb += tot;
+  }
+  __syncthreads();
+  constexpr u32 NW = GC_THREADS / CCLD_WAVE;
+  for (u32 q = block * NW + tid / CCLD_WAVE; q < nb; q += blocks * NW) {
+    const u32 r = S.flagged[q];
+    const u32 before = blamed_before(blame, n_ranks, S.flagged, nb, r, lane);
+    if (lane == 0) a.order[before] = r;
+  }
+  for (u32 t = block; t * ORDER_TILE < n_ranks; t += blocks) {
+    const u32 r0 = t * ORDER_TILE + tid * 4;
+    const u32 m = flags_of_four(r0);
+    u32 tot;
+    u32 before = S.before[t] + block_exclusive_sum<GC_THREADS>((u32)__popc(m), S.wave, &tot);       // flagged ranks below r0
+#pragma unroll
+    for (u32 k = 0; k < 4; ++k) {
+      if (r0 + k >= n_ranks) break;
+      if (m & (1u << k)) ++before; else a.order[nb + r0 + k - before] = r0 + k;
+    }
+  }
+}
 
-void launch_groups(hipStream_t st, const GroupArgs& a) {
-  hipLaunchKernelGGL(k_group_comm, dim3(a.n_comms), dim3(GC_THREADS), 0, st, a);
-  const u32 blocks = (a.n_comms + 3) / 4;
-  if (a.n_comms < GROUP_SCAN_COMMS) {
-    hipLaunchKernelGGL(k_group_emit<false>, dim3(blocks), dim3(256), 0, st, a);
+// ---- the launches -----------------------------------------------------------------------------------------
+// (Four workgroups per compute unit: with the registers that the compiler takes by itself there are three, and the groups of a
+// stream's 3,200 communicators take 49 us instead of 38.)
+template <bool GRID>
+__global__ __launch_bounds__(GC_THREADS, 8) void k_window_lists(EndArgs a, GridArgs d, FlagArgs f, u32 n_flags, u32 n_order) {
+  constexpr size_t LDS = std::max(sizeof(GroupShared), std::max(sizeof(FlagShared), sizeof(OrderShared)));
+  __shared__ unsigned long long s_mem[(LDS + 7) / 8];
+  // a data error found by an earlier kernel of this analysis: the tables are not valid and the detection state stays as it is
+  if (a.counters[CNT_STATUS] != 0) return;
+  // the groups, which take longest where there are many, start behind the others: they fill the chip by themselves
+  const u32 b = blockIdx.x;
+  if (b < n_order) list_order(a, *reinterpret_cast<OrderShared*>(s_mem), b, n_order);
+  else if (GRID && b - n_order < n_flags) list_flags(a, d, f, *reinterpret_cast<FlagShared*>(s_mem), b - n_order, n_flags);
+  else list_groups(a, *reinterpret_cast<GroupShared*>(s_mem), b - n_order - n_flags);
+}
+// Rows of the group table, END_COMMS communicators to a workgroup, and the report by the last one, past the caches.  The
+// communicators before are summed by the workgroup itself (a few thousand counts from the L2) unless they were scanned
+// before (SCANNED: many communicators, where that would be quadratic).
+constexpr u32 END_COMMS = 8, END_WAVES = GC_THREADS / CCLD_WAVE;
+template <bool SCANNED>
+__global__ __launch_bounds__(GC_THREADS) void k_window_end(EndArgs a) {
+  __shared__ u32 s_cnt[END_COMMS], s_wave[END_WAVES];
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE, c0 = blockIdx.x * END_COMMS;
+  if (a.counters[CNT_STATUS] == 0 && c0 < a.n_comms) {
+    u32 before = 0, base;
+    if (SCANNED) {
+      if (tid < END_COMMS) s_cnt[tid] = c0 + tid < a.n_comms ? a.comm_groups[c0 + tid + 1] - a.comm_groups[c0 + tid] : 0u;
+      before = tid == 0 ? a.comm_groups[c0] : 0u;
+    } else {
+      if (tid < END_COMMS) s_cnt[tid] = c0 + tid < a.n_comms ? a.comm_groups[c0 + tid] : 0u;
+#pragma unroll 4
+      for (u32 i = tid; i < c0; i += GC_THREADS) before += a.comm_groups[i];
+    }
+    block_exclusive_sum<GC_THREADS>(before, s_wave, &base);
+    const u64 C = a.group_cap;
+    for (u32 k = wave; k < END_COMMS && c0 + k < a.n_comms; k += END_WAVES) {
+      const u32 c = c0 + k, cnt = s_cnt[k], lo = a.comm_row[c];
+      u32 pos = base;
+      for (u32 i = 0; i < k; ++i) pos += s_cnt[i];
+      if (c + 1 == a.n_comms && lane == 0) store_agent(reinterpret_cast<i64*>(&a.counters[CNT_NGROUP]), (i64)((u64)pos + cnt));
+      for (u32 p = lane; p < cnt; p += CCLD_WAVE) {
+        const u64 at = (u64)pos + p;
+        if (at >= C) break;
+        const u32 w = a.stage[0][lo + p], sx = a.stage[1][lo + p];
+        const u32 code = w & 1023u, cls = w >> 12;
+        const bool dynamic = (w >> 10) & 1u, slow = (w >> 11) & 1u;
+        const GroupState G = a.gstate[(u64)c * GROUP_SLOTS + code];
+        auto col = [&](int q) -> i64 { return a.seg[(u64)q * a.seg_cap + sx]; };
+        auto put = [&](int q, i64 v) { store_agent(&a.group[(u64)q * C + at], v); };
+        put(CCLD_GRP_COMM, (i64)c);
+        put(CCLD_GRP_OP, (i64)(code / GROUP_CLS));
+        put(CCLD_GRP_CLS, (i64)(code % GROUP_CLS));
+        put(CCLD_GRP_N_USABLE, (i64)a.stage[2][lo + p]);
+        put(CCLD_GRP_RSTAR_SEQ, col(CCLD_SEG_SEQ));
+        put(CCLD_GRP_TMAX, col(CCLD_SEG_DUR_MAX));
+        put(CCLD_GRP_TMIN, col(CCLD_SEG_DUR_MIN));
+        put(CCLD_GRP_TBASE, dynamic ? G.tbase_dyn : a.p.tbase_init_ns);
+        put(CCLD_GRP_STATIC, dynamic ? 0 : 1);
+        put(CCLD_GRP_FROZEN, G.frozen);
+        put(CCLD_GRP_M, G.cnt);
+        put(CCLD_GRP_SLOW, slow ? 1 : 0);
+        put(CCLD_GRP_CLASS, (i64)cls);
+        put(CCLD_GRP_ROOT_S1, (slow && cls != CCLD_SLOW_S2_COMMUNICATION) ? col(CCLD_SEG_ARGMIN_RANK) : (i64)CCLD_NO_RANK);
+        // communication-slow root (Eq. 4): the communicator's member of minimal SendRate / RecvRate
+        put(CCLD_GRP_ROOT_S2, (cls == CCLD_SLOW_S2_COMMUNICATION || cls == CCLD_SLOW_S3_MIXED) ? a.rate_root[c] : (i64)CCLD_NO_RANK);
+        put(CCLD_GRP_REPEATS, G.repeats);
+        put(CCLD_GRP_LOCATE, (slow && G.repeats >= a.p.repeat_threshold) ? 1 : 0);
+      }
+    }
+  }
+  if (a.host) report_counters(a.counters, a.arrivals, a.host, a.ticket);
+}
+
+// From so many communicators on their counts are scanned by a launch of their own
+constexpr u32 END_SCAN_COMMS = 8192;
+bool launch_window_end(hipStream_t st, const EndArgs& a_in, const GridArgs* d, const FlagArgs* f, uint32_t fine_bound) {
+  EndArgs a = a_in;
+  const bool report = a.n_ranks <= END_ORDER_RANKS;
+  if (!report) a.host = nullptr;
+  a.flags_scanned = fine_bound > END_SCAN_FINE;                                     // the bound is the exact number there
+  const u32 n_flags = d ? (a.flags_scanned ? 256u : std::min<u32>((fine_bound + 63) / 64, 64)) : 0u;
+  if (d && a.flags_scanned) launch_scan_tiles(st, d->nflag, fine_bound, &a.counters[CNT_NFLAG]);
+  const u32 n_order = report ? std::min<u32>((a.n_ranks + 63) / 64, 64) : 0u, blocks = a.n_comms + n_flags + n_order;
+  if (blocks) {
+    if (d) hipLaunchKernelGGL(k_window_lists<true>, dim3(blocks), dim3(GC_THREADS), 0, st, a, *d, *f, n_flags, n_order);
+    else hipLaunchKernelGGL(k_window_lists<false>, dim3(blocks), dim3(GC_THREADS), 0, st, a, GridArgs{}, FlagArgs{}, 0u, n_order);
+  }
+  const u32 ends = std::max<u32>((a.n_comms + END_COMMS - 1) / END_COMMS, 1);
+  if (a.n_comms < END_SCAN_COMMS) {
+    hipLaunchKernelGGL(k_window_end<false>, dim3(ends), dim3(GC_THREADS), 0, st, a);
   } else {
     launch_scan_tiles(st, a.comm_groups, a.n_comms, &a.counters[CNT_NGROUP]);
-    hipLaunchKernelGGL(k_group_emit<true>, dim3(blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_window_end<true>, dim3(ends), dim3(GC_THREADS), 0, st, a);
   }
+  return report;
 }
 
 }  // namespace ccld

@@ -17,9 +17,9 @@ static_assert(CNT_COUNT <= 64, "one wavefront copies the counters");
 
 // The last workgroup to get here reports.  No cache is written back on the way: what the kernel wrote for later
 // kernels is, at its end; what the caller reads has been written by earlier kernels, or with store_agent.
-__device__ __forceinline__ void report_counters(u64* counters, u64* host, u64 ticket) {
+__device__ __forceinline__ void report_counters(u64* counters, u32* arrivals, u64* host, u64 ticket) {
   __shared__ u32 s_last;
-  if (last_block(reinterpret_cast<u32*>(&counters[CNT_DONE]), gridDim.x, &s_last)) report_words(counters, host, ticket);
+  if (last_arrival(arrivals, gridDim.x, &s_last)) report_words(counters, host, ticket);
 }
 
 }  // namespace ccld

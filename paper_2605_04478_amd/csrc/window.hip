@@ -1,8 +1,9 @@
 // Window analysis kernels for gfx950: ingest (validation, keys, bucketed placement), collective
 // heads per tile, compaction of the late-rank flags, per-rank blame, and hang alerts.  The
-// per-collective statistics are in segments.hip, the slow-detection rules (Eq. 1-4) in groups.hip, the
-// sort in radix_sort.hip.
+// per-collective statistics are in segments.hip, the end of an analysis (slow-detection rules, flags of a window on the grid,
+// blame order) in groups.hip, the sort in radix_sort.hip.
 #include "window_kernels.h"
+#include "blame_order.h"
 #include "device_utils.h"
 #include "grid.h"
 #include "report.h"
@@ -724,139 +725,14 @@ void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int6
   if (f.n) hipLaunchKernelGGL(k_blame_sums, dim3(std::min<u32>((f.n + 4095) / 4096, BH_BLOCKS)), dim3(256), 0, st, f, n_ranks, blame);
 }
 
-// ---- flags of a window on the grid placement ----------------------------------------------------------
-// The statistics kernels left the flagged records of every fine bucket in (counter, rank) order; here a wavefront per
-// bucket writes them to their place in the list and in the flag table.  The flags of the buckets before it are summed by
-// the workgroup itself (a few thousand words from the L2), or were scanned before (SCANNED: many buckets).
-constexpr u32 GF_SELF_SUM = 4096;
-template <bool SCANNED>
-__global__ __launch_bounds__(256) void k_grid_flags(GridArgs d, FlagArgs a) {
-  __shared__ u32 s_wave[4];
-  if (d.hdr->feasible == 0) return;
-  const u32 n_fine = d.hdr->n_fine, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
-  const u32 f0 = blockIdx.x * 4;
-  if (f0 >= n_fine) return;
-  const u32 f = f0 + wave;
-  u32 nf, pos;
-  if (SCANNED) {
-    if (f >= n_fine) return;
-    pos = d.nflag[f];
-    nf = d.nflag[f + 1] - pos;
-  } else {
-    u32 before = 0;
-    for (u32 i = tid; i < f0; i += 256) before += d.nflag[i];
-    u32 base;
-    block_exclusive_sum<256>(before, s_wave, &base);
-    u32 mine[4];
-#pragma unroll
-    for (u32 q = 0; q < 4; ++q) mine[q] = f0 + q < n_fine ? d.nflag[f0 + q] : 0u;
-    pos = base + (wave > 0 ? mine[0] : 0u) + (wave > 1 ? mine[1] : 0u) + (wave > 2 ? mine[2] : 0u);
-    nf = wave == 0 ? mine[0] : wave == 1 ? mine[1] : wave == 2 ? mine[2] : mine[3];
-    if (tid == 0 && f0 + 4 >= n_fine) a.counters[CNT_NFLAG] = (u64)base + mine[0] + mine[1] + mine[2] + mine[3];
-  }
-  if (nf == 0) return;
-  const FineDesc D = d.desc[f];
-  const u32 r0 = d.rec0[f];
-  for (u32 i = lane; i < nf; i += CCLD_WAVE) {
-    const u32 w = a.flag_stage[r0 + i], cell = w & 0xFFFFu, kind = w >> 16;
-    const u32 k = pos + i, round = cell / D.size, slot = cell - round * D.size;
-    a.flag_key[k] = ((u64)(D.srow0 + round) << 32) | slot;
-    a.flag_pos[k] = r0 + i;
-    if (a.flag && k < a.flag_cap) {
-      a.flag[(u64)CCLD_FLG_COMM * a.flag_cap + k] = (i64)D.comm;
-      a.flag[(u64)CCLD_FLG_SEQ * a.flag_cap + k] = (i64)(D.seq0 + round);
-      a.flag[(u64)CCLD_FLG_RANK * a.flag_cap + k] = (i64)rank_of_slot(a.member_off, a.members_sorted, D.comm, slot);
-      a.flag[(u64)CCLD_FLG_KIND * a.flag_cap + k] = (i64)kind;
-      a.flag[(u64)CCLD_FLG_LAG_ENTER * a.flag_cap + k] = a.flag_lag[r0 + i];
-      a.flag[(u64)CCLD_FLG_LAG_EXIT * a.flag_cap + k] = a.flag_lag[a.cap_n + r0 + i];
-    }
-  }
-}
-void launch_grid_flags(hipStream_t st, const GridArgs& d, const FlagArgs& a, uint32_t fine_bound) {
-  const u32 blocks = (fine_bound + 3) / 4;
-  if (fine_bound <= GF_SELF_SUM) {
-    hipLaunchKernelGGL(k_grid_flags<false>, dim3(blocks), dim3(256), 0, st, d, a);
-  } else {
-    launch_scan_tiles(st, d.nflag, fine_bound, &a.counters[CNT_NFLAG]);      // the bound is the exact number here
-    hipLaunchKernelGGL(k_grid_flags<true>, dim3(blocks), dim3(256), 0, st, d, a);
-  }
-}
-
-// order[] = ranks by (flags descending, summed lag descending, rank ascending).  Ranks with any flag come first and
-// only they need ranking: a wavefront per flagged rank counts the flagged ranks that precede it.  The ranks without a
-// flag follow in ascending order.
-// Number of flagged ranks that come before rank r, counted by one wavefront over a list of the flagged ranks.
-template <class T>
-__device__ __forceinline__ u32 blamed_before(const i64* __restrict__ blame, u32 n_ranks, const T* list, u32 nb, u32 r, u32 lane) {
-  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
-  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
-  const i64* SE = blame + (u64)CCLD_BLM_SUM_LAG_ENTER * n_ranks;
-  const i64* SX = blame + (u64)CCLD_BLM_SUM_LAG_EXIT * n_ranks;
-  const i64 myn = NE[r] + NX[r];
-  const i64 mys = (i64)((u64)SE[r] + (u64)SX[r]);
-  u32 before = 0;
-  for (u32 i = lane; i < nb; i += CCLD_WAVE) {
-    const u32 o = list[i];
-    const i64 on = NE[o] + NX[o];
-    const i64 os = (i64)((u64)SE[o] + (u64)SX[o]);
-    before += (on > myn) || (on == myn && (os > mys || (os == mys && o < r)));
-  }
-  return wave_sum(before);
-}
-// Up to ORDER_ONE_RANKS ranks in one launch: every workgroup lists the flagged ranks in LDS for itself (a scan over
-// two columns of the blame table), ranks its share of them and writes its share of the others.
-constexpr u32 ORDER_ONE_RANKS = 16384, ORDER_THREADS = 1024, ORDER_TILE = 4 * ORDER_THREADS;
-__global__ __launch_bounds__(ORDER_THREADS) void k_blame_order_one(const i64* __restrict__ blame, u32 n_ranks, u64* counters,
-                                                         u32* __restrict__ order, u64* host, u64 ticket) {
-  extern __shared__ unsigned short s_flagged[];      // [n_ranks] flagged ranks, ascending
-  __shared__ u32 s_before[ORDER_ONE_RANKS / ORDER_TILE], s_wave[ORDER_THREADS / CCLD_WAVE];
-  const u32 tid = threadIdx.x, lane = lane_id();
-  const i64* NE = blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks;
-  const i64* NX = blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks;
-  auto flags_of_four = [&](u32 r0) -> u32 {
-    u32 m = 0;
-#pragma unroll
-    for (u32 k = 0; k < 4; ++k) if (r0 + k < n_ranks && NE[r0 + k] + NX[r0 + k] != 0) m |= 1u << k;
-    return m;
-  };
-  u32 nb = 0;
-  for (u32 t = 0; t * ORDER_TILE < n_ranks; ++t) {
-    const u32 r0 = t * ORDER_TILE + tid * 4;
-    const u32 m = flags_of_four(r0);
-    u32 tot;
-    u32 at = nb + block_exclusive_sum<ORDER_THREADS>((u32)__popc(m), s_wave, &tot);
-#pragma unroll
-    for (u32 k = 0; k < 4; ++k) if (m & (1u << k)) s_flagged[at++] = (unsigned short)(r0 + k);
-    if (tid == 0) s_before[t] = nb;
-    nb += tot;
-  }
-  __syncthreads();
-  constexpr u32 NW = ORDER_THREADS / CCLD_WAVE;
-  for (u32 q = blockIdx.x * NW + tid / CCLD_WAVE; q < nb; q += gridDim.x * NW) {
-    const u32 r = s_flagged[q];
-    const u32 before = blamed_before(blame, n_ranks, s_flagged, nb, r, lane);
-    if (lane == 0) order[before] = r;
-  }
-  for (u32 t = blockIdx.x; t * ORDER_TILE < n_ranks; t += gridDim.x) {
-    const u32 r0 = t * ORDER_TILE + tid * 4;
-    const u32 m = flags_of_four(r0);
-    u32 tot;
-    u32 before = s_before[t] + block_exclusive_sum<ORDER_THREADS>((u32)__popc(m), s_wave, &tot);       // flagged ranks below r0
-#pragma unroll
-    for (u32 k = 0; k < 4; ++k) {
-      if (r0 + k >= n_ranks) break;
-      if (m & (1u << k)) ++before; else order[nb + r0 + k - before] = r0 + k;
-    }
-  }
-  report_counters(counters, host, ticket);
-}
+// The blame order of very many ranks (END_ORDER_RANKS and fewer: k_window_lists).
 struct PredBlamed {
   const i64 *ne, *nx;
   bool want;
   __device__ bool operator()(u32 r) const { return ((ne[r] + nx[r]) != 0) == want; }
 };
 __global__ __launch_bounds__(256) void k_blame_order(const i64* __restrict__ blame, u32 n_ranks,
-                                                     const u32* __restrict__ lists, u64* counters,
+                                                     const u32* __restrict__ lists, u64* counters, u32* arrivals,
                                                      u32* __restrict__ order, u64* host, u64 ticket) {
   const u32 nb = (u32)counters[CNT_NBLAMED];
   const u32 lane = lane_id();
@@ -867,23 +743,17 @@ __global__ __launch_bounds__(256) void k_blame_order(const i64* __restrict__ bla
   }
   const u32 stride = gridDim.x * 256;
   for (u32 i = blockIdx.x * 256 + threadIdx.x; i < n_ranks - nb; i += stride) order[nb + i] = lists[n_ranks + i];
-  report_counters(counters, host, ticket);
+  report_counters(counters, arrivals, host, ticket);
 }
 void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, uint32_t* lists,
-                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
+                        uint32_t* tile_counts, uint64_t* counters, uint32_t* arrivals, uint32_t* order, uint64_t* host_counters,
                         uint64_t ticket) {
-  if (n_ranks <= ORDER_ONE_RANKS) {
-    const u32 blocks = std::min<u32>((n_ranks + 255) / 256, 16);
-    hipLaunchKernelGGL(k_blame_order_one, dim3(blocks), dim3(ORDER_THREADS), sizeof(unsigned short) * n_ranks, st, blame, n_ranks, counters,
-                       order, host_counters, ticket);
-    return;
-  }
   PredBlamed p{blame + (u64)CCLD_BLM_N_LATE_ENTER * n_ranks, blame + (u64)CCLD_BLM_N_LATE_EXIT * n_ranks, true};
   run_select(st, p, n_ranks, tile_counts, lists, &counters[CNT_NBLAMED]);
   p.want = false;
   run_select(st, p, n_ranks, tile_counts, lists + n_ranks, &counters[CNT_NCLEAN]);
   const u32 blocks = std::min<u32>((n_ranks + 3) / 4, 512);
-  hipLaunchKernelGGL(k_blame_order, dim3(blocks), dim3(256), 0, st, blame, n_ranks, (const u32*)lists, counters, order,
+  hipLaunchKernelGGL(k_blame_order, dim3(blocks), dim3(256), 0, st, blame, n_ranks, (const u32*)lists, counters, arrivals, order,
                      host_counters, ticket);
 }
 
@@ -893,21 +763,23 @@ void launch_report(hipStream_t st, const uint64_t* counters, uint64_t* host, uin
   hipLaunchKernelGGL(k_report, dim3(1), dim3(CCLD_WAVE), 0, st, counters, host, ticket);
 }
 
-// the blame table and its order handed to the caller: one launch for both
-__global__ __launch_bounds__(256) void k_blame_out(const i64* __restrict__ blame, const u32* __restrict__ order_in,
-                                                   u32 n_ranks, i64* __restrict__ table_out, u32* __restrict__ order_out) {
-  const u64 nt = (u64)CCLD_BLM_NCOL * n_ranks, stride = (u64)gridDim.x * 256;
-  for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < nt; i += stride) {
-    if (table_out) table_out[i] = blame[i];
-    if (order_out && i < n_ranks) order_out[i] = order_in[i];
+// The blame table and its order handed to the caller: the last workgroup to finish reports, so what it hands over is stored
+// past the caches.  (A report in a launch of its own cost 4 us more per call.)
+__global__ __launch_bounds__(1024) void k_blame_out(const i64* __restrict__ blame, const u32* __restrict__ order_in, u32 n_ranks,
+                                                    i64* __restrict__ table_out, u32* __restrict__ order_out, u64* counters,
+                                                    u32* arrivals, u64* host, u64 ticket) {
+  const u64 nt = (u64)CCLD_BLM_NCOL * n_ranks, stride = (u64)gridDim.x * 1024;
+  for (u64 i = (u64)blockIdx.x * 1024 + threadIdx.x; i < nt; i += stride) {
+    if (table_out) store_agent(&table_out[i], blame[i]);
+    if (order_out && i < n_ranks) store_agent(&order_out[i], order_in[i]);
   }
+  report_counters(counters, arrivals, host, ticket);
 }
 void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* order_in, uint32_t n_ranks, int64_t* table_out,
-                      uint32_t* order_out) {
-  if (n_ranks == 0 || (!table_out && !order_out)) return;
+                      uint32_t* order_out, uint64_t* counters, uint32_t* arrivals, uint64_t* host, uint64_t ticket) {
   const u64 nt = (u64)CCLD_BLM_NCOL * n_ranks;
-  const u32 blocks = (u32)std::min<u64>((nt + 255) / 256, 2048);
-  hipLaunchKernelGGL(k_blame_out, dim3(blocks), dim3(256), 0, st, blame, order_in, n_ranks, table_out, order_out);
+  const u32 blocks = (u32)std::min<u64>((nt + 1023) / 1024, 256);
+  hipLaunchKernelGGL(k_blame_out, dim3(blocks), dim3(1024), 0, st, blame, order_in, n_ranks, table_out, order_out, counters, arrivals, host, ticket);
 }
 
 // ------------------------------------------------------------------------------------------

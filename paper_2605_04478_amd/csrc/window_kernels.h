@@ -100,31 +100,40 @@ void launch_keys_pass(hipStream_t st, const uint64_t* key, uint32_t n, const Squ
 // adds the flag list (its length is read from the counters) to the late columns of the blame table
 void launch_blame_sums(hipStream_t st, const FlagArgs& f, uint32_t n_ranks, int64_t* blame);
 // order[] = ranks by (flags, summed lag, rank); then the counters are reported to host_counters (pinned host memory), each
-// word with `ticket`: the last words of an analysis
+// word with `ticket`: the last words of an analysis of more than END_ORDER_RANKS ranks
 void launch_blame_order(hipStream_t st, const int64_t* blame, uint32_t n_ranks, uint32_t* lists,
-                        uint32_t* tile_counts, uint64_t* counters, uint32_t* order, uint64_t* host_counters,
+                        uint32_t* tile_counts, uint64_t* counters, uint32_t* arrivals, uint32_t* order, uint64_t* host_counters,
                         uint64_t ticket);
 
-struct GroupArgs {
+// The end of an analysis (groups.hip)
+struct EndArgs {
   const int64_t* seg;        // collective table; its row count is read from counters[CNT_NSEG]
   uint64_t seg_cap;
   uint64_t* counters;
   const uint16_t* gcode;     // [rows] op * GROUP_CLS + size class of each usable collective, NO_GROUP of the others
   const int64_t* range_c;    // [rows] T_max - T_min (written with the collectives' statistics)
-  uint32_t n_comms;
+  uint32_t n_comms;          // 0: a window without records
   uint32_t* comm_groups;     // [n_comms + 1] groups of each communicator
   uint32_t* comm_row;        // [n_comms] its first row of the table
-  uint32_t* stage[3];        // [rows] what k_group_comm leaves for k_group_emit
+  uint32_t* stage[3];        // [rows] what k_window_lists leaves for k_window_end
   GroupState* gstate;
   const int64_t* rate_root;  // [n_comms] minimal-rate member per communicator (CCLD_NO_RANK before any rate pass)
   int64_t* group;
   uint64_t group_cap;
   ccld_params p;
+  // blame order
+  const int64_t* blame;
+  uint32_t n_ranks;
+  uint32_t* order;
+  uint32_t flags_scanned;    // the flags per fine bucket were scanned before
+  uint32_t* arrivals;
+  uint64_t* host;            // pinned words of the report
+  uint64_t ticket;
 };
+constexpr uint32_t END_ORDER_RANKS = 16384;       // most ranks whose blame order k_window_lists finds
 void launch_report(hipStream_t st, const uint64_t* counters, uint64_t* host, uint64_t ticket);
 void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* order_in, uint32_t n_ranks, int64_t* table_out,
-                      uint32_t* order_out);
-void launch_groups(hipStream_t st, const GroupArgs& a);        // groups.hip
+                      uint32_t* order_out, uint64_t* counters, uint32_t* arrivals, uint64_t* host, uint64_t ticket);
 
 struct CommLayout;
 struct GridHeader;

@@ -1,0 +1,124 @@
+"""GPU parity of the end of an analysis (groups, flags, blame order, alerts and report in one launch) where it can go wrong:
+alerts around the number that it lists itself, flags at the edges of its tiles of fine buckets, more ranks than it orders, and
+of the calls that report from their last kernel when they follow one another."""
+import numpy as np
+import pytest
+
+from oracle import ccld_oracle as orc
+from paper_2605_04478_amd import tracegen as tg
+from tests.helpers import INFLIGHT, T0, ring_topology, toy_cols
+from tests.test_gpu_window import FAR, compare, run_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("step", [1, 10**6], ids=["grid", "sorted"])
+@pytest.mark.parametrize("n_alert", [1, 7, 8, 9, 40])
+def test_alerts_of_every_class(n_alert, step):
+    """collectives that some member has not entered, that some finished, that all hang in; sizes around a wavefront"""
+    sizes = [2, 3, 63, 64, 65, 130, 700]
+    topo = tg.make_topology(700, [list(range(n))[::-1] for n in sizes])
+    rng = np.random.default_rng(n_alert)
+    rows = []
+    for c, n in enumerate(sizes):
+        hung = {int(s) for s in rng.permutation(9)[:(n_alert + len(sizes) - 1 - c) // len(sizes)]}
+        for s in range(9):
+            cls = int(rng.integers(0, 3)) if s in hung else -1
+            for r in range(n):
+                te = T0 + s * 10**9 + int(rng.integers(0, 10**6))
+                tx = te + 10**6
+                if cls == 0 and r % 3 == 1 or cls >= 0 and r == 0 and cls != 1:
+                    if cls == 0 and r % 3 == 1:
+                        continue
+                    tx = INFLIGHT
+                if cls == 2 or cls == 1 and r % 2:
+                    tx = INFLIGHT
+                rows.append((r, c, 5 + s * step, 1, 1 << 20, te, tx))
+    p = np.random.default_rng(1).permutation(len(rows))
+    cols = {k: v[p] for k, v in toy_cols(rows).items()}
+    g, o = run_both(topo, cols, hang_threshold_ns=10**9, what=(n_alert, step))
+    assert g.n_alert == n_alert
+
+
+def test_truncated_alert_tables():
+    from paper_2605_04478_amd import ccld
+    topo = ring_topology(6)
+    rows = [(r, 0, s, 1, 64, T0 + s, INFLIGHT if r < 2 else T0 + s + 9) for s in range(5) for r in range(6)]
+    cols = toy_cols(rows)
+    ref = orc.Oracle(topo, dict(hang_threshold_ns=10)).analyze_window(cols, FAR)
+    for alert_cap, cand_cap in ((5, 20), (3, 20), (5, 7), (1, 1)):
+        an = ccld.Analyzer(topo, max_window_records=30, hang_threshold_ns=10)
+        an.ingest(an.to_device(cols))
+        g = an.analyze_window(FAR, n_records=30, alert_cap=alert_cap, cand_cap=cand_cap)
+        assert (g.n_alert, g.n_cand) == (5, 20) and g.status == ("OK" if (alert_cap, cand_cap) == (5, 20) else "W_TRUNCATED")
+        for k in ref.alert:
+            assert np.array_equal(g.alert[k], ref.alert[k][:alert_cap]), k
+        assert np.array_equal(g.cand, ref.cand[:cand_cap])
+        an.close()
+
+
+@pytest.mark.parametrize("buckets", [1, 127, 128, 129, 256, 257])
+def test_flags_at_the_edges_of_tiles(buckets):
+    """one communicator of 1,024 members (two rounds in a fine bucket), flags in every bucket"""
+    n = 1024
+    topo = ring_topology(n)
+    rng = np.random.default_rng(buckets)
+    q = np.repeat(np.arange(2 * buckets), n)
+    rank = np.tile(np.arange(n), 2 * buckets)
+    te = T0 + q * 10**9 + rng.integers(0, 1000, q.size)
+    te[rng.integers(0, q.size, 5 * buckets)] += 10**7
+    p = rng.permutation(q.size)
+    cols = {"rank": rank.astype(np.uint32), "comm": np.zeros(q.size, np.uint32), "seq": q.astype(np.uint64), "op": np.ones(q.size, np.uint8),
+            "bytes": np.full(q.size, 64, np.uint64), "t_enter": te, "t_exit": T0 + q * 10**9 + 5 * 10**7 + rng.integers(0, 1000, q.size)}
+    g, o = run_both(topo, {k: v[p] for k, v in cols.items()}, what=buckets)
+    assert g.n_flag >= 4 * buckets
+
+
+@pytest.mark.parametrize("n_ranks", [511, 512, 2048, 2049, 16384, 16385])
+def test_blame_order_of_many_ranks(n_ranks):
+    topo = tg.make_topology(n_ranks, [list(range(i, min(i + 8, n_ranks))) for i in range(0, n_ranks, 8)])
+    rng = np.random.default_rng(n_ranks)
+    r = np.tile(np.arange(n_ranks), 3)
+    q = np.repeat(np.arange(3), n_ranks)
+    te = T0 + q * 10**9 + rng.integers(0, 1000, r.size)
+    te[rng.random(r.size) < 0.1] += 10**7
+    cols = {"rank": r.astype(np.uint32), "comm": (r // 8).astype(np.uint32), "seq": q.astype(np.uint64), "op": np.ones(r.size, np.uint8),
+            "bytes": np.full(r.size, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**7}
+    run_both(topo, cols, what=n_ranks)
+
+
+def test_calls_that_report_from_their_last_kernel_in_turn():
+    """analysis, blame, chains, hang location, rates and frames on one context: each leaves the counters as the next needs them"""
+    from paper_2605_04478_amd import ccld
+    from tests.test_oracle_hang import snap_rows
+    tr = tg.generate(tg.config1(n_slots=60))
+    topo = tr.topo
+    o = orc.Oracle(topo)
+    m = int(topo.size.sum())
+    an = ccld.Analyzer(topo, max_window_records=tr.n, max_snapshot_rows=max(m * 4, 64 * topo.n_ranks))
+    snaps = snap_rows(topo, 4, 1, lambda s, c, q, ch: (3, 5 + s, 5) if q else (2, 9, 9))
+    bad = {k: np.concatenate([v[:-1], v[:1]]) for k, v in snaps.items()}
+    frames = np.zeros(topo.n_ranks, dtype=tg.FRAME_DTYPE)
+    frames["n_channels"] = 1
+    for i in range(4):
+        an.reset_window()
+        an.ingest(an.to_device(tr.cols))
+        g, ref = an.analyze_window(FAR, n_records=tr.n, per_record=True), o.analyze_window(tr.cols, FAR)
+        compare(g, ref, *an.rank_blame(), what=i)
+        chain, per_rank = o.flag_chains(tr.cols, ref)
+        for _ in range(2):
+            st, gc, gr = an.flag_chains(g)
+            assert st == "OK" and all(np.array_equal(gc[k], chain[k]) for k in chain) and all(np.array_equal(gr[k], per_rank[k]) for k in per_rank)
+        for rows, status in ((snaps, "OK"), (bad, "E_DUPLICATE_KEY"), (snaps, "OK")):
+            h = an.locate_hang(an.snapshots_to_device(rows), 4, 1)
+            r = an.progress_rates(an.snapshots_to_device(rows), 4, 1)
+            assert (h.status, r.status) == (status, status)
+            if status == "OK":
+                want, rate = orc.Oracle(topo).locate_hang(rows, 4, 1), orc.Oracle(topo).progress_rates(rows, 4, 1)
+                assert all(np.array_equal(h.root[k], want.root[k]) for k in want.root)
+                assert all(np.array_equal(r.comm[k], rate.comm[k]) for k in rate.comm)
+            assert an.decode_frames(frames.view(np.uint8).reshape(-1), np.arange(topo.n_ranks), i, 1)[0] == "OK"
+        blame, order = an.rank_blame()
+        assert np.array_equal(order, ref.order)
+        o = orc.Oracle(topo) if i == 9 else o
+    an.close()
