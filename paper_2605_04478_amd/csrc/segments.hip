@@ -1214,7 +1214,7 @@ struct GridShared {
   uint4 row[GRID_B];                     // rows by cell; y bits 16-26: number of the row in its bucket
   u32 pres[GRID_B / 32];
   unsigned short pre[ROUNDS];            // records of the bucket before each of its rounds
-  u32 wave[8];
+  u32 wave[1024 / CCLD_WAVE];
   GridFlags flags;
 };
 // Places bucket f's rows in LDS.  Returns status bits: a cell taken twice or more rows than cells (duplicate keys), a
@@ -1494,7 +1494,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
   return mine;
 }
 
-constexpr int GRID_THREADS = 256;
+template <int GRID_THREADS>
 __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   __shared__ GridShared<GRID_B> S;
   __shared__ u32 s_slot[CCLD_WAVE];
@@ -1585,6 +1585,20 @@ __device__ __forceinline__ void sort_multi32(i32 (&v)[E], u32 lane) {
 #pragma unroll
     for (int r = 0; r < E; ++r) v[r] = merge_groups32<64>(v[r], lane);
   }
+}
+// sorts a bitonic sequence
+template <int E>
+__device__ __forceinline__ void merge_multi32(i32 (&v)[E], u32 lane) {
+#pragma unroll
+  for (int jb = E >> 1; jb >= 1; jb >>= 1)
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+      if ((r & jb) == 0) {
+        const i32 x = v[r], y = v[r | jb];
+        v[r] = y < x ? y : x; v[r | jb] = y < x ? x : y;
+      }
+#pragma unroll
+  for (int r = 0; r < E; ++r) v[r] = merge_groups32<64>(v[r], lane);
 }
 // What a collective of a long communicator leaves for its table row; the times are absolute.
 struct LongRow {
@@ -1684,8 +1698,16 @@ __device__ __forceinline__ bool long_wave32(const SegArgs& a, const GridArgs& d,
       for (int r = 1; r < E; ++r) if ((q >> 6) == (u32)r) sel = v[r];
       return __builtin_amdgcn_readlane(sel, (int)(q & 63));
     };
-    st[w][0] = kth(0); st[w][1] = kth(km); st[w][2] = kth(kl);
-    st[w][3] = (i32)mad_of([&](u32 i) -> i64 { return (i64)kth(i); }, nd);
+    const i32 med = kth(km);
+    st[w][0] = kth(0); st[w][1] = med; st[w][2] = kth(kl);
+    // deviations of the sorted offsets: one merge sorts them (see grid_batches)
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const i32 t = (i32)((u32)v[r] - (u32)med), u = (i32)(0u - (u32)t);
+      v[r] = r * CCLD_WAVE + lane < nd ? (t > u ? t : u) : REL_NONE;
+    }
+    merge_multi32<E>(v, lane);
+    st[w][3] = kth(km);
   }
   const u64 hb = row_bytes(lead);
   const u32 hop = row_op(lead);
@@ -1827,9 +1849,11 @@ __device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d,
 // workgroup one after the other: their times are sorted in LDS, the median of the deviations is selected from the sorted
 // sequence.  A kernel each, because the sort's LDS would leave the wavefronts half of their occupancy (four workgroups per
 // compute unit without it), and the registers of eight members per lane those with two.  Bound by the chain of one collective
-// (two sorts, two selections): 4M records in collectives of 128 members 150 -> 106 us.
-template <int E>
-__global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+// (two sorts, two merges of the deviations; with a binary search for their median in place of the merge a 16,384-rank stream took
+// 714 instead of 702 us), so buckets of eight members per lane, of at most seven collectives, have eight wavefronts: 1.1M records
+// with collectives of 390 members 211 -> 189 us.
+template <int E, int THREADS>
+__global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   constexpr bool WAVES = E > 0;
   constexpr u32 MEMBERS = WAVES ? E * CCLD_WAVE : GRID_B, ABOVE = E == 0 ? SEG_MULTI_MAX : E * CCLD_WAVE / 2;
   __shared__ LongShared S;
@@ -1838,7 +1862,7 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
   __shared__ LongRow s_out[LONG_ROUNDS];
   __shared__ TeamAcc s_acc;
   __shared__ u32 s_first;
-  constexpr u32 NW = SEG_THREADS / CCLD_WAVE, U = GRID_B / SEG_THREADS;
+  constexpr u32 NW = THREADS / CCLD_WAVE, U = GRID_B / THREADS;
   const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
   if (d.hdr->feasible == 0) return;
   const u32 n_long = d.hdr->n_long;
@@ -1848,8 +1872,8 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
     const FineDesc D = d.desc[f];
     const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size, K = D.K;
     if (size <= ABOVE || size > MEMBERS) continue;
-    for (u32 i = tid; i < size; i += SEG_THREADS) s_slot[i] = 0;
-    const u64 bad = grid_place<SEG_THREADS>(d, D, cnt, S);
+    for (u32 i = tid; i < size; i += THREADS) s_slot[i] = 0;
+    const u64 bad = grid_place<THREADS>(d, D, cnt, S);
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
     if constexpr (WAVES) {
       long_rounds<E>(a, d, D, rec0, wref, S, s_slot, s_out, lane, wave, NW);
@@ -1875,7 +1899,7 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
         }
         if (here) atomicMin(&s_first, first_slot);
         u32 n;
-        const u32 before = block_exclusive_sum<SEG_THREADS>(here, S.wave, &n);
+        const u32 before = block_exclusive_sum<THREADS>(here, S.wave, &n);
         const Rec h = n ? unpack_row(S.row[k * size + s_first], wref, a.win.wide) : Rec{0, T_INFLIGHT, 0, 0};
         {
           u32 ni = 0, rmin = 0xFFFFFFFFu, rmax = 0xFFFFFFFFu;
@@ -1913,7 +1937,7 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
             if (i < P) s_v[i] = valid[u] && rec[u].t_exit != T_INFLIGHT ? (w ? rec[u].t_exit : rec[u].t_enter) : T_INFLIGHT;
           }
           __syncthreads();
-          team_sort(s_v, P, tid);
+          team_sort<THREADS>(s_v, P, tid);
           stat[w][0] = s_v[0]; stat[w][1] = s_v[km]; stat[w][2] = s_v[kl];
           stat[w][3] = mad_of([&](u32 i) -> i64 { return s_v[i]; }, nd);
           __syncthreads();
@@ -1952,7 +1976,7 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
     }
     __syncthreads();
     if (tid == 0) d.nflag[f] = S.flags.n;
-    grid_order_flags<SEG_THREADS>(a, D, rec0, S.flags, S.wave, blame, n_ranks);
+    grid_order_flags<THREADS>(a, D, rec0, S.flags, S.wave, blame, n_ranks);
     // the table rows: a lane per round, a column at a time
     for (u32 col = wave; col < STAGE_COLS; col += NW) {
       const u32 k = lane;
@@ -1983,7 +2007,7 @@ __global__ __launch_bounds__(SEG_THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_
       seg_put(a, (int)col, srow, v);
     }
     unsigned long long* nrec = (unsigned long long*)(blame + (u64)CCLD_BLM_N_RECORDS * n_ranks);
-    for (u32 i = tid; i < size; i += SEG_THREADS)
+    for (u32 i = tid; i < size; i += THREADS)
       if (s_slot[i]) atomicAdd(&nrec[a.members_sorted[a.member_off[D.comm] + i]], (unsigned long long)s_slot[i]);
     __syncthreads();     // LDS is reused by the next bucket
   }
@@ -2011,12 +2035,28 @@ static void launch_seg_listed(hipStream_t st, const SegArgs& a) {
 }
 
 void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks) {
-  if (fine_bound) hipLaunchKernelGGL(k_grid_stats, dim3(fine_bound), dim3(GRID_THREADS), 0, st, a, d, blame, n_ranks);
+  // Where there are no more fine buckets than compute units, or than two to each, a workgroup has sixteen or eight wavefronts
+  // instead of four: what takes the time then is one bucket's passes one after the other (16 ranks, 8 buckets: a window
+  // 70.9 -> 62.8 us).  More buckets overlap each other with four workgroups to a compute unit.
+  const u32 likely = a.n / GRID_MIN_FILL + d.n_comms / 2;
+  auto stats = [&](auto threads) {
+    hipLaunchKernelGGL((k_grid_stats<decltype(threads)::value>), dim3(fine_bound), dim3(decltype(threads)::value), 0, st, a, d, blame, n_ranks);
+  };
+  if (likely <= 256) stats(std::integral_constant<int, 1024>{});
+  else if (likely <= 512) stats(std::integral_constant<int, 512>{});
+  else stats(std::integral_constant<int, 256>{});
   // as many workgroups as are resident at once, which take the listed buckets in turn
-  if (a.long_classes & 1) hipLaunchKernelGGL(k_grid_long<2>, dim3(1024), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
-  if (a.long_classes & 2) hipLaunchKernelGGL(k_grid_long<4>, dim3(1024), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
-  if (a.long_classes & 4) hipLaunchKernelGGL(k_grid_long<8>, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
-  if (a.long_classes & 8) hipLaunchKernelGGL(k_grid_long<0>, dim3(512), dim3(SEG_THREADS), 0, st, a, d, blame, n_ranks);
+  const bool few = likely <= 256;
+  if (a.long_classes & 1) {
+    if (few) hipLaunchKernelGGL((k_grid_long<2, 1024>), dim3(256), dim3(1024), 0, st, a, d, blame, n_ranks);
+    else hipLaunchKernelGGL((k_grid_long<2, 256>), dim3(1024), dim3(256), 0, st, a, d, blame, n_ranks);
+  }
+  if (a.long_classes & 2) {
+    if (few) hipLaunchKernelGGL((k_grid_long<4, 1024>), dim3(256), dim3(1024), 0, st, a, d, blame, n_ranks);
+    else hipLaunchKernelGGL((k_grid_long<4, 256>), dim3(1024), dim3(256), 0, st, a, d, blame, n_ranks);
+  }
+  if (a.long_classes & 4) hipLaunchKernelGGL((k_grid_long<8, 512>), dim3(256), dim3(512), 0, st, a, d, blame, n_ranks);
+  if (a.long_classes & 8) hipLaunchKernelGGL((k_grid_long<0, 256>), dim3(512), dim3(256), 0, st, a, d, blame, n_ranks);
 }
 
 void launch_seg_analyze(hipStream_t st, const SegArgs& a) {
