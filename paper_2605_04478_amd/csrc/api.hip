@@ -62,7 +62,6 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   const uint64_t n_meta = (uint64_t)c->p.window_batches + 2;
   c->ing_table = w.take<uint32_t>((uint64_t)c->n_buckets * INGEST_BLOCKS);
   c->ing_base = w.take<uint32_t>(n_meta * (c->n_buckets + 1) + 4);
-  c->ing_done = w.take<uint32_t>(1);
   c->comm_range = c->grid_capable ? w.take<uint64_t>(n_meta * n_comms * 2) : nullptr;
   // sort
   // (the hang pass sorts its root list, at most one entry per communicator member, in these buffers too)
@@ -391,7 +390,6 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (hipMemsetAsync(c->gstate, 0, sizeof(GroupState) * (uint64_t)topo->n_comms * GROUP_SLOTS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->batch_meta, 0, sizeof(BatchMeta) * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (c->comm_range && hipMemsetAsync(c->comm_range, 0, 16ull * topo->n_comms * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
-  if (hipMemsetAsync(c->ing_done, 0, sizeof(uint32_t), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->arrivals, 0, sizeof(uint32_t) * ARRIVAL_WORDS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
@@ -472,7 +470,7 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
   a.n = n; a.win_key = c->win_key; a.win_row = c->win_row; a.win_wide = c->win_wide;
   a.tail = (uint32_t)((head + count) % std::max<uint64_t>(c->cap, 1));
   a.cap = (uint32_t)c->cap;
-  a.table = c->ing_table; a.bucket_base = c->ing_base + (uint64_t)slot * (c->n_buckets + 1); a.done = c->ing_done; a.scratch_total = &c->counters[CNT_COUNT - 1];
+  a.table = c->ing_table; a.bucket_base = c->ing_base + (uint64_t)slot * (c->n_buckets + 1); a.scratch_total = &c->counters[CNT_COUNT - 1];
   a.n_buckets = c->n_buckets; a.bshift = c->bshift;
   uint64_t rounds_end = c->rounds_next;
   if (c->n_buckets > 1) {

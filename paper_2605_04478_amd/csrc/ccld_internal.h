@@ -130,7 +130,6 @@ struct ccld_ctx {
   ccld::BatchMeta* batch_meta;        // [window_batches + 2]
   uint32_t* ing_table;                // [n_buckets][INGEST_BLOCKS]
   uint32_t* ing_base;                 // [window_batches + 2][n_buckets + 1]
-  uint32_t* ing_done;                 // zero between launches
   uint32_t n_buckets; int bshift;
   // sort
   ccld::SortBuffers sb;               // main sort

@@ -52,12 +52,11 @@ __device__ __forceinline__ void put_header(const IngestArgs& a, i64 ref) {
   a.meta->chunk = a.chunk; a.meta->round0 = a.round0; a.meta->n_rounds = a.per_group * gridDim.x; a.meta->per_group = a.per_group;
 }
 
-// Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Small
-// tables are scanned by the last workgroup to finish.
+// Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Tables
+// of no more words than this are scanned by every placement workgroup for itself, larger ones by two launches.
 constexpr u32 INGEST_SCAN_WORDS = 8192;
 __global__ __launch_bounds__(256) void k_ingest_hist(IngestArgs a, u32 n_comms) {
   extern __shared__ u32 s_cnt[];        // [n_buckets]
-  __shared__ u32 s_wave[4], s_last;
   for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) s_cnt[b] = 0;
   __syncthreads();
   const u64 chunk = a.chunk / a.hist_split;
@@ -75,28 +74,7 @@ __global__ __launch_bounds__(256) void k_ingest_hist(IngestArgs a, u32 n_comms) 
       if (i0 + (u64)u * 256 < i_end) atomicAdd(&s_cnt[c[u] < n_comms ? (c[u] >> a.bshift) : 0u], 1u);
   }
   __syncthreads();
-  const u32 g = gridDim.x;
-  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) store_agent(&a.table[(u64)b * g + blockIdx.x], s_cnt[b]);
-  if (a.n_buckets * g > INGEST_SCAN_WORDS) return;
-  if (!last_block(a.done, g, &s_last)) return;
-  if (threadIdx.x == 0) *a.done = 0;
-  // bucket by bucket: the counts of the workgroups become offsets inside the bucket, then the buckets' starts
-  u32 carry = 0;
-  for (u32 b = 0; b < a.n_buckets; ++b) {
-    u32* row = a.table + (u64)b * g;
-    u32 in_bucket = 0;
-    for (u32 i0 = 0; i0 < g; i0 += 256) {
-      const u32 i = i0 + threadIdx.x;
-      const u32 v = i < g ? load_agent(&row[i]) : 0u;
-      u32 tot;
-      const u32 ex = block_exclusive_sum<256>(v, s_wave, &tot);
-      if (i < g) row[i] = in_bucket + ex;
-      in_bucket += tot;
-    }
-    if (threadIdx.x == 0) a.bucket_base[b] = carry;
-    carry += in_bucket;
-  }
-  if (threadIdx.x == 0) a.bucket_base[a.n_buckets] = carry;
+  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) a.table[(u64)b * gridDim.x + blockIdx.x] = s_cnt[b];
 }
 // exclusive scan of every bucket's row of per-workgroup counts (row length <= 2048)
 __global__ __launch_bounds__(256) void k_ingest_scan(u32* table, u32* totals, u32 n_blocks) {
@@ -260,9 +238,34 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + CHUNK);
   u32* s_p = reinterpret_cast<u32*>(s_rng + (a.range ? 2 * T.n_comms : 0u));
   const u32 tid = threadIdx.x;
-  if (tid < a.n_buckets) {
-    const u32 o = a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
-    s_off[tid] = o; s_start[tid] = o;
+  if (a.table_words > INGEST_SCAN_WORDS) {
+    if (tid < a.n_buckets) {
+      const u32 o = a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
+      s_off[tid] = o; s_start[tid] = o;
+    }
+  } else {
+    // the buckets' records, and those of the workgroups before this one: a wavefront per bucket.  (One workgroup that scanned
+    // the table at the end of the counting took 20 of its 28 us at 2M records in 32 buckets.)
+    const u32 row = gridDim.x * a.hist_split, upto = blockIdx.x * a.hist_split;
+    for (u32 b = tid / CCLD_WAVE; b < a.n_buckets; b += THREADS / CCLD_WAVE) {
+      u32 before = 0, all = 0;
+#pragma unroll 4
+      for (u32 i = lane_id(); i < row; i += CCLD_WAVE) {
+        const u32 v = a.table[(u64)b * row + i];
+        all += v; before += i < upto ? v : 0u;
+      }
+      before = wave_sum(before); all = wave_sum(all);
+      if (lane_id() == 0) { s_start[b] = before; s_pre[b] = all; }
+    }
+    __syncthreads();
+    u32 total;
+    const u32 base = block_exclusive_sum<THREADS>(tid < a.n_buckets ? s_pre[tid] : 0u, s_scan, &total);
+    if (tid < a.n_buckets) {
+      const u32 o = base + s_start[tid];
+      s_off[tid] = o; s_start[tid] = o;
+      if (blockIdx.x == 0) a.bucket_base[tid] = base;
+    }
+    if (blockIdx.x == 0 && tid == 0) a.bucket_base[a.n_buckets] = total;
   }
   if (LDS_TABLE) {
     const uint4* __restrict__ g = reinterpret_cast<const uint4*>(T.rank_memb4);
@@ -439,8 +442,9 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
   const u64 g = shape.groups;
   a.hist_split = shape.hist_split; a.chunk = shape.chunk; a.per_group = shape.per_group;
   const u32 g_hist = (u32)(g * a.hist_split);
+  a.table_words = a.n_buckets * g_hist;
   hipLaunchKernelGGL(k_ingest_hist, dim3(g_hist), dim3(256), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
-  if (a.n_buckets * g_hist > INGEST_SCAN_WORDS) {
+  if (a.table_words > INGEST_SCAN_WORDS) {
     hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }

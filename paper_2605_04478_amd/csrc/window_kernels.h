@@ -18,7 +18,7 @@ struct IngestArgs {
   BatchMeta *meta, *meta_next;   // this batch's header and the one that the next batch will use
   uint32_t* table;           // [n_buckets][workgroups] records per communicator bucket and workgroup
   uint32_t* bucket_base;     // [n_buckets + 1] of this batch
-  uint32_t* done;            // zero between launches
+  uint32_t table_words;      // words of the table
   uint64_t* scratch_total;
   uint32_t n_buckets;
   int bshift;                // bucket = comm >> bshift
