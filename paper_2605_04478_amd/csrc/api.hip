@@ -114,6 +114,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->comm_groups = w.take<uint32_t>((uint64_t)n_comms + 1);
   c->comm_row = w.take<uint32_t>(n_comms);
   c->chain_parent = w.take<uint32_t>(N + 1);
+  c->alert_rows = w.take<uint32_t>(END_ALERTS);
   c->alert_list = w.take<uint32_t>(NT);
   c->alert_ncand = w.take<uint32_t>(N + 2);
   if (w.off - scratch_begin < B * 48) (void)w.take<uint8_t>(B * 48 - (w.off - scratch_begin));
@@ -554,10 +555,10 @@ static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine, bool* full) {
 constexpr uint32_t FINE_BOUND = 4096;
 
 // The last launches of an analysis: groups, flags (d and f: a window on the grid placement), blame order, report.
-static void launch_end(ccld_ctx* c, EndArgs& e, const GridArgs* d, const FlagArgs* f, uint32_t fine) {
+static void launch_end(ccld_ctx* c, EndArgs& e, const GridArgs* d, const FlagArgs* f, const AlertArgs* al, uint32_t fine) {
   e.counters = c->counters; e.blame = c->blame; e.n_ranks = c->topo.n_ranks; e.order = c->blame_order;
   e.arrivals = c->arrivals; e.host = c->h_pinned; e.ticket = c->ticket;
-  if (!launch_window_end(c->stream, e, d, f, fine))
+  if (!launch_window_end(c->stream, e, d, f, al, fine))
     launch_blame_order(c->stream, c->blame, c->topo.n_ranks, c->blame_list, c->blame_tiles, c->counters, c->arrivals, c->blame_order, c->h_pinned, c->ticket);
 }
 
@@ -573,7 +574,18 @@ static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   e.gstate = c->gstate; e.rate_root = c->rate_root; e.group = o->group; e.group_cap = o->group_cap; e.p = c->p;
   e.comm_groups = c->comm_groups; e.comm_row = c->comm_row;
   e.stage[0] = c->alert_list; e.stage[1] = c->alert_ncand; e.stage[2] = c->chain_parent;      // nothing lives there yet
-  launch_end(c, e, d, f, fine);
+  AlertArgs aa;
+  std::memset(&aa, 0, sizeof(aa));
+  aa.seg = o->seg; aa.seg_cap = o->seg_cap; aa.now_ns = now_ns;
+  aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = sa.key; aa.idx = sa.idx; aa.win = sa.win; aa.n = sa.n;
+  if (grid) {
+    aa.grid.lay = (const CommLayout*)c->g_lay; aa.grid.rows = c->g_rows; aa.grid.cell_row = c->g_cell_row; aa.grid.wide = c->win_wide;
+    aa.grid.hdr = (const GridHeader*)c->g_hdr;
+  }
+  aa.sf = c->sf; aa.topo = c->topo; aa.tile_counts = c->tile_heads; aa.alert_list = c->alert_rows;
+  aa.alert_ncand = c->alert_ncand; aa.alert = o->alert; aa.alert_cap = o->alert_cap; aa.cand = o->cand;
+  aa.cand_cap = o->cand_cap; aa.counters = c->counters;
+  launch_end(c, e, d, f, c->max_comm_size <= END_ALERT_MEMBERS ? &aa : nullptr, fine);
   c->prof.end(CCLD_PROF_GROUPS);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
@@ -590,19 +602,9 @@ static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   o->n_group = c->h_pinned[CNT_NGROUP];
   if (o->n_seg > o->seg_cap || o->n_flag > o->flag_cap || o->n_group > o->group_cap) o->status = CCLD_W_TRUNCATED;
 
-  // hang alerts: the collectives that raise one in table order, and the candidates of every alert
-  if (o->n_alert) {
-    AlertArgs aa;
-    std::memset(&aa, 0, sizeof(aa));
-    aa.seg = o->seg; aa.seg_cap = o->seg_cap; aa.n_seg = (uint32_t)std::min<uint64_t>(o->n_seg, o->seg_cap); aa.now_ns = now_ns;
-    aa.hang_threshold_ns = c->p.hang_threshold_ns; aa.key = sa.key; aa.idx = sa.idx; aa.win = sa.win; aa.n = sa.n;
-    if (grid) {
-      aa.grid.lay = (const CommLayout*)c->g_lay; aa.grid.rows = c->g_rows; aa.grid.cell_row = c->g_cell_row; aa.grid.wide = c->win_wide;
-      aa.grid.hdr = (const GridHeader*)c->g_hdr;
-    }
-    aa.sf = c->sf; aa.topo = c->topo; aa.tile_counts = c->tile_heads; aa.alert_list = c->alert_list;
-    aa.alert_ncand = c->alert_ncand; aa.alert = o->alert; aa.alert_cap = o->alert_cap; aa.cand = o->cand;
-    aa.cand_cap = o->cand_cap; aa.counters = c->counters;
+  // hang alerts: the collectives that raise one in table order, and the candidates of every alert; a few are listed already
+  if (o->n_alert > END_ALERTS || (o->n_alert && c->max_comm_size > END_ALERT_MEMBERS)) {
+    aa.n_seg = (uint32_t)std::min<uint64_t>(o->n_seg, o->seg_cap); aa.alert_list = c->alert_list;
     c->prof.begin(CCLD_PROF_ALERTS);
     launch_alert_select(st, aa);
     launch_alert_candidates(st, aa, (uint32_t)o->n_alert);
@@ -610,9 +612,9 @@ static ccld_status finish_analysis(ccld_ctx* c, int64_t now_ns, ccld_window_resu
     launch_report(st, c->counters, c->h_pinned, take_ticket(c));
     HIP_TRY(hipGetLastError());
     HIP_TRY(wait_report(c));
-    o->n_cand = c->h_pinned[CNT_NCAND];
-    if (o->n_alert > o->alert_cap || o->n_cand > o->cand_cap) o->status = CCLD_W_TRUNCATED;
   }
+  o->n_cand = o->n_alert ? c->h_pinned[CNT_NCAND] : 0;
+  if (o->n_alert > o->alert_cap || o->n_cand > o->cand_cap) o->status = CCLD_W_TRUNCATED;
   c->prof.collect();
   c->blame_valid = true;
   c->chain_ready = true;
@@ -629,7 +631,7 @@ static SegArgs seg_args(ccld_ctx* c, int64_t now_ns, const ccld_window_result* o
   sa.member_off = c->topo.member_off; sa.members_sorted = c->topo.members_sorted; sa.comm_info = c->comm_info;
   sa.seg = o->seg; sa.seg_cap = o->seg_cap;
   sa.lag_e = o->lag_enter; sa.lag_x = o->lag_exit; sa.flag_lag = c->flag_lag; sa.cap_n = c->cap;
-  sa.counters = c->counters;
+  sa.counters = c->counters; sa.alert_rows = c->alert_rows;
   sa.lag_floor = c->p.lag_floor_ns; sa.kmad_num = c->p.kmad_num; sa.kmad_den = c->p.kmad_den;
   sa.barrier_bytes = c->p.barrier_bytes; sa.now_ns = now_ns; sa.hang_threshold_ns = c->p.hang_threshold_ns; sa.max_size = c->max_comm_size; sa.long_classes = c->long_classes;
   sa.gcode = c->gcode; sa.range_c = c->range_c;
@@ -818,7 +820,7 @@ static ccld_status analyze_empty(ccld_ctx* c, ccld_window_result* o) {
   take_ticket(c);
   EndArgs e;
   std::memset(&e, 0, sizeof(e));
-  launch_end(c, e, nullptr, nullptr, 0);
+  launch_end(c, e, nullptr, nullptr, nullptr, 0);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   c->blame_valid = true;

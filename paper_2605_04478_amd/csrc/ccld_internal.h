@@ -152,6 +152,7 @@ struct ccld_ctx {
   uint32_t* comm_groups;              // [n_comms + 1] detection groups of each communicator
   uint32_t* comm_row;                 // [n_comms] its first row of the collective table
   uint32_t* chain_parent;             // [cap + 1] scratch of ccld_flag_chains: parent of every flag
+  uint32_t* alert_rows;               // [END_ALERTS]
   uint32_t* alert_list;               // [cap]
   uint32_t* alert_ncand;              // [cap + 1]
   uint2* comm_info;                   // [n_comms] (first member index, members) of every communicator: one load for both

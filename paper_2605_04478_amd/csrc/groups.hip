@@ -1,8 +1,9 @@
 // The end of an analysis, in two launches: what follows from the statistics alone (k_window_lists: the slow-detection rules
-// of Eq. 1-4 per detection group, the flag list of a window on the grid placement, the blame order; workgroups of their own
+// of Eq. 1-4 per detection group, the flag list of a window on the grid placement, the blame order, a few hang alerts; workgroups of their own
 // for each), then the group table and the report of the counters (k_window_end).
 #include <algorithm>
 
+#include "alerts.h"
 #include "blame_order.h"
 #include "device_utils.h"
 #include "grid.h"
@@ -367,20 +368,84 @@ __device__ __forceinline__ void list_order(const EndArgs& a, OrderShared& S, u32
   }
 }
 
+// ---- hang alerts ------------------------------------------------------------------------------------------
+// A few alerts in table order with their candidates in rank order, a wavefront each.  (Seven launches and a second wait for
+// the host otherwise, which longer lists take: one wavefront's chain of loads is some 10 us for 390 members.)
+struct AlertShared { u32 row[END_ALERTS], cnt[END_ALERTS]; u64 hit[END_ALERTS][END_ALERT_MEMBERS / CCLD_WAVE]; };
+template <bool GRID>
+__device__ __forceinline__ void list_alerts(const AlertArgs& a, AlertShared& S) {
+  const u32 n = (u32)a.counters[CNT_NALERT], tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  if (n == 0 || n > END_ALERTS) return;
+  if (tid < n) {
+    const u32 row = a.alert_list[tid];
+    u32 at = 0;
+    for (u32 i = 0; i < n; ++i) at += a.alert_list[i] < row ? 1u : 0u;
+    S.row[at] = row;
+  }
+  __syncthreads();
+  const bool on = wave < n;
+  const u64 C = a.seg_cap;
+  u32 s = 0, comm = 0, size = 0, moff = 0, total = 0;
+  int cls = 0;
+  if (on) {
+    s = S.row[wave];
+    comm = (u32)a.seg[CCLD_SEG_COMM * C + s];
+    const u32 nn = (u32)a.seg[CCLD_SEG_N * C + s], ninfl = (u32)a.seg[CCLD_SEG_INFLIGHT * C + s], first = (u32)a.seg[CCLD_SEG_FIRST * C + s];
+    size = a.topo.size[comm]; moff = a.topo.member_off[comm];
+    cls = alert_class(nn, ninfl, size);
+    for (u32 q0 = 0; q0 < size; q0 += CCLD_WAVE) {
+      const u32 q = q0 + lane;
+      bool hit = false;
+      if (q < size && cls != CCLD_HANG_H3_HARDWARE) {
+        i64 tx = INT64_MAX;
+        const bool here = alert_record<GRID>(a, s, comm, first, nn, q, &tx);
+        hit = cls == CCLD_HANG_H1_NOT_ENTERED ? !here : (here && tx != INT64_MAX);
+      }
+      const u64 m = ballot64(hit);
+      if (lane == 0) S.hit[wave][q0 / CCLD_WAVE] = m;
+      total += (u32)__popcll(m);
+    }
+    if (lane == 0) S.cnt[wave] = total;
+  }
+  __syncthreads();
+  if (!on) return;
+  u32 off = 0;
+  for (u32 i = 0; i < wave; ++i) off += S.cnt[i];
+  if (wave + 1 == n && lane == 0) a.counters[CNT_NCAND] = (u64)off + total;
+  if (lane == 0 && wave < a.alert_cap) {
+    const u64 A = a.alert_cap;
+    auto put = [&](int col, i64 v) { a.alert[(u64)col * A + wave] = v; };
+    put(CCLD_ALR_COMM, (i64)comm);
+    put(CCLD_ALR_SEQ, a.seg[CCLD_SEG_SEQ * C + s]);
+    put(CCLD_ALR_AGE, a.now_ns - a.seg[CCLD_SEG_INFLIGHT_ENTER_MIN * C + s]);
+    put(CCLD_ALR_CLASS, (i64)cls);
+    put(CCLD_ALR_NCAND, (i64)total);
+    put(CCLD_ALR_CAND_OFF, (i64)off);
+  }
+  u64 at = off;
+  for (u32 q0 = 0; q0 < size; q0 += CCLD_WAVE) {
+    const u64 m = S.hit[wave][q0 / CCLD_WAVE], k = at + mbcnt64(m);
+    if (((m >> lane) & 1u) && k < a.cand_cap) a.cand[k] = (i64)a.topo.members_sorted[moff + q0 + lane];
+    at += (u64)__popcll(m);
+  }
+}
+static_assert(END_ALERTS <= GC_THREADS / CCLD_WAVE, "a wavefront per alert");
+
 // ---- the launches -----------------------------------------------------------------------------------------
 // (Four workgroups per compute unit: with the registers that the compiler takes by itself there are three, and the groups of a
 // stream's 3,200 communicators take 49 us instead of 38.)
 template <bool GRID>
-__global__ __launch_bounds__(GC_THREADS, 8) void k_window_lists(EndArgs a, GridArgs d, FlagArgs f, u32 n_flags, u32 n_order) {
-  constexpr size_t LDS = std::max(sizeof(GroupShared), std::max(sizeof(FlagShared), sizeof(OrderShared)));
+__global__ __launch_bounds__(GC_THREADS, 8) void k_window_lists(EndArgs a, GridArgs d, FlagArgs f, AlertArgs al, u32 n_flags, u32 n_order, u32 n_alerts) {
+  constexpr size_t LDS = std::max(std::max(sizeof(GroupShared), sizeof(AlertShared)), std::max(sizeof(FlagShared), sizeof(OrderShared)));
   __shared__ unsigned long long s_mem[(LDS + 7) / 8];
   // a data error found by an earlier kernel of this analysis: the tables are not valid and the detection state stays as it is
   if (a.counters[CNT_STATUS] != 0) return;
   // the groups, which take longest where there are many, start behind the others: they fill the chip by themselves
   const u32 b = blockIdx.x;
-  if (b < n_order) list_order(a, *reinterpret_cast<OrderShared*>(s_mem), b, n_order);
-  else if (GRID && b - n_order < n_flags) list_flags(a, d, f, *reinterpret_cast<FlagShared*>(s_mem), b - n_order, n_flags);
-  else list_groups(a, *reinterpret_cast<GroupShared*>(s_mem), b - n_order - n_flags);
+  if (b < n_alerts) list_alerts<GRID>(al, *reinterpret_cast<AlertShared*>(s_mem));
+  else if (b - n_alerts < n_order) list_order(a, *reinterpret_cast<OrderShared*>(s_mem), b - n_alerts, n_order);
+  else if (GRID && b - n_alerts - n_order < n_flags) list_flags(a, d, f, *reinterpret_cast<FlagShared*>(s_mem), b - n_alerts - n_order, n_flags);
+  else list_groups(a, *reinterpret_cast<GroupShared*>(s_mem), b - n_alerts - n_order - n_flags);
 }
 // Rows of the group table, END_COMMS communicators to a workgroup, and the report by the last one, past the caches.  The
 // communicators before are summed by the workgroup itself (a few thousand counts from the L2) unless they were scanned
@@ -442,17 +507,19 @@ __global__ __launch_bounds__(GC_THREADS) void k_window_end(EndArgs a) {
 
 // From so many communicators on their counts are scanned by a launch of their own
 constexpr u32 END_SCAN_COMMS = 8192;
-bool launch_window_end(hipStream_t st, const EndArgs& a_in, const GridArgs* d, const FlagArgs* f, uint32_t fine_bound) {
+bool launch_window_end(hipStream_t st, const EndArgs& a_in, const GridArgs* d, const FlagArgs* f, const AlertArgs* al, uint32_t fine_bound) {
   EndArgs a = a_in;
   const bool report = a.n_ranks <= END_ORDER_RANKS;
   if (!report) a.host = nullptr;
   a.flags_scanned = fine_bound > END_SCAN_FINE;                                     // the bound is the exact number there
   const u32 n_flags = d ? (a.flags_scanned ? 256u : std::min<u32>((fine_bound + 63) / 64, 64)) : 0u;
   if (d && a.flags_scanned) launch_scan_tiles(st, d->nflag, fine_bound, &a.counters[CNT_NFLAG]);
-  const u32 n_order = report ? std::min<u32>((a.n_ranks + 63) / 64, 64) : 0u, blocks = a.n_comms + n_flags + n_order;
+  const u32 n_order = report ? std::min<u32>((a.n_ranks + 63) / 64, 64) : 0u, n_alerts = al ? 1u : 0u;
+  const u32 blocks = a.n_comms + n_flags + n_order + n_alerts;
   if (blocks) {
-    if (d) hipLaunchKernelGGL(k_window_lists<true>, dim3(blocks), dim3(GC_THREADS), 0, st, a, *d, *f, n_flags, n_order);
-    else hipLaunchKernelGGL(k_window_lists<false>, dim3(blocks), dim3(GC_THREADS), 0, st, a, GridArgs{}, FlagArgs{}, 0u, n_order);
+    const AlertArgs alerts = al ? *al : AlertArgs{};
+    if (d) hipLaunchKernelGGL(k_window_lists<true>, dim3(blocks), dim3(GC_THREADS), 0, st, a, *d, *f, alerts, n_flags, n_order, n_alerts);
+    else hipLaunchKernelGGL(k_window_lists<false>, dim3(blocks), dim3(GC_THREADS), 0, st, a, GridArgs{}, FlagArgs{}, alerts, 0u, n_order, n_alerts);
   }
   const u32 ends = std::max<u32>((a.n_comms + END_COMMS - 1) / END_COMMS, 1);
   if (a.n_comms < END_SCAN_COMMS) {

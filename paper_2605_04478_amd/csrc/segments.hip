@@ -33,9 +33,11 @@ __device__ __forceinline__ void seg_put_group(const SegArgs& a, u32 srow, bool u
   a.range_c[srow] = usable ? dmax - dmin : 0;
 }
 // counts a collective that raises a hang alert (an operation in flight longer than the threshold, barriers excepted);
-// the alert list itself is built only when there are any
+// the first few leave their rows for the end of the analysis, which lists them; longer lists are built when they are known
 __device__ __forceinline__ void seg_count_alert(const SegArgs& a, u32 srow, u32 ninfl, bool barrier, i64 imin) {
-  if (ninfl && !barrier && a.now_ns - imin > a.hang_threshold_ns && srow < a.seg_cap) atomic_add_u64(&a.counters[CNT_NALERT], 1);
+  if (!ninfl || barrier || a.now_ns - imin <= a.hang_threshold_ns || srow >= a.seg_cap) return;
+  const u64 at = atomic_add_u64(&a.counters[CNT_NALERT], 1);
+  if (at < END_ALERTS) a.alert_rows[at] = srow;
 }
 __device__ __forceinline__ i64 absdiff(i64 a, i64 b) { return a >= b ? a - b : b - a; }
 // the j-th record in (communicator, counter, rank) order

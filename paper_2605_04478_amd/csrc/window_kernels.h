@@ -40,6 +40,8 @@ void launch_ingest(hipStream_t st, const IngestArgs& a, const DeviceTopology& T,
 void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v);
 
 constexpr uint32_t NO_GROUP = 0xFFFFu;
+constexpr uint32_t END_ALERTS = 8;                // most hang alerts that k_window_lists lists, a wavefront each ...
+constexpr uint32_t END_ALERT_MEMBERS = 2048;      // ... where no communicator has more members
 struct SegArgs {
   const uint64_t* key;       // sorted squeezed keys
   const uint32_t* idx;       // window slot of each sorted record
@@ -65,6 +67,7 @@ struct SegArgs {
   int64_t lag_floor;
   uint32_t kmad_num, kmad_den, barrier_bytes;
   int64_t now_ns, hang_threshold_ns;             // collectives in flight for longer are counted in counters[CNT_NALERT]
+  uint32_t* alert_rows;      // [END_ALERTS] rows of the first ones, in any order
   uint32_t max_size;         // members of the largest communicator (host-side: which size classes can occur)
   uint32_t long_classes;     // which there are: bit 0 65 to 128 members, 1 up to 256, 2 up to 512, 3 more
   // (op, size class) code and T_max - T_min of every collective, for the group stage; a collective that takes
@@ -159,7 +162,7 @@ struct AlertArgs {
   GridView grid;             // lay is null for a sorted window
   DeviceTopology topo;
   uint32_t* tile_counts;
-  uint32_t* alert_list;
+  uint32_t* alert_list;      // rows of the collectives that raise one: ascending; for k_window_lists in any order
   uint32_t* alert_ncand;
   int64_t* alert;
   uint64_t alert_cap;
