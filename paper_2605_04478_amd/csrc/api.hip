@@ -139,6 +139,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   const uint64_t SN = std::max<uint64_t>(c->snap_cap, 1);
   c->n_members = n_members;
   c->rate_root = w.take<int64_t>(n_comms);
+  c->h_counters = w.take<uint64_t>(CNT_COUNT + HANG_REGIONS / 2);
   c->h_cell = w.take<uint64_t>(2 * SN);
   c->h_cnt = w.take<uint32_t>(SN / 32 + 1);
   c->h_pair = w.take<int64_t>((uint64_t)CCLD_HPAIR_NCOL * n_members);
@@ -314,7 +315,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   carve_all(c, w, topo->n_ranks, topo->n_comms, n_members);
   c->topo.n_ranks = topo->n_ranks; c->topo.n_comms = topo->n_comms;
   c->h_pinned = nullptr;
-  c->ticket = 0;
+  c->ticket = 0; c->h_clear = false;
 
   // derived host tables: sorted member lists, rank -> communicators CSR
   std::vector<uint32_t> sorted(topo->members, topo->members + n_members), sslot(n_members);

@@ -102,6 +102,7 @@ constexpr int SEG_TILE = 1024;       // sorted records owned by one workgroup of
 constexpr int SEG_THREADS = 256;
 constexpr int SEL_TILE = 2048;       // records per workgroup of the compaction kernels
 constexpr int RANKCOUNT_BLOCKS = 2048;
+constexpr uint32_t HANG_REGIONS = 512;       // most regions that snapshot rows are regrouped by
 
 // device counters written by kernels and read back by the host
 enum { CNT_NSEG, CNT_NFLAG, CNT_NBIG, CNT_NGROUP, CNT_NALERT, CNT_NCAND, CNT_STATUS, CNT_NBLAMED, CNT_NCLEAN,
@@ -166,7 +167,9 @@ struct ccld_ctx {
   uint64_t ticket;                    // of the latest report that the device was asked for
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
-  // hang location
+  // hang location and rates
+  uint64_t* h_counters;               // [CNT_COUNT] counters, then the rows of every region
+  bool h_clear;                       // both are clear
   uint64_t n_members;                 // member slots over all communicators
   uint64_t* h_cell;                   // [snap_cap][2]  (operation counter, sent | recv << 32)
   uint32_t* h_cnt;                    // [snap_cap / 32 + 1] presence bitmap of the grid cells

@@ -56,6 +56,8 @@ struct HangArgs {
   u32 n_regions;
   // hang location of large grids: rows regrouped by region of 2^sb members
   ulonglong2* part_row;   // [n_cell]
+  u32* arrivals;
+  int leave_clear;        // the pass clears counters and part_fill behind itself
   int sb;
   int pb;                 // rates: the members of a region are taken 2^pb at a time
   u32 snap_inv;           // ceil(2^32 / n_snap)
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(256) void k_hang_scan(HangArgs a) {
 // reserves room in every region with an atomic, and rounds of 2,048 rows with 512 regions spend 340 us on them; larger
 // rounds leave one workgroup per CU and nothing to hide the phases behind.
 constexpr int SPLIT_CELL_BITS = 18;
-constexpr u32 SPLIT_REGIONS = 512;
+constexpr u32 SPLIT_REGIONS = HANG_REGIONS;
 constexpr size_t SPLIT_LDS = 64000, RATE_LDS = 156000;      // LDS of a region: hang location, rates
 constexpr int RATE_PARTS = 3;                               // a region of rates is taken in up to 2^3 parts
 inline size_t rate_region_lds(u32 n_ch, u32 n_snap, int sb) {
@@ -506,9 +508,18 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
   for (int m2 = 32; m2 >= 1; m2 >>= 1) status |= shfl_xor_u64(status, m2);
   if (lane_id() == 0 && status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
 }
+// What a pass over regrouped rows counts in starts at zero: the last workgroup of the pass before left it so (a launch less:
+// 4 us of 39 on a small job), or this launch does.
 __global__ __launch_bounds__(SPLIT_REGIONS) void k_hang_clear(HangArgs a) {
   if (threadIdx.x < CNT_COUNT) a.counters[threadIdx.x] = 0;
-  if (threadIdx.x < a.n_regions) a.part_fill[threadIdx.x] = 0;
+  if (threadIdx.x < (a.leave_clear ? SPLIT_REGIONS : a.n_regions)) a.part_fill[threadIdx.x] = 0;      // all: a later pass may have more
+}
+__device__ __forceinline__ void report_and_clear(const HangArgs& a) {
+  report_words(a.counters, a.host, a.ticket);
+  if (!a.leave_clear) return;
+  __syncthreads();                     // the words have been read
+  if (threadIdx.x < CNT_COUNT) store_agent(reinterpret_cast<i64*>(&a.counters[threadIdx.x]), 0);
+  for (u32 i = threadIdx.x; i < a.n_regions; i += blockDim.x) a.part_fill[i] = 0;
 }
 __device__ __forceinline__ void store_member(const HangArgs& a, u64 p, u64 seq, u64 S, u64 R, u32 onset, bool moved) {
   PAIR(a, CCLD_HPAIR_STALLED, p) = a.n_snap - 1 >= a.stall_snapshots && !moved ? 1 : 0;
@@ -917,7 +928,7 @@ __global__ __launch_bounds__(256) void k_hang_final(HangArgs a) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
-  report_words(a.counters, a.host, a.ticket);
+  report_and_clear(a);
 }
 __global__ __launch_bounds__(256) void k_hang_root_emit(HangArgs a, const u32* sidx, u32 n_root) {
   const u32 k = blockIdx.x * 256 + threadIdx.x;
@@ -1077,11 +1088,9 @@ __device__ __forceinline__ bool rate_less(const RateCand& x, const RateCand& y) 
   return x.rank < y.rank;
 }
 
-// One workgroup per communicator: the member of minimal SendRate, RecvRate, and of both kinds; the caller's tables.
-// Small workgroups, and the report in a launch of its own: 1,008 ranks in 343 communicators took 30 us with 1,024 threads
-// each and the last one reporting (their arrivals are atomics on one word), 13 us before the tables were written here.
-__global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__ rate_root) {
-  __shared__ RateCand s_best[2][256];
+// One workgroup per communicator: the member of minimal SendRate, RecvRate, and of both kinds; the caller's tables, stored
+// past the caches, since the last workgroup reports.
+__device__ __forceinline__ void rate_comm(const HangArgs& a, i64* __restrict__ rate_root, RateCand (&s_best)[2][256]) {
   const u32 c = blockIdx.x, tid = threadIdx.x;
   const u32 off = a.T.member_off[c], n = a.T.size[c];
   if (!hang_rows_ok(a)) return;                  // the same for every thread
@@ -1092,12 +1101,10 @@ __global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__
     const RateCand snd{(u64)RPAIR(a, CCLD_RATE_OPS_SEND, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_SEND, p), rk};
     const RateCand rcv{(u64)RPAIR(a, CCLD_RATE_OPS_RECV, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_RECV, p), rk};
     if (a.out_pair && p < a.pair_cap) {
-      a.out_pair[CCLD_RATE_RANK * a.pair_cap + p] = (i64)rk;
-      a.out_pair[CCLD_RATE_COMM * a.pair_cap + p] = (i64)c;
-      a.out_pair[CCLD_RATE_OPS_SEND * a.pair_cap + p] = (i64)snd.ops;
-      a.out_pair[CCLD_RATE_CHANGES_SEND * a.pair_cap + p] = (i64)snd.chg;
-      a.out_pair[CCLD_RATE_OPS_RECV * a.pair_cap + p] = (i64)rcv.ops;
-      a.out_pair[CCLD_RATE_CHANGES_RECV * a.pair_cap + p] = (i64)rcv.chg;
+      auto put = [&](int col, u64 v) { store_agent(&a.out_pair[(u64)col * a.pair_cap + p], (i64)v); };
+      put(CCLD_RATE_RANK, rk); put(CCLD_RATE_COMM, c);
+      put(CCLD_RATE_OPS_SEND, snd.ops); put(CCLD_RATE_CHANGES_SEND, snd.chg);
+      put(CCLD_RATE_OPS_RECV, rcv.ops); put(CCLD_RATE_CHANGES_RECV, rcv.chg);
     }
     if (rate_less(snd, best[0])) best[0] = snd;
     if (rate_less(rcv, best[1])) best[1] = rcv;
@@ -1118,9 +1125,15 @@ __global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__
     const i64 row[CCLD_RCOMM_NCOL] = {(i64)c, snd.chg ? (i64)snd.rank : (i64)CCLD_NO_RANK, rcv.chg ? (i64)rcv.rank : (i64)CCLD_NO_RANK,
                                       both.chg ? (i64)both.rank : (i64)CCLD_NO_RANK};
     if (a.out_comm && c < a.comm_cap)
-      for (int col = 0; col < CCLD_RCOMM_NCOL; ++col) a.out_comm[(u64)col * a.comm_cap + c] = row[col];
+      for (int col = 0; col < CCLD_RCOMM_NCOL; ++col) store_agent(&a.out_comm[(u64)col * a.comm_cap + c], row[col]);
     rate_root[c] = row[CCLD_RCOMM_ROOT];
   }
+}
+__global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__ rate_root) {
+  __shared__ RateCand s_best[2][256];
+  __shared__ u32 s_last;
+  rate_comm(a, rate_root, s_best);
+  if (last_arrival(a.arrivals, gridDim.x, &s_last)) report_and_clear(a);
 }
 // ---- Probing Frames (Section 5.1) -------------------------------------------------------------------
 struct FrameArgs {
@@ -1135,6 +1148,7 @@ struct FrameArgs {
   u64* frame_of;      // [n_ranks] call << 32 | frame of the rank in that call
   u64* status;        // call << 8 | worst error of that call
   u32 call;           // number of this call: marks of earlier calls need no clearing
+  u32* arrivals;
   u64 *host, ticket;
 };
 // errors in the order in which they are reported
@@ -1190,11 +1204,10 @@ __global__ __launch_bounds__(256) void k_frames_check(FrameArgs a) {
 
 // A thread per member slot and channel: the latest kernel of the member's communicator in its rank's frame replaces
 // what is remembered, unless that is newer, and the snapshot row is written from it.
-__global__ __launch_bounds__(256) void k_frame_rows(FrameArgs a, ccld_snapshot_rows o) {
-  const u64 i = (u64)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void frame_row(const FrameArgs& a, const ccld_snapshot_rows& o, u64 i) {
   const u64 p = i / CCLD_FRAME_CHANNELS;
   const u32 ch = (u32)(i % CCLD_FRAME_CHANNELS);
-  if (p >= a.n_members || (*a.status >> 8) == a.call) return;
+  if (p >= a.n_members) return;
   const u32 r = a.T.members[p], c = a.T.member_comm[p];
   const u64 of = a.frame_of[r];
   u64* L = a.last + i * 2;
@@ -1219,13 +1232,17 @@ __global__ __launch_bounds__(256) void k_frame_rows(FrameArgs a, ccld_snapshot_r
   }
   if (ch >= a.n_ch) return;
   const u64 k = p * a.n_ch + ch;
-  o.snap[k] = a.snap; o.rank[k] = r; o.comm[k] = c; o.channel[k] = ch;
-  o.seq_posted[k] = l0; o.chunks_sent[k] = (u32)l1; o.chunks_recv[k] = (u32)(l1 >> 32);
+  store_agent(&o.snap[k], a.snap); store_agent(&o.rank[k], r); store_agent(&o.comm[k], c); store_agent(&o.channel[k], ch);
+  store_agent(reinterpret_cast<i64*>(&o.seq_posted[k]), (i64)l0);
+  store_agent(&o.chunks_sent[k], (u32)l1); store_agent(&o.chunks_recv[k], (u32)(l1 >> 32));
 }
-// the call's end: every launch before it is over
-__global__ void k_frame_report(const u64* status, u32 call, u64* host, u64 ticket) {
-  const u64 s = *status;
-  __hip_atomic_store(host, report_word((s >> 8) == call ? s & 0xFF : 0, ticket), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+// The last workgroup reports, so the rows are stored past the caches.  (A report in a launch of its own cost 4 us of 32.)
+__global__ __launch_bounds__(256) void k_frame_rows(FrameArgs a, ccld_snapshot_rows o) {
+  __shared__ u32 s_last;
+  const u64 s = *a.status;
+  if ((s >> 8) != a.call) frame_row(a, o, (u64)blockIdx.x * 256 + threadIdx.x);
+  if (!last_arrival(a.arrivals, gridDim.x, &s_last) || threadIdx.x != 0) return;
+  __hip_atomic_store(a.host, report_word((s >> 8) == a.call ? s & 0xFF : 0, a.ticket), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace ccld
@@ -1245,6 +1262,8 @@ static ccld_status hang_status(uint64_t bits) {
 // context's workspace or from the library's static device array.
 struct HangScratch {
   uint64_t* counters;        // [CNT_COUNT]
+  uint32_t* fill;            // [SPLIT_REGIONS]
+  bool* clear;               // counters and fill are clear (kept from pass to pass), or null: not known
   uint64_t* cell;            // [n_cell][2]
   uint32_t* cnt;             // presence bitmap, one bit per cell
   int64_t* pair;             // [CCLD_HPAIR_NCOL][n_members]
@@ -1263,7 +1282,7 @@ struct HangScratch {
 
 static HangScratch scratch_of_context(ccld_ctx* c, bool on_device) {
   HangScratch S;
-  S.counters = c->counters; S.cell = c->h_cell; S.cnt = c->h_cnt; S.pair = c->h_pair; S.hcomm = c->h_comm;
+  S.counters = c->h_counters; S.fill = reinterpret_cast<uint32_t*>(c->h_counters + CNT_COUNT); S.clear = &c->h_clear; S.cell = c->h_cell; S.cnt = c->h_cnt; S.pair = c->h_pair; S.hcomm = c->h_comm;
   S.wait_slot = c->h_wait_slot; S.cand = c->h_cand; S.layer_max = c->h_layer_max;
   S.sb.key[0] = c->sb.key[0]; S.sb.idx[0] = c->sb.idx[0]; S.sb.key[1] = c->sb.key[1]; S.sb.idx[1] = c->sb.idx[1];
   S.sb.table = c->table2; S.sb.totals = c->totals2;
@@ -1298,7 +1317,7 @@ static hipError_t snapshot_args(ccld_ctx* c, const HangScratch& S, const ccld_sn
   a.cand = S.cand; a.layer_max = S.layer_max; a.counters = S.counters;
   a.stall_snapshots = c->p.stall_snapshots; a.fifo_depth = c->p.fifo_depth;
   a.n_cell = n_cell; a.mark = reinterpret_cast<uint32_t*>(S.layer_max);
-  a.root_key = reinterpret_cast<int64_t*>(S.keyC); a.cb = c->kf.cb; a.host = c->h_pinned;
+  a.root_key = reinterpret_cast<int64_t*>(S.keyC); a.cb = c->kf.cb; a.host = c->h_pinned; a.arrivals = c->arrivals;
   return hipSuccess;
 }
 
@@ -1376,9 +1395,9 @@ static bool split_regions(HangArgs& a, const HangScratch& S, size_t (*lds)(u32, 
   while (sb > pb && ((a.n_members - 1) >> (sb - 1)) < SPLIT_REGIONS) --sb;
   const uint64_t regions = ((a.n_members - 1) >> sb) + 1;
   if (regions > SPLIT_REGIONS || per_member > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, pb) > lds_max || sb - pb > parts ||
-      regions > a.n_cell / 32 + 1) return false;
+      (!S.clear && regions > a.n_cell / 32 + 1)) return false;
   a.sb = sb; a.pb = pb; a.n_regions = (uint32_t)regions; a.snap_inv = (uint32_t)((1ull << 32) / a.n_snap + 1);
-  a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.cnt;
+  a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.fill; a.leave_clear = S.clear != nullptr;
   return true;
 }
 template <int THREADS, int U>
@@ -1389,8 +1408,9 @@ static void launch_split_of(hipStream_t st, const HangArgs& a) {
   g = (a.n_rows + chunk - 1) / chunk;
   hipLaunchKernelGGL(HIP_KERNEL_NAME(k_hang_split<THREADS, U>), dim3((uint32_t)g), dim3(THREADS), CHUNK * 18, st, a, chunk);
 }
-static void launch_split(hipStream_t st, const HangArgs& a) {
-  hipLaunchKernelGGL(k_hang_clear, dim3(1), dim3(SPLIT_REGIONS), 0, st, a);
+static void launch_split(hipStream_t st, const HangArgs& a, const HangScratch& S) {
+  if (!S.clear || !*S.clear) hipLaunchKernelGGL(k_hang_clear, dim3(1), dim3(SPLIT_REGIONS), 0, st, a);
+  if (S.clear) *S.clear = false;       // until the pass has reported
   // few rows: smaller rounds, for the sake of more workgroups
   if (a.n_rows < (1u << 18)) launch_split_of<512, 2>(st, a);
   else launch_split_of<512, 6>(st, a);
@@ -1419,10 +1439,10 @@ static ccld_status locate_hang_on(ccld_ctx* c, const HangScratch& S, const ccld_
   a.out_root = o->root; a.root_cap = o->root_cap;
   for (bool split = split_regions(a, S, region_lds, SPLIT_LDS, 0);; split = false) {
     a.ticket = take_ticket(c);
-    if (!split) a.final = reinterpret_cast<ulonglong2*>(S.cell);
+    if (!split) { a.final = reinterpret_cast<ulonglong2*>(S.cell); a.leave_clear = 0; if (S.clear) *S.clear = false; }
     c->prof.begin(CCLD_PROF_HANG_PLACE);
     if (split) {
-      launch_split(st, a);
+      launch_split(st, a, S);
       const size_t lds = region_lds(a.n_ch, a.n_snap, a.sb);
       if (((uint64_t)a.n_ch * a.n_snap << a.sb) >= 8192) hipLaunchKernelGGL(k_hang_region<1024>, dim3(a.n_regions), dim3(1024), lds, st, a);
       else hipLaunchKernelGGL(k_hang_region<256>, dim3(a.n_regions), dim3(256), lds, st, a);
@@ -1439,6 +1459,7 @@ static ccld_status locate_hang_on(ccld_ctx* c, const HangScratch& S, const ccld_
     c->prof.end(CCLD_PROF_HANG);
     HIP_TRY(hipGetLastError());
     HIP_TRY(wait_report(c));
+    if (split && S.clear) *S.clear = true;
     if (!split || !(c->h_pinned[CNT_STATUS] & DS_SUSPECT)) break;      // an operation counter too large to be regrouped
   }
   const uint64_t bits = snapshot_status(c, n_rows, n_cell);
@@ -1537,6 +1558,7 @@ extern "C" ccld_status ccld_locate_hang_static(ccld_ctx* c, const ccld_snapshots
   S.counters = w.take<uint64_t>(CNT_COUNT);
   S.cell = w.take<uint64_t>(2 * n_cell);
   S.cnt = w.take<uint32_t>(n_cell / 32 + 1);
+  S.fill = S.cnt; S.clear = nullptr;
   S.pair = w.take<int64_t>((uint64_t)CCLD_HPAIR_NCOL * nm);
   S.hcomm = w.take<int64_t>((uint64_t)CCLD_HCOMM_NCOL * nc);
   S.wait_slot = w.take<int32_t>(nm);
@@ -1575,14 +1597,13 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
     a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
     a.ticket = take_ticket(c);
     hipLaunchKernelGGL(k_rate_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a, c->rate_root);
-    launch_report(st, a.counters, a.host, a.ticket);
     c->prof.end(CCLD_PROF_HANG);
   };
   HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));
   bool split = split_regions(a, S, rate_region_lds, RATE_LDS, RATE_PARTS);
   if (split) {
     c->prof.begin(CCLD_PROF_HANG_PLACE);
-    launch_split(st, a);
+    launch_split(st, a, S);
     c->prof.split(CCLD_PROF_HANG_PLACE, CCLD_PROF_HANG);
     const size_t lds = rate_region_lds(a.n_ch, a.n_snap, a.pb);
     const uint32_t groups = a.sb == a.pb ? a.n_regions : ((a.n_regions + 7) / 8 * 8) << (a.sb - a.pb);
@@ -1594,11 +1615,14 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
     tables(false);
     HIP_TRY(hipGetLastError());
     HIP_TRY(wait_report(c));
+    *S.clear = true;
     const uint64_t bits = snapshot_status(c, n_rows, n_cell);
     split = !(bits & DS_SUSPECT);
     if (split && bits) { c->prof.collect(); return o->status = hang_status(bits); }
   }
   if (!split) {
+    a.leave_clear = 0;
+    *S.clear = false;
     // One row per cell is the normal case: the rows are placed without the presence bitmap (its atomics are a
     // third of the placement's time) and the per-member pass looks for cells that nobody wrote.  If it finds one
     // and no row was refused for a worse reason, or if the row count already rules the normal case out, the
@@ -1607,7 +1631,7 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
       HIP_TRY(place_snapshots(c, S, sn, n_rows, n_cell, a, exact));
       if (nm) hipLaunchKernelGGL(k_rate_pairs, dim3((nm + 3) / 4), dim3(256), 0, st, a);
       HIP_TRY(hipGetLastError());
-      HIP_TRY(hipMemcpyAsync(c->h_pinned, c->counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(c->h_pinned, S.counters, sizeof(uint64_t) * CNT_COUNT, hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
       if (exact || c->h_pinned[CNT_STATUS] != (uint64_t)DS_SUSPECT) break;
       c->prof.end(CCLD_PROF_HANG);
@@ -1661,12 +1685,11 @@ extern "C" ccld_status ccld_decode_frames(ccld_ctx* c, const ccld_frames* fr, co
   }
   a.n_frames = fr->n_frames; a.n_ch = fr->n_channels; a.snap = fr->snapshot; a.mb = c->kf.mb; a.T = c->topo;
   a.n_members = c->n_members; a.last = c->f_last; a.frame_of = c->f_frame; a.status = c->f_status; a.call = ++c->f_call;
-  a.ticket = take_ticket(c);
+  a.arrivals = c->arrivals; a.host = c->h_pinned; a.ticket = take_ticket(c);
   c->prof.begin(CCLD_PROF_FRAMES);
   const uint64_t slots = c->n_members * CCLD_FRAME_CHANNELS;
   if (fr->n_frames) hipLaunchKernelGGL(k_frames_check, dim3((uint32_t)((fr->n_frames + 3) / 4)), dim3(256), 0, st, a);
   hipLaunchKernelGGL(k_frame_rows, dim3((uint32_t)((slots + 255) / 256)), dim3(256), 0, st, a, *rows);
-  hipLaunchKernelGGL(k_frame_report, dim3(1), dim3(1), 0, st, (const u64*)a.status, a.call, c->h_pinned, a.ticket);
   c->prof.end(CCLD_PROF_FRAMES);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c, 1));

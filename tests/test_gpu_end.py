@@ -122,3 +122,28 @@ def test_calls_that_report_from_their_last_kernel_in_turn():
         assert np.array_equal(order, ref.order)
         o = orc.Oracle(topo) if i == 9 else o
     an.close()
+
+
+def test_snapshots_of_more_regions_than_the_pass_before():
+    """hang location and rates on one context over few, many and few snapshots: a pass leaves the fills of every region clear"""
+    from paper_2605_04478_amd import ccld
+    n = 1024
+    topo = tg.make_topology(n, [list(range(i, i + 16)) for i in range(0, n, 16)] + [list(range(i, n, 64)) for i in range(64)])
+    m = int(topo.size.sum())
+    comm = np.repeat(np.arange(topo.n_comms), topo.size)
+    rank = np.concatenate([topo.members_of(c) for c in range(topo.n_comms)])
+    rng = np.random.default_rng(5)
+    an = ccld.Analyzer(topo, max_window_records=64, max_snapshot_rows=m * 64)
+    for n_snap, n_ch in ((2, 1), (16, 4), (2, 1), (7, 2), (16, 4)):
+        i = rng.permutation(m * n_snap * n_ch)
+        q, s, ch = i // (n_snap * n_ch), i % n_snap, i // n_snap % n_ch
+        stuck = q % 97 == 5
+        cols = {"snap": s, "rank": rank[q], "comm": comm[q], "channel": ch, "seq_posted": np.where(stuck, 3, 4 + s),
+                "chunks_sent": np.where(stuck, 2, s), "chunks_recv": np.where(stuck, 1, s)}
+        cols = {k: v.astype(np.uint64 if k == "seq_posted" else np.uint32) for k, v in cols.items()}
+        h, want = an.locate_hang(an.snapshots_to_device(cols), n_snap, n_ch), orc.Oracle(topo).locate_hang(cols, n_snap, n_ch)
+        r, rate = an.progress_rates(an.snapshots_to_device(cols), n_snap, n_ch), orc.Oracle(topo).progress_rates(cols, n_snap, n_ch)
+        assert h.status == want.status and r.status == rate.status, (n_snap, n_ch)
+        assert all(np.array_equal(h.root[k], want.root[k]) for k in want.root), (n_snap, n_ch)
+        assert all(np.array_equal(r.comm[k], rate.comm[k]) for k in rate.comm), (n_snap, n_ch)
+    an.close()
