@@ -9,6 +9,7 @@
 
 #include "ccld_internal.h"
 #include "grid.h"
+#include "report.h"
 #include "rows.h"
 #include "window_kernels.h"
 
@@ -39,7 +40,8 @@ struct ChainArgs {
   u32* parent;               // [n_flag] parent flag or ~0
   u64* link;                 // [n_flag] an ancestor, links up to it << 32; a root leads to itself
   i64* per_rank;             // cleared by the parent kernel, or null
-  u64* looped;               // set if some links lead round in a loop
+  u32* arrivals;
+  u64* counters;             // CNT_CHAIN_LOOP is set if some links lead round in a loop
   u32 *anc[2], *dist[2];     // [n_flag] each: ancestors and links to them, where they do
 };
 
@@ -98,18 +100,14 @@ __device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
 }
 
 // The parent of a late entry: PARENT_LANES lanes per flag.  What takes the time is chains of dependent loads (the binary
-// search over a communicator's rounds makes two per step), so the lanes of a flag search its rank's communicators
-// side by side, and the flag list in PARENT_LANES + 1 parts at a time (8,000 flags: 42 us with a thread per flag).
-constexpr u32 PARENT_LANES = 4;
+// search over a communicator's rounds makes two per step), so the lanes of a flag search its rank's communicators side by side,
+// SEARCH_LANES to a communicator: one looks at the middle and two at the middles of both halves, which is two steps of
+// the same search at a time.  The flag list is searched in PARENT_LANES + 1 parts at a time.
+constexpr u32 PARENT_LANES = 16, SEARCH_LANES = 4;
 struct ChainBefore { i64 exit, enter; u32 comm, row; bool have; };
 template <bool GRID>
-__global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
-  const u32 t256 = blockIdx.x * 256 + threadIdx.x;
-  if (a.per_rank)
-    for (u64 i = t256; i < (u64)CCLD_CHR_NCOL * a.T.n_ranks; i += (u64)gridDim.x * 256) a.per_rank[i] = 0;
-  const u32 k = t256 / PARENT_LANES, l = t256 % PARENT_LANES;
+__device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
   const u32 group0 = lane_id() & ~(PARENT_LANES - 1);
-  if (k >= a.n_flag) return;                     // whole groups
   const ChainFlag F = chain_flag<GRID>(a, k);
   u32 parent = ~0u;
   if (F.kind & CCLD_FLAG_LATE_ENTER) {
@@ -124,32 +122,45 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
     const auto take = [&](const ChainBefore& f) {
       if (f.have && (!B.have || f.exit > B.exit || (f.exit == B.exit && (f.enter > B.enter || (f.enter == B.enter && f.comm > B.comm))))) B = f;
     };
-    for (u32 q = a.T.rank_comm_off[r] + l; q < a.T.rank_comm_off[r + 1]; q += PARENT_LANES) {
+    const u32 sub = l % SEARCH_LANES, lane0 = lane_id() - sub;
+    for (u32 q = a.T.rank_comm_off[r] + l / SEARCH_LANES; q < a.T.rank_comm_off[r + 1]; q += PARENT_LANES / SEARCH_LANES) {
       const u32 c2 = a.T.rank_comms[q], slot2 = a.T.rank_slots[q], size2 = a.T.size[c2];
       u32 lo, hi;
       if (GRID) { lo = a.grid.lay[c2].seg_base; hi = lo + a.grid.lay[c2].rounds; }
       else { lo = a.comm_first[c2]; hi = a.comm_first[c2 + 1]; }
       ChainBefore f{0, 0, c2, 0, false};
-      while (lo < hi) {
+      while (lo < hi) {                          // the same in all lanes of the communicator
         const u32 mid = (lo + hi) >> 1;
-        // the nearest round at or below mid in which the rank has a record
-        u32 probe = mid, pos = 0;
+        const u32 from = sub == 2 ? mid + 1 : lo, to = sub == 1 ? mid : hi, at = sub == 0 ? mid : (from + to) >> 1;
+        // the nearest round at or below the middle in which the rank has a record
+        u32 probe = at, pos = 0;
         i64 te = 0, tx = 0;
-        bool here;
-        while (true) {
-          here = chain_record_of<GRID>(a, c2, probe, slot2, size2, &pos, &te, &tx);
-          if (here || probe == lo) break;
-          --probe;
-        }
+        bool here = false;
+        if (sub < 3 && from < to)
+          while (true) {
+            here = chain_record_of<GRID>(a, c2, probe, slot2, size2, &pos, &te, &tx);
+            if (here || probe == from) break;
+            --probe;
+          }
         const bool ok = here && pos != own && tx != T_INFLIGHT && tx <= t;
-        if (ok) { f.have = true; f.row = probe; f.exit = tx; f.enter = te; lo = mid + 1; }
-        else if (!here) lo = mid + 1;            // no record of the rank in [lo, mid]
-        else hi = probe;
+        const u32 word = (here ? 1u : 0u) | (ok ? 2u : 0u);
+        // one step of the search with what lane k of the communicator found, at the middle of [lo, hi)
+        auto step = [&](u32 k) {
+          const u32 w = (u32)__shfl((int)word, (int)(lane0 + k), CCLD_WAVE), p = (u32)__shfl((int)probe, (int)(lane0 + k), CCLD_WAVE);
+          const i64 e = (i64)shfl_u64((u64)te, (int)(lane0 + k)), x = (i64)shfl_u64((u64)tx, (int)(lane0 + k));
+          const u32 m = (lo + hi) >> 1;
+          if (w & 2u) { f.have = true; f.row = p; f.exit = x; f.enter = e; lo = m + 1; }
+          else if (!(w & 1u)) lo = m + 1;        // no record of the rank in [lo, m]
+          else hi = p;
+        };
+        const u32 lo0 = lo;
+        step(0);
+        if (lo < hi && (lo != lo0 || hi == mid)) step(lo != lo0 ? 2u : 1u);      // the half that a lane has looked at
       }
       take(f);
     }
 #pragma unroll
-    for (u32 m = 1; m < PARENT_LANES; m <<= 1) {
+    for (u32 m = SEARCH_LANES; m < PARENT_LANES; m <<= 1) {
       const ChainBefore o{(i64)shfl_xor_u64((u64)B.exit, m), (i64)shfl_xor_u64((u64)B.enter, m), __shfl_xor(B.comm, m, CCLD_WAVE),
                           __shfl_xor(B.row, m, CCLD_WAVE), __shfl_xor((int)B.have, m, CCLD_WAVE) != 0};
       take(o);
@@ -199,6 +210,14 @@ __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
     a.link[k] = parent == ~0u ? (u64)k : (u64)parent | (u64)1 << 32;
   }
 }
+constexpr u32 PARENT_BLOCKS = 1u << 20;
+template <bool GRID>
+__global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
+  const u32 t = blockIdx.x * 256 + threadIdx.x, threads = gridDim.x * 256;
+  if (a.per_rank)
+    for (u64 i = t; i < (u64)CCLD_CHR_NCOL * a.T.n_ranks; i += threads) a.per_rank[i] = 0;
+  for (u64 k = t / PARENT_LANES; k < a.n_flag; k += threads / PARENT_LANES) chain_parent<GRID>(a, (u32)k, t % PARENT_LANES);
+}
 
 // Links that lead round in a loop: jumps in step, 2^i links after the i-th, from one pair of arrays into the other.
 __global__ __launch_bounds__(256) void k_chain_init(ChainArgs a) {
@@ -237,9 +256,7 @@ __device__ __forceinline__ void wave_count_by_index(i64* column, u32 idx, bool o
 // no root and what a flag finds would depend on who was faster, so the call is repeated with LOOPED on the ancestors that
 // the kernels below find, the same ones every time.
 template <bool GRID, bool LOOPED>
-__global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64 chain_cap) {
-  const u32 k = blockIdx.x * 256 + threadIdx.x;
-  if (k >= a.n_flag) return;
+__device__ __forceinline__ void chain_emit(const ChainArgs& a, u32 k, i64* chain, u64 chain_cap) {
   auto rank_at = [&](u32 flag) -> u32 {
     const ChainFlag f = chain_flag<GRID>(a, flag);
     return a.T.members_sorted[a.T.member_off[f.comm] + f.slot];
@@ -253,7 +270,7 @@ __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64
       const u64 w = (u64)load_agent(reinterpret_cast<const i64*>(&a.link[up]));
       if ((w >> 32) == 0) break;                 // up is a root: every other link has a length, a loop's included
       v = (u64)(u32)w | ((v >> 32) + (w >> 32)) << 32;
-      if ((v >> 32) > a.n_flag) { *a.looped = 1; break; }        // more links than flags: a loop
+      if ((v >> 32) > a.n_flag) { store_agent(reinterpret_cast<i64*>(&a.counters[CNT_CHAIN_LOOP]), 1); break; }        // more links than flags: a loop
       store_agent(reinterpret_cast<i64*>(&a.link[k]), (i64)v);
     }
   }
@@ -261,10 +278,11 @@ __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64
   i64* per_rank = a.per_rank;
   const u32 root_rank = rank_at(root);
   if (k < chain_cap) {
-    chain[(u64)CCLD_CHN_PARENT * chain_cap + k] = p == ~0u ? -1 : (i64)p;
-    chain[(u64)CCLD_CHN_ROOT * chain_cap + k] = (i64)root;
-    chain[(u64)CCLD_CHN_ROOT_RANK * chain_cap + k] = (i64)root_rank;
-    chain[(u64)CCLD_CHN_DEPTH * chain_cap + k] = (i64)(v >> 32);
+    auto put = [&](int col, i64 x) { store_agent(&chain[(u64)col * chain_cap + k], x); };
+    put(CCLD_CHN_PARENT, p == ~0u ? -1 : (i64)p);
+    put(CCLD_CHN_ROOT, (i64)root);
+    put(CCLD_CHN_ROOT_RANK, (i64)root_rank);
+    put(CCLD_CHN_DEPTH, (i64)(v >> 32));
   }
   if (per_rank) {
     const bool on = (chain_flag<GRID>(a, k).kind & CCLD_FLAG_LATE_ENTER) != 0;
@@ -274,6 +292,13 @@ __global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64
     wave_count_by_index(per_rank + (u64)CCLD_CHR_SECONDARY_ENTRIES * n_ranks, mine, on && p != ~0u);
     wave_count_by_index(per_rank + (u64)CCLD_CHR_CAUSED * n_ranks, root_rank, on);
   }
+}
+// The last workgroup reports, so the table is stored past the caches.
+template <bool GRID, bool LOOPED>
+__global__ __launch_bounds__(256) void k_chain_emit(ChainArgs a, i64* chain, u64 chain_cap, u64* host, u64 ticket) {
+  const u32 k = blockIdx.x * 256 + threadIdx.x;
+  if (k < a.n_flag) chain_emit<GRID, LOOPED>(a, k, chain, chain_cap);
+  report_counters(a.counters, a.arrivals, host, ticket);
 }
 
 }  // namespace ccld
@@ -294,13 +319,10 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
   const uint32_t n_flag = (uint32_t)c->last_n_flag, n_ranks = c->topo.n_ranks;
   o->n_chain = n_flag;
   if (o->per_rank && !n_flag) HIP_TRY(hipMemsetAsync(o->per_rank, 0, sizeof(int64_t) * CCLD_CHR_NCOL * (uint64_t)n_ranks, st));
-  auto report = [&]() -> hipError_t {
-    launch_report(st, c->counters, c->h_pinned, take_ticket(c));
-    const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : wait_report(c);
-  };
   if (!n_flag) {
-    HIP_TRY(report());
+    launch_report(st, c->counters, c->h_pinned, take_ticket(c));
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
   } else {
     ChainArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -314,29 +336,33 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
     a.comm_first = c->chain_first; a.parent = c->chain_parent;
     a.link = reinterpret_cast<uint64_t*>(c->range_c);                // scratch that the analysis no longer needs
     a.per_rank = o->per_rank;
-    const dim3 blocks((n_flag + 255) / 256), parents((uint32_t)(((uint64_t)n_flag * PARENT_LANES + 255) / 256));
-    a.looped = &c->counters[CNT_CHAIN_LOOP];       // cleared by the analysis; its flags lead round or they do not
+    const dim3 blocks((n_flag + 255) / 256), parents((uint32_t)std::min<uint64_t>(((uint64_t)n_flag * PARENT_LANES + 255) / 256, PARENT_BLOCKS));
+    a.arrivals = c->arrivals; a.counters = c->counters;                      // CNT_CHAIN_LOOP: cleared by the analysis; its flags lead round or they do not
+    take_ticket(c);
     if (grid) {
       hipLaunchKernelGGL(k_chain_parent<true>, parents, dim3(256), 0, st, a);
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
     } else {
       hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
       hipLaunchKernelGGL(k_chain_parent<false>, parents, dim3(256), 0, st, a);
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
     }
-    HIP_TRY(report());
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(wait_report(c));
     if (c->h_pinned[CNT_CHAIN_LOOP]) {
       a.anc[0] = reinterpret_cast<uint32_t*>(a.link); a.dist[0] = a.anc[0] + n_flag;
       a.anc[1] = c->alert_list; a.dist[1] = c->alert_ncand;
+      take_ticket(c);
       hipLaunchKernelGGL(k_chain_init, blocks, dim3(256), 0, st, a);
       for (uint64_t reach = 1; reach < n_flag; reach *= 2) {
         hipLaunchKernelGGL(k_chain_jump, blocks, dim3(256), 0, st, a);
         std::swap(a.anc[0], a.anc[1]);
         std::swap(a.dist[0], a.dist[1]);
       }
-      if (grid) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
-      else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap);
-      HIP_TRY(report());
+      if (grid) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
+      else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, true>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(wait_report(c));
     }
   }
   if (o->n_chain > o->chain_cap) o->status = CCLD_W_TRUNCATED;
