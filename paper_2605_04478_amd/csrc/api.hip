@@ -552,9 +552,6 @@ static hipError_t wait_fine(ccld_ctx* c, uint32_t* n_fine, bool* full) {
   *n_fine = (v & GRID_INFEASIBLE) ? 0u : (v & ~GRID_FULL) - 1;
   return hipSuccess;
 }
-// Most fine buckets that a launch is sized for without asking for their number.
-constexpr uint32_t FINE_BOUND = 4096;
-
 // The last launches of an analysis: groups, flags (d and f: a window on the grid placement), blame order, report.
 static void launch_end(ccld_ctx* c, EndArgs& e, const GridArgs* d, const FlagArgs* f, const AlertArgs* al, uint32_t fine) {
   e.counters = c->counters; e.blame = c->blame; e.n_ranks = c->topo.n_ranks; e.order = c->blame_order;
@@ -665,6 +662,8 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   // cells that this window may take, and the fine buckets that they can make
   d.cell_cap = (uint32_t)std::min<uint64_t>(c->cell_cap, (c->cap >= (4u << 20) ? (uint64_t)n + n / 5 : 2ull * n) + 4096);
   d.fine_cap = std::min(c->fine_cap, d.cell_cap / GRID_MIN_FILL + c->topo.n_comms);
+  d.likely = n / GRID_B + c->topo.n_comms / 2;
+  d.self_sum = d.likely <= GRID_SELF_SUM && d.fine_cap <= GRID_FINE_BOUND;
   d.rows = c->g_rows; d.slots = o->perm ? c->g_slots : nullptr;
   d.cell_row = c->g_cell_row; d.counters = c->counters;
   d.blame = (uint64_t*)c->blame; d.n_blame = CCLD_BLM_NCOL * n_ranks;
@@ -676,7 +675,7 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   c->prof.split(CCLD_PROF_DENSE_PARTITION, CCLD_PROF_SEGMENTS);
   c->sort_passes = 1;
   uint32_t fine = d.fine_cap;
-  if (fine > FINE_BOUND) {
+  if (fine > GRID_FINE_BOUND) {
     HIP_TRY(hipGetLastError());
     bool full;
     HIP_TRY(wait_fine(c, &fine, &full));

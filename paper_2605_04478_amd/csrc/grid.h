@@ -14,6 +14,8 @@ constexpr uint32_t GRID_B = 2048;            // grid cells (= LDS cells of the s
 constexpr uint32_t GRID_MIN_FILL = 1025;     // a full fine bucket holds at least this many cells (whole rounds of <= GRID_B members)
 constexpr uint32_t GRID_SPAN = 4096;         // fine buckets of one coarse bucket that a partition workgroup addresses
 constexpr uint32_t GRID_ONE_BUCKET = 3500;   // windows of no more fine buckets are partitioned in one go, without communicator buckets
+constexpr uint32_t GRID_FINE_BOUND = 4096;   // most fine buckets that a launch is sized for without asking for their number
+constexpr uint32_t GRID_SELF_SUM = 512;      // where so many fine buckets are likely, each workgroup of the statistics sums the records before its own
 constexpr uint32_t GRID_TARGET = 600;        // fine buckets per communicator bucket of the others
 constexpr uint32_t GRID_MAX_COMMS = INGEST_RANGE_COMMS;
 constexpr uint32_t GRID_MAX_BATCHES = 256;   // batches of a window whose batches are placed by communicator bucket
@@ -70,12 +72,13 @@ struct GridArgs {
   uint32_t* piece_at;            // [pieces + 1] records before each (coarse bucket, batch) piece, bucket by bucket
   uint32_t* piece_slot;          // [pieces] its first window slot
   // fine buckets
-  uint32_t* fill;                // [fine_cap + 1] records of each, then (rec0) the records before it
-  uint32_t* rec0;                // [fine_cap + 1]
+  uint32_t* fill;                // [fine_cap + 1] records of each
+  uint32_t* rec0;                // [fine_cap + 1] records before each (from the statistics on, where these sum them)
   uint32_t* nflag;               // [fine_cap + 1] flagged records of each
   FineDesc* desc;                // [fine_cap]
   uint32_t* long_list;           // [fine_cap] fine buckets of communicators of more than 64 members
   uint32_t fine_cap, cell_cap;
+  uint32_t likely, self_sum;     // fine buckets that the window most likely has; 1: they are not scanned (RecordsBefore)
   uint4* rows;                   // [cell_cap] partitioned rows
   uint32_t* slots;               // [cell_cap] their window slots, or null: not wanted
   uint16_t* cell_row;            // [cell_cap] row of each cell inside its bucket, GRID_EMPTY: no record

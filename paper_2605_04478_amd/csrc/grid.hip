@@ -191,10 +191,15 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   u32* s_src = s_start + GRID_SPAN;
   // the fine buckets' descriptors and the blame table: every workgroup's share
   const u32 n_fine = d.hdr->n_fine, G = gridDim.x;
+  u32* const s_first = reinterpret_cast<u32*>(s_row);      // the communicators' first buckets, searched in LDS: 4 of 16 us of a window
+  if (blockIdx.x * PART_THREADS < n_fine) {                // of 600K records went by with a search in memory
+    for (u32 c = tid; c < d.n_comms; c += PART_THREADS) s_first[c] = d.lay[c].fb_base;
+    __syncthreads();
+  }
   for (u32 f = blockIdx.x * PART_THREADS + tid; f < n_fine; f += G * PART_THREADS) {
     // the communicator whose fine buckets include f: the last one whose first bucket is <= f
     u32 lo = 0, hi = d.n_comms;
-    while (lo < hi) { const u32 m = (lo + hi) >> 1; if (d.lay[m].fb_base <= f) lo = m + 1; else hi = m; }
+    while (lo < hi) { const u32 m = (lo + hi) >> 1; if (s_first[m] <= f) lo = m + 1; else hi = m; }
     const u32 c = lo - 1;
     const CommLayout L = d.lay[c];
     const u32 r0 = (f - L.fb_base) * L.rpb;
@@ -348,8 +353,9 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) status |= shfl_xor_u64(status, m);
   if (lane_id() == 0 && status) atomicOr((unsigned long long*)&d.counters[CNT_STATUS], (unsigned long long)status);
-  // the last workgroup to finish scans the records per fine bucket
-  if (!last_block(&d.hdr->done, G, &s_last)) return;
+  // the last workgroup to finish scans the records per fine bucket; few buckets are summed by the statistics kernels' workgroups
+  // for themselves
+  if (d.self_sum || !last_block(&d.hdr->done, G, &s_last)) return;
   u32 carry = 0;
   for (u32 base = 0; base < n_fine; base += PART_THREADS * 4) {
     u32 v[4], sum = 0;
@@ -364,6 +370,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   if (tid == 0) d.rec0[n_fine] = carry;
 }
 static_assert(GRID_SPAN % PART_THREADS == 0, "whole buckets per thread");
+static_assert(GRID_MAX_COMMS * 4 <= PART_CHUNK * 16, "the first buckets fit the staging area");
 static_assert(ROW_CELL_SHIFT == 16 && ROW_CELL_MASK == GRID_B - 1, "the cell is packed as the row has it");
 
 constexpr size_t PART_LDS = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, PART_LDS_SLOTS = PART_LDS + (size_t)PART_CHUNK * 4;
@@ -382,7 +389,7 @@ void launch_grid_partition(hipStream_t st, const GridArgs& d) {
 // The statistics find them too, but behind them the whole window has still to be sorted: here they end the placement of a
 // window whose statistics take long, before these run.  A round can only be missing from a fine bucket that has at least
 // that many records fewer than cells; such buckets mark the rounds of their rows, a wavefront each.  Taken by windows of
-// more than FINE_BOUND fine buckets that have fewer records than cells: 20M records with one round missing 1.99 -> 1.79 ms,
+// more than GRID_FINE_BOUND fine buckets that have fewer records than cells: 20M records with one round missing 1.99 -> 1.79 ms,
 // the steps of a 20M-record stream that have one in the window 1.41 -> 1.27; where no round is missing it costs 5 us.
 constexpr u32 GAP_THREADS = 256, GAP_BLOCKS = 2048;
 __global__ __launch_bounds__(GAP_THREADS) void k_grid_gaps(GridArgs d) {
@@ -393,7 +400,7 @@ __global__ __launch_bounds__(GAP_THREADS) void k_grid_gaps(GridArgs d) {
   u32* const mark = s_round[wave];
   for (u32 f = blockIdx.x * NW + wave; f < n_fine; f += gridDim.x * NW) {
     const FineDesc D = d.desc[f];
-    const u32 cells = D.K * D.size, cnt = d.rec0[f + 1] - d.rec0[f];
+    const u32 cells = D.K * D.size, cnt = d.fill[f];
     if (cnt + D.size > cells) continue;
     if (lane < WORDS) mark[lane] = 0;
     __builtin_amdgcn_wave_barrier();

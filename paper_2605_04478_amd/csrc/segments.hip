@@ -1216,13 +1216,39 @@ struct GridShared {
   uint4 row[GRID_B];                     // rows by cell; y bits 16-26: number of the row in its bucket
   u32 pres[GRID_B / 32];
   unsigned short pre[ROUNDS];            // records of the bucket before each of its rounds
-  u32 wave[1024 / CCLD_WAVE];
+  u32 wave[1024 / CCLD_WAVE], rec0;      // rec0: records of the window before the bucket
   GridFlags flags;
 };
+// Records before fine bucket f.  The scan of the counts at the end of the partition is a chain of its own, and its workgroups
+// arrive at one word; where GRID_SELF_SUM buckets are likely their sum is a load or two per thread, on their way together with
+// the bucket's rows (384 buckets: a stream's step 118.7 -> 113.0 us).  At 900 and 3,900 buckets the sums cost 2 and 5 us more
+// than the scan.
+template <bool SELF_SUM>
+struct RecordsBefore {
+  u32 part;
+  template <int THREADS>
+  static __device__ __forceinline__ RecordsBefore load(const GridArgs& d, u32 f, bool scanned) {
+    u32 v = 0;
+    if (!scanned) {
+#pragma unroll 2
+      for (u32 i = threadIdx.x; i < f; i += THREADS) v += d.fill[i];
+    } else if (threadIdx.x == 0) {
+      v = d.rec0[f];
+    }
+    return {v};
+  }
+  // s_sum: a word of LDS, zero before the last barrier and complete behind the next one
+  __device__ __forceinline__ void add(u32* s_sum) const {
+    const u32 v = wave_sum(part);
+    if (lane_id() == 0 && v) atomicAdd(s_sum, v);
+  }
+};
+template <>
+struct RecordsBefore<false> { __device__ __forceinline__ void add(u32*) const {} };
 // Places bucket f's rows in LDS.  Returns status bits: a cell taken twice or more rows than cells (duplicate keys), a
 // round without any record (a hole in the grid).  Ends with a barrier.
-template <int THREADS, u32 ROUNDS>
-__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, GridShared<ROUNDS>& S) {
+template <int THREADS, u32 ROUNDS, bool SELF_SUM>
+__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, const RecordsBefore<SELF_SUM>& before, GridShared<ROUNDS>& S) {
   constexpr u32 U = GRID_B / THREADS;
   const u32 tid = threadIdx.x, cells = D.K * D.size;
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
@@ -1235,8 +1261,9 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
     if (i < cnt) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.rows + D.cell0 + i));
   }
   for (u32 i = tid; i < GRID_B / 32; i += THREADS) { S.pres[i] = 0; S.flags.bits[i] = 0; }
-  if (tid == 0) S.flags.n = 0;
+  if (tid == 0) { S.flags.n = 0; S.rec0 = 0; }
   __syncthreads();
+  before.add(&S.rec0);
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
     const u32 i = tid + u * THREADS;
@@ -1496,7 +1523,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
   return mine;
 }
 
-template <int GRID_THREADS>
+template <int GRID_THREADS, bool SELF_SUM>       // SELF_SUM: as d.self_sum
 __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   __shared__ GridShared<GRID_B> S;
   __shared__ u32 s_slot[CCLD_WAVE];
@@ -1506,9 +1533,18 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
   const FineDesc D = d.desc[f];
   if (D.size > (u32)SEG_WAVE_MAX) return;               // k_grid_long takes it
   const i64 wref = d.hdr->ref;
-  const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size;
+  const u32 cnt = d.fill[f], size = D.size;
   if (tid < CCLD_WAVE) s_slot[tid] = 0;
-  u64 bad = grid_place<GRID_THREADS>(d, D, cnt, S);
+  u64 bad;
+  u32 rec0;
+  if constexpr (SELF_SUM) {
+    bad = grid_place<GRID_THREADS>(d, D, cnt, RecordsBefore<true>::load<GRID_THREADS>(d, f, false), S);
+    rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
+    if (tid == 0) d.rec0[f] = rec0;
+  } else {
+    rec0 = d.rec0[f];
+    bad = grid_place<GRID_THREADS>(d, D, cnt, RecordsBefore<false>{}, S);
+  }
   u32 mine;
   if (size <= 2) mine = grid_batches<2>(a, d, D, rec0, wref, S, lane, wave, NW);
   else if (size <= 4) mine = grid_batches<4>(a, d, D, rec0, wref, S, lane, wave, NW);
@@ -1868,14 +1904,18 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
   const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
   if (d.hdr->feasible == 0) return;
   const u32 n_long = d.hdr->n_long;
+  const bool scanned = !d.self_sum;
   const i64 wref = d.hdr->ref;
   for (u32 ent = blockIdx.x; ent < n_long; ent += gridDim.x) {
     const u32 f = d.long_list[ent];
     const FineDesc D = d.desc[f];
-    const u32 rec0 = d.rec0[f], cnt = d.fill[f], size = D.size, K = D.K;
+    const u32 cnt = d.fill[f], size = D.size, K = D.K;
     if (size <= ABOVE || size > MEMBERS) continue;
+    const RecordsBefore<true> before = RecordsBefore<true>::load<THREADS>(d, f, scanned);
     for (u32 i = tid; i < size; i += THREADS) s_slot[i] = 0;
-    const u64 bad = grid_place<THREADS>(d, D, cnt, S);
+    const u64 bad = grid_place<THREADS>(d, D, cnt, before, S);
+    const u32 rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
+    if (tid == 0) d.rec0[f] = rec0;
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
     if constexpr (WAVES) {
       long_rounds<E>(a, d, D, rec0, wref, S, s_slot, s_out, lane, wave, NW);
@@ -2040,15 +2080,12 @@ void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint
   // Where there are no more fine buckets than compute units, or than two to each, a workgroup has sixteen or eight wavefronts
   // instead of four: what takes the time then is one bucket's passes one after the other (16 ranks, 8 buckets: a window
   // 70.9 -> 62.8 us).  More buckets overlap each other with four workgroups to a compute unit.
-  const u32 likely = a.n / GRID_MIN_FILL + d.n_comms / 2;
-  auto stats = [&](auto threads) {
-    hipLaunchKernelGGL((k_grid_stats<decltype(threads)::value>), dim3(fine_bound), dim3(decltype(threads)::value), 0, st, a, d, blame, n_ranks);
-  };
-  if (likely <= 256) stats(std::integral_constant<int, 1024>{});
-  else if (likely <= 512) stats(std::integral_constant<int, 512>{});
-  else stats(std::integral_constant<int, 256>{});
+  const dim3 g(fine_bound);
+  if (d.self_sum && d.likely <= 256) hipLaunchKernelGGL((k_grid_stats<1024, true>), g, dim3(1024), 0, st, a, d, blame, n_ranks);
+  else if (d.self_sum) hipLaunchKernelGGL((k_grid_stats<512, true>), g, dim3(512), 0, st, a, d, blame, n_ranks);
+  else hipLaunchKernelGGL((k_grid_stats<256, false>), g, dim3(256), 0, st, a, d, blame, n_ranks);
   // as many workgroups as are resident at once, which take the listed buckets in turn
-  const bool few = likely <= 256;
+  const bool few = d.likely <= 256;
   if (a.long_classes & 1) {
     if (few) hipLaunchKernelGGL((k_grid_long<2, 1024>), dim3(256), dim3(1024), 0, st, a, d, blame, n_ranks);
     else hipLaunchKernelGGL((k_grid_long<2, 256>), dim3(1024), dim3(256), 0, st, a, d, blame, n_ranks);

@@ -147,3 +147,23 @@ def test_snapshots_of_more_regions_than_the_pass_before():
         assert all(np.array_equal(h.root[k], want.root[k]) for k in want.root), (n_snap, n_ch)
         assert all(np.array_equal(r.comm[k], rate.comm[k]) for k in rate.comm), (n_snap, n_ch)
     an.close()
+
+
+@pytest.mark.parametrize("n_comms", [1, 510, 511, 512, 513, 1022, 1023, 1024, 1025, 1026])
+def test_windows_around_the_rules_of_the_statistics(n_comms):
+    """communicators of two and of 70 members, a fine bucket each: wavefronts per bucket, records summed or scanned"""
+    topo = tg.make_topology(1024, [[c % 1000, c % 1000 + 1 + c // 1000] if c % 8 or n_comms > 600 else list(range(70)) for c in range(n_comms)])
+    for rounds in (1, 3):
+        m = [np.asarray(topo.members_of(c)) for c in range(n_comms)]
+        comm = np.repeat(np.arange(n_comms), [x.size * rounds for x in m])
+        rank = np.concatenate([np.tile(x, rounds) for x in m])
+        seq = np.concatenate([np.repeat(np.arange(rounds), x.size) for x in m])
+        rng = np.random.default_rng(n_comms)
+        te = T0 + seq * 10**9 + rng.integers(0, 1000, comm.size)
+        te[rng.random(comm.size) < 0.05] += 10**7
+        keep = rng.random(comm.size) < 0.98
+        keep[0] = True
+        p = rng.permutation(np.flatnonzero(keep))
+        cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": seq.astype(np.uint64), "op": np.ones(comm.size, np.uint8),
+                "bytes": np.full(comm.size, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**7}
+        run_both(topo, {k: v[p] for k, v in cols.items()}, what=(n_comms, rounds))
