@@ -165,6 +165,8 @@ struct ccld_ctx {
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging
   uint64_t ticket;                    // of the latest report that the device was asked for
+  int device;                         // the device that the context was created on
+  hipStream_t copy_stream[2];         // of the threads that help to copy host batches, made for the first large one
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location and rates
