@@ -13,30 +13,36 @@ namespace ccld {
 // bucket.  The layout is infeasible (the host then sorts) when the grid has more cells or rounds than the buffers and
 // the records allow (counters that are far apart), when a coarse bucket spans more fine buckets than a partition
 // workgroup addresses, or when the batches lie so far apart that no single time serves all rows.
-// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 11 to 13 us at 1,088
+// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 7 us at 1,088
 // communicators and one batch, 31 us at 3,200 and ten.
 __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   __shared__ u32 s_wave[1024 / CCLD_WAVE];
+  __shared__ uint4 s_wave4[1024 / CCLD_WAVE];
   __shared__ u32 s_bad, s_any;
   __shared__ unsigned long long s_status;
+  __shared__ i64 s_ref;
   const u32 tid = threadIdx.x;
   if (tid == 0) { s_bad = 0; s_status = 0; s_any = 0xFFFFFFFFu; }
   if (tid < CNT_COUNT) d.counters[tid] = 0;
-  __syncthreads();
+  // the headers of the batches (those of the first 1,024 stay in registers), the pieces and the counter ranges are on their way together
   auto meta_of = [&](u32 i) -> const BatchMeta& { return d.meta[(d.slot0 + i) % d.n_meta]; };
-  for (u32 i = tid; i < d.nb; i += 1024) {
-    const BatchMeta& m = meta_of(i);
-    if (m.status) atomicOr(&s_status, (unsigned long long)m.status);
-    if (m.n) atomicMin(&s_any, i);
-  }
-  __syncthreads();
+  u64 m_status = 0, m_n = 0;
+  i64 m_ref = 0;
+  if (tid < d.nb) { const BatchMeta& m = meta_of(tid); m_status = m.status; m_n = m.n; m_ref = m.ref; }
+  // piece k: its records and its first window slot
+  const u32 n_stretches = d.n_buckets == 1 ? 0u : d.n_buckets * d.nb;
+  auto piece = [&](u32 k, u32* slot) -> u32 {
+    if (k >= n_stretches) return 0;
+    const u32 b = k / d.nb, i = k % d.nb, m = (d.slot0 + i) % d.n_meta;
+    const u32* bb = d.bucket_base + (u64)m * (d.n_buckets + 1);
+    const u32 from = bb[b], to = bb[b + 1];
+    const u64 p = d.meta[m].tail + from;
+    *slot = (u32)(p >= d.cap ? p - d.cap : p);
+    return d.meta[m].n ? to - from : 0u;
+  };
+  u32 slot0 = 0;
+  const u32 cnt0 = piece(tid, &slot0);
   bool bad = false;
-  const i64 ref = meta_of(s_any < d.nb ? s_any : 0).ref;
-  for (u32 i = tid; i < d.nb; i += 1024) {
-    const BatchMeta& m = meta_of(i);
-    const u64 off = (u64)m.ref - (u64)ref + ((u64)1 << 42);
-    if (m.n && (off >> 43) != 0) bad = true;
-  }
   // consecutive communicators per thread: all their counter ranges are loaded at once, one scan orders them
   constexpr u32 PER = (GRID_MAX_COMMS + 1023) / 1024;
   const u32 per = (d.n_comms + 1023) / 1024, c0 = tid * per;        // per <= PER
@@ -47,17 +53,30 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     mx[k] = 0; inv[k] = 0; size[k] = 0;
     if (k < per && c0 + k < d.n_comms) size[k] = d.comm_size[c0 + k];
   }
-  u32 m = d.slot0;
-#pragma unroll 2
-  for (u32 i = 0; i < d.nb; ++i) {
-    const ulonglong2* __restrict__ rng = reinterpret_cast<const ulonglong2*>(d.range) + (u64)m * d.n_comms;
-    m = m + 1 == d.n_meta ? 0 : m + 1;
+  constexpr u32 AHEAD = 5;              // batches whose ranges are on their way at a time
 #pragma unroll
-    for (u32 k = 0; k < PER; ++k)
-      if (k < per && c0 + k < d.n_comms) {
-        const ulonglong2 r = rng[c0 + k];
-        mx[k] = r.x > mx[k] ? r.x : mx[k]; inv[k] = r.y > inv[k] ? r.y : inv[k];
+  for (u32 k = 0; k < PER; ++k) {
+    if (k >= per) break;
+    const u32 c = c0 + k < d.n_comms ? c0 + k : d.n_comms - 1;
+    for (u32 i0 = 0, m = d.slot0; i0 < d.nb; i0 += AHEAD) {
+      ulonglong2 r[AHEAD];
+#pragma unroll
+      for (u32 u = 0; u < AHEAD; ++u) {
+        r[u] = reinterpret_cast<const ulonglong2*>(d.range)[(u64)m * d.n_comms + c];      // the last one again where there are no more
+        if (i0 + u + 1 < d.nb) m = m + 1 == d.n_meta ? 0 : m + 1;
       }
+#pragma unroll
+      for (u32 u = 0; u < AHEAD; ++u) { mx[k] = r[u].x > mx[k] ? r[u].x : mx[k]; inv[k] = r[u].y > inv[k] ? r[u].y : inv[k]; }
+    }
+    if (c0 + k >= d.n_comms) { mx[k] = 0; inv[k] = 0; }
+  }
+  __syncthreads();
+  if (m_status) atomicOr(&s_status, (unsigned long long)m_status);
+  if (m_n) atomicMin(&s_any, tid);
+  for (u32 i = tid + 1024; i < d.nb; i += 1024) {
+    const BatchMeta& b = meta_of(i);
+    if (b.status) atomicOr(&s_status, (unsigned long long)b.status);
+    if (b.n) atomicMin(&s_any, i);
   }
   u32 rounds[PER], nfb_sum = 0, rounds_sum = 0;
   u64 cells_sum = 0;
@@ -73,11 +92,20 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   }
   // the sum of the cells can pass 32 bits, so it is taken in halves (where it does, the layout is refused, and where it
   // does not, the sums of buckets and rounds do not either)
-  u32 fb_total, seg_total, tl, th;
-  u32 fb = block_exclusive_sum<1024>(nfb_sum, s_wave, &fb_total);
-  u32 seg = block_exclusive_sum<1024>(rounds_sum, s_wave, &seg_total);
-  const u32 el = block_exclusive_sum<1024>((u32)cells_sum & 0xFFFFu, s_wave, &tl);
-  const u32 eh = block_exclusive_sum<1024>((u32)(cells_sum >> 16), s_wave, &th);
+  const u32 fb_inc = wave_inclusive_sum(nfb_sum), seg_inc = wave_inclusive_sum(rounds_sum);
+  const u32 cl = (u32)cells_sum & 0xFFFFu, ch = (u32)(cells_sum >> 16), cl_inc = wave_inclusive_sum(cl), ch_inc = wave_inclusive_sum(ch);
+  if (lane_id() == CCLD_WAVE - 1) s_wave4[tid / CCLD_WAVE] = make_uint4(fb_inc, seg_inc, cl_inc, ch_inc);
+  __syncthreads();
+  u32 fb_total = 0, seg_total = 0, tl = 0, th = 0, fb = fb_inc - nfb_sum, seg = seg_inc - rounds_sum, el = cl_inc - cl, eh = ch_inc - ch;
+#pragma unroll
+  for (u32 w = 0; w < 1024 / CCLD_WAVE; ++w) {
+    const uint4 v = s_wave4[w];
+    if (w < tid / CCLD_WAVE) { fb += v.x; seg += v.y; el += v.z; eh += v.w; }
+    fb_total += v.x; seg_total += v.y; tl += v.z; th += v.w;
+  }
+  // one time serves the whole window, that of its first batch with records, unless its batches lie too far apart
+  const u32 any = s_any;
+  if (tid == (any < 1024 ? any : 0u)) s_ref = any < 1024 ? m_ref : meta_of(any < d.nb ? any : 0).ref;
   u64 cell = (u64)el + ((u64)eh << 16);
   const u64 cell_total = (u64)tl + ((u64)th << 16);
 #pragma unroll
@@ -99,10 +127,16 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     L.seg_base = (u32)seg_carry; L.cell_base = (u32)cell_carry; L.size = 1;
     d.lay[d.n_comms] = L;
   }
+  if (d.n_buckets == 1 && fb_total > GRID_SPAN) bad = true;
   if (bad) atomicOr(&s_bad, 1u);
   __threadfence_block();
   __syncthreads();
-  if (!s_bad) {
+  const i64 ref = s_ref;
+  auto far = [&](i64 t) { return (((u64)t - (u64)ref + ((u64)1 << 42)) >> 43) != 0; };
+  bool apart = m_n && far(m_ref);
+  for (u32 i = tid + 1024; i < d.nb; i += 1024) { const BatchMeta& b = meta_of(i); apart |= b.n && far(b.ref); }
+  if (apart) atomicOr(&s_bad, 1u);
+  if (d.n_buckets > 1) {
     bool wide = false;
     for (u32 b = tid; b < d.n_buckets; b += 1024) {
       u64 c0 = (u64)b << d.bshift, c1 = (u64)(b + 1) << d.bshift;
@@ -121,20 +155,12 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   if (d.n_buckets == 1) {
     if (tid == 0) { d.piece_at[0] = 0; d.piece_at[1] = d.n; d.piece_slot[0] = d.head; }
   } else {
-    n_pieces = d.n_buckets * d.nb;
+    n_pieces = n_stretches;
     u32 carry = 0;
     for (u32 base = 0; base < n_pieces; base += 1024) {
       const u32 k = base + tid;
-      u32 cnt = 0, slot = 0;
-      if (k < n_pieces) {
-        const u32 b = k / d.nb, i = k % d.nb, m = (d.slot0 + i) % d.n_meta;
-        const u32* bb = d.bucket_base + (u64)m * (d.n_buckets + 1);
-        if (d.meta[m].n) {
-          cnt = bb[b + 1] - bb[b];
-          const u64 p = d.meta[m].tail + bb[b];
-          slot = (u32)(p >= d.cap ? p - d.cap : p);
-        }
-      }
+      u32 slot = slot0;
+      const u32 cnt = base ? piece(k, &slot) : cnt0;
       u32 tot;
       const u32 ex = block_exclusive_sum<1024>(cnt, s_wave, &tot);
       if (k < n_pieces) { d.piece_at[k] = carry + ex; d.piece_slot[k] = slot; }
