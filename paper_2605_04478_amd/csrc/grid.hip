@@ -13,11 +13,13 @@ namespace ccld {
 // bucket.  The layout is infeasible (the host then sorts) when the grid has more cells or rounds than the buffers and
 // the records allow (counters that are far apart), when a coarse bucket spans more fine buckets than a partition
 // workgroup addresses, or when the batches lie so far apart that no single time serves all rows.
-// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 7 us at 1,088
-// communicators and one batch, 31 us at 3,200 and ten.
+// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 5 us at up to
+// 1,024 communicators and one batch, 19 at 3,200 and ten (31 with fewer loads on their way).
+// PER: most communicators of a thread; AHEAD: batches whose ranges are on their way at a time.
+template <u32 PER, u32 AHEAD>
 __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   __shared__ u32 s_wave[1024 / CCLD_WAVE];
-  __shared__ uint4 s_wave4[1024 / CCLD_WAVE];
+  __shared__ uint4 s_sums[CCLD_WAVE];
   __shared__ u32 s_bad, s_any;
   __shared__ unsigned long long s_status;
   __shared__ i64 s_ref;
@@ -43,33 +45,34 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   u32 slot0 = 0;
   const u32 cnt0 = piece(tid, &slot0);
   bool bad = false;
-  // consecutive communicators per thread: all their counter ranges are loaded at once, one scan orders them
-  constexpr u32 PER = (GRID_MAX_COMMS + 1023) / 1024;
-  const u32 per = (d.n_comms + 1023) / 1024, c0 = tid * per;        // per <= PER
+  // thread t has the communicators t, 1,024 + t, ..., so that neighbouring lanes read neighbouring ranges (with consecutive ones per
+  // thread every line went to the compute unit four times at 3,200 communicators)
+  constexpr u32 WAVES = 1024 / CCLD_WAVE;
+  static_assert(PER * WAVES <= CCLD_WAVE, "a lane per wavefront's sums");
   u64 mx[PER], inv[PER];
   u32 size[PER];
 #pragma unroll
   for (u32 k = 0; k < PER; ++k) {
     mx[k] = 0; inv[k] = 0; size[k] = 0;
-    if (k < per && c0 + k < d.n_comms) size[k] = d.comm_size[c0 + k];
+    if (k * 1024 + tid < d.n_comms) size[k] = d.comm_size[k * 1024 + tid];
   }
-  constexpr u32 AHEAD = 5;              // batches whose ranges are on their way at a time
+  for (u32 i0 = 0, m = d.slot0; i0 < d.nb; i0 += AHEAD) {
+    ulonglong2 r[AHEAD][PER];           // none of the loads is conditional: the compiler would wait for each
 #pragma unroll
-  for (u32 k = 0; k < PER; ++k) {
-    if (k >= per) break;
-    const u32 c = c0 + k < d.n_comms ? c0 + k : d.n_comms - 1;
-    for (u32 i0 = 0, m = d.slot0; i0 < d.nb; i0 += AHEAD) {
-      ulonglong2 r[AHEAD];
+    for (u32 u = 0; u < AHEAD; ++u) {
+      const ulonglong2* __restrict__ row = reinterpret_cast<const ulonglong2*>(d.range) + (u64)m * d.n_comms;
 #pragma unroll
-      for (u32 u = 0; u < AHEAD; ++u) {
-        r[u] = reinterpret_cast<const ulonglong2*>(d.range)[(u64)m * d.n_comms + c];      // the last one again where there are no more
-        if (i0 + u + 1 < d.nb) m = m + 1 == d.n_meta ? 0 : m + 1;
-      }
-#pragma unroll
-      for (u32 u = 0; u < AHEAD; ++u) { mx[k] = r[u].x > mx[k] ? r[u].x : mx[k]; inv[k] = r[u].y > inv[k] ? r[u].y : inv[k]; }
+      for (u32 k = 0; k < PER; ++k) r[u][k] = row[std::min(k * 1024 + tid, d.n_comms - 1)];
+      m = i0 + u + 1 < d.nb ? (m + 1 == d.n_meta ? 0 : m + 1) : m;
     }
-    if (c0 + k >= d.n_comms) { mx[k] = 0; inv[k] = 0; }
+#pragma unroll
+    for (u32 u = 0; u < AHEAD; ++u)
+#pragma unroll
+      for (u32 k = 0; k < PER; ++k) { mx[k] = r[u][k].x > mx[k] ? r[u][k].x : mx[k]; inv[k] = r[u][k].y > inv[k] ? r[u][k].y : inv[k]; }
   }
+#pragma unroll
+  for (u32 k = 0; k < PER; ++k)
+    if (k * 1024 + tid >= d.n_comms) { mx[k] = 0; inv[k] = 0; }
   __syncthreads();
   if (m_status) atomicOr(&s_status, (unsigned long long)m_status);
   if (m_n) atomicMin(&s_any, tid);
@@ -78,45 +81,51 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     if (b.status) atomicOr(&s_status, (unsigned long long)b.status);
     if (b.n) atomicMin(&s_any, i);
   }
-  u32 rounds[PER], nfb_sum = 0, rounds_sum = 0;
-  u64 cells_sum = 0;
+  // the sum of the cells can pass 32 bits, so it is taken in halves (where it does, the layout is refused, and where it
+  // does not, the sums of buckets and rounds do not either)
+  u32 rounds[PER];
+  uint4 before[PER];                    // fine buckets, rounds, cells (low and high half) before the communicator
+  const u32 lane = lane_id(), wave = tid / CCLD_WAVE;
+  auto sums = [](const uint4& v) { return make_uint4(wave_inclusive_sum(v.x), wave_inclusive_sum(v.y), wave_inclusive_sum(v.z), wave_inclusive_sum(v.w)); };
+  auto less = [](const uint4& a, const uint4& b) { return make_uint4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); };
+  auto from = [](const uint4& v, u32 l) { return make_uint4(__shfl(v.x, l, CCLD_WAVE), __shfl(v.y, l, CCLD_WAVE), __shfl(v.z, l, CCLD_WAVE), __shfl(v.w, l, CCLD_WAVE)); };
 #pragma unroll
   for (u32 k = 0; k < PER; ++k) {
     rounds[k] = 0;
-    if (!(mx[k] | inv[k])) continue;
-    const u64 r = mx[k] - ~inv[k] + 1;                 // largest >= smallest; r == 0 only for the full 64-bit range
-    if (r == 0 || r > 0x7FFFFFFFull || r * size[k] > (u64)d.cell_cap) { bad = true; continue; }
-    rounds[k] = (u32)r;
-    const u32 rpb = GRID_B / size[k];                  // size <= GRID_B: the host checked
-    nfb_sum += (rounds[k] + rpb - 1) / rpb; rounds_sum += rounds[k]; cells_sum += (u64)rounds[k] * size[k];
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (mx[k] | inv[k]) {
+      const u64 r = mx[k] - ~inv[k] + 1;                 // largest >= smallest; r == 0 only for the full 64-bit range
+      if (r == 0 || r > 0x7FFFFFFFull || r * size[k] > (u64)d.cell_cap) {
+        bad = true;
+      } else {
+        rounds[k] = (u32)r;
+        const u32 rpb = GRID_B / size[k];                // size <= GRID_B: the host checked
+        const u64 cells = r * size[k];
+        v = make_uint4((rounds[k] + rpb - 1) / rpb, rounds[k], (u32)cells & 0xFFFFu, (u32)(cells >> 16));
+      }
+    }
+    const uint4 inc = sums(v);
+    if (lane == CCLD_WAVE - 1) s_sums[k * WAVES + wave] = inc;
+    before[k] = less(inc, v);
   }
-  // the sum of the cells can pass 32 bits, so it is taken in halves (where it does, the layout is refused, and where it
-  // does not, the sums of buckets and rounds do not either)
-  const u32 fb_inc = wave_inclusive_sum(nfb_sum), seg_inc = wave_inclusive_sum(rounds_sum);
-  const u32 cl = (u32)cells_sum & 0xFFFFu, ch = (u32)(cells_sum >> 16), cl_inc = wave_inclusive_sum(cl), ch_inc = wave_inclusive_sum(ch);
-  if (lane_id() == CCLD_WAVE - 1) s_wave4[tid / CCLD_WAVE] = make_uint4(fb_inc, seg_inc, cl_inc, ch_inc);
   __syncthreads();
-  u32 fb_total = 0, seg_total = 0, tl = 0, th = 0, fb = fb_inc - nfb_sum, seg = seg_inc - rounds_sum, el = cl_inc - cl, eh = ch_inc - ch;
-#pragma unroll
-  for (u32 w = 0; w < 1024 / CCLD_WAVE; ++w) {
-    const uint4 v = s_wave4[w];
-    if (w < tid / CCLD_WAVE) { fb += v.x; seg += v.y; el += v.z; eh += v.w; }
-    fb_total += v.x; seg_total += v.y; tl += v.z; th += v.w;
-  }
+  const uint4 part = lane < PER * WAVES ? s_sums[lane] : make_uint4(0, 0, 0, 0), upto = sums(part), total = from(upto, CCLD_WAVE - 1);
+  const uint4 ahead = less(upto, part);
   // one time serves the whole window, that of its first batch with records, unless its batches lie too far apart
   const u32 any = s_any;
   if (tid == (any < 1024 ? any : 0u)) s_ref = any < 1024 ? m_ref : meta_of(any < d.nb ? any : 0).ref;
-  u64 cell = (u64)el + ((u64)eh << 16);
-  const u64 cell_total = (u64)tl + ((u64)th << 16);
+  const u64 cell_total = (u64)total.z + ((u64)total.w << 16);
+  const u32 fb_total = total.x, seg_total = total.y;
 #pragma unroll
   for (u32 k = 0; k < PER; ++k) {
-    if (k >= per || c0 + k >= d.n_comms) continue;
-    const u32 rpb = GRID_B / size[k];
+    const uint4 w = from(ahead, k * WAVES + wave);
+    const u32 c = k * 1024 + tid;
+    if (c >= d.n_comms) continue;
     CommLayout L;
-    L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.fb_base = fb; L.rpb = rpb; L.rounds = rounds[k]; L.seg_base = seg;
-    L.cell_base = (u32)cell; L.size = size[k];
-    d.lay[c0 + k] = L;
-    fb += (rounds[k] + rpb - 1) / rpb; seg += rounds[k]; cell += (u64)rounds[k] * size[k];
+    L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.rpb = GRID_B / size[k]; L.rounds = rounds[k]; L.size = size[k];
+    L.fb_base = w.x + before[k].x; L.seg_base = w.y + before[k].y;
+    L.cell_base = (u32)((u64)w.z + before[k].z + ((u64)(w.w + before[k].w) << 16));
+    d.lay[c] = L;
   }
   // more rounds than records means a round without any record: the sort handles such windows
   if (cell_total > d.cell_cap || fb_total > d.fine_cap || seg_total > d.n) bad = true;        // uniform
@@ -182,7 +191,12 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
 }
 
 void launch_grid_layout(hipStream_t st, const GridArgs& d) {
-  hipLaunchKernelGGL(k_grid_layout, dim3(1), dim3(1024), 0, st, d);
+  // One communicator per thread where there are no more than threads, and no loads ahead of a single batch: with the general form
+  // a window of one batch takes 7.8 us in place of 6.7, ten batches of a small job 8.6 in place of 5.7.
+  constexpr u32 MANY = (GRID_MAX_COMMS + 1023) / 1024;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, st, d); };
+  if (d.n_comms <= 1024) { if (d.nb > 1) go(k_grid_layout<1, 5>); else go(k_grid_layout<1, 1>); }
+  else { if (d.nb > 1) go(k_grid_layout<MANY, 5>); else go(k_grid_layout<MANY, 1>); }
 }
 
 // ---- partition --------------------------------------------------------------------------------------

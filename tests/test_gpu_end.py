@@ -167,3 +167,29 @@ def test_windows_around_the_rules_of_the_statistics(n_comms):
         cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": seq.astype(np.uint64), "op": np.ones(comm.size, np.uint8),
                 "bytes": np.full(comm.size, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**7}
         run_both(topo, {k: v[p] for k, v in cols.items()}, what=(n_comms, rounds))
+
+
+@pytest.mark.parametrize("batches", [2, 5, 6, 11])
+@pytest.mark.parametrize("n_comms", [1000, 1024, 1025, 2049, 3000])
+def test_layout_of_several_batches(n_comms, batches):
+    """counter ranges of more or fewer communicators than threads, of batches around the number that is loaded at a time; one is empty"""
+    from paper_2605_04478_amd import ccld
+    topo = tg.make_topology(1024, [[c % 1000, c % 1000 + 1 + c // 1000] for c in range(n_comms)])
+    rng = np.random.default_rng(n_comms + batches)
+    comm = np.tile(np.repeat(np.arange(n_comms), 2), 4)
+    rank = np.tile(np.concatenate([topo.members_of(c) for c in range(n_comms)]), 4)
+    seq = np.repeat(np.arange(4), 2 * n_comms) + 3 * comm
+    te = T0 + (seq - 3 * comm) * 10**9 + rng.integers(0, 1000, comm.size)
+    te[rng.random(comm.size) < 0.02] += 10**7
+    p = rng.permutation(comm.size)
+    cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": seq.astype(np.uint64), "op": np.ones(comm.size, np.uint8),
+            "bytes": np.full(comm.size, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**7}
+    cols = {k: v[p] for k, v in cols.items()}
+    cuts = np.sort(rng.integers(0, comm.size, batches - 2))
+    cuts = np.concatenate([[0], cuts, cuts[-1:] if cuts.size else [0], [comm.size]])          # an empty batch before the last
+    an = ccld.Analyzer(topo, max_window_records=comm.size, window_batches=batches)
+    for lo, hi in zip(cuts[:-1], cuts[1:]):
+        an.ingest(an.to_device({k: v[lo:hi] for k, v in cols.items()}))
+    g = an.analyze_window(FAR, n_records=comm.size, per_record=True)
+    compare(g, orc.Oracle(topo).analyze_window(cols, FAR), *an.rank_blame(), what=(n_comms, batches))
+    an.close()
