@@ -103,9 +103,12 @@ __device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
 // search over a communicator's rounds makes two per step), so the lanes of a flag search its rank's communicators side by side,
 // SEARCH_LANES to a communicator: one looks at the middle and two at the middles of both halves, which is two steps of
 // the same search at a time.  The flag list is searched in PARENT_LANES + 1 parts at a time.
-constexpr u32 PARENT_LANES = 16, SEARCH_LANES = 4;
+// Up to PARENT_FEW flags 16 lanes take a flag and four a communicator; more flags, whose searches hide each other's loads, have
+// four lanes, each with a communicator of its own (us with 16 and with 4 lanes: 7,900 flags 16.5 and 20.5, 16,400 19.7 and
+// 21.4, 32,800 35.9 and 25.2, 145,000 110 and 41).
+constexpr u32 PARENT_FEW = 1u << 14;
 struct ChainBefore { i64 exit, enter; u32 comm, row; bool have; };
-template <bool GRID>
+template <bool GRID, u32 PARENT_LANES, u32 SEARCH_LANES>
 __device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
   const u32 group0 = lane_id() & ~(PARENT_LANES - 1);
   const ChainFlag F = chain_flag<GRID>(a, k);
@@ -136,7 +139,7 @@ __device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
         u32 probe = at, pos = 0;
         i64 te = 0, tx = 0;
         bool here = false;
-        if (sub < 3 && from < to)
+        if (SEARCH_LANES == 1 || (sub < 3 && from < to))
           while (true) {
             here = chain_record_of<GRID>(a, c2, probe, slot2, size2, &pos, &te, &tx);
             if (here || probe == from) break;
@@ -155,7 +158,7 @@ __device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
         };
         const u32 lo0 = lo;
         step(0);
-        if (lo < hi && (lo != lo0 || hi == mid)) step(lo != lo0 ? 2u : 1u);      // the half that a lane has looked at
+        if (SEARCH_LANES > 1 && lo < hi && (lo != lo0 || hi == mid)) step(lo != lo0 ? 2u : 1u);      // the half that a lane has looked at
       }
       take(f);
     }
@@ -211,12 +214,20 @@ __device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
   }
 }
 constexpr u32 PARENT_BLOCKS = 1u << 20;
-template <bool GRID>
+template <bool GRID, u32 PARENT_LANES, u32 SEARCH_LANES>
 __global__ __launch_bounds__(256) void k_chain_parent(ChainArgs a) {
   const u32 t = blockIdx.x * 256 + threadIdx.x, threads = gridDim.x * 256;
   if (a.per_rank)
     for (u64 i = t; i < (u64)CCLD_CHR_NCOL * a.T.n_ranks; i += threads) a.per_rank[i] = 0;
-  for (u64 k = t / PARENT_LANES; k < a.n_flag; k += threads / PARENT_LANES) chain_parent<GRID>(a, (u32)k, t % PARENT_LANES);
+  for (u64 k = t / PARENT_LANES; k < a.n_flag; k += threads / PARENT_LANES) chain_parent<GRID, PARENT_LANES, SEARCH_LANES>(a, (u32)k, t % PARENT_LANES);
+}
+template <bool GRID>
+static void launch_parents(hipStream_t st, const ChainArgs& a) {
+  auto go = [&](auto kernel, uint32_t lanes) {
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)std::min<uint64_t>(((uint64_t)a.n_flag * lanes + 255) / 256, PARENT_BLOCKS)), dim3(256), 0, st, a);
+  };
+  if (a.n_flag <= PARENT_FEW) go(k_chain_parent<GRID, 16, 4>, 16);
+  else go(k_chain_parent<GRID, 4, 1>, 4);
 }
 
 // Links that lead round in a loop: jumps in step, 2^i links after the i-th, from one pair of arrays into the other.
@@ -336,15 +347,15 @@ extern "C" ccld_status ccld_flag_chains(ccld_ctx* c, const ccld_window_result* w
     a.comm_first = c->chain_first; a.parent = c->chain_parent;
     a.link = reinterpret_cast<uint64_t*>(c->range_c);                // scratch that the analysis no longer needs
     a.per_rank = o->per_rank;
-    const dim3 blocks((n_flag + 255) / 256), parents((uint32_t)std::min<uint64_t>(((uint64_t)n_flag * PARENT_LANES + 255) / 256, PARENT_BLOCKS));
+    const dim3 blocks((n_flag + 255) / 256);
     a.arrivals = c->arrivals; a.counters = c->counters;                      // CNT_CHAIN_LOOP: cleared by the analysis; its flags lead round or they do not
     take_ticket(c);
     if (grid) {
-      hipLaunchKernelGGL(k_chain_parent<true>, parents, dim3(256), 0, st, a);
+      launch_parents<true>(st, a);
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<true, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
     } else {
       hipLaunchKernelGGL(k_chain_comm_rows, dim3((c->topo.n_comms + 256) / 256), dim3(256), 0, st, a);
-      hipLaunchKernelGGL(k_chain_parent<false>, parents, dim3(256), 0, st, a);
+      launch_parents<false>(st, a);
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_chain_emit<false, false>), blocks, dim3(256), 0, st, a, o->chain, o->chain_cap, c->h_pinned, c->ticket);
     }
     HIP_TRY(hipGetLastError());

@@ -176,3 +176,24 @@ def test_clocks_that_contradict_each_other(loop, tail, sort):
             for name in per:
                 assert np.array_equal(per_rank[name], per[name]), (name, again)
         an.close()
+
+
+@pytest.mark.parametrize("step", [1, 10**6], ids=["grid", "sorted"])
+@pytest.mark.parametrize("rounds,many", [(900, False), (2300, True)])
+def test_few_and_many_flags(rounds, many, step):
+    """flags on both sides of the number from which fewer lanes search for a parent; ranks miss rounds and end in flight"""
+    R = 64
+    topo = tg.make_topology(R, [list(range(i, i + 8)) for i in range(0, R, 8)] + [list(range(i, R, 8)) for i in range(8)])
+    rng = np.random.default_rng(rounds)
+    q, half, rank = (x.reshape(-1) for x in np.meshgrid(np.arange(rounds), np.arange(2), np.arange(R), indexing="ij"))
+    comm = np.where(half == 0, rank // 8, 8 + rank % 8)
+    te = T0 + (2 * q + half) * 10 * MS + rng.integers(0, 1000, q.size)
+    te[rng.random(q.size) < 0.1] += 3 * MS
+    tx = T0 + (2 * q + half) * 10 * MS + 6 * MS + rng.integers(0, 1000, q.size)
+    tx[(q == rounds - 1) & (half == 1) & (rng.random(q.size) < 0.3)] = INFLIGHT         # a rank's last operation
+    keep = rng.random(q.size) < 0.99
+    p = rng.permutation(np.flatnonzero(keep))
+    cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": (1 + q * step).astype(np.uint64), "op": np.ones(q.size, np.uint8),
+            "bytes": np.full(q.size, 64, np.uint64), "t_enter": te, "t_exit": tx}
+    chain, per_rank = run_both(topo, {k: v[p] for k, v in cols.items()}, int(T0 + rounds * 30 * MS), what=(rounds, step), hang_threshold_ns=10**15)
+    assert (len(chain["parent"]) > 1 << 14) == many and (chain["parent"] >= 0).any()
