@@ -41,8 +41,8 @@ def kernel_sources_digest() -> str:
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2605_04478_amd", "csrc")
-    for name in ("device_utils.h", "radix_sort.h", "radix_sort.hip", "select.h", "segments.hip", "groups.hip", "window.hip",
-                 "window_kernels.h", "rows.h", "grid.h", "grid.hip"):
+    for name in ("device_utils.h", "radix_sort.h", "radix_sort.hip", "select.h", "segments.hip", "groups.hip", "window.hip", "alerts.h",
+                 "blame_order.h", "report.h", "window_kernels.h", "rows.h", "grid.h", "grid.hip"):
         h.update(name.encode())
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()
