@@ -280,7 +280,12 @@ static_assert(GROUP_SLOTS == 1024 && GROUP_SLOTS % GC_THREADS == 0, "ten bits of
 // its bucket by the flags before it and writes it to its place in the list and in the flag table: a few buckets hold most of the
 // flags (those of a slow rank's communicators), so a workgroup or a wavefront per bucket would wait for those.  The flags before
 // every bucket are scanned by each workgroup in LDS, or were scanned before (many buckets).
+// Where every eighth rank is late the list is long, and what takes the time is dependent loads: a wavefront looks for its 64 flags'
+// buckets at once (16 loads one after the other per flag before), and the workgroups grow with the buckets, one to 16 of them
+// (64 of them, 256 where scanned, before; the whole launch, us: 82M records with 7.6M flags 591 -> 266, 20M with 1.9M 129 -> 87,
+// 4M with 377,000 67 -> 31; with 132,000 flags in 82M records 73 both ways; twice as many workgroups: 258, 85, 29, 78).
 constexpr u32 END_SCAN_FINE = 4096;
+constexpr u32 END_FLAG_SHARE = 16, END_FLAG_BLOCKS = 1024, END_FLAG_SCANNED = 256;       // fine buckets per workgroup; at most; at least where scanned
 struct FlagShared { u32 pre[END_SCAN_FINE + 1], wave[GC_THREADS / CCLD_WAVE]; };
 __device__ __forceinline__ void list_flags(const EndArgs& e, const GridArgs& d, const FlagArgs& a, FlagShared& S, u32 block, u32 blocks) {
   const u32 n_fine = d.hdr->n_fine, tid = threadIdx.x;
@@ -298,12 +303,33 @@ __device__ __forceinline__ void list_flags(const EndArgs& e, const GridArgs& d, 
     if (block == 0 && tid == 0) e.counters[CNT_NFLAG] = total;
     __syncthreads();
   }
-  for (u32 k = block * GC_THREADS + tid; k < total; k += blocks * GC_THREADS) {
-    u32 lo = 0, hi = n_fine, first = 0;          // the bucket that holds flag k: the last one that starts at or before it
-    while (hi - lo > 1) {
-      const u32 m = (lo + hi) >> 1, v = e.flags_scanned ? d.nflag[m] : S.pre[m];
-      if (v <= k) { lo = m; first = v; } else hi = m;
+  const u32 lane = lane_id();
+  const auto before = [&](u32 f) -> u32 { return e.flags_scanned ? d.nflag[f] : S.pre[f]; };       // flags before fine bucket f
+  for (u32 k0 = block * GC_THREADS + (tid - lane); k0 < total; k0 += blocks * GC_THREADS) {        // 64 flags in a row per wavefront
+    // the bucket of the first of them, the last one that starts at or before it: 64 probes at a time
+    u32 lo = 0;
+    for (u32 hi = n_fine;;) {
+      const u32 step = (hi - lo + CCLD_WAVE - 1) / CCLD_WAVE, probe = lo + lane * step;
+      lo += ((u32)__popcll(ballot64(probe < hi && before(probe) <= k0)) - 1) * step;
+      if (step == 1) break;
+      hi = hi - lo < step ? hi : lo + step;
     }
+    // the bucket of the lane's own: as a rule among the next 64
+    const u32 k = k0 + lane, next = lo + 1 + lane < n_fine ? before(lo + 1 + lane) : ~0u;
+    u32 past = 0, first = before(lo);
+#pragma unroll
+    for (u32 m = CCLD_WAVE / 2; m; m >>= 1)
+      if (lane_read(next, past + m - 1) <= k) past += m;
+    if (lane_read(next, past) <= k) ++past;
+    const u32 start = lane_read(next, past ? past - 1 : 0u);
+    if (past) first = start;
+    if (k >= total) continue;
+    lo += past;
+    if (past == CCLD_WAVE)
+      for (u32 hi = n_fine; hi - lo > 1;) {
+        const u32 m = (lo + hi) >> 1, v = before(m);
+        if (v <= k) { lo = m; first = v; } else hi = m;
+      }
     const FineDesc D = d.desc[lo];
     const u32 at = d.rec0[lo] + (k - first);
     const u32 w = a.flag_stage[at], cell = w & 0xFFFFu, kind = w >> 16, round = cell / D.size, slot = cell - round * D.size;
@@ -512,7 +538,7 @@ bool launch_window_end(hipStream_t st, const EndArgs& a_in, const GridArgs* d, c
   const bool report = a.n_ranks <= END_ORDER_RANKS;
   if (!report) a.host = nullptr;
   a.flags_scanned = fine_bound > END_SCAN_FINE;                                     // the bound is the exact number there
-  const u32 n_flags = d ? (a.flags_scanned ? 256u : std::min<u32>((fine_bound + 63) / 64, 64)) : 0u;
+  const u32 n_flags = !d ? 0u : std::min(std::max((fine_bound + END_FLAG_SHARE - 1) / END_FLAG_SHARE, a.flags_scanned ? END_FLAG_SCANNED : 0u), END_FLAG_BLOCKS);
   if (d && a.flags_scanned) launch_scan_tiles(st, d->nflag, fine_bound, &a.counters[CNT_NFLAG]);
   const u32 n_order = report ? std::min<u32>((a.n_ranks + 63) / 64, 64) : 0u, n_alerts = al ? 1u : 0u;
   const u32 blocks = a.n_comms + n_flags + n_order + n_alerts;

@@ -74,6 +74,31 @@ def test_flags_at_the_edges_of_tiles(buckets):
     assert g.n_flag >= 4 * buckets
 
 
+@pytest.mark.parametrize("first,pairs,last", [(1, 0, 1), (63, 1, 2), (65, 0, 70), (130, 300, 66), (398, 3300, 398), (398, 3300, 399), (500, 3400, 333)])
+def test_flags_far_apart_and_close_together(first, pairs, last):
+    """the fine buckets of two rings of 1,025 members (a round each) around those of pairs, which have no flag: runs of 64 flags within a
+    bucket, in as many buckets and over thousands of them, and numbers of buckets on both sides of what a workgroup scans"""
+    n = 1025
+    topo = tg.make_topology(n, [list(range(n))] + [[c % 1000, c % 1000 + 1 + c // 1000] for c in range(pairs)] + [list(range(n))[::-1]])
+    rng = np.random.default_rng(first + last)
+    rows = [(np.zeros(first * n, np.int64), np.repeat(np.arange(first), n), np.tile(np.arange(n), first)),
+            (np.repeat(np.arange(1, pairs + 1), 2), np.zeros(2 * pairs, np.int64), np.concatenate([topo.members_of(1 + c) for c in range(pairs)] + [np.zeros(0, np.int64)])),
+            (np.full(last * n, pairs + 1), np.repeat(np.arange(last), n), np.tile(np.arange(n), last))]
+    comm, seq, rank = (np.concatenate(x) for x in zip(*rows))
+    te = T0 + seq * 10**9 + rng.integers(0, 1000, comm.size)
+    late = np.zeros(comm.size, bool)
+    late[rng.integers(0, n, min(first, 70)) + np.arange(min(first, 70)) * n] = True                     # one flag a bucket
+    late[(comm == 0) & (seq == first - 1) & (rank % 7 == 3)] = True                                     # 146 in one
+    late[(comm == pairs + 1) & (seq == 0) & (rank % 16 == 1)] = True                                    # 64
+    late[(comm == pairs + 1) & (seq == last - 1) & (rank % 3 == 0)] = True                              # 342, in the last bucket
+    te[late] += 10**7
+    p = rng.permutation(comm.size)
+    cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": seq.astype(np.uint64), "op": np.ones(comm.size, np.uint8),
+            "bytes": np.full(comm.size, 64, np.uint64), "t_enter": te, "t_exit": T0 + seq * 10**9 + 5 * 10**7 + rng.integers(0, 1000, comm.size)}
+    g, o = run_both(topo, {k: v[p] for k, v in cols.items()}, what=(first, pairs, last))
+    assert g.n_flag == int(late.sum())
+
+
 @pytest.mark.parametrize("n_ranks", [511, 512, 2048, 2049, 16384, 16385])
 def test_blame_order_of_many_ranks(n_ranks):
     topo = tg.make_topology(n_ranks, [list(range(i, min(i + 8, n_ranks))) for i in range(0, n_ranks, 8)])
