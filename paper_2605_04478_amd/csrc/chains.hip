@@ -105,7 +105,10 @@ __device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
 // the same search at a time.  The flag list is searched in PARENT_LANES + 1 parts at a time.
 // Up to PARENT_FEW flags 16 lanes take a flag and four a communicator; more flags, whose searches hide each other's loads, have
 // four lanes, each with a communicator of its own (us with 16 and with 4 lanes: 7,900 flags 16.5 and 20.5, 16,400 19.7 and
-// 21.4, 32,800 35.9 and 25.2, 145,000 110 and 41).
+// 21.4, 32,800 35.9 and 25.2, 145,000 110 and 41; the whole call on sorted windows, where the lanes also share the walk over a
+// collective's records: 9,800 flags 53 and 56, 12,600 59 and 63, 48,800 81 and 67, 377,000 392 and 208; beside a world communicator
+// of 4,096 members 1,300 flags 89 and 178, 12,500 110 and 189, 48,700 194 and 223, 717,000 2,779 and 2,075.  With the walk in
+// every lane those were 560 to 4,630 us).
 constexpr u32 PARENT_FEW = 1u << 14;
 struct ChainBefore { i64 exit, enter; u32 comm, row; bool have; };
 template <bool GRID, u32 PARENT_LANES, u32 SEARCH_LANES>
@@ -194,12 +197,19 @@ __device__ __forceinline__ void chain_parent(const ChainArgs& a, u32 k, u32 l) {
         }
       } else {
         const u32 first = (u32)a.seg[(u64)CCLD_SEG_FIRST * a.seg_cap + B.row], n = (u32)a.seg[(u64)CCLD_SEG_N * a.seg_cap + B.row];
-        u32 m_pos = 0;
-        for (u32 p = first; p < first + n; ++p)
+        u32 m_pos = 0;                           // the lanes share its records, the widest collective's 4,096 and more
+        for (u32 p = first + l; p < first + n; p += PARENT_LANES)
           if (a.rec_flag[p] & CCLD_FLAG_LATE_ENTER) {
             const i64 lag = a.flag_lag[p];
             if (!any || lag > m_lag) { any = true; m_pos = p; m_lag = lag; }
           }
+#pragma unroll
+        for (u32 m = 1; m < PARENT_LANES; m <<= 1) {
+          const bool o_any = __shfl_xor((int)any, m, CCLD_WAVE) != 0;
+          const i64 o_lag = (i64)shfl_xor_u64((u64)m_lag, m);
+          const u32 o_pos = __shfl_xor(m_pos, m, CCLD_WAVE);
+          if (o_any && (!any || o_lag > m_lag || (o_lag == m_lag && o_pos < m_pos))) { any = true; m_lag = o_lag; m_pos = o_pos; }
+        }
         if (any) {
           u32 lo = 0, hi = a.n_flag;
           while (lo < hi) { const u32 m = (lo + hi) >> 1; if (a.flag_pos[m] < m_pos) lo = m + 1; else hi = m; }

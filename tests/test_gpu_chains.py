@@ -197,3 +197,20 @@ def test_few_and_many_flags(rounds, many, step):
             "bytes": np.full(q.size, 64, np.uint64), "t_enter": te, "t_exit": tx}
     chain, per_rank = run_both(topo, {k: v[p] for k, v in cols.items()}, int(T0 + rounds * 30 * MS), what=(rounds, step), hang_threshold_ns=10**15)
     assert (len(chain["parent"]) > 1 << 14) == many and (chain["parent"] >= 0).any()
+
+
+@pytest.mark.parametrize("n,rounds,share", [(3, 30, 0.3), (16, 20, 0.2), (17, 20, 0.2), (63, 20, 0.1), (70, 20, 0.1), (1000, 12, 0.02), (4100, 8, 0.01),
+                                            (4100, 45, 0.12)])
+@pytest.mark.parametrize("step", [1, 10**6], ids=["grid", "sorted"])
+def test_parents_among_many_late_members(n, rounds, share, step):
+    """late members anywhere in collectives of fewer and of more members than lanes look for the parent, many with the same lag (the
+    smallest rank is the parent); the last one is past the number of flags from which fewer lanes look"""
+    topo = tg.make_topology(n, [list(range(n))])
+    rng = np.random.default_rng(n + rounds)
+    q, rank = np.repeat(np.arange(rounds), n), np.tile(np.arange(n), rounds)
+    te = T0 + q * 10 * MS + np.where(rng.random(q.size) < share, rng.integers(2, 4, q.size) * MS, 0)
+    p = rng.permutation(q.size)
+    cols = {"rank": rank.astype(np.uint32), "comm": np.zeros(q.size, np.uint32), "seq": (1 + q * step).astype(np.uint64), "op": np.ones(q.size, np.uint8),
+            "bytes": np.full(q.size, 64, np.uint64), "t_enter": te, "t_exit": T0 + q * 10 * MS + 6 * MS}
+    chain, _ = run_both(topo, {k: v[p] for k, v in cols.items()}, int(T0 + rounds * 30 * MS), what=(n, step))
+    assert (len(chain["parent"]) > 1 << 14) == (rounds == 45) and (chain["parent"] >= 0).any()
