@@ -1,15 +1,14 @@
 // extern "C" entry points: context set-up, workspace carving, ingest, window analysis, blame.
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cstring>
 #include <new>
-#include <thread>
 
 #include "ccld_internal.h"
 #include "device_utils.h"
 #include "window_kernels.h"
 #include "grid.h"
+#include "host_copy.h"
 #include "merge.h"
 
 using namespace ccld;
@@ -23,6 +22,8 @@ static_assert(CNT_COUNT <= PINNED_FINE, "the counters come first");
 static int bits_for_host(uint64_t v) { int b = 0; while (v) { ++b; v >>= 1; } return b; }
 
 namespace {
+
+CopyStreams g_copy_streams;
 
 // Bump allocator over the caller's workspace; with base == nullptr it only measures.
 struct Carver {
@@ -307,8 +308,8 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   const int mb = c->kf.mb, cb = c->kf.cb;
   if (mb + cb > 63) { delete c; return CCLD_E_KEY_WIDTH; }
   c->stream = (hipStream_t)hip_stream;
-  c->copy_stream[0] = c->copy_stream[1] = nullptr;
-  if (hipGetDevice(&c->device) != hipSuccess) { (void)hipGetLastError(); delete c; return CCLD_E_HIP; }
+  c->copy_earned = 0;
+  if (hipGetDevice(&c->device) != hipSuccess || c->device >= COPY_DEVICES) { (void)hipGetLastError(); delete c; return CCLD_E_HIP; }
   c->chain_ready = false;
   c->rank_bits = bits_for_host(topo->n_ranks - 1);
   c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0; c->total_ingested = 0;
@@ -416,6 +417,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
     delete c;
     return rs;
   }
+  g_copy_streams.join(c->device);
   *out = c;
   return CCLD_OK;
 }
@@ -423,7 +425,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
 ccld_status ccld_destroy(ccld_ctx* c) {
   if (!c) return CCLD_E_NULL;
   (void)hipStreamSynchronize(c->stream);
-  for (hipStream_t s : c->copy_stream) if (s) (void)hipStreamDestroy(s);
+  g_copy_streams.leave(c->device);
   if (c->h_pinned) (void)hipHostFree(c->h_pinned);
   c->prof.destroy();
   delete c;
@@ -436,52 +438,6 @@ ccld_status ccld_reset_window(ccld_ctx* c) {
   c->inc_ok = false;
   c->chain_ready = false;
   return CCLD_OK;
-}
-
-// The columns of a host batch, on the way to the staging area in the order of the context's stream.  Ordinary memory is made known
-// to the device, copied and forgotten again by the runtime, column by column, and the calling thread waits for each; two more
-// threads with a stream each keep the link busy meanwhile: a window of 1,024,000 records (42 MB) 1,624 -> 1,146 us (42 MB
-// from pinned memory alone: 795).  The gain is 14% at 16 MB and nothing below 12; the line lies where a first batch, for which the streams are
-// made, does not lose either (a new context, 41 MB: 1,731 -> 1,436 us; 25 MB: 917 -> 2,300).  A process whose first streams they
-// are waits 7 ms for them, once.
-constexpr uint64_t COPY_ALONE_BYTES = 32ull << 20;
-struct HostCopy { void* dst; const void* src; uint64_t bytes; };
-static hipError_t copy_from_host(ccld_ctx* c, const HostCopy* copies, int n) {
-  uint64_t bytes = 0;
-  for (int i = 0; i < n; ++i) bytes += copies[i].bytes;
-  std::atomic<int> next{0};
-  auto take = [&](hipStream_t st) -> hipError_t {
-    hipError_t e = hipSuccess;
-    for (int i; e == hipSuccess && (i = next.fetch_add(1)) < n;)
-      e = hipMemcpyAsync(copies[i].dst, copies[i].src, copies[i].bytes, hipMemcpyHostToDevice, st);
-    return e;
-  };
-  if (bytes < COPY_ALONE_BYTES) return take(c->stream);
-  hipError_t e = hipStreamSynchronize(c->stream);          // what still uses the staging area
-  if (e != hipSuccess) return e;
-  hipError_t helped[2] = {hipSuccess, hipSuccess};
-  std::thread helper[2];                                   // what none of them takes, the calling thread copies
-  for (int t = 0; t < 2; ++t) {
-    if (!c->copy_stream[t] && hipStreamCreateWithFlags(&c->copy_stream[t], hipStreamNonBlocking) != hipSuccess) {
-      (void)hipGetLastError();
-      c->copy_stream[t] = nullptr;
-      break;
-    }
-    try {
-      helper[t] = std::thread([&, t] {
-        if ((helped[t] = hipSetDevice(c->device)) != hipSuccess) return;
-        helped[t] = take(c->copy_stream[t]);
-        const hipError_t done = hipStreamSynchronize(c->copy_stream[t]);
-        if (helped[t] == hipSuccess) helped[t] = done;
-      });
-    } catch (...) {
-      break;
-    }
-  }
-  e = take(c->stream);
-  for (int t = 0; t < 2; ++t)
-    if (helper[t].joinable()) { helper[t].join(); if (e == hipSuccess) e = helped[t]; }
-  return e;
 }
 
 ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
@@ -513,7 +469,7 @@ ccld_status ccld_ingest(ccld_ctx* c, const ccld_records* b, uint64_t n) {
     uint8_t* d_op = (uint8_t*)(d_comm + n);
     const HostCopy copies[] = {{d_seq, b->seq, 8 * n}, {d_bytes, b->bytes, 8 * n}, {d_te, b->t_enter, 8 * n}, {d_tx, b->t_exit, 8 * n},
                                {d_rank, b->rank, 4 * n}, {d_comm, b->comm, 4 * n}, {d_op, b->op, n}};
-    HIP_TRY(copy_from_host(c, copies, 7));
+    HIP_TRY(copy_from_host(g_copy_streams, c->device, c->copy_earned, c->stream, copies, 7));
     a.rank = d_rank; a.comm = d_comm; a.seq = d_seq; a.op = d_op; a.bytes = d_bytes; a.t_enter = d_te; a.t_exit = d_tx;
   }
   a.n = n; a.win_key = c->win_key; a.win_row = c->win_row; a.win_wide = c->win_wide;

@@ -166,7 +166,7 @@ struct ccld_ctx {
   uint64_t* h_pinned;                 // pinned host staging
   uint64_t ticket;                    // of the latest report that the device was asked for
   int device;                         // the device that the context was created on
-  hipStream_t copy_stream[2];         // of the threads that help to copy host batches, made for the first large one
+  uint64_t copy_earned;               // bytes of large host batches that the caller has copied alone (host_copy.h)
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location and rates

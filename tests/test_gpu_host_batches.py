@@ -38,6 +38,18 @@ def _run(sizes, seed, out):
     an.close()
 
 
+@pytest.fixture(scope="module", autouse=True)
+def helping_threads():
+    """a context that has handed over so much that threads help with large batches, its own and those of the contexts below"""
+    an = ccld.Analyzer(tg.make_topology(256, TOPO), max_window_records=LINE + 4096)
+    cols = _cols(LINE + 1, 99)
+    for _ in range(34):
+        an.reset_window()
+        an.ingest(cols)
+    yield an, cols
+    an.close()
+
+
 def _check(out):
     o = orc.Oracle(tg.make_topology(256, TOPO))
     for cols, g, (blame, order) in out:
@@ -49,6 +61,14 @@ def test_batches_on_both_sides_of_the_line():
     _run([LINE + 1, 500, LINE, LINE + 4096], 1, out)
     assert len(out) == 4
     _check(out)
+
+
+def test_batches_before_and_after_the_threads_help(helping_threads):
+    an, cols = helping_threads
+    for _ in range(2):
+        an.reset_window()
+        an.ingest({k: v.copy() for k, v in cols.items()})
+        _check([(cols, an.analyze_window(FAR, n_records=LINE + 1), an.rank_blame())])
 
 
 def test_two_contexts_in_two_threads():
