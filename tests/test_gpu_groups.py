@@ -77,3 +77,20 @@ def test_baselines_that_end_at_the_edges_of_a_walk(tbase_rounds, warmup_rounds):
         windows.append(rows)
     ref = _windows(topo, windows, tbase_rounds=tbase_rounds, tbase_init_ns=300, tbase_warmup_ns=warmup_rounds * SPACING)
     assert len(ref.group["comm"]) == 2
+
+
+@pytest.mark.parametrize("rounds", [1, 511, 512, 513, 2047, 2048, 2049, 4095, 4096, 4097])
+def test_rows_at_the_edges_of_a_step(rounds):
+    """the slowest round of a group in the first, a middle or the last row of its communicator; equal ones, of which the first counts"""
+    topo = ring_topology(3, comms=[[0, 1], [1, 2, 0], [2, 1]])
+    rng = np.random.default_rng(rounds)
+    windows = []
+    for w, slow in enumerate(([0], [rounds // 2, rounds - 1], [rounds - 1])):
+        rows = []
+        for c in range(3):
+            for j in range(rounds):
+                t = T0 + (w * rounds + j) * 1_000_000
+                for r in topo.members_of(c):
+                    rows.append((int(r), c, w * rounds + j, j % 2, 64 << (j % 3), t, t + (5000 if j in slow and r == 1 else 100 + int(rng.integers(0, 900)))))
+        windows.append(rows)
+    _windows(topo, windows, tbase_init_ns=400, tbase_rounds=max(rounds // 4, 1))
