@@ -320,7 +320,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   carve_all(c, w, topo->n_ranks, topo->n_comms, n_members);
   c->topo.n_ranks = topo->n_ranks; c->topo.n_comms = topo->n_comms;
   c->h_pinned = nullptr;
-  c->ticket = 0; c->h_clear = false;
+  c->ticket = 0; c->h_clear = true;
 
   // derived host tables: sorted member lists, rank -> communicators CSR
   std::vector<uint32_t> sorted(topo->members, topo->members + n_members), sslot(n_members);
@@ -398,6 +398,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (hipMemsetAsync(c->batch_meta, 0, sizeof(BatchMeta) * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (c->comm_range && hipMemsetAsync(c->comm_range, 0, 16ull * topo->n_comms * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
+  if (hipMemsetAsync(c->h_counters, 0, sizeof(uint64_t) * (CNT_COUNT + HANG_REGIONS / 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->arrivals, 0, sizeof(uint32_t) * ARRIVAL_WORDS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
   c->f_status = c->f_frame + topo->n_ranks;

@@ -508,8 +508,9 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
   for (int m2 = 32; m2 >= 1; m2 >>= 1) status |= shfl_xor_u64(status, m2);
   if (lane_id() == 0 && status) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)status);
 }
-// What a pass over regrouped rows counts in starts at zero: the last workgroup of the pass before left it so (a launch less:
-// 4 us of 39 on a small job), or this launch does.
+// What a pass over regrouped rows counts in starts at zero: the context was made so, the last workgroup of the pass before left
+// it so, or this launch does (61,440 rows: 38.6 -> 36.4 us without it; a context's first pass 68 -> 65.5, of 2.4M rows of
+// rates 118.5 -> 112.5).
 __global__ __launch_bounds__(SPLIT_REGIONS) void k_hang_clear(HangArgs a) {
   if (threadIdx.x < CNT_COUNT) a.counters[threadIdx.x] = 0;
   if (threadIdx.x < (a.leave_clear ? SPLIT_REGIONS : a.n_regions)) a.part_fill[threadIdx.x] = 0;      // all: a later pass may have more

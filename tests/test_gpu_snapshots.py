@@ -45,6 +45,40 @@ def test_sizes_and_wide_counters(n, n_snap, n_ch, seq0):
     _both(topo, _random(topo, n_snap, n_ch, rng, seq0), n_snap, n_ch, (n, n_snap, n_ch, seq0))
 
 
+def test_contexts_whose_workspace_holds_anything():
+    """the first hang location and the first rates of a context, and those behind a pass that does not regroup"""
+    import torch
+
+    from oracle import ccld_oracle as orc
+    from paper_2605_04478_amd import ccld
+    n, n_snap, n_ch = 600, 9, 2
+    topo = ring_topology(n)
+    rng = np.random.default_rng(3)
+    new = lambda: ccld.Analyzer(topo, max_window_records=64, max_snapshot_rows=n * n_snap * n_ch, stall_snapshots=3)
+    small, wide = (_random(topo, n_snap, n_ch, rng, seq0) for seq0 in (50, 2**62))
+    want = [(orc.Oracle(topo, dict(stall_snapshots=3)).locate_hang(c, n_snap, n_ch), orc.Oracle(topo).progress_rates(c, n_snap, n_ch)) for c in (small, wide)]
+    an = new()
+    size = an.workspace.numel()
+    for first in ("hang", "rates", "wide"):
+        an.close()
+        del an
+        dirt = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda:0")
+        at = dirt.data_ptr()
+        torch.cuda.synchronize()
+        del dirt
+        an = new()
+        assert an.workspace.data_ptr() == at
+        for kind, k in ((first, 0),) if first != "wide" else (("hang", 1), ("hang", 0), ("rates", 1), ("rates", 0), ("rates", 1), ("hang", 0), ("hang", 1), ("rates", 0)):
+            rows = an.snapshots_to_device((small, wide)[k])
+            g = an.locate_hang(rows, n_snap, n_ch) if kind == "hang" else an.progress_rates(rows, n_snap, n_ch)
+            o = want[k][kind == "rates"]
+            assert g.status == o.status == "OK", (first, kind, k)
+            for name in ("root", "pair", "comm") if kind == "hang" else ("pair", "comm"):
+                ot, gt = getattr(o, name), getattr(g, name)
+                assert all(np.array_equal(gt[q], ot[q]) for q in ot), (first, kind, k, name)
+    an.close()
+
+
 @pytest.mark.parametrize("n,n_snap", [(40, 6), (600, 70)])
 def test_duplicates_gaps_and_extra_rows(n, n_snap):
     rng = np.random.default_rng(n)
