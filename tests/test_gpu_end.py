@@ -1,12 +1,13 @@
-"""GPU parity of the end of an analysis (groups, flags, blame order, alerts and report in one launch) where it can go wrong:
-alerts around the number that it lists itself, flags at the edges of its tiles of fine buckets, more ranks than it orders, and
-of the calls that report from their last kernel when they follow one another."""
+"""GPU parity of the end of an analysis (groups, flags, blame order and alerts side by side, then group table and report) where it
+can go wrong: alerts around the number and the communicators that it lists itself, flags around the fine buckets of a thread and of
+a workgroup, more ranks than it orders, and of the calls that report from their last kernel when they follow one another."""
 import numpy as np
 import pytest
 
 from oracle import ccld_oracle as orc
 from paper_2605_04478_amd import tracegen as tg
 from tests.helpers import INFLIGHT, T0, ring_topology, toy_cols
+from tests.test_gpu_frames import both
 from tests.test_gpu_window import FAR, compare, run_both
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +41,32 @@ def test_alerts_of_every_class(n_alert, step):
     assert g.n_alert == n_alert
 
 
+@pytest.mark.parametrize("step", [1, 10**6], ids=["grid", "sorted"])
+@pytest.mark.parametrize("n", [2048, 2049])
+@pytest.mark.parametrize("n_alert", [1, 8, 9])
+def test_alerts_of_large_communicators(n_alert, n, step):
+    """the most members whose candidates a wavefront marks, and one more, which is listed by the launches of longer lists"""
+    topo = tg.make_topology(n, [list(range(n))[::-1], [5, 3, 4]])
+    rng = np.random.default_rng(n_alert)
+    q, r = np.repeat(np.arange(10), n), np.tile(np.arange(n), 10)
+    te = T0 + q * 10**9 + rng.integers(0, 10**6, q.size)
+    tx, keep = te + 10**6, np.ones(q.size, bool)
+    for a in range(n_alert):               # not entered by the last and by some others, finished by some, hung in by all
+        on = q == a
+        some = on & ((r % 5 == 1) | (r == n - 1))
+        if a % 3 == 0:
+            keep &= ~some
+        tx[on & ~some if a % 3 == 1 else on] = INFLIGHT
+    more = np.arange(3, 6)
+    cols = {"rank": np.concatenate([r[keep], more]), "comm": np.concatenate([0 * r[keep], 0 * more + 1]), "seq": np.concatenate([q[keep] * step, 0 * more]),
+            "t_enter": np.concatenate([te[keep], T0 + more]), "t_exit": np.concatenate([tx[keep], T0 + 9 + more])}
+    cols = {**{k: v.astype(np.uint32 if k in ("rank", "comm") else np.uint64 if k == "seq" else np.int64) for k, v in cols.items()},
+            "op": np.ones(keep.sum() + 3, np.uint8), "bytes": np.full(keep.sum() + 3, 64, np.uint64)}
+    p = rng.permutation(keep.sum() + 3)
+    g, o = run_both(topo, {k: v[p] for k, v in cols.items()}, hang_threshold_ns=10**9, what=(n_alert, n, step))
+    assert g.n_alert == n_alert and g.n_cand > n // 5
+
+
 def test_truncated_alert_tables():
     from paper_2605_04478_amd import ccld
     topo = ring_topology(6)
@@ -57,9 +84,10 @@ def test_truncated_alert_tables():
         an.close()
 
 
-@pytest.mark.parametrize("buckets", [1, 127, 128, 129, 256, 257])
-def test_flags_at_the_edges_of_tiles(buckets):
-    """one communicator of 1,024 members (two rounds in a fine bucket), flags in every bucket"""
+@pytest.mark.parametrize("buckets", [1, 8, 9, 16, 17, 63, 64, 65, 128, 129, 257])
+def test_flags_in_every_bucket(buckets):
+    """one communicator of 1,024 members (two rounds in a fine bucket); eight buckets to a thread of the scan, sixteen to a workgroup
+    of the list, 64 probed at a time"""
     n = 1024
     topo = ring_topology(n)
     rng = np.random.default_rng(buckets)
@@ -125,6 +153,10 @@ def test_calls_that_report_from_their_last_kernel_in_turn():
     bad = {k: np.concatenate([v[:-1], v[:1]]) for k, v in snaps.items()}
     frames = np.zeros(topo.n_ranks, dtype=tg.FRAME_DTYPE)
     frames["n_channels"] = 1
+    frames["block"]["ext"][:, :1], frames["block"]["comm"][:, :1] = 1, 0
+    decoder = orc.Oracle(topo)
+    decoder.frames_begin(1)
+    call = 0
     for i in range(4):
         an.reset_window()
         an.ingest(an.to_device(tr.cols))
@@ -140,12 +172,16 @@ def test_calls_that_report_from_their_last_kernel_in_turn():
             assert (h.status, r.status) == (status, status)
             if status == "OK":
                 want, rate = orc.Oracle(topo).locate_hang(rows, 4, 1), orc.Oracle(topo).progress_rates(rows, 4, 1)
-                assert all(np.array_equal(h.root[k], want.root[k]) for k in want.root)
-                assert all(np.array_equal(r.comm[k], rate.comm[k]) for k in rate.comm)
-            assert an.decode_frames(frames.view(np.uint8).reshape(-1), np.arange(topo.n_ranks), i, 1)[0] == "OK"
+                for got, ref_of in ((h, want), (r, rate)):
+                    for name in ("root", "pair", "comm") if got is h else ("pair", "comm"):
+                        table, expected = getattr(got, name), getattr(ref_of, name)
+                        assert all(np.array_equal(table[k], expected[k]) for k in expected), (i, status, name)
+            call += 1
+            frames["block"]["counter"][:, 0] = call
+            frames["block"]["count"][:, 0, 0] = np.arange(topo.n_ranks)[:, None] * [3, 5] + call
+            both(an, decoder, frames.view(np.uint8).reshape(topo.n_ranks, -1), np.arange(topo.n_ranks, dtype=np.uint32), call, 1, on_device=bool(call % 2), what=call)
         blame, order = an.rank_blame()
-        assert np.array_equal(order, ref.order)
-        o = orc.Oracle(topo) if i == 9 else o
+        assert np.array_equal(order, ref.order) and all(np.array_equal(blame[k], ref.blame[k]) for k in ref.blame)
     an.close()
 
 

@@ -155,3 +155,47 @@ def test_rounds_that_nobody_recorded_in_large_layouts(comm, place):
     times, _ = an.profile_read()
     assert (times["sort_hist"][1] > 0) == (comm is not None)
     an.close()
+
+
+def _one(topo, cols, cap):
+    """one batch in a context of a larger window"""
+    from paper_2605_04478_amd import ccld
+    n = cols["rank"].size
+    an = ccld.Analyzer(topo, max_window_records=cap, max_batch_records=n)
+    an.ingest(an.to_device(cols))
+    g = an.analyze_window(FAR, n_records=n, per_record=True)
+    compare(g, orc.Oracle(topo).analyze_window(cols, FAR), *an.rank_blame(), what=(topo.n_comms, n))
+    an.close()
+
+
+@pytest.mark.parametrize("n_comms,n", [(32, 256 * 2048), (33, 248 * 2048), (33, 248 * 2048 + 1)])
+def test_counts_summed_by_the_placement_or_scanned(n_comms, n):
+    """as many words of counts (communicator buckets times workgroups) as every placement workgroup sums for itself, fewer, and more"""
+    topo = tg.make_topology(64, [[c, c + 1, c + 9] for c in range(n_comms)])
+    per = n // (3 * n_comms)
+    i = np.random.default_rng(n).permutation(3 * n_comms * (per + 1))[:n]
+    comm, seq = i // 3 % n_comms, i // (3 * n_comms)
+    rng = np.random.default_rng(n_comms)
+    te = T0 + seq * 10**6 + rng.integers(0, 1000, n)
+    te[rng.random(n) < 0.001] += 10**5
+    cols = {"rank": np.concatenate([topo.members_of(c) for c in range(n_comms)])[3 * comm + i % 3].astype(np.uint32), "comm": comm.astype(np.uint32),
+            "seq": seq.astype(np.uint64), "op": np.ones(n, np.uint8), "bytes": np.full(n, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**5}
+    _one(topo, cols, 28_000_000)
+
+
+def test_one_batch_of_few_buckets_and_four_counting_workgroups_each():
+    """2^23 records and more in one batch, a communicator that the grid does not take, eight buckets"""
+    n = 2100
+    topo = tg.make_topology(n, [list(range(n))] + [list(range(300 * c, 300 * c + 300)) for c in range(7)])
+    rounds = 1998
+    q = np.repeat(np.arange(rounds), 2 * n)
+    rank = np.tile(np.concatenate([np.arange(n)] * 2), rounds)
+    comm = np.tile(np.concatenate([np.zeros(n, np.int64), 1 + np.arange(n) // 300]), rounds)
+    rng = np.random.default_rng(8)
+    te = T0 + q * 10**6 + rng.integers(0, 1000, q.size)
+    te[rng.integers(0, q.size, 500)] += 10**5
+    p = rng.permutation(q.size)
+    cols = {"rank": rank.astype(np.uint32), "comm": comm.astype(np.uint32), "seq": q.astype(np.uint64), "op": np.ones(q.size, np.uint8),
+            "bytes": np.full(q.size, 64, np.uint64), "t_enter": te, "t_exit": te + 5 * 10**5}
+    assert q.size >= 1 << 23
+    _one(topo, {k: v[p] for k, v in cols.items()}, 26_000_000)
