@@ -8,6 +8,7 @@
 #include "device_utils.h"
 #include "grid.h"
 #include "report.h"
+#include "rows.h"
 #include "window_kernels.h"
 
 namespace ccld {
@@ -400,8 +401,13 @@ __device__ __forceinline__ void list_order(const EndArgs& a, OrderShared& S, u32
 
 // ---- hang alerts ------------------------------------------------------------------------------------------
 // A few alerts in table order with their candidates in rank order, a wavefront each.  (Seven launches and a second wait for
-// the host otherwise, which longer lists take: one wavefront's chain of loads is some 10 us for 390 members.)
-struct AlertShared { u32 row[END_ALERTS], cnt[END_ALERTS]; u64 hit[END_ALERTS][END_ALERT_MEMBERS / CCLD_WAVE]; };
+// the host otherwise, which longer lists take.)  What takes the time is the trips to memory of one wavefront: ALERT_AHEAD pieces of 64
+// members are on their way together, and a sorted collective's records are read in their order, where they say which members have
+// one, and are the members in order where all have.  (Windows of 82K records in collectives of 2,048 members, eight alerts: 212 us on the
+// grid with a piece after the other, 171 or 196 by their class so, 206 with launches of their own; sorted 543 with a search per
+// member, 436 or 451, 495.)
+constexpr u32 ALERT_AHEAD = 4;
+struct AlertShared { u32 row[END_ALERTS], cnt[END_ALERTS]; unsigned long long hit[END_ALERTS][END_ALERT_MEMBERS / CCLD_WAVE]; };
 template <bool GRID>
 __device__ __forceinline__ void list_alerts(const AlertArgs& a, AlertShared& S) {
   const u32 n = (u32)a.counters[CNT_NALERT], tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
@@ -415,26 +421,62 @@ __device__ __forceinline__ void list_alerts(const AlertArgs& a, AlertShared& S) 
   __syncthreads();
   const bool on = wave < n;
   const u64 C = a.seg_cap;
-  u32 s = 0, comm = 0, size = 0, moff = 0, total = 0;
+  u32 s = 0, comm = 0, size = 0, moff = 0, total = 0, before = 0;      // before: the hits of the pieces before the lane's
   int cls = 0;
+  auto& hit = S.hit[wave];               // a word per 64 members
   if (on) {
     s = S.row[wave];
     comm = (u32)a.seg[CCLD_SEG_COMM * C + s];
     const u32 nn = (u32)a.seg[CCLD_SEG_N * C + s], ninfl = (u32)a.seg[CCLD_SEG_INFLIGHT * C + s], first = (u32)a.seg[CCLD_SEG_FIRST * C + s];
     size = a.topo.size[comm]; moff = a.topo.member_off[comm];
     cls = alert_class(nn, ninfl, size);
-    for (u32 q0 = 0; q0 < size; q0 += CCLD_WAVE) {
-      const u32 q = q0 + lane;
-      bool hit = false;
-      if (q < size && cls != CCLD_HANG_H3_HARDWARE) {
-        i64 tx = INT64_MAX;
-        const bool here = alert_record<GRID>(a, s, comm, first, nn, q, &tx);
-        hit = cls == CCLD_HANG_H1_NOT_ENTERED ? !here : (here && tx != INT64_MAX);
+    const u32 words = (size + CCLD_WAVE - 1) / CCLD_WAVE;
+    if (lane < words) hit[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    CommLayout L{};
+    if (GRID) L = a.grid.lay[comm];
+    const u32 k = s - L.seg_base, cells = L.cell_base + k * L.size;
+    for (u32 q0 = 0; cls != CCLD_HANG_H3_HARDWARE && q0 < size; q0 += CCLD_WAVE * ALERT_AHEAD) {
+      u32 at[ALERT_AHEAD];
+      u64 m[ALERT_AHEAD];
+      bool found[ALERT_AHEAD];
+      auto member = [&](u32 u) { return std::min(q0 + u * CCLD_WAVE + lane, size - 1); };
+      if (cls == CCLD_HANG_H1_NOT_ENTERED && !GRID) {
+        const u64 mmask = ((u64)1 << a.sf.mb) - 1;      // key slot = position among the members in ascending rank order
+#pragma unroll
+        for (u32 u = 0; u < ALERT_AHEAD; ++u) m[u] = a.key[first + std::min(member(u), nn - 1)] & mmask;
+#pragma unroll
+        for (u32 u = 0; u < ALERT_AHEAD; ++u)
+          if (q0 + u * CCLD_WAVE + lane < nn) atomicOr(&hit[m[u] / CCLD_WAVE], 1ull << (m[u] % CCLD_WAVE));      // has a record
+        continue;
       }
-      const u64 m = ballot64(hit);
-      if (lane == 0) S.hit[wave][q0 / CCLD_WAVE] = m;
-      total += (u32)__popcll(m);
+#pragma unroll
+      for (u32 u = 0; u < ALERT_AHEAD; ++u) at[u] = GRID ? (u32)a.grid.cell_row[cells + member(u)] : a.idx[first + member(u)];
+      if (cls == CCLD_HANG_H1_NOT_ENTERED) {
+#pragma unroll
+        for (u32 u = 0; u < ALERT_AHEAD; ++u) found[u] = at[u] == GRID_EMPTY;
+      } else {                           // every member has a record
+        i64 tx[ALERT_AHEAD];
+#pragma unroll
+        for (u32 u = 0; u < ALERT_AHEAD; ++u)
+          tx[u] = (GRID ? unpack_row(a.grid.rows[L.cell_base + k / L.rpb * L.rpb * L.size + at[u]], a.grid.hdr->ref, a.grid.wide) : load_rec(a.win, at[u])).t_exit;
+#pragma unroll
+        for (u32 u = 0; u < ALERT_AHEAD; ++u) found[u] = tx[u] != INT64_MAX;
+      }
+#pragma unroll
+      for (u32 u = 0; u < ALERT_AHEAD; ++u) {
+        m[u] = ballot64(found[u] && q0 + u * CCLD_WAVE + lane < size);
+        if (lane == 0 && q0 + u * CCLD_WAVE < size) hit[q0 / CCLD_WAVE + u] = m[u];
+      }
     }
+    __builtin_amdgcn_wave_barrier();
+    u64 mine = lane < words ? hit[lane] : 0ull;
+    if (cls == CCLD_HANG_H1_NOT_ENTERED && !GRID && lane < words) {
+      mine = ~mine & (lane + 1 < words || size % CCLD_WAVE == 0 ? ~0ull : ((u64)1 << size % CCLD_WAVE) - 1);
+      hit[lane] = mine;
+    }
+    const u32 inc = wave_inclusive_sum((u32)__popcll(mine));
+    before = inc - (u32)__popcll(mine); total = lane_read(inc, CCLD_WAVE - 1);
     if (lane == 0) S.cnt[wave] = total;
   }
   __syncthreads();
@@ -452,13 +494,20 @@ __device__ __forceinline__ void list_alerts(const AlertArgs& a, AlertShared& S) 
     put(CCLD_ALR_NCAND, (i64)total);
     put(CCLD_ALR_CAND_OFF, (i64)off);
   }
-  u64 at = off;
-  for (u32 q0 = 0; q0 < size; q0 += CCLD_WAVE) {
-    const u64 m = S.hit[wave][q0 / CCLD_WAVE], k = at + mbcnt64(m);
-    if (((m >> lane) & 1u) && k < a.cand_cap) a.cand[k] = (i64)a.topo.members_sorted[moff + q0 + lane];
-    at += (u64)__popcll(m);
+  for (u32 q0 = 0; q0 < size; q0 += CCLD_WAVE * ALERT_AHEAD) {
+    u32 rank[ALERT_AHEAD];
+#pragma unroll
+    for (u32 u = 0; u < ALERT_AHEAD; ++u) rank[u] = a.topo.members_sorted[moff + std::min(q0 + u * CCLD_WAVE + lane, size - 1)];
+#pragma unroll
+    for (u32 u = 0; u < ALERT_AHEAD; ++u) {
+      const u32 w = q0 / CCLD_WAVE + u;
+      if (w * CCLD_WAVE >= size) break;
+      const u64 m = hit[w], at = (u64)off + lane_read(before, w) + mbcnt64(m);
+      if (((m >> lane) & 1u) && at < a.cand_cap) a.cand[at] = (i64)rank[u];
+    }
   }
 }
+static_assert(END_ALERT_MEMBERS <= CCLD_WAVE * CCLD_WAVE, "a lane per 64 members");
 static_assert(END_ALERTS <= GC_THREADS / CCLD_WAVE, "a wavefront per alert");
 
 // ---- the launches -----------------------------------------------------------------------------------------

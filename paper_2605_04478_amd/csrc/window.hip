@@ -803,6 +803,25 @@ void launch_alert_select(hipStream_t st, const AlertArgs& a) {
   run_select(st, p, a.n_seg, a.tile_counts, a.alert_list, &a.counters[CNT_NALERT]);
 }
 
+// Where the records of a collective are found: by binary search among the sorted keys, or by cell on the grid.
+// t_exit of member slot q's record in table row s, or false: no record
+template <bool GRID>
+__device__ __forceinline__ bool alert_record(const AlertArgs& a, u32 s, u32 comm, u32 first, u32 nn, u32 q, i64* t_exit) {
+  if (GRID) {
+    const CommLayout L = a.grid.lay[comm];
+    const u32 k = s - L.seg_base, fr = k / L.rpb;
+    const u32 li = a.grid.cell_row[L.cell_base + k * L.size + q];
+    if (li == GRID_EMPTY) return false;
+    *t_exit = unpack_row(a.grid.rows[L.cell_base + fr * L.rpb * L.size + li], a.grid.hdr->ref, a.grid.wide).t_exit;
+    return true;
+  }
+  const u64 mmask = ((u64)1 << a.sf.mb) - 1;      // key slot = position among the members in ascending rank order
+  u32 lo = first, hi = first + nn;
+  while (lo < hi) { const u32 m = (lo + hi) / 2; if ((u32)(a.key[m] & mmask) < q) lo = m + 1; else hi = m; }
+  if (lo >= first + nn || (u32)(a.key[lo] & mmask) != q) return false;
+  *t_exit = load_rec(a.win, a.idx[lo]).t_exit;
+  return true;
+}
 // candidates of one alert, in ascending rank order; EMIT = false only counts them
 template <bool EMIT, bool GRID>
 __global__ __launch_bounds__(256) void k_alert_cand(AlertArgs a, u32 n_alert) {
