@@ -110,6 +110,19 @@ def test_many_roots(n_late):
     assert g.n_root == n_late
 
 
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 1280, 2048, 2303, 5000])
+def test_rates_of_large_communicators(n):
+    """the slowest member in the last or the first row of a communicator: whole steps of a workgroup over its members, and what is left"""
+    topo, rng = ring_topology(n, comms=[list(range(n)), list(range(n))[::-1], list(range(n // 2))]), np.random.default_rng(n)
+    cols = _random(topo, 9, 1, rng, 3)
+    test_gpu_rates.run_both(topo, cols, 9, 1, what=n)
+    last = cols["rank"] == n - 1
+    cols["chunks_sent"][last] = cols["chunks_recv"][last] = cols["snap"][last]
+    cols["seq_posted"][last] = 9 + (cols["snap"][last] > 7)
+    _, o = test_gpu_rates.run_both(topo, cols, 9, 1, what=("slow", n))
+    assert list(o.comm["root"][:2]) == [n - 1, n - 1]
+
+
 @pytest.mark.parametrize("n,n_snap,n_ch", [(600, 500, 16), (733, 1000, 8)])
 def test_rates_of_regions_in_parts(n, n_snap, n_ch):
     """one member's series fill LDS, more members than regions: two and four parts per region, the last ones empty"""
