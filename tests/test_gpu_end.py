@@ -140,6 +140,24 @@ def test_blame_order_of_many_ranks(n_ranks):
     run_both(topo, cols, what=n_ranks)
 
 
+@pytest.mark.parametrize("n_ranks", [1, 65, 16384, 16385])
+def test_windows_without_records(n_ranks):
+    from paper_2605_04478_amd import ccld
+    topo = ring_topology(n_ranks)
+    an = ccld.Analyzer(topo, max_window_records=2 * n_ranks)
+    rows = toy_cols([(r, 0, 1, 1, 64, T0 + (10**7 if r % 50 == 7 else r % 13), T0 + 10**8) for r in range(n_ranks)])
+    for cols in ({k: v[:0] for k, v in rows.items()}, rows, None, {k: v[:0] for k, v in rows.items()}):
+        an.reset_window()
+        if cols is not None:
+            an.ingest(an.to_device(cols))
+        g = an.analyze_window(FAR, n_records=n_ranks, per_record=True)
+        ref = orc.Oracle(topo).analyze_window(cols if cols is not None else {k: v[:0] for k, v in rows.items()}, FAR)
+        blame, order = an.rank_blame()
+        assert g.status == ref.status == "OK" and g.n_seg == len(ref.seg["comm"]) and g.n_flag == len(ref.flag["comm"])
+        assert np.array_equal(order, ref.order) and all(np.array_equal(blame[k], ref.blame[k]) for k in ref.blame)
+    an.close()
+
+
 def test_calls_that_report_from_their_last_kernel_in_turn():
     """analysis, blame, chains, hang location, rates and frames on one context: each leaves the counters as the next needs them"""
     from paper_2605_04478_amd import ccld
