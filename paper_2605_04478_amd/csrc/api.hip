@@ -822,9 +822,7 @@ static ccld_status analyze_empty(ccld_ctx* c, ccld_window_result* o) {
   HIP_TRY(hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, st));
   HIP_TRY(hipMemsetAsync(c->blame, 0, sizeof(int64_t) * CCLD_BLM_NCOL * (uint64_t)n_ranks, st));
   take_ticket(c);
-  EndArgs e;
-  std::memset(&e, 0, sizeof(e));
-  launch_end(c, e, nullptr, nullptr, nullptr, 0);
+  launch_window_empty(st, n_ranks, c->blame_order, c->counters, c->arrivals, c->h_pinned, c->ticket);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_report(c));
   c->blame_valid = true;

@@ -101,7 +101,7 @@ void launch_grid_gaps(hipStream_t st, const GridArgs& d, uint32_t n_fine);
 void launch_grid_stats(hipStream_t st, const SegArgs& a, const GridArgs& d, uint32_t fine_bound, int64_t* blame, uint32_t n_ranks);
 
 // groups, blame order, a few alerts and report, and the flags of a window on the grid placement (groups.hip); d and f null: a
-// sorted window, whose flags are listed; al null: a window without records.  True if it reports.
+// sorted window, whose flags are listed; al null: alerts are not listed here.  True if it reports.
 bool launch_window_end(hipStream_t st, const EndArgs& a, const GridArgs* d, const FlagArgs* f, const AlertArgs* al, uint32_t fine_bound);
 
 }  // namespace ccld

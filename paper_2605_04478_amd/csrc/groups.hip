@@ -584,12 +584,14 @@ __global__ __launch_bounds__(GC_THREADS) void k_window_end(EndArgs a) {
   if (a.host) report_counters(a.counters, a.arrivals, a.host, a.ticket);
 }
 
-// A window without records has its blame order and the report to give, in one launch (64 ranks with ccld_rank_blame: 25.5 us in two
-// launches, 23.3).
-__global__ __launch_bounds__(GC_THREADS) void k_window_empty(EndArgs a) {
-  __shared__ OrderShared S;
-  list_order(a, S, blockIdx.x, gridDim.x);
-  report_counters(a.counters, a.arrivals, a.host, a.ticket);
+// A window without records blames nobody: the ranks in ascending order, and the report.
+__global__ __launch_bounds__(GC_THREADS) void k_window_empty(u32 n_ranks, u32* order, u64* counters, u32* arrivals, u64* host, u64 ticket) {
+  for (u32 r = blockIdx.x * GC_THREADS + threadIdx.x; r < n_ranks; r += gridDim.x * GC_THREADS) order[r] = r;
+  report_counters(counters, arrivals, host, ticket);
+}
+void launch_window_empty(hipStream_t st, uint32_t n_ranks, uint32_t* order, uint64_t* counters, uint32_t* arrivals, uint64_t* host, uint64_t ticket) {
+  const u32 blocks = std::min<u32>((n_ranks + GC_THREADS - 1) / GC_THREADS, 64);
+  hipLaunchKernelGGL(k_window_empty, dim3(blocks), dim3(GC_THREADS), 0, st, n_ranks, order, counters, arrivals, host, ticket);
 }
 
 // From so many communicators on their counts are scanned by a launch of their own
@@ -602,10 +604,6 @@ bool launch_window_end(hipStream_t st, const EndArgs& a_in, const GridArgs* d, c
   const u32 n_flags = !d ? 0u : std::min(std::max((fine_bound + END_FLAG_SHARE - 1) / END_FLAG_SHARE, a.flags_scanned ? END_FLAG_SCANNED : 0u), END_FLAG_BLOCKS);
   if (d && a.flags_scanned) launch_scan_tiles(st, d->nflag, fine_bound, &a.counters[CNT_NFLAG]);
   const u32 n_order = report ? std::min<u32>((a.n_ranks + 63) / 64, 64) : 0u, n_alerts = al ? 1u : 0u;
-  if (a.n_comms == 0) {
-    if (report) hipLaunchKernelGGL(k_window_empty, dim3(n_order), dim3(GC_THREADS), 0, st, a);
-    return report;
-  }
   const u32 blocks = a.n_comms + n_flags + n_order + n_alerts, ends = (a.n_comms + END_COMMS - 1) / END_COMMS;
   const AlertArgs alerts = al ? *al : AlertArgs{};
   if (d) hipLaunchKernelGGL(k_window_lists<true>, dim3(blocks), dim3(GC_THREADS), 0, st, a, *d, *f, alerts, n_flags, n_order, n_alerts);

@@ -115,7 +115,7 @@ struct EndArgs {
   uint64_t* counters;
   const uint16_t* gcode;     // [rows] op * GROUP_CLS + size class of each usable collective, NO_GROUP of the others
   const int64_t* range_c;    // [rows] T_max - T_min (written with the collectives' statistics)
-  uint32_t n_comms;          // 0: a window without records
+  uint32_t n_comms;
   uint32_t* comm_groups;     // [n_comms + 1] groups of each communicator
   uint32_t* comm_row;        // [n_comms] its first row of the table
   uint32_t* stage[3];        // [rows] what k_window_lists leaves for k_window_end
@@ -134,6 +134,8 @@ struct EndArgs {
   uint64_t ticket;
 };
 constexpr uint32_t END_ORDER_RANKS = 16384;       // most ranks whose blame order k_window_lists finds
+// a window without records: its blame order and the report
+void launch_window_empty(hipStream_t st, uint32_t n_ranks, uint32_t* order, uint64_t* counters, uint32_t* arrivals, uint64_t* host, uint64_t ticket);
 void launch_report(hipStream_t st, const uint64_t* counters, uint64_t* host, uint64_t ticket);
 void launch_blame_out(hipStream_t st, const int64_t* blame, const uint32_t* order_in, uint32_t n_ranks, int64_t* table_out,
                       uint32_t* order_out, uint64_t* counters, uint32_t* arrivals, uint64_t* host, uint64_t ticket);
