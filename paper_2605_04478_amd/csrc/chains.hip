@@ -104,11 +104,12 @@ __device__ __forceinline__ ChainFlag chain_flag(const ChainArgs& a, u32 k) {
 // SEARCH_LANES to a communicator: one looks at the middle and two at the middles of both halves, which is two steps of
 // the same search at a time.  The flag list is searched in PARENT_LANES + 1 parts at a time.
 // Up to PARENT_FEW flags 16 lanes take a flag and four a communicator; more flags, whose searches hide each other's loads, have
-// four lanes, each with a communicator of its own (us with 16 and with 4 lanes: 7,900 flags 16.5 and 20.5, 16,400 19.7 and
-// 21.4, 32,800 35.9 and 25.2, 145,000 110 and 41; the whole call on sorted windows, where the lanes also share the walk over a
-// collective's records: 9,800 flags 53 and 56, 12,600 59 and 63, 48,800 81 and 67, 377,000 392 and 208; beside a world communicator
-// of 4,096 members 1,300 flags 89 and 178, 12,500 110 and 189, 48,700 194 and 223, 717,000 2,779 and 2,075.  With the walk in
-// every lane those were 560 to 4,630 us).
+// four lanes, each with a communicator of its own.  The two cost the same somewhere between 16,400 and 32,800 flags on the grid and
+// later on sorted windows; at the line, the last power of two before, they differ by a tenth.  (us with 16 and with 4 lanes: 7,900
+// flags 16.5 and 20.5, 16,400 19.7 and 21.4, 32,800 35.9 and 25.2, 145,000 110 and 41; the whole call on sorted windows, where the
+// lanes also share the walk over a collective's records: 9,800 flags 53 and 56, 12,600 59 and 63, 48,800 81 and 67, 377,000 392 and
+// 208; beside a world communicator of 4,096 members 1,300 flags 89 and 178, 12,500 110 and 189, 48,700 194 and 223, 717,000 2,779
+// and 2,075.  With the walk in every lane those were 560 to 4,630 us.)
 constexpr u32 PARENT_FEW = 1u << 14;
 struct ChainBefore { i64 exit, enter; u32 comm, row; bool have; };
 template <bool GRID, u32 PARENT_LANES, u32 SEARCH_LANES>

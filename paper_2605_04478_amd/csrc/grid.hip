@@ -13,8 +13,8 @@ namespace ccld {
 // bucket.  The layout is infeasible (the host then sorts) when the grid has more cells or rounds than the buffers and
 // the records allow (counters that are far apart), when a coarse bucket spans more fine buckets than a partition
 // workgroup addresses, or when the batches lie so far apart that no single time serves all rows.
-// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 5 us at up to
-// 1,024 communicators and one batch, 19 at 3,200 and ten (31 with fewer loads on their way).
+// Bound by its few dependent loads and, with many batches, by one workgroup reading all their ranges: 4 to 5 us at up to
+// 1,024 communicators and one batch, 12 at 3,200, and 18.5 with ten batches (31 with fewer loads on their way).
 // PER: most communicators of a thread; AHEAD: batches whose ranges are on their way at a time.
 template <u32 PER, u32 AHEAD>
 __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
@@ -192,7 +192,8 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
 
 void launch_grid_layout(hipStream_t st, const GridArgs& d) {
   // One communicator per thread where there are no more than threads, and no loads ahead of a single batch: with the general form
-  // a window of one batch takes 7.8 us in place of 6.7, ten batches of a small job 8.6 in place of 5.7.
+  // a window of one batch takes 7.3 us in place of 4.7 at 512 ranks, ten batches of that job 9.3 in place of 4.9.  Two, five or ten
+  // batches ahead: 3,200 communicators with four batches 11.2, 11.3 and 13.6, with ten 19.3, 18.4 and 18.6, with 16 24.7, 25.6 and 26.1.
   constexpr u32 MANY = (GRID_MAX_COMMS + 1023) / 1024;
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, st, d); };
   if (d.n_comms <= 1024) { if (d.nb > 1) go(k_grid_layout<1, 5>); else go(k_grid_layout<1, 1>); }

@@ -519,7 +519,8 @@ __global__ __launch_bounds__(GC_THREADS, 8) void k_window_lists(EndArgs a, GridA
   __shared__ unsigned long long s_mem[(LDS + 7) / 8];
   // a data error found by an earlier kernel of this analysis: the tables are not valid and the detection state stays as it is
   if (a.counters[CNT_STATUS] != 0) return;
-  // the groups, which take longest where there are many, start behind the others: they fill the chip by themselves
+  // The groups, which take longest where there are many, start behind the others: they fill the chip by themselves (in front of
+  // the flags, us: 82M records 54.5 both ways, a stream of 3,200 communicators 37.5 and 38.3, 512 ranks 11.7 and 10.8).
   const u32 b = blockIdx.x;
   if (b < n_alerts) list_alerts<GRID>(al, *reinterpret_cast<AlertShared*>(s_mem));
   else if (b - n_alerts < n_order) list_order(a, *reinterpret_cast<OrderShared*>(s_mem), b - n_alerts, n_order);

@@ -1257,7 +1257,8 @@ __device__ __forceinline__ void frame_row(const FrameArgs& a, const ccld_snapsho
   store_agent(reinterpret_cast<i64*>(&o.seq_posted[k]), (i64)l0);
   store_agent(&o.chunks_sent[k], (u32)l1); store_agent(&o.chunks_recv[k], (u32)(l1 >> 32));
 }
-// The last workgroup reports, so the rows are stored past the caches.  (A report in a launch of its own cost 4 us of 32.)
+// The last workgroup reports, so the rows are stored past the caches.  (With a report in a launch of its own a call took 1 us more:
+// 4,096 frames 43.5 and 42.5 us with the GPU waited for; of 65,536 ranks 116.3 and 114.4 one after another.)
 __global__ __launch_bounds__(256) void k_frame_rows(FrameArgs a, ccld_snapshot_rows o) {
   __shared__ u32 s_last;
   const u64 s = *a.status;
