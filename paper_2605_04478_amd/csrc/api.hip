@@ -142,6 +142,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   const uint64_t SN = std::max<uint64_t>(c->snap_cap, 1);
   c->n_members = n_members;
   c->rate_root = w.take<int64_t>(n_comms);
+  c->long_comms = w.take<LongComm>(n_comms);
   c->h_counters = w.take<uint64_t>(CNT_COUNT + HANG_REGIONS / 2);
   c->h_cell = w.take<uint64_t>(2 * SN);
   c->h_cnt = w.take<uint32_t>(SN / 32 + 1);
@@ -392,6 +393,14 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   for (uint32_t k = 0; k < topo->n_comms; ++k) cinfo[k] = make_uint2(topo->member_off[k], topo->size[k]);
   up(c->comm_info, cinfo.data(), sizeof(uint2) * cinfo.size());
   up(c->topo.member_comm, mcomm.data(), 4ull * n_members);
+  std::vector<LongComm> longs;
+  c->short_lanes = 1;
+  for (uint32_t k = 0; k < topo->n_comms; ++k) {
+    if (topo->size[k] > SHORT_COMM) longs.push_back({k, topo->member_off[k], topo->size[k], 0});
+    else while (c->short_lanes < topo->size[k]) c->short_lanes *= 2;
+  }
+  c->n_long_comms = (uint32_t)longs.size();
+  up(c->long_comms, longs.data(), sizeof(LongComm) * longs.size());
   up(c->topo.rank_cell4, rp4.data(), 4ull * rp4.size());
   if (!fits_cell4) c->topo.rank_cell4 = nullptr;
   if (hipMemsetAsync(c->gstate, 0, sizeof(GroupState) * (uint64_t)topo->n_comms * GROUP_SLOTS, c->stream) != hipSuccess) rs = CCLD_E_HIP;

@@ -102,6 +102,8 @@ constexpr int SEG_TILE = 1024;       // sorted records owned by one workgroup of
 constexpr int SEG_THREADS = 256;
 constexpr int SEL_TILE = 2048;       // records per workgroup of the compaction kernels
 constexpr int RANKCOUNT_BLOCKS = 2048;
+constexpr uint32_t SHORT_COMM = 64;          // most members of a communicator whose rates part of a wavefront compares
+struct LongComm { uint32_t comm, off, size, unused; };
 constexpr uint32_t HANG_REGIONS = 512;       // most regions that snapshot rows are regrouped by
 
 // device counters written by kernels and read back by the host
@@ -161,6 +163,9 @@ struct ccld_ctx {
   uint64_t* counters;                 // [CNT_COUNT] device
   uint32_t* arrivals;                 // [ARRIVAL_WORDS] of the kernels whose last workgroup reports; zero between launches
   uint32_t max_comm_size;             // members of the largest communicator
+  ccld::LongComm* long_comms;         // [n_comms] the first n_long_comms: communicators of more than SHORT_COMM members, ascending
+  uint32_t n_long_comms;
+  uint32_t short_lanes;               // the smallest power of two that no other communicator's members exceed
   uint32_t long_classes;              // which sizes beyond 64 members there are (SegArgs)
   uint64_t sort_cap;                  // items the sort buffers hold: max(window records, communicator members)
   uint64_t* h_pinned;                 // pinned host staging

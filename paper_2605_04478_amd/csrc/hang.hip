@@ -1089,46 +1089,51 @@ __device__ __forceinline__ bool rate_less(const RateCand& x, const RateCand& y) 
   return x.rank < y.rank;
 }
 
-constexpr u32 RATE_AHEAD = 4;
-// One workgroup per communicator: the member of minimal SendRate, RecvRate, and of both kinds; the caller's tables, stored
-// past the caches, since the last workgroup reports.
-__device__ __forceinline__ void rate_comm(const HangArgs& a, i64* __restrict__ rate_root, RateCand (&s_best)[2][256]) {
-  const u32 c = blockIdx.x, tid = threadIdx.x;
-  const u32 off = a.T.member_off[c], n = a.T.size[c];
-  if (!hang_rows_ok(a)) return;                  // the same for every thread
+constexpr u32 RATE_MANY = 4;
+__device__ __forceinline__ void rate_load(const HangArgs& a, u64 p, RateCand& snd, RateCand& rcv) {
+  const u32 rk = a.T.members[p];
+  snd = {(u64)RPAIR(a, CCLD_RATE_OPS_SEND, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_SEND, p), rk};
+  rcv = {(u64)RPAIR(a, CCLD_RATE_OPS_RECV, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_RECV, p), rk};
+}
+// member p of communicator c: the caller's row, and the best of both kinds
+__device__ __forceinline__ void rate_use(const HangArgs& a, u32 c, u64 p, const RateCand& snd, const RateCand& rcv, RateCand (&best)[2]) {
+  if (a.out_pair && p < a.pair_cap) {
+    auto put = [&](int col, u64 v) { store_agent(&a.out_pair[(u64)col * a.pair_cap + p], (i64)v); };
+    put(CCLD_RATE_RANK, snd.rank); put(CCLD_RATE_COMM, c);
+    put(CCLD_RATE_OPS_SEND, snd.ops); put(CCLD_RATE_CHANGES_SEND, snd.chg);
+    put(CCLD_RATE_OPS_RECV, rcv.ops); put(CCLD_RATE_CHANGES_RECV, rcv.chg);
+  }
+  if (rate_less(snd, best[0])) best[0] = snd;
+  if (rate_less(rcv, best[1])) best[1] = rcv;
+}
+__device__ __forceinline__ void rate_root_of(const HangArgs& a, i64* __restrict__ rate_root, u32 c, const RateCand& snd, const RateCand& rcv) {
+  const RateCand both = rate_less(snd, rcv) ? snd : rcv;
+  const i64 row[CCLD_RCOMM_NCOL] = {(i64)c, snd.chg ? (i64)snd.rank : (i64)CCLD_NO_RANK, rcv.chg ? (i64)rcv.rank : (i64)CCLD_NO_RANK,
+                                    both.chg ? (i64)both.rank : (i64)CCLD_NO_RANK};
+  if (a.out_comm && c < a.comm_cap)
+    for (int col = 0; col < CCLD_RCOMM_NCOL; ++col) store_agent(&a.out_comm[(u64)col * a.comm_cap + c], row[col]);
+  rate_root[c] = row[CCLD_RCOMM_ROOT];
+}
+// A communicator of more than SHORT_COMM members, by a workgroup.
+template <u32 AHEAD>
+__device__ __forceinline__ void rate_long(const HangArgs& a, i64* __restrict__ rate_root, RateCand (&s_best)[2][256], const LongComm& L) {
+  const u32 tid = threadIdx.x, c = L.comm, off = L.off, n = L.size;
   RateCand best[2] = {{0, 0, 0xFFFFFFFFu}, {0, 0, 0xFFFFFFFFu}};
-  auto load = [&](u32 q, RateCand& snd, RateCand& rcv) {
-    const u64 p = (u64)off + q;
-    const u32 rk = a.T.members[p];
-    snd = {(u64)RPAIR(a, CCLD_RATE_OPS_SEND, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_SEND, p), rk};
-    rcv = {(u64)RPAIR(a, CCLD_RATE_OPS_RECV, p), (u64)RPAIR(a, CCLD_RATE_CHANGES_RECV, p), rk};
-  };
-  auto use = [&](u32 q, const RateCand& snd, const RateCand& rcv) {
-    const u64 p = (u64)off + q;
-    if (a.out_pair && p < a.pair_cap) {
-      auto put = [&](int col, u64 v) { store_agent(&a.out_pair[(u64)col * a.pair_cap + p], (i64)v); };
-      put(CCLD_RATE_RANK, snd.rank); put(CCLD_RATE_COMM, c);
-      put(CCLD_RATE_OPS_SEND, snd.ops); put(CCLD_RATE_CHANGES_SEND, snd.chg);
-      put(CCLD_RATE_OPS_RECV, rcv.ops); put(CCLD_RATE_CHANGES_RECV, rcv.chg);
-    }
-    if (rate_less(snd, best[0])) best[0] = snd;
-    if (rate_less(rcv, best[1])) best[1] = rcv;
-  };
-  // RATE_AHEAD members of a thread at a time: a load behind the stores of the member before would wait for those too, and they go
+  // AHEAD members of a thread at a time: a load behind the stores of the member before would wait for those too, and they go
   // past the caches (16,384 members: the call 129.5 us with one at a time, 110 so, 119.6 with plain stores and a report of its own;
   // 60,000: 308, 235 and 273; 1,008 members in four communicators each: 81.0, 80.7 and 83.1)
   u32 q = tid;
-  for (; q - tid + 256 * RATE_AHEAD <= n; q += 256 * RATE_AHEAD) {
-    RateCand snd[RATE_AHEAD], rcv[RATE_AHEAD];
+  for (; AHEAD > 1 && q - tid + 256 * AHEAD <= n; q += 256 * AHEAD) {
+    RateCand snd[AHEAD], rcv[AHEAD];
 #pragma unroll
-    for (u32 u = 0; u < RATE_AHEAD; ++u) load(q + u * 256, snd[u], rcv[u]);
+    for (u32 u = 0; u < AHEAD; ++u) rate_load(a, (u64)off + q + u * 256, snd[u], rcv[u]);
 #pragma unroll
-    for (u32 u = 0; u < RATE_AHEAD; ++u) use(q + u * 256, snd[u], rcv[u]);
+    for (u32 u = 0; u < AHEAD; ++u) rate_use(a, c, (u64)off + q + u * 256, snd[u], rcv[u], best);
   }
   for (; q < n; q += 256) {
     RateCand snd, rcv;
-    load(q, snd, rcv);
-    use(q, snd, rcv);
+    rate_load(a, (u64)off + q, snd, rcv);
+    rate_use(a, c, (u64)off + q, snd, rcv, best);
   }
   s_best[0][tid] = best[0]; s_best[1][tid] = best[1];
   __syncthreads();
@@ -1141,20 +1146,52 @@ __device__ __forceinline__ void rate_comm(const HangArgs& a, i64* __restrict__ r
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    const RateCand snd = s_best[0][0], rcv = s_best[1][0], both = rate_less(snd, rcv) ? snd : rcv;
-    const i64 row[CCLD_RCOMM_NCOL] = {(i64)c, snd.chg ? (i64)snd.rank : (i64)CCLD_NO_RANK, rcv.chg ? (i64)rcv.rank : (i64)CCLD_NO_RANK,
-                                      both.chg ? (i64)both.rank : (i64)CCLD_NO_RANK};
-    if (a.out_comm && c < a.comm_cap)
-      for (int col = 0; col < CCLD_RCOMM_NCOL; ++col) store_agent(&a.out_comm[(u64)col * a.comm_cap + c], row[col]);
-    rate_root[c] = row[CCLD_RCOMM_ROOT];
-  }
+  if (tid == 0) rate_root_of(a, rate_root, c, s_best[0][0], s_best[1][0]);
 }
-__global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__ rate_root) {
+// The member of minimal SendRate, RecvRate, and of both kinds of every communicator, and the caller's tables, stored past the
+// caches, since the last workgroup reports.  A long communicator (they are listed, and begin first) has a workgroup; of the others
+// each has S.lanes lanes of a wavefront, a member to a lane.  With a workgroup each, most of a wavefront idled, and all of them
+// arrived for the report at words that take 35 to 50 ns per arrival (the call, us: 262,144 communicators of two members 579 -> 205,
+// 32,768 131 -> 82, 8,192 60.2 -> 49.5; 16,384 ranks in 3,200 83 -> 79, 4,096 of 16 83.4 -> 77.5; of 64 members, which take a wavefront,
+// 79 -> 78; of 65 and more, which have a workgroup, as before).
+constexpr u32 RATE_BLOCKS = 2048;               // most workgroups of the short ones
+struct RateShape { const LongComm* longs; u32 n_long, lanes; };
+template <u32 AHEAD>
+__global__ __launch_bounds__(256) void k_rate_comm(HangArgs a, i64* __restrict__ rate_root, RateShape S) {
   __shared__ RateCand s_best[2][256];
   __shared__ u32 s_last;
-  rate_comm(a, rate_root, s_best);
+  if (!hang_rows_ok(a)) {                        // the same for every thread
+  } else if (blockIdx.x < S.n_long) {
+    rate_long<AHEAD>(a, rate_root, s_best, S.longs[blockIdx.x]);
+  } else {
+    const u32 per = 256 / S.lanes, l = threadIdx.x % S.lanes, end = a.T.n_comms;
+    for (u32 c0 = (blockIdx.x - S.n_long) * per; c0 < end; c0 += (gridDim.x - S.n_long) * per) {
+      const u32 c = c0 + threadIdx.x / S.lanes, at = c < end ? c : end - 1, n = a.T.size[at], off = a.T.member_off[at];
+      const bool mine = c < end && n <= SHORT_COMM;
+      RateCand best[2] = {{0, 0, 0xFFFFFFFFu}, {0, 0, 0xFFFFFFFFu}};
+      if (mine && l < n) {
+        RateCand snd, rcv;
+        rate_load(a, (u64)off + l, snd, rcv);
+        rate_use(a, c, (u64)off + l, snd, rcv, best);
+      }
+      for (u32 m = 1; m < S.lanes; m <<= 1)
+#pragma unroll
+        for (u32 k = 0; k < 2; ++k) {
+          const RateCand o{shfl_xor_u64(best[k].ops, m), shfl_xor_u64(best[k].chg, m), (u32)__shfl_xor((int)best[k].rank, (int)m, CCLD_WAVE)};
+          if (rate_less(o, best[k])) best[k] = o;
+        }
+      if (mine && l == 0) rate_root_of(a, rate_root, c, best[0], best[1]);
+    }
+  }
   if (last_arrival(a.arrivals, gridDim.x, &s_last)) report_and_clear(a);
+}
+static void launch_rate_comm(hipStream_t st, const ccld_ctx* c, const HangArgs& a) {
+  const RateShape S{c->long_comms, c->n_long_comms, c->short_lanes};
+  // (the short ones' workgroups pass over the long ones' numbers)
+  const u32 n = c->topo.n_comms, per = 256 / S.lanes, blocks = n > S.n_long ? std::min((n + per - 1) / per, RATE_BLOCKS) : 0u;
+  // where nobody has the members for it, several at a time would only cost registers (5 wavefronts per SIMD instead of 8)
+  if (c->max_comm_size >= 256 * RATE_MANY) hipLaunchKernelGGL(k_rate_comm<RATE_MANY>, dim3(S.n_long + blocks), dim3(256), 0, st, a, c->rate_root, S);
+  else hipLaunchKernelGGL(k_rate_comm<1>, dim3(S.n_long + blocks), dim3(256), 0, st, a, c->rate_root, S);
 }
 // ---- Probing Frames (Section 5.1) -------------------------------------------------------------------
 struct FrameArgs {
@@ -1618,7 +1655,7 @@ extern "C" ccld_status ccld_progress_rates(ccld_ctx* c, const ccld_snapshots* sn
     a.checked = checked ? 1 : 0;
     a.out_pair = o->pair; a.pair_cap = o->pair_cap; a.out_comm = o->comm; a.comm_cap = o->comm_cap;
     a.ticket = take_ticket(c);
-    hipLaunchKernelGGL(k_rate_comm, dim3(c->topo.n_comms), dim3(256), 0, st, a, c->rate_root);
+    launch_rate_comm(st, c, a);
     c->prof.end(CCLD_PROF_HANG);
   };
   HIP_TRY(snapshot_args(c, S, sn, n_rows, n_cell, a));

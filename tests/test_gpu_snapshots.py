@@ -123,6 +123,18 @@ def test_rates_of_large_communicators(n):
     assert list(o.comm["root"][:2]) == [n - 1, n - 1]
 
 
+@pytest.mark.parametrize("sizes", [[1] * 300, [2] * 131, [3, 4, 1] * 45, [1, 63, 64, 65, 2, 64, 66, 1], [65, 70], [64], [128] * 3 + [33] * 9,
+                                   [2, 1] * 4100 + [65, 64, 1]],
+                         ids=["ones", "pairs", "to four", "around 64", "long", "one of 64", "long first", "more than are resident"])
+def test_rates_of_many_communicators(sizes):
+    """communicators with some lanes of a wavefront each beside those with a workgroup each; the last workgroup partly empty, and
+    more communicators than the workgroups take at once"""
+    rng = np.random.default_rng(len(sizes))
+    topo = ring_topology(150, comms=[list(rng.choice(150, k, replace=False)) for k in sizes])
+    for snaps, ch in ((9, 2), (3, 1)):
+        test_gpu_rates.run_both(topo, _random(topo, snaps, ch, rng, 3), snaps, ch, what=(len(sizes), snaps))
+
+
 @pytest.mark.parametrize("n,n_snap,n_ch", [(600, 500, 16), (733, 1000, 8)])
 def test_rates_of_regions_in_parts(n, n_snap, n_ch):
     """one member's series fill LDS, more members than regions: two and four parts per region, the last ones empty"""
