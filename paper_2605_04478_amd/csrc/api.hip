@@ -143,7 +143,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   c->n_members = n_members;
   c->rate_root = w.take<int64_t>(n_comms);
   c->long_comms = w.take<LongComm>(n_comms);
-  c->h_counters = w.take<uint64_t>(CNT_COUNT + HANG_REGIONS / 2);
+  c->h_counters = w.take<uint64_t>(CNT_COUNT + HANG_REGIONS);
   c->h_cell = w.take<uint64_t>(2 * SN);
   c->h_cnt = w.take<uint32_t>(SN / 32 + 1);
   c->h_pair = w.take<int64_t>((uint64_t)CCLD_HPAIR_NCOL * n_members);
@@ -407,7 +407,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   if (hipMemsetAsync(c->batch_meta, 0, sizeof(BatchMeta) * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (c->comm_range && hipMemsetAsync(c->comm_range, 0, 16ull * topo->n_comms * ((uint64_t)c->p.window_batches + 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->counters, 0, sizeof(uint64_t) * CNT_COUNT, c->stream) != hipSuccess) rs = CCLD_E_HIP;
-  if (hipMemsetAsync(c->h_counters, 0, sizeof(uint64_t) * (CNT_COUNT + HANG_REGIONS / 2), c->stream) != hipSuccess) rs = CCLD_E_HIP;
+  if (hipMemsetAsync(c->h_counters, 0, sizeof(uint64_t) * (CNT_COUNT + HANG_REGIONS), c->stream) != hipSuccess) rs = CCLD_E_HIP;
   if (hipMemsetAsync(c->arrivals, 0, sizeof(uint32_t) * ARRIVAL_WORDS, c->stream) != hipSuccess) rs = CCLD_E_HIP;
   launch_fill_u64(c->stream, (uint64_t*)c->rate_root, topo->n_comms, (uint64_t)CCLD_NO_RANK);
   c->f_status = c->f_frame + topo->n_ranks;

@@ -175,7 +175,7 @@ struct ccld_ctx {
   // staging for host-resident batches
   uint8_t* stage;                     // [batch_cap * 41] device
   // hang location and rates
-  uint64_t* h_counters;               // [CNT_COUNT] counters, then the rows of every region
+  uint64_t* h_counters;               // [CNT_COUNT] counters, then two words per region: its rows
   bool h_clear;                       // both are clear
   uint64_t n_members;                 // member slots over all communicators
   uint64_t* h_cell;                   // [snap_cap][2]  (operation counter, sent | recv << 32)

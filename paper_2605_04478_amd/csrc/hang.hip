@@ -51,7 +51,7 @@ struct HangArgs {
   // two-step placement of large grids: rows regrouped by region of 2^rb cells
   ulonglong2* part_pay;   // [n_regions << rb] cell contents
   u32* part_idx;          // [n_regions << rb] cell number inside the region
-  u32* part_fill;         // [n_regions] rows received
+  u32* part_fill;         // [n_regions] rows received; with `ends`, [2][SPLIT_REGIONS] rows from the front and from the end
   int rb;
   u32 n_regions;
   // hang location of large grids: rows regrouped by region of 2^sb members
@@ -59,6 +59,7 @@ struct HangArgs {
   u32* arrivals;
   int leave_clear;        // the pass clears counters and part_fill behind itself
   int sb;
+  int ends;               // regions are filled from both ends (contexts; the static array has no room for the second counters)
   int pb;                 // rates: the members of a region are taken 2^pb at a time
   u32 snap_inv;           // ceil(2^32 / n_snap)
 };
@@ -399,10 +400,13 @@ __global__ __launch_bounds__(256) void k_hang_scan(HangArgs a) {
 //   x   operation counter << SPLIT_CELL_BITS | cell inside the region
 //   y   sent | received << 32
 // Rows with an operation counter of 2^46 or more do not fit; the host then takes the two passes above.  Bytes bound it:
-// 32 in and 16 out, then 16 in.  At 16.8M rows in 256 regions the split takes 186 us (4.3 TB/s), the regions 47 us
+// 32 in and 16 out, then 16 in.  At 16.8M rows in 256 regions the split takes 181 us (4.4 TB/s), the regions 47 us
 // (5.7 TB/s), where placing the rows in a grid in memory and scanning that took 540 us.  Rounds of 3,072 rows: each
-// reserves room in every region with an atomic, and rounds of 2,048 rows with 512 regions spend 340 us on them; larger
-// rounds leave one workgroup per CU and nothing to hide the phases behind.
+// reserves room in every region with an atomic, and those of all workgroups for one line of counters follow one another at
+// about 34 ns (rounds of 2,048 rows with 512 regions: 340 us).  So there are two sets of counters: every second workgroup fills
+// the regions from their ends (2.4M rows of rates 80 -> 75 us per call, hang location of 16.8M rows 268 -> 261).  Larger
+// rounds leave one workgroup per CU and nothing to hide the phases behind: with 4,096 or 6,144 rows and whole lines
+// stored (the rest of a line waiting in LDS for the next round) the call took 262 and 309 us, with rounds of 2,048 269.
 constexpr int SPLIT_CELL_BITS = 18;
 constexpr u32 SPLIT_REGIONS = HANG_REGIONS;
 constexpr size_t SPLIT_LDS = 64000, RATE_LDS = 156000;      // LDS of a region: hang location, rates
@@ -414,6 +418,22 @@ inline size_t rate_region_lds(u32 n_ch, u32 n_snap, int sb) {
 inline size_t region_lds(u32 n_ch, u32 n_snap, int sb) {
   return ((20ull * n_ch + 4) << sb) + ((((u64)n_ch * n_snap << sb) + 31) / 32) * 4;
 }
+// A region's rows: those from the front, the room between these and the ones from the end, all.
+struct RegionRows { u32 front, gap, n; };
+__device__ __forceinline__ u32 region_room(const HangArgs& a, u32 reg, u32 cap) {
+  const u64 left = a.n_cell - (u64)reg * cap;
+  return left < cap ? (u32)left : cap;
+}
+__device__ __forceinline__ RegionRows region_rows(const HangArgs& a, u32 reg, u32 cap) {
+  const u32 room = region_room(a, reg, cap), front = a.part_fill[reg], back = a.ends ? a.part_fill[SPLIT_REGIONS + reg] : 0u;
+  if (front > room || back > room - front) {         // more rows than cells
+    if (threadIdx.x == 0) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)DS_DUPLICATE);
+    return {room, 0, room};
+  }
+  return {front, room - front - back, front + back};
+}
+// where row i of a region lies
+__device__ __forceinline__ u32 region_row(const RegionRows& r, u32 i) { return i < r.front ? i : i + r.gap; }
 template <int THREADS, int U>
 __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
   constexpr u32 CHUNK = THREADS * U;
@@ -424,6 +444,8 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
   const u32 tid = threadIdx.x;
   const u32 L = a.n_snap - 1, per_member = a.n_ch * a.n_snap, cap = per_member << a.sb, smask = (1u << a.sb) - 1;
   u64 status = 0;
+  const bool from_end = a.ends && (blockIdx.x & 1);
+  u32* const fill = a.part_fill + (from_end ? SPLIT_REGIONS : 0u);
   const u64 i_begin = chunk * blockIdx.x;
   const u64 i_end = chunk * (blockIdx.x + 1) < a.n_rows ? chunk * (blockIdx.x + 1) : a.n_rows;
   u32 c[U], r[U], ch[U], sn[U], se[U], rv[U];
@@ -470,14 +492,14 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
       for (u32 k = 0; k < PER; ++k) { v[k] = PER * tid + k < a.n_regions ? s_cnt[PER * tid + k] : 0u; sum += v[k]; }
       u32 f[PER];
 #pragma unroll
-      for (u32 k = 0; k < PER; ++k) if (v[k]) f[k] = atomicAdd(&a.part_fill[PER * tid + k], v[k]);
+      for (u32 k = 0; k < PER; ++k) if (v[k]) f[k] = atomicAdd(&fill[PER * tid + k], v[k]);
       u32 tot;
       u32 ex = block_exclusive_sum<THREADS>(sum, s_scan, &tot);
 #pragma unroll
       for (u32 k = 0; k < PER; ++k)
         if (PER * tid + k < a.n_regions) {
           s_pre[PER * tid + k] = ex;
-          if (v[k]) s_off[PER * tid + k] = f[k] - ex;
+          if (v[k]) s_off[PER * tid + k] = (from_end ? region_room(a, PER * tid + k, cap) - f[k] - v[k] : f[k]) - ex;
           ex += v[k];
           s_cnt[PER * tid + k] = 0;
         }
@@ -496,7 +518,7 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
     const u32 total = s_total;
     for (u32 i = tid; i < total; i += THREADS) {
       const u32 reg = s_reg[i], pos = s_off[reg] + i;
-      if (pos < cap && (u64)reg * cap + pos < a.n_cell) {
+      if (pos < region_room(a, reg, cap)) {
         a.part_row[(u64)reg * cap + pos] = s_row[i];
       } else {
         status |= DS_DUPLICATE;            // more rows than cells
@@ -513,14 +535,14 @@ __global__ __launch_bounds__(THREADS) void k_hang_split(HangArgs a, u64 chunk) {
 // rates 118.5 -> 112.5).
 __global__ __launch_bounds__(SPLIT_REGIONS) void k_hang_clear(HangArgs a) {
   if (threadIdx.x < CNT_COUNT) a.counters[threadIdx.x] = 0;
-  if (threadIdx.x < (a.leave_clear ? SPLIT_REGIONS : a.n_regions)) a.part_fill[threadIdx.x] = 0;      // all: a later pass may have more
+  for (u32 i = threadIdx.x; i < (a.ends ? 2 * SPLIT_REGIONS : a.n_regions); i += SPLIT_REGIONS) a.part_fill[i] = 0;      // all: a later pass may have more
 }
 __device__ __forceinline__ void report_and_clear(const HangArgs& a) {
   report_words(a.counters, a.host, a.ticket);
   if (!a.leave_clear) return;
   __syncthreads();                     // the words have been read
   if (threadIdx.x < CNT_COUNT) store_agent(reinterpret_cast<i64*>(&a.counters[threadIdx.x]), 0);
-  for (u32 i = threadIdx.x; i < a.n_regions; i += blockDim.x) a.part_fill[i] = 0;
+  for (u32 i = threadIdx.x; i < a.n_regions; i += blockDim.x) { a.part_fill[i] = 0; a.part_fill[SPLIT_REGIONS + i] = 0; }
 }
 __device__ __forceinline__ void store_member(const HangArgs& a, u64 p, u64 seq, u64 S, u64 R, u32 onset, bool moved) {
   PAIR(a, CCLD_HPAIR_STALLED, p) = a.n_snap - 1 >= a.stall_snapshots && !moved ? 1 : 0;
@@ -544,7 +566,8 @@ __global__ __launch_bounds__(THREADS) void k_hang_region(HangArgs a) {
   u32* s_moved = s_bits + words;                                       // [2^sb]
   __shared__ u32 s_cells;
   const u64 p0 = (u64)reg << a.sb, q0 = p0 * a.n_ch, q_end = a.n_members * a.n_ch;
-  const u32 have = a.part_fill[reg], n = have < cap ? have : cap;
+  const RegionRows R = region_rows(a, reg, cap);
+  const u32 n = R.n;
   const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * cap;
   for (u32 i = tid; i < n_ser; i += THREADS) {
     s_final[i] = q0 + i < q_end ? a.final[q0 + i] : make_ulonglong2(0, 0);
@@ -560,7 +583,7 @@ __global__ __launch_bounds__(THREADS) void k_hang_region(HangArgs a) {
     u64x2 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (i0 + u * THREADS < n) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS));
+      if (i0 + u * THREADS < n) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rows + region_row(R, i0 + u * THREADS)));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (i0 + u * THREADS >= n) continue;
@@ -1029,7 +1052,8 @@ __global__ __launch_bounds__(THREADS) void k_rate_region(HangArgs a) {
   u32* s_bits = reinterpret_cast<u32*>(s_sum + 4 * members);
   __shared__ u32 s_cells;
   const u64 p0 = ((u64)reg << a.sb) + (db ? (u64)part << a.pb : 0);
-  const u32 have = a.part_fill[reg], n = have < room ? have : room;
+  const RegionRows R = region_rows(a, reg, room);
+  const u32 n = R.n;
   const ulonglong2* __restrict__ rows = a.part_row + (u64)reg * room;
   for (u32 i = tid; i < words; i += THREADS) s_bits[i] = 0;
   for (u32 i = tid; i < 4 * members; i += THREADS) s_sum[i] = 0;
@@ -1042,7 +1066,7 @@ __global__ __launch_bounds__(THREADS) void k_rate_region(HangArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (i0 + u * THREADS < n) {
-        const u64x2* row = reinterpret_cast<const u64x2*>(rows + i0 + u * THREADS);
+        const u64x2* row = reinterpret_cast<const u64x2*>(rows + region_row(R, i0 + u * THREADS));
         v[u] = db ? *row : __builtin_nontemporal_load(row);
       }
 #pragma unroll
@@ -1456,7 +1480,7 @@ static bool split_regions(HangArgs& a, const HangScratch& S, size_t (*lds)(u32, 
   if (regions > SPLIT_REGIONS || per_member > (1ull << SPLIT_CELL_BITS) || lds(a.n_ch, a.n_snap, pb) > lds_max || sb - pb > parts ||
       (!S.clear && regions > a.n_cell / 32 + 1)) return false;
   a.sb = sb; a.pb = pb; a.n_regions = (uint32_t)regions; a.snap_inv = (uint32_t)((1ull << 32) / a.n_snap + 1);
-  a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.fill; a.leave_clear = S.clear != nullptr;
+  a.part_row = S.split_row; a.final = S.split_final; a.part_fill = S.fill; a.leave_clear = S.clear != nullptr; a.ends = S.clear != nullptr;
   return true;
 }
 template <int THREADS, int U>

@@ -91,6 +91,23 @@ def test_duplicates_gaps_and_extra_rows(n, n_snap):
         _both(topo, c, n_snap, 2, what)
 
 
+@pytest.mark.parametrize("n,n_snap", [(3, 9), (601, 70), (1051, 150)])
+def test_a_row_too_many_in_a_region(n, n_snap):
+    """regions are filled from both ends: one more row than the first or the last, smaller region has cells, and as many fewer in
+    another one, or in none"""
+    rng = np.random.default_rng(n)
+    topo = ring_topology(n)
+    cols = _random(topo, n_snap, 2, rng, 100)
+    for rank in (0, n - 1):
+        mine, others = np.flatnonzero(cols["rank"] == rank), np.flatnonzero(cols["rank"] == n // 2)
+        _both(topo, {k: np.insert(v, n, v[mine[0]]) for k, v in cols.items()}, n_snap, 2, ("more", rank))
+        moved = {k: v.copy() for k, v in cols.items()}
+        for v in moved.values():
+            v[others[0]] = v[mine[-1]]
+        _both(topo, moved, n_snap, 2, ("moved", rank))
+        _both(topo, {k: np.delete(v, mine[1]) for k, v in cols.items()}, n_snap, 2, ("fewer", rank))
+
+
 @pytest.mark.parametrize("n", [64, 255, 257, 4096, 4097])
 def test_hops_along_rings(n):
     topo, rng = ring_topology(n), np.random.default_rng(n)
