@@ -576,3 +576,13 @@ def test_tiles_of_many_short_collectives_beside_longer_ones():
     cols = {k: v[perm] for k, v in cols.items()}
     g, o = run_both(topo, cols, what="short-and-long", lag_floor_ns=1000, tbase_init_ns=1000)
     assert g.n_seg > 24 * 130 and g.n_flag > 0
+
+
+@pytest.mark.parametrize("n", [262_143, 262_144, 262_145, 262_401, 327_681, 333_333])
+def test_batches_around_a_workgroup_per_compute_unit(n):
+    """one more record than 256 workgroups of 256 threads take, slices of 1,280 and 1,536 records by workgroups of 1,024 threads,
+    whole and with a last one that is partly or wholly empty"""
+    tr = tg.generate(tg.config3(n_cycles=190, layout=tg.Layout3D(tp=6, pp=5, dp=6))).shuffled(2)
+    cols = {k: v[:n] for k, v in tr.cols.items()}
+    assert cols["rank"].size == n
+    run_both(tr.topo, cols, what=n)
