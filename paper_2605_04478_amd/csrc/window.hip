@@ -221,29 +221,41 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
 // on consecutive pieces: every bucket's share of the round leaves as one contiguous run instead of one scattered store
 // per lane.  LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS: with records in random order that
 // lookup is a gather with no locality, cheaper from LDS than from the L2.
-// At most INGEST_STAGED_BUCKETS buckets.  Bound by the lines that are written in parts at the ends of the runs: 82M records into
-// 68 buckets, 65 bytes each, 1,214 us (4.4 TB/s; 1,471 us with an arrival number per record), 190 us more with streaming stores
-// everywhere and 230 more without any.
-template <int THREADS, bool LDS_TABLE>
+//
+// Bound by memory: a line that a round leaves unfinished would be completed by the next one 7 us later, when it has left the
+// L2 in parts.  So rows leave eight slots at a time (LINES: a line of rows, half a line of keys), with the streaming
+// hint; up to seven of a bucket wait in registers for the next round.  82M records into 68 buckets: 1,125 us (4.7 TB/s), 1,260 with
+// every round written as it is; four slots at a time 1,150.  Ranks' rows from the L2: 1,150 to 1,180.
+constexpr u32 INGEST_LINE = 8;
+// LDS words for a round: rows that waited and lines that are not filled come on top of the round's records
+__host__ __device__ constexpr u32 ingest_stage_rows(u32 n_buckets, bool lines) {
+  return INGEST_ROUND + (lines ? 2 * (INGEST_LINE - 1) * n_buckets : 0u);
+}
+template <int THREADS, bool LDS_TABLE, bool LINES>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
-  constexpr u32 CHUNK = THREADS * U;
+  constexpr u32 CHUNK = THREADS * U, LINE = LINES ? INGEST_LINE : 1;
+  constexpr u32 HELD = LINES ? INGEST_STAGED_BUCKETS * LINE / THREADS : 0;       // rows that wait in a thread
   static_assert(CHUNK == INGEST_ROUND, "a row has room for the record's number in its round");
-  // [n_ranks] membership rows (LDS_TABLE) | [CHUNK] rows | [CHUNK] keys | [n_comms][2] ranges | [CHUNK] window slots
+  static_assert(INGEST_STAGED_BUCKETS <= 256 && INGEST_STAGED_BUCKETS <= THREADS, "a byte and a thread per bucket");
+  // [n_ranks] membership rows (LDS_TABLE) | [ingest_stage_rows] rows | the same number of keys | [n_comms][2] ranges
   extern __shared__ uint4 s_dyn[];
   __shared__ u64 s_status[THREADS / CCLD_WAVE], s_max[THREADS / CCLD_WAVE], s_inv[THREADS / CCLD_WAVE];
-  __shared__ u32 s_off[INGEST_STAGED_BUCKETS], s_start[INGEST_STAGED_BUCKETS], s_pre[INGEST_STAGED_BUCKETS], s_total;
+  // per bucket: its next slot; and what turns a slot into a place in the staging order, the first slot not written yet, the
+  // first slot that this round leaves unwritten
+  __shared__ u32 s_off[INGEST_STAGED_BUCKETS], s_total;
+  __shared__ uint4 s_run[INGEST_STAGED_BUCKETS];
+  __shared__ uint8_t s_bucket[ingest_stage_rows(INGEST_STAGED_BUCKETS, LINES) / LINE];   // of every LINE staged rows
   __shared__ u32 s_scan[THREADS / CCLD_WAVE];
+  const u32 stage_rows = ingest_stage_rows(a.n_buckets, LINES);
   uint4* s_row = s_dyn + (LDS_TABLE ? T.n_ranks : 0u);
-  u64* s_key = reinterpret_cast<u64*>(s_row + CHUNK);
-  unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + CHUNK);
-  u32* s_p = reinterpret_cast<u32*>(s_rng + (a.range ? 2 * T.n_comms : 0u));
+  u64* s_key = reinterpret_cast<u64*>(s_row + stage_rows);
+  unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + stage_rows);
   const u32 tid = threadIdx.x;
+  // slots count from the window's first one: a.tail is the first of the batch
+  u32 from = 0, start = 0;              // of the thread's bucket: first slot not written yet, next slot at the start of the round
   if (a.table_words > INGEST_SCAN_WORDS) {
-    if (tid < a.n_buckets) {
-      const u32 o = a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
-      s_off[tid] = o; s_start[tid] = o;
-    }
+    if (tid < a.n_buckets) start = a.tail + a.bucket_base[tid] + a.table[((u64)tid * gridDim.x + blockIdx.x) * a.hist_split];
   } else {
     // the buckets' records, and those of the workgroups before this one: a wavefront per bucket.  (One workgroup that scanned
     // the table at the end of the counting took 20 of its 28 us at 2M records in 32 buckets.)
@@ -256,18 +268,19 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
         all += v; before += i < upto ? v : 0u;
       }
       before = wave_sum(before); all = wave_sum(all);
-      if (lane_id() == 0) { s_start[b] = before; s_pre[b] = all; }
+      if (lane_id() == 0) { s_run[b].x = before; s_run[b].y = all; }
     }
     __syncthreads();
     u32 total;
-    const u32 base = block_exclusive_sum<THREADS>(tid < a.n_buckets ? s_pre[tid] : 0u, s_scan, &total);
+    const u32 base = block_exclusive_sum<THREADS>(tid < a.n_buckets ? s_run[tid].y : 0u, s_scan, &total);
     if (tid < a.n_buckets) {
-      const u32 o = base + s_start[tid];
-      s_off[tid] = o; s_start[tid] = o;
+      start = a.tail + base + s_run[tid].x;
       if (blockIdx.x == 0) a.bucket_base[tid] = base;
     }
     if (blockIdx.x == 0 && tid == 0) a.bucket_base[a.n_buckets] = total;
   }
+  from = start;
+  if (tid < a.n_buckets) s_off[tid] = start;
   if (LDS_TABLE) {
     const uint4* __restrict__ g = reinterpret_cast<const uint4*>(T.rank_memb4);
     for (u32 r = tid; r < T.n_ranks; r += THREADS) s_dyn[r] = g[r];
@@ -308,6 +321,10 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
     }
   };
   u32* round_row = a.rounds + ((u64)a.round0 + (u64)blockIdx.x * a.per_group) * a.n_buckets + tid;      // used below n_buckets only
+  // rows that wait: of bucket i / LINE the one at place i % LINE of its line, i = tid, tid + THREADS, ...
+  uint4 h_row[HELD ? HELD : 1];
+  u64 h_key[HELD ? HELD : 1];
+  u32 held = 0;                          // a bit each
   load_round(i_begin, r, c, sq, op, nb, te, tx);
   wait_vector_memory();
   for (u64 base = i_begin; base < i_end; base += CHUNK) {        // uniform over the workgroup
@@ -334,64 +351,82 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       at[u] = atomicAdd(&s_off[bk[u]], 1u);
     }
     __syncthreads();
-    // this round's records per bucket -> where each bucket's run starts in the staging order
-    if (a.n_buckets <= CCLD_WAVE) {
-      if (tid < CCLD_WAVE) {
-        const u32 cnt = tid < a.n_buckets ? s_off[tid] - s_start[tid] : 0u;
+    // the staging order: every bucket's slots from the line on that holds its first one not written yet, in whole lines
+    {
+      const u32 to = tid < a.n_buckets ? s_off[tid] : 0u, first = from & ~(LINE - 1);
+      const u32 cnt = tid < a.n_buckets && to != from ? (to - first + LINE - 1) & ~(LINE - 1) : 0u;
+      u32 pre, all;
+      if (a.n_buckets <= CCLD_WAVE) {
         const u32 inc = wave_inclusive_sum(cnt);
-        s_pre[tid] = inc - cnt;
-        if (tid == CCLD_WAVE - 1) s_total = inc;
+        pre = inc - cnt; all = inc;
+        if (tid == CCLD_WAVE - 1) s_total = all;
+      } else {
+        pre = block_exclusive_sum<THREADS>(cnt, s_scan, &all);
+        if (tid == 0) s_total = all;
       }
-      __syncthreads();
-    } else {
-      const u32 cnt = tid < a.n_buckets ? s_off[tid] - s_start[tid] : 0u;
-      u32 tot;
-      const u32 ex = block_exclusive_sum<THREADS>(cnt, s_scan, &tot);
-      if (tid < a.n_buckets) s_pre[tid] = ex;
-      if (tid == 0) s_total = tot;
-      __syncthreads();
+      if (tid < a.n_buckets) {
+        // rows of lines that are not full wait, unless there is no next round
+        u32 upto = to;
+        if (LINES && base + CHUNK < i_end) { const u32 whole = to & ~(LINE - 1); upto = whole > from ? whole : from; }
+        s_run[tid] = make_uint4(pre - first, from, upto, 0u);
+        from = upto;
+        *round_row = start - a.tail;
+        start = to;
+      }
+      round_row += a.n_buckets;
     }
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (!on[u]) continue;
-      const u32 q = s_pre[bk[u]] + (at[u] - s_start[bk[u]]);
-      u64 p = (u64)a.tail + at[u];
-      if (p >= a.cap) p -= a.cap;
-      s_p[q] = (u32)p;
+      const u32 q = s_run[bk[u]].x + at[u];
+      s_bucket[q / LINE] = (uint8_t)bk[u];       // every line has a row that names its bucket
+      const u32 p = at[u] >= a.cap ? at[u] - a.cap : at[u];
       s_key[q] = key[u];
       uint4 row;
-      if (!pack_row(te[u], tx[u], nb[u], op[u], ref, (u32)p, &row)) {
-        a.win_wide[3 * p] = te[u]; a.win_wide[3 * p + 1] = tx[u]; a.win_wide[3 * p + 2] = (i64)nb[u];
+      if (!pack_row(te[u], tx[u], nb[u], op[u], ref, p, &row)) {
+        a.win_wide[3 * (u64)p] = te[u]; a.win_wide[3 * (u64)p + 1] = tx[u]; a.win_wide[3 * (u64)p + 2] = (i64)nb[u];
       }
       row.y |= ((u32)u * THREADS + tid) << ROW_CELL_SHIFT;
       s_row[q] = row;
     }
+#pragma unroll
+    for (u32 h = 0; h < HELD; ++h) {
+      const u32 i = tid + h * THREADS;
+      if (held >> h & 1) {
+        const u32 q = s_run[i / LINE].x + (s_run[i / LINE].y & ~(LINE - 1)) + i % LINE;
+        s_bucket[q / LINE] = (uint8_t)(i / LINE);
+        s_row[q] = h_row[h]; s_key[q] = h_key[h];
+      }
+    }
     __syncthreads();
     wait_vector_memory();              // the next round's columns; the stores below have the next round's time
     const u32 total = s_total;
-    // Pieces of a line that this round writes completely leave with the streaming hint: they do not stay in
-    // the L2, where they would displace the partially written lines at the buckets' frontiers before the
-    // next round completes them.
-    {
+    // Whole lines leave with the streaming hint: they do not stay in the L2
+    for (u32 q = tid; q < total; q += THREADS) {
       typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-      for (u32 q = tid; q < total; q += THREADS) {
-        const u32 D = s_p[q];
-        const u32 o = D & 7;
-        const bool full = q >= o && q + 7 - o < total && (s_p[q - o] == D - o) && (s_p[q + 7 - o] == D + 7 - o);
-        const uint4 v = s_row[q];
-        if (full) { u32x4 vv = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(out_row + D)); }
-        else out_row[D] = v;
-      }
-      for (u32 q = tid; q < total; q += THREADS) {
-        const u32 D = s_p[q];
-        const u32 o = D & 15;
-        const bool full = q >= o && q + 15 - o < total && (s_p[q - o] == D - o) && (s_p[q + 15 - o] == D + 15 - o);
-        if (full) __builtin_nontemporal_store(s_key[q], out_key + D);
-        else out_key[D] = s_key[q];
+      const uint4 run = s_run[s_bucket[q / LINE]];
+      const u32 v = q - run.x, lo = run.y, hi = run.z, D = v >= a.cap ? v - a.cap : v;
+      const bool full = (v & ~(INGEST_LINE - 1)) >= lo && (v | (INGEST_LINE - 1)) < hi;
+      if (v < lo || v >= hi) continue;
+      const uint4 row = s_row[q];
+      const u64 k = s_key[q];
+      if (full) {
+        u32x4 vv = {row.x, row.y, row.z, row.w};
+        __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(out_row + D));
+        __builtin_nontemporal_store(k, out_key + D);
+      } else {
+        out_row[D] = row; out_key[D] = k;
       }
     }
-    if (tid < a.n_buckets) { *round_row = s_start[tid]; s_start[tid] = s_off[tid]; }
-    round_row += a.n_buckets;
+    held = 0;
+#pragma unroll
+    for (u32 h = 0; h < HELD; ++h) {
+      const u32 i = tid + h * THREADS, b = i / LINE;
+      if (b >= a.n_buckets) continue;
+      const u32 to = s_off[b], v = (to & ~(LINE - 1)) + i % LINE;
+      if (v >= s_run[b].z && v < to) { const u32 q = s_run[b].x + v; h_row[h] = s_row[q]; h_key[h] = s_key[q]; held |= 1u << h; }
+    }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -400,7 +435,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   }
   // rounds that this workgroup did not need: they start where it ends
   for (u32 k = (u32)((i_end > i_begin ? i_end - i_begin + CHUNK - 1 : 0) / CHUNK); k < a.per_group; ++k, round_row += a.n_buckets)
-    if (tid < a.n_buckets) *round_row = s_start[tid];
+    if (tid < a.n_buckets) *round_row = start - a.tail;
   ingest_publish<THREADS>(status, maxseq, maxinv, s_status, s_max, s_inv, a, s_rng, T.n_comms);
 }
 // a batch without records: its header names its place in the window
@@ -422,9 +457,15 @@ IngestShape ingest_shape(uint64_t n) {
   s.per_group = (uint32_t)((s.chunk + INGEST_ROUND - 1) / INGEST_ROUND);
   return s;
 }
+constexpr size_t INGEST_LDS = 152 * 1024;      // beside the 8 KB of the static tables
+template <class F>
+static void each_ingest_staged(F f) {
+  f(&k_ingest_staged<1024, true, true>); f(&k_ingest_staged<1024, false, true>); f(&k_ingest_staged<1024, false, false>);
+}
 hipError_t allow_lds_window() {
-  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_ingest_staged<1024, true>), 156 * 1024);
-  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_ingest_staged<1024, false>), 156 * 1024);
+  hipError_t e = hipSuccess;
+  each_ingest_staged([&](auto k) { if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(k), INGEST_LDS); });
+  return e;
 }
 void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology& T, const KeyFormat& kf) {
   IngestArgs a = a_in;
@@ -456,12 +497,14 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
-  // the membership rows go to LDS when they fit beside the staging area
-  const size_t stage_bytes = (size_t)INGEST_ROUND * (16 + 8 + 4) + range_lds;
-  if (T.rank_memb4 && (u64)T.n_ranks * 16 + stage_bytes <= 156 * 1024)
-    hipLaunchKernelGGL((k_ingest_staged<1024, true>), dim3((u32)g), dim3(1024), stage_bytes + (size_t)T.n_ranks * 16, st, a, T, kf);
-  else
-    hipLaunchKernelGGL((k_ingest_staged<1024, false>), dim3((u32)g), dim3(1024), stage_bytes, st, a, T, kf);
+  // whole lines, and the membership rows in LDS, where they fit: with 68 buckets lines without the rows in LDS take 1,180 us in place of 1,155
+  // with both (82M records of 4,096 ranks), the rows without lines 1,285
+  const size_t table = T.rank_memb4 ? (size_t)T.n_ranks * 16 : 0;
+  auto lds = [&](bool lines, bool in_lds) { return (size_t)ingest_stage_rows(a.n_buckets, lines) * 24 + range_lds + (in_lds ? table : 0); };
+  auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3((u32)g), dim3(1024), bytes, st, a, T, kf); };
+  if (table && lds(true, true) <= INGEST_LDS) go(k_ingest_staged<1024, true, true>, lds(true, true));
+  else if (lds(true, false) <= INGEST_LDS) go(k_ingest_staged<1024, false, true>, lds(true, false));
+  else go(k_ingest_staged<1024, false, false>, lds(false, false));
 }
 
 // ------------------------------------------------------------------------------------------

@@ -112,6 +112,40 @@ def test_order_of_arrival_over_many_ingest_rounds(disjoint, step):
     an.close()
 
 
+@pytest.mark.parametrize("disjoint", [1, 0], ids=["lookup_in_lds", "many_comms_per_rank"])
+def test_rows_that_wait_for_a_whole_line(disjoint):
+    """buckets with none, a few and hundreds of records in a round of the ingest, several rounds per workgroup; batches that start in the middle
+    of a line, and a window whose last line is cut by its end"""
+    from paper_2605_04478_amd import ccld
+    n_comms, size = 40, 3
+    topo = tg.make_topology(size * (n_comms if disjoint else 1), [[r + size * c * disjoint for r in range(size)] for c in range(n_comms)])
+    rng = np.random.default_rng(disjoint)
+    share = 1.0 / (1 + np.arange(n_comms)) ** 3
+    an = ccld.Analyzer(topo, max_window_records=6_000_011, max_batch_records=2_600_000, window_batches=2)
+    prev, seq0 = None, np.full(n_comms, 7)
+    for n in (2_500_001, 1_800_003, 2_599_999, 1_700_002):
+        rounds = np.maximum(n / size * share / share.sum(), 1).astype(np.int64)
+        comm = np.repeat(np.arange(n_comms), rounds * size)
+        place = np.concatenate([np.arange(r * size) for r in rounds])
+        p = rng.permutation(comm.size)[:n - n % 2]
+        comm, seq, slot = comm[p], seq0[comm[p]] + place[p] // size, place[p] % size
+        te = T0 + seq * 1_000 + rng.integers(0, 500, p.size)
+        b = {"rank": (slot + size * comm * disjoint).astype(np.uint32), "comm": comm.astype(np.uint32), "seq": seq.astype(np.uint64),
+             "op": np.ones(p.size, np.uint8), "bytes": np.full(p.size, 1 << 20, np.uint64), "t_enter": te, "t_exit": te + rng.integers(1, 400, p.size)}
+        seq0 = seq0 + rounds
+        an.ingest(an.to_device(b))
+        win = b if prev is None else {k: np.concatenate([prev[k], b[k]]) for k in b}
+        res = an.analyze_window(FAR, n_records=len(win["rank"]), per_record=True)
+        order = np.lexsort((win["rank"], win["seq"], win["comm"]))
+        assert np.array_equal(res.per_record()["perm"], order)
+        seg = res.seg
+        first = seg["first"][:res.n_seg]
+        te, dur = win["t_enter"][order], (win["t_exit"] - win["t_enter"])[order]
+        assert np.array_equal(np.minimum.reduceat(te, first), seg["enter_min"]) and np.array_equal(np.maximum.reduceat(dur, first), seg["dur_max"])
+        prev = b
+    an.close()
+
+
 GAP_SIZES = [1, 2, 3, 31, 64, 65, 700, 2048]
 
 
