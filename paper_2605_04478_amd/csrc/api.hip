@@ -223,8 +223,9 @@ void plan(ccld_ctx* c, const ccld_params* p, const ccld_topology* t, uint64_t n_
   c->fine_cap = c->cell_cap / GRID_MIN_FILL + t->n_comms + 16;
   // Communicator buckets of the ingest.  A partition workgroup addresses GRID_SPAN fine buckets at a time, so a window that
   // may have more of them is placed by bucket, into as many buckets as leave about GRID_TARGET fine buckets in one:
-  // fewer in one lengthen the runs that the partition writes and shorten those that the ingest writes (82M records with 300 /
-  // 600 / 1,200 in one: a step of 3,943 / 3,890 / 3,963 us).  A window that cannot be placed on the grid
+  // fewer in one lengthen the runs that the partition writes, more leave the ingest room for the ranks' rows in LDS (82M records
+  // with 300 / 600 in one: ingest 1,184 / 1,122 us, partition 703 / 911; 20M: ingest 299 / 300, partition 164 / 190).  A window that
+  // cannot be placed on the grid
   // takes buckets whose rows (16 bytes per record) stay within about 100 MB, which the memory-side cache holds while the
   // statistics gather from one.
   int bb = 0;

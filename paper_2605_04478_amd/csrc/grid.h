@@ -16,7 +16,7 @@ constexpr uint32_t GRID_SPAN = 4096;         // fine buckets of one coarse bucke
 constexpr uint32_t GRID_ONE_BUCKET = 3500;   // windows of no more fine buckets are partitioned in one go, without communicator buckets
 constexpr uint32_t GRID_FINE_BOUND = 4096;   // most fine buckets that a launch is sized for without asking for their number
 constexpr uint32_t GRID_SELF_SUM = 512;      // where so many fine buckets are likely, each workgroup of the statistics sums the records before its own
-constexpr uint32_t GRID_TARGET = 600;        // fine buckets per communicator bucket of the others
+constexpr uint32_t GRID_TARGET = 300;        // fine buckets per communicator bucket of the others
 constexpr uint32_t GRID_MAX_COMMS = INGEST_RANGE_COMMS;
 constexpr uint32_t GRID_MAX_BATCHES = 256;   // batches of a window whose batches are placed by communicator bucket
 constexpr uint32_t GRID_MAX_PIECES = 4096;   // (coarse bucket, batch) pairs of such a window
@@ -31,6 +31,7 @@ struct __attribute__((aligned(16))) CommLayout {
   uint32_t seg_base;       // row of the collective table of the first round
   uint32_t cell_base;      // first cell
   uint32_t size;           // members
+  uint32_t div, shift;     // a round's fine bucket is its number * 2 * div >> (32 + shift) (partition)
 };
 
 // One fine bucket (written by the partition kernel).
@@ -42,6 +43,11 @@ struct __attribute__((aligned(16))) FineDesc {
   uint32_t pad;
   uint64_t seq0;           // operation counter of the first round
 };
+
+// Rows of a fine bucket: those from its first cell on, and those that end with its last one (in the upper half of the word).
+__host__ __device__ inline uint32_t fill_front(uint32_t fill) { return fill & 0xFFFFu; }
+__host__ __device__ inline uint32_t fill_back(uint32_t fill) { return fill >> 16; }
+__host__ __device__ inline uint32_t fill_rows(uint32_t fill) { return fill_front(fill) + fill_back(fill); }
 
 // device-side header of the layout
 struct GridHeader {
@@ -72,7 +78,7 @@ struct GridArgs {
   uint32_t* piece_at;            // [pieces + 1] records before each (coarse bucket, batch) piece, bucket by bucket
   uint32_t* piece_slot;          // [pieces] its first window slot
   // fine buckets
-  uint32_t* fill;                // [fine_cap + 1] records of each
+  uint32_t* fill;                // [fine_cap + 1] rows of each (fill_front, fill_back)
   uint32_t* rec0;                // [fine_cap + 1] records before each (from the statistics on, where these sum them)
   uint32_t* nflag;               // [fine_cap + 1] flagged records of each
   FineDesc* desc;                // [fine_cap]

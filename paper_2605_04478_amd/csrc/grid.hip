@@ -1,12 +1,20 @@
 // Grid placement for gfx950: the layout of the (communicator, operation counter, member slot) grid from the
 // window's counter ranges, and the partition pass that moves every payload row into the fine bucket of its cell.
 #include <algorithm>
+#include <type_traits>
 
 #include "grid.h"
 #include "rows.h"
 
 namespace ccld {
 
+// A division by n as a multiplication: x * 2^s / d = x / n for x < 2^31, with the smallest 2^s >= n and 2^(31 + s) / n rounded up
+// (below 2^32; its error of less than one adds less than 1 / n to the quotient).  The doubles round up as they should: the
+// quotient is whole or at least 1 / n away from a whole number.
+__device__ __forceinline__ void divide_by(u32 n, u32* div, u32* shift) {
+  *shift = n > 1 ? 32 - (u32)__clz((int)(n - 1)) : 0u;
+  *div = (u32)ceil(ldexp(1.0, 31 + (int)*shift) / (double)n);
+}
 // ---- layout ------------------------------------------------------------------------------------------
 // One workgroup: data errors of the batches; per communicator the rounds in the window, its fine buckets, cells and rows
 // of the collective table (exclusive scans over the communicators); the pieces of the window that hold each coarse
@@ -125,6 +133,7 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.rpb = GRID_B / size[k]; L.rounds = rounds[k]; L.size = size[k];
     L.fb_base = w.x + before[k].x; L.seg_base = w.y + before[k].y;
     L.cell_base = (u32)((u64)w.z + before[k].z + ((u64)(w.w + before[k].w) << 16));
+    divide_by(L.rpb, &L.div, &L.shift);
     d.lay[c] = L;
   }
   // more rounds than records means a round without any record: the sort handles such windows
@@ -133,7 +142,7 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   if (tid == 0) {
     CommLayout L;
     L.seq_min = 0; L.fb_base = (u32)(fb_carry > d.fine_cap ? d.fine_cap : fb_carry); L.rpb = 1; L.rounds = 0;
-    L.seg_base = (u32)seg_carry; L.cell_base = (u32)cell_carry; L.size = 1;
+    L.seg_base = (u32)seg_carry; L.cell_base = (u32)cell_carry; L.size = 1; L.div = 0; L.shift = 0;
     d.lay[d.n_comms] = L;
   }
   if (d.n_buckets == 1 && fb_total > GRID_SPAN) bad = true;
@@ -201,28 +210,270 @@ void launch_grid_layout(hipStream_t st, const GridArgs& d) {
 }
 
 // ---- partition --------------------------------------------------------------------------------------
-// A workgroup takes one slice of the window, bucket by bucket: PART_CHUNK records per round, each counted into its fine
-// bucket in LDS; the round's share of every fine bucket is reserved with one atomic, the rows are staged in LDS in
-// (bucket, rank) order and leave with consecutive lanes on consecutive 16-byte pieces.  Pieces of a line that the round
-// writes completely leave with the streaming hint, which keeps them from displacing the partially written lines at the
-// buckets' frontiers from the L2.  A bucket takes as many rows as it has cells; more can only be duplicate keys.
+// A workgroup takes one slice of the window, bucket by bucket: a few thousand records per round, each counted into its fine
+// bucket in LDS; rooms in the fine buckets are reserved, the rows are staged in LDS in (bucket, rank) order and leave with
+// consecutive lanes on consecutive 16-byte pieces.  A fine bucket takes as many rows as it has cells; more can only be duplicate keys.
 //
-// Bound by the lines that are written in pieces, so the runs are as long as LDS allows: rounds of 4,096 records and one
-// workgroup per compute unit (two of 2,048 records, which overlap their phases, took 4.10 instead of 3.89 ms for a
-// window of 82M records, two with 1,024 threads each 4.90).  Workgroups go to the eight XCDs in turn and every XCD has an L2
-// of its own: those of one XCD take neighbouring slices, so that a bucket's frontier lines are completed in one L2
-// instead of leaving several in parts (82M records 4.13 -> 3.89 ms, where a communicator bucket is four slices long).
+// Runs: a round's share of every fine bucket is reserved with one atomic and leaves as it is.  Pieces of a line that the round
+// writes completely leave with the streaming hint, which keeps them from displacing the partially written lines at the
+// buckets' frontiers from the L2.  Bound by memory and by the instructions and LDS traffic of a round, between which there are
+// barriers: the fields of a key are 32-bit words, the division is a multiplication, the next round's keys are asked for behind the
+// reservations (operations of vector memory are waited for in the order of their issue) and its rows when this round's are staged:
+// 20.5M records 205 -> 164 us (4.9 TB/s, buckets of half the communicators included), 5.1M 55.7 -> 52.1, 2M-record batches of
+// 16,384 ranks, ten in the window, 215 -> 185.
+//
+// Lines (part_lines): the largest windows have more lines on their way than the caches hold, and what a round left of one unwritten
+// leaves in parts before the next completes it.  There rooms are reserved eight rows at a time from the fine bucket's start, up to
+// seven rows of a fine bucket wait in registers for the next round, and what is left when the workgroup's share of the coarse
+// bucket ends goes to the fine bucket's end: 82M records 959 us before, 842 as runs, 703 so (4.7 TB/s).
+//
+// One workgroup per compute unit.  Workgroups go to the eight XCDs in turn and every XCD has an L2 of its own: those of one XCD
+// take neighbouring slices, so that the lines that several workgroups write are completed in one L2.
 constexpr u32 PART_THREADS = 1024, PART_U = 4, PART_CHUNK = PART_THREADS * PART_U;
 constexpr u32 PART_BLOCKS = 256, PART_XCDS = 8;
-constexpr u32 PART_LAY = 64;           // communicators of a bucket whose layout rows wait in LDS
+constexpr u32 PART_LAY = 256;          // communicators of a bucket whose layout waits in LDS
+constexpr u32 LINE_ROWS = 8;           // rows of a 128-byte line
+constexpr u32 LINES_U = 3, LINES_CHUNK = PART_THREADS * LINES_U;
+constexpr u32 LINES_SPAN = 384;        // most fine buckets of a coarse bucket whose rows leave in whole lines
+constexpr u32 LINES_STAGE = LINES_CHUNK + 2 * (LINE_ROWS - 1) * LINES_SPAN;     // and rows that waited, and lines that are not filled
+constexpr u32 LINES_MIN = 16 * LINES_CHUNK;      // fewest records of a workgroup in such a bucket: its rows that wait at the end are few beside them
+constexpr u32 LINES_SLICE = 64 * LINES_CHUNK;    // fewest records of a workgroup in such a window
+static_assert(LINES_SPAN <= PART_THREADS, "a thread per fine bucket");
+static_assert(GRID_B == 2048 && (u64)LINES_SPAN * GRID_B < 1u << 21, "a bucket's first cell and cells in a word");
 
-template <bool SLOTS>
+// The pieces of a coarse bucket, walked from front to back: the piece that held the first record of the last round asked for.
+struct PartCursor {
+  const u32 *at, *slot0;               // records of the window before each piece, its first slot
+  u32 piece, first, last, slot;
+  __device__ __forceinline__ PartCursor(const u32* at_, const u32* slot0_) : at(at_), slot0(slot0_), piece(0) { load(); }
+  __device__ __forceinline__ void load() { first = scalar(at[piece]); last = scalar(at[piece + 1]); slot = scalar(slot0[piece]); }
+  static __device__ __forceinline__ u32 scalar(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+};
+// slots and keys of a round, its rows: asked for without conditions, since the compiler waits for what is issued before
+// conditional loads with them
+template <u32 U>
+__device__ __forceinline__ void part_keys(const GridArgs& d, PartCursor& C, u32 base, u32 end, u32 (&src)[U], u64 (&key)[U]) {
+  base = std::min(base, end - 1);
+  while (base >= C.last) { ++C.piece; C.load(); }    // base < end <= the last entry of the table
+  if (std::min(base + U * PART_THREADS, end) <= C.last) {            // one piece holds the round
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) src[u] = C.slot + (std::min(base + u * PART_THREADS + threadIdx.x, end - 1) - C.first);
+  } else {
+    u32 k = C.piece;
+#pragma unroll
+    for (u32 u = 0; u < U; ++u) {
+      const u32 j = std::min(base + u * PART_THREADS + threadIdx.x, end - 1);
+      while (j >= C.at[k + 1]) ++k;
+      src[u] = C.slot0[k] + (j - C.at[k]);
+    }
+  }
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) { src[u] = src[u] >= d.cap ? src[u] - d.cap : src[u]; key[u] = __builtin_nontemporal_load(d.win_key + src[u]); }
+}
+typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+template <u32 U>
+__device__ __forceinline__ void part_rows(const GridArgs& d, const u32 (&src)[U], uint4 (&row)[U]) {
+#pragma unroll
+  for (u32 u = 0; u < U; ++u) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.win_row + src[u]));
+    row[u] = make_uint4(v.x, v.y, v.z, v.w);
+  }
+}
+// The fields of a key in 32-bit words: a round's number inside the window has fewer bits.
+struct PartKey {
+  u32 comm_shift, comm_mask, mb, seq_mask, slot_mask;
+  __device__ __forceinline__ PartKey(const KeyFormat& kf) {
+    comm_shift = kf.cb ? 32 - kf.cb : 0; comm_mask = kf.cb ? ~0u : 0u; mb = kf.mb;
+    seq_mask = kf.sb >= 32 ? ~0u : (1u << kf.sb) - 1;
+    slot_mask = (1u << kf.mb) - 1;
+  }
+  __device__ __forceinline__ u32 comm(u64 k) const { return (u32)(k >> 32) >> comm_shift & comm_mask; }
+  __device__ __forceinline__ u32 seq(u64 k) const { return (u32)(k >> mb) & seq_mask; }
+  __device__ __forceinline__ u32 slot(u64 k) const { return (u32)k & slot_mask; }
+};
+static_assert(GRID_MAX_COMMS <= 1u << 16 && GRID_B <= 1u << 16, "communicator and slot fields of fewer than 32 bits");
+// A communicator of a coarse bucket: the smallest counter's low word, its first fine bucket relative to the coarse bucket's, rounds
+// per fine bucket | members << 12 | shift << 24, and the multiplier that divides by the rounds per fine bucket.
+struct PartComm {
+  u32 seq, fb, rss, div;
+  __device__ __forceinline__ PartComm() = default;
+  __device__ __forceinline__ PartComm(const CommLayout& L, u32 f_lo)
+      : seq((u32)L.seq_min), fb(L.fb_base - f_lo), rss(L.rpb | (L.size << 12) | (L.shift << 24)), div(L.div) {}
+  __device__ __forceinline__ u32 rpb() const { return rss & 0xFFFu; }
+  __device__ __forceinline__ u32 size() const { return (rss >> 12) & 0xFFFu; }
+  __device__ __forceinline__ u32 bucket(u32 rel) const { return __umulhi(rel << 1, div) >> (rss >> 24); }
+};
+__device__ __forceinline__ uint4 part_row(const uint4& row, u32 cell) {
+  return make_uint4(row.x, (row.y & ~(ROW_CELL_MASK << ROW_CELL_SHIFT)) | (cell << ROW_CELL_SHIFT), row.z, row.w);
+}
+
+// The thread's number, not known to be the same every time: what follows from it is worked out again in every round.  Kept over the
+// rounds, a thread's places and addresses take thirty registers, and a kernel that spills needs scratch memory (1 us more to start).
+__device__ __forceinline__ u32 thread_here() { u32 t = threadIdx.x; asm("" : "+v"(t)); return t; }
+
+struct PartLines {
+  u32x4 row[LINES_STAGE];              // a round's rows by fine bucket, each bucket's from a whole line on
+  uint2 place[2][LINES_SPAN];          // of each fine bucket: place of its first new row; first place that stays | rows that stay << 16
+  uint2 leave[2][LINES_SPAN];          // what turns a place into a destination; first place that stays (0: nothing leaves)
+  u32 cnt[LINES_SPAN];                 // rows of the next round
+  u32 fine[LINES_SPAN];                // first cell relative to the coarse bucket's << 11 | cells - 1
+  uint16_t line[LINES_STAGE / LINE_ROWS];      // fine bucket of every line
+};
+// The records [pos, end) of a coarse bucket of `span` fine buckets from f_lo on, whose n_lay communicators (from c0 on) are in s_lay
+// and s_base (first cell, rounds).  Ends with a barrier.
+//
+// Vector memory operations are waited for in the order of their issue, so a round asks for its rooms first, then for rows two
+// rounds ahead, and stores last; the stores are as many in every round (those of places without a row lie outside the
+// buffer and are dropped), so that the wait for rows does not become one for everything.
+__device__ __forceinline__ void part_lines(const GridArgs& d, PartLines& S, const PartComm* s_lay, const uint2* s_base, u32 c0, u32 n_lay, const PartKey& pk,
+                                           const u32* s_at, const u32* s_slot0, u32* s_wave, u32 pos, u32 end, u32 f_lo, u32 span, u64& status) {
+  constexpr u32 HELD = LINES_SPAN * LINE_ROWS / PART_THREADS, OUT = (LINES_STAGE + PART_THREADS - 1) / PART_THREADS, OUT_MOST = 6;
+  static_assert(LINES_SPAN * LINE_ROWS % PART_THREADS == 0, "rows that wait: as many places in every thread");
+  const u32 tid = threadIdx.x;
+  const u32 cell_lo = s_base[0].x;
+  uint4 row0[LINES_U], row1[LINES_U];
+  u64 key0[LINES_U], key1[LINES_U];
+  u32 src0[LINES_U], src1[LINES_U];
+  // round r: rows in set r % 2; the keys of the round behind it in the other set; slots of a round where its keys were
+  PartCursor C(s_at, s_slot0);
+  part_keys(d, C, pos, end, src0, key0);
+  part_rows(d, src0, row0);
+  part_keys(d, C, pos + LINES_CHUNK, end, src1, key1);
+  part_rows(d, src1, row1);
+  u32 left = 0;                        // rows of the thread's fine bucket that wait
+  if (tid < span) {
+    u32 lo = 0, hi = n_lay;
+    while (lo < hi) { const u32 m = (lo + hi) >> 1; if (s_lay[m].fb <= tid) lo = m + 1; else hi = m; }
+    const PartComm L = s_lay[lo - 1];
+    const uint2 B = s_base[lo - 1];
+    const u32 r0 = (tid - L.fb) * L.rpb(), k = B.y - r0;
+    S.fine[tid] = (B.x + r0 * L.size() - cell_lo) << 11 | ((k < L.rpb() ? k : L.rpb()) * L.size() - 1);
+    S.cnt[tid] = 0;
+  }
+  __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(d.rows + cell_lo, 0, (int)(span * GRID_B * 16), 0x00027000);
+  u32 total = 0, held = 0;
+  u32x4 h_row[HELD];
+  u32 h_at[HELD];                      // place relative to the bucket's first new row
+  u32 fi_cell[LINES_U], at[LINES_U];
+  auto count = [&](u32 base, const u64 (&key)[LINES_U]) {
+#pragma unroll
+    for (u32 u = 0; u < LINES_U; ++u) {
+      fi_cell[u] = ~0u;
+      if (base + u * PART_THREADS + tid >= end) continue;
+      const PartComm L = s_lay[pk.comm(key[u]) - c0];
+      const u32 rel = pk.seq(key[u]) - L.seq, fr = L.bucket(rel), fi = L.fb + fr;
+      if (fi >= span) continue;
+      fi_cell[u] = fi | (__umul24(rel - __umul24(fr, L.rpb()), L.size()) + pk.slot(key[u])) << 16;
+      at[u] = atomicAdd(&S.cnt[fi], 1u);
+    }
+  };
+  // rooms for the lines that the counted rows make up, and their places
+  u32 t = 0, got = 0;                  // rows of the thread's bucket, and those of others that have a room
+  auto ask = [&] {
+    const u32 tid = thread_here();
+    t = left + (tid < span ? S.cnt[tid] : 0u);
+    const u32 out = t & ~(LINE_ROWS - 1);
+    if (out) got = atomicAdd(&d.fill[f_lo + tid], out);
+  };
+  auto places = [&](u32* all) { return block_exclusive_sum<PART_THREADS>((t + LINE_ROWS - 1) & ~(LINE_ROWS - 1), s_wave, all); };
+  auto settle = [&](u32 b, u32 pre) {
+    const u32 tid = thread_here();
+    if (tid >= span) return;
+    S.cnt[tid] = 0;
+    const u32 fine = S.fine[tid], out = t & ~(LINE_ROWS - 1), first = fine >> 11, cells = (fine & 2047u) + 1;
+    const bool dup = out && fill_front(got) + fill_back(got) + out > cells;
+    if (dup) status |= DS_DUPLICATE;
+    S.place[b][tid] = make_uint2(pre + left, (pre + out) | ((t - out) << 16));
+    S.leave[b][tid] = make_uint2(first + fill_front(got) - pre, dup ? 0u : pre + out);
+    left = t - out;
+  };
+  auto round = [&](u32 base, u32 b, uint4 (&row)[LINES_U], u64 (&key)[LINES_U], u32 (&src)[LINES_U], u32 (&src_key)[LINES_U]) {
+    const u32 tid = thread_here();
+#pragma unroll
+    for (u32 u = 0; u < LINES_U; ++u) {
+      if (fi_cell[u] == ~0u) continue;
+      const u32 fi = fi_cell[u] & 0xFFFFu, q = S.place[b][fi].x + at[u];
+      if (q % LINE_ROWS == 0) S.line[q / LINE_ROWS] = (uint16_t)fi;      // every line has a row at its first place
+      const uint4 v = part_row(row[u], (fi_cell[u] >> 16) & ROW_CELL_MASK);
+      S.row[q] = u32x4{v.x, v.y, v.z, v.w};
+    }
+#pragma unroll
+    for (u32 h = 0; h < HELD; ++h) {
+      const u32 fi = (tid + h * PART_THREADS) / LINE_ROWS;
+      if (held >> h & 1) { const u32 q = S.place[b][fi].x + h_at[h]; S.row[q] = h_row[h]; if (q % LINE_ROWS == 0) S.line[q / LINE_ROWS] = (uint16_t)fi; }
+    }
+    count(base + LINES_CHUNK, key);
+    __syncthreads();
+    const u32 here = total;
+    __builtin_amdgcn_sched_barrier(0);
+    ask();
+    part_rows(d, src, row);
+    part_keys(d, C, base + 3 * LINES_CHUNK, end, src_key, key);
+    held = 0;
+#pragma unroll
+    for (u32 h = 0; h < HELD; ++h) {
+      const u32 i = tid + h * PART_THREADS, fi = i / LINE_ROWS, k = i % LINE_ROWS;
+      const u32 stay = fi < span ? S.place[b][fi].y : 0u;
+      if (k < stay >> 16) { h_row[h] = S.row[(stay & 0xFFFFu) + k]; h_at[h] = k - (stay >> 16); held |= 1u << h; }
+    }
+    const u32 pre = places(&total);
+    __builtin_amdgcn_sched_barrier(0);
+    auto leave = [&](u32 i) {
+      const u32 q = std::min(tid + i * PART_THREADS, LINES_STAGE - 1);
+      const uint2 L = S.leave[b][q < here ? S.line[q / LINE_ROWS] : 0u];
+      // whole lines, with the streaming hint
+      __builtin_amdgcn_raw_buffer_store_b128(S.row[q], rsrc, q < here && q < L.y && tid + i * PART_THREADS < LINES_STAGE ? (int)((q + L.x) * 16) : -1, 0, 2);
+      if (i % 3 == 2) __builtin_amdgcn_sched_barrier(0);        // three rows in registers at a time
+    };
+#pragma unroll
+    for (u32 i = 0; i < OUT_MOST; ++i) leave(i);
+    if (here > OUT_MOST * PART_THREADS) {
+#pragma unroll
+      for (u32 i = OUT_MOST; i < OUT; ++i) leave(i);
+    }
+    settle(b ^ 1, pre);
+    __syncthreads();
+  };
+  __syncthreads();
+  count(pos, key0);
+  part_keys(d, C, pos + 2 * LINES_CHUNK, end, src0, key0);
+  __syncthreads();
+  ask();
+  settle(0, places(&total));
+  __syncthreads();
+  for (u32 base = pos; base < end; base += 2 * LINES_CHUNK) {
+    round(base, 0, row0, key1, src0, src1);
+    if (base + LINES_CHUNK < end) round(base + LINES_CHUNK, 1, row1, key0, src1, src0);
+  }
+  // what did not make up a line goes to the fine buckets' ends
+  if (tid < span) {
+    u32 start = ~0u;
+    if (left) {
+      const u32 old = atomicAdd(&d.fill[f_lo + tid], left << 16);
+      const u32 fine = S.fine[tid], first = fine >> 11, cells = (fine & 2047u) + 1;
+      if (fill_front(old) + fill_back(old) + left > cells) status |= DS_DUPLICATE;
+      else start = first + cells - fill_back(old);
+    }
+    S.cnt[tid] = start;
+  }
+  __syncthreads();
+#pragma unroll
+  for (u32 h = 0; h < HELD; ++h) {
+    if (!(held >> h & 1)) continue;
+    const u32 start = S.cnt[(tid + h * PART_THREADS) / LINE_ROWS];
+    if (start != ~0u) *reinterpret_cast<u32x4*>(d.rows + (cell_lo + start + h_at[h])) = h_row[h];        // (the place is negative)
+  }
+  __syncthreads();
+}
+
+template <bool SLOTS, bool LINES>
 __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   extern __shared__ uint4 s_row[];      // [PART_CHUNK] staged rows | [PART_CHUNK] destinations | 3 x [GRID_SPAN] tables | [PART_CHUNK] slots
   __shared__ u32 s_wave[PART_THREADS / CCLD_WAVE];
   __shared__ u32 s_at[GRID_MAX_BATCHES + 1], s_slot0[GRID_MAX_BATCHES];
-  __shared__ u32 s_total, s_b0, s_last;
-  __shared__ CommLayout s_lay[PART_LAY];
+  __shared__ u32 s_total, s_last;
+  __shared__ PartComm s_lay[PART_LAY];
+  __shared__ uint2 s_base[PART_LAY];    // first cell, rounds
   const u32 tid = threadIdx.x;
   if (d.hdr->feasible == 0) return;
   u32* s_dst = reinterpret_cast<u32*>(s_row + PART_CHUNK);
@@ -253,8 +504,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
     d.nflag[f] = 0;
   }
   for (u32 i = blockIdx.x * PART_THREADS + tid; i < d.n_blame; i += G * PART_THREADS) d.blame[i] = 0;
-  const u64 lo_mask = d.kf.cb > 0 ? (((u64)1 << (64 - d.kf.cb)) - 1) : ~0ull;
-  const u32 slot_mask = d.kf.mb < 32 ? (1u << d.kf.mb) - 1 : ~0u;
+  const PartKey pk(d.kf);
   const u32 per = ((d.n + G - 1) / G + CCLD_WAVE - 1) / CCLD_WAVE * CCLD_WAVE;
   // a permutation of the slices for grids of whole XCD rounds, which all windows of more than 256K records take
   const u32 slice = G % PART_XCDS == 0 ? (blockIdx.x % PART_XCDS) * (G / PART_XCDS) + blockIdx.x / PART_XCDS : blockIdx.x;
@@ -262,54 +512,45 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   const u32 lo = lo64 < d.n ? (u32)lo64 : d.n, hi = lo64 + per < d.n ? (u32)(lo64 + per) : d.n;
   u64 status = 0;
   const u32 nb = d.n_buckets == 1 ? 1u : d.nb;          // pieces of one coarse bucket
-  if (tid == 0 && lo < hi) {
-    u32 a = 0, b = d.n_buckets;                         // the coarse bucket that holds record lo
-    while (b - a > 1) { const u32 m = (a + b) >> 1; if (d.piece_at[(u64)m * nb] <= lo) a = m; else b = m; }
-    s_b0 = a;
-  }
-  for (u32 i = tid; i < 2 * GRID_SPAN; i += PART_THREADS) s_cnt[i] = 0;
+  // the coarse bucket that holds record lo: the last one that starts at or before it
+  static_assert(INGEST_STAGED_BUCKETS <= PART_THREADS, "a thread per coarse bucket");
+  const u32 b_lo = d.n_buckets == 1 ? 0u : (u32)__syncthreads_count(tid < d.n_buckets && d.piece_at[(u64)tid * nb] <= lo) - 1;
   __syncthreads();
-  u32 pos = lo, widest = 0;              // of the spans so far: entries behind a bucket's own may be another's
-  for (u32 b = lo < hi ? s_b0 : d.n_buckets; b < d.n_buckets && pos < hi; ++b) {
-    // the bucket's pieces, its records of this slice and its fine buckets
-    for (u32 i = tid; i <= nb; i += PART_THREADS) {
-      s_at[i] = d.piece_at[b * nb + i];
-      if (i < nb) s_slot0[i] = d.piece_slot[b * nb + i];
-    }
-    u64 c0 = (u64)b << d.bshift, c1 = (u64)(b + 1) << d.bshift;
-    if (c0 > d.n_comms) c0 = d.n_comms;
-    if (c1 > d.n_comms) c1 = d.n_comms;
+  u32 pos = lo;
+  for (u32 b = lo < hi ? b_lo : d.n_buckets; b < d.n_buckets && pos < hi; ++b) {
+    // the bucket's pieces, its records of this slice, its communicators and fine buckets, all on their way together
+    const u32 c0 = (u32)std::min<u64>((u64)b << d.bshift, d.n_comms), c1 = (u32)std::min<u64>((u64)(b + 1) << d.bshift, d.n_comms);
     const bool near = c1 - c0 <= PART_LAY;
-    if (near && tid < c1 - c0) s_lay[tid] = d.lay[c0 + tid];
+    static_assert(GRID_MAX_BATCHES < PART_THREADS && PART_LAY <= PART_THREADS, "a thread per piece and per communicator");
+    u32 at = 0, slot = 0;
+    CommLayout L;
+    if (tid <= nb) at = d.piece_at[b * nb + tid];
+    if (tid < nb) slot = d.piece_slot[b * nb + tid];
+    if (near && tid < c1 - c0) L = d.lay[c0 + tid];
+    const u32 f_lo = d.lay[c0].fb_base, span = d.lay[c1].fb_base - f_lo;
+    if (tid <= nb) s_at[tid] = at;
+    if (tid < nb) s_slot0[tid] = slot;
+    if (near && tid < c1 - c0) { s_lay[tid] = PartComm(L, f_lo); s_base[tid] = make_uint2(L.cell_base, L.rounds); }
     __syncthreads();
     const u32 end = s_at[nb] < hi ? s_at[nb] : hi;
-    const u32 f_lo = d.lay[c0].fb_base, span = d.lay[c1].fb_base - f_lo;
-    widest = span > widest ? span : widest;
-    // the next round's keys and rows are on their way while a round is staged and written
+    if (end <= pos) { __syncthreads(); continue; }         // no record of the bucket in the slice
+    if constexpr (LINES) if (near && span <= LINES_SPAN && end - pos >= LINES_MIN) {
+      part_lines(d, *reinterpret_cast<PartLines*>(s_row), s_lay, s_base, c0, c1 - c0, pk, s_at, s_slot0, s_wave, pos, end, f_lo, span, status);
+      pos = end;
+      continue;
+    }
+    for (u32 i = tid; i < span; i += PART_THREADS) s_cnt[i] = 0;
+    PartCursor C(s_at, s_slot0);
     u64 key[PART_U], nkey[PART_U];
-    uint4 row[PART_U], nrow[PART_U];
+    uint4 row[PART_U];
     u32 src[PART_U], nsrc[PART_U];
-    u32 piece = 0;
-    auto load_round = [&](u32 base, u64 (&K)[PART_U], uint4 (&R)[PART_U], u32 (&S)[PART_U]) {
-#pragma unroll
-      for (u32 u = 0; u < PART_U; ++u) {
-        const u32 j = base + u * PART_THREADS + tid;
-        K[u] = 0; S[u] = 0;
-        if (j < end) {
-          while (j >= s_at[piece + 1]) ++piece;          // j < end <= s_at[nb]: ends within the table
-          u32 p = s_slot0[piece] + (j - s_at[piece]);
-          if (p >= d.cap) p -= d.cap;
-          S[u] = p;
-          K[u] = __builtin_nontemporal_load(d.win_key + p);
-          typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-          const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.win_row + p));
-          R[u] = make_uint4(v.x, v.y, v.z, v.w);
-        }
-      }
-    };
-    load_round(pos, key, row, src);
+    part_keys(d, C, pos, end, src, key);
+    part_rows(d, src, row);
     wait_vector_memory();        // so that no register of the loop below is waited for behind the loads inside it
-    for (u32 base = pos; base < end; base += PART_CHUNK) {
+    __syncthreads();
+    // MORE: another round follows
+    auto round = [&](auto MORE, u32 base) {
+      const u32 tid = thread_here();
       // (packed: at 128 registers per thread the kernel spills with a word for each)
       u32 fi_cell[PART_U], at_room[PART_U], first[PART_U];       // fi | cell << 16, at | room << 16
       bool on[PART_U];
@@ -318,24 +559,25 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         on[u] = base + u * PART_THREADS + tid < end;
         if (!on[u]) continue;
         const u64 k = key[u];
-        const u32 comm = d.kf.cb ? (u32)(k >> (64 - d.kf.cb)) : 0u;
-        CommLayout L;
+        PartComm L;
+        uint2 B;                       // first cell, rounds
         if (near) {
-          L = s_lay[comm - (u32)c0];
+          L = s_lay[pk.comm(k) - c0]; B = s_base[pk.comm(k) - c0];
         } else {
-          L = d.lay[comm];
+          const CommLayout G = d.lay[pk.comm(k)];
           wait_vector_memory();        // nothing of this branch is waited for behind it
+          L = PartComm(G, f_lo); B = make_uint2(G.cell_base, G.rounds);
         }
-        const u32 rel = (u32)(((k & lo_mask) >> d.kf.mb) - L.seq_min);
-        const u32 fr = rel / L.rpb, rr = rel - fr * L.rpb, left = L.rounds - fr * L.rpb;
-        const u32 fi = L.fb_base + fr - f_lo, room = (left < L.rpb ? left : L.rpb) * L.size;
-        first[u] = L.cell_base + fr * L.rpb * L.size;
+        const u32 rel = pk.seq(k) - L.seq, fr = L.bucket(rel), r0 = fr * L.rpb(), left = B.y - r0;
+        const u32 fi = L.fb + fr, room = (left < L.rpb() ? left : L.rpb()) * L.size();
+        first[u] = B.x + r0 * L.size();
         on[u] = fi < span;
-        fi_cell[u] = fi | ((rr * L.size + ((u32)k & slot_mask)) << 16);
+        fi_cell[u] = fi | (((rel - r0) * L.size() + pk.slot(k)) << 16);
         if (on[u]) at_room[u] = atomicAdd(&s_cnt[fi], 1u) | (room << 16);
       }
       __syncthreads();
-      {     // one reservation per bucket, all on their way at once, and meanwhile the exclusive scan of the round's counts
+      {     // one reservation per bucket, all on their way at once, behind them the next rows, and meanwhile the exclusive scan of
+            // the round's counts
         constexpr u32 PER = GRID_SPAN / PART_THREADS;
         u32 v[PER], got[PER], sum = 0;
 #pragma unroll
@@ -344,6 +586,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
           got[i] = 0;
           if (c) got[i] = atomicAdd(&d.fill[f_lo + q], c);
         }
+        if constexpr (MORE) part_keys(d, C, base + PART_CHUNK, end, nsrc, nkey);
 #pragma unroll
         for (u32 i = 0; i < PER; ++i) { const u32 q = PER * tid + i; v[i] = q < span ? s_cnt[q] : 0u; sum += v[i]; }
         u32 tot;
@@ -355,21 +598,29 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         if (tid == 0) s_total = tot;
       }
       __syncthreads();
-      // loads and returning atomics complete in order: asked for before the reservations, the next rows would be waited for
-      // with them
-      if (base + PART_CHUNK < end) load_round(base + PART_CHUNK, nkey, nrow, nsrc);
-      for (u32 i = tid; i < widest; i += PART_THREADS) s_next[i] = 0;
+      for (u32 i = tid; i < span; i += PART_THREADS) s_next[i] = 0;
 #pragma unroll
       for (u32 u = 0; u < PART_U; ++u) {
         if (!on[u]) continue;
         const u32 fi = fi_cell[u] & 0xFFFFu, at = at_room[u] & 0xFFFFu, room = at_room[u] >> 16;
-        const u32 q = s_cnt[fi] + at, w = s_start[fi] + at;
+        const u32 q = s_cnt[fi] + at, w = fill_front(s_start[fi]) + at;
         if (w >= room) status |= DS_DUPLICATE;
         s_dst[q] = w < room ? first[u] + w : ~0u;
-        s_row[q] = make_uint4(row[u].x, (row[u].y & ~(ROW_CELL_MASK << ROW_CELL_SHIFT)) | (fi_cell[u] & (ROW_CELL_MASK << ROW_CELL_SHIFT)), row[u].z, row[u].w);
+        s_row[q] = part_row(row[u], (fi_cell[u] >> 16) & ROW_CELL_MASK);
         if (SLOTS) s_src[q] = src[u];
       }
+      // the next round's rows take the place of this one's; its keys are here (4: the loads behind theirs)
+      if constexpr (MORE) {
+#pragma unroll
+        for (u32 u = 0; u < PART_U; ++u) src[u] = nsrc[u];
+        part_rows(d, src, row);
+        __builtin_amdgcn_s_waitcnt(0x0F74);
+#pragma unroll
+        for (u32 u = 0; u < PART_U; ++u) key[u] = nkey[u];
+      }
       __syncthreads();
+      // Pieces of a line that the round writes completely leave with the streaming hint, which keeps them from displacing the
+      // partially written lines at the buckets' frontiers from the L2.
       const u32 total = s_total;
       for (u32 i = tid; i < total; i += PART_THREADS) {
         const u32 D = s_dst[i];
@@ -377,7 +628,6 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
         const u32 o = D & 7;
         const bool full = i >= o && i + 7 - o < total && s_dst[i - o] == D - o && s_dst[i + 7 - o] == D + 7 - o;
         const uint4 v = s_row[i];
-        typedef u32 u32x4 __attribute__((ext_vector_type(4)));
         u32x4 vv = {v.x, v.y, v.z, v.w};
         if (full) __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(d.rows + D));
         else d.rows[D] = v;
@@ -385,9 +635,10 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
       }
       // no barrier here: the staging area is written again behind two barriers of the next round
       u32* const t = s_cnt; s_cnt = s_next; s_next = t;
-#pragma unroll
-      for (u32 u = 0; u < PART_U; ++u) { key[u] = nkey[u]; row[u] = nrow[u]; src[u] = nsrc[u]; }
-    }
+    };
+    u32 base = pos;
+    for (; base + PART_CHUNK < end; base += PART_CHUNK) round(std::true_type{}, base);
+    round(std::false_type{}, base);
     pos = end;
     __syncthreads();        // the piece table is rewritten for the next bucket
   }
@@ -401,7 +652,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   for (u32 base = 0; base < n_fine; base += PART_THREADS * 4) {
     u32 v[4], sum = 0;
 #pragma unroll
-    for (u32 i = 0; i < 4; ++i) { const u32 f = base + tid * 4 + i; v[i] = f < n_fine ? load_agent(&d.fill[f]) : 0u; sum += v[i]; }
+    for (u32 i = 0; i < 4; ++i) { const u32 f = base + tid * 4 + i; v[i] = f < n_fine ? fill_rows(load_agent(&d.fill[f])) : 0u; sum += v[i]; }
     u32 tot;
     u32 ex = carry + block_exclusive_sum<PART_THREADS>(sum, s_wave, &tot);
 #pragma unroll
@@ -415,15 +666,19 @@ static_assert(GRID_MAX_COMMS * 4 <= PART_CHUNK * 16, "the first buckets fit the 
 static_assert(ROW_CELL_SHIFT == 16 && ROW_CELL_MASK == GRID_B - 1, "the cell is packed as the row has it");
 
 constexpr size_t PART_LDS = (size_t)PART_CHUNK * 20 + (size_t)GRID_SPAN * 12, PART_LDS_SLOTS = PART_LDS + (size_t)PART_CHUNK * 4;
+constexpr size_t PART_LDS_LINES = std::max(PART_LDS, sizeof(PartLines));
 hipError_t allow_lds_grid() {
-  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_grid_partition<false>), PART_LDS);
-  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_grid_partition<true>), PART_LDS_SLOTS);
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_grid_partition<false, false>), PART_LDS);
+  if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void*>(&k_grid_partition<true, false>), PART_LDS_SLOTS);
+  return e != hipSuccess ? e : allow_lds(reinterpret_cast<const void*>(&k_grid_partition<false, true>), PART_LDS_LINES);
 }
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   // small windows: a thousand records per workgroup, so that there are several of them
   const u32 g = std::min<u32>(PART_BLOCKS, std::max<u32>((d.n + PART_THREADS - 1) / PART_THREADS, 1));
-  if (d.slots) hipLaunchKernelGGL(k_grid_partition<true>, dim3(g), dim3(PART_THREADS), PART_LDS_SLOTS, st, d);
-  else hipLaunchKernelGGL(k_grid_partition<false>, dim3(g), dim3(PART_THREADS), PART_LDS, st, d);
+  if (d.slots) hipLaunchKernelGGL((k_grid_partition<true, false>), dim3(g), dim3(PART_THREADS), PART_LDS_SLOTS, st, d);
+  // 33M, 41M, 57M and 82M records: 270, 367, 500 and 844 us as runs, 304, 378, 489 and 704 in whole lines
+  else if (d.n / PART_BLOCKS < LINES_SLICE) hipLaunchKernelGGL((k_grid_partition<false, false>), dim3(g), dim3(PART_THREADS), PART_LDS, st, d);
+  else hipLaunchKernelGGL((k_grid_partition<false, true>), dim3(g), dim3(PART_THREADS), PART_LDS_LINES, st, d);
 }
 
 // ---- rounds without any record ------------------------------------------------------------------------
@@ -441,18 +696,19 @@ __global__ __launch_bounds__(GAP_THREADS) void k_grid_gaps(GridArgs d) {
   u32* const mark = s_round[wave];
   for (u32 f = blockIdx.x * NW + wave; f < n_fine; f += gridDim.x * NW) {
     const FineDesc D = d.desc[f];
-    const u32 cells = D.K * D.size, cnt = d.fill[f];
-    if (cnt + D.size > cells) continue;
+    const u32 cells = D.K * D.size, fill = d.fill[f], front = fill_front(fill), back = cells - fill_back(fill);
+    if (fill_rows(fill) + D.size > cells) continue;
     if (lane < WORDS) mark[lane] = 0;
     __builtin_amdgcn_wave_barrier();
-    for (u32 i0 = lane; i0 < cnt; i0 += U * CCLD_WAVE) {
+    auto on = [&](u32 i) { return i < front || (i >= back && i < cells); };
+    for (u32 i0 = lane; i0 < cells; i0 += U * CCLD_WAVE) {
       u32 y[U];
 #pragma unroll
-      for (u32 u = 0; u < U; ++u) y[u] = i0 + u * CCLD_WAVE < cnt ? d.rows[D.cell0 + i0 + u * CCLD_WAVE].y : ~0u;
+      for (u32 u = 0; u < U; ++u) y[u] = on(i0 + u * CCLD_WAVE) ? d.rows[D.cell0 + i0 + u * CCLD_WAVE].y : ~0u;
 #pragma unroll
       for (u32 u = 0; u < U; ++u) {
         const u32 cell = (y[u] >> ROW_CELL_SHIFT) & ROW_CELL_MASK, round = cell / D.size;
-        if (i0 + u * CCLD_WAVE < cnt && round < D.K) atomicOr(&mark[round >> 5], 1u << (round & 31));
+        if (on(i0 + u * CCLD_WAVE) && round < D.K) atomicOr(&mark[round >> 5], 1u << (round & 31));
       }
     }
     __builtin_amdgcn_wave_barrier();

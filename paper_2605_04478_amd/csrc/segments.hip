@@ -1231,7 +1231,7 @@ struct RecordsBefore {
     u32 v = 0;
     if (!scanned) {
 #pragma unroll 2
-      for (u32 i = threadIdx.x; i < f; i += THREADS) v += d.fill[i];
+      for (u32 i = threadIdx.x; i < f; i += THREADS) v += fill_rows(d.fill[i]);
     } else if (threadIdx.x == 0) {
       v = d.rec0[f];
     }
@@ -1248,17 +1248,18 @@ struct RecordsBefore<false> { __device__ __forceinline__ void add(u32*) const {}
 // Places bucket f's rows in LDS.  Returns status bits: a cell taken twice or more rows than cells (duplicate keys), a
 // round without any record (a hole in the grid).  Ends with a barrier.
 template <int THREADS, u32 ROUNDS, bool SELF_SUM>
-__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 cnt, const RecordsBefore<SELF_SUM>& before, GridShared<ROUNDS>& S) {
+__device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, u32 fill, const RecordsBefore<SELF_SUM>& before, GridShared<ROUNDS>& S) {
   constexpr u32 U = GRID_B / THREADS;
   const u32 tid = threadIdx.x, cells = D.K * D.size;
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
   u32x4 v[U];
+  const u32 cnt = fill_rows(fill), front = fill_front(fill), back = cells - fill_back(fill);
   bool dup = cnt > cells;
-  if (dup) cnt = cells;
+  auto holds = [&](u32 i) { return i < cells && (i < front || i >= back || dup); };
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
     const u32 i = tid + u * THREADS;
-    if (i < cnt) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.rows + D.cell0 + i));
+    if (holds(i)) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.rows + D.cell0 + i));
   }
   for (u32 i = tid; i < GRID_B / 32; i += THREADS) { S.pres[i] = 0; S.flags.bits[i] = 0; }
   if (tid == 0) { S.flags.n = 0; S.rec0 = 0; }
@@ -1267,7 +1268,7 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
     const u32 i = tid + u * THREADS;
-    if (i >= cnt) continue;
+    if (!holds(i)) continue;
     const u32 cell = (v[u].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK;
     if (cell >= cells) { dup = true; continue; }
     const u32 bit = 1u << (cell & 31);
@@ -1285,7 +1286,7 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
   // records per round and their exclusive scan; a bucket with as many rows as cells has a record in every cell, unless one
   // was taken twice, which fails the analysis
   bool gap = false;
-  if (cnt == cells) {
+  if (cnt >= cells) {
     for (u32 k = tid; k < D.K; k += THREADS) S.pre[k] = (unsigned short)(k * D.size);
     __syncthreads();
     return dup ? (u64)DS_DUPLICATE : 0;
@@ -1533,17 +1534,17 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
   const FineDesc D = d.desc[f];
   if (D.size > (u32)SEG_WAVE_MAX) return;               // k_grid_long takes it
   const i64 wref = d.hdr->ref;
-  const u32 cnt = d.fill[f], size = D.size;
+  const u32 fill = d.fill[f], size = D.size;
   if (tid < CCLD_WAVE) s_slot[tid] = 0;
   u64 bad;
   u32 rec0;
   if constexpr (SELF_SUM) {
-    bad = grid_place<GRID_THREADS>(d, D, cnt, RecordsBefore<true>::load<GRID_THREADS>(d, f, false), S);
+    bad = grid_place<GRID_THREADS>(d, D, fill, RecordsBefore<true>::load<GRID_THREADS>(d, f, false), S);
     rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
     if (tid == 0) d.rec0[f] = rec0;
   } else {
     rec0 = d.rec0[f];
-    bad = grid_place<GRID_THREADS>(d, D, cnt, RecordsBefore<false>{}, S);
+    bad = grid_place<GRID_THREADS>(d, D, fill, RecordsBefore<false>{}, S);
   }
   u32 mine;
   if (size <= 2) mine = grid_batches<2>(a, d, D, rec0, wref, S, lane, wave, NW);
@@ -1909,11 +1910,11 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
   for (u32 ent = blockIdx.x; ent < n_long; ent += gridDim.x) {
     const u32 f = d.long_list[ent];
     const FineDesc D = d.desc[f];
-    const u32 cnt = d.fill[f], size = D.size, K = D.K;
+    const u32 fill = d.fill[f], size = D.size, K = D.K;
     if (size <= ABOVE || size > MEMBERS) continue;
     const RecordsBefore<true> before = RecordsBefore<true>::load<THREADS>(d, f, scanned);
     for (u32 i = tid; i < size; i += THREADS) s_slot[i] = 0;
-    const u64 bad = grid_place<THREADS>(d, D, cnt, before, S);
+    const u64 bad = grid_place<THREADS>(d, D, fill, before, S);
     const u32 rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
     if (tid == 0) d.rec0[f] = rec0;
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);

@@ -146,6 +146,66 @@ def test_rows_that_wait_for_a_whole_line(disjoint):
     an.close()
 
 
+def _large(sizes, rounds, drop, seed):
+    """device columns of rounds[c] collectives of every communicator c in a random order, most of the first `drop` left out, and what follows
+    from them per collective in table order: records, earliest arrival, longest duration"""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    i64 = dict(dtype=torch.int64, device="cuda")
+    size, first = torch.tensor(sizes, **i64), torch.tensor(np.concatenate([[0], np.cumsum(sizes)[:-1]]), **i64)
+    rounds = torch.tensor(rounds, **i64)
+    comm = torch.repeat_interleave(torch.arange(len(sizes), **i64), rounds * size)
+    place = torch.arange(comm.numel(), **i64) - torch.repeat_interleave(torch.cumsum(rounds * size, 0) - rounds * size, rounds * size)
+    row = torch.repeat_interleave(torch.cumsum(rounds, 0) - rounds, rounds * size) + place // size[comm]
+    keep = torch.randperm(comm.numel(), generator=gen, device="cuda")
+    keep = keep[(keep >= drop) | (place[keep] % size[comm[keep]] == 0)]        # (the first member of every collective stays)
+    comm, place, row = comm[keep], place[keep], row[keep]
+    te = T0 + row * 1000 + torch.randint(0, 500, row.shape, generator=gen, device="cuda")
+    dur = torch.randint(1, 400, row.shape, generator=gen, device="cuda")
+    n_seg = int(rounds.sum())
+    want = (torch.bincount(row, minlength=n_seg), torch.full((n_seg,), 2**62, **i64).scatter_reduce_(0, row, te, "amin"),
+            torch.zeros(n_seg, **i64).scatter_reduce_(0, row, dur, "amax"))
+    cols = {"rank": (first[comm] + place % size[comm]).int(), "comm": comm.int(), "seq": 5 + place // size[comm],
+            "op": torch.ones(comm.numel(), dtype=torch.uint8, device="cuda"), "bytes": torch.full((comm.numel(),), 64, **i64), "t_enter": te, "t_exit": te + dur}
+    return cols, want
+
+
+# 192 communicators, 24 to a coarse bucket: such of 2,048 cells per fine bucket and of fewer, one of 1,500 fine buckets (too many for
+# whole lines) beside others
+@pytest.mark.parametrize("mix", ["even", "odd", "skewed"])
+def test_largest_windows_leave_in_whole_lines(mix):
+    from paper_2605_04478_amd import ccld
+    n, n_comms = 51_000_000, 192
+    sizes = {"even": [8] * n_comms, "odd": [3 + (5 * c) % 62 for c in range(n_comms)], "skewed": [64] * n_comms}[mix]
+    share = np.ones(n_comms) if mix != "skewed" else 1.0 / (1 + np.arange(n_comms) % 24) ** 2
+    rounds = np.maximum(n * share / share.sum() / sizes, 1).astype(int) + np.arange(n_comms) % 3
+    cols, want = _large(sizes, rounds, 0 if mix == "even" else 1001, len(mix))
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    topo = tg.make_topology(int(off[-1]), [list(range(off[c], off[c + 1])) for c in range(n_comms)])
+    n = cols["comm"].numel()
+    assert n // 256 >= 64 * 3072
+    an = ccld.Analyzer(topo, max_window_records=n)
+    bufs = an.alloc_window_result(n, seg_cap=int(rounds.sum()), flag_cap=1024, group_cap=1 << 18)
+    for again in range(2):
+        an.reset_window()
+        an.ingest(cols)
+        res = an.analyze_window(FAR, buffers=bufs)
+        assert res.n_seg == rounds.sum() and res.status in ("OK", "TRUNCATED", "W_TRUNCATED")
+        seg = res.dev["seg"].view(21, -1)
+        for name, w in zip(("n", "enter_min", "dur_max"), want):
+            assert bool((seg[ccld.SEG_COLS.index(name)] == w).all()), (mix, again, name)
+    # a record twice; one a hundred thousand times, more than a fine bucket's counts of rows can tell
+    for copies in (2, 100_000):
+        bad = {k: v.clone() for k, v in cols.items()}
+        at = slice(1000, 1000 + copies)
+        for k in bad:
+            bad[k][at] = bad[k][999]
+        an.reset_window()
+        an.ingest(bad)
+        assert an.analyze_window(FAR, buffers=bufs).status == "E_DUPLICATE_KEY"
+    an.close()
+
+
 GAP_SIZES = [1, 2, 3, 31, 64, 65, 700, 2048]
 
 
