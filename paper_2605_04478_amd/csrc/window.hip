@@ -56,26 +56,27 @@ __device__ __forceinline__ void put_header(const IngestArgs& a, i64 ref) {
 // Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Tables
 // of no more words than this are scanned by every placement workgroup for itself, larger ones by two launches.
 constexpr u32 INGEST_SCAN_WORDS = 8192;
-__global__ __launch_bounds__(256) void k_ingest_hist(IngestArgs a, u32 n_comms) {
+template <u32 THREADS>
+__global__ __launch_bounds__(THREADS) void k_ingest_hist(IngestArgs a, u32 n_comms) {
   extern __shared__ u32 s_cnt[];        // [n_buckets]
-  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) s_cnt[b] = 0;
+  for (u32 b = threadIdx.x; b < a.n_buckets; b += THREADS) s_cnt[b] = 0;
   __syncthreads();
   const u64 chunk = a.chunk / a.hist_split;
   const u64 i_end = (chunk * (blockIdx.x + 1)) < a.n ? chunk * (blockIdx.x + 1) : a.n;
   const u32* __restrict__ in_comm = a.comm;
-  for (u64 i0 = chunk * blockIdx.x + threadIdx.x; i0 < i_end; i0 += 256 * 8) {
+  for (u64 i0 = chunk * blockIdx.x + threadIdx.x; i0 < i_end; i0 += THREADS * 8) {
     u32 c[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const bool on = i0 + (u64)u * 256 < i_end;
-      c[u] = on ? __builtin_nontemporal_load(in_comm + i0 + (u64)u * 256) : 0xFFFFFFFFu;
+      const bool on = i0 + (u64)u * THREADS < i_end;
+      c[u] = on ? __builtin_nontemporal_load(in_comm + i0 + (u64)u * THREADS) : 0xFFFFFFFFu;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (i0 + (u64)u * 256 < i_end) atomicAdd(&s_cnt[c[u] < n_comms ? (c[u] >> a.bshift) : 0u], 1u);
+      if (i0 + (u64)u * THREADS < i_end) atomicAdd(&s_cnt[c[u] < n_comms ? (c[u] >> a.bshift) : 0u], 1u);
   }
   __syncthreads();
-  for (u32 b = threadIdx.x; b < a.n_buckets; b += 256) a.table[(u64)b * gridDim.x + blockIdx.x] = s_cnt[b];
+  for (u32 b = threadIdx.x; b < a.n_buckets; b += THREADS) a.table[(u64)b * gridDim.x + blockIdx.x] = s_cnt[b];
 }
 // exclusive scan of every bucket's row of per-workgroup counts (row length <= 2048)
 __global__ __launch_bounds__(256) void k_ingest_scan(u32* table, u32* totals, u32 n_blocks) {
@@ -492,7 +493,10 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
   a.hist_split = shape.hist_split; a.chunk = shape.chunk; a.per_group = shape.per_group;
   const u32 g_hist = (u32)(g * a.hist_split);
   a.table_words = a.n_buckets * g_hist;
-  hipLaunchKernelGGL(k_ingest_hist, dim3(g_hist), dim3(256), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
+  // (one counting workgroup to a placement workgroup: of 1,024 threads, so that the compute units have as much on their way as with
+  // four of 256)
+  if (a.hist_split == 1) hipLaunchKernelGGL(k_ingest_hist<1024>, dim3(g_hist), dim3(1024), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
+  else hipLaunchKernelGGL(k_ingest_hist<256>, dim3(g_hist), dim3(256), sizeof(u32) * a.n_buckets, st, a, T.n_comms);
   if (a.table_words > INGEST_SCAN_WORDS) {
     hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
