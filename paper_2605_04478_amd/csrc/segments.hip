@@ -1530,11 +1530,13 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
   __shared__ u32 s_slot[CCLD_WAVE];
   constexpr u32 NW = GRID_THREADS / CCLD_WAVE;
   const u32 f = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
-  if (d.hdr->feasible == 0 || f >= d.hdr->n_fine) return;
+  // the header and what it may turn out that there is not (every table has an entry for every workgroup) in one trip to memory
+  const GridHeader H = *d.hdr;
   const FineDesc D = d.desc[f];
-  if (D.size > (u32)SEG_WAVE_MAX) return;               // k_grid_long takes it
-  const i64 wref = d.hdr->ref;
-  const u32 fill = d.fill[f], size = D.size;
+  const u32 fill = d.fill[f], size = D.size, scanned = SELF_SUM ? 0u : d.rec0[f];
+  if (H.feasible == 0 || f >= H.n_fine) return;
+  if (size > (u32)SEG_WAVE_MAX) return;                 // k_grid_long takes it
+  const i64 wref = H.ref;
   if (tid < CCLD_WAVE) s_slot[tid] = 0;
   u64 bad;
   u32 rec0;
@@ -1543,7 +1545,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
     rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
     if (tid == 0) d.rec0[f] = rec0;
   } else {
-    rec0 = d.rec0[f];
+    rec0 = scanned;
     bad = grid_place<GRID_THREADS>(d, D, fill, RecordsBefore<false>{}, S);
   }
   u32 mine;
