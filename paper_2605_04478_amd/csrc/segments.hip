@@ -5,6 +5,8 @@
 // of 65 to 512 records take a wavefront each with 2, 4 or 8 values per lane in registers, those of
 // up to 16,384 records a workgroup each with a bitonic sort in LDS (k_seg_team, k_seg_large), and longer ones
 // the counting selection of k_seg_big.  Windows on the grid placement (grid.h) have kernels of their own at the end.
+#include <type_traits>
+
 #include "window_kernels.h"
 #include "grid.h"
 #include "rows.h"
@@ -1217,6 +1219,7 @@ struct GridShared {
   u32 pres[GRID_B / 32];
   unsigned short pre[ROUNDS];            // records of the bucket before each of its rounds
   u32 wave[1024 / CCLD_WAVE], rec0;      // rec0: records of the window before the bucket
+  u32 odd;                               // operations in flight, rows of full width or two rows of a cell among them
   GridFlags flags;
 };
 // Records before fine bucket f.  The scan of the counts at the end of the partition is a chain of its own, and its workgroups
@@ -1262,19 +1265,23 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
     if (holds(i)) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(d.rows + D.cell0 + i));
   }
   for (u32 i = tid; i < GRID_B / 32; i += THREADS) { S.pres[i] = 0; S.flags.bits[i] = 0; }
-  if (tid == 0) { S.flags.n = 0; S.rec0 = 0; }
+  if (tid == 0) { S.flags.n = 0; S.rec0 = 0; S.odd = 0; }
   __syncthreads();
   before.add(&S.rec0);
+  u32 most = 0;
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
     const u32 i = tid + u * THREADS;
     if (!holds(i)) continue;
+    most = v[u].z > most ? v[u].z : most;
     const u32 cell = (v[u].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK;
     if (cell >= cells) { dup = true; continue; }
     const u32 bit = 1u << (cell & 31);
     if (atomicOr(&S.pres[cell >> 5], bit) & bit) { dup = true; continue; }
     S.row[cell] = make_uint4(v[u].x, (v[u].y & ~(ROW_CELL_MASK << ROW_CELL_SHIFT)) | (i << ROW_CELL_SHIFT), v[u].z, v[u].w);
   }
+  static_assert(ROW_INFLIGHT > ROW_WIDE, "the two largest words");
+  if (most >= ROW_WIDE || dup) S.odd = 1;
   __syncthreads();
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
@@ -1411,13 +1418,23 @@ __device__ __forceinline__ u32 first_bit(u64 m) { return (u32)__builtin_ctzll(m)
 
 // Bound by the vector instructions of this loop, so every lane does only what its own record needs: 252 instead of 388 per 64
 // records over the whole kernel, 82M records in 8.4M collectives 1,053 -> 822 us (3.0 GB: 3.7 TB/s).
-template <int G>
+// The kernel's first argument, read again where it is used: what few passes need would be kept in scalar registers over all of them,
+// which are too few, and every spill and reload of one is a vector instruction.  (Not where there are FEW buckets, whose passes would
+// wait for it.)  With FULL: 82M records 809 -> 778 us, 5.1M 73.1 -> 68.5, ten batches of 2M 167 -> 160.
+__device__ __forceinline__ const SegArgs& args_again() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));
+  return *(const SegArgs*)p;
+}
+// FULL: every cell of the bucket has a record, of a finished operation (a pass of eight lanes to a collective is 160 instructions then
+// instead of 190).
+template <int G, bool FULL, bool FEW>
 __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d, const FineDesc& D, u32 rec0, i64 wref,
                                             GridShared<GRID_B>& S, u32 lane, u32 wave, u32 n_waves) {
   constexpr int SPW = CCLD_WAVE / G;
   constexpr u32 LIM = 1u << 30;
   const u32 K = D.K, size = D.size;
-  const bool stage = size >= 4, per_record = a.rec_flag || a.lag_e || a.lag_x;
+  const bool stage = size >= 4, per_record = a.rec_flag || a.lag_e || a.lag_x || a.perm;
   const i32 floor32 = a.lag_floor > 0x7FFFFFFF ? 0x7FFFFFFF : a.lag_floor < -0x7FFFFFFF ? -0x7FFFFFFF : (i32)a.lag_floor;
   const u32 q = lane / G, l = lane % G, gbase = q * G;
   const u32 rank = l < size ? a.members_sorted[a.member_off[D.comm] + l] : 0u;
@@ -1426,23 +1443,23 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
     const u32 k = b * SPW + q;
     const bool in = k < K && l < size;
     const u32 cell = in ? k * size + l : 0u;
-    const bool valid = in && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
-    const auto pm = group_bits<G>(ballot64(valid), gbase);
-    const u32 n = count_bits(pm), fl = pm ? first_bit(pm) : 0u;
+    const bool valid = FULL ? in : in && ((S.pres[cell >> 5] >> (cell & 31)) & 1u);
+    const auto pm = group_bits<G>(FULL ? 0ull : ballot64(valid), gbase);
+    const u32 n = FULL ? size : count_bits(pm), fl = !FULL && pm ? first_bit(pm) : 0u;
     const uint4 v = S.row[cell];
-    const uint4 lead = S.row[pm ? k * size + fl : 0u];                // one address per group: a broadcast
+    const uint4 lead = S.row[(FULL ? k < K : pm != 0) ? k * size + fl : 0u];                // one address per group: a broadcast
     __builtin_amdgcn_wave_barrier();                                  // read before the row is staged over it
     mine += valid ? 1u : 0u;
     // arrival relative to the first record's: the 44 bits of the times sit at the bottom of x and y
     const u64 diff = (((u64)v.y << 32) | v.x) - (((u64)lead.y << 32) | lead.x);
     const i32 er = (i32)(u32)diff, xr = (i32)((u32)er + v.z);
-    const bool infl = valid && v.z == ROW_INFLIGHT, done = valid && v.z != ROW_INFLIGHT;
+    const bool infl = !FULL && valid && v.z == ROW_INFLIGHT, done = FULL ? valid : valid && v.z != ROW_INFLIGHT;
     // (a first record of full width shows in its own lane)
     const bool wide = (valid && ((((u32)(diff >> 32) ^ (u32)(er >> 31)) & 0xFFFu) != 0 || (u32)er + LIM >= 2 * LIM)) ||
                       (done && (v.z >= LIM || xr >= (i32)LIM));
     const u32 first = rec0 + (k < K ? S.pre[k] : 0u);
-    const auto j_of = [&] { return first + (G == 64 ? mbcnt64((u64)pm) : count_bits((u32)pm & ((1u << l) - 1u))); };
-    if (a.perm && valid) a.perm[j_of()] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+    const auto j_of = [&] { return first + (FULL ? l : G == 64 ? mbcnt64((u64)pm) : count_bits((u32)pm & ((1u << l) - 1u))); };
+    if (per_record && a.perm && valid) a.perm[j_of()] = grid_arrival(a, d, D.cell0 + ((v.y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
     const StageRow at(k, size);
     if (ballot64(wide) != 0) {
       DenseLane L;
@@ -1451,11 +1468,11 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
       L.n = n; L.first = first; L.j = j_of(); L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k;
       L.stage = nullptr; L.staged = false; L.cell = cell; L.rec0 = rec0; L.flags = &S.flags;
       const u64 gmask = (G == 64 ? ~0ull : (((u64)1 << (G & 63)) - 1)) << gbase;
-      dense_pass64<G, PUT_GRID>(a, L, size, lane, gbase, gmask);
+      dense_pass64<G, PUT_GRID>(FEW ? a : args_again(), L, size, lane, gbase, gmask);
       if (stage && valid && l == fl) *at.word(S.row, 15) = ROW_NOT_STAGED;
       continue;
     }
-    const u32 nd = count_bits(group_bits<G>(ballot64(done), gbase)), ninfl = n - nd;
+    const u32 nd = FULL ? size : count_bits(group_bits<G>(ballot64(done), gbase)), ninfl = n - nd;
     const u32 kl = nd ? nd - 1 : 0, km = kl / 2;
     const i32 se = sort_groups32<G>(done ? er : REL_NONE, lane);
     const i32 sx = sort_groups32<G>(done ? xr : REL_NONE, lane);
@@ -1470,7 +1487,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
     const u32 dmin = reduce_u32<G, false>(done ? v.z : ~0u), dmax = reduce_u32<G, true>(done ? v.z : 0u);
     const auto mmin = group_bits<G>(ballot64(done && v.z == dmin), gbase), mmax = group_bits<G>(ballot64(done && v.z == dmax), gbase);
     const bool incons = group_bits<G>(ballot64(valid && (v.w != lead.w || ((v.y ^ lead.y) & ROW_SAME_MASK))), gbase) != 0;
-    if (stage && ninfl == 0 && n) {
+    if (stage && ninfl == 0 && (FULL ? k < K : n != 0)) {
       // every lane writes the words it holds
       if (l == 0) {
         *at.word(S.row, 0) = lead.x; *at.word(S.row, 1) = lead.y; *at.word(S.row, 2) = (u32)se; *at.word(S.row, 6) = (u32)sx;
@@ -1505,7 +1522,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
       if (valid && l == fl && (!stage || ninfl)) {
         DenseLane L;
         L.n = n; L.first = first; L.srow = D.srow0 + k; L.comm = D.comm; L.seq = D.seq0 + k; L.staged = false;
-        dense_put_row<PUT_GRID>(a, L, ninfl, complete, incons, barrier, usable, hop, hb, ninfl ? ref + imin : T_INFLIGHT, nd,
+        dense_put_row<PUT_GRID>(FEW ? a : args_again(), L, ninfl, complete, incons, barrier, usable, hop, hb, ninfl ? ref + imin : T_INFLIGHT, nd,
                                 ref + min_e, ref + med_e, ref + max_e, (i64)mad_e, ref + min_x, ref + med_x, ref + max_x,
                                 (i64)mad_x, (i64)dmin, (i64)dmax, rmin, rmax);
         if (stage) *at.word(S.row, 15) = ROW_NOT_STAGED;
@@ -1513,13 +1530,14 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
     }
     u32 f = 0;
     const i32 mad_e = lane_read(sde, gbase + km), mad_x = lane_read(sdx, gbase + km);
+    const SegArgs& A = FEW ? a : args_again();
     if (usable) {
-      if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
-      if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
+      if (is_late32(le, A.lag_floor, A.kmad_num, A.kmad_den, mad_e)) f |= CCLD_FLAG_LATE_ENTER;
+      if (is_late32(lx, A.lag_floor, A.kmad_num, A.kmad_den, mad_x)) f |= CCLD_FLAG_LATE_EXIT;
     } else {
       le = 0; lx = 0;
     }
-    if (valid) grid_put_record(a, per_record ? j_of() : 0u, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
+    if (valid) grid_put_record(A, per_record ? j_of() : 0u, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
   }
   return mine;
 }
@@ -1549,12 +1567,23 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs
     bad = grid_place<GRID_THREADS>(d, D, fill, RecordsBefore<false>{}, S);
   }
   u32 mine;
-  if (size <= 2) mine = grid_batches<2>(a, d, D, rec0, wref, S, lane, wave, NW);
-  else if (size <= 4) mine = grid_batches<4>(a, d, D, rec0, wref, S, lane, wave, NW);
-  else if (size <= 8) mine = grid_batches<8>(a, d, D, rec0, wref, S, lane, wave, NW);
-  else if (size <= 16) mine = grid_batches<16>(a, d, D, rec0, wref, S, lane, wave, NW);
-  else if (size <= 32) mine = grid_batches<32>(a, d, D, rec0, wref, S, lane, wave, NW);
-  else mine = grid_batches<64>(a, d, D, rec0, wref, S, lane, wave, NW);
+  constexpr bool FEW = GRID_THREADS == 1024;
+  auto batches = [&](auto FULL) {
+    if (size <= 2) mine = grid_batches<2, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+    else if (size <= 4) mine = grid_batches<4, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+    else if (size <= 8) mine = grid_batches<8, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+    else if (size <= 16) mine = grid_batches<16, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+    else if (size <= 32) mine = grid_batches<32, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+    else mine = grid_batches<64, FULL, FEW>(a, d, D, rec0, wref, S, lane, wave, NW);
+  };
+  // (not where a workgroup has sixteen wavefronts and there are few of them: what counts there are the instructions that are fetched
+  // for the first time, 8 buckets 11.7 -> 13.2 us)
+  bool full = false;
+  if constexpr (!FEW) {
+    full = fill_rows(fill) == D.K * size && (u32)__builtin_amdgcn_readfirstlane((int)S.odd) == 0;
+    if (full) batches(std::true_type{});
+  }
+  if (!full) batches(std::false_type{});
   // the lane's member slot is the same in every pass
   u32 G = 2; while (G < size) G <<= 1;
   if (mine) atomicAdd(&s_slot[lane % G], mine);
