@@ -1800,6 +1800,17 @@ __device__ __forceinline__ bool long_wave32(const SegArgs& a, const GridArgs& d,
               (usable ? CCLD_SEG_USABLE : 0);
   }
   const bool per_record = a.rec_flag || a.lag_e || a.lag_x || a.perm;
+  // a lag within the floor is never late: most collectives end here (with rare arguments read where they are used, ten batches of 2M
+  // records with collectives of 128 members 99 -> 91 us, 1.1M records with collectives of 390 members 30.4 -> 28.8)
+  const i32 floor32 = a.lag_floor > 0x7FFFFFFF ? 0x7FFFFFFF : a.lag_floor < -0x7FFFFFFF ? -0x7FFFFFFF : (i32)a.lag_floor;
+  bool above = false;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const i32 le = (i32)((u32)er[r] - (u32)st[0][1]), lx = (i32)((u32)er[r] + z[r] - (u32)st[1][1]);
+    above |= ((pm[r] >> lane) & 1u) && (le > floor32 || lx > floor32);
+  }
+  if (!per_record && !(usable && ballot64(above))) return true;
+  const SegArgs& A = args_again();
   u32 before = rec0 + S.pre[k];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
@@ -1808,13 +1819,13 @@ __device__ __forceinline__ bool long_wave32(const SegArgs& a, const GridArgs& d,
     u32 f = 0;
     if (usable) {
       le = er[r] - st[0][1]; lx = (i32)((u32)er[r] + z[r]) - st[1][1];
-      if (is_late32(le, a.lag_floor, a.kmad_num, a.kmad_den, st[0][3])) f |= CCLD_FLAG_LATE_ENTER;
-      if (is_late32(lx, a.lag_floor, a.kmad_num, a.kmad_den, st[1][3])) f |= CCLD_FLAG_LATE_EXIT;
+      if (is_late32(le, A.lag_floor, A.kmad_num, A.kmad_den, st[0][3])) f |= CCLD_FLAG_LATE_ENTER;
+      if (is_late32(lx, A.lag_floor, A.kmad_num, A.kmad_den, st[1][3])) f |= CCLD_FLAG_LATE_EXIT;
     }
     if (valid && (f || per_record)) {
       const u32 cell = k * size + r * CCLD_WAVE + lane, j = before + mbcnt64(pm[r]);
-      if (a.perm) a.perm[j] = grid_arrival(a, d, D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
-      grid_put_record(a, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
+      if (A.perm) A.perm[j] = grid_arrival(A, d, D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+      grid_put_record(A, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
     }
     before += (u32)__popcll(pm[r]);
   }
@@ -1909,7 +1920,7 @@ __device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d,
 #pragma unroll
   for (int r = 0; r < E; ++r) mine[r] = 0;
   for (u32 k = wave; k < D.K; k += n_waves)
-    if (!long_wave32<E>(a, d, D, rec0, wref, S, mine, out, k, lane)) long_wave<E>(a, d, D, rec0, wref, S, mine, out, k, lane);
+    if (!long_wave32<E>(a, d, D, rec0, wref, S, mine, out, k, lane)) long_wave<E>(args_again(), d, D, rec0, wref, S, mine, out, k, lane);
 #pragma unroll
   for (int r = 0; r < E; ++r) if (mine[r]) atomicAdd(&s_slot[r * CCLD_WAVE + lane], mine[r]);
 }
