@@ -843,12 +843,10 @@ __global__ __launch_bounds__(THREADS) void k_hang_comm(HangArgs a) {
 }
 
 // ---- victims, hops along the wait-for edges to a root, candidates per communicator, the tables and the roots -------
-// A not-entered rank that has entered another hung communicator is a victim: no candidate.
-__device__ __forceinline__ bool is_victim(const HangArgs& a, u32 c, u32 r) {
-  if (HCOMM(a, CCLD_HCOMM_CLASS, c) != CCLD_HANG_H1_NOT_ENTERED) return false;
+// A rank that has not entered communicator c and has entered another hung one is a victim: no candidate.  m: its packed memberships.
+__device__ __forceinline__ bool is_victim(const HangArgs& a, u32 c, u32 r, const uint4& m) {
   auto entered_hung = [&](u32 c2, u64 p2) { return (HCOMM(a, CCLD_HCOMM_HUNG, c2) != 0) & (PAIR(a, CCLD_HPAIR_ENTERED, p2) != 0); };
   if (a.T.rank_cell4) {                    // the rank's (at most four) memberships in one load, then all looked at side by side
-    const uint4 m = grid_row_lookup(a, r);
     const u32 w[4] = {m.x, m.y, m.z, m.w};
     bool hit = false;
 #pragma unroll
@@ -879,19 +877,29 @@ __global__ __launch_bounds__(256) void k_hang_final(HangArgs a) {
   __shared__ u32 s_last;
   const u64 p = (u64)blockIdx.x * 256 + threadIdx.x;
   const u32 tid = threadIdx.x, lane = lane_id();
-  if (hang_rows_ok(a)) {
+  // Few dependent trips to memory are what this takes, so everything that is known by the member's number alone is asked for at
+  // once, before it is known whether the rows are good, then what follows from its communicator and rank.
+  const u64 pm = p < a.n_members ? p : 0;
+  u32 c = a.T.member_comm[pm];
+  const u32 rank = a.T.members[pm];
+  const bool cand = a.cand[pm] != 0;
+  i64 row[CCLD_HPAIR_NCOL];
+#pragma unroll
+  for (int col = 0; col < CCLD_HPAIR_NCOL; ++col) row[col] = col == CCLD_HPAIR_RANK || col == CCLD_HPAIR_COMM ? 0 : PAIR(a, col, pm);
+  const bool ok = hang_rows_ok(a);
+  const i64 cls = HCOMM(a, CCLD_HCOMM_CLASS, c);
+  const bool tree = a.T.algo[c] == CCLD_ALGO_TREE;
+  const uint4 memb = a.T.rank_cell4 ? grid_row_lookup(a, rank) : make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (ok) {
     bool root = false;
-    u32 c = ~0u, rank = 0;
     if (p < a.n_members) {
-      c = a.T.member_comm[p];
-      rank = a.T.members[p];
       // only a communicator that not everyone has entered has victims, and it has no wait-for edges: no walk meets one
-      root = a.cand[p] && !is_victim(a, c, rank);
+      root = cand && !(cls == CCLD_HANG_H1_NOT_ENTERED && is_victim(a, c, rank, memb));
       i64 hops = -1;
       if (root) {
         hops = 0;
-      } else if (HCOMM(a, CCLD_HCOMM_CLASS, c) == CCLD_HANG_H3_HARDWARE && a.T.algo[c] != CCLD_ALGO_TREE) {
-        if (a.hops_known) hops = PAIR(a, CCLD_HPAIR_HOPS, p);
+      } else if (cls == CCLD_HANG_H3_HARDWARE && !tree) {
+        if (a.hops_known) hops = row[CCLD_HPAIR_HOPS];
         const u32 off = a.T.member_off[c], n = a.T.size[c];
         u32 cur = (u32)(p - off);
         i64 walked = 0;
@@ -904,9 +912,7 @@ __global__ __launch_bounds__(256) void k_hang_final(HangArgs a) {
         }
       }
       if (a.out_pair && p < a.pair_cap) {
-        const i64 row[CCLD_HPAIR_NCOL] = {(i64)rank, (i64)c, PAIR(a, CCLD_HPAIR_STALLED, p), PAIR(a, CCLD_HPAIR_ENTERED, p),
-                                          PAIR(a, CCLD_HPAIR_SEQ, p), PAIR(a, CCLD_HPAIR_SENT, p), PAIR(a, CCLD_HPAIR_RECV, p),
-                                          PAIR(a, CCLD_HPAIR_WAITS_ON, p), hops, PAIR(a, CCLD_HPAIR_ONSET, p)};
+        row[CCLD_HPAIR_RANK] = (i64)rank; row[CCLD_HPAIR_COMM] = (i64)c; row[CCLD_HPAIR_HOPS] = hops;
 #pragma unroll
         for (int col = 0; col < CCLD_HPAIR_NCOL; ++col) store_agent(&a.out_pair[(u64)col * a.pair_cap + p], row[col]);
       }
