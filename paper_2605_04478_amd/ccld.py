@@ -478,8 +478,9 @@ class Analyzer:
             fptr, rptr = buf.ctypes.data_as(C.c_void_p), fr.ctypes.data_as(C.c_void_p)
             keep = (buf, fr)
         cap = self._n_members * int(n_channels)
-        i32 = dict(dtype=t.int32, device=self.device)
-        out = {k: t.empty(cap, **i32) for k in ("snap", "rank", "comm", "channel", "chunks_sent", "chunks_recv")}
+        # one allocation for the six 32-bit columns (seven allocations took 9 of a call's 25 us)
+        cols = t.empty((6, cap), dtype=t.int32, device=self.device).unbind(0)
+        out = dict(zip(("snap", "rank", "comm", "channel", "chunks_sent", "chunks_recv"), cols))
         out["seq_posted"] = t.empty(cap, dtype=t.int64, device=self.device)
         f = _Frames(fptr, rptr, n, 1 if on_device else 0, int(n_channels), int(snapshot), 0)
         r = _SnapshotRows(*[out[k].data_ptr() for k in ("snap", "rank", "comm", "channel", "seq_posted",
