@@ -1257,8 +1257,9 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
   u32x4 v[U];
   const u32 cnt = fill_rows(fill), front = fill_front(fill), back = cells - fill_back(fill);
-  bool dup = cnt > cells;
-  auto holds = [&](u32 i) { return i < cells && (i < front || i >= back || dup); };
+  const bool over = cnt > cells;
+  bool dup = over;
+  auto holds = [&](u32 i) { return i < cells && (i < front || i >= back || over); };
 #pragma unroll
   for (u32 u = 0; u < U; ++u) {
     const u32 i = tid + u * THREADS;
