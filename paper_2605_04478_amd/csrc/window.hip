@@ -323,7 +323,9 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   };
   u32* round_row = a.rounds + ((u64)a.round0 + (u64)blockIdx.x * a.per_group) * a.n_buckets + tid;      // used below n_buckets only
   // rows that wait: of bucket i / LINE the one at place i % LINE of its line, i = tid, tid + THREADS, ...
-  uint4 h_row[HELD ? HELD : 1];
+  // (an array of uint4 would lie in scratch memory: 82M records 1,330 us in place of 1,251)
+  typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 h_row[HELD ? HELD : 1];
   u64 h_key[HELD ? HELD : 1];
   u32 held = 0;                          // a bit each
   load_round(i_begin, r, c, sq, op, nb, te, tx);
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       if (held >> h & 1) {
         const u32 q = s_run[i / LINE].x + (s_run[i / LINE].y & ~(LINE - 1)) + i % LINE;
         s_bucket[q / LINE] = (uint8_t)(i / LINE);
-        s_row[q] = h_row[h]; s_key[q] = h_key[h];
+        s_row[q] = make_uint4(h_row[h].x, h_row[h].y, h_row[h].z, h_row[h].w); s_key[q] = h_key[h];
       }
     }
     __syncthreads();
@@ -405,7 +407,6 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
     const u32 total = s_total;
     // Whole lines leave with the streaming hint: they do not stay in the L2
     for (u32 q = tid; q < total; q += THREADS) {
-      typedef u32 u32x4 __attribute__((ext_vector_type(4)));
       const uint4 run = s_run[s_bucket[q / LINE]];
       const u32 v = q - run.x, lo = run.y, hi = run.z, D = v >= a.cap ? v - a.cap : v;
       const bool full = (v & ~(INGEST_LINE - 1)) >= lo && (v | (INGEST_LINE - 1)) < hi;
@@ -426,7 +427,11 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       const u32 i = tid + h * THREADS, b = i / LINE;
       if (b >= a.n_buckets) continue;
       const u32 to = s_off[b], v = (to & ~(LINE - 1)) + i % LINE;
-      if (v >= s_run[b].z && v < to) { const u32 q = s_run[b].x + v; h_row[h] = s_row[q]; h_key[h] = s_key[q]; held |= 1u << h; }
+      if (v >= s_run[b].z && v < to) {
+        const u32 q = s_run[b].x + v;
+        const uint4 row = s_row[q];
+        h_row[h] = u32x4{row.x, row.y, row.z, row.w}; h_key[h] = s_key[q]; held |= 1u << h;
+      }
     }
     __syncthreads();
 #pragma unroll
@@ -502,7 +507,8 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
   // whole lines, and the membership rows in LDS, where they fit: with 68 buckets lines without the rows in LDS take 1,180 us in place of 1,155
-  // with both (82M records of 4,096 ranks), the rows without lines 1,285
+  // with both (82M records of 4,096 ranks), the rows without lines 1,285.  With 136 buckets both do not fit: lines 1,251 us, half
+  // lines (four slots) beside the rows 1,352.
   const size_t table = T.rank_memb4 ? (size_t)T.n_ranks * 16 : 0;
   auto lds = [&](bool lines, bool in_lds) { return (size_t)ingest_stage_rows(a.n_buckets, lines) * 24 + range_lds + (in_lds ? table : 0); };
   auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3((u32)g), dim3(1024), bytes, st, a, T, kf); };
