@@ -1427,6 +1427,13 @@ __device__ __forceinline__ const SegArgs& args_again() {
   asm("" : "+s"(p));
   return *(const SegArgs*)p;
 }
+// The second one.
+__device__ __forceinline__ const GridArgs& grid_again() {
+  constexpr size_t at = (sizeof(SegArgs) + alignof(GridArgs) - 1) / alignof(GridArgs) * alignof(GridArgs);
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));
+  return *(const GridArgs*)((const char*)p + at);
+}
 // FULL: every cell of the bucket has a record, of a finished operation (a pass of eight lanes to a collective is 160 instructions then
 // instead of 190).
 template <int G, bool FULL, bool FEW>
@@ -1825,7 +1832,7 @@ __device__ __forceinline__ bool long_wave32(const SegArgs& a, const GridArgs& d,
     }
     if (valid && (f || per_record)) {
       const u32 cell = k * size + r * CCLD_WAVE + lane, j = before + mbcnt64(pm[r]);
-      if (A.perm) A.perm[j] = grid_arrival(A, d, D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
+      if (A.perm) A.perm[j] = grid_arrival(A, grid_again(), D.cell0 + ((S.row[cell].y >> ROW_CELL_SHIFT) & ROW_CELL_MASK));
       grid_put_record(A, j, cell, rec0, &S.flags, f, (i64)le, (i64)lx);
     }
     before += (u32)__popcll(pm[r]);
@@ -1921,7 +1928,7 @@ __device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d,
 #pragma unroll
   for (int r = 0; r < E; ++r) mine[r] = 0;
   for (u32 k = wave; k < D.K; k += n_waves)
-    if (!long_wave32<E>(a, d, D, rec0, wref, S, mine, out, k, lane)) long_wave<E>(args_again(), d, D, rec0, wref, S, mine, out, k, lane);
+    if (!long_wave32<E>(a, d, D, rec0, wref, S, mine, out, k, lane)) long_wave<E>(args_again(), grid_again(), D, rec0, wref, S, mine, out, k, lane);
 #pragma unroll
   for (int r = 0; r < E; ++r) if (mine[r]) atomicAdd(&s_slot[r * CCLD_WAVE + lane], mine[r]);
 }
@@ -1945,7 +1952,7 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
   __shared__ TeamAcc s_acc;
   __shared__ u32 s_first;
   constexpr u32 NW = THREADS / CCLD_WAVE, U = GRID_B / THREADS;
-  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / CCLD_WAVE;
+  const u32 tid = threadIdx.x, wave = tid / CCLD_WAVE;
   if (d.hdr->feasible == 0) return;
   const u32 n_long = d.hdr->n_long;
   const bool scanned = !d.self_sum;
@@ -1961,6 +1968,11 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
     const u32 rec0 = (u32)__builtin_amdgcn_readfirstlane((int)S.rec0);
     if (tid == 0) d.rec0[f] = rec0;
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
+    // the lane's number, not known to be the same for every bucket: what the sorts make of it is not kept over the placing of the next
+    // rows, where it took 28 registers too many (with the arguments read again, ten batches of 2M records with collectives of 128
+    // members 84 -> 70 us, 1.1M records with collectives of 390 members 28.3 -> 27.5)
+    u32 lane = lane_id();
+    asm("" : "+v"(lane));
     if constexpr (WAVES) {
       long_rounds<E>(a, d, D, rec0, wref, S, s_slot, s_out, lane, wave, NW);
       __syncthreads();
@@ -2061,8 +2073,9 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
       }
     }
     __syncthreads();
-    if (tid == 0) d.nflag[f] = S.flags.n;
-    grid_order_flags<THREADS>(a, D, rec0, S.flags, S.wave, blame, n_ranks);
+    const SegArgs& A = args_again();
+    if (tid == 0) grid_again().nflag[f] = S.flags.n;
+    grid_order_flags<THREADS>(A, D, rec0, S.flags, S.wave, blame, n_ranks);
     // the table rows: a lane per round, a column at a time
     for (u32 col = wave; col < STAGE_COLS; col += NW) {
       const u32 k = lane;
@@ -2071,8 +2084,8 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
       const u32 srow = D.srow0 + k;
       const bool none = R.n == R.ninfl, usable = (R.state & CCLD_SEG_USABLE) != 0;
       const bool barrier = (R.state & CCLD_SEG_BARRIER) != 0;
-      if (col == (u32)CCLD_SEG_NCOL) { a.gcode[srow] = (uint16_t)seg_group_code(usable, R.op, R.bytes); continue; }
-      if (col == (u32)CCLD_SEG_NCOL + 1) { a.range_c[srow] = usable ? R.dmax - R.dmin : 0; seg_count_alert(a, srow, R.ninfl, barrier, R.imin); continue; }
+      if (col == (u32)CCLD_SEG_NCOL) { A.gcode[srow] = (uint16_t)seg_group_code(usable, R.op, R.bytes); continue; }
+      if (col == (u32)CCLD_SEG_NCOL + 1) { A.range_c[srow] = usable ? R.dmax - R.dmin : 0; seg_count_alert(A, srow, R.ninfl, barrier, R.imin); continue; }
       i64 v = 0;
       switch (col) {
         case CCLD_SEG_COMM: v = (i64)D.comm; break;
@@ -2090,11 +2103,11 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
         case CCLD_SEG_FIRST: v = (i64)(rec0 + S.pre[k]); break;
         default: v = none ? 0 : R.stat[(col - CCLD_SEG_ENTER_MIN) >> 2][(col - CCLD_SEG_ENTER_MIN) & 3]; break;
       }
-      seg_put(a, (int)col, srow, v);
+      seg_put(A, (int)col, srow, v);
     }
     unsigned long long* nrec = (unsigned long long*)(blame + (u64)CCLD_BLM_N_RECORDS * n_ranks);
     for (u32 i = tid; i < size; i += THREADS)
-      if (s_slot[i]) atomicAdd(&nrec[a.members_sorted[a.member_off[D.comm] + i]], (unsigned long long)s_slot[i]);
+      if (s_slot[i]) atomicAdd(&nrec[A.members_sorted[A.member_off[D.comm] + i]], (unsigned long long)s_slot[i]);
     __syncthreads();     // LDS is reused by the next bucket
   }
 }
