@@ -6,6 +6,7 @@
 // apart, rounds without any record, communicators larger than a fine bucket) are sorted instead.
 #pragma once
 #include "ccld_internal.h"
+#include "rooms.h"
 #include "window_kernels.h"
 
 namespace ccld {
@@ -44,11 +45,6 @@ struct __attribute__((aligned(16))) FineDesc {
   uint64_t seq0;           // operation counter of the first round
 };
 
-// Rows of a fine bucket: those from its first cell on, and those that end with its last one (in the upper half of the word).
-__host__ __device__ inline uint32_t fill_front(uint32_t fill) { return fill & 0xFFFFu; }
-__host__ __device__ inline uint32_t fill_back(uint32_t fill) { return fill >> 16; }
-__host__ __device__ inline uint32_t fill_rows(uint32_t fill) { return fill_front(fill) + fill_back(fill); }
-
 // device-side header of the layout
 struct GridHeader {
   uint32_t feasible, n_fine, n_seg, n_pieces;
@@ -78,7 +74,7 @@ struct GridArgs {
   uint32_t* piece_at;            // [pieces + 1] records before each (coarse bucket, batch) piece, bucket by bucket
   uint32_t* piece_slot;          // [pieces] its first window slot
   // fine buckets
-  uint32_t* fill;                // [fine_cap + 1] rows of each (fill_front, fill_back)
+  uint32_t* fill;                // [fine_cap + 1] rows of each (rooms.h)
   uint32_t* rec0;                // [fine_cap + 1] records before each (from the statistics on, where these sum them)
   uint32_t* nflag;               // [fine_cap + 1] flagged records of each
   FineDesc* desc;                // [fine_cap]

@@ -314,7 +314,7 @@ __device__ __forceinline__ u32 thread_here() { u32 t = threadIdx.x; asm("" : "+v
 struct PartLines {
   u32x4 row[LINES_STAGE];              // a round's rows by fine bucket, each bucket's from a whole line on
   uint2 place[2][LINES_SPAN];          // of each fine bucket: place of its first new row; first place that stays | rows that stay << 16
-  uint2 leave[2][LINES_SPAN];          // what turns a place into a destination; first place that stays (0: nothing leaves)
+  uint2 leave[2][LINES_SPAN];          // what turns a place into a destination; first place that does not leave
   u32 cnt[LINES_SPAN];                 // rows of the next round
   u32 fine[LINES_SPAN];                // first cell relative to the coarse bucket's << 11 | cells - 1
   uint16_t line[LINES_STAGE / LINE_ROWS];      // fine bucket of every line
@@ -381,10 +381,9 @@ __device__ __forceinline__ void part_lines(const GridArgs& d, PartLines& S, cons
     if (tid >= span) return;
     S.cnt[tid] = 0;
     const u32 fine = S.fine[tid], out = t & ~(LINE_ROWS - 1), first = fine >> 11, cells = (fine & 2047u) + 1;
-    const bool dup = out && fill_front(got) + fill_back(got) + out > cells;
-    if (dup) status |= DS_DUPLICATE;
+    if (out && fill_rows(got) + out > cells) status |= DS_DUPLICATE;
     S.place[b][tid] = make_uint2(pre + left, (pre + out) | ((t - out) << 16));
-    S.leave[b][tid] = make_uint2(first + fill_front(got) - pre, dup ? 0u : pre + out);
+    S.leave[b][tid] = make_uint2(first + fill_front(got) - pre, pre + front_room(got, out, cells));
     left = t - out;
   };
   auto round = [&](u32 base, u32 b, uint4 (&row)[LINES_U], u64 (&key)[LINES_U], u32 (&src)[LINES_U], u32 (&src_key)[LINES_U]) {
@@ -446,22 +445,20 @@ __device__ __forceinline__ void part_lines(const GridArgs& d, PartLines& S, cons
     if (base + LINES_CHUNK < end) round(base + LINES_CHUNK, 1, row1, key0, src1, src0);
   }
   // what did not make up a line goes to the fine buckets' ends
-  if (tid < span) {
-    u32 start = ~0u;
-    if (left) {
-      const u32 old = atomicAdd(&d.fill[f_lo + tid], left << 16);
-      const u32 fine = S.fine[tid], first = fine >> 11, cells = (fine & 2047u) + 1;
-      if (fill_front(old) + fill_back(old) + left > cells) status |= DS_DUPLICATE;
-      else start = first + cells - fill_back(old);
-    }
-    S.cnt[tid] = start;
+  const u32 t_end = thread_here();
+  if (t_end < span && left) {
+    const u32 old = atomicAdd(&d.fill[f_lo + t_end], left << 16);
+    const u32 fine = S.fine[t_end], cells = (fine & 2047u) + 1;
+    if (fill_rows(old) + left > cells) status |= DS_DUPLICATE;
+    S.cnt[t_end] = (u32)back_place(old, 0, cells);
   }
   __syncthreads();
 #pragma unroll
   for (u32 h = 0; h < HELD; ++h) {
     if (!(held >> h & 1)) continue;
-    const u32 start = S.cnt[(tid + h * PART_THREADS) / LINE_ROWS];
-    if (start != ~0u) *reinterpret_cast<u32x4*>(d.rows + (cell_lo + start + h_at[h])) = h_row[h];        // (the place is negative)
+    const u32 fi = (t_end + h * PART_THREADS) / LINE_ROWS;
+    const i32 place = (i32)(S.cnt[fi] + h_at[h]);
+    if (place >= 0) *reinterpret_cast<u32x4*>(d.rows + (cell_lo + (S.fine[fi] >> 11) + (u32)place)) = h_row[h];
   }
   __syncthreads();
 }

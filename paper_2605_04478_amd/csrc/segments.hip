@@ -1257,7 +1257,7 @@ __device__ __forceinline__ u64 grid_place(const GridArgs& d, const FineDesc& D, 
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
   u32x4 v[U];
   const u32 cnt = fill_rows(fill), front = fill_front(fill), back = cells - fill_back(fill);
-  const bool over = cnt > cells;
+  const bool over = cnt > cells;              // every cell has been written then (rooms.h)
   bool dup = over;
   auto holds = [&](u32 i) { return i < cells && (i < front || i >= back || over); };
 #pragma unroll
