@@ -19,7 +19,6 @@ using namespace ccld;
 constexpr size_t PINNED_FINE = 32, PINNED_META = 64;
 static_assert(CNT_COUNT <= PINNED_FINE, "the counters come first");
 
-static int bits_for_host(uint64_t v) { int b = 0; while (v) { ++b; v >>= 1; } return b; }
 
 namespace {
 
@@ -208,7 +207,7 @@ void plan(ccld_ctx* c, const ccld_params* p, const ccld_topology* t, uint64_t n_
   c->cap = cap; c->batch_cap = batch_cap; c->snap_cap = snap_cap;
   uint32_t max_size = 1;
   for (uint32_t k = 0; k < t->n_comms; ++k) max_size = std::max(max_size, t->size[k]);
-  const int mb = bits_for_host(max_size - 1), cb = bits_for_host(t->n_comms - 1);
+  const int mb = bits_for(max_size - 1), cb = bits_for(t->n_comms - 1);
   c->max_comm_size = max_size;
   c->long_classes = 0;
   for (uint32_t k = 0; k < t->n_comms; ++k) if (t->size[k] > 64) c->long_classes |= t->size[k] <= 128 ? 1u : t->size[k] <= 256 ? 2u : t->size[k] <= 512 ? 4u : 8u;
@@ -221,23 +220,16 @@ void plan(ccld_ctx* c, const ccld_params* p, const ccld_topology* t, uint64_t n_
   c->grid_over_sort = N >= (4u << 20) && p->placement != CCLD_PLACEMENT_DENSE;
   c->cell_cap = (uint32_t)std::min<uint64_t>(N >= (4u << 20) ? N + N / 5 : 2 * N + 4096, 0xFFFFFF00u);
   c->fine_cap = c->cell_cap / GRID_MIN_FILL + t->n_comms + 16;
-  // Communicator buckets of the ingest.  A partition workgroup addresses GRID_SPAN fine buckets at a time, so a window that
-  // may have more of them is placed by bucket, into as many buckets as leave about GRID_TARGET fine buckets in one:
-  // fewer in one lengthen the runs that the partition writes, more leave the ingest room for the ranks' rows in LDS (82M records
-  // with 300 / 600 in one: ingest 1,184 / 1,122 us, partition 703 / 911; 20M: ingest 299 / 300, partition 164 / 190).  A window that
-  // cannot be placed on the grid
-  // takes buckets whose rows (16 bytes per record) stay within about 100 MB, which the memory-side cache holds while the
-  // statistics gather from one.
+  // Communicator buckets of the ingest.  A window that cannot be placed on the grid takes buckets whose rows (16 bytes per record) stay
+  // within about 100 MB, which the memory-side cache holds while the statistics gather from one.
   int bb = 0;
   if (c->grid_capable) {
-    const uint64_t fine = N / 1400 + t->n_comms;
-    if (fine > GRID_ONE_BUCKET) while (bb < 8 && (fine >> bb) > GRID_TARGET) ++bb;
-    while (bb > 0 && ((W << bb) > GRID_MAX_PIECES)) --bb;
+    bb = grid_bucket_bits(N / 1400 + t->n_comms, W, t->n_comms);
     if (bb > 0 && W > GRID_MAX_BATCHES) c->grid_capable = false;
   }
   if (!c->grid_capable) { bb = 0; while (bb < 6 && ((N * 16) >> bb) > 100000000ull) ++bb; }
-  c->bshift = cb > bb ? cb - bb : 0;
-  c->n_buckets = ((t->n_comms - 1) >> c->bshift) + 1;
+  c->bshift = bucket_shift(bb, t->n_comms);
+  c->n_buckets = bucket_count(bb, t->n_comms);
   c->n_members = n_members;
 }
 
@@ -313,7 +305,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
   c->copy_earned = 0;
   if (hipGetDevice(&c->device) != hipSuccess || c->device >= COPY_DEVICES) { (void)hipGetLastError(); delete c; return CCLD_E_HIP; }
   c->chain_ready = false;
-  c->rank_bits = bits_for_host(topo->n_ranks - 1);
+  c->rank_bits = bits_for(topo->n_ranks - 1);
   c->head = 0; c->count = 0; c->next_slot = 0; c->rounds_next = 0; c->total_ingested = 0;
   c->inc_ok = false; c->inc_head = c->inc_count = c->inc_total = 0;
   c->sorted_buf = 0; c->blame_valid = false; c->sort_passes = 0;
@@ -360,7 +352,7 @@ ccld_status ccld_create(const ccld_params* params, const ccld_topology* topo, ui
 
   // the same rows with the member index (the row of the snapshot grid) in place of the sorted position: the
   // snapshot placement then needs one lookup per row instead of three
-  const int pb = bits_for_host(n_members ? n_members - 1 : 0);
+  const int pb = bits_for(n_members ? n_members - 1 : 0);
   std::vector<uint32_t> rp4(4ull * topo->n_ranks, 0xFFFFFFFFu);
   const bool fits_cell4 = fits4 && pb + cb <= 31;
   for (uint32_t r = 0; fits_cell4 && r < topo->n_ranks; ++r)
@@ -776,7 +768,7 @@ static ccld_status analyze_sorted(ccld_ctx* c, int64_t now_ns, ccld_window_resul
   // 2. sort by (communicator, operation counter, rank) on the significant bits only, the operation counters relative to
   //    the smallest one of the window
   if (min_seq > max_seq) min_seq = max_seq;
-  const int mb = c->kf.mb, cb = c->kf.cb, ws = bits_for_host(max_seq - min_seq);
+  const int mb = c->kf.mb, cb = c->kf.cb, ws = bits_for(max_seq - min_seq);
   c->sf.mb = mb; c->sf.ws = ws; c->sf.seq_base = min_seq;
   KeySource src;
   src.key = c->win_key; src.head = sa.win.head; src.cap = sa.win.cap;

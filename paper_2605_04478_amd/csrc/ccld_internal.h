@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "ccld.h"
+#include "buckets.h"
 #include "radix_sort.h"
 #include "profiler.h"
 #include "ticket.h"
@@ -93,7 +94,6 @@ struct WindowRows {
   const uint32_t* rounds;        // [rounds][n_buckets]
   uint32_t n_buckets;
 };
-constexpr uint32_t INGEST_ROUND = 2048;      // records that a placement workgroup regroups at a time
 // Rounds of all resident batches and of one more: a batch of n records has at most 3 n / 2048 + 2, and as much again keeps
 // a batch's rounds in one piece where the table starts over.
 inline uint64_t ingest_rounds_cap(uint64_t records, uint64_t batches) { return 2 * (3 * records / INGEST_ROUND + 2 * batches) + 64; }

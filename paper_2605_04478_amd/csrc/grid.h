@@ -14,13 +14,10 @@ namespace ccld {
 constexpr uint32_t GRID_B = 2048;            // grid cells (= LDS cells of the statistics kernels) per fine bucket
 constexpr uint32_t GRID_MIN_FILL = 1025;     // a full fine bucket holds at least this many cells (whole rounds of <= GRID_B members)
 constexpr uint32_t GRID_SPAN = 4096;         // fine buckets of one coarse bucket that a partition workgroup addresses
-constexpr uint32_t GRID_ONE_BUCKET = 3500;   // windows of no more fine buckets are partitioned in one go, without communicator buckets
 constexpr uint32_t GRID_FINE_BOUND = 4096;   // most fine buckets that a launch is sized for without asking for their number
 constexpr uint32_t GRID_SELF_SUM = 512;      // where so many fine buckets are likely, each workgroup of the statistics sums the records before its own
-constexpr uint32_t GRID_TARGET = 300;        // fine buckets per communicator bucket of the others
 constexpr uint32_t GRID_MAX_COMMS = INGEST_RANGE_COMMS;
 constexpr uint32_t GRID_MAX_BATCHES = 256;   // batches of a window whose batches are placed by communicator bucket
-constexpr uint32_t GRID_MAX_PIECES = 4096;   // (coarse bucket, batch) pairs of such a window
 
 // Per communicator: where its part of the grid lies.  Rounds are numbered from the window's smallest
 // operation counter of the communicator; rpb rounds make one fine bucket.

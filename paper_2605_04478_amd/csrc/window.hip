@@ -224,19 +224,14 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
 // lookup is a gather with no locality, cheaper from LDS than from the L2.
 //
 // Bound by memory: a line that a round leaves unfinished would be completed by the next one 7 us later, when it has left the
-// L2 in parts.  So rows leave eight slots at a time (LINES: a line of rows, half a line of keys), with the streaming
+// L2 in parts.  So rows leave eight slots at a time (a line of rows, half a line of keys), with the streaming
 // hint; up to seven of a bucket wait in registers for the next round.  82M records into 68 buckets: 1,125 us (4.7 TB/s), 1,260 with
 // every round written as it is; four slots at a time 1,150.  Ranks' rows from the L2: 1,150 to 1,180.
-constexpr u32 INGEST_LINE = 8;
-// LDS words for a round: rows that waited and lines that are not filled come on top of the round's records
-__host__ __device__ constexpr u32 ingest_stage_rows(u32 n_buckets, bool lines) {
-  return INGEST_ROUND + (lines ? 2 * (INGEST_LINE - 1) * n_buckets : 0u);
-}
-template <int THREADS, bool LDS_TABLE, bool LINES>
+template <int THREADS, bool LDS_TABLE>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
-  constexpr u32 CHUNK = THREADS * U, LINE = LINES ? INGEST_LINE : 1;
-  constexpr u32 HELD = LINES ? INGEST_STAGED_BUCKETS * LINE / THREADS : 0;       // rows that wait in a thread
+  constexpr u32 CHUNK = THREADS * U, LINE = INGEST_LINE;
+  constexpr u32 HELD = INGEST_STAGED_BUCKETS * LINE / THREADS;       // rows that wait in a thread
   static_assert(CHUNK == INGEST_ROUND, "a row has room for the record's number in its round");
   static_assert(INGEST_STAGED_BUCKETS <= 256 && INGEST_STAGED_BUCKETS <= THREADS, "a byte and a thread per bucket");
   // [n_ranks] membership rows (LDS_TABLE) | [ingest_stage_rows] rows | the same number of keys | [n_comms][2] ranges
@@ -246,9 +241,9 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   // first slot that this round leaves unwritten
   __shared__ u32 s_off[INGEST_STAGED_BUCKETS], s_total;
   __shared__ uint4 s_run[INGEST_STAGED_BUCKETS];
-  __shared__ uint8_t s_bucket[ingest_stage_rows(INGEST_STAGED_BUCKETS, LINES) / LINE];   // of every LINE staged rows
+  __shared__ uint8_t s_bucket[ingest_stage_rows(INGEST_STAGED_BUCKETS) / LINE];   // of every LINE staged rows
   __shared__ u32 s_scan[THREADS / CCLD_WAVE];
-  const u32 stage_rows = ingest_stage_rows(a.n_buckets, LINES);
+  const u32 stage_rows = ingest_stage_rows(a.n_buckets);
   uint4* s_row = s_dyn + (LDS_TABLE ? T.n_ranks : 0u);
   u64* s_key = reinterpret_cast<u64*>(s_row + stage_rows);
   unsigned long long* s_rng = reinterpret_cast<unsigned long long*>(s_key + stage_rows);
@@ -325,8 +320,8 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
   // rows that wait: of bucket i / LINE the one at place i % LINE of its line, i = tid, tid + THREADS, ...
   // (an array of uint4 would lie in scratch memory: 82M records 1,330 us in place of 1,251)
   typedef u32 u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 h_row[HELD ? HELD : 1];
-  u64 h_key[HELD ? HELD : 1];
+  u32x4 h_row[HELD];
+  u64 h_key[HELD];
   u32 held = 0;                          // a bit each
   load_round(i_begin, r, c, sq, op, nb, te, tx);
   wait_vector_memory();
@@ -370,7 +365,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
       if (tid < a.n_buckets) {
         // rows of lines that are not full wait, unless there is no next round
         u32 upto = to;
-        if (LINES && base + CHUNK < i_end) { const u32 whole = to & ~(LINE - 1); upto = whole > from ? whole : from; }
+        if (base + CHUNK < i_end) { const u32 whole = to & ~(LINE - 1); upto = whole > from ? whole : from; }
         s_run[tid] = make_uint4(pre - first, from, upto, 0u);
         from = upto;
         *round_row = start - a.tail;
@@ -409,7 +404,7 @@ __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceT
     for (u32 q = tid; q < total; q += THREADS) {
       const uint4 run = s_run[s_bucket[q / LINE]];
       const u32 v = q - run.x, lo = run.y, hi = run.z, D = v >= a.cap ? v - a.cap : v;
-      const bool full = (v & ~(INGEST_LINE - 1)) >= lo && (v | (INGEST_LINE - 1)) < hi;
+      const bool full = (v & ~(LINE - 1)) >= lo && (v | (LINE - 1)) < hi;
       if (v < lo || v >= hi) continue;
       const uint4 row = s_row[q];
       const u64 k = s_key[q];
@@ -463,10 +458,9 @@ IngestShape ingest_shape(uint64_t n) {
   s.per_group = (uint32_t)((s.chunk + INGEST_ROUND - 1) / INGEST_ROUND);
   return s;
 }
-constexpr size_t INGEST_LDS = 152 * 1024;      // beside the 8 KB of the static tables
 template <class F>
 static void each_ingest_staged(F f) {
-  f(&k_ingest_staged<1024, true, true>); f(&k_ingest_staged<1024, false, true>); f(&k_ingest_staged<1024, false, false>);
+  f(&k_ingest_staged<1024, true>); f(&k_ingest_staged<1024, false>);
 }
 hipError_t allow_lds_window() {
   hipError_t e = hipSuccess;
@@ -506,15 +500,14 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
-  // whole lines, and the membership rows in LDS, where they fit: with 68 buckets lines without the rows in LDS take 1,180 us in place of 1,155
+  // the membership rows in LDS where they fit beside the lines: with 68 buckets lines without the rows in LDS take 1,180 us in place of 1,155
   // with both (82M records of 4,096 ranks), the rows without lines 1,285.  With 136 buckets both do not fit: lines 1,251 us, half
   // lines (four slots) beside the rows 1,352.
-  const size_t table = T.rank_memb4 ? (size_t)T.n_ranks * 16 : 0;
-  auto lds = [&](bool lines, bool in_lds) { return (size_t)ingest_stage_rows(a.n_buckets, lines) * 24 + range_lds + (in_lds ? table : 0); };
+  const u32 range_comms = a.range ? T.n_comms : 0;
+  const size_t lines = ingest_lds(a.n_buckets, range_comms, 0), both = ingest_lds(a.n_buckets, range_comms, T.n_ranks);
   auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3((u32)g), dim3(1024), bytes, st, a, T, kf); };
-  if (table && lds(true, true) <= INGEST_LDS) go(k_ingest_staged<1024, true, true>, lds(true, true));
-  else if (lds(true, false) <= INGEST_LDS) go(k_ingest_staged<1024, false, true>, lds(true, false));
-  else go(k_ingest_staged<1024, false, false>, lds(false, false));
+  if (T.rank_memb4 && both <= INGEST_LDS) go(k_ingest_staged<1024, true>, both);
+  else go(k_ingest_staged<1024, false>, lines);
 }
 
 // ------------------------------------------------------------------------------------------

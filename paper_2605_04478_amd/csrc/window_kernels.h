@@ -34,8 +34,6 @@ struct IngestArgs {
 struct IngestShape { uint32_t groups, per_group, hist_split; uint64_t chunk; };
 IngestShape ingest_shape(uint64_t n);
 constexpr uint32_t INGEST_BLOCKS = 1024;
-constexpr uint32_t INGEST_STAGED_BUCKETS = 256;   // most buckets the LDS-regrouped placement kernel handles
-constexpr uint32_t INGEST_RANGE_COMMS = 3584;     // most communicators whose counter ranges fit the counting kernel's LDS
 void launch_ingest(hipStream_t st, const IngestArgs& a, const DeviceTopology& T, const KeyFormat& kf);
 void launch_fill_u64(hipStream_t st, uint64_t* p, uint64_t n, uint64_t v);
 
