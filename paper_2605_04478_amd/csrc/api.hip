@@ -74,7 +74,7 @@ void carve_all(ccld_ctx* c, Carver& w, uint32_t n_ranks, uint32_t n_comms, uint6
   // on the grid, so in large contexts they lie over the sort buffers; small ones, and contexts that ask for
   // the placement, have them apart.
   auto take_grid = [&](Carver& g) {
-    const uint64_t cells = c->cell_cap;
+    const uint64_t cells = c->cell_cap + (grid_in_lines(N, false) ? (LINE_ROWS - 1) * (uint64_t)n_comms : 0);
     c->g_rows = g.take<uint4>(cells);
     c->g_slots = g.take<uint32_t>(cells);
     c->g_cell_row = g.take<uint16_t>(cells);
@@ -670,6 +670,7 @@ static ccld_status analyze_on_grid(ccld_ctx* c, int64_t now_ns, ccld_window_resu
   d.fine_cap = std::min(c->fine_cap, d.cell_cap / GRID_MIN_FILL + c->topo.n_comms);
   d.likely = n / GRID_B + c->topo.n_comms / 2;
   d.self_sum = d.likely <= GRID_SELF_SUM && d.fine_cap <= GRID_FINE_BOUND;
+  d.lines = grid_in_lines(n, o->perm != nullptr);
   d.rows = c->g_rows; d.slots = o->perm ? c->g_slots : nullptr;
   d.cell_row = c->g_cell_row; d.counters = c->counters;
   d.blame = (uint64_t*)c->blame; d.n_blame = CCLD_BLM_NCOL * n_ranks;

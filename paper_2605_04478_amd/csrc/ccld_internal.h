@@ -201,7 +201,7 @@ struct ccld_ctx {
   void* g_desc;                       // [fine_cap] FineDesc
   uint32_t *g_piece_at, *g_piece_slot;
   uint32_t *g_fill, *g_rec0, *g_nflag, *g_long;   // [fine_cap + 1]
-  uint4* g_rows;                      // [cell_cap]
+  uint4* g_rows;                      // [cell_cap, and what stays empty where rows leave in whole lines]
   uint32_t* g_slots;                  // [cell_cap]
   uint16_t* g_cell_row;               // [cell_cap]
   uint32_t* flag_stage;               // [cap]

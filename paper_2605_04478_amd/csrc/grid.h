@@ -11,8 +11,6 @@
 
 namespace ccld {
 
-constexpr uint32_t GRID_B = 2048;            // grid cells (= LDS cells of the statistics kernels) per fine bucket
-constexpr uint32_t GRID_MIN_FILL = 1025;     // a full fine bucket holds at least this many cells (whole rounds of <= GRID_B members)
 constexpr uint32_t GRID_SPAN = 4096;         // fine buckets of one coarse bucket that a partition workgroup addresses
 constexpr uint32_t GRID_FINE_BOUND = 4096;   // most fine buckets that a launch is sized for without asking for their number
 constexpr uint32_t GRID_SELF_SUM = 512;      // where so many fine buckets are likely, each workgroup of the statistics sums the records before its own
@@ -24,7 +22,7 @@ constexpr uint32_t GRID_MAX_BATCHES = 256;   // batches of a window whose batche
 struct __attribute__((aligned(16))) CommLayout {
   uint64_t seq_min;        // smallest operation counter in the window
   uint32_t fb_base;        // first fine bucket
-  uint32_t rpb;            // rounds per fine bucket: GRID_B / members
+  uint32_t rpb;            // rounds per fine bucket (bucket_rounds)
   uint32_t rounds;         // largest - smallest operation counter + 1 (0: no record)
   uint32_t seg_base;       // row of the collective table of the first round
   uint32_t cell_base;      // first cell
@@ -77,8 +75,9 @@ struct GridArgs {
   FineDesc* desc;                // [fine_cap]
   uint32_t* long_list;           // [fine_cap] fine buckets of communicators of more than 64 members
   uint32_t fine_cap, cell_cap;
+  uint32_t lines;                // 1: rows leave in whole lines (grid_in_lines), and up to seven cells behind those of a communicator stay empty
   uint32_t likely, self_sum;     // fine buckets that the window most likely has; 1: they are not scanned (RecordsBefore)
-  uint4* rows;                   // [cell_cap] partitioned rows
+  uint4* rows;                   // [cell_cap, and what stays empty] partitioned rows
   uint32_t* slots;               // [cell_cap] their window slots, or null: not wanted
   uint16_t* cell_row;            // [cell_cap] row of each cell inside its bucket, GRID_EMPTY: no record
   uint64_t* counters;
@@ -91,6 +90,8 @@ struct GridArgs {
 constexpr uint32_t GRID_INFEASIBLE = 0x80000000u, GRID_FULL = 0x40000000u;
 constexpr uint32_t GRID_EMPTY = 0xFFFFu;
 
+// whether the rows of n records leave in whole lines
+bool grid_in_lines(uint64_t n, bool with_slots);
 void launch_grid_layout(hipStream_t st, const GridArgs& d);
 void launch_grid_partition(hipStream_t st, const GridArgs& d);
 // ends the placement of a window that has a round without any record (behind the partition)

@@ -28,11 +28,11 @@ template <u32 PER, u32 AHEAD>
 __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   __shared__ u32 s_wave[1024 / CCLD_WAVE];
   __shared__ uint4 s_sums[CCLD_WAVE];
-  __shared__ u32 s_bad, s_any;
+  __shared__ u32 s_bad, s_any, s_empty;
   __shared__ unsigned long long s_status;
   __shared__ i64 s_ref;
   const u32 tid = threadIdx.x;
-  if (tid == 0) { s_bad = 0; s_status = 0; s_any = 0xFFFFFFFFu; }
+  if (tid == 0) { s_bad = 0; s_status = 0; s_any = 0xFFFFFFFFu; s_empty = 0; }
   if (tid < CNT_COUNT) d.counters[tid] = 0;
   // the headers of the batches (those of the first 1,024 stay in registers), the pieces and the counter ranges are on their way together
   auto meta_of = [&](u32 i) -> const BatchMeta& { return d.meta[(d.slot0 + i) % d.n_meta]; };
@@ -91,7 +91,8 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
   }
   // the sum of the cells can pass 32 bits, so it is taken in halves (where it does, the layout is refused, and where it
   // does not, the sums of buckets and rounds do not either)
-  u32 rounds[PER];
+  const bool lines = d.lines != 0;
+  u32 rounds[PER], empty = 0;
   uint4 before[PER];                    // fine buckets, rounds, cells (low and high half) before the communicator
   const u32 lane = lane_id(), wave = tid / CCLD_WAVE;
   auto sums = [](const uint4& v) { return make_uint4(wave_inclusive_sum(v.x), wave_inclusive_sum(v.y), wave_inclusive_sum(v.z), wave_inclusive_sum(v.w)); };
@@ -107,8 +108,9 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
         bad = true;
       } else {
         rounds[k] = (u32)r;
-        const u32 rpb = GRID_B / size[k];                // size <= GRID_B: the host checked
-        const u64 cells = r * size[k];
+        const u32 rpb = bucket_rounds(size[k], lines);   // size <= GRID_B: the host checked
+        const u64 cells = grid_cells(size[k], rounds[k], lines);
+        empty += (u32)(cells - r * size[k]);
         v = make_uint4((rounds[k] + rpb - 1) / rpb, rounds[k], (u32)cells & 0xFFFFu, (u32)(cells >> 16));
       }
     }
@@ -116,13 +118,14 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     if (lane == CCLD_WAVE - 1) s_sums[k * WAVES + wave] = inc;
     before[k] = less(inc, v);
   }
+  if (lines) { empty = wave_sum(empty); if (lane == 0 && empty) atomicAdd(&s_empty, empty); }
   __syncthreads();
   const uint4 part = lane < PER * WAVES ? s_sums[lane] : make_uint4(0, 0, 0, 0), upto = sums(part), total = from(upto, CCLD_WAVE - 1);
   const uint4 ahead = less(upto, part);
   // one time serves the whole window, that of its first batch with records, unless its batches lie too far apart
   const u32 any = s_any;
   if (tid == (any < 1024 ? any : 0u)) s_ref = any < 1024 ? m_ref : meta_of(any < d.nb ? any : 0).ref;
-  const u64 cell_total = (u64)total.z + ((u64)total.w << 16);
+  const u64 cell_total = (u64)total.z + ((u64)total.w << 16), cell_used = cell_total - s_empty;
   const u32 fb_total = total.x, seg_total = total.y;
 #pragma unroll
   for (u32 k = 0; k < PER; ++k) {
@@ -130,14 +133,14 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     const u32 c = k * 1024 + tid;
     if (c >= d.n_comms) continue;
     CommLayout L;
-    L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.rpb = GRID_B / size[k]; L.rounds = rounds[k]; L.size = size[k];
+    L.seq_min = (mx[k] | inv[k]) ? ~inv[k] : 0; L.rpb = bucket_rounds(size[k], lines); L.rounds = rounds[k]; L.size = size[k];
     L.fb_base = w.x + before[k].x; L.seg_base = w.y + before[k].y;
     L.cell_base = (u32)((u64)w.z + before[k].z + ((u64)(w.w + before[k].w) << 16));
     divide_by(L.rpb, &L.div, &L.shift);
     d.lay[c] = L;
   }
   // more rounds than records means a round without any record: the sort handles such windows
-  if (cell_total > d.cell_cap || fb_total > d.fine_cap || seg_total > d.n) bad = true;        // uniform
+  if (cell_used > d.cell_cap || fb_total > d.fine_cap || seg_total > d.n) bad = true;        // uniform
   const u64 fb_carry = fb_total, seg_carry = seg_total, cell_carry = cell_total;
   if (tid == 0) {
     CommLayout L;
@@ -195,7 +198,7 @@ __global__ __launch_bounds__(1024) void k_grid_layout(GridArgs d) {
     if (s_status) d.counters[CNT_STATUS] = s_status;
     else if (!ok) d.counters[CNT_STATUS] = DS_DENSE_FALLBACK;
     d.counters[CNT_NSEG] = ok ? seg_carry : 0;
-    __hip_atomic_store(d.host_fine, ok ? (n_fine + 1) | (cell_carry == d.n ? GRID_FULL : 0u) : GRID_INFEASIBLE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(d.host_fine, ok ? (n_fine + 1) | (cell_used == d.n ? GRID_FULL : 0u) : GRID_INFEASIBLE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -225,14 +228,16 @@ void launch_grid_layout(hipStream_t st, const GridArgs& d) {
 // Lines (part_lines): the largest windows have more lines on their way than the caches hold, and what a round left of one unwritten
 // leaves in parts before the next completes it.  There rooms are reserved eight rows at a time from the fine bucket's start, up to
 // seven rows of a fine bucket wait in registers for the next round, and what is left when the workgroup's share of the coarse
-// bucket ends goes to the fine bucket's end: 82M records 959 us before, 842 as runs, 703 so (4.7 TB/s).
+// bucket ends goes to the fine bucket's end: 82M records 959 us before, 842 as runs, 703 so (4.7 TB/s).  The layout starts fine
+// buckets on lines there (bucket_rounds), since eight rows that lie across two lines are two parts of lines: communicators of 6, 8 and 64
+// members, 60M / 100M records 530 / 1,042 us as runs, 613 / 1,277 as rows in eights anywhere, 532 / 962 so; of 3, 9 and 13 members 497 /
+// 976, 622 / 1,320, 507 / 905.  (Coarse buckets with a communicator that has too few rounds in a fine bucket for that leave as runs.)
 //
 // One workgroup per compute unit.  Workgroups go to the eight XCDs in turn and every XCD has an L2 of its own: those of one XCD
 // take neighbouring slices, so that the lines that several workgroups write are completed in one L2.
 constexpr u32 PART_THREADS = 1024, PART_U = 4, PART_CHUNK = PART_THREADS * PART_U;
 constexpr u32 PART_BLOCKS = 256, PART_XCDS = 8;
 constexpr u32 PART_LAY = 256;          // communicators of a bucket whose layout waits in LDS
-constexpr u32 LINE_ROWS = 8;           // rows of a 128-byte line
 constexpr u32 LINES_U = 3, LINES_CHUNK = PART_THREADS * LINES_U;
 constexpr u32 LINES_SPAN = 384;        // most fine buckets of a coarse bucket whose rows leave in whole lines
 constexpr u32 LINES_STAGE = LINES_CHUNK + 2 * (LINE_ROWS - 1) * LINES_SPAN;     // and rows that waited, and lines that are not filled
@@ -471,6 +476,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   __shared__ u32 s_wave[PART_THREADS / CCLD_WAVE];
   __shared__ u32 s_at[GRID_MAX_BATCHES + 1], s_slot0[GRID_MAX_BATCHES];
   __shared__ u32 s_total, s_last;
+  __shared__ u32 s_off;                // 1 + the last coarse bucket with a fine bucket that does not start on a line
   __shared__ PartComm s_lay[PART_LAY];
   __shared__ uint2 s_base[PART_LAY];    // first cell, rounds
   const u32 tid = threadIdx.x;
@@ -514,6 +520,7 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
   // the coarse bucket that holds record lo: the last one that starts at or before it
   static_assert(INGEST_STAGED_BUCKETS <= PART_THREADS, "a thread per coarse bucket");
   const u32 b_lo = d.n_buckets == 1 ? 0u : (u32)__syncthreads_count(tid < d.n_buckets && d.piece_at[(u64)tid * nb] <= lo) - 1;
+  if (tid == 0) s_off = 0;
   __syncthreads();
   u32 pos = lo;
   for (u32 b = lo < hi ? b_lo : d.n_buckets; b < d.n_buckets && pos < hi; ++b) {
@@ -530,10 +537,11 @@ __global__ __launch_bounds__(PART_THREADS) void k_grid_partition(GridArgs d) {
     if (tid <= nb) s_at[tid] = at;
     if (tid < nb) s_slot0[tid] = slot;
     if (near && tid < c1 - c0) { s_lay[tid] = PartComm(L, f_lo); s_base[tid] = make_uint2(L.cell_base, L.rounds); }
+    if constexpr (LINES) if (near && tid < c1 - c0 && off_lines(L.size, L.rpb, L.rounds)) s_off = b + 1;
     __syncthreads();
     const u32 end = s_at[nb] < hi ? s_at[nb] : hi;
     if (end <= pos) { __syncthreads(); continue; }         // no record of the bucket in the slice
-    if constexpr (LINES) if (near && span <= LINES_SPAN && end - pos >= LINES_MIN) {
+    if constexpr (LINES) if (near && s_off != b + 1 && span <= LINES_SPAN && end - pos >= LINES_MIN) {
       part_lines(d, *reinterpret_cast<PartLines*>(s_row), s_lay, s_base, c0, c1 - c0, pk, s_at, s_slot0, s_wave, pos, end, f_lo, span, status);
       pos = end;
       continue;
@@ -677,6 +685,7 @@ static hipError_t each_partition(F f) {
 hipError_t allow_lds_grid() {
   return each_partition([](auto k, size_t bytes) { return allow_lds(reinterpret_cast<const void*>(k), bytes); });
 }
+bool grid_in_lines(uint64_t n, bool with_slots) { return !with_slots && n / PART_BLOCKS >= LINES_SLICE; }
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   // small windows: a thousand records per workgroup, so that there are several of them
   const u32 g = std::min<u32>(PART_BLOCKS, std::max<u32>((d.n + PART_THREADS - 1) / PART_THREADS, 1));
@@ -685,7 +694,7 @@ void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   if (d.slots) one ? go(k_grid_partition<true, false, 1>, PART_LDS_SLOTS) : go(k_grid_partition<true, false, PART_U>, PART_LDS_SLOTS);
   else if (one) go(k_grid_partition<false, false, 1>, PART_LDS);
   // 33M, 41M, 57M and 82M records: 270, 367, 500 and 844 us as runs, 304, 378, 489 and 704 in whole lines
-  else if (d.n / PART_BLOCKS < LINES_SLICE) go(k_grid_partition<false, false, PART_U>, PART_LDS);
+  else if (!d.lines) go(k_grid_partition<false, false, PART_U>, PART_LDS);
   else go(k_grid_partition<false, true, PART_U>, PART_LDS_LINES);
 }
 

@@ -93,3 +93,34 @@ def test_the_partition_takes_its_rooms_by_this_rule():
     text = open(os.path.join(CSRC, "grid.hip")).read()
     lines = text[text.index("void part_lines("):text.index("void k_grid_partition(")]
     assert lines.count("atomicAdd(&d.fill[") == 2 and "front_room(got, out, cells)" in lines and "back_place(old, 0, cells)" in lines and "if (place >= 0)" in lines
+
+
+LAYOUT = r"""
+#include <cstdio>
+#include "rooms.h"
+using namespace ccld;
+int main() {
+  for (uint32_t size = 1; size <= GRID_B; ++size)
+    for (int lines = 0; lines < 2; ++lines) {
+      const uint32_t rpb = bucket_rounds(size, lines), cells = rpb * size;
+      if (cells > GRID_B || (size < GRID_B && cells < GRID_MIN_FILL && GRID_B / size > 1) || (!lines && rpb != GRID_B / size)) { std::printf("%u members: %u cells\n", size, cells); return 1; }
+      if (lines && size <= 256 && off_lines(size, rpb, rpb + 1)) { std::printf("%u members: a second bucket that starts at cell %u\n", size, cells); return 1; }
+      if (off_lines(size, rpb, rpb) || off_lines(size, rpb, rpb + 1) != (cells % 8 != 0)) return 2;
+      for (uint32_t rounds : {1u, rpb, rpb + 1, 3 * rpb, 3 * rpb + 2, 100000u}) {
+        const uint64_t have = grid_cells(size, rounds, lines), want = (uint64_t)size * rounds;
+        if (have < want || have - want > 7 || (lines ? have % 8 != 0 : have != want)) { std::printf("%u members, %u rounds: %llu cells\n", size, rounds, (unsigned long long)have); return 3; }
+        // the fine buckets' cells, 2,048 at most, hold the communicator's
+        if (have > (uint64_t)((rounds + rpb - 1) / rpb) * GRID_B) return 4;
+      }
+    }
+  return 0;
+}
+"""
+
+
+def test_fine_buckets_start_on_lines_where_rows_leave_in_lines(tmp_path):
+    src, exe = tmp_path / "layout.cpp", tmp_path / "layout"
+    src.write_text("#include <initializer_list>\n" + LAYOUT)
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", CSRC, "-o", str(exe), str(src)])
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert run.returncode == 0, (run.returncode, run.stdout)
