@@ -108,3 +108,22 @@ def test_hang_series_decoded_on_the_device(lay, n_ch):
     g = an.locate_hang(an.snapshots_to_device(cols), n_snap, n_ch)
     assert g.status == "OK" and list(g.root["rank"]) == [ht.root_rank] and list(g.root["comm"]) == [ht.root_comm]
     an.close()
+
+
+@pytest.mark.parametrize("n,n_ch", [(3, 1), (3, 2), (43, 3), (128, 1), (129, 8)])
+def test_columns_of_a_snapshot_are_aligned_for_any_number_of_rows(n, n_ch):
+    """every column is contiguous and starts where an allocation of its own would, so that wider loads and views of other widths stay possible"""
+    import torch
+    from paper_2605_04478_amd import ccld
+    topo = ring_topology(n)
+    an = ccld.Analyzer(topo, max_window_records=16, max_snapshot_rows=64 * n * n_ch)
+    o = orc.Oracle(topo)
+    o.frames_begin(n_ch)
+    _, rows = both(an, o, np.zeros((0, G["frame_bytes"]), np.uint8), np.zeros(0, np.uint32), 5, n_ch, what=n)
+    st, rows = an.decode_frames(np.zeros((0, G["frame_bytes"]), np.uint8), np.zeros(0, np.uint32), 6, n_ch)
+    spans = sorted((v.data_ptr(), v.data_ptr() + v.numel() * v.element_size()) for v in rows.values())
+    assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+    for k, v in rows.items():
+        assert v.shape == (n * n_ch,) and v.is_contiguous() and v.data_ptr() % 256 == 0, k
+        assert v[:v.numel() // 2 * 2].view(torch.int64 if v.dtype == torch.int32 else torch.int32).numel() > 0
+    an.close()
