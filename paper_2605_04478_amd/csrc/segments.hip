@@ -1422,6 +1422,8 @@ __device__ __forceinline__ u32 first_bit(u64 m) { return (u32)__builtin_ctzll(m)
 // The kernel's first argument, read again where it is used: what few passes need would be kept in scalar registers over all of them,
 // which are too few, and every spill and reload of one is a vector instruction.  (Not where there are FEW buckets, whose passes would
 // wait for it.)  With FULL: 82M records 809 -> 778 us, 5.1M 73.1 -> 68.5, ten batches of 2M 167 -> 160.
+// These two take the arguments by their places: only for the kernels whose signatures are checked below (reads_args_again), whose
+// copies of the arguments are const.
 __device__ __forceinline__ const SegArgs& args_again() {
   auto p = __builtin_amdgcn_kernarg_segment_ptr();
   asm("" : "+s"(p));
@@ -1551,7 +1553,7 @@ __device__ __forceinline__ u32 grid_batches(const SegArgs& a, const GridArgs& d,
 }
 
 template <int GRID_THREADS, bool SELF_SUM>       // SELF_SUM: as d.self_sum
-__global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+__global__ __launch_bounds__(GRID_THREADS) void k_grid_stats(const SegArgs a, const GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   __shared__ GridShared<GRID_B> S;
   __shared__ u32 s_slot[CCLD_WAVE];
   constexpr u32 NW = GRID_THREADS / CCLD_WAVE;
@@ -1942,7 +1944,7 @@ __device__ __forceinline__ void long_rounds(const SegArgs& a, const GridArgs& d,
 // 714 instead of 702 us), so buckets of eight members per lane, of at most seven collectives, have eight wavefronts: 1.1M records
 // with collectives of 390 members 211 -> 189 us.
 template <int E, int THREADS>
-__global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(SegArgs a, GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
+__global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long(const SegArgs a, const GridArgs d, i64* __restrict__ blame, u32 n_ranks) {
   constexpr bool WAVES = E > 0;
   constexpr u32 MEMBERS = WAVES ? E * CCLD_WAVE : GRID_B, ABOVE = E == 0 ? SEG_MULTI_MAX : E * CCLD_WAVE / 2;
   __shared__ LongShared S;
@@ -2111,6 +2113,10 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
     __syncthreads();     // LDS is reused by the next bucket
   }
 }
+template <class Kernel>
+constexpr bool reads_args_again = std::is_same_v<Kernel, void (*)(SegArgs, GridArgs, i64*, u32)>;
+static_assert(reads_args_again<decltype(&k_grid_stats<256, false>)> && reads_args_again<decltype(&k_grid_long<8, 512>)>,
+              "args_again and grid_again take the arguments by their places");
 static_assert(LONG_ROUNDS <= CCLD_WAVE, "a lane per round");
 static_assert(CCLD_SEG_ENTER_MIN == 7 && CCLD_SEG_EXIT_MIN == 11 && CCLD_SEG_DUR_MIN == 15, "four columns of arrival, four of completion");
 
