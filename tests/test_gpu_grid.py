@@ -170,8 +170,8 @@ def _large(sizes, rounds, drop, seed):
     return cols, want
 
 
-# 192 communicators, 24 to a coarse bucket: such of 2,048 cells per fine bucket and of fewer, one of 1,500 fine buckets (too many for
-# whole lines) beside others
+# 192 communicators, two to a coarse bucket: such of 2,048 cells per fine bucket and of fewer, some with so many fine buckets that they
+# leave as runs beside others
 @pytest.mark.parametrize("mix", ["even", "odd", "skewed"])
 def test_largest_windows_leave_in_whole_lines(mix):
     from paper_2605_04478_amd import ccld
@@ -185,6 +185,7 @@ def test_largest_windows_leave_in_whole_lines(mix):
     n = cols["comm"].numel()
     assert n // 256 >= 64 * 3072
     an = ccld.Analyzer(topo, max_window_records=n)
+    an.profile_enable(True)
     bufs = an.alloc_window_result(n, seg_cap=int(rounds.sum()), flag_cap=1024, group_cap=1 << 18)
     for again in range(2):
         an.reset_window()
@@ -194,16 +195,215 @@ def test_largest_windows_leave_in_whole_lines(mix):
         seg = res.dev["seg"].view(21, -1)
         for name, w in zip(("n", "enter_min", "dur_max"), want):
             assert bool((seg[ccld.SEG_COLS.index(name)] == w).all()), (mix, again, name)
-    # a record twice; one a hundred thousand times, more than a fine bucket's counts of rows can tell
+    assert an.profile_read()[0]["sort_hist"][1] == 0                  # it stayed on the grid
+    # a record twice; one a hundred thousand times, more than a fine bucket's counts of rows can tell; in a context that has analysed
+    # the same layout and in a new one
     for copies in (2, 100_000):
         bad = {k: v.clone() for k, v in cols.items()}
         at = slice(1000, 1000 + copies)
         for k in bad:
             bad[k][at] = bad[k][999]
-        an.reset_window()
-        an.ingest(bad)
-        assert an.analyze_window(FAR, buffers=bufs).status == "E_DUPLICATE_KEY"
+        for fresh in (False, True):
+            if fresh:
+                an.close()
+                an = ccld.Analyzer(topo, max_window_records=n)
+            an.reset_window()
+            an.ingest(bad)
+            assert an.analyze_window(FAR, buffers=bufs).status == "E_DUPLICATE_KEY"
+    an.reset_window()
+    an.ingest(cols)
+    assert an.analyze_window(FAR, buffers=bufs).n_seg == rounds.sum()
     an.close()
+
+
+def _edited(cols, seed):
+    """some of the records late, of another size, in flight or of full width"""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    n = cols["comm"].numel()
+    at = lambda k: torch.randint(0, n, (k,), generator=gen, device="cuda")
+    late, slow, wide, far, other, open_ = at(4000), at(4000), at(800), at(200), at(400), at(100)
+    cols["t_enter"][late] += 100_000
+    cols["t_exit"][late] += 100_000
+    cols["t_exit"][slow] += 200_000
+    cols["t_exit"][wide] += 2**32
+    cols["t_enter"][far] -= 2**42
+    cols["bytes"][other] = 2**37 + 5
+    cols["t_exit"][open_] = INFLIGHT
+    return cols
+
+
+LINES_FROM = 256 * 64 * 3072          # records of a window whose rows leave the partition in whole lines
+LINES_SIZES = {
+    "even": [8] * 192, "odd": [3 + (5 * c) % 62 for c in range(192)],
+    # communicators whose rounds are too few for fine buckets that start on lines (257, 301, 701), beside such as are enough
+    "long": [(64, 257, 65, 300, 301, 129, 255, 701, 700, 33, 7, 128)[c % 12] for c in range(192)],
+    # every eighth coarse bucket holds so few records that they leave as runs
+    "sparse": [16 + c % 3 for c in range(192)],
+}
+
+
+@pytest.mark.parametrize("mix", list(LINES_SIZES))
+def test_whole_lines_and_runs_give_the_same_tables(mix):
+    """A sliding window of three batches whose rows leave in whole lines, and the same with the order of the records, with which they leave as
+    runs from a grid that does not start on lines: rounds of the partition that cross pieces, a circular window that wraps, members
+    missing here and there, late records, rows of full width, and operations in flight; every table of both is the same."""
+    import torch
+    from paper_2605_04478_amd import ccld
+    sizes = LINES_SIZES[mix]
+    n_comms = len(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    topo = tg.make_topology(int(off[-1]), [list(range(off[c], off[c + 1])) for c in range(n_comms)])
+    share = np.where((mix == "sparse") & (np.arange(n_comms) // 2 % 8 == 3), 0.0, 1.0) / sizes
+    W, batches, seq0 = 3, [], np.zeros(n_comms, np.int64)
+    for i, n in enumerate((17_500_000, 17_800_003, 17_600_001, 17_550_000, 17_700_005)):
+        rounds = np.maximum(n * share / (share * sizes).sum(), 3).astype(int) + (np.arange(n_comms) + i) % 3
+        cols, _ = _large(sizes, rounds, 0 if mix == "even" else 500_000, 10 * i + len(mix))
+        cols["seq"] += torch.from_numpy(seq0).cuda()[cols["comm"].long()]
+        later = int(rounds.max()) * 2000
+        for k in ("t_enter", "t_exit"):
+            cols[k] += i * later
+        seq0 += rounds
+        batches.append(_edited(cols, i))
+    count = [b["comm"].numel() for b in batches]
+    cap = max(sum(count[i:i + W]) for i in range(len(count) - W + 1))
+    kw = dict(window_batches=W, lag_floor_ns=10_000, hang_threshold_ns=10**9, tbase_init_ns=1000)
+    an = [ccld.Analyzer(topo, max_window_records=cap, max_batch_records=max(count), **kw) for _ in range(2)]
+    bufs = [a.alloc_window_result(cap, seg_cap=cap // 2, flag_cap=1 << 20, group_cap=1 << 18, cand_cap=1 << 20, per_record=r) for a, r in zip(an, (False, True))]
+    for a in an:
+        a.profile_enable(True)
+    for i, b in enumerate(batches):
+        for a in an:
+            a.ingest(b)
+        if i + 1 < W:
+            continue
+        n = sum(count[i + 1 - W:i + 1])
+        assert n >= LINES_FROM
+        g, ref = (a.analyze_window(FAR, buffers=x) for a, x in zip(an, bufs))
+        assert g.status == ref.status == "OK" and g.n_records == ref.n_records == n
+        assert (g.n_seg, g.n_flag, g.n_group, g.n_alert, g.n_cand) == (ref.n_seg, ref.n_flag, ref.n_group, ref.n_alert, ref.n_cand)
+        assert g.n_flag > 1000 and g.n_alert > 100 and g.n_seg >= n // 701
+        for name, m in (("seg", g.n_seg), ("flag", g.n_flag), ("group", g.n_group), ("alert", g.n_alert), ("cand", g.n_cand)):
+            x, y = (r.dev[name].view(-1, r.caps[name])[:, :m] for r in (g, ref))
+            assert bool((x == y).all()), (mix, i, name)
+        (blame, order), (blame2, order2) = (a.rank_blame() for a in an)
+        assert all(np.array_equal(blame[k], blame2[k]) for k in blame) and np.array_equal(order, order2), (mix, i)
+    for a in an:
+        assert a.profile_read()[0]["sort_hist"][1] == 0
+        a.close()
+
+
+@pytest.mark.parametrize("mix", ["even", "odd"])
+@pytest.mark.parametrize("gone", [False, True], ids=["on_the_grid", "a_round_gone"])
+def test_rounds_that_nobody_recorded_in_whole_lines(mix, gone):
+    """a twentieth of the records missing, so that the rounds of most fine buckets are looked at one by one, filled from both ends: the window stays
+    on the grid; with the first, one inner or the last round of a communicator's second fine bucket gone too, it is sorted"""
+    from paper_2605_04478_amd import ccld
+    sizes = LINES_SIZES[mix]
+    n_comms = len(sizes)
+    rounds = np.full(n_comms, 53_500_000 // sum(sizes) + 1)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    topo = tg.make_topology(int(off[-1]), [list(range(off[c], off[c + 1])) for c in range(n_comms)])
+    cols, (want_n, _, _) = _large(sizes, rounds, 3_000_000, 5)
+    n = cols["comm"].numel()
+    assert 0.045 < 1 - n / (rounds * sizes).sum() < 0.06 and n >= LINES_FROM + 5000
+    an = ccld.Analyzer(topo, max_window_records=n)
+    bufs = an.alloc_window_result(n, seg_cap=int(rounds.sum()), flag_cap=1024, group_cap=1 << 18)
+    c = 100
+    rpb = 2048 // sizes[c] // 8 * 8
+    for q in ((rpb, rpb + 77 % rpb, 2 * rpb - 1) if gone else (None,)):
+        keep = slice(None) if q is None else ~((cols["comm"] == c) & (cols["seq"] == 5 + q))
+        b = {k: v[keep] for k, v in cols.items()}
+        an.profile_enable(True)
+        sorts = an.profile_read()[0]["sort_hist"][1]
+        an.reset_window()
+        an.ingest(b)
+        res = an.analyze_window(FAR, buffers=bufs)
+        assert res.n_seg == rounds.sum() - (q is not None) and res.status in ("OK", "W_TRUNCATED"), (q, res.status)
+        assert (an.profile_read()[0]["sort_hist"][1] > sorts) == gone
+        have, row = res.dev["seg"].view(21, -1)[ccld.SEG_COLS.index("n")], int(rounds[:c].sum())
+        if q is None:
+            assert bool((have == want_n).all())
+        else:
+            assert bool((have[:row + q] == want_n[:row + q]).all()) and bool((have[row + q:res.n_seg] == want_n[row + q + 1:]).all())
+    an.close()
+
+
+SHORT_SIZES = [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64]
+
+
+@pytest.mark.parametrize("per_record", [True, False], ids=["per_record", "tables"])
+@pytest.mark.parametrize("n_comms", [620, 1300], ids=["eight_wavefronts", "four_wavefronts"])
+def test_buckets_that_are_full_but_for_one_record(n_comms, per_record):
+    """Fine buckets with a record in every cell, beside such where one operation is in flight, one row is of full width or at an edge of it, or one
+    record is missing, in the first, an inner or the last cell, in the layouts whose statistics take full buckets by a path of their own"""
+    from paper_2605_04478_amd import ccld
+    rng = np.random.default_rng(n_comms)
+    sizes = [SHORT_SIZES[c % 16] for c in range(n_comms)]
+    topo = tg.make_topology(64, [list(range(n)) for n in sizes])
+    rows = []
+    for c, n in enumerate(sizes):
+        K = 4 + c % 5
+        odd, where = c // 16 % 9, (0, K * n - 1, int(rng.integers(K * n)))[c // 7 % 3]
+        for s in range(K):
+            t = T0 + s * 10**7 + c * 1000
+            for r in range(n):
+                te = t + int(rng.integers(0, 50_000)) + (10**6 if rng.random() < 0.02 else 0)
+                tx, nb = te + int(rng.integers(1, 200_000)), 1 << 20
+                if s * n + r == where:
+                    if odd == 1:
+                        tx = INFLIGHT
+                    elif odd in (2, 3, 4, 5):
+                        tx = te + (2**32 - 3, 2**32 - 2, 2**30, 2**30 - 1)[odd - 2]
+                    elif odd == 6:
+                        te = te - 2**42
+                    elif odd == 7:
+                        nb = 2**37
+                    elif odd == 8 and n > 1:
+                        continue
+                rows.append((r, c, 3 + s, 1, nb, te, tx))
+    cols = toy_cols([rows[i] for i in rng.permutation(len(rows))])
+    n = len(rows)
+    assert n // 2048 + n_comms // 2 > 256 and (n // 2048 + n_comms // 2 <= 512) == (n_comms == 620)
+    kw = dict(lag_floor_ns=100_000, tbase_init_ns=200_000, hang_threshold_ns=10**9)
+    an = ccld.Analyzer(topo, max_window_records=n, **kw)
+    an.profile_enable(True)
+    an.ingest(an.to_device(cols))
+    g = an.analyze_window(FAR, n_records=n, alert_cap=n, cand_cap=2 * n, per_record=per_record)
+    ref = orc.Oracle(topo, kw).analyze_window(cols, FAR)
+    compare(g, ref, *an.rank_blame(), per_record=per_record, what=n_comms)
+    assert an.profile_read()[0]["sort_hist"][1] == 0 and g.n_flag > 100 and g.n_alert > 30
+    an.close()
+
+
+@pytest.mark.parametrize("floor_ns", [0, -1, -2**31, -2**40, 5, 2**31 - 2, 2**31 - 1, 2**31, 2**40])
+@pytest.mark.parametrize("many", [1, 40], ids=["few", "many"])
+def test_floors_of_the_lag_at_the_edges_of_32_bits(floor_ns, many):
+    """a collective is done with when no lag is above the floor: floors of zero, below it, and beyond what a lag can be"""
+    from paper_2605_04478_amd import ccld
+    rng = np.random.default_rng(9)
+    sizes = [2, 4, 8, 33, 64, 65, 100, 128, 129, 200, 256, 257, 400, 512, 513] * many
+    topo = tg.make_topology(max(sizes), [list(range(n)) for n in sizes])
+    rows = []
+    for c, n in enumerate(sizes):
+        for s in range(3):
+            t = T0 + s * 10**10 + c * 1000
+            te = t + rng.integers(0, (2, 1000, 2**29)[s], n)
+            te[rng.random(n) < 0.05] += 2**29
+            tx = te + rng.integers(1, 100, n)
+            tx[rng.random(n) < 0.05] += 2**28
+            rows += [(r, c, s, 1, 64, int(a), int(b)) for r, (a, b) in enumerate(zip(te, tx))]
+    cols = toy_cols([rows[i] for i in rng.permutation(len(rows))])
+    n = len(rows)
+    for kmad in (0, 9):
+        kw = dict(lag_floor_ns=floor_ns, kmad_num=kmad, kmad_den=2)
+        an = ccld.Analyzer(topo, max_window_records=n, **kw)
+        an.ingest(an.to_device(cols))
+        g = an.analyze_window(FAR, n_records=n)
+        ref = orc.Oracle(topo, kw).analyze_window(cols, FAR)
+        compare(g, ref, *an.rank_blame(), per_record=False, what=(floor_ns, kmad))
+        assert (g.n_flag > 0) == (floor_ns < 2**31 - 2)
+        an.close()
 
 
 GAP_SIZES = [1, 2, 3, 31, 64, 65, 700, 2048]
