@@ -313,7 +313,8 @@ __device__ __forceinline__ uint4 part_row(const uint4& row, u32 cell) {
 }
 
 // The thread's number, not known to be the same every time: what follows from it is worked out again in every round.  Kept over the
-// rounds, a thread's places and addresses take thirty registers, and a kernel that spills needs scratch memory (1 us more to start).
+// rounds, a thread's places and addresses take thirty registers, and a kernel that spills needs scratch memory (1 us more to start;
+// part_lines still spills eleven, around its loop).
 __device__ __forceinline__ u32 thread_here() { u32 t = threadIdx.x; asm("" : "+v"(t)); return t; }
 
 struct PartLines {
@@ -685,6 +686,8 @@ static hipError_t each_partition(F f) {
 hipError_t allow_lds_grid() {
   return each_partition([](auto k, size_t bytes) { return allow_lds(reinterpret_cast<const void*>(k), bytes); });
 }
+// 33M, 41M, 57M and 82M records (communicators of 8 and 64 members): 270, 367, 500 and 844 us as runs, 304, 378, 489 and 704 in whole
+// lines; 61M of 8 and 60: 503 and 552.  (The order of the records is wanted for small windows, so rows with slots have no lines.)
 bool grid_in_lines(uint64_t n, bool with_slots) { return !with_slots && n / PART_BLOCKS >= LINES_SLICE; }
 void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   // small windows: a thousand records per workgroup, so that there are several of them
@@ -693,7 +696,6 @@ void launch_grid_partition(hipStream_t st, const GridArgs& d) {
   auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3(g), dim3(PART_THREADS), bytes, st, d); };
   if (d.slots) one ? go(k_grid_partition<true, false, 1>, PART_LDS_SLOTS) : go(k_grid_partition<true, false, PART_U>, PART_LDS_SLOTS);
   else if (one) go(k_grid_partition<false, false, 1>, PART_LDS);
-  // 33M, 41M, 57M and 82M records: 270, 367, 500 and 844 us as runs, 304, 378, 489 and 704 in whole lines
   else if (!d.lines) go(k_grid_partition<false, false, PART_U>, PART_LDS);
   else go(k_grid_partition<false, true, PART_U>, PART_LDS_LINES);
 }

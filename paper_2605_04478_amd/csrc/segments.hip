@@ -1972,7 +1972,7 @@ __global__ __launch_bounds__(THREADS, E == 2 || E == 4 ? 4 : 2) void k_grid_long
     if (bad) atomicOr((unsigned long long*)&a.counters[CNT_STATUS], (unsigned long long)bad);
     // the lane's number, not known to be the same for every bucket: what the sorts make of it is not kept over the placing of the next
     // rows, where it took 28 registers too many (with the arguments read again, ten batches of 2M records with collectives of 128
-    // members 84 -> 70 us, 1.1M records with collectives of 390 members 28.3 -> 27.5)
+    // members 84 -> 70 us, 1.1M records with collectives of 390 members 28.3 -> 27.5; eleven registers still spill with two members per lane)
     u32 lane = lane_id();
     asm("" : "+v"(lane));
     if constexpr (WAVES) {

@@ -220,13 +220,15 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
 // Windows placed by bucket.  A workgroup takes CHUNK records per round, gives each its slot in its bucket (LDS atomic),
 // then stages keys and rows in LDS ordered by (bucket, slot) and writes them out with consecutive lanes
 // on consecutive pieces: every bucket's share of the round leaves as one contiguous run instead of one scattered store
-// per lane.  LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS: with records in random order that
-// lookup is a gather with no locality, cheaper from LDS than from the L2.
+// per lane.  LDS_TABLE keeps a copy of the ranks' packed membership rows in LDS, since with records in random order that
+// lookup is a gather with no locality.
 //
 // Bound by memory: a line that a round leaves unfinished would be completed by the next one 7 us later, when it has left the
 // L2 in parts.  So rows leave eight slots at a time (a line of rows, half a line of keys), with the streaming
-// hint; up to seven of a bucket wait in registers for the next round.  82M records into 68 buckets: 1,125 us (4.7 TB/s), 1,260 with
-// every round written as it is; four slots at a time 1,150.  Ranks' rows from the L2: 1,150 to 1,180.
+// hint; up to seven of a bucket wait in registers for the next round.  82M records of 4,096 ranks on one card: 136 buckets, which is
+// what such windows have, ranks' rows from the L2, 1,265 us (4.2 TB/s); 68 buckets 1,257 with the ranks' rows in LDS, 1,255 without, and
+// 1,410 with every round written as it is.  (Four slots at a time took 2 % longer with 68 buckets, and 8 % with 136 beside the ranks'
+// rows in LDS.)
 template <int THREADS, bool LDS_TABLE>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
@@ -477,7 +479,9 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
   if (a.n_buckets == 1) {
     // A workgroup of 256 threads per 1,024 records while that makes no more of them than compute units, then one of 1,024 threads to
     // each: every workgroup raises the ranges of the communicators that it met, and the requests for one line of them follow
-    // one another at 10 to 20 ns (1,024 workgroups and 174 communicators: 32 us for 1.07M records, 21 so; a window 157 -> 146).
+    // one another at 10 to 20 ns (1,024 workgroups and 174 communicators: 32 us for 1.07M records, 21 so; a window 157 -> 146).  The line
+    // is where the first kind would have more workgroups than compute units: windows of 262,860, 319,800, 390,000 and 858,000 records of
+    // 390 ranks take 75, 82, 85 and 109 us with the first kind, 75, 82, 82 and 94 with the second.
     if (a.n <= INGEST_GROUPS * 1024) {
       a.chunk = 1024;
       hipLaunchKernelGGL(k_ingest<256>, dim3((u32)((a.n + 1023) / 1024)), dim3(256), range_lds, st, a, T, kf);
@@ -500,9 +504,8 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     hipLaunchKernelGGL(k_ingest_scan, dim3(a.n_buckets), dim3(256), 0, st, a.table, a.bucket_base, g_hist);
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
-  // the membership rows in LDS where they fit beside the lines: with 68 buckets lines without the rows in LDS take 1,180 us in place of 1,155
-  // with both (82M records of 4,096 ranks), the rows without lines 1,285.  With 136 buckets both do not fit: lines 1,251 us, half
-  // lines (four slots) beside the rows 1,352.
+  // the ranks' membership rows in LDS where they fit beside the lines: since rows leave in lines that is worth 1 % at most (15.4M records of
+  // 512 ranks in a random order 220 us in place of 222; 20M and 82M of 4,096 ranks the same with and without)
   const u32 range_comms = a.range ? T.n_comms : 0;
   const size_t lines = ingest_lds(a.n_buckets, range_comms, 0), both = ingest_lds(a.n_buckets, range_comms, T.n_ranks);
   auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3((u32)g), dim3(1024), bytes, st, a, T, kf); };
