@@ -33,11 +33,11 @@ constexpr uint32_t bucket_count(int bits, uint32_t n_comms) { return ((n_comms -
 // Bits of a communicator's number that name its bucket, for a window of `batches` batches placed on a grid that may have `fine`
 // fine buckets.  A partition workgroup addresses a few thousand fine buckets at a time, so a window that may have more of them is
 // placed by bucket, into as many buckets as leave about GRID_TARGET fine buckets in one: fewer fine buckets in one lengthen the runs
-// that the partition writes, more those that the ingest writes (82M records with 300 / 600 in one: ingest
-// 1,265 / 1,257 us, partition 724 / 935; 20M: ingest 299 / 300, partition 164 / 190).  Half as many buckets where the ingest could not
-// stage whole lines of so many beside the counter ranges (more than 1,280 communicators in the largest windows: 60M records of
-// 16,384 ranks in 3,200 communicators, 200 / 100 buckets: ingest 1,142 / 805 us, partition 541 / 551, a window 2,557 / 2,214; 100M: ingest
-// 1,880 / 1,425, partition 925 / 1,106, a window 4,166 / 3,738).
+// that the partition writes, more those that the ingest writes (82M records with 300 / 600 in one: ingest 1,131 / 1,114 us, partition
+// 704 / 910, a window 2,820 / 3,010; 20M: ingest 299 / 300, partition 164 / 190).  Half as many buckets where the ingest could not
+// stage whole lines of so many beside the counter ranges (the largest windows of 1,833 to 2,048 and of 2,877 or more communicators:
+// 60M records of 16,384 ranks in 3,200, 200 / 100 buckets: ingest 1,142 / 805 us, partition 541 / 551, a window 2,557 / 2,214; 100M:
+// ingest 1,880 / 1,425, partition 925 / 1,106, a window 4,166 / 3,738).
 constexpr int grid_bucket_bits(uint64_t fine, uint64_t batches, uint32_t n_comms) {
   int bits = 0;
   if (fine > GRID_ONE_BUCKET) while (bits < GRID_BUCKET_BITS && (fine >> bits) > GRID_TARGET) ++bits;

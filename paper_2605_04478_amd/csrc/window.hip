@@ -54,7 +54,9 @@ __device__ __forceinline__ void put_header(const IngestArgs& a, i64 ref) {
 }
 
 // Records per communicator bucket in each workgroup's slice of the batch (first half of the bucketed placement).  Tables
-// of no more words than this are scanned by every placement workgroup for itself, larger ones by two launches.
+// of no more words than this are scanned by every placement workgroup for itself, larger ones by two launches.  Streams at 6 TB/s where
+// records come in a random order; in time order neighbouring lanes add to the same few words of LDS one after the other (70M records 49
+// and 199 us).
 constexpr u32 INGEST_SCAN_WORDS = 8192;
 template <u32 THREADS>
 __global__ __launch_bounds__(THREADS) void k_ingest_hist(IngestArgs a, u32 n_comms) {
@@ -225,10 +227,10 @@ __global__ __launch_bounds__(THREADS) void k_ingest(IngestArgs a, DeviceTopology
 //
 // Bound by memory: a line that a round leaves unfinished would be completed by the next one 7 us later, when it has left the
 // L2 in parts.  So rows leave eight slots at a time (a line of rows, half a line of keys), with the streaming
-// hint; up to seven of a bucket wait in registers for the next round.  82M records of 4,096 ranks on one card: 136 buckets, which is
-// what such windows have, ranks' rows from the L2, 1,265 us (4.2 TB/s); 68 buckets 1,257 with the ranks' rows in LDS, 1,255 without, and
-// 1,410 with every round written as it is.  (Four slots at a time took 2 % longer with 68 buckets, and 8 % with 136 beside the ranks'
-// rows in LDS.)
+// hint; up to seven of a bucket wait in registers for the next round.  82M records of 4,096 ranks, all in one session: 136 buckets, which
+// is what such windows have, ranks' rows from the L2, 1,131 us (4.7 TB/s); 68 buckets 1,114 with the ranks' rows in LDS, 1,118 without, and
+// 1,245 with every round written as it is.  (Four slots at a time took 2 % longer with 68 buckets, and 8 % with 136 beside the ranks'
+// rows in LDS.)  A tenth more where one record in eight lies 2^42 ns from the batch's first and is written at full width too.
 template <int THREADS, bool LDS_TABLE>
 __global__ __launch_bounds__(THREADS) void k_ingest_staged(IngestArgs a, DeviceTopology T, KeyFormat kf) {
   constexpr int U = 2;
@@ -505,7 +507,7 @@ void launch_ingest(hipStream_t st, const IngestArgs& a_in, const DeviceTopology&
     launch_scan_tiles(st, a.bucket_base, a.n_buckets, a.scratch_total);
   }
   // the ranks' membership rows in LDS where they fit beside the lines: since rows leave in lines that is worth 1 % at most (15.4M records of
-  // 512 ranks in a random order 220 us in place of 222; 20M and 82M of 4,096 ranks the same with and without)
+  // 512 ranks in a random order 220 us in place of 222; 20M of 4,096 ranks 299 both ways)
   const u32 range_comms = a.range ? T.n_comms : 0;
   const size_t lines = ingest_lds(a.n_buckets, range_comms, 0), both = ingest_lds(a.n_buckets, range_comms, T.n_ranks);
   auto go = [&](auto kernel, size_t bytes) { hipLaunchKernelGGL(kernel, dim3((u32)g), dim3(1024), bytes, st, a, T, kf); };
